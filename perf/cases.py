@@ -124,6 +124,54 @@ def run(state):
     return (out.detach(), *torch.autograd.grad(out, leaves, dout))
 
 
+def _gather_indices(case):
+    """For each window slot: the flat key position of every query and the flat cell of the bias table it uses."""
+    k, dev = case["k"], "cuda"
+
+    def axis(length, window):
+        pos = torch.arange(length, device=dev)
+        first = (pos - (window - 1) // 2).clamp(0, length - window)
+        return [(first + a, first + a - pos + window - 1) for a in range(window)]
+
+    cells = 2 * k - 1
+    for y, cy in axis(case["H"], 1 if _is_1d(case) else k):
+        for x, cx in axis(case["W"], k):
+            yield (y[:, None] * case["W"] + x).flatten(), (cy[:, None] * cells + cx).flatten()
+
+
+def exact(case, seed):
+    """The operator and its chain rule in 64 bits, one window slot at a time."""
+    state = prepare(case, seed)
+    B, heads, D, n = case["B"], case["heads"], case["D"], case["H"] * case["W"]
+    wide = lambda t: t.detach().double()
+    flat = lambda t: wide(t).reshape(B, heads, n, D)
+    shaped = state["q"].shape
+    q, key, v = (flat(state[name]) for name in ("q", "k", "v"))
+    scale = float(D) ** -0.5
+    slots = list(_gather_indices(case))
+    table = wide(state["rpb"]).flatten(1) if case["bias"] else None
+    logits = torch.stack([(q * key[:, :, at]).sum(-1).mul_(scale) + (0 if table is None else table[:, cell])
+                          for at, cell in slots])
+    p = torch.softmax(logits, 0)
+    out = sum(p[s].unsqueeze(-1) * v[:, :, at] for s, (at, _) in enumerate(slots))
+    if state["dout"] is None:
+        return out.reshape(shaped)
+    dout = flat(state["dout"])
+    dp = torch.stack([(dout * v[:, :, at]).sum(-1) for at, _ in slots])
+    ds = p * (dp - (p * dp).sum(0))
+    dq, dk, dv = (torch.zeros_like(q) for _ in range(3))
+    dtable = None if table is None else torch.zeros_like(table)
+    for s, (at, cell) in enumerate(slots):
+        w = ds[s].unsqueeze(-1)
+        dq += w * key[:, :, at]
+        dk.index_add_(2, at, w * q)
+        dv.index_add_(2, at, p[s].unsqueeze(-1) * dout)
+        if dtable is not None:
+            dtable.index_add_(1, cell, ds[s].sum(0))
+    grads = [t.mul_(f).reshape(shaped) for t, f in ((dq, scale), (dk, scale), (dv, 1.0))]
+    return (out.reshape(shaped), *grads) + (() if dtable is None else (dtable.reshape(state["rpb"].shape),))
+
+
 def work(case):
     """q, k, v (and the upstream gradient) read once, the output (and three gradients) written once, the bias table
     (and its gradient); two contractions forward, four backward, over every (query, key) pair of a window."""
