@@ -22,13 +22,14 @@ struct Problem {
 constexpr int kMaxTunedK = 13, kMaxGenericK = 63;
 bool generic_window(const Problem &p);   // neither the tuned window sides nor a plain-ALU tile that fits the LDS
 bool untuned_window(const Problem &p);   // k beyond the tuned sides (what the kernels that do not depend on D ask)
-hipError_t launch_qk_generic(const Problem &p, const void *x, const void *y, const void *rpb, float scale, void *logits,
+// the contractions of those problems: matrix cores, any window side, head dim and storage type (na2d_strip.hip)
+hipError_t launch_qk_strip(const Problem &p, const void *x, const void *y, const void *rpb, float scale, void *logits,
                              hipStream_t s);
-hipError_t launch_av_generic(const Problem &p, const void *w, const void *y, float scale, void *out, hipStream_t s);
-hipError_t launch_inverse_generic(const Problem &p, const void *w, const void *x, float scale, void *out, hipStream_t s);
+hipError_t launch_av_strip(const Problem &p, const void *w, const void *y, float scale, void *out, hipStream_t s);
+hipError_t launch_inverse_strip(const Problem &p, const void *w, const void *x, float scale, void *out, hipStream_t s);
 hipError_t launch_softmax_generic(const Problem &p, const void *in, void *out, hipStream_t s);
 hipError_t launch_softmax_bwd_generic(const Problem &p, const void *attn, const void *dp, void *ds, hipStream_t s);
-hipError_t launch_fused_generic(const Problem &p, const void *q, const void *k, const void *v, const void *rpb, float scale,
+hipError_t launch_fused_strip(const Problem &p, const void *q, const void *k, const void *v, const void *rpb, float scale,
                                 void *out, float *lse, hipStream_t s);
 size_t rpb_generic_workspace_bytes(const Problem &p);
 hipError_t launch_rpb_generic(const Problem &p, const void *ds, float *d_rpb, void *workspace, hipStream_t s);

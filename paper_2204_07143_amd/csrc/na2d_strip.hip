@@ -1,0 +1,423 @@
+// Neighbourhood attention on the matrix cores for any window side and any storage type, fp32 included (arXiv
+// 2204.07143, Eq. 2-4 and the gradients of Appendix A): the contractions of the problems that have no kernel of a
+// fixed window side.
+//
+// A workgroup owns a strip of 16 consecutive positions of one map row; its four waves take the window rows in turn.
+// For one window row the strip's windows together cover 16 + K - 1 consecutive positions of one row of the other
+// operand, i.e. one small dense product of 16 strip positions with blocks of 16 partner positions, masked by the
+// window.  Nothing but the waves' partial sums is staged in LDS, so neither the window nor the head dim is limited
+// by it: partner positions come from global memory (neighbouring strips re-read them out of L2), the weights are
+// read or written in place.  What bounds it is the number of load / store instructions per block of 16 x 16
+// products (a 4 x 4 patch would have fewer masked products, but its weights do not lie in one run per row).
+//
+// Measured against one thread per output element (4 x 2 x 64 x 64 x 32, k = 21, bf16, forward and backward of the
+// fused operator, together with the steps of na2d_generic.hip): 3099 -> 288 us.
+//
+// Weights that are stored are products of 16-bit (or fp32) operands summed in fp32: exact products as on the plain
+// ALU.  The fused forward keeps its weights in fp32; in 16 bit they enter as a high and a low half (p = hi + lo to
+// 2^-17 in bf16, 2^-22 in fp16), two products instead of one.
+//
+// A masked product is 0 * y.  Where y is not finite that would spoil positions whose window does not hold it, so an
+// output that is not finite is computed once more from its own window only.
+#include "na2d_kernels.hpp"
+#include "na2d_mfma.hpp"
+#include "na2d_tile.hpp"
+
+namespace na2d {
+
+namespace {
+
+constexpr int kStrip = 16, kStripWaves = 4, kStripThreads = kStripWaves * kWave;
+
+struct SShape {
+    int heads, H, W, K, strips, ntiles;
+};
+
+struct Strip {
+    int plane, y, x0;
+};
+__device__ __forceinline__ bool decode_strip(const SShape &g, Strip &s) {
+    const int t = xcd_contiguous_block(blockIdx.x, gridDim.x);
+    if (t >= g.ntiles) return false;
+    s.x0 = (t % g.strips) * kStrip;
+    const int rest = t / g.strips;
+    s.y = rest % g.H;
+    s.plane = rest / g.H;
+    return true;
+}
+
+template <typename T> __device__ __forceinline__ uint32_t pack2(T lo, T hi) {
+    return (uint32_t)__builtin_bit_cast(uint16_t, lo) | ((uint32_t)__builtin_bit_cast(uint16_t, hi) << 16);
+}
+__device__ __forceinline__ f32x4 mfma_16x16x4(float a, float b, f32x4 c) { return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0); }
+
+// One head vector per 16-lane column, as an operand whose contraction runs over channels.  Lane (column j, group g)
+// holds, of each `step` channels, the 16-byte chunk g (both operands alike, so the order of channels is free).
+template <typename T, int D> struct ChannelOp {
+    static constexpr int EPC = 16 / (int)sizeof(T);            // channels per chunk
+    static constexpr int N = (D + 4 * EPC - 1) / (4 * EPC);    // chunks per lane (D = 16 in 16 bit: half the lanes hold zeros)
+    u32x4 c[N];
+    __device__ __forceinline__ void load(const T *vec, int g) {
+#pragma unroll
+        for (int i = 0; i < N; ++i) {
+            c[i] = u32x4{0u, 0u, 0u, 0u};
+            if ((4 * i + g) * EPC < D) c[i] = *reinterpret_cast<const u32x4 *>(vec + (4 * i + g) * EPC);
+        }
+    }
+};
+// result rows: positions 4 g + r of the first operand; columns: positions of the second
+template <typename T, int D>
+__device__ __forceinline__ f32x4 dot_block(const ChannelOp<T, D> &a, const ChannelOp<T, D> &b) {
+    f32x4 acc{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int i = 0; i < ChannelOp<T, D>::N; ++i) {
+        if constexpr (sizeof(T) == 4) {
+            const f32x4 x = __builtin_bit_cast(f32x4, a.c[i]), y = __builtin_bit_cast(f32x4, b.c[i]);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) acc = mfma_16x16x4(x[e], y[e], acc);
+        } else {
+            acc = mfma_16x16x32<T>(a.c[i], b.c[i], acc);
+        }
+    }
+    return acc;
+}
+
+// The weighted sum of 16 positions, channels as result rows: lane (column j, group g) brings channel(s) j of the
+// positions 4 g .. 4 g + 3 and the weights of strip position j for the same four.  Head dims of 32 and more are
+// loaded two channels at a time: rows of block 2 p are the even, of block 2 p + 1 the odd channels of slice p.
+template <typename T, int D> struct SumAcc {
+    static constexpr int NB = D / 16;
+    f32x4 acc[NB];
+    __device__ __forceinline__ void clear() {
+#pragma unroll
+        for (int i = 0; i < NB; ++i) acc[i] = f32x4{0.f, 0.f, 0.f, 0.f};
+    }
+    __device__ static __forceinline__ int channel(int block, int row) {
+        return D == 16 ? row : (block >> 1) * 32 + 2 * row + (block & 1);
+    }
+    // NW sets of weights (their sum is meant): w[s][e] for position e
+    template <int NW> __device__ __forceinline__ void add(const T *y, const int (&off)[4], int j, const T (&w)[NW][4]) {
+        if constexpr (D == 16) {
+            T v[4];
+#pragma unroll
+            for (int e = 0; e < 4; ++e) v[e] = y[off[e] + j];
+            product<NW>(acc[0], v, w);
+        } else {
+#pragma unroll
+            for (int p = 0; p < D / 32; ++p) {
+                T lo[4], hi[4];
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    struct alignas(2 * sizeof(T)) Pair { T a, b; };
+                    const Pair t = *reinterpret_cast<const Pair *>(y + off[e] + p * 32 + 2 * j);
+                    lo[e] = t.a;
+                    hi[e] = t.b;
+                }
+                product<NW>(acc[2 * p], lo, w);
+                product<NW>(acc[2 * p + 1], hi, w);
+            }
+        }
+    }
+    template <int NW> __device__ static __forceinline__ void product(f32x4 &c, const T (&v)[4], const T (&w)[NW][4]) {
+#pragma unroll
+        for (int s = 0; s < NW; ++s) {
+            if constexpr (sizeof(T) == 4) {
+#pragma unroll
+                for (int e = 0; e < 4; ++e) c = mfma_16x16x4(v[e], w[s][e], c);
+            } else {
+                c = mfma_16x16x16<T>(pack2(v[0], v[1]), pack2(v[2], v[3]), pack2(w[s][0], w[s][1]), pack2(w[s][2], w[s][3]), c);
+            }
+        }
+    }
+    // the wave's sums to LDS as [strip position][channel]
+    static constexpr int kPitch = D + 1;
+    __device__ __forceinline__ void to_lds(float *dst, int j, int g) const {
+#pragma unroll
+        for (int i = 0; i < NB; ++i)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) dst[j * kPitch + channel(i, 4 * g + r)] = acc[i][r];
+    }
+};
+
+__device__ __forceinline__ int clamp_to(int v, int hi) { return v < 0 ? 0 : (v < hi ? v : hi); }
+
+// logits[n, a, c] = scale <x_n, y_key(n; a, c)> + bias (and grad-a: x = dout, y = v)
+template <typename T, int D>
+__global__ __launch_bounds__(kStripThreads) void qk_strip_kernel(const T *__restrict__ x, const T *__restrict__ y,
+                                                                 const T *__restrict__ rpb, float scale, T *__restrict__ logits, SShape g) {
+    Strip st;
+    if (!decode_strip(g, st)) return;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave), lane = threadIdx.x % kWave, j = lane % 16, grp = lane / 16;
+    const int K = g.K, W = g.W, KK = K * K, NB = 2 * K - 1;
+    const size_t plane0 = (size_t)st.plane * g.H * W;
+    const bool mine = st.x0 + j < W;
+    const int qx = mine ? st.x0 + j : W - 1, sx = win_start(qx, W, K), sy = win_start(st.y, g.H, K);
+    const int kx0 = win_start(st.x0, W, K);
+    const int xl = st.x0 + kStrip - 1 < W ? st.x0 + kStrip - 1 : W - 1, nblk = (win_start(xl, W, K) + K - 1 - kx0) / 16 + 1;
+    ChannelOp<T, D> xo;
+    xo.load(x + (plane0 + (size_t)st.y * W + qx) * D, grp);
+    const T *yp = y + plane0 * D;
+    T *row = logits + (plane0 + (size_t)st.y * W + qx) * KK;
+    const T *bt = rpb ? rpb + ((size_t)(st.plane % g.heads) * NB + (sy - st.y + K - 1)) * NB + (sx - qx + K - 1) : nullptr;
+    for (int a = wave; a < K; a += kStripWaves) {
+        const T *yrow = yp + (size_t)(sy + a) * W * D;
+#pragma unroll 2
+        for (int b = 0; b < nblk; ++b) {
+            const int k0 = kx0 + 16 * b, kl = k0 + j < W ? k0 + j : W - 1;
+            ChannelOp<T, D> yo;
+            yo.load(yrow + (size_t)kl * D, grp);
+            const f32x4 s = dot_block<T, D>(yo, xo);
+            const int c0 = k0 + 4 * grp - sx;
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                if (mine && (unsigned)(c0 + r) < (unsigned)K) {
+                    float v = scale * s[r];
+                    if (bt) v += to_f32(bt[a * NB + c0 + r]);
+                    row[a * K + c0 + r] = from_f32<T>(v);
+                }
+            }
+        }
+    }
+}
+
+// One output of the weighted sum from its own window, in raster order (strip outputs that are not finite)
+template <typename T, int D, bool INV>
+__device__ __noinline__ float sum_one(const T *w, const T *y, int H, int W, int K, int py, int px, int d) {
+    const int KK = K * K;
+    float acc = 0.f;
+    const int y0 = INV ? inv_first(py, H, K) : win_start(py, H, K), y1 = INV ? inv_last(py, H, K) : y0 + K - 1;
+    const int x0 = INV ? inv_first(px, W, K) : win_start(px, W, K), x1 = INV ? inv_last(px, W, K) : x0 + K - 1;
+    for (int oy = y0; oy <= y1; ++oy)
+        for (int ox = x0; ox <= x1; ++ox) {
+            const size_t n = INV ? (size_t)oy * W + ox : (size_t)py * W + px;
+            const int slot = INV ? (py - win_start(oy, H, K)) * K + px - win_start(ox, W, K) : (oy - y0) * K + ox - x0;
+            acc = __builtin_fmaf(to_f32(w[n * KK + slot]), to_f32(y[((size_t)oy * W + ox) * D + d]), acc);
+        }
+    return acc;
+}
+
+// INV false: out[n, :] = scale sum_slot w[n, slot] y_key(n; slot).  INV true: out[j, :] = scale sum of w[i, slot(i, j)] y_i
+// over the queries i that see key j.  The waves' sums are added in wave order: the same bits in every run.
+template <typename T, int D, bool INV>
+__global__ __launch_bounds__(kStripThreads) void sum_strip_kernel(const T *__restrict__ w, const T *__restrict__ y, float scale,
+                                                                  T *__restrict__ out, SShape g) {
+    using A = SumAcc<T, D>;
+    __shared__ float part[kStripWaves][kStrip * A::kPitch];
+    Strip st;
+    if (!decode_strip(g, st)) return;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave), lane = threadIdx.x % kWave, j = lane % 16, grp = lane / 16;
+    const int K = g.K, W = g.W, H = g.H, KK = K * K;
+    const size_t plane0 = (size_t)st.plane * H * W;
+    const T *wp = w + plane0 * KK, *yp = y + plane0 * D;
+    const int px = st.x0 + j < W ? st.x0 + j : W - 1;
+    const int xl = st.x0 + kStrip - 1 < W ? st.x0 + kStrip - 1 : W - 1;
+    const int first = INV ? inv_first(st.x0, W, K) : win_start(st.x0, W, K);
+    const int last = INV ? inv_last(xl, W, K) : win_start(xl, W, K) + K - 1;
+    const int nblk = (last - first) / 16 + 1;
+    const int y0 = INV ? inv_first(st.y, H, K) : win_start(st.y, H, K);
+    const int y1 = INV ? inv_last(st.y, H, K) : y0 + K - 1;
+    const int sx = win_start(px, W, K);
+    A acc;
+    acc.clear();
+    for (int oy = y0 + wave; oy <= y1; oy += kStripWaves) {
+        const int a = INV ? st.y - win_start(oy, H, K) : oy - y0;
+        const int wrow = INV ? oy * W * KK + a * K : (st.y * W + px) * KK + a * K;
+#pragma unroll 2
+        for (int b = 0; b < nblk; ++b) {
+            T wt[1][4];
+            int off[4];
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const int ox = first + 16 * b + 4 * grp + e, oc = ox < W ? ox : W - 1;
+                const int c = INV ? px - win_start(oc, W, K) : ox - sx;
+                const bool in = (unsigned)c < (unsigned)K && ox < W;
+                const T v = wp[wrow + (INV ? oc * KK : 0) + clamp_to(c, K - 1)];
+                wt[0][e] = in ? v : (T)0.f;
+                off[e] = (oy * W + oc) * D;
+            }
+            acc.template add<1>(yp, off, j, wt);
+        }
+    }
+    acc.to_lds(part[wave], j, grp);
+    workgroup_sync();
+    for (int i = threadIdx.x; i < kStrip * D; i += kStripThreads) {
+        const int p = i / D, d = i % D;
+        if (st.x0 + p >= W) break;   // (p grows with i)
+        float v = 0.f;
+#pragma unroll
+        for (int s = 0; s < kStripWaves; ++s) v += part[s][p * A::kPitch + d];
+        if (!(fabsf(v) < INFINITY)) v = sum_one<T, D, INV>(wp, yp, H, W, K, st.y, st.x0 + p, d);
+        out[(plane0 + (size_t)st.y * W + st.x0 + p) * D + d] = from_f32<T>(scale * v);
+    }
+}
+
+// fp32 dot product of two head vectors, and one fused output from its own window (strip outputs that are not finite)
+template <typename T, int D> __device__ __forceinline__ float dot_one(const T *a, const T *b) {
+    float acc = 0.f;
+    for (int d = 0; d < D; ++d) acc = __builtin_fmaf(to_f32(a[d]), to_f32(b[d]), acc);
+    return acc;
+}
+template <typename T, int D>
+__device__ __noinline__ float fused_one(const T *q, const T *kp, const T *vp, const T *bt, float scale, float m, int W, int K, int sy, int sx, int d) {
+    float acc = 0.f;
+    for (int a = 0; a < K; ++a)
+        for (int c = 0; c < K; ++c) {
+            const size_t key = ((size_t)(sy + a) * W + sx + c) * D;
+            float s = scale * dot_one<T, D>(q, kp + key);
+            if (bt) s += to_f32(bt[a * (2 * K - 1) + c]);
+            acc = __builtin_fmaf(__expf(s - m), to_f32(vp[key + d]), acc);
+        }
+    return acc;
+}
+
+// Fused forward.  Each wave keeps a running maximum, sum and weighted values of its window rows, NBX blocks of 16 keys
+// at a time; the logits leave the matrix cores in the layout in which the weights enter them again.  The waves'
+// results are joined in wave order.
+template <typename T, int D, int NBX>
+__global__ __launch_bounds__(kStripThreads) void fused_strip_kernel(const T *__restrict__ q, const T *__restrict__ k,
+                                                                    const T *__restrict__ v, const T *__restrict__ rpb, float scale,
+                                                                    T *__restrict__ out, float *__restrict__ lse, SShape g) {
+    using A = SumAcc<T, D>;
+    constexpr int NW = sizeof(T) == 4 ? 1 : 2;
+    __shared__ float part[kStripWaves][kStrip * A::kPitch];
+    __shared__ float wm[kStripWaves][kStrip], wl[kStripWaves][kStrip];
+    Strip st;
+    if (!decode_strip(g, st)) return;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave), lane = threadIdx.x % kWave, j = lane % 16, grp = lane / 16;
+    const int K = g.K, W = g.W, NB = 2 * K - 1;
+    const size_t plane0 = (size_t)st.plane * g.H * W;
+    const int qx = st.x0 + j < W ? st.x0 + j : W - 1, sx = win_start(qx, W, K), sy = win_start(st.y, g.H, K);
+    const int kx0 = win_start(st.x0, W, K);
+    const int xl = st.x0 + kStrip - 1 < W ? st.x0 + kStrip - 1 : W - 1, nblk = (win_start(xl, W, K) + K - 1 - kx0) / 16 + 1;
+    ChannelOp<T, D> qo;
+    qo.load(q + (plane0 + (size_t)st.y * W + qx) * D, grp);
+    const T *kp = k + plane0 * D, *vp = v + plane0 * D;
+    const T *table = rpb ? rpb + ((size_t)(st.plane % g.heads) * NB + (sy - st.y + K - 1)) * NB : nullptr;
+    const int tx = sx - qx + K - 1;
+    float m = -INFINITY, l = 0.f;
+    A acc;
+    acc.clear();
+    for (int a = wave; a < K; a += kStripWaves) {
+        const int row = (sy + a) * W;
+        for (int b0 = 0; b0 < nblk; b0 += NBX) {
+            float s[NBX][4];
+            float gm = -INFINITY;
+#pragma unroll
+            for (int b = 0; b < NBX; ++b) {
+                const int k0 = kx0 + 16 * (b0 + b), kl = k0 + j < W ? k0 + j : W - 1;
+                ChannelOp<T, D> ko;
+                ko.load(kp + (size_t)(row + kl) * D, grp);
+                const f32x4 t = dot_block<T, D>(ko, qo);
+                const int c0 = k0 + 4 * grp - sx;
+#pragma unroll
+                for (int r = 0; r < 4; ++r) {
+                    float x = scale * t[r];
+                    if (table) x += to_f32(table[a * NB + tx + clamp_to(c0 + r, K - 1)]);
+                    s[b][r] = (unsigned)(c0 + r) < (unsigned)K ? x : -INFINITY;
+                    gm = fmaxf(gm, s[b][r]);
+                }
+            }
+            gm = fmaxf(gm, __shfl_xor(gm, 16));
+            gm = fmaxf(gm, __shfl_xor(gm, 32));
+            const float mnew = fmaxf(m, gm), base = mnew == -INFINITY ? 0.f : mnew;   // nothing in reach yet: weights 0
+            const float corr = __expf(m - base);
+            m = mnew;
+            l *= corr;
+#pragma unroll
+            for (int i = 0; i < A::NB; ++i) acc.acc[i] *= corr;
+#pragma unroll
+            for (int b = 0; b < NBX; ++b) {
+                T wt[NW][4];
+                int off[4];
+#pragma unroll
+                for (int r = 0; r < 4; ++r) {
+                    const float p = __expf(s[b][r] - base);
+                    l += p;
+                    wt[0][r] = from_f32<T>(p);
+                    if constexpr (NW == 2) wt[NW - 1][r] = from_f32<T>(p - to_f32(wt[0][r]));
+                    const int kx = kx0 + 16 * (b0 + b) + 4 * grp + r;
+                    off[r] = (row + (kx < W ? kx : W - 1)) * D;
+                }
+                acc.template add<NW>(vp, off, j, wt);
+            }
+        }
+    }
+    l += __shfl_xor(l, 16);
+    l += __shfl_xor(l, 32);
+    if (grp == 0) {
+        wm[wave][j] = m;
+        wl[wave][j] = l;
+    }
+    acc.to_lds(part[wave], j, grp);
+    workgroup_sync();
+    for (int i = threadIdx.x; i < kStrip * D; i += kStripThreads) {
+        const int p = i / D, d = i % D, x = st.x0 + p;
+        if (x >= W) break;
+        float mm = wm[0][p];
+#pragma unroll
+        for (int t = 1; t < kStripWaves; ++t) mm = fmaxf(mm, wm[t][p]);
+        float num = 0.f, den = 0.f;
+#pragma unroll
+        for (int t = 0; t < kStripWaves; ++t) {
+            const float f = wm[t][p] == -INFINITY ? 0.f : __expf(wm[t][p] - mm);   // a wave without rows adds nothing
+            num = __builtin_fmaf(f, part[t][p * A::kPitch + d], num);
+            den = __builtin_fmaf(f, wl[t][p], den);
+        }
+        if (den == 0.f) den = NAN;   // every logit -inf
+        const size_t n = plane0 + (size_t)st.y * W + x;
+        if (!(fabsf(num) < INFINITY)) {
+            const int osx = win_start(x, W, K);
+            num = fused_one<T, D>(q + n * D, kp, vp, table ? table + osx - x + K - 1 : nullptr, scale, mm, W, K, sy, osx, d);
+        }
+        out[n * D + d] = from_f32<T>(num * (1.f / den));
+        if (lse != nullptr && d == 0) lse[n] = mm + __logf(den);
+    }
+}
+
+SShape strip_shape(const Problem &p) {
+    const int strips = (p.W + kStrip - 1) / kStrip;
+    return SShape{p.heads, p.H, p.W, p.K, strips, p.planes() * p.H * strips};
+}
+
+}  // namespace
+
+#define NA2D_STRIP_LAUNCH(kern, ...)                                                                                         \
+    do {                                                                                                                     \
+        hipLaunchKernelGGL(kern, dim3(xcd_padded_grid(g.ntiles)), dim3(kStripThreads), 0, s, __VA_ARGS__, g);                \
+        return hipGetLastError();                                                                                            \
+    } while (0)
+
+hipError_t launch_qk_strip(const Problem &p, const void *x, const void *y, const void *rpb, float scale, void *logits, hipStream_t s) {
+    const SShape g = strip_shape(p);
+    NA2D_DISPATCH_T(p.dtype, NA2D_DISPATCH_D(p.D, NA2D_STRIP_LAUNCH((qk_strip_kernel<T, D>), static_cast<const T *>(x), static_cast<const T *>(y),
+                                                                    static_cast<const T *>(rpb), scale, static_cast<T *>(logits))));
+    return hipErrorInvalidValue;
+}
+
+hipError_t launch_av_strip(const Problem &p, const void *w, const void *y, float scale, void *out, hipStream_t s) {
+    const SShape g = strip_shape(p);
+    NA2D_DISPATCH_T(p.dtype, NA2D_DISPATCH_D(p.D, NA2D_STRIP_LAUNCH((sum_strip_kernel<T, D, false>), static_cast<const T *>(w),
+                                                                    static_cast<const T *>(y), scale, static_cast<T *>(out))));
+    return hipErrorInvalidValue;
+}
+
+hipError_t launch_inverse_strip(const Problem &p, const void *w, const void *x, float scale, void *out, hipStream_t s) {
+    const SShape g = strip_shape(p);
+    NA2D_DISPATCH_T(p.dtype, NA2D_DISPATCH_D(p.D, NA2D_STRIP_LAUNCH((sum_strip_kernel<T, D, true>), static_cast<const T *>(w),
+                                                                    static_cast<const T *>(x), scale, static_cast<T *>(out))));
+    return hipErrorInvalidValue;
+}
+
+// blocks of keys at a time: two while the strip's windows then fit one pass (K <= 17), three for wider ones
+hipError_t launch_fused_strip(const Problem &p, const void *q, const void *k, const void *v, const void *rpb, float scale,
+                              void *out, float *lse, hipStream_t s) {
+    const SShape g = strip_shape(p);
+    if (p.K <= 17)
+        NA2D_DISPATCH_T(p.dtype, NA2D_DISPATCH_D(p.D, NA2D_STRIP_LAUNCH((fused_strip_kernel<T, D, 2>), static_cast<const T *>(q), static_cast<const T *>(k),
+                                                                        static_cast<const T *>(v), static_cast<const T *>(rpb), scale, static_cast<T *>(out), lse)));
+    NA2D_DISPATCH_T(p.dtype, NA2D_DISPATCH_D(p.D, NA2D_STRIP_LAUNCH((fused_strip_kernel<T, D, 3>), static_cast<const T *>(q), static_cast<const T *>(k),
+                                                                    static_cast<const T *>(v), static_cast<const T *>(rpb), scale, static_cast<T *>(out), lse)));
+    return hipErrorInvalidValue;
+}
+
+}  // namespace na2d

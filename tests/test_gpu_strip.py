@@ -1,0 +1,55 @@
+"""The strip kernels (na2d_strip.hip) where they can go wrong: maps of one strip, a strip and a remainder, a strip more
+than the windows' reach; and values that are not finite, which must reach exactly the outputs whose window holds them."""
+from __future__ import annotations
+
+import numpy as np
+import pytest
+import torch
+
+from paper_2204_07143_amd import functional as F
+from paper_2204_07143_amd import synth
+from gpu_util import assert_close
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("dtype", ["f32", "f16", "bf16"])
+@pytest.mark.parametrize("H,W,D,k", [(15, 16, 32, 15), (17, 33, 16, 17), (19, 19, 64, 19), (34, 49, 32, 33), (63, 65, 16, 63), (13, 31, 128, 13)])
+def test_forward_at_strip_edges(oracle, H, W, D, k, dtype):
+    p = synth.Problem(1, 2, H, W, D, k, dtype)
+    host = synth.make_inputs(p, seed=H * W + D)
+    q, key, v, rpb = (synth.to_device(host[n], dtype) for n in ("q", "k", "v", "rpb"))
+    out = F.na2d(q, key, v, rpb, kernel_size=k)
+    h = {n: host[n].astype(np.float64) for n in host}
+    assert_close("out", out, oracle.fwd(h["q"], h["k"], h["v"], h["rpb"], p.default_scale, k), dtype)
+
+
+@pytest.mark.parametrize("dtype", ["f32", "f16", "bf16"])
+def test_infinities_reach_their_windows_only(dtype):
+    H, W, D, k, y, x = 21, 40, 32, 15, 2, 20
+    torch.manual_seed(1)
+    dt = synth.TORCH_DTYPES[dtype]
+    q, key, v, dout = (torch.randn(1, 1, H, W, D, device="cuda").to(dt) for _ in range(4))
+    want = F.na2d(q, key, v, None, kernel_size=k)
+    v2 = v.clone()
+    v2[0, 0, y, x, 5] = float("inf")
+    got = F.na2d(q, key, v2, None, kernel_size=k)
+    attn = F.na2d_softmax(F.na2d_qk_rpb(q, key, None, k), q, k)
+    got_av = F.na2d_av(attn, v2, k)
+    first = lambda n, L: (torch.arange(n, device="cuda") - k // 2).clamp(0, L - k)
+    sees = lambda c, L: (first(L, L) <= c) & (c < first(L, L) + k)
+    hit = sees(y, H)[:, None] & sees(x, W)[None, :]
+    for g in (got, got_av):
+        assert torch.equal(torch.isinf(g[0, 0, :, :, 5]) | torch.isnan(g[0, 0, :, :, 5]), hit)
+        rest = torch.ones(D, dtype=torch.bool, device="cuda")
+        rest[5] = False
+        assert torch.isfinite(g[..., rest]).all()
+    assert (got[0, 0, :, :, 5][~hit].float() - want[0, 0, :, :, 5][~hit].float()).abs().max() < 8e-3
+    # grad-v: the same for an upstream gradient that is not finite, seen by the keys of that query's window
+    dout[0, 0, y, x, 5] = float("inf")
+    leaf = v.clone().requires_grad_()
+    F.na2d_av(attn, leaf, k).backward(dout)
+    sy, sx = max(0, min(y - k // 2, H - k)), max(0, min(x - k // 2, W - k))
+    want_hit = torch.zeros(H, W, dtype=torch.bool, device="cuda")
+    want_hit[sy:sy + k, sx:sx + k] = True
+    assert torch.equal(~torch.isfinite(leaf.grad[0, 0, :, :, 5]), want_hit)
