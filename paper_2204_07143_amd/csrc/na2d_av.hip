@@ -71,7 +71,8 @@ __global__ __launch_bounds__(kTileX *TY) void av_kernel(const T *__restrict__ w,
 
 template <typename T, int K, int D>
 static hipError_t launch_av_t(const Problem &p, const void *w, const void *y, float scale, void *out, hipStream_t s) {
-    if constexpr (!valu_fits<T, K, D>()) return hipErrorInvalidValue; else {
+    if constexpr (K > valu_most_k(ValuOp::weighted_sum, D)) return hipErrorInvalidValue; else {
+    static_assert(tile_fits<AvCfg, T, K, D>());
     constexpr int TY = tile_rows<AvCfg, T, K, D>();
     using C = AvCfg<T, K, TY, D>;
     const int tiles_x = (p.W + kTileX - 1) / kTileX, tiles_y = (p.H + TY - 1) / TY;
@@ -86,10 +87,15 @@ static hipError_t launch_av_t(const Problem &p, const void *w, const void *y, fl
     }
 }
 
+// Four slices of 32 channels are four launches of the matrix-core kernel; while the launches are what takes the time, one
+// launch of strips is faster (D = 128, f16, 56 x 56 maps, two heads, k = 7 .. 13: 21 .. 28 -> 10 us at 6k, 20 .. 29 -> 16 .. 22
+// at 25k queries; even at 50k, 32 .. 57 against 45 .. 70 at 100k).
+static bool av_strip_preferred(const Problem &p) { return p.D == 4 * kHeadDim && p.queries() < 32768; }
+
 hipError_t launch_av(const Problem &p, const void *w, const void *y, float scale, void *out, hipStream_t s) {
-    if (av_mfma_supported(p)) return launch_av_mfma(p, w, y, scale, out, s);
-    if (generic_window(p)) return launch_av_strip(p, w, y, scale, out, s);
-    NA2D_DISPATCH_T(p.dtype, NA2D_DISPATCH_K(p.K, NA2D_DISPATCH_D(p.D, return (launch_av_t<T, K, D>(p, w, y, scale, out, s)))));
+    if (av_mfma_supported(p) && !av_strip_preferred(p)) return launch_av_mfma(p, w, y, scale, out, s);
+    if (!valu_preferred(p, ValuOp::weighted_sum)) return launch_av_strip(p, w, y, scale, out, s);
+    NA2D_DISPATCH_K(p.K, NA2D_DISPATCH_D(p.D, return (launch_av_t<float, K, D>(p, w, y, scale, out, s))));
     return hipErrorInvalidValue;
 }
 

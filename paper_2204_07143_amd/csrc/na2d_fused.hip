@@ -94,7 +94,8 @@ __global__ __launch_bounds__(kTileX *TY) void fused_fwd_kernel(const T *__restri
 template <typename T, int K, int D>
 static hipError_t launch_fused_t(const Problem &p, const void *q, const void *k, const void *v, const void *rpb,
                                  float scale, void *out, float *lse, hipStream_t s) {
-    if constexpr (!valu_fits<T, K, D>()) return hipErrorInvalidValue; else {
+    if constexpr (K > valu_most_k(ValuOp::fused, D)) return hipErrorInvalidValue; else {
+    static_assert(tile_fits<FusedCfg, T, K, D>());
     constexpr int TY = tile_rows<FusedCfg, T, K, D>();
     using C = FusedCfg<T, K, TY, D>;
     const int tiles_x = (p.W + kTileX - 1) / kTileX, tiles_y = (p.H + TY - 1) / TY;
@@ -113,8 +114,8 @@ static hipError_t launch_fused_t(const Problem &p, const void *q, const void *k,
 hipError_t launch_fused_fwd(const Problem &p, const void *q, const void *k, const void *v, const void *rpb, float scale,
                             void *out, float *lse, hipStream_t s) {
     if (fused_mfma_supported(p)) return launch_fused_mfma(p, q, k, v, rpb, scale, out, lse, s);
-    if (generic_window(p)) return launch_fused_strip(p, q, k, v, rpb, scale, out, lse, s);
-    NA2D_DISPATCH_T(p.dtype, NA2D_DISPATCH_K(p.K, NA2D_DISPATCH_D(p.D, return (launch_fused_t<T, K, D>(p, q, k, v, rpb, scale, out, lse, s)))));
+    if (!valu_preferred(p, ValuOp::fused)) return launch_fused_strip(p, q, k, v, rpb, scale, out, lse, s);
+    NA2D_DISPATCH_K(p.K, NA2D_DISPATCH_D(p.D, return (launch_fused_t<float, K, D>(p, q, k, v, rpb, scale, out, lse, s))));
     return hipErrorInvalidValue;
 }
 

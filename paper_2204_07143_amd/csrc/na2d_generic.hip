@@ -3,7 +3,6 @@
 // the window side as a run-time argument, fp32 arithmetic, any of the three storage types.
 #include "na2d_kernels.hpp"
 #include "na2d_common.hpp"
-#include "na2d_valu_cfg.hpp"
 
 namespace na2d {
 
@@ -148,10 +147,6 @@ GShape shape_of(const Problem &p) { return GShape{p.B, p.heads, p.H, p.W, p.K, p
 
 }  // namespace
 
-// Which problems have no kernel of a fixed window side: window sides beyond the tuned ones, and the combinations of
-// dtype, window and head dim whose plain-ALU tiles do not fit the LDS (fp32 with D >= 64 and a larger window, D = 128
-// in 16 bit with k = 13).
-bool generic_window(const Problem &p) { return p.K > kMaxTunedK || !head_dim_supported(p.dtype, p.K, p.D); }
 bool untuned_window(const Problem &p) { return p.K > kMaxTunedK; }
 
 // values a lane keeps of a row, rounded up to a power of two: 4 for K = 15 up to 64 for K = 63

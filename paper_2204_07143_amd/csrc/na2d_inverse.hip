@@ -65,7 +65,8 @@ __global__ __launch_bounds__(kTileX *TY) void inverse_kernel(const T *__restrict
 template <typename T, int K, int D>
 static hipError_t launch_inverse_t(const Problem &p, const void *w, const void *x, float scale, void *out,
                                    hipStream_t s) {
-    if constexpr (!valu_fits<T, K, D>()) return hipErrorInvalidValue; else {
+    if constexpr (K > valu_most_k(ValuOp::inverse, D)) return hipErrorInvalidValue; else {
+    static_assert(tile_fits<InvCfg, T, K, D>());
     constexpr int TY = tile_rows<InvCfg, T, K, D>();
     using C = InvCfg<T, K, TY, D>;
     const int tiles_x = (p.W + kTileX - 1) / kTileX, tiles_y = (p.H + TY - 1) / TY;
@@ -80,14 +81,24 @@ static hipError_t launch_inverse_t(const Problem &p, const void *w, const void *
     }
 }
 
+// Of the head dims that the matrix-core kernels of a fixed window side serve in slices of 32 channels, one launch per
+// slice, these run in strips, one launch that reads the weights once (f16, 56 x 56 maps, two heads, us, slices / strips):
+// from k = 9 on at every size (D = 128, k = 9: 168 / 127 at 300k queries, 35 / 10 at 6k; D = 64: k = 9 85 / 85 and 19 / 10,
+// k = 11 146 / 99 and 56 / 10), and four slices of any window while the launches are what takes the time (D = 128, k = 7:
+// 27 / 10 at 6k, 27 / 14 at 25k queries, 92 / 108 at 300k).
+static bool inverse_strip_preferred(const Problem &p) {
+    if (p.dtype == NA2D_F32 || p.D < 2 * kHeadDim) return false;
+    return p.K >= 9 || (p.D == 4 * kHeadDim && p.queries() < 32768);
+}
+
 hipError_t launch_inverse(const Problem &p, const void *w, const void *x, float scale, void *out, hipStream_t s) {
-    if (!untuned_window(p)) {
+    if (!untuned_window(p) && !inverse_strip_preferred(p)) {
         if (inverse_ring_supported(p)) return launch_inverse_ring(p, w, x, scale, out, s);
         if (inverse_mfma_supported(p)) return launch_inverse_mfma(p, w, x, scale, out, s);
         if (inverse_rows_supported(p)) return launch_inverse_rows(p, w, x, scale, out, s);
     }
-    if (generic_window(p)) return launch_inverse_strip(p, w, x, scale, out, s);
-    NA2D_DISPATCH_T(p.dtype, NA2D_DISPATCH_K(p.K, NA2D_DISPATCH_D(p.D, return (launch_inverse_t<T, K, D>(p, w, x, scale, out, s)))));
+    if (!valu_preferred(p, ValuOp::inverse)) return launch_inverse_strip(p, w, x, scale, out, s);
+    NA2D_DISPATCH_K(p.K, NA2D_DISPATCH_D(p.D, return (launch_inverse_t<float, K, D>(p, w, x, scale, out, s))));
     return hipErrorInvalidValue;
 }
 

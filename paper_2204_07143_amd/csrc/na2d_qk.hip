@@ -85,7 +85,8 @@ __global__ __launch_bounds__(kTileX *TY) void qk_kernel(const T *__restrict__ x,
 template <typename T, int K, int D>
 static hipError_t launch_qk_t(const Problem &p, const void *x, const void *y, const void *rpb, float scale,
                               void *logits, hipStream_t s) {
-    if constexpr (!valu_fits<T, K, D>()) return hipErrorInvalidValue; else {
+    if constexpr (K > valu_most_k(ValuOp::logits, D)) return hipErrorInvalidValue; else {
+    static_assert(tile_fits<QkCfg, T, K, D>());
     constexpr int TY = tile_rows<QkCfg, T, K, D>();
     using C = QkCfg<T, K, TY, D>;
     const int tiles_x = (p.W + kTileX - 1) / kTileX, tiles_y = (p.H + TY - 1) / TY;
@@ -100,23 +101,12 @@ static hipError_t launch_qk_t(const Problem &p, const void *x, const void *y, co
     }
 }
 
-// do the LDS tiles of every plain-ALU kernel fit for this dtype, window and head dim?
-bool head_dim_supported(int dtype, int K, int D) {
-    if (K > kMaxTunedK) return false;
-    auto probe = [&]() -> hipError_t {
-        NA2D_DISPATCH_T(dtype, NA2D_DISPATCH_K(K, NA2D_DISPATCH_D(D, return (valu_fits<T, K, D>() ? hipSuccess : hipErrorInvalidValue))));
-        return hipErrorInvalidValue;
-    };
-    return probe() == hipSuccess;
-}
-
 hipError_t launch_qk(const Problem &p, const void *x, const void *y, const void *rpb, float scale, void *logits,
                      hipStream_t s) {
-    // matrix cores where they take the problem; else the tiled plain-ALU kernel while its tile fits the LDS; else the
-    // kernels that stage nothing
+    // the kernels of a fixed window side where they take the problem, else strips
     if (qk_mfma_supported(p)) return launch_qk_mfma(p, x, y, rpb, scale, logits, s);
-    if (generic_window(p)) return launch_qk_strip(p, x, y, rpb, scale, logits, s);
-    NA2D_DISPATCH_T(p.dtype, NA2D_DISPATCH_K(p.K, NA2D_DISPATCH_D(p.D, return (launch_qk_t<T, K, D>(p, x, y, rpb, scale, logits, s)))));
+    if (!valu_preferred(p, ValuOp::logits)) return launch_qk_strip(p, x, y, rpb, scale, logits, s);
+    NA2D_DISPATCH_K(p.K, NA2D_DISPATCH_D(p.D, return (launch_qk_t<float, K, D>(p, x, y, rpb, scale, logits, s))));
     return hipErrorInvalidValue;
 }
 

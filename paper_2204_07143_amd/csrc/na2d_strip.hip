@@ -2,7 +2,7 @@
 // 2204.07143, Eq. 2-4 and the gradients of Appendix A): the contractions of the problems that have no kernel of a
 // fixed window side.
 //
-// A workgroup owns a strip of 16 consecutive positions of one map row; its four waves take the window rows in turn.
+// A strip is 16 consecutive positions of one map row; a workgroup's four waves take its window rows in turn, or a strip each.
 // For one window row the strip's windows together cover 16 + K - 1 consecutive positions of one row of the other
 // operand, i.e. one small dense product of 16 strip positions with blocks of 16 partner positions, masked by the
 // window.  Nothing but the waves' partial sums is staged in LDS, so neither the window nor the head dim is limited
@@ -30,20 +30,34 @@ namespace {
 constexpr int kStrip = 16, kStripWaves = 4, kStripThreads = kStripWaves * kWave;
 
 struct SShape {
-    int heads, H, W, K, strips, ntiles;
+    int heads, H, W, K, strips, rows, ntiles;   // strips per map row, rows of workgroups per plane
 };
 
+// SPLIT waves share a strip; the kStripWaves / SPLIT strips of a workgroup lie one below the other.
 struct Strip {
     int plane, y, x0;
+    int wave, part;   // wave of the workgroup, and which of the strip's window rows (part, part + SPLIT, ...) it takes
 };
-__device__ __forceinline__ bool decode_strip(const SShape &g, Strip &s) {
+template <int SPLIT> __device__ __forceinline__ bool decode_strip(const SShape &g, Strip &s) {
     const int t = xcd_contiguous_block(blockIdx.x, gridDim.x);
     if (t >= g.ntiles) return false;
+    s.wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+    s.part = s.wave % SPLIT;
     s.x0 = (t % g.strips) * kStrip;
     const int rest = t / g.strips;
-    s.y = rest % g.H;
-    s.plane = rest / g.H;
-    return true;
+    s.y = (rest % g.rows) * (kStripWaves / SPLIT) + s.wave / SPLIT;
+    s.plane = rest / g.rows;
+    return s.y < g.H;   // (with SPLIT = 4 the same for all waves of a workgroup, which then meet at a barrier)
+}
+// the waves of a strip have left their sums in LDS
+template <int SPLIT> __device__ __forceinline__ void join_waves() {
+    if constexpr (SPLIT > 1) {
+        workgroup_sync();
+    } else {
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    }
 }
 
 template <typename T> __device__ __forceinline__ uint32_t pack2(T lo, T hi) {
@@ -142,12 +156,12 @@ template <typename T, int D> struct SumAcc {
 __device__ __forceinline__ int clamp_to(int v, int hi) { return v < 0 ? 0 : (v < hi ? v : hi); }
 
 // logits[n, a, c] = scale <x_n, y_key(n; a, c)> + bias (and grad-a: x = dout, y = v)
-template <typename T, int D>
+template <typename T, int D, int SPLIT>
 __global__ __launch_bounds__(kStripThreads) void qk_strip_kernel(const T *__restrict__ x, const T *__restrict__ y,
                                                                  const T *__restrict__ rpb, float scale, T *__restrict__ logits, SShape g) {
     Strip st;
-    if (!decode_strip(g, st)) return;
-    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave), lane = threadIdx.x % kWave, j = lane % 16, grp = lane / 16;
+    if (!decode_strip<SPLIT>(g, st)) return;
+    const int lane = threadIdx.x % kWave, j = lane % 16, grp = lane / 16;
     const int K = g.K, W = g.W, KK = K * K, NB = 2 * K - 1;
     const size_t plane0 = (size_t)st.plane * g.H * W;
     const bool mine = st.x0 + j < W;
@@ -159,9 +173,8 @@ __global__ __launch_bounds__(kStripThreads) void qk_strip_kernel(const T *__rest
     const T *yp = y + plane0 * D;
     T *row = logits + (plane0 + (size_t)st.y * W + qx) * KK;
     const T *bt = rpb ? rpb + ((size_t)(st.plane % g.heads) * NB + (sy - st.y + K - 1)) * NB + (sx - qx + K - 1) : nullptr;
-    for (int a = wave; a < K; a += kStripWaves) {
+    for (int a = st.part; a < K; a += SPLIT) {
         const T *yrow = yp + (size_t)(sy + a) * W * D;
-#pragma unroll 2
         for (int b = 0; b < nblk; ++b) {
             const int k0 = kx0 + 16 * b, kl = k0 + j < W ? k0 + j : W - 1;
             ChannelOp<T, D> yo;
@@ -198,14 +211,14 @@ __device__ __noinline__ float sum_one(const T *w, const T *y, int H, int W, int 
 
 // INV false: out[n, :] = scale sum_slot w[n, slot] y_key(n; slot).  INV true: out[j, :] = scale sum of w[i, slot(i, j)] y_i
 // over the queries i that see key j.  The waves' sums are added in wave order: the same bits in every run.
-template <typename T, int D, bool INV>
+template <typename T, int D, bool INV, int SPLIT>
 __global__ __launch_bounds__(kStripThreads) void sum_strip_kernel(const T *__restrict__ w, const T *__restrict__ y, float scale,
                                                                   T *__restrict__ out, SShape g) {
     using A = SumAcc<T, D>;
     __shared__ float part[kStripWaves][kStrip * A::kPitch];
     Strip st;
-    if (!decode_strip(g, st)) return;
-    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave), lane = threadIdx.x % kWave, j = lane % 16, grp = lane / 16;
+    if (!decode_strip<SPLIT>(g, st)) return;
+    const int lane = threadIdx.x % kWave, j = lane % 16, grp = lane / 16;
     const int K = g.K, W = g.W, H = g.H, KK = K * K;
     const size_t plane0 = (size_t)st.plane * H * W;
     const T *wp = w + plane0 * KK, *yp = y + plane0 * D;
@@ -219,7 +232,7 @@ __global__ __launch_bounds__(kStripThreads) void sum_strip_kernel(const T *__res
     const int sx = win_start(px, W, K);
     A acc;
     acc.clear();
-    for (int oy = y0 + wave; oy <= y1; oy += kStripWaves) {
+    for (int oy = y0 + st.part; oy <= y1; oy += SPLIT) {
         const int a = INV ? st.y - win_start(oy, H, K) : oy - y0;
         const int wrow = INV ? oy * W * KK + a * K : (st.y * W + px) * KK + a * K;
 #pragma unroll 2
@@ -238,14 +251,15 @@ __global__ __launch_bounds__(kStripThreads) void sum_strip_kernel(const T *__res
             acc.template add<1>(yp, off, j, wt);
         }
     }
-    acc.to_lds(part[wave], j, grp);
-    workgroup_sync();
-    for (int i = threadIdx.x; i < kStrip * D; i += kStripThreads) {
+    acc.to_lds(part[st.wave], j, grp);
+    join_waves<SPLIT>();
+    const int w0 = st.wave - st.part;   // the strip's first wave
+    for (int i = st.part * kWave + lane; i < kStrip * D; i += SPLIT * kWave) {
         const int p = i / D, d = i % D;
         if (st.x0 + p >= W) break;   // (p grows with i)
         float v = 0.f;
 #pragma unroll
-        for (int s = 0; s < kStripWaves; ++s) v += part[s][p * A::kPitch + d];
+        for (int s = 0; s < SPLIT; ++s) v += part[w0 + s][p * A::kPitch + d];
         if (!(fabsf(v) < INFINITY)) v = sum_one<T, D, INV>(wp, yp, H, W, K, st.y, st.x0 + p, d);
         out[(plane0 + (size_t)st.y * W + st.x0 + p) * D + d] = from_f32<T>(scale * v);
     }
@@ -273,7 +287,7 @@ __device__ __noinline__ float fused_one(const T *q, const T *kp, const T *vp, co
 // Fused forward.  Each wave keeps a running maximum, sum and weighted values of its window rows, NBX blocks of 16 keys
 // at a time; the logits leave the matrix cores in the layout in which the weights enter them again.  The waves'
 // results are joined in wave order.
-template <typename T, int D, int NBX>
+template <typename T, int D, int NBX, int SPLIT>
 __global__ __launch_bounds__(kStripThreads) void fused_strip_kernel(const T *__restrict__ q, const T *__restrict__ k,
                                                                     const T *__restrict__ v, const T *__restrict__ rpb, float scale,
                                                                     T *__restrict__ out, float *__restrict__ lse, SShape g) {
@@ -282,8 +296,8 @@ __global__ __launch_bounds__(kStripThreads) void fused_strip_kernel(const T *__r
     __shared__ float part[kStripWaves][kStrip * A::kPitch];
     __shared__ float wm[kStripWaves][kStrip], wl[kStripWaves][kStrip];
     Strip st;
-    if (!decode_strip(g, st)) return;
-    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave), lane = threadIdx.x % kWave, j = lane % 16, grp = lane / 16;
+    if (!decode_strip<SPLIT>(g, st)) return;
+    const int lane = threadIdx.x % kWave, j = lane % 16, grp = lane / 16;
     const int K = g.K, W = g.W, NB = 2 * K - 1;
     const size_t plane0 = (size_t)st.plane * g.H * W;
     const int qx = st.x0 + j < W ? st.x0 + j : W - 1, sx = win_start(qx, W, K), sy = win_start(st.y, g.H, K);
@@ -297,7 +311,7 @@ __global__ __launch_bounds__(kStripThreads) void fused_strip_kernel(const T *__r
     float m = -INFINITY, l = 0.f;
     A acc;
     acc.clear();
-    for (int a = wave; a < K; a += kStripWaves) {
+    for (int a = st.part; a < K; a += SPLIT) {
         const int row = (sy + a) * W;
         for (int b0 = 0; b0 < nblk; b0 += NBX) {
             float s[NBX][4];
@@ -345,20 +359,21 @@ __global__ __launch_bounds__(kStripThreads) void fused_strip_kernel(const T *__r
     l += __shfl_xor(l, 16);
     l += __shfl_xor(l, 32);
     if (grp == 0) {
-        wm[wave][j] = m;
-        wl[wave][j] = l;
+        wm[st.wave][j] = m;
+        wl[st.wave][j] = l;
     }
-    acc.to_lds(part[wave], j, grp);
-    workgroup_sync();
-    for (int i = threadIdx.x; i < kStrip * D; i += kStripThreads) {
+    acc.to_lds(part[st.wave], j, grp);
+    join_waves<SPLIT>();
+    const int w0 = st.wave - st.part;   // the strip's first wave
+    for (int i = st.part * kWave + lane; i < kStrip * D; i += SPLIT * kWave) {
         const int p = i / D, d = i % D, x = st.x0 + p;
         if (x >= W) break;
-        float mm = wm[0][p];
+        float mm = wm[w0][p];
 #pragma unroll
-        for (int t = 1; t < kStripWaves; ++t) mm = fmaxf(mm, wm[t][p]);
+        for (int t = 1; t < SPLIT; ++t) mm = fmaxf(mm, wm[w0 + t][p]);
         float num = 0.f, den = 0.f;
 #pragma unroll
-        for (int t = 0; t < kStripWaves; ++t) {
+        for (int t = w0; t < w0 + SPLIT; ++t) {
             const float f = wm[t][p] == -INFINITY ? 0.f : __expf(wm[t][p] - mm);   // a wave without rows adds nothing
             num = __builtin_fmaf(f, part[t][p * A::kPitch + d], num);
             den = __builtin_fmaf(f, wl[t][p], den);
@@ -374,50 +389,64 @@ __global__ __launch_bounds__(kStripThreads) void fused_strip_kernel(const T *__r
     }
 }
 
-SShape strip_shape(const Problem &p) {
-    const int strips = (p.W + kStrip - 1) / kStrip;
-    return SShape{p.heads, p.H, p.W, p.K, strips, p.planes() * p.H * strips};
+// Logits and fused forward: four waves to a strip while that is what fills the chip; with enough strips each wave keeps
+// one to itself, the four of a workgroup one below the other: they read nearly the same rows at the same time, and
+// nothing has to be joined (fp32, 56 x 56 maps, us, one wave / four: fused D = 128, k = 7 613 / 716 at 21k strips, 210 / 233
+// at 7k, 125 / 122 at 3.6k, 41 / 23 at 450).  The weighted sums gain nothing from it (D = 64, k = 9: 198 / 196 at 21k).
+int strip_split(const Problem &p) { return (long long)p.planes() * p.H * ((p.W + kStrip - 1) / kStrip) >= 6144 ? 1 : kStripWaves; }
+
+SShape strip_shape(const Problem &p, int split) {
+    const int strips = (p.W + kStrip - 1) / kStrip, per = kStripWaves / split, rows = (p.H + per - 1) / per;
+    return SShape{p.heads, p.H, p.W, p.K, strips, rows, p.planes() * rows * strips};
 }
 
 }  // namespace
 
-#define NA2D_STRIP_LAUNCH(kern, ...)                                                                                         \
-    do {                                                                                                                     \
-        hipLaunchKernelGGL(kern, dim3(xcd_padded_grid(g.ntiles)), dim3(kStripThreads), 0, s, __VA_ARGS__, g);                \
-        return hipGetLastError();                                                                                            \
+#define NA2D_STRIP_LAUNCH(kern, ...)                                                                              \
+    do {                                                                                                          \
+        hipLaunchKernelGGL(kern, dim3(xcd_padded_grid(g.ntiles)), dim3(kStripThreads), 0, s, __VA_ARGS__, g);     \
+        return hipGetLastError();                                                                                 \
+    } while (0)
+// BODY with T, D and SPLIT bound
+#define NA2D_STRIP_DISPATCH(...)                                                                                  \
+    do {                                                                                                          \
+        const int split = strip_split(p);                                                                         \
+        const SShape g = strip_shape(p, split);                                                                   \
+        if (split == 1) { constexpr int SPLIT = 1; NA2D_DISPATCH_T(p.dtype, NA2D_DISPATCH_D(p.D, __VA_ARGS__)); } \
+        else { constexpr int SPLIT = kStripWaves; NA2D_DISPATCH_T(p.dtype, NA2D_DISPATCH_D(p.D, __VA_ARGS__)); }  \
     } while (0)
 
 hipError_t launch_qk_strip(const Problem &p, const void *x, const void *y, const void *rpb, float scale, void *logits, hipStream_t s) {
-    const SShape g = strip_shape(p);
-    NA2D_DISPATCH_T(p.dtype, NA2D_DISPATCH_D(p.D, NA2D_STRIP_LAUNCH((qk_strip_kernel<T, D>), static_cast<const T *>(x), static_cast<const T *>(y),
-                                                                    static_cast<const T *>(rpb), scale, static_cast<T *>(logits))));
+    NA2D_STRIP_DISPATCH(NA2D_STRIP_LAUNCH((qk_strip_kernel<T, D, SPLIT>), static_cast<const T *>(x), static_cast<const T *>(y),
+                                          static_cast<const T *>(rpb), scale, static_cast<T *>(logits)));
     return hipErrorInvalidValue;
 }
 
 hipError_t launch_av_strip(const Problem &p, const void *w, const void *y, float scale, void *out, hipStream_t s) {
-    const SShape g = strip_shape(p);
-    NA2D_DISPATCH_T(p.dtype, NA2D_DISPATCH_D(p.D, NA2D_STRIP_LAUNCH((sum_strip_kernel<T, D, false>), static_cast<const T *>(w),
-                                                                    static_cast<const T *>(y), scale, static_cast<T *>(out))));
+    const SShape g = strip_shape(p, kStripWaves);
+    NA2D_DISPATCH_T(p.dtype, NA2D_DISPATCH_D(p.D, NA2D_STRIP_LAUNCH((sum_strip_kernel<T, D, false, kStripWaves>), static_cast<const T *>(w),
+                                          static_cast<const T *>(y), scale, static_cast<T *>(out))));
     return hipErrorInvalidValue;
 }
 
 hipError_t launch_inverse_strip(const Problem &p, const void *w, const void *x, float scale, void *out, hipStream_t s) {
-    const SShape g = strip_shape(p);
-    NA2D_DISPATCH_T(p.dtype, NA2D_DISPATCH_D(p.D, NA2D_STRIP_LAUNCH((sum_strip_kernel<T, D, true>), static_cast<const T *>(w),
-                                                                    static_cast<const T *>(x), scale, static_cast<T *>(out))));
+    const SShape g = strip_shape(p, kStripWaves);
+    NA2D_DISPATCH_T(p.dtype, NA2D_DISPATCH_D(p.D, NA2D_STRIP_LAUNCH((sum_strip_kernel<T, D, true, kStripWaves>), static_cast<const T *>(w),
+                                          static_cast<const T *>(x), scale, static_cast<T *>(out))));
     return hipErrorInvalidValue;
 }
 
 // blocks of keys at a time: two while the strip's windows then fit one pass (K <= 17), three for wider ones
+template <int NBX>
+static hipError_t launch_fused_strip_t(const Problem &p, const void *q, const void *k, const void *v, const void *rpb, float scale,
+                                       void *out, float *lse, hipStream_t s) {
+    NA2D_STRIP_DISPATCH(NA2D_STRIP_LAUNCH((fused_strip_kernel<T, D, NBX, SPLIT>), static_cast<const T *>(q), static_cast<const T *>(k),
+                                          static_cast<const T *>(v), static_cast<const T *>(rpb), scale, static_cast<T *>(out), lse));
+    return hipErrorInvalidValue;
+}
 hipError_t launch_fused_strip(const Problem &p, const void *q, const void *k, const void *v, const void *rpb, float scale,
                               void *out, float *lse, hipStream_t s) {
-    const SShape g = strip_shape(p);
-    if (p.K <= 17)
-        NA2D_DISPATCH_T(p.dtype, NA2D_DISPATCH_D(p.D, NA2D_STRIP_LAUNCH((fused_strip_kernel<T, D, 2>), static_cast<const T *>(q), static_cast<const T *>(k),
-                                                                        static_cast<const T *>(v), static_cast<const T *>(rpb), scale, static_cast<T *>(out), lse)));
-    NA2D_DISPATCH_T(p.dtype, NA2D_DISPATCH_D(p.D, NA2D_STRIP_LAUNCH((fused_strip_kernel<T, D, 3>), static_cast<const T *>(q), static_cast<const T *>(k),
-                                                                    static_cast<const T *>(v), static_cast<const T *>(rpb), scale, static_cast<T *>(out), lse)));
-    return hipErrorInvalidValue;
+    return p.K <= 17 ? launch_fused_strip_t<2>(p, q, k, v, rpb, scale, out, lse, s) : launch_fused_strip_t<3>(p, q, k, v, rpb, scale, out, lse, s);
 }
 
 }  // namespace na2d

@@ -1,9 +1,8 @@
-// LDS footprints and tile heights of the plain-ALU 2D kernels, shared by the kernels and by the argument
-// validation of the C ABI (a head dim / kernel size pair is accepted only if every kernel's tile fits the
-// 160 KB LDS of a compute unit at the smallest tile height).
+// LDS footprints and tile heights of the plain-ALU 2D kernels, and which problems they serve.
 #pragma once
 
 #include "na2d_common.hpp"
+#include "na2d_kernels.hpp"
 #include "na2d_tile.hpp"
 
 namespace na2d {
@@ -74,14 +73,27 @@ template <template <typename, int, int, int> class Cfg, typename T, int K, int D
 constexpr bool tile_fits() {
     return Cfg<T, K, tile_rows<Cfg, T, K, D>(), D>::kLdsBytes <= kLdsLimit;
 }
-// every plain-ALU kernel of the forward and the backward has a tile that fits
-template <typename T, int K, int D>
-constexpr bool valu_fits() {
-    return tile_fits<QkCfg, T, K, D>() && tile_fits<AvCfg, T, K, D>() && tile_fits<InvCfg, T, K, D>() &&
-           tile_fits<FusedCfg, T, K, D>();
-}
 
-// run-time form (false for window sides beyond the tuned ones)
-bool head_dim_supported(int dtype, int K, int D);
+// Which problems run these kernels: fp32 (16 bit is the matrix cores' throughout), windows up to the side below, and
+// enough queries that their large tiles fill the chip.  Measured on 56 x 56 maps, two heads, against the strip kernels
+// (na2d_strip.hip), us, tile / strip: from 50k queries on the tiles win up to these sides (logits D = 32, k = 7:
+// 18 / 27 at 50k and 91 / 123 at 300k queries; weighted sum 17 / 22 and 86 / 109; inverse D = 16, k = 5: 43 / 51 at
+// 300k; fused D = 32, k = 7: 33 / 37 at 50k) and lose beyond them (k = 9: logits 219 / 161, weighted sum 200 / 138,
+// inverse 341 / 115, fused 508 / 215 at 300k; D = 64, k = 9: 348 / 240, 463 / 196, 755 / 175, 1513 / 398; D = 128, k = 3:
+// 220 / 148, 256 / 150, 275 / 147, 1010 / 336); at 25k and fewer the strips are as fast or faster at every side
+// (inverse D = 32, k = 7 at 6k: 37 / 10).
+enum class ValuOp { logits, weighted_sum, inverse, fused };
+constexpr int valu_most_k(ValuOp op, int D) {
+    switch (op) {
+        case ValuOp::logits: return D == 16 ? 9 : D == 32 ? 7 : D == 64 ? 5 : 0;
+        case ValuOp::weighted_sum: return D == 16 ? 9 : D == 32 ? 7 : 0;
+        case ValuOp::inverse: return D == 16 ? 5 : D == 32 ? 3 : 0;
+        default: return D == 16 ? 11 : D == 32 ? 7 : 0;
+    }
+}
+constexpr size_t kValuQueries = 32768;
+inline bool valu_preferred(const Problem &p, ValuOp op) {
+    return p.dtype == NA2D_F32 && p.K <= valu_most_k(op, p.D) && p.queries() >= kValuQueries;
+}
 
 }  // namespace na2d
