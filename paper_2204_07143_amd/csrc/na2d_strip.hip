@@ -14,8 +14,10 @@
 // fused operator, together with the steps of na2d_generic.hip): 3099 -> 288 us.
 //
 // Weights that are stored are products of 16-bit (or fp32) operands summed in fp32: exact products as on the plain
-// ALU.  The fused forward keeps its weights in fp32; in 16 bit they enter as a high and a low half (p = hi + lo to
-// 2^-17 in bf16, 2^-22 in fp16), two products instead of one.
+// ALU.  The fused forward keeps its weights in fp32; in 16 bit they enter as a high and a low half, two products instead
+// of one: p = hi + lo to 2^-17 of p in bf16.  In fp16 they are scaled by 2^15 first (kWeightUp; the sum of the weights
+// likewise, so that it cancels): then the halves hold p to 2^-22 of itself down to p = 2^-18 of the largest weight and to
+// 2^-40 of the largest below, instead of to 2^-25 (below which a weight left the numerator but not the sum).
 //
 // A masked product is 0 * y.  Where y is not finite that would spoil positions whose window does not hold it, so an
 // output that is not finite is computed once more from its own window only.
@@ -284,6 +286,10 @@ __device__ __noinline__ float fused_one(const T *q, const T *kp, const T *vp, co
     return acc;
 }
 
+// the power of two by which the fused forward's weights are scaled: the largest is then 2^15, within fp16's range
+template <typename T> constexpr float kWeightUp = 1.f;
+template <> constexpr float kWeightUp<f16_t> = 32768.f;
+
 // Fused forward.  Each wave keeps a running maximum, sum and weighted values of its window rows, NBX blocks of 16 keys
 // at a time; the logits leave the matrix cores in the layout in which the weights enter them again.  The waves'
 // results are joined in wave order.
@@ -345,7 +351,7 @@ __global__ __launch_bounds__(kStripThreads) void fused_strip_kernel(const T *__r
                 int off[4];
 #pragma unroll
                 for (int r = 0; r < 4; ++r) {
-                    const float p = __expf(s[b][r] - base);
+                    const float p = kWeightUp<T> * __expf(s[b][r] - base);
                     l += p;
                     wt[0][r] = from_f32<T>(p);
                     if constexpr (NW == 2) wt[NW - 1][r] = from_f32<T>(p - to_f32(wt[0][r]));
@@ -382,10 +388,10 @@ __global__ __launch_bounds__(kStripThreads) void fused_strip_kernel(const T *__r
         const size_t n = plane0 + (size_t)st.y * W + x;
         if (!(fabsf(num) < INFINITY)) {
             const int osx = win_start(x, W, K);
-            num = fused_one<T, D>(q + n * D, kp, vp, table ? table + osx - x + K - 1 : nullptr, scale, mm, W, K, sy, osx, d);
+            num = kWeightUp<T> * fused_one<T, D>(q + n * D, kp, vp, table ? table + osx - x + K - 1 : nullptr, scale, mm, W, K, sy, osx, d);
         }
         out[n * D + d] = from_f32<T>(num * (1.f / den));
-        if (lse != nullptr && d == 0) lse[n] = mm + __logf(den);
+        if (lse != nullptr && d == 0) lse[n] = mm + __logf(den * (1.f / kWeightUp<T>));
     }
 }
 

@@ -24,6 +24,28 @@ def test_forward_at_strip_edges(oracle, H, W, D, k, dtype):
     assert_close("out", out, oracle.fwd(h["q"], h["k"], h["v"], h["rpb"], p.default_scale, k), dtype)
 
 
+@pytest.mark.parametrize("dtype", ["f16", "bf16"])            # the types whose weights enter in two halves
+@pytest.mark.parametrize("planes", [1, 50])   # four waves to a strip, and (6200 strips) one
+def test_small_weights_of_large_values(oracle, planes, dtype):
+    # One key takes all but 2.5e-8 of every weight and the values next to it are large: where a query's own column holds
+    # zeros its output is the sum of some 480 weights below 2^-25 times 6e4 (about 0.7).  The logits are the bias alone.
+    H, W, D, k = 62, 31, 16, 31
+    p = synth.Problem(planes, 1, H, W, D, k, dtype)
+    host = synth.make_inputs(synth.Problem(1, 1, H, W, D, k, dtype), seed=8)
+    host["q"][:] = 0
+    host["rpb"][:] = 0
+    host["rpb"][:, k - 1, k - 1] = 17.5
+    host["v"][..., 0::2, :] = 0
+    host["v"][..., 1::2, :] = synth.round_to(np.full(D, 6e4, dtype=np.float32), dtype)
+    q, key, v, rpb = (synth.to_device(host[n], dtype) for n in ("q", "k", "v", "rpb"))
+    q, key, v = (t.expand(p.B, -1, -1, -1, -1).contiguous() for t in (q, key, v))
+    out = F.na2d(q, key, v, rpb, kernel_size=k)
+    want = oracle.fwd(*(host[n].astype(np.float64) for n in ("q", "k", "v", "rpb")), p.default_scale, k)
+    for b in {0, planes - 1}:
+        # columns whose own value is zero (the others are 6e4 themselves)
+        assert_close("out", out[b:b + 1, :, :, 0::2], want[:, :, :, 0::2], dtype)
+
+
 @pytest.mark.parametrize("dtype", ["f32", "f16", "bf16"])
 def test_infinities_reach_their_windows_only(dtype):
     H, W, D, k, y, x = 21, 40, 32, 15, 2, 20
