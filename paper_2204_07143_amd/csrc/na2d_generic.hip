@@ -26,57 +26,94 @@ __device__ __forceinline__ float wave_sum(float v) {
     return v;
 }
 
-// Softmax of one row per wave (max-subtracted, fp32).  The row stays in registers, NPL values a lane, between the
-// maximum, the sum and the store; out may alias in: the whole row is read before any of it is written.
-template <typename T, int NPL>
-__global__ __launch_bounds__(256) void softmax_generic_kernel(const T *in, T *out, int KK, size_t nrows) {
-    const size_t row = (size_t)blockIdx.x * 4 + threadIdx.x / kWave;
-    const int lane = threadIdx.x % kWave;
-    if (row >= nrows) return;
-    const T *r = in + row * KK;
+// The rows of a workgroup of four waves: WPR waves share a row, NPL values a lane, which stay in registers between the
+// reductions and the store.  One wave up to 1024 elements (k = 31), four beyond: with one, 32 and 64 values a lane left
+// one to three waves per SIMD.  Measured in 16 bit, us, loop over memory / one wave, loads behind conditions / as here:
+// k = 21, 5 x 2 x 64 x 64 rows, softmax 35 / 22 / 13, backward 26 / 28 / 13; k = 45, 2 x 64 x 64 rows, 35 / 19 / 13 and
+// 25 / 39 / 12; k = 63, 2 x 63 x 70 rows, 100 / 75 / 23 and 73 / 115 / 22 (5 TB/s).
+constexpr int kRowWaves = 4;
+template <int WPR> struct RowWave {
+    static_assert(WPR == 1 || WPR == kRowWaves);
+    size_t row;
+    int first;   // the lane's first element; the others follow WPR * kWave apart
+    __device__ __forceinline__ RowWave() {
+        const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+        row = (size_t)blockIdx.x * (kRowWaves / WPR) + wave / WPR;
+        first = (wave % WPR) * kWave + threadIdx.x % kWave;
+    }
+    __device__ __forceinline__ int at(int t) const { return first + t * WPR * kWave; }
+    // Past the row's end a lane reads its last element again (the caller drops it): no load is behind a condition, where
+    // the conversion of a 16-bit element would wait for its own load, so all of them are in flight at once.
+    template <typename T> __device__ __forceinline__ T load(const T *r, int t, int KK) const {
+        return r[(unsigned)(at(t) < KK ? at(t) : KK - 1)];
+    }
+};
+// the waves' values of a row, joined in wave order; every wave has read its part of the row before this returns
+template <int WPR, typename Op> __device__ __forceinline__ float join_row(float v, float *lds, Op op) {
+    if constexpr (WPR == 1) return v;
+    else {
+        if (threadIdx.x % kWave == 0) lds[threadIdx.x / kWave] = v;
+        workgroup_sync();
+        float r = lds[0];
+#pragma unroll
+        for (int w = 1; w < WPR; ++w) r = op(r, lds[w]);
+        return r;
+    }
+}
+
+// softmax of a row (max-subtracted, fp32); out may alias in: the whole row is read before any of it is written
+template <typename T, int NPL, int WPR>
+__global__ __launch_bounds__(kRowWaves *kWave) void softmax_generic_kernel(const T *in, T *out, int KK, size_t nrows) {
+    __shared__ float maxima[kRowWaves], sums[kRowWaves];
+    const RowWave<WPR> rw;
+    if (rw.row >= nrows) return;   // (with WPR = 4 the same for all waves)
+    const T *r = in + rw.row * KK;
+    T raw[NPL];
+#pragma unroll
+    for (int t = 0; t < NPL; ++t) raw[t] = rw.load(r, t, KK);
     float x[NPL], m = -INFINITY;
 #pragma unroll
     for (int t = 0; t < NPL; ++t) {
-        const int i = lane + t * kWave;
-        x[t] = i < KK ? ld(r, i) : -INFINITY;
+        x[t] = rw.at(t) < KK ? to_f32(raw[t]) : -INFINITY;
         m = fmaxf(m, x[t]);
     }
-    m = wave_max(m);
+    m = join_row<WPR>(wave_max(m), maxima, [](float a, float b) { return fmaxf(a, b); });
     float l = 0.f;
 #pragma unroll
     for (int t = 0; t < NPL; ++t) {
-        x[t] = lane + t * kWave < KK ? __expf(x[t] - m) : 0.f;
+        x[t] = rw.at(t) < KK ? __expf(x[t] - m) : 0.f;
         l += x[t];
     }
-    l = wave_sum(l);
+    l = join_row<WPR>(wave_sum(l), sums, [](float a, float b) { return a + b; });
     const float inv = 1.f / l;
-    T *o = out + row * KK;
+    T *o = out + rw.row * KK;
 #pragma unroll
     for (int t = 0; t < NPL; ++t)
-        if (lane + t * kWave < KK) o[lane + t * kWave] = from_f32<T>(x[t] * inv);
+        if (rw.at(t) < KK) o[(unsigned)rw.at(t)] = from_f32<T>(x[t] * inv);
 }
 
-// ds = attn * (dp - <attn, dp>), one row per wave, in registers likewise; ds may alias dp
-template <typename T, int NPL>
-__global__ __launch_bounds__(256) void softmax_bwd_generic_kernel(const T *attn, const T *dp, T *ds, int KK, size_t nrows) {
-    const size_t row = (size_t)blockIdx.x * 4 + threadIdx.x / kWave;
-    const int lane = threadIdx.x % kWave;
-    if (row >= nrows) return;
-    const T *pr = attn + row * KK, *dr = dp + row * KK;
-    float p[NPL], d[NPL], dot = 0.f;
+// ds = attn * (dp - <attn, dp>), likewise; ds may alias dp
+template <typename T, int NPL, int WPR>
+__global__ __launch_bounds__(kRowWaves *kWave) void softmax_bwd_generic_kernel(const T *attn, const T *dp, T *ds, int KK, size_t nrows) {
+    __shared__ float dots[kRowWaves];
+    const RowWave<WPR> rw;
+    if (rw.row >= nrows) return;
+    T p[NPL], d[NPL];
+    const T *pr = attn + rw.row * KK, *dr = dp + rw.row * KK;
 #pragma unroll
-    for (int t = 0; t < NPL; ++t) {
-        const int i = lane + t * kWave;
-        p[t] = i < KK ? ld(pr, i) : 0.f;
-        d[t] = i < KK ? ld(dr, i) : 0.f;
+    for (int t = 0; t < NPL; ++t) {   // (by turns: all of p before all of d took 281 us instead of 255 in fp32, k = 63)
+        p[t] = rw.load(pr, t, KK);
+        d[t] = rw.load(dr, t, KK);
     }
-#pragma unroll
-    for (int t = 0; t < NPL; ++t) dot = __builtin_fmaf(p[t], d[t], dot);
-    dot = wave_sum(dot);
-    T *o = ds + row * KK;
+    float dot = 0.f;
 #pragma unroll
     for (int t = 0; t < NPL; ++t)
-        if (lane + t * kWave < KK) o[lane + t * kWave] = from_f32<T>(p[t] * (d[t] - dot));
+        if (rw.at(t) < KK) dot = __builtin_fmaf(to_f32(p[t]), to_f32(d[t]), dot);
+    dot = join_row<WPR>(wave_sum(dot), dots, [](float a, float b) { return a + b; });
+    T *o = ds + rw.row * KK;
+#pragma unroll
+    for (int t = 0; t < NPL; ++t)
+        if (rw.at(t) < KK) o[(unsigned)rw.at(t)] = from_f32<T>(to_f32(p[t]) * (to_f32(d[t]) - dot));
 }
 
 // Bias gradient, first level: one partial table per (plane, range of query rows), one thread per cell (u, v), the
@@ -149,16 +186,20 @@ GShape shape_of(const Problem &p) { return GShape{p.B, p.heads, p.H, p.W, p.K, p
 
 bool untuned_window(const Problem &p) { return p.K > kMaxTunedK; }
 
-// values a lane keeps of a row, rounded up to a power of two: 4 for K = 15 up to 64 for K = 63
-template <typename T, int NPL = 4>
+// values a lane keeps of a row: 4 for k = 15, 8 to k = 21, 16 to k = 31; of a quarter of it 8 to k = 45, 16 to k = 63
+template <typename T, int NPL = 4, int WPR = 1>
 static hipError_t launch_softmax_generic_t(const Problem &p, const T *in, const T *dp, T *out, hipStream_t s) {
     const int KK = p.K * p.K;
-    if constexpr (NPL < 64)
-        if (KK > NPL * kWave) return launch_softmax_generic_t<T, 2 * NPL>(p, in, dp, out, s);
+    if constexpr (NPL < 16) {
+        if (KK > NPL * WPR * kWave) return launch_softmax_generic_t<T, 2 * NPL, WPR>(p, in, dp, out, s);
+    } else if constexpr (WPR == 1) {
+        if (KK > NPL * kWave) return launch_softmax_generic_t<T, 8, kRowWaves>(p, in, dp, out, s);
+    }
+    static_assert(kMaxGenericK * kMaxGenericK <= 16 * kRowWaves * kWave);
     const size_t rows = p.queries();
-    const dim3 grid((unsigned)((rows + 3) / 4)), block(256);
-    if (dp) hipLaunchKernelGGL((softmax_bwd_generic_kernel<T, NPL>), grid, block, 0, s, in, dp, out, KK, rows);
-    else hipLaunchKernelGGL((softmax_generic_kernel<T, NPL>), grid, block, 0, s, in, out, KK, rows);
+    const dim3 grid((unsigned)((rows * WPR + kRowWaves - 1) / kRowWaves)), block(kRowWaves * kWave);
+    if (dp) hipLaunchKernelGGL((softmax_bwd_generic_kernel<T, NPL, WPR>), grid, block, 0, s, in, dp, out, KK, rows);
+    else hipLaunchKernelGGL((softmax_generic_kernel<T, NPL, WPR>), grid, block, 0, s, in, out, KK, rows);
     return hipGetLastError();
 }
 
