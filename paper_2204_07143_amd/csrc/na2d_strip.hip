@@ -175,7 +175,7 @@ __global__ __launch_bounds__(kStripThreads) void qk_strip_kernel(const T *__rest
     const T *yp = y + plane0 * D;
     T *row = logits + (plane0 + (size_t)st.y * W + qx) * KK;
     const T *bt = rpb ? rpb + ((size_t)(st.plane % g.heads) * NB + (sy - st.y + K - 1)) * NB + (sx - qx + K - 1) : nullptr;
-    for (int a = st.part; a < K; a += SPLIT) {
+    for (int a = blockIdx.y * SPLIT + st.part; a < K; a += SPLIT * gridDim.y) {
         const T *yrow = yp + (size_t)(sy + a) * W * D;
         for (int b = 0; b < nblk; ++b) {
             const int k0 = kx0 + 16 * b, kl = k0 + j < W ? k0 + j : W - 1;
@@ -408,10 +408,12 @@ SShape strip_shape(const Problem &p, int split) {
 
 }  // namespace
 
-#define NA2D_STRIP_LAUNCH(kern, ...)                                                                              \
-    do {                                                                                                          \
-        hipLaunchKernelGGL(kern, dim3(xcd_padded_grid(g.ntiles)), dim3(kStripThreads), 0, s, __VA_ARGS__, g);     \
-        return hipGetLastError();                                                                                 \
+#define NA2D_STRIP_LAUNCH(kern, ...) NA2D_STRIP_LAUNCH_ROWS(1, kern, __VA_ARGS__)
+// a grid of `ngroups` workgroups per strip, each with its part of the window rows
+#define NA2D_STRIP_LAUNCH_ROWS(ngroups, kern, ...)                                                                        \
+    do {                                                                                                                  \
+        hipLaunchKernelGGL(kern, dim3(xcd_padded_grid(g.ntiles), ngroups), dim3(kStripThreads), 0, s, __VA_ARGS__, g);   \
+        return hipGetLastError();                                                                                         \
     } while (0)
 // BODY with T, D and SPLIT bound
 #define NA2D_STRIP_DISPATCH(...)                                                                                  \
@@ -422,9 +424,17 @@ SShape strip_shape(const Problem &p, int split) {
         else { constexpr int SPLIT = kStripWaves; NA2D_DISPATCH_T(p.dtype, NA2D_DISPATCH_D(p.D, __VA_ARGS__)); }  \
     } while (0)
 
+// Workgroups per strip for the logits, whose window rows need no joining: one window row to a wave at least, and no more
+// than 2048 workgroups (fp32: 1024).  A small call is bound by the chain of loads and stores along a wave's rows (us, one
+// group / at most 512 / 1024 / 2048 workgroups: bf16, D = 16, k = 17, 2 x 33 x 17 8.6 / 5.2 / 4.4 / 4.4, 10 x 33 x 17
+// 11.5 / 11.5 / 11.6 / 7.6; fp32, D = 128, k = 5, 16 x 28 x 28 16.4 / 16.4 / 16.5 / 17.6).
+static int qk_row_groups(const Problem &p, int ntiles) {
+    const int most = (p.K + kStripWaves - 1) / kStripWaves, fill = 4096 / p.elem_bytes() / ntiles;
+    return fill < 1 ? 1 : fill < most ? fill : most;
+}
 hipError_t launch_qk_strip(const Problem &p, const void *x, const void *y, const void *rpb, float scale, void *logits, hipStream_t s) {
-    NA2D_STRIP_DISPATCH(NA2D_STRIP_LAUNCH((qk_strip_kernel<T, D, SPLIT>), static_cast<const T *>(x), static_cast<const T *>(y),
-                                          static_cast<const T *>(rpb), scale, static_cast<T *>(logits)));
+    NA2D_STRIP_DISPATCH(NA2D_STRIP_LAUNCH_ROWS(qk_row_groups(p, g.ntiles), (qk_strip_kernel<T, D, SPLIT>), static_cast<const T *>(x),
+                                               static_cast<const T *>(y), static_cast<const T *>(rpb), scale, static_cast<T *>(logits)));
     return hipErrorInvalidValue;
 }
 

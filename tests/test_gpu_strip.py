@@ -6,6 +6,7 @@ import numpy as np
 import pytest
 import torch
 
+from paper_2204_07143_amd import binding as na
 from paper_2204_07143_amd import functional as F
 from paper_2204_07143_amd import synth
 from gpu_util import assert_close
@@ -44,6 +45,22 @@ def test_small_weights_of_large_values(oracle, planes, dtype):
     for b in {0, planes - 1}:
         # columns whose own value is zero (the others are 6e4 themselves)
         assert_close("out", out[b:b + 1, :, :, 0::2], want[:, :, :, 0::2], dtype)
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("H,W,k", [(15, 17, 15), (19, 21, 17), (33, 22, 21), (63, 63, 63)])
+def test_logits_whose_rows_are_shared_by_workgroups(oracle, H, W, k, dtype):
+    # One plane alone (every window row of a strip in a wave of its own) and many planes (all of a strip's rows in one
+    # workgroup) write the same bits, and the oracle's.
+    planes = 1 + 2048 // (H * ((W + 15) // 16)) if k < 63 else 20
+    p = synth.Problem(planes, 1, H, W, 16, k, dtype)
+    host = synth.make_inputs(synth.Problem(1, 1, H, W, 16, k, dtype), seed=k)
+    q, key, rpb = (synth.to_device(host[n], dtype) for n in ("q", "k", "rpb"))
+    empty = lambda b: torch.full((b, 1, H, W, k * k), float("nan"), dtype=q.dtype, device="cuda")
+    one = na.na2d_qk_rpb(q, key, rpb, p.default_scale, k, empty(1))
+    assert_close("logits", one, oracle.qk_rpb(*(host[n].astype(np.float64) for n in ("q", "k", "rpb")), p.default_scale, k), dtype)
+    many = na.na2d_qk_rpb(*(t.expand(planes, -1, -1, -1, -1).contiguous() for t in (q, key)), rpb, p.default_scale, k, empty(planes))
+    assert all(torch.equal(many[b:b + 1], one) for b in (0, planes // 2, planes - 1))
 
 
 @pytest.mark.parametrize("dtype", ["f32", "f16", "bf16"])
