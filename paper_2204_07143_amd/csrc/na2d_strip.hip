@@ -20,7 +20,10 @@
 // 2^-40 of the largest below, instead of to 2^-25 (below which a weight left the numerator but not the sum).
 //
 // A masked product is 0 * y.  Where y is not finite that would spoil positions whose window does not hold it, so an
-// output that is not finite is computed once more from its own window only.
+// output that is not finite is computed once more from its own window only, in a pass of its own that ends as soon as
+// its sums are NaN.  A call on values of NaN then takes (us, finite values in brackets): fused forward 7 x 100 x 134,
+// D = 128, k = 9, f16 654 (123; a thread per output that worked out every logit again: 15400), 4 x 2 x 64 x 64, D = 32,
+// k = 21, bf16 66 (45; 1230); weighted sum there 52 (44; with the whole window 178), inverse 39 (25; 263).
 #include "na2d_kernels.hpp"
 #include "na2d_mfma.hpp"
 #include "na2d_tile.hpp"
@@ -195,19 +198,21 @@ __global__ __launch_bounds__(kStripThreads) void qk_strip_kernel(const T *__rest
     }
 }
 
-// One output of the weighted sum from its own window, in raster order (strip outputs that are not finite)
+// One output of the weighted sum from its own window, in raster order (strip outputs that are not finite).  A sum that is
+// NaN stays NaN, so the walk ends there: where a whole tensor is NaN (a step that diverged) it reads one window row.
 template <typename T, int D, bool INV>
 __device__ __noinline__ float sum_one(const T *w, const T *y, int H, int W, int K, int py, int px, int d) {
     const int KK = K * K;
     float acc = 0.f;
     const int y0 = INV ? inv_first(py, H, K) : win_start(py, H, K), y1 = INV ? inv_last(py, H, K) : y0 + K - 1;
     const int x0 = INV ? inv_first(px, W, K) : win_start(px, W, K), x1 = INV ? inv_last(px, W, K) : x0 + K - 1;
-    for (int oy = y0; oy <= y1; ++oy)
+    for (int oy = y0; oy <= y1 && acc == acc; ++oy) {
         for (int ox = x0; ox <= x1; ++ox) {
             const size_t n = INV ? (size_t)oy * W + ox : (size_t)py * W + px;
             const int slot = INV ? (py - win_start(oy, H, K)) * K + px - win_start(ox, W, K) : (oy - y0) * K + ox - x0;
             acc = __builtin_fmaf(to_f32(w[n * KK + slot]), to_f32(y[((size_t)oy * W + ox) * D + d]), acc);
         }
+    }
     return acc;
 }
 
@@ -256,33 +261,70 @@ __global__ __launch_bounds__(kStripThreads) void sum_strip_kernel(const T *__res
     acc.to_lds(part[st.wave], j, grp);
     join_waves<SPLIT>();
     const int w0 = st.wave - st.part;   // the strip's first wave
-    for (int i = st.part * kWave + lane; i < kStrip * D; i += SPLIT * kWave) {
-        const int p = i / D, d = i % D;
-        if (st.x0 + p >= W) break;   // (p grows with i)
+    const auto joined = [&](int p, int d) {
         float v = 0.f;
 #pragma unroll
         for (int s = 0; s < SPLIT; ++s) v += part[w0 + s][p * A::kPitch + d];
-        if (!(fabsf(v) < INFINITY)) v = sum_one<T, D, INV>(wp, yp, H, W, K, st.y, st.x0 + p, d);
+        return v;
+    };
+    bool again = false;
+    for (int i = st.part * kWave + lane; i < kStrip * D; i += SPLIT * kWave) {
+        const int p = i / D, d = i % D;
+        if (st.x0 + p >= W) break;   // (p grows with i)
+        const float v = joined(p, d);
+        again |= !(fabsf(v) < INFINITY);
         out[(plane0 + (size_t)st.y * W + st.x0 + p) * D + d] = from_f32<T>(scale * v);
+    }
+    if (!again) return;
+#pragma unroll 1
+    for (int i = st.part * kWave + lane; i < kStrip * D; i += SPLIT * kWave) {
+        const int p = i / D, d = i % D;
+        if (st.x0 + p >= W) break;
+        if (!(fabsf(joined(p, d)) < INFINITY))
+            out[(plane0 + (size_t)st.y * W + st.x0 + p) * D + d] = from_f32<T>(scale * sum_one<T, D, INV>(wp, yp, H, W, K, st.y, st.x0 + p, d));
     }
 }
 
-// fp32 dot product of two head vectors, and one fused output from its own window (strip outputs that are not finite)
+// fp32 dot product of two head vectors
 template <typename T, int D> __device__ __forceinline__ float dot_one(const T *a, const T *b) {
     float acc = 0.f;
+#pragma unroll 8
     for (int d = 0; d < D; ++d) acc = __builtin_fmaf(to_f32(a[d]), to_f32(b[d]), acc);
     return acc;
 }
+// The fused outputs of one position from its own window, in raster order (strip outputs that are not finite): the whole
+// wave works out the weights of 64 slots, a slot to a lane, then each lane adds up its channel d.  `wanted`: the lanes whose
+// sum is asked for; once all of them are NaN nothing changes any more.
 template <typename T, int D>
-__device__ __noinline__ float fused_one(const T *q, const T *kp, const T *vp, const T *bt, float scale, float m, int W, int K, int sy, int sx, int d) {
+__device__ __noinline__ float fused_position(const T *q, const T *kp, const T *vp, const T *bt, float scale, float m, int W, int K, int sy, int sx, int d, bool wanted) {
+    constexpr int kAtOnce = 8;
+    const int KK = K * K, lane = threadIdx.x % kWave;
     float acc = 0.f;
-    for (int a = 0; a < K; ++a)
-        for (int c = 0; c < K; ++c) {
-            const size_t key = ((size_t)(sy + a) * W + sx + c) * D;
-            float s = scale * dot_one<T, D>(q, kp + key);
-            if (bt) s += to_f32(bt[a * (2 * K - 1) + c]);
-            acc = __builtin_fmaf(__expf(s - m), to_f32(vp[key + d]), acc);
+    int a0 = 0, c0 = 0;   // the chunk's first slot
+    for (int first = 0; first < KK; first += kWave) {
+        const int slot = first + lane < KK ? first + lane : KK - 1, a = slot / K, c = slot - a * K;
+        float s = scale * dot_one<T, D>(q, kp + ((size_t)(sy + a) * W + sx + c) * D);
+        if (bt) s += to_f32(bt[a * (2 * K - 1) + c]);
+        const float w = __expf(s - m);
+        const int n = KK - first < kWave ? KK - first : kWave;
+        for (int t = 0; t < n; t += kAtOnce) {   // (their loads do not wait for each other)
+            float wt[kAtOnce], y[kAtOnce];
+#pragma unroll
+            for (int e = 0; e < kAtOnce; ++e) {
+                wt[e] = __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, w), (t + e) % kWave));
+                y[e] = to_f32(vp[((size_t)(sy + a0) * W + sx + c0) * D + d]);
+                if (++c0 == K) {   // (past the last slot it stays there: read once more, not added)
+                    const bool more = a0 < K - 1;
+                    c0 = more ? 0 : K - 1;
+                    a0 += more;
+                }
+            }
+#pragma unroll
+            for (int e = 0; e < kAtOnce; ++e)
+                if (t + e < n) acc = __builtin_fmaf(wt[e], y[e], acc);
+            if (__ballot(wanted && acc == acc) == 0) return acc;
         }
+    }
     return acc;
 }
 
@@ -371,13 +413,13 @@ __global__ __launch_bounds__(kStripThreads) void fused_strip_kernel(const T *__r
     acc.to_lds(part[st.wave], j, grp);
     join_waves<SPLIT>();
     const int w0 = st.wave - st.part;   // the strip's first wave
-    for (int i = st.part * kWave + lane; i < kStrip * D; i += SPLIT * kWave) {
-        const int p = i / D, d = i % D, x = st.x0 + p;
-        if (x >= W) break;
-        float mm = wm[w0][p];
+    // the waves' parts of output i: maximum, weighted sum and sum of the weights
+    const auto joined = [&](int i, float &mm, float &num, float &den) {
+        const int p = i / D, d = i % D;
+        mm = wm[w0][p];
 #pragma unroll
         for (int t = 1; t < SPLIT; ++t) mm = fmaxf(mm, wm[w0 + t][p]);
-        float num = 0.f, den = 0.f;
+        num = den = 0.f;
 #pragma unroll
         for (int t = w0; t < w0 + SPLIT; ++t) {
             const float f = wm[t][p] == -INFINITY ? 0.f : __expf(wm[t][p] - mm);   // a wave without rows adds nothing
@@ -385,13 +427,38 @@ __global__ __launch_bounds__(kStripThreads) void fused_strip_kernel(const T *__r
             den = __builtin_fmaf(f, wl[t][p], den);
         }
         if (den == 0.f) den = NAN;   // every logit -inf
+    };
+    // (where the sum of the weights is NaN the output is, whatever the weighted sum is)
+    const auto spoilt = [](float num, float den) { return den == den && !(fabsf(num) < INFINITY); };
+    bool again = false;
+    for (int i = st.part * kWave + lane; i < kStrip * D; i += SPLIT * kWave) {
+        const int d = i % D, x = st.x0 + i / D;
+        if (x >= W) break;   // (the position grows with i)
+        float mm, num, den;
+        joined(i, mm, num, den);
+        again |= spoilt(num, den);
         const size_t n = plane0 + (size_t)st.y * W + x;
-        if (!(fabsf(num) < INFINITY)) {
-            const int osx = win_start(x, W, K);
-            num = kWeightUp<T> * fused_one<T, D>(q + n * D, kp, vp, table ? table + osx - x + K - 1 : nullptr, scale, mm, W, K, sy, osx, d);
-        }
         out[n * D + d] = from_f32<T>(num * (1.f / den));
         if (lse != nullptr && d == 0) lse[n] = mm + __logf(den * (1.f / kWeightUp<T>));
+    }
+    if (__ballot(again) == 0) return;
+    // outputs that are not finite once more from their own windows only, a position at a time
+    static_assert(kStrip * D % (SPLIT * kWave) == 0);   // (all lanes of a wave stay together)
+#pragma unroll 1
+    for (int i = st.part * kWave + lane; i < kStrip * D; i += SPLIT * kWave) {
+        const int p = i / D, d = i % D;
+        float mm, num, den;
+        joined(i, mm, num, den);
+        const bool redo = st.x0 + p < W && spoilt(num, den);
+        for (unsigned long long left = __ballot(redo); left != 0;) {
+            const int first = __builtin_ctzll(left), pp = __builtin_amdgcn_readlane(p, first), px = st.x0 + pp, osx = win_start(px, W, K);
+            const float mp = __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, mm), first));
+            const size_t n = plane0 + (size_t)st.y * W + px;
+            const bool here = redo && p == pp;
+            const float own = fused_position<T, D>(q + n * D, kp, vp, table ? table + osx - px + K - 1 : nullptr, scale, mp, W, K, sy, osx, d, here);
+            if (here) out[n * D + d] = from_f32<T>(kWeightUp<T> * own * (1.f / den));
+            left &= ~__ballot(here);
+        }
     }
 }
 

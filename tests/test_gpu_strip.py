@@ -92,3 +92,54 @@ def test_infinities_reach_their_windows_only(dtype):
     want_hit = torch.zeros(H, W, dtype=torch.bool, device="cuda")
     want_hit[sy:sy + k, sx:sx + k] = True
     assert torch.equal(~torch.isfinite(leaf.grad[0, 0, :, :, 5]), want_hit)
+
+
+@pytest.mark.parametrize("dtype", ["f32", "f16", "bf16"])
+@pytest.mark.parametrize("planes,H,W,D,k", [(1, 17, 33, 16, 15), (190, 17, 17, 16, 15), (1, 21, 40, 32, 21), (1, 13, 18, 128, 13), (420, 15, 17, 128, 15)])
+def test_values_that_are_not_finite_change_no_other_output(planes, H, W, D, k, dtype):
+    # four waves to a strip and (from 6144 strips on) one; four, two and one positions side by side in a wave
+    torch.manual_seed(3)
+    q, key, v = (torch.randn(planes, 1, H, W, D, device="cuda").to(synth.TORCH_DTYPES[dtype]) for _ in range(3))
+    attn = F.na2d_softmax(F.na2d_qk_rpb(q, key, None, k), q, k)
+    b, spots = planes // 2, [(2, 1, 5, float("inf")), (H - 3, W - 2, 5, -float("inf")), (H // 2, 0, 9, float("nan"))]
+    v2 = v.clone()
+    for y, x, d, value in spots:
+        v2[b, 0, y, x, d] = value
+    first = lambda n, L: (torch.arange(n, device="cuda") - k // 2).clamp(0, L - k)
+    sees = lambda c, L: (first(L, L) <= c) & (c < first(L, L) + k)
+    for op in (lambda t: F.na2d(q, key, t, None, kernel_size=k), lambda t: F.na2d_av(attn, t, k)):
+        want, got = op(v).float(), op(v2).float()
+        for y, x, d, value in spots:
+            hit = sees(y, H)[:, None] & sees(x, W)[None, :]
+            want[b, 0, :, :, d][hit] += value   # (an infinity of each sign: NaN)
+        # one rounding to the storage type (outputs next to a spoilt one are added up in another order)
+        ulp = {"f32": 2.0 ** -20, "f16": 2.0 ** -10, "bf16": 2.0 ** -7}[dtype]
+        torch.testing.assert_close(got, want, rtol=ulp, atol=ulp / 4, equal_nan=True)
+
+
+@pytest.mark.parametrize("B,H,W,D,k,dtype", [(8, 64, 64, 32, 21, "bf16"), (4, 56, 56, 128, 9, "f16"), (8, 56, 56, 64, 9, "f32")])
+def test_tensors_of_nan_take_no_multiple_of_the_time(B, H, W, D, k, dtype):
+    # a step that diverged: each output is worked out once more from its own window, and that must not go the long way
+    torch.manual_seed(4)
+    q, key, v = (torch.randn(B, 1, H, W, D, device="cuda").to(synth.TORCH_DTYPES[dtype]) for _ in range(3))
+    attn = F.na2d_softmax(F.na2d_qk_rpb(q, key, None, k), q, k)
+    out, nan = torch.empty_like(q), torch.full_like(v, float("nan"))
+
+    def best(call):
+        times = []
+        for _ in range(6):
+            a, b = (torch.cuda.Event(enable_timing=True) for _ in range(2))
+            a.record()
+            for _ in range(5):
+                call()
+            b.record()
+            b.synchronize()
+            times.append(a.elapsed_time(b))
+        return min(times)
+
+    fused = lambda t: best(lambda: na.na2d_fused_fwd(q, key, t, None, D ** -0.5, k, out))
+    finite = fused(v)
+    assert fused(nan) <= 10 * finite and torch.isnan(out).all()   # (D logits of every slot where one would do: 30 to 120 times)
+    for op in (na.na2d_av, na.na2d_av_bwd_v):
+        finite = best(lambda: op(attn, v, k, out))
+        assert best(lambda: op(attn, nan, k, out)) <= 3 * finite and torch.isnan(out).all()   # (10 times with the whole window)
