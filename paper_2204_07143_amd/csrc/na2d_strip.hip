@@ -20,8 +20,7 @@
 // 2^-40 of the largest below, instead of to 2^-25 (below which a weight left the numerator but not the sum).
 //
 // A masked product is 0 * y.  Where y is not finite that would spoil positions whose window does not hold it, so an
-// output that is not finite is computed once more from its own window only, in a pass of its own that ends as soon as
-// its sums are NaN.  A call on values of NaN then takes (us, finite values in brackets): fused forward 7 x 100 x 134,
+// output that is not finite is computed once more from its own window only, which ends as soon as its sum is NaN.  A call on values of NaN then takes (us, finite values in brackets): fused forward 7 x 100 x 134,
 // D = 128, k = 9, f16 654 (123; a thread per output that worked out every logit again: 15400), 4 x 2 x 64 x 64, D = 32,
 // k = 21, bf16 66 (45; 1230); weighted sum there 52 (44; with the whole window 178), inverse 39 (25; 263).
 #include "na2d_kernels.hpp"
@@ -261,27 +260,14 @@ __global__ __launch_bounds__(kStripThreads) void sum_strip_kernel(const T *__res
     acc.to_lds(part[st.wave], j, grp);
     join_waves<SPLIT>();
     const int w0 = st.wave - st.part;   // the strip's first wave
-    const auto joined = [&](int p, int d) {
-        float v = 0.f;
-#pragma unroll
-        for (int s = 0; s < SPLIT; ++s) v += part[w0 + s][p * A::kPitch + d];
-        return v;
-    };
-    bool again = false;
     for (int i = st.part * kWave + lane; i < kStrip * D; i += SPLIT * kWave) {
         const int p = i / D, d = i % D;
         if (st.x0 + p >= W) break;   // (p grows with i)
-        const float v = joined(p, d);
-        again |= !(fabsf(v) < INFINITY);
+        float v = 0.f;
+#pragma unroll
+        for (int s = 0; s < SPLIT; ++s) v += part[w0 + s][p * A::kPitch + d];
+        if (!(fabsf(v) < INFINITY)) v = sum_one<T, D, INV>(wp, yp, H, W, K, st.y, st.x0 + p, d);
         out[(plane0 + (size_t)st.y * W + st.x0 + p) * D + d] = from_f32<T>(scale * v);
-    }
-    if (!again) return;
-#pragma unroll 1
-    for (int i = st.part * kWave + lane; i < kStrip * D; i += SPLIT * kWave) {
-        const int p = i / D, d = i % D;
-        if (st.x0 + p >= W) break;
-        if (!(fabsf(joined(p, d)) < INFINITY))
-            out[(plane0 + (size_t)st.y * W + st.x0 + p) * D + d] = from_f32<T>(scale * sum_one<T, D, INV>(wp, yp, H, W, K, st.y, st.x0 + p, d));
     }
 }
 
