@@ -23,6 +23,8 @@
 // output that is not finite is computed once more from its own window only, which ends as soon as its sum is NaN.  A call on values of NaN then takes (us, finite values in brackets): fused forward 7 x 100 x 134,
 // D = 128, k = 9, f16 654 (123; a thread per output that worked out every logit again: 15400), 4 x 2 x 64 x 64, D = 32,
 // k = 21, bf16 66 (45; 1230); weighted sum there 52 (44; with the whole window 178), inverse 39 (25; 263).
+#include <limits.h>
+
 #include "na2d_kernels.hpp"
 #include "na2d_mfma.hpp"
 #include "na2d_tile.hpp"
@@ -450,9 +452,24 @@ __global__ __launch_bounds__(kStripThreads) void fused_strip_kernel(const T *__r
 
 // Logits and fused forward: four waves to a strip while that is what fills the chip; with enough strips each wave keeps
 // one to itself, the four of a workgroup one below the other: they read nearly the same rows at the same time, and
-// nothing has to be joined (fp32, 56 x 56 maps, us, one wave / four: fused D = 128, k = 7 613 / 716 at 21k strips, 210 / 233
-// at 7k, 125 / 122 at 3.6k, 41 / 23 at 450).  The weighted sums gain nothing from it (D = 64, k = 9: 198 / 196 at 21k).
-int strip_split(const Problem &p) { return (long long)p.planes() * p.H * ((p.W + kStrip - 1) / kStrip) >= 6144 ? 1 : kStripWaves; }
+// nothing has to be joined.  The weighted sums gain nothing from it (D = 64, k = 9: 198 / 196 us at 21k strips).
+// Measured on 14 x 14, 28 x 28, 33 x 70 and 56 x 56 maps, fp32, and f16 where it comes here, time with one wave over time with
+// four.  k = 3 (three rows leave one of four waves idle) and 5, D = 128 at 1.8k strips 0.80 .. 0.91, D = 64 0.93 (fused) and
+// 0.96 .. 1.10 (logits), narrower 0.96 .. 1.18; all of them 0.77 .. 1.10 at 4k, 0.71 .. 0.92 at 40k.  Fused, k = 7 and 9:
+// 1.08 .. 1.22 at 3k, 0.90 .. 1.15 at 4k, 0.90 .. 1.09 at 6k, 0.84 .. 0.96 at 40k; k >= 11: to 1.39, 1.29, 1.29 and, at 12k,
+// 0.93 .. 1.08, but with D = 128 1.27, 1.21 and 0.84 .. 1.08.  Logits beyond k = 5, D = 64 and 128 to k = 13: 1.02 .. 1.22 at 3k,
+// 0.87 .. 1.08 at 6k, 0.88 .. 1.06 at 12k; narrower heads and wider windows 0.84 .. 1.39, 0.94 .. 1.18, 0.97 .. 1.17, and
+// 0.90 .. 1.19 at 40k: four waves throughout.
+enum class StripOp { logits, fused };
+int strip_split(const Problem &p, StripOp op) {
+    const long long strips = (long long)p.planes() * p.H * ((p.W + kStrip - 1) / kStrip);
+    const bool fused = op == StripOp::fused;
+    long long least;   // strips from which on a wave keeps one to itself
+    if (p.K <= 5) least = p.D == 128 || (p.D == 64 && fused) ? 1536 : 3584;
+    else if (fused) least = p.K <= 9 || p.D == 128 ? 6144 : 12288;
+    else least = p.D >= 64 && p.K <= 13 ? 6144 : LLONG_MAX;
+    return strips >= least ? 1 : kStripWaves;
+}
 
 SShape strip_shape(const Problem &p, int split) {
     const int strips = (p.W + kStrip - 1) / kStrip, per = kStripWaves / split, rows = (p.H + per - 1) / per;
@@ -469,9 +486,9 @@ SShape strip_shape(const Problem &p, int split) {
         return hipGetLastError();                                                                                         \
     } while (0)
 // BODY with T, D and SPLIT bound
-#define NA2D_STRIP_DISPATCH(...)                                                                                  \
+#define NA2D_STRIP_DISPATCH(op, ...)                                                                               \
     do {                                                                                                          \
-        const int split = strip_split(p);                                                                         \
+        const int split = strip_split(p, op);                                                                     \
         const SShape g = strip_shape(p, split);                                                                   \
         if (split == 1) { constexpr int SPLIT = 1; NA2D_DISPATCH_T(p.dtype, NA2D_DISPATCH_D(p.D, __VA_ARGS__)); } \
         else { constexpr int SPLIT = kStripWaves; NA2D_DISPATCH_T(p.dtype, NA2D_DISPATCH_D(p.D, __VA_ARGS__)); }  \
@@ -486,7 +503,7 @@ static int qk_row_groups(const Problem &p, int ntiles) {
     return fill < 1 ? 1 : fill < most ? fill : most;
 }
 hipError_t launch_qk_strip(const Problem &p, const void *x, const void *y, const void *rpb, float scale, void *logits, hipStream_t s) {
-    NA2D_STRIP_DISPATCH(NA2D_STRIP_LAUNCH_ROWS(qk_row_groups(p, g.ntiles), (qk_strip_kernel<T, D, SPLIT>), static_cast<const T *>(x),
+    NA2D_STRIP_DISPATCH(StripOp::logits, NA2D_STRIP_LAUNCH_ROWS(qk_row_groups(p, g.ntiles), (qk_strip_kernel<T, D, SPLIT>), static_cast<const T *>(x),
                                                static_cast<const T *>(y), static_cast<const T *>(rpb), scale, static_cast<T *>(logits)));
     return hipErrorInvalidValue;
 }
@@ -509,7 +526,7 @@ hipError_t launch_inverse_strip(const Problem &p, const void *w, const void *x, 
 template <int NBX>
 static hipError_t launch_fused_strip_t(const Problem &p, const void *q, const void *k, const void *v, const void *rpb, float scale,
                                        void *out, float *lse, hipStream_t s) {
-    NA2D_STRIP_DISPATCH(NA2D_STRIP_LAUNCH((fused_strip_kernel<T, D, NBX, SPLIT>), static_cast<const T *>(q), static_cast<const T *>(k),
+    NA2D_STRIP_DISPATCH(StripOp::fused, NA2D_STRIP_LAUNCH((fused_strip_kernel<T, D, NBX, SPLIT>), static_cast<const T *>(q), static_cast<const T *>(k),
                                           static_cast<const T *>(v), static_cast<const T *>(rpb), scale, static_cast<T *>(out), lse));
     return hipErrorInvalidValue;
 }
