@@ -71,7 +71,7 @@ __global__ __launch_bounds__(kTileX *TY) void av_kernel(const T *__restrict__ w,
 
 template <typename T, int K, int D>
 static hipError_t launch_av_t(const Problem &p, const void *w, const void *y, float scale, void *out, hipStream_t s) {
-    if constexpr (K > valu_most_k(ValuOp::weighted_sum, D)) return hipErrorInvalidValue; else {
+    if constexpr (!valu_has_tile(ValuOp::weighted_sum, D, K)) return hipErrorInvalidValue; else {
     static_assert(tile_fits<AvCfg, T, K, D>());
     constexpr int TY = tile_rows<AvCfg, T, K, D>();
     using C = AvCfg<T, K, TY, D>;

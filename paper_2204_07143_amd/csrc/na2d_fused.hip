@@ -94,7 +94,7 @@ __global__ __launch_bounds__(kTileX *TY) void fused_fwd_kernel(const T *__restri
 template <typename T, int K, int D>
 static hipError_t launch_fused_t(const Problem &p, const void *q, const void *k, const void *v, const void *rpb,
                                  float scale, void *out, float *lse, hipStream_t s) {
-    if constexpr (K > valu_most_k(ValuOp::fused, D)) return hipErrorInvalidValue; else {
+    if constexpr (!valu_has_tile(ValuOp::fused, D, K)) return hipErrorInvalidValue; else {
     static_assert(tile_fits<FusedCfg, T, K, D>());
     constexpr int TY = tile_rows<FusedCfg, T, K, D>();
     using C = FusedCfg<T, K, TY, D>;

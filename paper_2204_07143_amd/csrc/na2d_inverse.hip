@@ -65,7 +65,7 @@ __global__ __launch_bounds__(kTileX *TY) void inverse_kernel(const T *__restrict
 template <typename T, int K, int D>
 static hipError_t launch_inverse_t(const Problem &p, const void *w, const void *x, float scale, void *out,
                                    hipStream_t s) {
-    if constexpr (K > valu_most_k(ValuOp::inverse, D)) return hipErrorInvalidValue; else {
+    if constexpr (!valu_has_tile(ValuOp::inverse, D, K)) return hipErrorInvalidValue; else {
     static_assert(tile_fits<InvCfg, T, K, D>());
     constexpr int TY = tile_rows<InvCfg, T, K, D>();
     using C = InvCfg<T, K, TY, D>;

@@ -10,11 +10,14 @@
 
 namespace na2d {
 
+constexpr int kStrip = 16;   // positions of a map row that the strip kernels take together
+
 struct Problem {
     int B, heads, H, W, K, dtype;
     int D = 32;
     int planes() const { return B * heads; }
     size_t queries() const { return (size_t)B * heads * H * W; }
+    long long strips() const { return (long long)planes() * H * ((W + kStrip - 1) / kStrip); }
     int elem_bytes() const { return dtype == NA2D_F32 ? 4 : 2; }
 };
 

@@ -85,7 +85,7 @@ __global__ __launch_bounds__(kTileX *TY) void qk_kernel(const T *__restrict__ x,
 template <typename T, int K, int D>
 static hipError_t launch_qk_t(const Problem &p, const void *x, const void *y, const void *rpb, float scale,
                               void *logits, hipStream_t s) {
-    if constexpr (K > valu_most_k(ValuOp::logits, D)) return hipErrorInvalidValue; else {
+    if constexpr (!valu_has_tile(ValuOp::logits, D, K)) return hipErrorInvalidValue; else {
     static_assert(tile_fits<QkCfg, T, K, D>());
     constexpr int TY = tile_rows<QkCfg, T, K, D>();
     using C = QkCfg<T, K, TY, D>;

@@ -33,7 +33,7 @@ namespace na2d {
 
 namespace {
 
-constexpr int kStrip = 16, kStripWaves = 4, kStripThreads = kStripWaves * kWave;
+constexpr int kStripWaves = 4, kStripThreads = kStripWaves * kWave;
 
 struct SShape {
     int heads, H, W, K, strips, rows, ntiles;   // strips per map row, rows of workgroups per plane
@@ -462,13 +462,12 @@ __global__ __launch_bounds__(kStripThreads) void fused_strip_kernel(const T *__r
 // 0.90 .. 1.19 at 40k: four waves throughout.
 enum class StripOp { logits, fused };
 int strip_split(const Problem &p, StripOp op) {
-    const long long strips = (long long)p.planes() * p.H * ((p.W + kStrip - 1) / kStrip);
     const bool fused = op == StripOp::fused;
     long long least;   // strips from which on a wave keeps one to itself
     if (p.K <= 5) least = p.D == 128 || (p.D == 64 && fused) ? 1536 : 3584;
     else if (fused) least = p.K <= 9 || p.D == 128 ? 6144 : 12288;
     else least = p.D >= 64 && p.K <= 13 ? 6144 : LLONG_MAX;
-    return strips >= least ? 1 : kStripWaves;
+    return p.strips() >= least ? 1 : kStripWaves;
 }
 
 SShape strip_shape(const Problem &p, int split) {

@@ -74,26 +74,45 @@ constexpr bool tile_fits() {
     return Cfg<T, K, tile_rows<Cfg, T, K, D>(), D>::kLdsBytes <= kLdsLimit;
 }
 
-// Which problems run these kernels: fp32 (16 bit is the matrix cores' throughout), windows up to the side below, and
-// enough queries that their large tiles fill the chip.  Measured on 56 x 56 maps, two heads, against the strip kernels
-// (na2d_strip.hip), us, tile / strip: from 50k queries on the tiles win up to these sides (logits D = 32, k = 7:
-// 18 / 27 at 50k and 91 / 123 at 300k queries; weighted sum 17 / 22 and 86 / 109; inverse D = 16, k = 5: 43 / 51 at
-// 300k; fused D = 32, k = 7: 33 / 37 at 50k) and lose beyond them (k = 9: logits 219 / 161, weighted sum 200 / 138,
-// inverse 341 / 115, fused 508 / 215 at 300k; D = 64, k = 9: 348 / 240, 463 / 196, 755 / 175, 1513 / 398; D = 128, k = 3:
-// 220 / 148, 256 / 150, 275 / 147, 1010 / 336); at 25k and fewer the strips are as fast or faster at every side
-// (inverse D = 32, k = 7 at 6k: 37 / 10).
+// Which problems run these kernels: fp32 (16 bit is the matrix cores' throughout), a window that is not too wide for the
+// head dim, and from a number of strips (na2d_strip.hip) on: the strips' time grows with their number, whatever part of
+// their 16 positions lies in the map, while below 1300 or so the chip is idle and a tile's one thread per query waits for
+// LDS.  A row of one strip (W <= 16) takes its window rows in one block of keys instead of two, so the strips that load or
+// store weights win sooner there.  Measured over 54k fp32 problems (D = 16, 32, 64, k = 3 .. 13, 16 maps from 7 x 7 to
+// 200 x 334, 500 to 500k queries); time of the strips over that of the tiles, medians on maps of more than 60k queries:
+//   logits        D = 16, k = 3 .. 9 wide maps 2.0, 1.9, 1.5, 1.0 (k = 11: 0.5); W <= 16: 1.6, 1.4, 1.1, 0.8;
+//                 D = 32, k = 3 .. 7 1.8, 1.6, 1.1 (k = 9: 0.6); 1.3, 1.1, 0.8;  D = 64 1.0, 1.0; 0.7, 0.7
+//   weighted sum  D = 16, k = 3 .. 9 1.6, 1.8, 1.6, 1.3 (k = 11: 0.7); 1.4, 1.2, 0.9, 0.7;
+//                 D = 32, k = 3 .. 7 1.3, 1.4, 1.0 (0.8 .. 1.2); 1.0, 0.9, 0.6;  D = 64 0.8
+//   inverse       D = 16, k = 3 .. 7 1.7, 1.1, 0.7; 1.3, 0.8, 0.5;  D = 32 1.3, 0.9, 0.4; 1.0, 0.6
+//   fused         D = 16, k = 3 .. 13 2.2, 2.0, 1.8, 1.1, 1.0, 0.8;  D = 32 1.6, 1.1, 0.9 (k = 9: 0.4);  D = 64 0.8
+// and they cross where strips are few (same maps): fused 1300 to 1800 strips, logits 1300 to 2000 (W <= 16: 2500), weighted
+// sum 1500 to 2500 (3000 to 4000), inverse 3000; at the widest windows with tiles both ways win in turns up to 6000.  With this
+// rule a problem takes 0.6 % longer on average than with the faster of the two, and 0.2 % of them run more than a tenth slower
+// than in tiles; with one line at 32768 queries for all of them it was 2.2 % and 1.2 % (fused D = 16, k = 5, 458 7 x 7
+// maps 18.8 us where the tiles take 9.3).
 enum class ValuOp { logits, weighted_sum, inverse, fused };
-constexpr int valu_most_k(ValuOp op, int D) {
+constexpr int kNoTiles = 0x7fffffff;
+// strips from which on the tiles are taken
+constexpr int valu_least_strips(ValuOp op, int D, int K, bool one_strip_rows) {
+    const int quick = K <= 5 && D <= 32 ? 1280 : 1536;
     switch (op) {
-        case ValuOp::logits: return D == 16 ? 9 : D == 32 ? 7 : D == 64 ? 5 : 0;
-        case ValuOp::weighted_sum: return D == 16 ? 9 : D == 32 ? 7 : 0;
-        case ValuOp::inverse: return D == 16 ? 5 : D == 32 ? 3 : 0;
-        default: return D == 16 ? 11 : D == 32 ? 7 : 0;
+        case ValuOp::logits:
+            if (one_strip_rows) return K <= (D == 16 ? 7 : D == 32 ? 5 : 0) ? 2560 : kNoTiles;
+            return K <= (D == 16 ? 9 : D == 32 ? 7 : D == 64 ? 5 : 0) ? quick : kNoTiles;
+        case ValuOp::weighted_sum:
+            if (one_strip_rows) return K <= (D == 16 ? 5 : D == 32 ? 3 : 0) ? 3072 : kNoTiles;
+            return K <= (D == 16 ? 9 : D == 32 ? 5 : 0) ? 1536 : D == 32 && K == 7 ? 2560 : kNoTiles;
+        case ValuOp::inverse:
+            if (one_strip_rows) return D == 16 && K == 3 ? 4096 : kNoTiles;
+            return K == 3 && D <= 32 ? 3072 : D == 16 && K == 5 ? 6144 : kNoTiles;
+        default: return K <= (D == 16 ? 9 : D == 32 ? 5 : 0) ? quick : D == 16 && K == 11 ? 2560 : kNoTiles;
     }
 }
-constexpr size_t kValuQueries = 32768;
+constexpr bool valu_has_tile(ValuOp op, int D, int K) { return valu_least_strips(op, D, K, false) != kNoTiles; }
 inline bool valu_preferred(const Problem &p, ValuOp op) {
-    return p.dtype == NA2D_F32 && p.K <= valu_most_k(op, p.D) && p.queries() >= kValuQueries;
+    const int least = valu_least_strips(op, p.D, p.K, p.W <= kStrip);
+    return p.dtype == NA2D_F32 && least != kNoTiles && p.strips() >= least;
 }
 
 }  // namespace na2d
