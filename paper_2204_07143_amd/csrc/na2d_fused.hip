@@ -1,25 +1,26 @@
 // Fused neighbourhood attention forward (arXiv 2204.07143, Eq. 2-4 in one kernel):
 //   out_n = softmax_{a,c}( scale * <q_n, k_{rho(n;a,c)}> + B(n, rho(n;a,c)) ) . v_{rho(n;a,c)}
 // The K*K logits and weights never reach HBM: the h*w*k^2 attention tensor is the memory
-// term of the paper's complexity table (Section 3.3) and fusing removes its round trip.
+// term of the paper's complexity table (Section 3.3) and fusing removes its round trip.  In fp32 on the plain ALU, for the
+// problems of valu_preferred().
 //
 // One workgroup per TY x 16 query tile; the key halo and the value halo of the tile are staged
 // once in LDS.  Each thread owns one query and walks its window row by row with a running
-// max / running sum (online softmax), rescaling its 32 fp32 accumulators once per window row.
+// max / running sum (online softmax), rescaling its D accumulators once per window row.
 #include "na2d_kernels.hpp"
 #include "na2d_tile.hpp"
 #include "na2d_valu_cfg.hpp"
 
 namespace na2d {
 
-template <typename T, int K, int TY, int D>
-__global__ __launch_bounds__(kTileX *TY) void fused_fwd_kernel(const T *__restrict__ q, const T *__restrict__ k,
-                                                                const T *__restrict__ v, const T *__restrict__ rpb,
-                                                                float scale, T *__restrict__ out,
+template <int K, int TY, int D>
+__global__ __launch_bounds__(kTileX *TY) void fused_fwd_kernel(const float *__restrict__ q, const float *__restrict__ k,
+                                                                const float *__restrict__ v, const float *__restrict__ rpb,
+                                                                float scale, float *__restrict__ out,
                                                                 float *__restrict__ lse, int H, int W, int heads,
                                                                 int tiles_x, int tiles_y, int ntiles) {
-    using C = FusedCfg<T, K, TY, D>;
-    constexpr int KBYTES = VecTraits<T, D>::kKeyBytes, STRIDE = VecTraits<T, D>::kKeyStride;
+    using C = FusedCfg<K, TY, D>;
+    constexpr int KBYTES = VecTraits<float, D>::kKeyBytes, STRIDE = VecTraits<float, D>::kKeyStride;
     extern __shared__ __align__(16) char lds[];
     char *khalo = lds;
     char *vhalo = lds + C::kHaloBytes;
@@ -33,21 +34,21 @@ __global__ __launch_bounds__(kTileX *TY) void fused_fwd_kernel(const T *__restri
     const int hy0 = win_start(ty0, H, K), hx0 = win_start(tx0, W, K);
     const size_t plane_q = (size_t)tc.plane * H * W;
 
-    load_halo<T, C::HALO_H, C::HALO_W, C::kThreads, false, D>(reinterpret_cast<const char *>(k) + plane_q * KBYTES,
+    load_halo<C::HALO_H, C::HALO_W, C::kThreads, D>(reinterpret_cast<const char *>(k) + plane_q * KBYTES,
                                                     H, W, hy0, hx0, khalo, tid);
-    load_halo<T, C::HALO_H, C::HALO_W, C::kThreads, false, D>(reinterpret_cast<const char *>(v) + plane_q * KBYTES,
+    load_halo<C::HALO_H, C::HALO_W, C::kThreads, D>(reinterpret_cast<const char *>(v) + plane_q * KBYTES,
                                                     H, W, hy0, hx0, vhalo, tid);
     {
         const int head = tc.plane % heads;
         for (int i = tid; i < C::NB * C::NB; i += C::kThreads)
-            bias[i] = rpb ? to_f32(rpb[(size_t)head * C::NB * C::NB + i]) : 0.f;
+            bias[i] = rpb ? rpb[(size_t)head * C::NB * C::NB + i] : 0.f;
     }
     workgroup_sync();
 
     const int lx = tid % kTileX, ly = tid / kTileX;
     const int qy = ty0 + ly, qx = tx0 + lx;
     if (qy < H && qx < W) {
-        VecN<T, D> qv;
+        VecN<float, D> qv;
         load_vec32(qv, reinterpret_cast<const char *>(q) + (plane_q + (size_t)qy * W + qx) * KBYTES);
         const int sy = win_start(qy, H, K), sx = win_start(qx, W, K);
         const int py = sy - qy + (K - 1), px = sx - qx + (K - 1);
@@ -63,8 +64,8 @@ __global__ __launch_bounds__(kTileX *TY) void fused_fwd_kernel(const T *__restri
             float rowmax = -INFINITY;
 #pragma unroll
             for (int c = 0; c < K; ++c) {
-                VecN<T, D> kv;
-                lds_load_vec32(kv, khalo + hoff + (a * C::HALO_W + c) * STRIDE);
+                VecN<float, D> kv;
+                load_vec32(kv, khalo + hoff + (a * C::HALO_W + c) * STRIDE);
                 s[c] = __builtin_fmaf(scale, dot32(qv, kv), bbase[a * C::NB + c]);
                 rowmax = fmaxf(rowmax, s[c]);
             }
@@ -77,8 +78,8 @@ __global__ __launch_bounds__(kTileX *TY) void fused_fwd_kernel(const T *__restri
             for (int c = 0; c < K; ++c) {
                 const float e = __expf(s[c] - mnew);
                 l += e;
-                VecN<T, D> vv;
-                lds_load_vec32(vv, vhalo + hoff + (a * C::HALO_W + c) * STRIDE);
+                VecN<float, D> vv;
+                load_vec32(vv, vhalo + hoff + (a * C::HALO_W + c) * STRIDE);
                 axpy32(acc, e, vv);
             }
             m = mnew;
@@ -86,26 +87,26 @@ __global__ __launch_bounds__(kTileX *TY) void fused_fwd_kernel(const T *__restri
         const float inv = 1.0f / l;
 #pragma unroll
         for (int d = 0; d < D; ++d) acc[d] *= inv;
-        store_vec32<T>(reinterpret_cast<char *>(out) + (plane_q + (size_t)qy * W + qx) * KBYTES, acc);
+        store_vec32<float>(reinterpret_cast<char *>(out) + (plane_q + (size_t)qy * W + qx) * KBYTES, acc);
         if (lse) lse[plane_q + (size_t)qy * W + qx] = m + __logf(l);
     }
 }
 
-template <typename T, int K, int D>
+template <int K, int D>
 static hipError_t launch_fused_t(const Problem &p, const void *q, const void *k, const void *v, const void *rpb,
                                  float scale, void *out, float *lse, hipStream_t s) {
     if constexpr (!valu_has_tile(ValuOp::fused, D, K)) return hipErrorInvalidValue; else {
-    static_assert(tile_fits<FusedCfg, T, K, D>());
-    constexpr int TY = tile_rows<FusedCfg, T, K, D>();
-    using C = FusedCfg<T, K, TY, D>;
+    static_assert(tile_fits<FusedCfg, K, D>());
+    constexpr int TY = tile_rows<FusedCfg, K, D>();
+    using C = FusedCfg<K, TY, D>;
     const int tiles_x = (p.W + kTileX - 1) / kTileX, tiles_y = (p.H + TY - 1) / TY;
     const int ntiles = tiles_x * tiles_y * p.planes();
-    auto kern = fused_fwd_kernel<T, K, TY, D>;
+    auto kern = fused_fwd_kernel<K, TY, D>;
     static LdsAllowed allowed;
     if (hipError_t e = allow_lds(kern, C::kLdsBytes, allowed); e != hipSuccess) return e;
     hipLaunchKernelGGL(kern, dim3(xcd_padded_grid(ntiles)), dim3(C::kThreads), C::kLdsBytes, s,
-                       static_cast<const T *>(q), static_cast<const T *>(k), static_cast<const T *>(v),
-                       static_cast<const T *>(rpb), scale, static_cast<T *>(out), lse, p.H, p.W, p.heads, tiles_x,
+                       static_cast<const float *>(q), static_cast<const float *>(k), static_cast<const float *>(v),
+                       static_cast<const float *>(rpb), scale, static_cast<float *>(out), lse, p.H, p.W, p.heads, tiles_x,
                        tiles_y, ntiles);
     return hipGetLastError();
     }
@@ -115,7 +116,7 @@ hipError_t launch_fused_fwd(const Problem &p, const void *q, const void *k, cons
                             void *out, float *lse, hipStream_t s) {
     if (fused_mfma_supported(p)) return launch_fused_mfma(p, q, k, v, rpb, scale, out, lse, s);
     if (!valu_preferred(p, ValuOp::fused)) return launch_fused_strip(p, q, k, v, rpb, scale, out, lse, s);
-    NA2D_DISPATCH_K(p.K, NA2D_DISPATCH_D(p.D, return (launch_fused_t<float, K, D>(p, q, k, v, rpb, scale, out, lse, s))));
+    NA2D_DISPATCH_K(p.K, NA2D_DISPATCH_D(p.D, return (launch_fused_t<K, D>(p, q, k, v, rpb, scale, out, lse, s))));
     return hipErrorInvalidValue;
 }
 

@@ -9,7 +9,7 @@ namespace na2d {
 namespace {
 
 struct GShape {
-    int B, heads, H, W, K, D;
+    int H, W, K;
 };
 
 // fp32 value of element i of a head vector / row stored as T
@@ -180,7 +180,7 @@ __global__ __launch_bounds__(256) void indices_generic_kernel(int32_t *key_index
     if (rpb_index) rpb_index[i] = (rpb_start(qy, H, K) + a) * NB + (rpb_start(qx, W, K) + c);
 }
 
-GShape shape_of(const Problem &p) { return GShape{p.B, p.heads, p.H, p.W, p.K, p.D}; }
+GShape shape_of(const Problem &p) { return GShape{p.H, p.W, p.K}; }
 
 }  // namespace
 

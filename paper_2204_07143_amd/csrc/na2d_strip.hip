@@ -20,9 +20,9 @@
 // 2^-40 of the largest below, instead of to 2^-25 (below which a weight left the numerator but not the sum).
 //
 // A masked product is 0 * y.  Where y is not finite that would spoil positions whose window does not hold it, so an
-// output that is not finite is computed once more from its own window only, which ends as soon as its sum is NaN.  A call on values of NaN then takes (us, finite values in brackets): fused forward 7 x 100 x 134,
-// D = 128, k = 9, f16 654 (123; a thread per output that worked out every logit again: 15400), 4 x 2 x 64 x 64, D = 32,
-// k = 21, bf16 66 (45; 1230); weighted sum there 52 (44; with the whole window 178), inverse 39 (25; 263).
+// output that is not finite is computed once more from its own window only, which ends as soon as its sum is NaN.  A call
+// on values of NaN then takes (us, finite values in brackets): fused forward 7 x 100 x 134, D = 128, k = 9, f16 654 (123; a
+// thread per output that worked out every logit again: 15400), 4 x 2 x 64 x 64, D = 32, k = 21, bf16 66 (45; 1230); weighted sum there 52 (44; with the whole window 178), inverse 39 (25; 263).
 #include <limits.h>
 
 #include "na2d_kernels.hpp"
@@ -243,7 +243,6 @@ __global__ __launch_bounds__(kStripThreads) void sum_strip_kernel(const T *__res
     for (int oy = y0 + st.part; oy <= y1; oy += SPLIT) {
         const int a = INV ? st.y - win_start(oy, H, K) : oy - y0;
         const int wrow = INV ? oy * W * KK + a * K : (st.y * W + px) * KK + a * K;
-#pragma unroll 2
         for (int b = 0; b < nblk; ++b) {
             T wt[1][4];
             int off[4];

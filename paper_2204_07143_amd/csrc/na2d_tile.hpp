@@ -38,15 +38,14 @@ __device__ __forceinline__ TileCoord decode_tile(int t, int tiles_x, int tiles_y
 }
 
 // Stage the keys (oy + ry, ox + rx), ry < ROWS, rx < COLS, of one plane into LDS with the padded
-// per-key stride.  The origin may be negative or the halo may reach beyond the map ("virtual"
-// coordinates): positions outside the map are zero-filled when ZERO is set and skipped
-// otherwise (no window ever reads them).  Loads are issued in batches of up to 4 per thread
-// before the matching LDS stores, so a thread keeps its share of the halo in flight at once.
-template <typename T, int ROWS, int COLS, int NTHREADS, bool ZERO = false, int D = kHeadDim>
+// per-key stride (fp32).  The halo may reach beyond the map: positions outside it are skipped (no
+// window ever reads them).  Loads are issued in batches of up to 4 per thread before the matching
+// LDS stores, so a thread keeps its share of the halo in flight at once.
+template <int ROWS, int COLS, int NTHREADS, int D>
 __device__ __forceinline__ void load_halo(const char *plane_base, int H, int W, int oy, int ox, char *lds, int tid) {
-    constexpr int KBYTES = VecTraits<T, D>::kKeyBytes;
+    constexpr int KBYTES = VecTraits<float, D>::kKeyBytes;
     constexpr int CPK = KBYTES / 16;
-    constexpr int STRIDE = VecTraits<T, D>::kKeyStride;
+    constexpr int STRIDE = VecTraits<float, D>::kKeyStride;
     constexpr int TOTAL = ROWS * COLS * CPK;
     constexpr int NITER = (TOTAL + NTHREADS - 1) / NTHREADS;
     constexpr int BATCH = 4;
@@ -71,18 +70,13 @@ __device__ __forceinline__ void load_halo(const char *plane_base, int H, int W, 
                 const bool in_map = y >= 0 && y < H && x >= 0 && x < W;
                 if (in_tile && in_map)
                     v[u] = *reinterpret_cast<const u32x4 *>(plane_base + ((size_t)y * W + x) * KBYTES + c * 16);
-                if (in_tile && (in_map || ZERO)) dst[u] = (ry * COLS + rx) * STRIDE + c * 16;
+                if (in_tile && in_map) dst[u] = (ry * COLS + rx) * STRIDE + c * 16;
             }
         }
 #pragma unroll
         for (int u = 0; u < BATCH; ++u)
             if (dst[u] >= 0) *reinterpret_cast<u32x4 *>(lds + dst[u]) = v[u];
     }
-}
-
-template <typename T, int D>
-__device__ __forceinline__ void lds_load_vec32(VecN<T, D> &v, const char *lds_key) {
-    load_vec32(v, lds_key);
 }
 
 // compile-time integer passed as a lambda argument
