@@ -332,6 +332,7 @@ FULL = [
     ("segmentation_like", True),
     ("stage1_head_dim_64", True),   # head dims other than 32
     ("stage1_head_dim_16", True),
+    ("nat_tiny_stage1_f32", True),  # fp32: tiles for all but the inverse sums, which run in strips
 ]
 
 
@@ -362,8 +363,8 @@ def test_config5_kernel_size_sweep_fwd_bwd(oracle, k):
 @pytest.mark.parametrize("dtype", ["f32", "f16", "bf16"])
 @pytest.mark.parametrize("D,k", [(16, 3), (16, 7), (16, 13), (64, 5), (64, 9), (64, 11), (64, 13), (128, 3), (128, 5), (128, 7), (128, 9), (128, 11), (128, 13)])
 def test_generic_head_dims(oracle, dtype, D, k):
-    # (the fp32 tiles of the largest head dims do not fit the LDS for larger windows: (64, 13) and (128, 9) in fp32,
-    # and (128, 13) in any type, run the kernels that take the window side at run time)
+    # (fp32 problems this small run in strips at every head dim; in 16 bit the inverse sums of D >= 64 do from k = 9 on, the
+    # weighted sums of D = 128, its fused forward from k = 9 and its logits at k = 13)
     p = synth.Problem(2, 2, 19, 22, D, k, dtype)
     prob = na.problem(p.B, p.heads, p.H, p.W, D, k, synth.TORCH_DTYPES[dtype])
     assert na.na2d_validate_problem(prob) == 0

@@ -1,4 +1,5 @@
-"""The rule by which a 2D fp32 problem takes the plain-ALU tiles or the strips: every stage on both sides of it, against the oracle."""
+"""Both sides of the rules by which a 2D problem takes the plain-ALU tiles (fp32), strips shared by four waves or strips of
+one wave each, and the instances that only wide windows reach: every stage, forward and backward, against the oracle."""
 from __future__ import annotations
 
 import pytest
@@ -48,3 +49,37 @@ def test_fp32_rows_shorter_than_a_strip():
             times.append(a.elapsed_time(b))
         return min(times)
     assert best(458, 7, 7) <= 1.25 * best(28, 28, 28)   # (strips / strips 1.5, tiles / tiles 0.95)
+
+
+# The strips (planes x H x ceil(W / 16)) from which on a wave keeps one to itself, in the order of the rule: k <= 5 at
+# D = 128, then the fused forward at D = 64, then its logits on rows of one strip (what has no tiles there); the fused forward to k = 9 and at D = 128; the logits at
+# D >= 64; the fused forward beyond k = 9.  H is no multiple of the four strips of a workgroup; W leaves 0, 1, 2 or 15
+# positions in a row's last strip.
+@pytest.mark.parametrize("H,W,D,k,dtype,strips", [
+    (5, 16, 128, 3, "f32", 1536), (6, 17, 64, 5, "f32", 1536), (7, 15, 64, 5, "f32", 3584),
+    (13, 17, 32, 9, "f32", 6144), (14, 31, 128, 9, "f32", 6144), (15, 16, 128, 9, "f16", 6144),
+    (13, 33, 128, 13, "f16", 6144), (14, 18, 128, 13, "bf16", 6144), (11, 17, 64, 11, "f32", 6144),
+    (17, 18, 32, 15, "bf16", 12288), (15, 31, 16, 15, "f16", 12288), (15, 16, 64, 15, "f32", 12288),
+])
+@pytest.mark.parametrize("above", [False, True])
+def test_strips_of_four_waves_and_of_one(oracle, H, W, D, k, dtype, strips, above):
+    per_plane = H * ((W + 15) // 16)
+    p = synth.Problem((strips + per_plane - 1) // per_plane - (0 if above else 1), 1, H, W, D, k, dtype)
+    run_all(oracle, p, seed=H * W + k, planes=_some_planes(p), rpb_std=0.5)
+
+
+@pytest.mark.parametrize("B", [46, 47])   # 32338 and 33041 queries; from 32768 on 128 channels are summed slice by slice
+@pytest.mark.parametrize("k,dtype", [(3, "f16"), (5, "bf16"), (7, "f16"), (9, "bf16"), (13, "f16")])
+def test_four_slices_and_strips(oracle, k, dtype, B):
+    p = synth.Problem(B, 1, 19, 37, 128, k, dtype)
+    run_all(oracle, p, seed=B + k, planes=_some_planes(p), rpb_std=0.5, e2e_unfused=False)
+
+
+@pytest.mark.parametrize("dtype", ["f32", "f16", "bf16"])
+@pytest.mark.parametrize("heads,H,W,D,k", [
+    (2, 15, 16, 32, 15), (2, 17, 33, 16, 17), (2, 19, 19, 64, 19), (2, 13, 31, 128, 13),   # the strips' edges
+    # as many positions as the windows reach, a strip more, and the softmax instances of k = 23 .. 31, 33 .. 45, 47 .. 63
+    (2, 23, 47, 32, 23), (2, 31, 33, 16, 31), (1, 34, 49, 32, 33), (1, 45, 47, 64, 45), (1, 63, 65, 16, 63), (1, 25, 40, 128, 25),
+])
+def test_wide_windows_forward_and_backward(oracle, heads, H, W, D, k, dtype):
+    run_all(oracle, synth.Problem(1, heads, H, W, D, k, dtype), seed=H * W + D + k, rpb_std=0.5)
