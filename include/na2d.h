@@ -34,20 +34,21 @@
  *    2^-14 <= |b| <= 65504, a larger one counts as +-65504 and a smaller one is rounded to a
  *    multiple of 2^-24.
  *  - Supported: odd k from 3 to 63 with k <= min(H, W); k = H = W is the self-attention limit
- *    (Section 3.1).  k in {3, 5, 7, 9, 11, 13}, the sizes the paper tunes for (Appendix A,
- *    "Tiled Neighborhood Attention"), run the tiled kernels described below; k >= 15 runs plain
- *    kernels with the window side as a run-time argument (every dtype, every head dim below;
- *    correct and deterministic, not tuned).  Head dims
- *    D in {16, 32, 64, 128}.  D = 32 (every NAT variant, Section 3.2) runs the matrix-core
- *    kernels in the 16-bit types; so do the weighted sums (av, grad-q, grad-v, grad-k) for
- *    D = 64 and 128, the logits, grad-a and the fused forward for D = 64 (for D = 128 the
- *    logits and grad-a with k <= 11, the fused forward with k <= 7), and all
- *    of these for D = 16 (a 16-channel head rides in the lower half of the 32-channel
- *    kernels); the softmax kernels and grad-b do not depend on D; the rest runs tiled
- *    plain-ALU kernels while their tiles fit the
- *    160 KB LDS (every k for D = 16 and for D = 64 in the 16-bit types, k <= 9 for D = 128 in
- *    the 16-bit types and for D = 64 in fp32, k = 3 for D = 128 in fp32) and the run-time-k
- *    kernels otherwise.
+ *    (Section 3.1).  Head dims D in {16, 32, 64, 128}.  The contractions run on three families of kernels:
+ *      - 16-bit types with k in {3, 5, 7, 9, 11, 13}, the sizes the paper tunes for (Appendix A, "Tiled
+ *        Neighborhood Attention"): matrix-core kernels built for one window side each, at D = 32 (every NAT
+ *        variant, Section 3.2), at D = 16 (a 16-channel head rides in the lower half of the 32-channel kernels)
+ *        and, in slices of 32 channels, at D = 64 and 128 where the strips below are not faster;
+ *      - everything else, i.e. k >= 15, fp32, and of the large head dims grad-v and grad-k from k = 9 on and, at
+ *        D = 128, the fused forward from k = 9 on, the logits and grad-a at k = 13 and the weighted sums (av,
+ *        grad-q, grad-v, grad-k) of small calls: matrix-core kernels that take strips of 16 positions of a map row, with
+ *        the window side as a run-time argument;
+ *      - fp32 calls of narrow windows and D <= 64 with enough queries: tiled plain-ALU kernels.
+ *    The softmax kernels and grad-b do not depend on D; beyond k = 13 they take k as a run-time argument too.
+ *  - Results are bitwise reproducible: the same call gives the same bits again.  Which kernel runs, and so the
+ *    order in which sums are added, depends on the sizes of the problem, B and heads among them: in fp32, at
+ *    D = 128 and in the fused forward with k >= 15 one batch item's results can differ in their last bits
+ *    between calls of different batch size.
  *  - Inputs are expected to be finite.  The matrix-core kernels multiply values of
  *    neighbouring positions (up to a tile's query rectangle away) by zero weights instead of
  *    skipping them, so a NaN or an infinity in q, k, v, dout or a weight tensor can turn

@@ -21,7 +21,8 @@ struct Problem {
     int elem_bytes() const { return dtype == NA2D_F32 ? 4 : 2; }
 };
 
-// Window sides: 3..13 (odd) run the tuned kernels, 15..63 (odd) the run-time-K kernels of na2d_generic.hip.
+// Window sides: 3..13 (odd) have kernels of a fixed window side; 15..63 (odd) run the strips of na2d_strip.hip and the
+// run-time-K softmax, bias gradient and index tables of na2d_generic.hip.
 constexpr int kMaxTunedK = 13, kMaxGenericK = 63;
 bool untuned_window(const Problem &p);   // k beyond the tuned sides (what the kernels that do not depend on D ask)
 // contractions on the matrix cores in strips: any window side, head dim and storage type (na2d_strip.hip)
@@ -43,7 +44,7 @@ hipError_t launch_qk(const Problem &p, const void *x, const void *y, const void 
 // the same contraction on the matrix cores (f16 / bf16 only)
 hipError_t launch_qk_mfma(const Problem &p, const void *x, const void *y, const void *rpb, float scale, void *logits,
                           hipStream_t s);
-// D = 32, and for k <= 7 also D = 64 (two 32-channel slices accumulated in the matrix cores)
+// D = 16, 32, 64 and, to k = 11, 128 (32-channel slices accumulated in the matrix cores)
 bool qk_mfma_supported(const Problem &p);
 // grad-a fused with the softmax backward (f16 / bf16, K <= 7): ds from attn, dout and v
 bool bwd_fused_supported(const Problem &p);
@@ -51,7 +52,7 @@ hipError_t launch_bwd_fused(const Problem &p, const void *attn, const void *dout
 // out = scale * sum_window w * y          (AV, and grad-q with w = ds, y = k)
 hipError_t launch_av(const Problem &p, const void *w, const void *y, float scale, void *out, hipStream_t s);
 hipError_t launch_av_mfma(const Problem &p, const void *w, const void *y, float scale, void *out, hipStream_t s);
-// the matrix-core kernel takes any multiple of 32 channels, one launch per 32-channel slice
+// the matrix-core kernel takes D = 16 and any multiple of 32 channels, one launch per 32-channel slice
 bool av_mfma_supported(const Problem &p);
 // out_j = scale * sum_{inverse neighbourhood} w[i, slot(i, j)] * x_i   (grad-v, grad-k)
 hipError_t launch_inverse(const Problem &p, const void *w, const void *x, float scale, void *out, hipStream_t s);
@@ -95,7 +96,7 @@ hipError_t launch_fbwd_kv(const Problem &p, const void *q, const void *k, const 
                           const float *lse2, const float *delta, const void *dout, void *dk, void *dv, hipStream_t s);
 hipError_t launch_fused_fwd(const Problem &p, const void *q, const void *k, const void *v, const void *rpb, float scale,
                             void *out, float *lse, hipStream_t s);
-// D = 32, and for k <= 7 also D = 64 (two 32-channel slices)
+// D = 16, 32, 64 and, to k = 7, 128 (32-channel slices)
 bool fused_mfma_supported(const Problem &p);
 hipError_t launch_fused_mfma(const Problem &p, const void *q, const void *k, const void *v, const void *rpb, float scale,
                              void *out, float *lse, hipStream_t s);
@@ -103,7 +104,7 @@ hipError_t launch_indices(const Problem &p, int32_t *key_index, int32_t *rpb_ind
 
 }  // namespace na2d
 
-// Expands BODY once with `T` bound to the storage type and `K` to the window side.
+// Expands BODY once with `K` bound to the window side.
 #define NA2D_DISPATCH_K(kval, ...)                                   \
     switch (kval) {                                                  \
         case 3: { constexpr int K = 3; __VA_ARGS__; } break;         \
@@ -114,7 +115,7 @@ hipError_t launch_indices(const Problem &p, int32_t *key_index, int32_t *rpb_ind
         case 13: { constexpr int K = 13; __VA_ARGS__; } break;       \
         default: return hipErrorInvalidValue;                        \
     }
-// Head dims the plain-ALU kernels are built for (the matrix-core kernels serve D = 32 only).
+// Expands BODY once with `D` bound to the head dim (strips and the fp32 tiles).
 #define NA2D_DISPATCH_D(dval, ...)                                    \
     switch (dval) {                                                   \
         case 16: { constexpr int D = 16; __VA_ARGS__; } break;        \
