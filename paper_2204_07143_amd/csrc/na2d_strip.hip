@@ -520,18 +520,36 @@ hipError_t launch_qk_strip(const Problem &p, const void *x, const void *y, const
     return hipErrorInvalidValue;
 }
 
-hipError_t launch_av_strip(const Problem &p, const void *w, const void *y, float scale, void *out, hipStream_t s) {
-    const SShape g = strip_shape(p, kStripWaves);
-    NA2D_DISPATCH_T(p.dtype, NA2D_DISPATCH_D(p.D, NA2D_STRIP_LAUNCH((sum_strip_kernel<T, D, false, kStripWaves>), static_cast<const T *>(w),
-                                          static_cast<const T *>(y), scale, static_cast<T *>(out))));
+template <typename T, int D, bool INV>
+static hipError_t launch_sum_strip_t(const Problem &p, const T *w, const T *y, float scale, T *out, hipStream_t s) {
+    // A launch holds fewer than 2^32 threads; beyond, the runtime takes the number modulo 2^32 and reports nothing.  With a
+    // workgroup to a strip, 50 million positions on maps of three columns are more than that (fp32, D = 32, k = 3), so the planes
+    // go in as many launches as it takes: one in any other call.  (Logits and fused forward stay below 0.4 of the limit for every
+    // problem that comes here: what they store is wider, or a wave keeps a strip to itself.)
+    constexpr int kMost = (int)((1ll << 32) / kStripThreads) - 2 * kNumXcd;
+    SShape g = strip_shape(p, kStripWaves);
+    const int planes = p.planes(), per_plane = g.ntiles / planes, step = kMost / per_plane;
+    if (step < 1) return hipErrorInvalidConfiguration;   // (a plane below 2^31 bytes of fp32 has at most 11.2 million strips)
+    for (int first = 0; first < planes; first += step) {
+        g.ntiles = (planes - first < step ? planes - first : step) * per_plane;
+        const size_t q0 = (size_t)first * p.H * p.W;
+        hipLaunchKernelGGL((sum_strip_kernel<T, D, INV, kStripWaves>), dim3(xcd_padded_grid(g.ntiles)), dim3(kStripThreads), 0, s,
+                           w + q0 * p.K * p.K, y + q0 * D, scale, out + q0 * D, g);
+        if (hipError_t e = hipGetLastError(); e != hipSuccess) return e;
+    }
+    return hipSuccess;
+}
+template <bool INV>
+static hipError_t launch_sum_strip(const Problem &p, const void *w, const void *y, float scale, void *out, hipStream_t s) {
+    NA2D_DISPATCH_T(p.dtype, NA2D_DISPATCH_D(p.D, return (launch_sum_strip_t<T, D, INV>(p, static_cast<const T *>(w),
+                                          static_cast<const T *>(y), scale, static_cast<T *>(out), s))));
     return hipErrorInvalidValue;
 }
-
+hipError_t launch_av_strip(const Problem &p, const void *w, const void *y, float scale, void *out, hipStream_t s) {
+    return launch_sum_strip<false>(p, w, y, scale, out, s);
+}
 hipError_t launch_inverse_strip(const Problem &p, const void *w, const void *x, float scale, void *out, hipStream_t s) {
-    const SShape g = strip_shape(p, kStripWaves);
-    NA2D_DISPATCH_T(p.dtype, NA2D_DISPATCH_D(p.D, NA2D_STRIP_LAUNCH((sum_strip_kernel<T, D, true, kStripWaves>), static_cast<const T *>(w),
-                                          static_cast<const T *>(x), scale, static_cast<T *>(out))));
-    return hipErrorInvalidValue;
+    return launch_sum_strip<true>(p, w, x, scale, out, s);
 }
 
 // blocks of keys at a time: two while the strip's windows then fit one pass (K <= 17), three for wider ones

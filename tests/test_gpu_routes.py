@@ -83,3 +83,20 @@ def test_four_slices_and_strips(oracle, k, dtype, B):
 ])
 def test_wide_windows_forward_and_backward(oracle, heads, H, W, D, k, dtype):
     run_all(oracle, synth.Problem(1, heads, H, W, D, k, dtype), seed=H * W + D + k, rpb_std=0.5)
+
+
+def test_more_strips_than_a_launch_holds():
+    # 16.8 million strips (more than 2^32 threads) on 3 x 3 maps, where every query sees every key: slot = key
+    B, D = 5592500, 32
+    gen = torch.Generator(device="cuda").manual_seed(7)
+    attn = torch.rand(B, 1, 3, 3, 9, device="cuda", generator=gen)
+    dout = torch.rand(B, 1, 3, 3, D, device="cuda", generator=gen)
+    dv = torch.full_like(dout, float("nan"))
+    na.na2d_av_bwd_v(attn, dout, 3, dv)
+    assert not torch.isnan(dv).any()
+    for first in (0, B // 2, 5592380, B - 64):   # (a launch holds 5592400 planes)
+        part = slice(first, first + 64)
+        a, x = attn[part].double().cpu().view(64, 9, 9), dout[part].double().cpu().view(64, 9, D)
+        want = (a.unsqueeze(-1) * x.unsqueeze(2)).sum(1)
+        # nine products of numbers below 1, added in fp32
+        torch.testing.assert_close(dv[part].double().cpu().view(64, 9, D), want, rtol=0, atol=9 * 9 * 2.0 ** -24)
