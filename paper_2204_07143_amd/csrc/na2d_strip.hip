@@ -7,11 +7,13 @@
 // operand, i.e. one small dense product of 16 strip positions with blocks of 16 partner positions, masked by the
 // window.  Nothing but the waves' partial sums is staged in LDS, so neither the window nor the head dim is limited
 // by it: partner positions come from global memory (neighbouring strips re-read them out of L2), the weights are
-// read or written in place.  What bounds it is the number of load / store instructions per block of 16 x 16
-// products (a 4 x 4 patch would have fewer masked products, but its weights do not lie in one run per row).
+// read or written in place (a 4 x 4 patch would have fewer masked products, but its weights do not lie in one run per row).
+// What bounds it, by counters at 4 x 2 x 64 x 64 x 32, k = 21, bf16 (107520 blocks of 16 x 16 products): the logits (41 us)
+// their 430k stores, two bytes a lane, 59 % of the wave cycles waiting; the weighted sums (44 us, inverse 26) 8 loads per block, 67
+// and 54 % waiting; the fused forward (50 us) its 188 vector instructions per block, 33 us at four cycles each, 20 % waiting.
 //
-// Measured against one thread per output element (4 x 2 x 64 x 64 x 32, k = 21, bf16, forward and backward of the
-// fused operator, together with the steps of na2d_generic.hip): 3099 -> 288 us.
+// Measured against one thread per output element (that shape, forward and backward of the fused operator, together with
+// the steps of na2d_generic.hip): 3099 -> 268 us.
 //
 // Weights that are stored are products of 16-bit (or fp32) operands summed in fp32: exact products as on the plain
 // ALU.  The fused forward keeps its weights in fp32; in 16 bit they enter as a high and a low half, two products instead
@@ -507,8 +509,8 @@ SShape strip_shape(const Problem &p, int split) {
     } while (0)
 
 // Workgroups per strip for the logits, whose window rows need no joining: one window row to a wave at least, and no more
-// than 2048 workgroups (fp32: 1024).  A small call is bound by the chain of loads and stores along a wave's rows (us, one
-// group / at most 512 / 1024 / 2048 workgroups: bf16, D = 16, k = 17, 2 x 33 x 17 8.6 / 5.2 / 4.4 / 4.4, 10 x 33 x 17
+// than 2048 workgroups (fp32: 1024).  A small call is bound by the chain of loads and stores along a wave's rows (us, with the
+// bias entries still behind the stores, which is about 0.6 of each figure of 4 to 6; one group / at most 512 / 1024 / 2048 workgroups: bf16, D = 16, k = 17, 2 x 33 x 17 8.6 / 5.2 / 4.4 / 4.4, 10 x 33 x 17
 // 11.5 / 11.5 / 11.6 / 7.6; fp32, D = 128, k = 5, 16 x 28 x 28 16.4 / 16.4 / 16.5 / 17.6).
 static int qk_row_groups(const Problem &p, int ntiles) {
     const int most = (p.K + kStripWaves - 1) / kStripWaves, fill = 4096 / p.elem_bytes() / ntiles;
