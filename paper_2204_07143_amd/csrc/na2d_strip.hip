@@ -509,9 +509,9 @@ SShape strip_shape(const Problem &p, int split) {
     } while (0)
 
 // Workgroups per strip for the logits, whose window rows need no joining: one window row to a wave at least, and no more
-// than 2048 workgroups (fp32: 1024).  A small call is bound by the chain of loads and stores along a wave's rows (us, with the
-// bias entries still behind the stores, which is about 0.6 of each figure of 4 to 6; one group / at most 512 / 1024 / 2048 workgroups: bf16, D = 16, k = 17, 2 x 33 x 17 8.6 / 5.2 / 4.4 / 4.4, 10 x 33 x 17
-// 11.5 / 11.5 / 11.6 / 7.6; fp32, D = 128, k = 5, 16 x 28 x 28 16.4 / 16.4 / 16.5 / 17.6).
+// than 2048 workgroups (fp32: 1024).  A small call is bound by the chain of loads and stores along a wave's rows (us, one
+// group / at most 512 / 1024 / 2048 workgroups, measured while the bias entries were still loaded behind the stores: bf16, D = 16,
+// k = 17, 2 x 33 x 17 8.6 / 5.2 / 4.4 / 4.4, 10 x 33 x 17 11.5 / 11.5 / 11.6 / 7.6; fp32, D = 128, k = 5, 16 x 28 x 28 16.4 / 16.4 / 16.5 / 17.6).
 static int qk_row_groups(const Problem &p, int ntiles) {
     const int most = (p.K + kStripWaves - 1) / kStripWaves, fill = 4096 / p.elem_bytes() / ntiles;
     return fill < 1 ? 1 : fill < most ? fill : most;
