@@ -203,6 +203,21 @@ int na2d_fused_bwd(const na2d_problem *p, const void *q, const void *k, const vo
  * weights and runs the unfused steps, a negative na2d_status for an invalid problem.  Host only. */
 int na2d_fused_bwd_is_fused(const na2d_problem *p);
 
+/*
+ * The same gradients, from the same arguments, where na2d_fused_bwd would recompute the k*k weights into memory (wider
+ * windows, larger head dims, fp32): two kernels over 4 x 4 patches, query patches (dq, delta) and key patches (dk, dv and,
+ * if d_rpb != NULL, the bias gradient), whatever the window side.  Products, weights' exponentials and sums are fp32; in 16 bit
+ * P dP, P and dS are rounded to the storage type where they enter a sum.  d_rpb is summed per workgroup in integers whose
+ * scale follows the largest |dS| a workgroup can meet in a plane (a term is off by at most 2^-24 of that, in fp32 2^-51), so the
+ * results are bitwise reproducible; cells that a dS that is not finite belongs to are NaN.
+ * na2d_direct_bwd_workspace_bytes(p) says how many bytes `workspace` must hold (no initialisation needed); 0 means that the
+ * call refuses the problem (NA2D_ERR_WORKSPACE): it is invalid, or na2d_fused_bwd is the faster one or the only one.
+ */
+int na2d_direct_bwd(const na2d_problem *p, const void *q, const void *k, const void *v, const void *rpb,
+                    float scale, const float *lse, const void *dout, void *dq, void *dk, void *dv, float *d_rpb,
+                    void *workspace, size_t workspace_bytes, void *stream);
+size_t na2d_direct_bwd_workspace_bytes(const na2d_problem *p);
+
 /* Bytes of device workspace the given call needs for this problem (0 on invalid problems). */
 size_t na2d_workspace_bytes(const na2d_problem *p, int kind);
 

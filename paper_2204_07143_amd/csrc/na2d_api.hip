@@ -235,13 +235,12 @@ int na2d_fused_bwd_is_fused(const na2d_problem *p) {
 static size_t fused_bwd_delta_bytes(const Problem &pr) { return (pr.queries() * sizeof(float) + 255) & ~(size_t)255; }
 static size_t fused_bwd_attn_bytes(const Problem &pr) { return (pr.queries() * pr.K * pr.K * pr.elem_bytes() + 255) & ~(size_t)255; }
 
-int na2d_fused_bwd(const na2d_problem *p, const void *q, const void *k, const void *v, const void *rpb, float scale,
-                   const float *lse, const void *dout, void *dq, void *dk, void *dv, float *d_rpb, void *workspace,
-                   size_t workspace_bytes, void *stream) {
-    NA2D_CHECK_PROBLEM(p);
+// What na2d_fused_bwd and na2d_direct_bwd ask of their arguments.
+static int check_fused_bwd(const na2d_problem *p, const void *q, const void *k, const void *v, const void *rpb, const float *lse, const void *dout,
+                           void *dq, void *dk, void *dv, float *d_rpb, void *workspace, size_t workspace_bytes, size_t needed) {
     NA2D_REQUIRE(q); NA2D_REQUIRE(k); NA2D_REQUIRE(v); NA2D_OPTIONAL(rpb); NA2D_REQUIRE(lse); NA2D_REQUIRE(dout);
     NA2D_REQUIRE(dq); NA2D_REQUIRE(dk); NA2D_REQUIRE(dv); NA2D_OPTIONAL(d_rpb);
-    if (!workspace || misaligned(workspace) || workspace_bytes < na2d_workspace_bytes(p, NA2D_WS_FUSED_BWD))
+    if (!workspace || misaligned(workspace) || workspace_bytes < needed)
         return NA2D_ERR_WORKSPACE;
     const void *ins[6] = {q, k, v, rpb, lse, dout};
     void *outs[4] = {dq, dk, dv, d_rpb};
@@ -249,6 +248,14 @@ int na2d_fused_bwd(const na2d_problem *p, const void *q, const void *k, const vo
         for (const void *i : ins)
             if (o && o == i) return NA2D_ERR_ALIAS;
     if (dq == dk || dq == dv || dk == dv || d_rpb == dq || d_rpb == dk || d_rpb == dv) return NA2D_ERR_ALIAS;
+    return NA2D_OK;
+}
+
+int na2d_fused_bwd(const na2d_problem *p, const void *q, const void *k, const void *v, const void *rpb, float scale,
+                   const float *lse, const void *dout, void *dq, void *dk, void *dv, float *d_rpb, void *workspace,
+                   size_t workspace_bytes, void *stream) {
+    NA2D_CHECK_PROBLEM(p);
+    if (int st = check_fused_bwd(p, q, k, v, rpb, lse, dout, dq, dk, dv, d_rpb, workspace, workspace_bytes, na2d_workspace_bytes(p, NA2D_WS_FUSED_BWD)); st != NA2D_OK) return st;
     const Problem pr = to_problem(p);
     hipStream_t s = static_cast<hipStream_t>(stream);
     char *ws = static_cast<char *>(workspace);
@@ -269,6 +276,22 @@ int na2d_fused_bwd(const na2d_problem *p, const void *q, const void *k, const vo
     if (launch_qk(pr, q, k, rpb, scale, attn, s) != hipSuccess) return from_hip(hipErrorLaunchFailure);
     if (launch_softmax(pr, attn, attn, s) != hipSuccess) return from_hip(hipErrorLaunchFailure);
     return run_bwd(pr, q, k, v, attn, dout, scale, dq, dk, dv, d_rpb, ws + fused_bwd_attn_bytes(pr), s);
+}
+
+size_t na2d_direct_bwd_workspace_bytes(const na2d_problem *p) {
+    if (validate(p) != NA2D_OK) return 0;
+    const Problem pr = to_problem(p);
+    return patch_bwd_supported(pr) ? patch_bwd_workspace_bytes(pr) : 0;
+}
+
+int na2d_direct_bwd(const na2d_problem *p, const void *q, const void *k, const void *v, const void *rpb, float scale,
+                    const float *lse, const void *dout, void *dq, void *dk, void *dv, float *d_rpb, void *workspace,
+                    size_t workspace_bytes, void *stream) {
+    NA2D_CHECK_PROBLEM(p);
+    const size_t needed = na2d_direct_bwd_workspace_bytes(p);
+    if (int st = check_fused_bwd(p, q, k, v, rpb, lse, dout, dq, dk, dv, d_rpb, workspace, workspace_bytes, needed); st != NA2D_OK) return st;
+    if (needed == 0) return NA2D_ERR_WORKSPACE;
+    return from_hip(launch_patch_bwd(to_problem(p), q, k, v, rpb, scale, lse, dout, dq, dk, dv, d_rpb, workspace, static_cast<hipStream_t>(stream)));
 }
 
 int na2d_debug_indices(const na2d_problem *p, int32_t *key_index, int32_t *rpb_index, void *stream) {

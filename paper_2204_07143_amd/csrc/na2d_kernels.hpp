@@ -94,6 +94,11 @@ hipError_t launch_fbwd_q(const Problem &p, const void *q, const void *k, const v
                          hipStream_t s);
 hipError_t launch_fbwd_kv(const Problem &p, const void *q, const void *k, const void *v, const void *rpb, float scale,
                           const float *lse2, const float *delta, const void *dout, void *dk, void *dv, hipStream_t s);
+// the backward without k * k tensors of the problems that fused_bwd_supported() does not take (na2d_patch_bwd.hip)
+bool patch_bwd_supported(const Problem &p);
+size_t patch_bwd_workspace_bytes(const Problem &p);
+hipError_t launch_patch_bwd(const Problem &p, const void *q, const void *k, const void *v, const void *rpb, float scale,
+                            const float *lse, const void *dout, void *dq, void *dk, void *dv, float *d_rpb, void *workspace, hipStream_t s);
 hipError_t launch_fused_fwd(const Problem &p, const void *q, const void *k, const void *v, const void *rpb, float scale,
                             void *out, float *lse, hipStream_t s);
 // D = 16, 32, 64 and, to k = 7, 128 (32-channel slices)

@@ -1,0 +1,829 @@
+// Backward of neighbourhood attention without the k * k tensors, for any window side, head dim and storage type
+// (arXiv 2204.07143: Eq. 2-4 differentiated): what na2d_fused_bwd.hip is for narrow windows of 16 and 32 channels in 16 bit,
+// with the window side as a run-time argument and the rows of the streamed operand passing through LDS four at a time, so that
+// neither the window nor the head dim is limited by a whole halo.
+//
+//   P[i, j] = exp(scale <q_i, k_j> + B(i, j) - lse_i)   dP[i, j] = <dout_i, v_j>   delta_i = sum_j P dP   dS = P (dP - delta)
+//
+// Part 1 keeps 4 x 4 query patches and streams keys and values once: delta and
+//   dq_i = scale sum_j dS k_j = scale (sum_j P dP k_j - delta_i sum_j P k_j)
+// so that delta need not be known before the sums (a second sweep would evaluate both products again).  In 16 bit P dP and P are
+// rounded to the storage type, as the stored dp and the stored weights of the unfused steps are.
+// Part 2 keeps 4 x 4 key patches and streams queries, upstream gradients, lse and delta: dv_j = sum_i P dout_i,
+// dk_j = scale sum_i dS q_i, and the bias gradient: every dS is added to its cell of a table in LDS, as an integer (additions of
+// integers commute: the result is bitwise reproducible).  Their scale follows a bound of the |dS|
+// that the workgroup meets in a plane (part 1 leaves one per query patch); see BiasSums.
+//
+// A masked product is 0 * x: where x is not finite it would spoil positions whose window does not hold it, so results that are not
+// finite are computed once more from their own window only.
+// Measured (us, both parts and the bias gradient, in brackets the steps before: weights recomputed into memory and the unfused backward):
+// 64 x 2 x 56 x 56 queries, fp16, 32 channels, k = 13 82 + 149 + 6 (455); fp32, k = 7 189 + 216 + 6 (700); fp16, 64 channels (one head), k = 7 47 + 66 + 8
+// (165); 4 x 2 x 64 x 64, bf16, k = 21 17 + 44 + 5 (220).  By counters at the first shape part 1 issues 60 vector instructions per
+// 16 x 16 products, of which a block needs 40, and waits 43 % of its wave cycles: its four waves per SIMD do not cover the chain from LDS through
+// two products, the exponential and two more.  Part 2 adds the integer additions in LDS (43 us with a bias, 4 copies of the table).  fp32 is
+// nearer to its matrix cores: 32 instructions of 32 cycles per block, 94 us a part.
+#include <limits.h>
+
+#include "na2d_kernels.hpp"
+#include "na2d_patch.hpp"
+
+namespace na2d {
+
+namespace {
+
+constexpr float kLog2e = 1.4426950408889634f, kLog2eLow = (float)(1.4426950408889634 - (double)kLog2e);
+// What part 1 leaves of a query for part 2: the base of its exponents and delta.  In 16 bit the base is log2(e) lse.  In fp32 it is 0
+// (log2(e) lse rounded to a whole number where that is beyond +-32), and the inverse of the sum of the exponentials to that base
+// follows (and a word of padding): P = exp2(t - base) / sum has neither the rounding of lse nor that of the difference in it.
+template <typename T> constexpr bool kNormalised = sizeof(T) == 4;
+template <typename T> constexpr int kQueryWords = kNormalised<T> ? 4 : 2;
+
+// waves per SIMD the kernels are built for: two workgroups per compute unit where 128 registers hold a wave
+template <typename T, int D> constexpr int kPatchOcc = D * sizeof(T) <= 128 ? 4 : 2;
+
+// blocks of a row whose loads are in flight together: two where the registers hold them
+template <typename T, int D> constexpr int kAtOnceQ = (sizeof(T) == 2 && D <= 32) || kPatchOcc<T, D> == 2 ? 2 : 1;
+template <typename T, int D> constexpr int kAtOnceKv = (sizeof(T) == 2 && D <= 32) || kPatchOcc<T, D> == 2 ? 2 : 1;
+
+// fp32 dot product of two head vectors in memory
+template <typename T, int D> __device__ __forceinline__ float dot_memory(const T *a, const T *b) {
+    float acc = 0.f;
+#pragma unroll
+    for (int d = 0; d < D; d += 8) {
+        VecN<T, 8> x, y;
+        load_vec32(x, a + d);
+        load_vec32(y, b + d);
+        acc += dot32(x, y);
+    }
+    return acc;
+}
+__device__ __forceinline__ float wave_sum(float x) {
+#pragma unroll
+    for (int m = 1; m < kWave; m *= 2) x += __shfl_xor(x, m);
+    return x;
+}
+__device__ __forceinline__ uint32_t wave_max(uint32_t x) {
+#pragma unroll
+    for (int m = 1; m < kWave; m *= 2) {
+        const uint32_t o = (uint32_t)__shfl_xor((int)x, m);
+        x = x > o ? x : o;
+    }
+    return x;
+}
+// |dS| = P |dP - delta| is at most this, given the largest P |dP| and P of the window; as bits (NaN above all others, where delta is not finite)
+__device__ __forceinline__ uint32_t ds_bound(float most_pdp, float most_p, float delta) {
+    return __float_as_uint(fabsf(__builtin_fmaf(most_p, fabsf(delta), most_pdp)));
+}
+__device__ __forceinline__ float lane_value(float x, int lane) {
+    return __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, x), lane));
+}
+
+// Weight and upstream product of one (query, key) pair, from memory.
+template <typename T, int D> struct PlanePtrs {
+    const T *q, *k, *v, *dout, *rpb;   // of the plane; the head's bias table or null
+};
+template <typename T, int D>
+__device__ __forceinline__ void pair_weight(const PlanePtrs<T, D> &m, const PatchShape &g, float scale, int iy, int ix, int y, int x,
+                                            float base, float &p, float &dp) {
+    const size_t i = ((size_t)iy * g.W + ix) * D, j = ((size_t)y * g.W + x) * D;
+    float s = scale * dot_memory<T, D>(m.q + i, m.k + j);
+    if (m.rpb) s += to_f32(m.rpb[(y - iy + g.K - 1) * (2 * g.K - 1) + x - ix + g.K - 1]);
+    p = __builtin_amdgcn_exp2f(__builtin_fmaf(s, kLog2e, -base));
+    dp = dot_memory<T, D>(m.dout + i, m.v + j);
+}
+
+// delta, dq and the bound of one query from its own window (a wave works on it: 64 window slots at a time, then a channel to
+// a lane).  A delta that is NaN makes every dS NaN, so the sums need not be formed.
+template <typename T, int D>
+__device__ __forceinline__ float query_once_more(const PlanePtrs<T, D> &m, const PatchShape &g, float scale, int iy, int ix, float base, T *dq, uint32_t &bound, float &inv) {
+    const int lane = threadIdx.x % kWave, K = g.K, KK = K * K, sy = win_start(iy, g.H, K), sx = win_start(ix, g.W, K);
+    float delta = 0.f, z = 0.f;
+    uint32_t most = 0, most_p = 0;
+    for (int first = 0; first < KK; first += kWave) {
+        const int slot = first + lane < KK ? first + lane : KK - 1, a = slot / K, c = slot - a * K;
+        float p, dp;
+        pair_weight(m, g, scale, iy, ix, sy + a, sx + c, base, p, dp);
+        if (first + lane < KK) {
+            delta = __builtin_fmaf(p, dp, delta);
+            z += p;
+            const uint32_t bits = __float_as_uint(fabsf(p * dp)), bits_p = __float_as_uint(p);
+            most = most > bits ? most : bits;
+            most_p = most_p > bits_p ? most_p : bits_p;
+        }
+        if (!kNormalised<T> && __ballot(delta != delta)) break;   // (fp32: part 2 needs the whole sum of the weights)
+    }
+    inv = kNormalised<T> ? 1.f / wave_sum(z) : 1.f;
+    delta = wave_sum(delta) * inv;
+    bound = ds_bound(__uint_as_float(wave_max(most)) * inv, __uint_as_float(wave_max(most_p)) * inv, delta);
+    float acc[(D + kWave - 1) / kWave] = {};
+    for (int first = 0; first < KK && delta == delta; first += kWave) {
+        const int slot = first + lane < KK ? first + lane : KK - 1, a = slot / K, c = slot - a * K;
+        float p, dp;
+        pair_weight(m, g, scale, iy, ix, sy + a, sx + c, base, p, dp);
+        const float ds = p * inv * (dp - delta);
+        const int n = KK - first < kWave ? KK - first : kWave;
+        for (int t = 0; t < n; ++t) {
+            const float w = lane_value(ds, t);
+            const int ta = (first + t) / K, tc = first + t - ta * K;
+#pragma unroll
+            for (int u = 0; u < (D + kWave - 1) / kWave; ++u) {
+                const int d = u * kWave + lane < D ? u * kWave + lane : D - 1;
+                acc[u] = __builtin_fmaf(w, to_f32(m.k[((size_t)(sy + ta) * g.W + sx + tc) * D + d]), acc[u]);
+            }
+        }
+    }
+#pragma unroll
+    for (int u = 0; u < (D + kWave - 1) / kWave; ++u)
+        if (u * kWave + lane < D) dq[((size_t)iy * g.W + ix) * D + u * kWave + lane] = from_f32<T>(delta == delta ? scale * acc[u] : NAN);
+    return delta;
+}
+
+// dk and dv of one key from the queries that see it, likewise.
+template <typename T, int D>
+__device__ __forceinline__ void key_once_more(const PlanePtrs<T, D> &m, const PatchShape &g, float scale, int y, int x, const float *ld, T *dk, T *dv) {
+    const int lane = threadIdx.x % kWave, K = g.K;
+    const int y0 = inv_first(y, g.H, K), x0 = inv_first(x, g.W, K), nx = inv_last(x, g.W, K) - x0 + 1, total = (inv_last(y, g.H, K) - y0 + 1) * nx;
+    constexpr int NU = (D + kWave - 1) / kWave;
+    float ak[NU] = {}, av[NU] = {};
+    for (int first = 0; first < total; first += kWave) {
+        const int s = first + lane < total ? first + lane : total - 1, iy = y0 + s / nx, ix = x0 + s % nx;
+        const float *of = ld + kQueryWords<T> * ((size_t)iy * g.W + ix);
+        float p, dp;
+        pair_weight(m, g, scale, iy, ix, y, x, of[0], p, dp);
+        if constexpr (kNormalised<T>) p *= of[2];
+        const float delta = of[1];
+        const float ds = p * (dp - delta);
+        const int n = total - first < kWave ? total - first : kWave;
+        for (int t = 0; t < n; ++t) {
+            const float wp = lane_value(p, t), ws = lane_value(ds, t);
+            const size_t i = ((size_t)(y0 + (first + t) / nx) * g.W + x0 + (first + t) % nx) * D;
+#pragma unroll
+            for (int u = 0; u < NU; ++u) {
+                const int d = u * kWave + lane < D ? u * kWave + lane : D - 1;
+                av[u] = __builtin_fmaf(wp, to_f32(m.dout[i + d]), av[u]);
+                ak[u] = __builtin_fmaf(ws, to_f32(m.q[i + d]), ak[u]);
+            }
+        }
+        bool open = false;   // a sum that is NaN stays NaN
+#pragma unroll
+        for (int u = 0; u < NU; ++u) open |= ak[u] == ak[u] || av[u] == av[u];
+        if (__ballot(open) == 0) break;
+    }
+#pragma unroll
+    for (int u = 0; u < NU; ++u)
+        if (u * kWave + lane < D) {
+            const size_t o = ((size_t)y * g.W + x) * D + u * kWave + lane;
+            dk[o] = from_f32<T>(scale * ak[u]);
+            dv[o] = from_f32<T>(av[u]);
+        }
+}
+
+// exp2(scale2 s + bias - base), bias in units of log2
+template <typename T> __device__ __forceinline__ float exponential(float s, float scale2, float scale2_low, float bias, float base) {
+    if constexpr (kNormalised<T>) return __builtin_amdgcn_exp2f(__builtin_fmaf(scale2, s, __builtin_fmaf(scale2_low, s, bias)) - base);
+    return __builtin_amdgcn_exp2f(__builtin_fmaf(scale2, s, bias - base));
+}
+template <typename T> __device__ __forceinline__ void store_query(float *ld, unsigned n, float base, float delta, float inv) {
+    if constexpr (kNormalised<T>) *reinterpret_cast<f32x4 *>(ld + 4 * n) = f32x4{base, delta, inv, 0.f};
+    else *reinterpret_cast<f32x2 *>(ld + 2 * n) = f32x2{base, delta};
+}
+
+// the lane's index, worked out anew
+__device__ __forceinline__ int own_lane_index() {
+    int zero = 0;
+    asm volatile("" : "+v"(zero));
+    return __builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, zero));
+}
+
+// ---- part 1 ------------------------------------------------------------------------------------------------------------
+// ld: kQueryWords of every query, for part 2; bound: per query patch what no |dS| exceeds (bits of a float; null
+// where no bias gradient is wanted).
+template <typename T, int D>
+__global__ __launch_bounds__(kPatchThreads, (kPatchOcc<T, D>)) void patch_bwd_q_kernel(
+    const T *__restrict__ q, const T *__restrict__ k, const T *__restrict__ v, const T *__restrict__ rpb, float scale,
+    const float *__restrict__ lse, const T *__restrict__ dout, T *__restrict__ dq, float *__restrict__ ld, uint32_t *__restrict__ bound, PatchShape g) {
+    using CV = ChanVec<T, D>;
+    using Op = PosOp<T, D>;
+    constexpr int POSB = Op::POSB;
+    extern __shared__ __align__(16) char lds[];
+    const int wg = xcd_contiguous_block(blockIdx.x, gridDim.x);
+    if (wg >= g.units * g.splits) return;
+    const WorkItem work = decode_work(wg, g.heads, g.tiles_y, g.splits, g.gd);
+    const int head = work.head, K = g.K, H = g.H, W = g.W, NB = 2 * K - 1, pitch = bias_pitch(K);
+    const int tid = threadIdx.x, lane = tid % kWave, wave = __builtin_amdgcn_readfirstlane(tid / kWave);
+    const int j = lane & 15, gr = lane >> 4;
+    const int bias0 = dynamic_lds(lds), img0 = bias0 + bias_rows(K, g.with_bias) * pitch * 4;
+    const int img_bytes = 4 * g.rw * POSB, stage_bytes = 2 * img_bytes;
+
+    // a 4 x 4 patch per wave, 32 x 4, 16 x 8 or 8 x 16 positions per workgroup
+    const int lg = g.lg_cols, tw = 4 << lg, th = 32 >> lg, ty0 = work.ty * th, tx0 = work.tx * tw;
+    const int ty1 = ty0 + th - 1 < H - 1 ? ty0 + th - 1 : H - 1;
+    const int ry0 = win_start(ty0, H, K), cx0 = win_start(tx0, W, K);            // first key row and column of the tile
+    const int nsteps = (win_start(ty1, H, K) + K - ry0 + 3) >> 2;
+    const int sy0 = ty0 + 4 * (wave >> lg), px0 = tx0 + 4 * (lg == 2 ? patch_of_wave(wave) : wave & ((1 << lg) - 1));   // this wave's patch
+    const bool active = sy0 < H && px0 < W;
+    const int sy3 = sy0 + 3 < H - 1 ? sy0 + 3 : H - 1, px3 = px0 + 3 < W - 1 ? px0 + 3 : W - 1;
+    const int pyc = sy0 < H ? sy0 : H - 1, pxc = px0 < W ? px0 : W - 1;
+    const int s_lo = (win_start(pyc, H, K) - ry0) >> 2, s_hi = (win_start(sy3, H, K) + K - 1 - ry0) >> 2;
+    const int ox = win_start(pxc, W, K), nbx = (win_start(px3, W, K) + K - ox + 3) >> 2;
+    const int qy = sy0 + (j >> 2), qx = px0 + (j & 3);
+    const bool q_ok = qy < H && qx < W;
+    const int iy = qy < H ? qy : H - 1, ix = qx < W ? qx : W - 1;
+    const int wy = win_start(iy, H, K), wx = win_start(ix, W, K) - ox;           // window: first row, first column from ox
+    const int aoff = ((j >> 2) * g.rw + (ox - cx0) + (j & 3)) * POSB + gr * CV::kLaneBytes;
+    const int toff = Op::lane_offset(lane, g.rw) + (ox - cx0) * POSB;
+    const int clear_lo = win_start(px3, W, K) - ox;   // columns [clear_lo, K) are in the window of every query of the patch
+    const int u0 = ry0 + gr - iy + K - 1, boff = bias0 + (ox - ix + K - 1 + kBiasPad) * 4;
+    const int no_row = boff + (bias_rows(K, g.with_bias) - 1) * pitch * 4;
+    const size_t plane_px = (size_t)H * W;
+    const int qlin = iy * W + ix;
+    const float scale2 = scale * kLog2e, scale2_low = __builtin_fmaf(scale, kLog2e, -scale2) + scale * kLog2eLow;
+
+    auto issue = [&](int b, int s, int par) {
+        const size_t off = ((size_t)b * g.heads + head) * plane_px * POSB;
+        const int img = img0 + par * stage_bytes;
+        issue_rows<POSB>(reinterpret_cast<const char *>(k) + off, reinterpret_cast<const char *>(v) + off, H, W, ry0 + 4 * s, cx0, g.rw, img, img_bytes, wave, lane);
+    };
+    if (work.b_begin < work.b_end) issue(work.b_begin, 0, 0);
+    stage_bias<T>(g.with_bias ? rpb + (size_t)head * NB * NB : nullptr, K, g.by_pitch, bias0, tid);
+
+    int par = 0;
+    for (int b = work.b_begin; b < work.b_end; ++b) {
+        const size_t plane = (size_t)b * g.heads + head;
+        CV qo, dO;
+        const size_t plane_off = plane * plane_px * POSB;
+        // (a plane is smaller than 2^31 bytes: one 32-bit offset per lane for all tensors)
+        qo.load(reinterpret_cast<const char *>(q) + plane_off + (unsigned)(qlin * POSB + gr * CV::kLaneBytes));
+        dO.load(reinterpret_cast<const char *>(dout) + plane_off + (unsigned)(qlin * POSB + gr * CV::kLaneBytes));
+        float base = (lse + plane * plane_px)[(unsigned)qlin] * kLog2e;
+        if constexpr (kNormalised<T>) base = fabsf(base) < 32.f ? 0.f : __builtin_rintf(base);
+        settle(qo);
+        settle(dO);
+        // sum of P dP k and of P k.  fp32: of a row of blocks at a time, then of the rows (one chain of K * K additions is off by twice as much)
+        PosSum<T, D> sa, sp, row_a, row_p;
+        sa.clear();
+        sp.clear();
+        if constexpr (sizeof(T) == 4) {
+            row_a.clear();
+            row_p.clear();
+        }
+        float delta = 0.f, most = 0.f, most_p = 0.f, z = 0.f;
+        // N blocks of a row of blocks, from block column bx on
+        auto blocks = [&](auto n, int img, int brow, int bx) {
+            constexpr int N = decltype(n)::value;
+            const int ka0 = img + aoff + bx * 4 * POSB, va0 = ka0 + img_bytes, kt0 = img + toff + bx * 4 * POSB, b0 = brow + bx * 16;
+            CV ka[N], va[N];
+            f32x4 sv[N], dp[N];
+            Op kt[N];
+            Weights4<T> wa[N], wp[N];
+            float bias[N][4];
+#pragma unroll
+            for (int i = 0; i < N; ++i) {
+                ka[i].load_lds(ka0 + i * 4 * POSB);
+                va[i].load_lds(va0 + i * 4 * POSB);
+#pragma unroll
+                for (int r = 0; r < 4; ++r) bias[i][r] = *lds_ptr<float>(b0 + i * 16 + r * 4);
+                // columns outside the window: weight 0 (decided here: where a branch came
+                // between a product and the first use of its result, the compiler left out the wait that the use needs)
+                if (4 * (bx + i) < clear_lo || 4 * (bx + i) + 4 > K) {
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) bias[i][r] = (unsigned)(4 * (bx + i) + r - wx) < (unsigned)K ? bias[i][r] : -INFINITY;
+                }
+            }
+#pragma unroll
+            for (int i = 0; i < N; ++i) {
+                sv[i] = chan_dot<T, D>(ka[i], qo);
+                dp[i] = chan_dot<T, D>(va[i], dO);
+            }
+#pragma unroll
+            for (int i = 0; i < N; ++i) {
+                kt[i].load_lds(kt0 + i * 4 * POSB);
+                float p[4], w[4];
+#pragma unroll
+                for (int r = 0; r < 4; ++r) p[r] = exponential<T>(sv[i][r], scale2, scale2_low, bias[i][r], base);
+#pragma unroll
+                for (int r = 0; r < 4; ++r) {
+                    w[r] = p[r] * dp[i][r];
+                    delta += w[r];
+                    if constexpr (kNormalised<T>) z += p[r];
+                    most = fmaxf(most, fabsf(w[r]));
+                    most_p = fmaxf(most_p, p[r]);
+                }
+                wa[i] = Weights4<T>(w);
+                wp[i] = Weights4<T>(p);
+            }
+            auto &ta = sizeof(T) == 4 ? row_a : sa, &tp = sizeof(T) == 4 ? row_p : sp;
+            if constexpr (N == 2) {
+                ta.add2(kt[0], wa[0], kt[1], wa[1]);
+                tp.add2(kt[0], wp[0], kt[1], wp[1]);
+            } else {
+                ta.add(kt[0], wa[0]);
+                tp.add(kt[0], wp[0]);
+            }
+        };
+        for (int s = 0; s < nsteps; ++s) {
+            wait_global_loads();
+            workgroup_sync();   // this step's rows have landed for every wave, and nobody still reads the other buffer
+            const int img = img0 + par * stage_bytes;
+            const bool last = s + 1 == nsteps;
+            if (g.nstage == 2) {
+                par ^= 1;
+                if (!last || b + 1 < work.b_end) issue(last ? b + 1 : b, last ? 0 : s + 1, par);
+            }
+            if (active && s >= s_lo && s <= s_hi) {
+                const int u = u0 + 4 * s, uc = u < 0 ? 0 : (u < NB - 1 ? u : NB - 1);
+                const bool rowok = (unsigned)(ry0 + 4 * s + gr - wy) < (unsigned)K;
+                const int brow = rowok ? boff + (g.with_bias ? uc * pitch * 4 : 0) : no_row;
+                constexpr int kAtOnce = kAtOnceQ<T, D>;
+                int bx = 0;
+                for (; bx + kAtOnce <= nbx; bx += kAtOnce) blocks(IntC<kAtOnce>{}, img, brow, bx);
+                if (kAtOnce > 1 && bx < nbx) blocks(IntC<1>{}, img, brow, bx);
+                if constexpr (sizeof(T) == 4) {
+                    sa.take(row_a);
+                    sp.take(row_p);
+                }
+            }
+            if (g.nstage == 1 && (!last || b + 1 < work.b_end)) {
+                workgroup_sync();   // nobody still reads the rows
+                issue(last ? b + 1 : b, last ? 0 : s + 1, 0);
+            }
+        }
+        if (!active) continue;
+        delta += __shfl_xor(delta, 16);
+        delta += __shfl_xor(delta, 32);
+        float inv = 1.f;
+        if constexpr (kNormalised<T>) {
+            z += __shfl_xor(z, 16);
+            z += __shfl_xor(z, 32);
+            inv = 1.f / z;
+            delta *= inv;
+        }
+#pragma unroll
+        for (int i = 0; i < Op::NA; ++i) sa.acc[i] -= delta * sp.acc[i];
+        const float odd = __builtin_fmaf(delta, 0.f, sa.not_finite());   // NaN where something is not finite
+        uint32_t bits = ds_bound(most * inv, most_p * inv, delta);
+        if (q_ok) {
+            sa.store(reinterpret_cast<char *>(dq) + plane_off, (unsigned)(qlin * POSB), gr, scale * inv);
+            if (gr == 0) store_query<T>(ld + plane * plane_px * kQueryWords<T>, (unsigned)qlin, base, delta, inv);
+        }
+        unsigned long long again = __ballot(odd != odd);
+        if (again) {
+            wait_global_loads();   // (the stores above come first)
+            PatchShape gc = g;     // (nothing of this is prepared outside of the branch)
+            asm volatile("" : "+s"(gc.H), "+s"(gc.W), "+s"(gc.K));
+            unsigned cols = (unsigned)((again | (again >> 16) | (again >> 32) | (again >> 48)) & 0xffffu);
+            if ((cols >> j) & 1u) bits = 0;
+            const PlanePtrs<T, D> m{q + plane * plane_px * D, k + plane * plane_px * D, v + plane * plane_px * D, dout + plane * plane_px * D,
+                                    g.with_bias ? rpb + (size_t)head * NB * NB : nullptr};
+            for (; cols; cols &= cols - 1) {
+                const int c = __builtin_ctz(cols), cy = sy0 + (c >> 2), cx = px0 + (c & 3);
+                if (cy >= H || cx >= W) continue;
+                uint32_t own;
+                float own_inv;
+                const float b2 = lane_value(base, c);
+                const float dl = query_once_more<T, D>(m, gc, scale, cy, cx, b2, dq + plane * plane_px * D, own, own_inv);
+                if (lane == 0) store_query<T>(ld + plane * plane_px * kQueryWords<T>, (unsigned)(cy * W + cx), b2, dl, own_inv);
+                bits = bits > own ? bits : own;
+            }
+        }
+        if (bound != nullptr) {
+            bits = wave_max(bits);
+            if (lane == 0) bound[(plane * ((H + 3) >> 2) + (sy0 >> 2)) * ((W + 3) >> 2) + (px0 >> 2)] = bits;
+        }
+    }
+}
+
+// ---- part 2 ------------------------------------------------------------------------------------------------------------
+// The bias gradient in LDS.  A plane's dS are added as integers dS 2^(kBits - E), 2^E bounding every |dS| that the workgroup
+// meets in the plane (additions of integers commute, so waves may share the table); then the integers are added to the floating-point
+// sums and cleared.  At most 128 keys of a tile add to a cell.  16 bit: 32-bit integers, rounded at 2^-24 of the bound, where
+// the stored ds of the unfused steps is rounded at 2^-12 (fp16) of itself; fp32: 64-bit integers, rounded at 2^-51.
+template <typename T> struct BiasSums {
+    typedef int Int;
+    typedef float Sum;
+    static constexpr int kIntBytes = 4, kSumBytes = 4, kBits = 23;
+    __device__ static __forceinline__ void add(int addr, float ds, float up) {   // (a NaN counts as 0)
+        __hip_atomic_fetch_add(lds_ptr<int>(addr), (int)__builtin_rintf(ds * up), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    }
+};
+template <> struct BiasSums<float> {
+    typedef long long Int;
+    typedef double Sum;
+    static constexpr int kIntBytes = 8, kSumBytes = 8, kBits = 50;
+    __device__ static __forceinline__ void add(int addr, float ds, float up) {
+        constexpr double kBig = 6755399441055744.0;   // 1.5 * 2^52: its mantissa's last bit counts 1
+        const double x = __builtin_fma((double)(ds == ds ? ds : 0.f), (double)up, kBig);
+        __hip_atomic_fetch_add(lds_ptr<long long>(addr), __builtin_bit_cast(long long, x) - __builtin_bit_cast(long long, kBig), __ATOMIC_RELAXED,
+                               __HIP_MEMORY_SCOPE_WORKGROUP);
+    }
+};
+// Lanes of a wave whose offsets agree meet in one cell (row g of the block, row jy of the patch: jy - g), so each lane group has a
+// copy of the integers of its own where the LDS holds four (copy g: the rows of its products start in banks that the other
+// groups' do not use).
+__host__ __device__ constexpr int int_words(int cells) { return (cells + 63) / 64 * 64 + 64; }   // per copy (integers)
+__device__ __forceinline__ int copy_offset(int g, int cells) { return g * int_words(cells) + 8 * g + (g & 1) * 4 + (g >> 1) * 32; }
+__host__ __device__ constexpr int flag_bytes(int cells) { return (cells + 127) / 128 * 16; }
+template <typename T> __host__ __device__ constexpr int table_bytes(int cells, int copies) { return (copies > 1 ? copies * int_words(cells) : cells) * BiasSums<T>::kIntBytes; }
+template <typename T> __host__ __device__ constexpr int dbias_bytes(int cells, int copies) { return cells * BiasSums<T>::kSumBytes + table_bytes<T>(cells, copies) + flag_bytes(cells); }
+
+template <typename T, int D>
+__global__ __launch_bounds__(kPatchThreads, (kPatchOcc<T, D>)) void patch_bwd_kv_kernel(
+    const T *__restrict__ q, const T *__restrict__ k, const T *__restrict__ v, const T *__restrict__ rpb, float scale,
+    const float *__restrict__ ld, const uint32_t *__restrict__ bound, const T *__restrict__ dout, T *__restrict__ dk, T *__restrict__ dv,
+    float *__restrict__ partial, PatchShape g) {
+    using CV = ChanVec<T, D>;
+    using Op = PosOp<T, D>;
+    constexpr int POSB = Op::POSB, QB = kQueryWords<T> * 4;
+    extern __shared__ __align__(16) char lds[];
+    const int wg = xcd_contiguous_block(blockIdx.x, gridDim.x);
+    if (wg >= g.units * g.splits) return;
+    const WorkItem work = decode_work(wg, g.heads, g.tiles_y, g.splits, g.gd);
+    const int head = work.head, K = g.K, H = g.H, W = g.W, NB = 2 * K - 1, pitch = bias_pitch(K);
+    const int tid = threadIdx.x, lane = tid % kWave, wave = __builtin_amdgcn_readfirstlane(tid / kWave);
+    const int j = lane & 15, gr = lane >> 4;
+    using Table = BiasSums<T>;
+    const int cells = NB * pitch, sums0 = dynamic_lds(lds), table0 = sums0 + (g.with_dbias ? cells * Table::kSumBytes : 0);
+    const int flags0 = table0 + (g.with_dbias ? table_bytes<T>(cells, g.copies) : 0), bias0 = flags0 + (g.with_dbias ? flag_bytes(cells) : 0);
+    const int img0 = bias0 + bias_rows(K, g.with_bias) * pitch * 4;
+    const int img_bytes = 4 * g.rw * POSB, stage_bytes = 2 * img_bytes + 4 * g.rw * QB;
+
+    const int lg = g.lg_cols, tw = 4 << lg, th = 32 >> lg, ty0 = work.ty * th, tx0 = work.tx * tw;
+    const int ty1 = ty0 + th - 1 < H - 1 ? ty0 + th - 1 : H - 1, tx1 = tx0 + tw - 1 < W - 1 ? tx0 + tw - 1 : W - 1;
+    const int ry0 = inv_first(ty0, H, K), cx0 = inv_first(tx0, W, K);            // first query row and column of the tile
+    const int ry1 = inv_last(ty1, H, K), cx1 = inv_last(tx1, W, K);
+    const int nsteps = (ry1 - ry0 + 4) >> 2;
+    const int sy0 = ty0 + 4 * (wave >> lg), px0 = tx0 + 4 * (lg == 2 ? patch_of_wave(wave) : wave & ((1 << lg) - 1));   // this wave's patch
+    const bool active = sy0 < H && px0 < W;
+    const int sy3 = sy0 + 3 < H - 1 ? sy0 + 3 : H - 1, px3 = px0 + 3 < W - 1 ? px0 + 3 : W - 1;
+    const int pyc = sy0 < H ? sy0 : H - 1, pxc = px0 < W ? px0 : W - 1;
+    const int s_lo = (inv_first(pyc, H, K) - ry0) >> 2, s_hi = (inv_last(sy3, H, K) - ry0) >> 2;
+    const int ox = inv_first(pxc, W, K), nbx = (inv_last(px3, W, K) - ox + 4) >> 2;
+    const int ky = sy0 + (j >> 2), kx = px0 + (j & 3);
+    const bool key_ok = ky < H && kx < W;
+    const int jx = kx < W ? kx : W - 1;
+    // the columns of the queries that see the lane's key: the first (from ox) and their number
+    const int fx = inv_first(jx, W, K) - ox, nx = inv_last(jx, W, K) - ox - fx + 1;
+    const int aoff = ((j >> 2) * g.rw + (ox - cx0) + (j & 3)) * POSB + gr * CV::kLaneBytes;
+    const int toff = Op::lane_offset(lane, g.rw) + (ox - cx0) * POSB;
+    // columns [clear_lo, clear_hi) see every key of the patch
+    const int clear_lo = inv_first(px3, W, K) - ox, clear_hi = inv_last(pxc, W, K) + 1 - ox, no_row = bias_rows(K, g.with_bias) - 1;
+    const int loff = (gr * g.rw + (ox - cx0)) * QB;
+    const int v0 = jx - ox + K - 1 + kBiasPad;     // (the cell falls with the query's row and column)
+    const size_t plane_px = (size_t)H * W;
+    const auto own_lane = own_lane_index;   // (recomputed where it is used: a register less in the inner loop)
+    const auto key_offset = [&](int lv) {
+        const int y = sy0 + ((lv & 15) >> 2), x = px0 + (lv & 3);
+        return (unsigned)(((y < H - 1 ? y : H - 1) * W + (x < W - 1 ? x : W - 1)) * POSB);
+    };
+    const int table_lane = table0 + (g.copies > 1 ? copy_offset(gr, cells) * Table::kIntBytes : 0);
+    const float scale2 = scale * kLog2e, scale2_low = __builtin_fmaf(scale, kLog2e, -scale2) + scale * kLog2eLow;
+
+    auto issue = [&](int b, int s, int par) {
+        const size_t px = ((size_t)b * g.heads + head) * plane_px;
+        const int img = img0 + par * stage_bytes;
+        issue_rows<POSB>(reinterpret_cast<const char *>(q) + px * POSB, reinterpret_cast<const char *>(dout) + px * POSB, H, W, ry0 + 4 * s, cx0, g.rw, img, img_bytes, wave, lane);
+        int w = wave;
+        asm volatile("" : "+s"(w));
+        const int row = w & 3, y = ry0 + 4 * s + row < H - 1 ? ry0 + 4 * s + row : H - 1;
+        constexpr int LB = kNormalised<T> ? 16 : 4, PER = QB / LB;   // bytes a lane loads, lanes per query
+        for (int s0 = (w >> 2) * kWave; s0 < PER * g.rw; s0 += (kPatchWaves / 4) * kWave) {
+            const int c = s0 + lane;
+            int x = cx0 + c / PER;
+            x = x < W - 1 ? x : W - 1;
+            const unsigned off = (unsigned)((y * W + x) * QB + (c % PER) * LB);
+            const int dst = img + 2 * img_bytes + row * g.rw * QB + s0 * LB;
+            if (c < PER * g.rw) {
+                if constexpr (LB == 16) global_to_lds_16(reinterpret_cast<const char *>(ld) + px * QB, off, dst);
+                else global_to_lds_4(reinterpret_cast<const char *>(ld) + px * QB, off, dst);
+            }
+        }
+    };
+    if (work.b_begin < work.b_end) issue(work.b_begin, 0, 0);
+    stage_bias<T>(g.with_bias ? rpb + (size_t)head * NB * NB : nullptr, K, g.by_pitch, bias0, tid);
+    if (g.with_dbias)
+        for (int i = sums0 + tid * 16; i < bias0; i += kPatchThreads * 16) *lds_ptr<u32x4>(i) = u32x4{0u, 0u, 0u, 0u};
+
+    int par = 0;
+    for (int b = work.b_begin; b < work.b_end; ++b) {
+        const size_t plane = (size_t)b * g.heads + head;
+        CV ko, vo;
+        const size_t plane_off = plane * plane_px * POSB;
+        const int lv0 = own_lane();
+        const unsigned key_lane = key_offset(lv0) + (lv0 >> 4) * CV::kLaneBytes;
+        ko.load(reinterpret_cast<const char *>(k) + plane_off + key_lane);
+        vo.load(reinterpret_cast<const char *>(v) + plane_off + key_lane);
+        settle(ko);
+        settle(vo);
+        float up = 0.f, down = 0.f;   // 2^(kBits - E) and its inverse
+        bool poisoned = false;  // some dS of the plane's rectangle is not finite
+        if (g.with_dbias) {
+            // the bounds of the query patches that the rectangle touches: every wave finds the same maximum
+            const int pw = (W + 3) >> 2, ph = (H + 3) >> 2, by0 = ry0 >> 2, bx0 = cx0 >> 2, bw = (cx1 >> 2) - bx0 + 1, nbound = ((ry1 >> 2) - by0 + 1) * bw;
+            uint32_t most = 0, odd = 0;
+            for (int i = own_lane(); i < nbound; i += kWave) {
+                const uint32_t bits = bound[(plane * ph + by0 + i / bw) * pw + bx0 + i % bw];
+                if (bits >= 0x7f800000u) odd = 1;
+                else most = most > bits ? most : bits;
+            }
+            most = wave_max(most);
+            poisoned = __ballot(odd != 0) != 0;
+            int e = __builtin_amdgcn_readfirstlane((int)(most >> 23)) - 126;   // most < 2^e
+            e = e < -70 ? -70 : e;                                             // (2^(50 + 70) is a float)
+            up = __builtin_ldexpf(1.f, Table::kBits - e);
+            down = __builtin_ldexpf(1.f, e - Table::kBits);
+        }
+        PosSum<T, D> sk, sv, row_k, row_v;   // (fp32: of a row of blocks, then of the rows, as in part 1)
+        sk.clear();
+        sv.clear();
+        if constexpr (sizeof(T) == 4) {
+            row_k.clear();
+            row_v.clear();
+        }
+        // N blocks of a row of blocks, from block column bx on
+        auto blocks = [&](auto n, int img, int brow, int cell, bool rowok, int bx) {
+            constexpr int N = decltype(n)::value;
+            const int qa0 = img + aoff + bx * 4 * POSB, da0 = qa0 + img_bytes, qt0 = img + toff + bx * 4 * POSB, dt0 = qt0 + img_bytes;
+            constexpr bool kTight = D == 32 || (sizeof(T) == 2 && D == 64);
+            const int l0 = img + 2 * img_bytes + loff + bx * 4 * QB, b0 = brow - bx * 16, c0 = cell - 4 * bx;
+            f32x4 s4[N], dp[N];
+            Weights4<T> wp[N], ws[N];
+            typedef float Of __attribute__((ext_vector_type(kNormalised<T> ? 3 : 2)));
+            Of l[N][4];   // what part 1 left of the queries
+            float bias[N][4];
+            CV qa[N], da[N];
+#pragma unroll
+            for (int i = 0; i < N; ++i) {
+                if constexpr (!kTight) {
+                    qa[i].load_lds(qa0 + i * 4 * POSB);
+                    da[i].load_lds(da0 + i * 4 * POSB);
+                }
+                if constexpr (sizeof(T) == 2) {
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) bias[i][r] = *lds_ptr<float>(b0 - i * 16 - r * 4);
+                    // queries whose windows do not hold the key: weight 0 (decided before the products, as in part 1)
+                    if (4 * (bx + i) < clear_lo || 4 * (bx + i) + 4 > clear_hi) {
+#pragma unroll
+                        for (int r = 0; r < 4; ++r) bias[i][r] = (unsigned)(4 * (bx + i) + r - fx) < (unsigned)nx ? bias[i][r] : -INFINITY;
+                    }
+                }
+            }
+#pragma unroll
+            for (int i = 0; i < N; ++i) {
+                if constexpr (kTight) qa[i].load_lds(qa0 + i * 4 * POSB);
+                s4[i] = chan_dot<T, D>(qa[i], ko);
+                if constexpr (kTight && sizeof(T) == 4) __builtin_amdgcn_sched_barrier(0);   // (not all loads at once: the registers)
+                if constexpr (kTight) da[i].load_lds(da0 + i * 4 * POSB);
+                dp[i] = chan_dot<T, D>(da[i], vo);
+                if constexpr (kTight) __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                for (int r = 0; r < 4; ++r) {
+                    l[i][r] = *lds_ptr<Of>(l0 + (4 * i + r) * QB);
+                    // (fp32, bound by the matrix cores: every block is masked, and the bias comes late, for the registers)
+                    if constexpr (sizeof(T) == 4) {
+                        const float t = *lds_ptr<float>(b0 - i * 16 - r * 4);
+                        bias[i][r] = (unsigned)(4 * (bx + i) + r - fx) < (unsigned)nx ? t : -INFINITY;
+                    }
+                }
+            }
+#pragma unroll
+            for (int i = 0; i < N; ++i) {
+                if constexpr (kTight) __builtin_amdgcn_sched_barrier(0);
+                float p[4], ds[4];
+#pragma unroll
+                for (int r = 0; r < 4; ++r) {
+                    p[r] = exponential<T>(s4[i][r], scale2, scale2_low, bias[i][r], l[i][r].x);
+                    if constexpr (kNormalised<T>) p[r] *= l[i][r].z;
+                }
+#pragma unroll
+                for (int r = 0; r < 4; ++r) ds[r] = p[r] * (dp[i][r] - l[i][r].y);
+                if (g.with_dbias) {
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) Table::add(table_lane + (c0 - 4 * i - r) * Table::kIntBytes, ds[r], up);   // (outside the window: 0)
+                    if (poisoned) {
+#pragma unroll
+                        for (int r = 0; r < 4; ++r) {
+                            const int c = c0 - 4 * i - r;
+                            const bool in = rowok && (unsigned)(4 * (bx + i) + r - fx) < (unsigned)nx;
+                            if (in && !(fabsf(ds[r]) < INFINITY)) __hip_atomic_fetch_or(lds_ptr<unsigned>(flags0 + (c >> 5) * 4), 1u << (c & 31), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+                        }
+                    }
+                }
+                wp[i] = Weights4<T>(p);
+                ws[i] = Weights4<T>(ds);
+            }
+            if constexpr (kTight) __builtin_amdgcn_sched_barrier(0);
+            Op t[N];
+#pragma unroll
+            for (int i = 0; i < N; ++i) t[i].load_lds(dt0 + i * 4 * POSB);
+            auto &tk = sizeof(T) == 4 ? row_k : sk, &tv = sizeof(T) == 4 ? row_v : sv;
+            if constexpr (N == 2) tv.add2(t[0], wp[0], t[1], wp[1]);
+            else tv.add(t[0], wp[0]);
+            if constexpr (kTight) __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int i = 0; i < N; ++i) t[i].load_lds(qt0 + i * 4 * POSB);
+            if constexpr (N == 2) tk.add2(t[0], ws[0], t[1], ws[1]);
+            else tk.add(t[0], ws[0]);
+        };
+        for (int s = 0; s < nsteps; ++s) {
+            wait_global_loads();
+            workgroup_sync();   // this step's rows have landed for every wave, and nobody still reads the other buffer
+            const int img = img0 + par * stage_bytes;
+            const bool last = s + 1 == nsteps;
+            if (g.nstage == 2) {
+                par ^= 1;
+                if (!last || b + 1 < work.b_end) issue(last ? b + 1 : b, last ? 0 : s + 1, par);
+            }
+            if (active && s >= s_lo && s <= s_hi) {
+                // the lane's row of the block against its key (fp32: worked out anew in each step, for the registers)
+                const int lv = sizeof(T) == 4 ? own_lane_index() : lane;
+                const int qrow = ry0 + 4 * s + (lv >> 4), krow = sy0 + ((lv & 15) >> 2), kc = krow < H ? krow : H - 1, first = inv_first(kc, H, K);
+                const bool rowok = krow < H && px0 + (lv & 3) < W && qrow >= first && qrow <= inv_last(kc, H, K);
+                const int u = kc - qrow + K - 1, uc = u < 0 ? 0 : (u < NB - 1 ? u : NB - 1);
+                const int cell = uc * pitch + v0, brow = bias0 + ((rowok ? (g.with_bias ? uc : 0) : no_row) * pitch + v0) * 4;
+                constexpr int kAtOnce = kAtOnceKv<T, D>;
+                int bx = 0;
+                for (; bx + kAtOnce <= nbx; bx += kAtOnce) blocks(IntC<kAtOnce>{}, img, brow, cell, rowok, bx);
+                if (kAtOnce > 1 && bx < nbx) blocks(IntC<1>{}, img, brow, cell, rowok, bx);
+                if constexpr (sizeof(T) == 4) {
+                    sk.take(row_k);
+                    sv.take(row_v);
+                }
+            }
+            if (g.nstage == 1 && (!last || b + 1 < work.b_end)) {
+                workgroup_sync();   // nobody still reads the rows
+                issue(last ? b + 1 : b, last ? 0 : s + 1, 0);
+            }
+        }
+        if (g.with_dbias) {
+            workgroup_sync();   // every wave has added its part; nobody adds more before the next step's barrier
+            for (int i = wave * kWave + own_lane(); i < cells; i += kPatchThreads) {
+                typename Table::Int n = 0;
+                for (int c = 0; c < g.copies; ++c) {
+                    const int a = table0 + ((c ? copy_offset(c, cells) : 0) + i) * Table::kIntBytes;
+                    n += *lds_ptr<typename Table::Int>(a);
+                    *lds_ptr<typename Table::Int>(a) = 0;
+                }
+                *lds_ptr<typename Table::Sum>(sums0 + i * Table::kSumBytes) += (typename Table::Sum)n * (typename Table::Sum)down;
+            }
+        }
+        if (!active) continue;
+        if (key_ok) {
+            const int lv = own_lane();
+            const unsigned o = key_offset(lv);
+            sk.store(reinterpret_cast<char *>(dk) + plane_off, o, lv >> 4, scale);
+            sv.store(reinterpret_cast<char *>(dv) + plane_off, o, lv >> 4, 1.f);
+        }
+        const float odd = sk.not_finite() + sv.not_finite();
+        const unsigned long long again = __ballot(odd != odd);
+        if (again) {
+            wait_global_loads();   // (the stores above come first)
+            PatchShape gc = g;     // (nothing of this is prepared outside of the branch)
+            asm volatile("" : "+s"(gc.H), "+s"(gc.W), "+s"(gc.K));
+            const PlanePtrs<T, D> m{q + plane * plane_px * D, k + plane * plane_px * D, v + plane * plane_px * D, dout + plane * plane_px * D,
+                                    g.with_bias ? rpb + (size_t)head * NB * NB : nullptr};
+            for (unsigned cols = (unsigned)((again | (again >> 16) | (again >> 32) | (again >> 48)) & 0xffffu); cols; cols &= cols - 1) {
+                const int c = __builtin_ctz(cols), cy = sy0 + (c >> 2), cx = px0 + (c & 3);
+                if (cy < H && cx < W) key_once_more<T, D>(m, gc, scale, cy, cx, ld + kQueryWords<T> * plane * plane_px, dk + plane * plane_px * D, dv + plane * plane_px * D);
+            }
+        }
+    }
+    if (g.with_dbias) {   // (each thread reads the sums it added up)
+        float *row = partial + (size_t)((head * g.splits + work.split) * g.gd.npos + work.pos) * rpb_cell_stride(NB * NB);
+        for (int i = wave * kWave + own_lane(); i < cells; i += kPatchThreads) {
+            const int u = fdiv(i, g.by_pitch), v = i - u * pitch - kBiasPad;
+            if ((unsigned)v >= (unsigned)NB) continue;
+            const bool odd = (*lds_ptr<unsigned>(flags0 + (i >> 5) * 4) >> (i & 31)) & 1u;
+            row[u * NB + v] = odd ? NAN : (float)*lds_ptr<typename Table::Sum>(sums0 + i * Table::kSumBytes);
+        }
+    }
+}
+
+// ---- host ------------------------------------------------------------------------------------------------------------
+struct PatchPlan {
+    PatchShape q, kv;
+    int lds_q, lds_kv;
+    bool ok;
+};
+// Image buffers: two while two workgroups then share a compute unit, one where that is what lets two share it (or what fits at all)
+int stages(int fixed, int stage, int &lds_bytes) {
+    constexpr int kCu = 160 * 1024;
+    const int n = fixed + 2 * stage <= kCu / 2 || (fixed + stage > kCu / 2 && fixed + 2 * stage <= kCu) ? 2 : 1;
+    lds_bytes = fixed + n * stage;
+    return lds_bytes <= kCu ? n : 0;
+}
+int query_bytes(const Problem &p) { return 4 * (p.dtype == NA2D_F32 ? kQueryWords<float> : kQueryWords<f16_t>); }
+PatchPlan patch_plan(const Problem &p, bool bias, bool dbias) {
+    PatchPlan pl{};
+    const int K = p.K, posb = p.D * p.elem_bytes(), pitch = bias_pitch(K), cells = (2 * K - 1) * pitch;
+    const int table = bias_rows(K, bias) * pitch * 4;
+    const auto sums = [&](int copies) { return !dbias ? 0 : p.dtype == NA2D_F32 ? dbias_bytes<float>(cells, copies) : dbias_bytes<f16_t>(cells, copies); };
+    // the tile's shape: the one that takes the fewest steps of four streamed rows
+    int lg = 3;
+    long long least = LLONG_MAX;
+    for (int l = 3; l >= 1; --l) {
+        const int rows = (32 >> l) + K - 1 < p.H ? (32 >> l) + K - 1 : p.H;
+        const long long steps = (long long)((p.W + (4 << l) - 1) / (4 << l)) * ((p.H + (32 >> l) - 1) / (32 >> l)) * ((rows + 3) / 4);
+        if (steps < least) least = steps, lg = l;
+    }
+    const int tw = 4 << lg, th = 32 >> lg;
+    const int tiles_x = (p.W + tw - 1) / tw, tiles_y = (p.H + th - 1) / th;
+    int rwq = 0, rwkv = 0;   // what the widest tile's patches reach from the image's first column
+    for (int px = 0; px < p.W; px += 4) {
+        const int px3 = px + 3 < p.W - 1 ? px + 3 : p.W - 1, tx = px / tw * tw;
+        const int oq = win_start(px, p.W, K), okv = inv_first(px, p.W, K);
+        const int eq = oq - win_start(tx, p.W, K) + ((win_start(px3, p.W, K) + K - oq + 3) & ~3);
+        const int ekv = okv - inv_first(tx, p.W, K) + ((inv_last(px3, p.W, K) - okv + 4) & ~3);
+        rwq = rwq > eq ? rwq : eq;
+        rwkv = rwkv > ekv ? rwkv : ekv;
+    }
+    const int unit = 1024 / posb > 1 ? 1024 / posb : 1;
+    rwq = (rwq + unit - 1) / unit * unit;
+    rwkv = (rwkv + unit - 1) / unit * unit;
+    UnitSplit us;
+    us.units = tiles_x * tiles_y * p.heads;
+    // more workgroups than fit at a time: those next to the borders have up to twice the work, and what waits fills the gaps
+    us.splits = 2048 / us.units;
+    us.splits = us.splits < 1 ? 1 : us.splits < p.B ? us.splits : p.B;
+    us.gd = make_grid_decode(tiles_x, tiles_y, p.heads, p.B, us.splits);
+    PatchShape s{p.H, p.W, K, p.heads, tiles_y, us.units, us.splits, rwq, lg, 0, 1, bias ? 1 : 0, dbias ? 1 : 0, us.gd, make_fastdiv(pitch)};
+    pl.q = s;
+    s.rw = rwkv;
+    pl.kv = s;
+    pl.q.nstage = stages(table, 2 * 4 * rwq * posb, pl.lds_q);
+    // four copies of the integers where they cost neither a buffer nor the second workgroup
+    const int stage = 2 * 4 * rwkv * posb + 4 * rwkv * query_bytes(p);
+    int lds4 = 0;
+    pl.kv.nstage = stages(table + sums(1), stage, pl.lds_kv);
+    pl.kv.copies = 1;
+    if (dbias && pl.kv.nstage > 0 && stages(table + sums(4), stage, lds4) == pl.kv.nstage && (lds4 <= 80 * 1024 || pl.lds_kv > 80 * 1024)) {
+        pl.kv.copies = 4;
+        pl.lds_kv = lds4;
+    }
+    pl.ok = pl.q.nstage > 0 && pl.kv.nstage > 0;
+    return pl;
+}
+
+size_t up256(size_t n) { return (n + 255) & ~(size_t)255; }
+size_t bound_count(const Problem &p) { return (size_t)p.planes() * ((p.H + 3) / 4) * ((p.W + 3) / 4); }
+
+template <typename T, int D>
+hipError_t launch_patch_bwd_t(const Problem &p, const PatchPlan &pl, const T *q, const T *k, const T *v, const T *rpb, float scale,
+                              const float *lse, const T *dout, T *dq, T *dk, T *dv, float *ld, uint32_t *bound, float *partial, hipStream_t s) {
+    static LdsAllowed allowed_q, allowed_kv;
+    if (hipError_t e = allow_lds(patch_bwd_q_kernel<T, D>, 160 * 1024, allowed_q); e != hipSuccess) return e;
+    if (hipError_t e = allow_lds(patch_bwd_kv_kernel<T, D>, 160 * 1024, allowed_kv); e != hipSuccess) return e;
+    const dim3 grid(xcd_padded_grid(pl.q.units * pl.q.splits));
+    hipLaunchKernelGGL((patch_bwd_q_kernel<T, D>), grid, dim3(kPatchThreads), pl.lds_q, s, q, k, v, rpb, scale, lse, dout, dq, ld, bound, pl.q);
+    if (hipError_t e = hipGetLastError(); e != hipSuccess) return e;
+    hipLaunchKernelGGL((patch_bwd_kv_kernel<T, D>), grid, dim3(kPatchThreads), pl.lds_kv, s, q, k, v, rpb, scale, ld, bound, dout, dk, dv, partial, pl.kv);
+    return hipGetLastError();
+}
+
+}  // namespace
+
+// Where the two kernels are the faster ones, time over that of recomputing the weights into memory and the unfused steps (with the bias
+// gradient; 14 x 14, 33 x 70 and 56 x 56 maps; a wave works its patch off alone, so that a call of few tiles lasts as long as one tile).
+// 16 bit, to 64 channels: 0.23 .. 0.9, but 64 channels with k >= 15 1.25 .. 1.45 at 27 tiles (0.68 at 135).  128 channels: k <= 11
+// 0.9 .. 1.7; k >= 13 1.1 .. 2.4 at up to 135 tiles, 0.63 .. 0.95 at 1000.  fp32, 16 channels: 0.5 .. 0.99, but k >= 11 1.1 .. 1.4 at 8
+// and 27 tiles (0.73 .. 0.9 at 84 and more).  fp32, 32 channels: k = 3 0.8 .. 1.08, the large calls above 1; k = 5 0.6 .. 0.95; beyond 1.2 .. 1.9 at
+// 27 tiles, 0.82 .. 1.09 at 84, 0.74 .. 1.0 at 135, 0.5 .. 0.85 at 1000.  fp32, 64 channels: k = 3 0.9 .. 1.5; beyond 1.0 .. 2.4 to 135 tiles, and at 1000
+// 0.64 .. 0.93, but 0.97 .. 1.27 on maps narrower than a tile of 32.  128 channels in fp32: the registers do not hold a wave's sums.
+bool patch_bwd_supported(const Problem &p) {
+    if (fused_bwd_supported(p) || p.D * p.elem_bytes() > 256) return false;
+    const PatchPlan pl = patch_plan(p, true, true);
+    if (!pl.ok) return false;
+    const long long tiles = (long long)pl.q.units * p.B;
+    if (p.dtype != NA2D_F32) return p.D <= 32 || (p.D == 64 && (p.K <= 13 || tiles >= 64)) || (p.D == 128 && p.K >= 13 && tiles >= 512);
+    if (p.D == 16) return p.K <= 9 || tiles >= 64;
+    if (p.D == 32) return p.K == 5 || (p.K >= 7 && tiles >= 128);
+    return p.K >= 5 && p.W >= 32 && tiles >= 512;
+}
+
+// (log2(e) lse, delta) per query, a bound per query patch, a partial bias gradient per workgroup of part 2
+size_t patch_bwd_workspace_bytes(const Problem &p) {
+    const PatchPlan pl = patch_plan(p, true, true);
+    const int nb = 2 * p.K - 1;
+    return up256(p.queries() * query_bytes(p)) + up256(bound_count(p) * 4) + up256((size_t)pl.kv.units * pl.kv.splits * rpb_cell_stride(nb * nb) * 4);
+}
+
+hipError_t launch_patch_bwd(const Problem &p, const void *q, const void *k, const void *v, const void *rpb, float scale, const float *lse,
+                            const void *dout, void *dq, void *dk, void *dv, float *d_rpb, void *workspace, hipStream_t s) {
+    const PatchPlan pl = patch_plan(p, rpb != nullptr, d_rpb != nullptr);
+    if (!pl.ok) return hipErrorInvalidValue;
+    char *ws = static_cast<char *>(workspace);
+    float *ld = reinterpret_cast<float *>(ws);
+    uint32_t *bound = d_rpb ? reinterpret_cast<uint32_t *>(ws + up256(p.queries() * query_bytes(p))) : nullptr;
+    float *partial = d_rpb ? reinterpret_cast<float *>(ws + up256(p.queries() * query_bytes(p)) + up256(bound_count(p) * 4)) : nullptr;
+    hipError_t e = hipErrorInvalidValue;
+    const auto run = [&]() -> hipError_t {
+        NA2D_DISPATCH_T(p.dtype, NA2D_DISPATCH_D(p.D, if constexpr (D * sizeof(T) <= 256) return (launch_patch_bwd_t<T, D>(p, pl,
+            static_cast<const T *>(q), static_cast<const T *>(k), static_cast<const T *>(v), static_cast<const T *>(rpb), scale, lse,
+            static_cast<const T *>(dout), static_cast<T *>(dq), static_cast<T *>(dk), static_cast<T *>(dv), ld, bound, partial, s))));
+        return hipErrorInvalidValue;
+    };
+    e = run();
+    if (e != hipSuccess || d_rpb == nullptr) return e;
+    return launch_rpb_final_av(p, partial, d_rpb, AvRpbSplit{pl.kv.units / p.heads, pl.kv.splits}, s);
+}
+
+}  // namespace na2d

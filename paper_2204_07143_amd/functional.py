@@ -106,8 +106,13 @@ class _NA2D(torch.autograd.Function):
         dq, dk, dv = torch.empty_like(q), torch.empty_like(k), torch.empty_like(v)
         want_bias = ctx.has_rpb and ctx.needs_input_grad[3]
         d32 = torch.empty((q.shape[1], 2 * ks - 1, 2 * ks - 1), dtype=torch.float32, device=q.device) if want_bias else None
-        na.na2d_fused_bwd(q, k, v, rpb, ctx.scale, lse, dout.contiguous(), ks, dq, dk, dv, d32,
-                          _workspace(q, ks, na.WS_FUSED_BWD))
+        direct = na.na2d_direct_bwd_workspace_bytes(na.problem(*q.shape, ks, q.dtype))   # 0: not for this problem
+        if direct:
+            na.na2d_direct_bwd(q, k, v, rpb, ctx.scale, lse, dout.contiguous(), ks, dq, dk, dv, d32,
+                               torch.empty(direct, dtype=torch.uint8, device=q.device))
+        else:
+            na.na2d_fused_bwd(q, k, v, rpb, ctx.scale, lse, dout.contiguous(), ks, dq, dk, dv, d32,
+                              _workspace(q, ks, na.WS_FUSED_BWD))
         return dq, dk, dv, (d32.to(rpb.dtype) if want_bias else None), None, None
 
 
