@@ -115,7 +115,8 @@ static hipError_t launch_fused_t(const Problem &p, const void *q, const void *k,
 hipError_t launch_fused_fwd(const Problem &p, const void *q, const void *k, const void *v, const void *rpb, float scale,
                             void *out, float *lse, hipStream_t s) {
     if (fused_mfma_supported(p)) return launch_fused_mfma(p, q, k, v, rpb, scale, out, lse, s);
-    if (!valu_preferred(p, ValuOp::fused)) return launch_fused_strip(p, q, k, v, rpb, scale, out, lse, s);
+    if (!valu_preferred(p, ValuOp::fused))
+        return patch_fwd_preferred(p) ? launch_patch_fwd(p, q, k, v, rpb, scale, out, lse, s) : launch_fused_strip(p, q, k, v, rpb, scale, out, lse, s);
     NA2D_DISPATCH_K(p.K, NA2D_DISPATCH_D(p.D, return (launch_fused_t<K, D>(p, q, k, v, rpb, scale, out, lse, s))));
     return hipErrorInvalidValue;
 }

@@ -99,6 +99,10 @@ bool patch_bwd_supported(const Problem &p);
 size_t patch_bwd_workspace_bytes(const Problem &p);
 hipError_t launch_patch_bwd(const Problem &p, const void *q, const void *k, const void *v, const void *rpb, float scale,
                             const float *lse, const void *dout, void *dq, void *dk, void *dv, float *d_rpb, void *workspace, hipStream_t s);
+// fused forward over query patches, any window side, head dim and storage type while its rows fit the LDS (na2d_patch_fwd.hip)
+bool patch_fwd_preferred(const Problem &p);
+hipError_t launch_patch_fwd(const Problem &p, const void *q, const void *k, const void *v, const void *rpb, float scale, void *out,
+                            float *lse, hipStream_t s);
 hipError_t launch_fused_fwd(const Problem &p, const void *q, const void *k, const void *v, const void *rpb, float scale,
                             void *out, float *lse, hipStream_t s);
 // D = 16, 32, 64 and, to k = 7, 128 (32-channel slices)

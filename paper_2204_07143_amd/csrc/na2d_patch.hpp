@@ -200,29 +200,74 @@ template <typename T, int D> struct PosSum {
     }
 };
 
-// Four consecutive map rows of one plane of two tensors, `rw` positions each from column x0 on, into two LDS images (the second
-// img_bytes behind the first) by direct loads.  Positions outside the map are replaced by the nearest one inside it (they only
-// meet zero weights).  Wave w takes row w % 4; the waves of a row deal its 1 KB pieces (rw is a whole number of them).
+// `rows` (4, 8 or 16) consecutive map rows of one plane of two tensors, `rw` positions each from column x0 on, into two LDS images
+// (the second img_bytes behind the first) by direct loads.  Positions outside the map are replaced by the nearest one inside it (they
+// only meet zero weights).  A row's 1 KB pieces go to the waves of a workgroup in turn (two waves to a row while there are four;
+// rw is a whole number of pieces).
 constexpr int kPatchWaves = 8, kPatchThreads = kPatchWaves * kWave;
 template <int POSB> constexpr int kRowUnit = POSB >= 1024 ? 1 : 1024 / POSB;   // positions per piece
 template <int POSB>
-__device__ __forceinline__ void issue_rows(const char *plane_a, const char *plane_b, int H, int W, int y0, int x0, int rw, int img, int img_bytes, int wave, int lane) {
+__device__ __forceinline__ void issue_rows(const char *plane_a, const char *plane_b, int H, int W, int y0, int x0, int rw, int img, int img_bytes, int wave, int lane,
+                                           int rows = 4) {
     constexpr int CPP = POSB / 16;
     // (recomputed at every call: as loop invariants the addresses below would spill scalar registers)
     asm volatile("" : "+s"(rw), "+s"(W), "+s"(wave));
-    const int row = wave & 3;
-    const unsigned line = (unsigned)((y0 + row < H - 1 ? y0 + row : H - 1) * W);   // (a plane is smaller than 2^31 bytes)
-    const char *a = plane_a + (size_t)line * POSB, *b = plane_b + (size_t)line * POSB;
-    int dst = img + (row * rw) * POSB + (wave >> 2) * 1024;
-    const int end = img + (row + 1) * rw * POSB;
-    int x = x0 + (wave >> 2) * kRowUnit<POSB> + lane / CPP;
-    for (; dst < end; dst += (kPatchWaves / 4) * 1024, x += (kPatchWaves / 4) * kRowUnit<POSB>) {
-        const unsigned off = (unsigned)((x < W - 1 ? x : W - 1) * POSB + (lane % CPP) * 16);
-        global_to_lds_16(a, off, dst);
-        global_to_lds_16(b, off, dst + img_bytes);
+    const int per_row = rows == 4 ? 2 : 1, first = rows == 4 ? wave >> 2 : 0;
+    for (int row = rows == 4 ? wave & 3 : wave; row < rows; row += kPatchWaves) {
+        const unsigned line = (unsigned)((y0 + row < H - 1 ? y0 + row : H - 1) * W);   // (a plane is smaller than 2^31 bytes)
+        const char *a = plane_a + (size_t)line * POSB, *b = plane_b + (size_t)line * POSB;
+        int dst = img + (row * rw) * POSB + first * 1024;
+        const int end = img + (row + 1) * rw * POSB;
+        int x = x0 + first * kRowUnit<POSB> + lane / CPP;
+        for (; dst < end; dst += per_row * 1024, x += per_row * kRowUnit<POSB>) {
+            const unsigned off = (unsigned)((x < W - 1 ? x : W - 1) * POSB + (lane % CPP) * 16);
+            global_to_lds_16(a, off, dst);
+            global_to_lds_16(b, off, dst + img_bytes);
+        }
     }
 }
 
+constexpr float kLog2e = 1.4426950408889634f, kLog2eLow = (float)(1.4426950408889634 - (double)kLog2e);
+// scale2 s + bias with scale2 to twice its digits (an infinite s must not meet the infinity of the other sign)
+__device__ __forceinline__ float exponent_fp32(float s, float scale2, float scale2_low, float bias) {
+    return __builtin_fmaf(scale2, s, __builtin_fmaf(scale2_low, __builtin_amdgcn_fmed3f(s, -3e38f, 3e38f), bias));
+}
+// fp32 dot product of two head vectors in memory
+template <typename T, int D> __device__ __forceinline__ float dot_memory(const T *a, const T *b) {
+    float acc = 0.f;
+#pragma unroll
+    for (int d = 0; d < D; d += 8) {
+        VecN<T, 8> x, y;
+        load_vec32(x, a + d);
+        load_vec32(y, b + d);
+        acc += dot32(x, y);
+    }
+    return acc;
+}
+__device__ __forceinline__ float lane_value(float x, int lane) {
+    return __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, x), lane));
+}
+
+// Slots of a rectangle in raster order, one after the other (past the last it stays there)
+struct RasterWalk {
+    int row = 0, col = 0;
+    __device__ __forceinline__ void next(int rows, int cols) {
+        const bool wrap = col == cols - 1, more = row < rows - 1;
+        col = !wrap ? col + 1 : more ? 0 : col;
+        row += wrap && more;
+    }
+};
+// A result worked out once more takes the place of one that is not finite; the others, added up in another order, stay.
+template <typename T> __device__ __forceinline__ void replace_not_finite(T *at, float x) {
+    if (!(fabsf(to_f32(*at)) < INFINITY)) *at = from_f32<T>(x);
+}
+// Image buffers: two while two workgroups then share a compute unit, one where that is what lets two share it (or what fits at all); 0: too large
+static inline int image_buffers(int fixed, int stage, int &lds_bytes) {
+    constexpr int kCu = 160 * 1024;
+    const int n = fixed + 2 * stage <= kCu / 2 || (fixed + stage > kCu / 2 && fixed + 2 * stage <= kCu) ? 2 : 1;
+    lds_bytes = fixed + n * stage;
+    return lds_bytes <= kCu ? n : 0;
+}
 // The bias table in LDS: rows of bias_pitch() fp32 entries, kBiasPad of padding (zeros) in front of entry 0 and as much
 // behind the last; a patch's products reach that far beyond the table outside their windows.  The pitch is 8 mod 32 so that the
 // rows a wave reads at once start in different banks.  One more row holds -inf: where a lane's row of a block is not in its
@@ -251,7 +296,8 @@ __device__ __forceinline__ int dynamic_lds(const char *lds) {
 struct PatchShape {
     int H, W, K, heads, tiles_y, units, splits;
     int rw;                // positions per image row
-    int lg_cols;           // a tile is 2^lg_cols patches wide and 8 / 2^lg_cols patches high
+    int lg_split;          // 2^lg_split waves share a patch, each with its rows of blocks (forward)
+    int lg_cols;           // a tile is 2^lg_cols patches wide and (8 >> lg_split) / 2^lg_cols patches high
     int nstage;            // LDS buffers (1: reloaded between steps)
     int copies;            // of the integer bias gradients
     int with_bias, with_dbias;

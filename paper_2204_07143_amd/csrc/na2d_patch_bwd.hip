@@ -31,7 +31,6 @@ namespace na2d {
 
 namespace {
 
-constexpr float kLog2e = 1.4426950408889634f, kLog2eLow = (float)(1.4426950408889634 - (double)kLog2e);
 // What part 1 leaves of a query for part 2: the base of its exponents and delta.  In 16 bit the base is log2(e) lse.  In fp32 it is 0
 // (log2(e) lse rounded to a whole number where that is beyond +-32), and the inverse of the sum of the exponentials to that base
 // follows (and a word of padding): P = exp2(t - base) / sum has neither the rounding of lse nor that of the difference in it.
@@ -45,18 +44,6 @@ template <typename T, int D> constexpr int kPatchOcc = D * sizeof(T) <= 128 ? 4 
 template <typename T, int D> constexpr int kAtOnceQ = (sizeof(T) == 2 && D <= 32) || kPatchOcc<T, D> == 2 ? 2 : 1;
 template <typename T, int D> constexpr int kAtOnceKv = (sizeof(T) == 2 && D <= 32) || kPatchOcc<T, D> == 2 ? 2 : 1;
 
-// fp32 dot product of two head vectors in memory
-template <typename T, int D> __device__ __forceinline__ float dot_memory(const T *a, const T *b) {
-    float acc = 0.f;
-#pragma unroll
-    for (int d = 0; d < D; d += 8) {
-        VecN<T, 8> x, y;
-        load_vec32(x, a + d);
-        load_vec32(y, b + d);
-        acc += dot32(x, y);
-    }
-    return acc;
-}
 __device__ __forceinline__ float wave_sum(float x) {
 #pragma unroll
     for (int m = 1; m < kWave; m *= 2) x += __shfl_xor(x, m);
@@ -74,10 +61,6 @@ __device__ __forceinline__ uint32_t wave_max(uint32_t x) {
 __device__ __forceinline__ uint32_t ds_bound(float most_pdp, float most_p, float delta) {
     return __float_as_uint(fabsf(__builtin_fmaf(most_p, fabsf(delta), most_pdp)));
 }
-__device__ __forceinline__ float lane_value(float x, int lane) {
-    return __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, x), lane));
-}
-
 // Weight and upstream product of one (query, key) pair, from memory.
 template <typename T, int D> struct PlanePtrs {
     const T *q, *k, *v, *dout, *rpb;   // of the plane; the head's bias table or null
@@ -116,6 +99,7 @@ __device__ __forceinline__ float query_once_more(const PlanePtrs<T, D> &m, const
     delta = wave_sum(delta) * inv;
     bound = ds_bound(__uint_as_float(wave_max(most)) * inv, __uint_as_float(wave_max(most_p)) * inv, delta);
     float acc[(D + kWave - 1) / kWave] = {};
+    RasterWalk at;
     for (int first = 0; first < KK && delta == delta; first += kWave) {
         const int slot = first + lane < KK ? first + lane : KK - 1, a = slot / K, c = slot - a * K;
         float p, dp;
@@ -124,17 +108,17 @@ __device__ __forceinline__ float query_once_more(const PlanePtrs<T, D> &m, const
         const int n = KK - first < kWave ? KK - first : kWave;
         for (int t = 0; t < n; ++t) {
             const float w = lane_value(ds, t);
-            const int ta = (first + t) / K, tc = first + t - ta * K;
 #pragma unroll
             for (int u = 0; u < (D + kWave - 1) / kWave; ++u) {
                 const int d = u * kWave + lane < D ? u * kWave + lane : D - 1;
-                acc[u] = __builtin_fmaf(w, to_f32(m.k[((size_t)(sy + ta) * g.W + sx + tc) * D + d]), acc[u]);
+                acc[u] = __builtin_fmaf(w, to_f32(m.k[((size_t)(sy + at.row) * g.W + sx + at.col) * D + d]), acc[u]);
             }
+            at.next(K, K);
         }
     }
 #pragma unroll
     for (int u = 0; u < (D + kWave - 1) / kWave; ++u)
-        if (u * kWave + lane < D) dq[((size_t)iy * g.W + ix) * D + u * kWave + lane] = from_f32<T>(delta == delta ? scale * acc[u] : NAN);
+        if (u * kWave + lane < D) replace_not_finite(dq + ((size_t)iy * g.W + ix) * D + u * kWave + lane, delta == delta ? scale * acc[u] : NAN);
     return delta;
 }
 
@@ -142,9 +126,10 @@ __device__ __forceinline__ float query_once_more(const PlanePtrs<T, D> &m, const
 template <typename T, int D>
 __device__ __forceinline__ void key_once_more(const PlanePtrs<T, D> &m, const PatchShape &g, float scale, int y, int x, const float *ld, T *dk, T *dv) {
     const int lane = threadIdx.x % kWave, K = g.K;
-    const int y0 = inv_first(y, g.H, K), x0 = inv_first(x, g.W, K), nx = inv_last(x, g.W, K) - x0 + 1, total = (inv_last(y, g.H, K) - y0 + 1) * nx;
+    const int y0 = inv_first(y, g.H, K), x0 = inv_first(x, g.W, K), nx = inv_last(x, g.W, K) - x0 + 1, ny = inv_last(y, g.H, K) - y0 + 1, total = ny * nx;
     constexpr int NU = (D + kWave - 1) / kWave;
     float ak[NU] = {}, av[NU] = {};
+    RasterWalk at;
     for (int first = 0; first < total; first += kWave) {
         const int s = first + lane < total ? first + lane : total - 1, iy = y0 + s / nx, ix = x0 + s % nx;
         const float *of = ld + kQueryWords<T> * ((size_t)iy * g.W + ix);
@@ -154,33 +139,50 @@ __device__ __forceinline__ void key_once_more(const PlanePtrs<T, D> &m, const Pa
         const float delta = of[1];
         const float ds = p * (dp - delta);
         const int n = total - first < kWave ? total - first : kWave;
-        for (int t = 0; t < n; ++t) {
-            const float wp = lane_value(p, t), ws = lane_value(ds, t);
-            const size_t i = ((size_t)(y0 + (first + t) / nx) * g.W + x0 + (first + t) % nx) * D;
+        constexpr int kChunk = sizeof(T) == 4 ? 2 : 8;
+        bool open = true;   // (a sum that is NaN stays NaN)
+        for (int t0 = 0; t0 < n && open; t0 += kChunk) {
+            float wp[kChunk], ws[kChunk], xd[kChunk][NU], xq[kChunk][NU];
+#pragma unroll
+            for (int e = 0; e < kChunk; ++e) {   // (their loads do not wait for each other; past the end: once more, not added)
+                wp[e] = lane_value(p, (t0 + e) % kWave);
+                ws[e] = lane_value(ds, (t0 + e) % kWave);
+                const size_t i = ((size_t)(y0 + at.row) * g.W + x0 + at.col) * D;
+                at.next(ny, nx);
+#pragma unroll
+                for (int u = 0; u < NU; ++u) {
+                    const int d = u * kWave + lane < D ? u * kWave + lane : D - 1;
+                    xd[e][u] = to_f32(m.dout[i + d]);
+                    xq[e][u] = to_f32(m.q[i + d]);
+                }
+            }
+            bool any = false;
 #pragma unroll
             for (int u = 0; u < NU; ++u) {
-                const int d = u * kWave + lane < D ? u * kWave + lane : D - 1;
-                av[u] = __builtin_fmaf(wp, to_f32(m.dout[i + d]), av[u]);
-                ak[u] = __builtin_fmaf(ws, to_f32(m.q[i + d]), ak[u]);
-            }
-        }
-        bool open = false;   // a sum that is NaN stays NaN
 #pragma unroll
-        for (int u = 0; u < NU; ++u) open |= ak[u] == ak[u] || av[u] == av[u];
-        if (__ballot(open) == 0) break;
+                for (int e = 0; e < kChunk; ++e)
+                    if (t0 + e < n) {
+                        av[u] = __builtin_fmaf(wp[e], xd[e][u], av[u]);
+                        ak[u] = __builtin_fmaf(ws[e], xq[e][u], ak[u]);
+                    }
+                any |= ak[u] == ak[u] || av[u] == av[u];
+            }
+            open = __ballot(any) != 0;
+        }
+        if (!open) break;
     }
 #pragma unroll
     for (int u = 0; u < NU; ++u)
         if (u * kWave + lane < D) {
             const size_t o = ((size_t)y * g.W + x) * D + u * kWave + lane;
-            dk[o] = from_f32<T>(scale * ak[u]);
-            dv[o] = from_f32<T>(av[u]);
+            replace_not_finite(dk + o, scale * ak[u]);
+            replace_not_finite(dv + o, av[u]);
         }
 }
 
 // exp2(scale2 s + bias - base), bias in units of log2
 template <typename T> __device__ __forceinline__ float exponential(float s, float scale2, float scale2_low, float bias, float base) {
-    if constexpr (kNormalised<T>) return __builtin_amdgcn_exp2f(__builtin_fmaf(scale2, s, __builtin_fmaf(scale2_low, s, bias)) - base);
+    if constexpr (kNormalised<T>) return __builtin_amdgcn_exp2f(exponent_fp32(s, scale2, scale2_low, bias) - base);
     return __builtin_amdgcn_exp2f(__builtin_fmaf(scale2, s, bias - base));
 }
 template <typename T> __device__ __forceinline__ void store_query(float *ld, unsigned n, float base, float delta, float inv) {
@@ -704,13 +706,6 @@ struct PatchPlan {
     int lds_q, lds_kv;
     bool ok;
 };
-// Image buffers: two while two workgroups then share a compute unit, one where that is what lets two share it (or what fits at all)
-int stages(int fixed, int stage, int &lds_bytes) {
-    constexpr int kCu = 160 * 1024;
-    const int n = fixed + 2 * stage <= kCu / 2 || (fixed + stage > kCu / 2 && fixed + 2 * stage <= kCu) ? 2 : 1;
-    lds_bytes = fixed + n * stage;
-    return lds_bytes <= kCu ? n : 0;
-}
 int query_bytes(const Problem &p) { return 4 * (p.dtype == NA2D_F32 ? kQueryWords<float> : kQueryWords<f16_t>); }
 PatchPlan patch_plan(const Problem &p, bool bias, bool dbias) {
     PatchPlan pl{};
@@ -745,17 +740,17 @@ PatchPlan patch_plan(const Problem &p, bool bias, bool dbias) {
     us.splits = 2048 / us.units;
     us.splits = us.splits < 1 ? 1 : us.splits < p.B ? us.splits : p.B;
     us.gd = make_grid_decode(tiles_x, tiles_y, p.heads, p.B, us.splits);
-    PatchShape s{p.H, p.W, K, p.heads, tiles_y, us.units, us.splits, rwq, lg, 0, 1, bias ? 1 : 0, dbias ? 1 : 0, us.gd, make_fastdiv(pitch)};
+    PatchShape s{p.H, p.W, K, p.heads, tiles_y, us.units, us.splits, rwq, 0, lg, 0, 1, bias ? 1 : 0, dbias ? 1 : 0, us.gd, make_fastdiv(pitch)};
     pl.q = s;
     s.rw = rwkv;
     pl.kv = s;
-    pl.q.nstage = stages(table, 2 * 4 * rwq * posb, pl.lds_q);
+    pl.q.nstage = image_buffers(table, 2 * 4 * rwq * posb, pl.lds_q);
     // four copies of the integers where they cost neither a buffer nor the second workgroup
     const int stage = 2 * 4 * rwkv * posb + 4 * rwkv * query_bytes(p);
     int lds4 = 0;
-    pl.kv.nstage = stages(table + sums(1), stage, pl.lds_kv);
+    pl.kv.nstage = image_buffers(table + sums(1), stage, pl.lds_kv);
     pl.kv.copies = 1;
-    if (dbias && pl.kv.nstage > 0 && stages(table + sums(4), stage, lds4) == pl.kv.nstage && (lds4 <= 80 * 1024 || pl.lds_kv > 80 * 1024)) {
+    if (dbias && pl.kv.nstage > 0 && image_buffers(table + sums(4), stage, lds4) == pl.kv.nstage && (lds4 <= 80 * 1024 || pl.lds_kv > 80 * 1024)) {
         pl.kv.copies = 4;
         pl.lds_kv = lds4;
     }

@@ -85,8 +85,9 @@ constexpr bool tile_fits() {
 //   weighted sum  D = 16, k = 3 .. 9 1.6, 1.8, 1.6, 1.3 (k = 11: 0.7); 1.4, 1.2, 0.9, 0.7;
 //                 D = 32, k = 3 .. 7 1.3, 1.4, 1.0 (0.8 .. 1.2); 1.0, 0.9, 0.6;  D = 64 0.8
 //   inverse       D = 16, k = 3 .. 7 1.7, 1.1, 0.7; 1.3, 0.8, 0.5;  D = 32 1.3, 0.9, 0.4; 1.0, 0.6
-//   fused         D = 16, k = 3 .. 13 2.2, 2.0, 1.8, 1.1, 1.0, 0.8;  D = 32 1.6, 1.1, 0.9 (k = 9: 0.4);  D = 64 0.8
-// and they cross where strips are few (same maps): fused 1300 to 1800 strips, logits 1300 to 2000 (W <= 16: 2500), weighted
+//   fused         against the patches of na2d_patch_fwd.hip (100k queries on 14 x 14, 33 x 70 and 56 x 56 maps; their time over that of the
+//                 tiles): D = 16, k = 3 .. 7 1.3 .. 1.6, 1.0 .. 1.5, 0.97 .. 1.36 (k = 9: 0.58 .. 0.71);  D = 32 0.82 .. 0.97, 0.54 .. 0.73
+// and they cross where strips are few (same maps): fused 1300 to 1800 strips (then against strips), logits 1300 to 2000 (W <= 16: 2500), weighted
 // sum 1500 to 2500 (3000 to 4000), inverse 3000; at the widest windows with tiles both ways win in turns up to 6000.  With this
 // rule a problem takes 0.6 % longer on average than with the faster of the two, and 0.2 % of them run more than a tenth slower
 // than in tiles; with one line at 32768 queries for all of them it was 2.2 % and 1.2 % (fused D = 16, k = 5, 458 7 x 7
@@ -106,7 +107,7 @@ constexpr int valu_least_strips(ValuOp op, int D, int K, bool one_strip_rows) {
         case ValuOp::inverse:
             if (one_strip_rows) return D == 16 && K == 3 ? 4096 : kNoTiles;
             return K == 3 && D <= 32 ? 3072 : D == 16 && K == 5 ? 6144 : kNoTiles;
-        default: return K <= (D == 16 ? 9 : D == 32 ? 5 : 0) ? quick : D == 16 && K == 11 ? 2560 : kNoTiles;
+        default: return K <= (D == 16 ? 7 : 0) ? quick : kNoTiles;
     }
 }
 constexpr bool valu_has_tile(ValuOp op, int D, int K) { return valu_least_strips(op, D, K, false) != kNoTiles; }
