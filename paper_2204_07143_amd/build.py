@@ -3,22 +3,27 @@
     python -m paper_2204_07143_amd.build [--force] [-j N]
 
 Every csrc/*.hip is compiled to an object under _build/ (in parallel) and linked into
-paper_2204_07143_amd/libna2d.so.  Cross-compiles without a GPU.
+paper_2204_07143_amd/libna2d.so; csrc/host/torch_ops.cpp, the differentiable operators' host side, into
+na2d_torch.so beside it (host code, against torch's own headers).  Cross-compiles without a GPU.
 """
 from __future__ import annotations
 
 import argparse
 import concurrent.futures
 import glob
+import importlib.util
 import os
 import subprocess
 import sys
+import sysconfig
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 OBJ_DIR = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libna2d.so")
+HOST_SRC = os.path.join(CSRC, "host", "torch_ops.cpp")
+HOST_LIB = os.path.join(HERE, "na2d_torch.so")
 # measurement build (-DNA2D_PROBE_MEMORY_ONLY: loads and stores only in the tiled contraction kernels); bench.py --lib
 PROBE_LIB = os.path.join(OBJ_DIR, "libna2d_probe_memory_only.so")
 
@@ -83,6 +88,25 @@ def _check_no_scratch(src: str, stderr: str) -> None:
         raise RuntimeError(f"{os.path.basename(src)}: kernels spill to scratch:\n  " + "\n  ".join(bad))
 
 
+def _build_host(force: bool) -> None:
+    """na2d_torch.so from csrc/host: the host compiler, torch's headers and libraries, libna2d.so beside it."""
+    if not force and os.path.exists(HOST_LIB) and os.path.getmtime(HOST_LIB) >= max(os.path.getmtime(HOST_SRC), _newest_header()):
+        return
+    torch_dir = importlib.util.find_spec("torch").submodule_search_locations[0]
+    rocm = os.path.dirname(os.path.dirname(HIPCC))
+    cmd = [os.environ.get("CXX", "g++"), "-std=c++17", "-O2", "-fPIC", "-shared", "-Wall", "-Wno-sign-compare",
+           "-D__HIP_PLATFORM_AMD__", "-DUSE_ROCM", "-isystem", os.path.join(torch_dir, "include"),
+           "-isystem", os.path.join(torch_dir, "include", "torch", "csrc", "api", "include"),
+           "-isystem", os.path.join(rocm, "include"), "-I", sysconfig.get_paths()["include"], "-I", os.path.join(ROOT, "include"),
+           HOST_SRC, "-o", HOST_LIB, "-L", os.path.join(torch_dir, "lib"), "-ltorch_python", "-ltorch_hip", "-ltorch_cpu", "-ltorch",
+           "-lc10_hip", "-lc10", "-L", HERE, "-l:libna2d.so", "-Wl,-rpath,$ORIGIN"]
+    r = subprocess.run(cmd, capture_output=True, text=True)
+    if r.returncode != 0:
+        raise RuntimeError(f"host build failed:\n{r.stdout}\n{r.stderr}")
+    if r.stderr:
+        sys.stderr.write(r.stderr)
+
+
 def build_probe(force: bool = False, jobs: int | None = None) -> str:
     """The measurement build: the whole library with the arithmetic of the tiled contraction kernels left out."""
     os.makedirs(OBJ_DIR, exist_ok=True)
@@ -111,6 +135,7 @@ def build(force: bool = False, jobs: int | None = None) -> str:
         r = subprocess.run(cmd, capture_output=True, text=True)
         if r.returncode != 0:
             raise RuntimeError(f"link failed:\n{r.stdout}\n{r.stderr}")
+    _build_host(force)
     return LIB
 
 

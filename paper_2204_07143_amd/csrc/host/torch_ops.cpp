@@ -1,0 +1,379 @@
+// The differentiable operators of functional.py as native autograd nodes: argument checks, allocation and the calls of the C ABI
+// (na2d.h, na1d.h) without the interpreter in between.  Every gradient comes from the library's kernels, as there.
+//
+// Each function of the module returns the operator's output, or None where something is not as the plain case has it (a tensor that is
+// not dense on one GPU, shapes or types that do not fit, a functorch transform, forward-mode differentiation, tracing, a dispatch mode, a
+// call that the library refuses): the caller then takes the interpreted functions, which serve those or raise.  A pass of a small operator
+// is bound by this path, not by its kernels (us a pass of 1 x 8 x 14 x 14 fp16, k = 7, inference, and of 5 x 3 x 61 x 45 bf16, k = 5, without a
+// bias, forward and backward; through ctypes and Python's autograd functions / here: 20 / 6.4, 159 / 71; of the latter 34 are what a pass of any operator takes in autograd).
+#include <Python.h>
+
+#include <ATen/ATen.h>
+#include <ATen/FuncTorchTLS.h>
+#include <ATen/hip/impl/HIPStreamMasqueradingAsCUDA.h>
+#include <c10/core/impl/LocalDispatchKeySet.h>
+#include <torch/csrc/Exceptions.h>
+#include <torch/csrc/autograd/custom_function.h>
+#include <torch/csrc/autograd/forward_grad.h>
+#include <torch/csrc/autograd/python_variable.h>
+#include <torch/csrc/jit/frontend/tracer.h>
+
+#include <cmath>
+#include <limits>
+#include <optional>
+
+#include "na1d.h"
+#include "na2d.h"
+
+namespace {
+
+using at::Tensor;
+using torch::autograd::AutogradContext;
+using torch::autograd::variable_list;
+
+// ---- checks ------------------------------------------------------------------------------------------------------------
+
+// a strided tensor on a GPU with nothing wrapped around it
+bool plain(const Tensor &t) {
+    static const c10::DispatchKeySet allowed{c10::DispatchKey::CUDA, c10::DispatchKey::AutogradCUDA, c10::DispatchKey::ADInplaceOrView, c10::DispatchKey::AutocastCUDA};
+    return t.defined() && t.is_cuda() && (t.key_set() | allowed) == allowed;
+}
+bool plain_context() {
+    static const c10::DispatchKeySet modes{c10::DispatchKey::Python, c10::DispatchKey::PythonTLSSnapshot, c10::DispatchKey::PythonDispatcher,
+                                           c10::DispatchKey::FuncTorchDynamicLayerFrontMode, c10::DispatchKey::FuncTorchDynamicLayerBackMode,
+                                           c10::DispatchKey::Functionalize, c10::DispatchKey::Tracer, c10::DispatchKey::PreDispatch};
+    return !c10::impl::tls_local_dispatch_key_set().included_.has_any(modes) && !at::functorch::functorchTLSAccessor() &&
+           !torch::jit::tracer::isTracing() && !torch::autograd::ForwardADLevel::try_get_by_idx(0);
+}
+
+std::optional<int> dtype_code(at::ScalarType t) {
+    switch (t) {
+        case at::kFloat: return NA2D_F32;
+        case at::kHalf: return NA2D_F16;
+        case at::kBFloat16: return NA2D_BF16;
+        default: return std::nullopt;
+    }
+}
+bool fits(int64_t n) { return n >= 0 && n <= std::numeric_limits<int32_t>::max(); }
+
+std::optional<na2d_problem> problem_2d(at::IntArrayRef s, at::ScalarType type, int64_t k) {
+    const auto code = dtype_code(type);
+    if (s.size() != 5 || !code || !fits(k)) return std::nullopt;
+    for (int64_t n : s)
+        if (!fits(n)) return std::nullopt;
+    const na2d_problem p{(int32_t)s[0], (int32_t)s[1], (int32_t)s[2], (int32_t)s[3], (int32_t)s[4], (int32_t)k, *code};
+    return na2d_validate_problem(&p) == NA2D_OK ? std::optional(p) : std::nullopt;
+}
+std::optional<na1d_problem> problem_1d(at::IntArrayRef s, at::ScalarType type, int64_t k) {
+    const auto code = dtype_code(type);
+    if (s.size() != 4 || !code || !fits(k)) return std::nullopt;
+    for (int64_t n : s)
+        if (!fits(n)) return std::nullopt;
+    const na1d_problem p{(int32_t)s[0], (int32_t)s[1], (int32_t)s[2], (int32_t)s[3], (int32_t)k, *code};
+    return na1d_validate_problem(&p) == NA2D_OK ? std::optional(p) : std::nullopt;
+}
+// `t` (a tensor the operator takes beside `of`) is plain, on the same device, of the same type and of these sizes
+bool matches(const Tensor &t, const Tensor &of, at::IntArrayRef sizes) {
+    return plain(t) && t.scalar_type() == of.scalar_type() && t.device() == of.device() && t.sizes() == sizes;
+}
+
+// ---- calls -------------------------------------------------------------------------------------------------------------
+
+void *stream() {   // of the current device, as the interpreted binding takes it
+    return c10::hip::getCurrentHIPStreamMasqueradingAsCUDA().stream();
+}
+void *ptr(const Tensor &t) { return t.defined() ? t.data_ptr() : nullptr; }
+Tensor workspace(size_t bytes, const Tensor &like) { return at::empty({(int64_t)(bytes < 16 ? 16 : bytes)}, like.options().dtype(at::kByte)); }
+Tensor fp32(at::IntArrayRef sizes, const Tensor &like) { return at::empty(sizes, like.options().dtype(at::kFloat)); }
+
+// a call that the library refused inside a backward pass: the error the interpreted binding raises
+void check(int status) {
+    if (status == NA2D_OK) return;
+    const PyGILState_STATE gil = PyGILState_Ensure();
+    if (PyObject *m = PyImport_ImportModule("paper_2204_07143_amd.binding")) {
+        Py_XDECREF(PyObject_CallMethod(m, "_check", "i", status));
+        Py_DECREF(m);
+    }
+    python_error err;
+    if (PyErr_Occurred()) err.persist();
+    PyGILState_Release(gil);
+    throw std::move(err);
+}
+struct Refused {};   // a forward call that the library refused
+void forward_check(int status) {
+    if (status != NA2D_OK) throw Refused{};
+}
+
+bool wants_grad(std::initializer_list<const Tensor *> in) {
+    if (!at::GradMode::is_enabled()) return false;
+    for (const Tensor *t : in)
+        if (t->defined() && t->requires_grad()) return true;
+    return false;
+}
+
+// ---- the whole operator in 2D --------------------------------------------------------------------------------------------
+
+struct NA2D : torch::autograd::Function<NA2D> {
+    // lse: where the log-sum-exp is kept for the backward pass
+    static Tensor run(const Tensor &q, const Tensor &k, const Tensor &v, const Tensor &rpb, const na2d_problem &p, double scale, Tensor *lse) {
+        Tensor out = at::empty(q.sizes(), q.options());
+        if (lse) *lse = fp32(q.sizes().slice(0, 4), q);
+        forward_check(na2d_fused_fwd(&p, ptr(q), ptr(k), ptr(v), ptr(rpb), (float)scale, ptr(out), lse ? (float *)ptr(*lse) : nullptr, stream()));
+        return out;
+    }
+    static Tensor forward(AutogradContext *ctx, const Tensor &q_, const Tensor &k_, const Tensor &v_, const std::optional<Tensor> &rpb_, int64_t ks, double scale) {
+        const Tensor q = q_.contiguous(), k = k_.contiguous(), v = v_.contiguous(), rpb = rpb_ ? rpb_->contiguous() : Tensor();
+        Tensor lse;
+        Tensor out = run(q, k, v, rpb, *problem_2d(q.sizes(), q.scalar_type(), ks), scale, &lse);
+        ctx->save_for_backward({q, k, v, lse, rpb});
+        ctx->saved_data["k"] = ks;
+        ctx->saved_data["scale"] = scale;
+        ctx->saved_data["want"] = rpb_ && rpb_->requires_grad();
+        return out;
+    }
+    static variable_list backward(AutogradContext *ctx, variable_list grads) {
+        const auto saved = ctx->get_saved_variables();
+        const Tensor &q = saved[0], &k = saved[1], &v = saved[2], &lse = saved[3], &rpb = saved[4];
+        const float scale = (float)ctx->saved_data["scale"].toDouble();
+        const bool want = ctx->saved_data["want"].toBool();
+        const na2d_problem p = *problem_2d(q.sizes(), q.scalar_type(), ctx->saved_data["k"].toInt());
+        const Tensor dout = grads[0].contiguous();
+        Tensor dq = at::empty(q.sizes(), q.options()), dk = at::empty(q.sizes(), q.options()), dv = at::empty(q.sizes(), q.options());
+        Tensor d32 = want ? fp32(rpb.sizes(), q) : Tensor();
+        const size_t direct = na2d_direct_bwd_workspace_bytes(&p);   // 0: not for this problem
+        const Tensor ws = workspace(direct ? direct : na2d_workspace_bytes(&p, NA2D_WS_FUSED_BWD), q);
+        check((direct ? na2d_direct_bwd : na2d_fused_bwd)(&p, ptr(q), ptr(k), ptr(v), ptr(rpb), scale, (const float *)ptr(lse), ptr(dout), ptr(dq), ptr(dk), ptr(dv),
+                                                          (float *)ptr(d32), ptr(ws), (size_t)ws.numel(), stream()));
+        variable_list r{dq, dk, dv, want ? d32.to(rpb.scalar_type()) : Tensor()};
+        r.resize(6);
+        return r;
+    }
+};
+
+// ---- the whole operator in 1D --------------------------------------------------------------------------------------------
+
+struct NA1D : torch::autograd::Function<NA1D> {
+    static Tensor run(const Tensor &q, const Tensor &k, const Tensor &v, const Tensor &rpb, const na1d_problem &p, double scale, Tensor *lse) {
+        Tensor out = at::empty(q.sizes(), q.options());
+        if (lse) *lse = fp32(q.sizes().slice(0, 3), q);
+        forward_check(na1d_fused_fwd(&p, ptr(q), ptr(k), ptr(v), ptr(rpb), (float)scale, ptr(out), lse ? (float *)ptr(*lse) : nullptr, stream()));
+        return out;
+    }
+    static Tensor forward(AutogradContext *ctx, const Tensor &q_, const Tensor &k_, const Tensor &v_, const std::optional<Tensor> &rpb_, int64_t ks, double scale) {
+        const Tensor q = q_.contiguous(), k = k_.contiguous(), v = v_.contiguous(), rpb = rpb_ ? rpb_->contiguous() : Tensor();
+        Tensor lse;
+        Tensor out = run(q, k, v, rpb, *problem_1d(q.sizes(), q.scalar_type(), ks), scale, &lse);
+        ctx->save_for_backward({q, k, v, lse, rpb});
+        ctx->saved_data["k"] = ks;
+        ctx->saved_data["scale"] = scale;
+        ctx->saved_data["want"] = rpb_ && rpb_->requires_grad();
+        return out;
+    }
+    static variable_list backward(AutogradContext *ctx, variable_list grads) {
+        const auto saved = ctx->get_saved_variables();
+        const Tensor &q = saved[0], &k = saved[1], &v = saved[2], &lse = saved[3], &rpb = saved[4];
+        const bool want = ctx->saved_data["want"].toBool();
+        const na1d_problem p = *problem_1d(q.sizes(), q.scalar_type(), ctx->saved_data["k"].toInt());
+        const Tensor dout = grads[0].contiguous();
+        Tensor dq = at::empty(q.sizes(), q.options()), dk = at::empty(q.sizes(), q.options()), dv = at::empty(q.sizes(), q.options());
+        Tensor d32 = want ? fp32(rpb.sizes(), q) : Tensor();
+        const Tensor ws = workspace(na1d_fused_bwd_workspace_bytes(&p), q);
+        check(na1d_fused_bwd(&p, ptr(q), ptr(k), ptr(v), ptr(rpb), (float)ctx->saved_data["scale"].toDouble(), (const float *)ptr(lse), ptr(dout), ptr(dq), ptr(dk), ptr(dv),
+                             (float *)ptr(d32), ptr(ws), (size_t)ws.numel(), stream()));
+        variable_list r{dq, dk, dv, want ? d32.to(rpb.scalar_type()) : Tensor()};
+        r.resize(6);
+        return r;
+    }
+};
+
+// ---- the steps of the unfused operator ---------------------------------------------------------------------------------
+
+Tensor attention_like(const Tensor &q, int64_t ks) {
+    const auto s = q.sizes();
+    return at::empty({s[0], s[1], s[2], s[3], ks * ks}, q.options());
+}
+
+struct QKRPB : torch::autograd::Function<QKRPB> {
+    static Tensor forward(AutogradContext *ctx, const Tensor &q_, const Tensor &k_, const std::optional<Tensor> &rpb_, int64_t ks, double scale) {
+        const Tensor q = q_.contiguous(), k = k_.contiguous(), rpb = rpb_ ? rpb_->contiguous() : Tensor();
+        const na2d_problem p = *problem_2d(q.sizes(), q.scalar_type(), ks);
+        Tensor logits = attention_like(q, ks);
+        forward_check(na2d_qk_rpb(&p, ptr(q), ptr(k), ptr(rpb), (float)scale, ptr(logits), stream()));
+        ctx->save_for_backward({q, k});
+        ctx->saved_data["k"] = ks;
+        ctx->saved_data["scale"] = scale;
+        ctx->saved_data["want_q"] = q_.requires_grad();
+        ctx->saved_data["want_k"] = k_.requires_grad();
+        ctx->saved_data["want_rpb"] = rpb_ && rpb_->requires_grad();
+        ctx->saved_data["type"] = rpb_ ? rpb_->scalar_type() : q.scalar_type();
+        return logits;
+    }
+    static variable_list backward(AutogradContext *ctx, variable_list grads) {
+        const auto saved = ctx->get_saved_variables();
+        const Tensor &q = saved[0], &k = saved[1];
+        const int64_t ks = ctx->saved_data["k"].toInt();
+        const float scale = (float)ctx->saved_data["scale"].toDouble();
+        const na2d_problem p = *problem_2d(q.sizes(), q.scalar_type(), ks);
+        const Tensor ds = grads[0].contiguous();
+        Tensor dq, dk, d_rpb;
+        if (ctx->saved_data["want_q"].toBool()) {
+            dq = at::empty(q.sizes(), q.options());
+            check(na2d_qk_bwd_q(&p, ptr(ds), ptr(k), scale, ptr(dq), stream()));
+        }
+        if (ctx->saved_data["want_k"].toBool()) {
+            dk = at::empty(k.sizes(), k.options());
+            check(na2d_qk_bwd_k(&p, ptr(ds), ptr(q), scale, ptr(dk), stream()));
+        }
+        if (ctx->saved_data["want_rpb"].toBool()) {
+            Tensor d32 = fp32({q.size(1), 2 * ks - 1, 2 * ks - 1}, q);
+            const Tensor ws = workspace(na2d_workspace_bytes(&p, NA2D_WS_QK_BWD_RPB), q);
+            check(na2d_qk_bwd_rpb(&p, ptr(ds), (float *)ptr(d32), ptr(ws), (size_t)ws.numel(), stream()));
+            d_rpb = d32.to(ctx->saved_data["type"].toScalarType());
+        }
+        return {dq, dk, d_rpb, Tensor(), Tensor()};
+    }
+};
+
+struct AV : torch::autograd::Function<AV> {
+    static Tensor forward(AutogradContext *ctx, const Tensor &attn_, const Tensor &v_, int64_t ks) {
+        const Tensor attn = attn_.contiguous(), v = v_.contiguous();
+        const na2d_problem p = *problem_2d(v.sizes(), v.scalar_type(), ks);
+        Tensor out = at::empty(v.sizes(), v.options());
+        forward_check(na2d_av(&p, ptr(attn), ptr(v), ptr(out), stream()));
+        ctx->save_for_backward({attn, v});
+        ctx->saved_data["k"] = ks;
+        ctx->saved_data["want_attn"] = attn_.requires_grad();
+        ctx->saved_data["want_v"] = v_.requires_grad();
+        return out;
+    }
+    static variable_list backward(AutogradContext *ctx, variable_list grads) {
+        const auto saved = ctx->get_saved_variables();
+        const Tensor &attn = saved[0], &v = saved[1];
+        const na2d_problem p = *problem_2d(v.sizes(), v.scalar_type(), ctx->saved_data["k"].toInt());
+        const Tensor dout = grads[0].contiguous();
+        Tensor dattn, dv;
+        if (ctx->saved_data["want_attn"].toBool()) {
+            dattn = at::empty(attn.sizes(), attn.options());
+            check(na2d_av_bwd_p(&p, ptr(dout), ptr(v), ptr(dattn), stream()));
+        }
+        if (ctx->saved_data["want_v"].toBool()) {
+            dv = at::empty(v.sizes(), v.options());
+            check(na2d_av_bwd_v(&p, ptr(attn), ptr(dout), ptr(dv), stream()));
+        }
+        return {dattn, dv, Tensor()};
+    }
+};
+
+struct Softmax : torch::autograd::Function<Softmax> {
+    static Tensor forward(AutogradContext *ctx, const Tensor &logits_, at::IntArrayRef like, int64_t ks) {
+        const Tensor logits = logits_.contiguous();
+        const na2d_problem p = *problem_2d(like, logits.scalar_type(), ks);
+        Tensor attn = at::empty(logits.sizes(), logits.options());
+        forward_check(na2d_softmax(&p, ptr(logits), ptr(attn), stream()));
+        ctx->save_for_backward({attn});
+        ctx->saved_data["k"] = ks;
+        ctx->saved_data["like"] = like.vec();
+        return attn;
+    }
+    static variable_list backward(AutogradContext *ctx, variable_list grads) {
+        const Tensor attn = ctx->get_saved_variables()[0];
+        const na2d_problem p = *problem_2d(ctx->saved_data["like"].toIntVector(), attn.scalar_type(), ctx->saved_data["k"].toInt());
+        const Tensor dattn = grads[0].contiguous();
+        Tensor ds = at::empty(attn.sizes(), attn.options());
+        check(na2d_softmax_bwd(&p, ptr(attn), ptr(dattn), ptr(ds), stream()));
+        return {ds, Tensor(), Tensor()};
+    }
+};
+
+// ---- module ------------------------------------------------------------------------------------------------------------
+
+struct NoGil {
+    PyThreadState *state = PyEval_SaveThread();
+    ~NoGil() { PyEval_RestoreThread(state); }
+};
+
+// args[i] as a tensor; undefined for None where that is allowed.  false: it is neither.
+bool tensor_arg(PyObject *o, Tensor &t, bool optional = false) {
+    if (optional && o == Py_None) return true;
+    if (!THPVariable_Check(o)) return false;
+    t = THPVariable_Unpack(o);
+    return true;
+}
+std::optional<Tensor> maybe(const Tensor &t) { return t.defined() ? std::optional(t) : std::nullopt; }
+
+// BODY computes `out`; anything that the plain case does not have leaves it undefined
+template <typename Body> PyObject *guarded(Body body) {
+    HANDLE_TH_ERRORS
+    Tensor out;
+    {
+        NoGil no_gil;
+        try {
+            if (plain_context()) out = body();
+        } catch (const Refused &) {
+        }
+    }
+    if (!out.defined()) Py_RETURN_NONE;
+    return THPVariable_Wrap(std::move(out));
+    END_HANDLE_TH_ERRORS
+}
+
+// (q, k, v, rpb or None, kernel size, scale or None)
+struct Args {
+    Tensor q, k, v, rpb;
+    int64_t ks = 0;
+    double scale = 0;
+    bool ok = false;
+    Args(PyObject *const *a, Py_ssize_t n) {
+        if (n != 6 || !tensor_arg(a[0], q) || !tensor_arg(a[1], k) || !tensor_arg(a[2], v) || !tensor_arg(a[3], rpb, true)) return;
+        ks = PyLong_AsLongLong(a[4]);
+        scale = a[5] == Py_None ? (q.dim() > 0 ? std::pow((double)q.size(-1), -0.5) : 0.) : PyFloat_AsDouble(a[5]);
+        ok = !PyErr_Occurred();
+        if (!ok) PyErr_Clear();
+    }
+    bool check(at::IntArrayRef table) const {
+        return plain(q) && matches(k, q, q.sizes()) && matches(v, q, q.sizes()) && (!rpb.defined() || matches(rpb, q, table));
+    }
+};
+
+PyObject *py_na2d(PyObject *, PyObject *const *a, Py_ssize_t n) {
+    const Args x(a, n);
+    if (!x.ok) Py_RETURN_NONE;
+    return guarded([&]() -> Tensor {
+        const auto p = problem_2d(x.q.sizes(), x.q.scalar_type(), x.ks);
+        if (!p || !x.check({x.q.size(1), 2 * x.ks - 1, 2 * x.ks - 1})) return Tensor();
+        if (wants_grad({&x.q, &x.k, &x.v, &x.rpb})) return NA2D::apply(x.q, x.k, x.v, maybe(x.rpb), x.ks, x.scale);
+        return NA2D::run(x.q.contiguous(), x.k.contiguous(), x.v.contiguous(), x.rpb.defined() ? x.rpb.contiguous() : x.rpb, *p, x.scale, nullptr);
+    });
+}
+
+PyObject *py_na1d(PyObject *, PyObject *const *a, Py_ssize_t n) {
+    const Args x(a, n);
+    if (!x.ok) Py_RETURN_NONE;
+    return guarded([&]() -> Tensor {
+        const auto p = problem_1d(x.q.sizes(), x.q.scalar_type(), x.ks);
+        if (!p || !x.check({x.q.size(1), 2 * x.ks - 1})) return Tensor();
+        if (wants_grad({&x.q, &x.k, &x.v, &x.rpb})) return NA1D::apply(x.q, x.k, x.v, maybe(x.rpb), x.ks, x.scale);
+        return NA1D::run(x.q.contiguous(), x.k.contiguous(), x.v.contiguous(), x.rpb.defined() ? x.rpb.contiguous() : x.rpb, *p, x.scale, nullptr);
+    });
+}
+
+// QK + bias, softmax and AV as three differentiable steps
+PyObject *py_na2d_unfused(PyObject *, PyObject *const *a, Py_ssize_t n) {
+    const Args x(a, n);
+    if (!x.ok) Py_RETURN_NONE;
+    return guarded([&]() -> Tensor {
+        if (!problem_2d(x.q.sizes(), x.q.scalar_type(), x.ks) || !x.check({x.q.size(1), 2 * x.ks - 1, 2 * x.ks - 1})) return Tensor();
+        const Tensor logits = QKRPB::apply(x.q, x.k, maybe(x.rpb), x.ks, x.scale);
+        return AV::apply(Softmax::apply(logits, x.q.sizes(), x.ks), x.v, x.ks);
+    });
+}
+
+PyMethodDef methods[] = {{"na2d", (PyCFunction)(void (*)(void))py_na2d, METH_FASTCALL, nullptr},
+                         {"na1d", (PyCFunction)(void (*)(void))py_na1d, METH_FASTCALL, nullptr},
+                         {"na2d_unfused", (PyCFunction)(void (*)(void))py_na2d_unfused, METH_FASTCALL, nullptr},
+                         {nullptr, nullptr, 0, nullptr}};
+PyModuleDef module = {PyModuleDef_HEAD_INIT, "na2d_torch", nullptr, -1, methods, nullptr, nullptr, nullptr, nullptr};
+
+}  // namespace
+
+PyMODINIT_FUNC PyInit_na2d_torch() { return PyModule_Create(&module); }

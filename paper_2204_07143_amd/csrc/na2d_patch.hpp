@@ -305,4 +305,20 @@ struct PatchShape {
     FastDiv by_pitch;
 };
 
+// Host: positions per image row for tiles of `tw` columns on a map of `W`: what the widest tile's patches reach from the image's first
+// column, in whole pieces.  `first` and `last`: the first and the last position of the streamed operand that a position of the kept one
+// meets.  Tiles clear of both borders are alike: of those one is enough.
+template <typename First, typename Last> inline int image_row(int W, int K, int tw, int posb, First first, Last last) {
+    int rw = 0;
+    const int border = 2 * K + 2 * tw, skip_to = (W - border) / tw * tw;   // (at least a tile of the middle is looked at)
+    for (int px = 0; px < W; px += 4) {
+        if (px >= border + tw && px < skip_to) px = skip_to;
+        const int px3 = px + 3 < W - 1 ? px + 3 : W - 1, o = first(px);
+        const int e = o - first(px / tw * tw) + ((last(px3) - o + 4) & ~3);
+        rw = rw > e ? rw : e;
+    }
+    const int unit = 1024 / posb > 1 ? 1024 / posb : 1;
+    return (rw + unit - 1) / unit * unit;
+}
+
 }  // namespace na2d

@@ -722,18 +722,8 @@ PatchPlan patch_plan(const Problem &p, bool bias, bool dbias) {
     }
     const int tw = 4 << lg, th = 32 >> lg;
     const int tiles_x = (p.W + tw - 1) / tw, tiles_y = (p.H + th - 1) / th;
-    int rwq = 0, rwkv = 0;   // what the widest tile's patches reach from the image's first column
-    for (int px = 0; px < p.W; px += 4) {
-        const int px3 = px + 3 < p.W - 1 ? px + 3 : p.W - 1, tx = px / tw * tw;
-        const int oq = win_start(px, p.W, K), okv = inv_first(px, p.W, K);
-        const int eq = oq - win_start(tx, p.W, K) + ((win_start(px3, p.W, K) + K - oq + 3) & ~3);
-        const int ekv = okv - inv_first(tx, p.W, K) + ((inv_last(px3, p.W, K) - okv + 4) & ~3);
-        rwq = rwq > eq ? rwq : eq;
-        rwkv = rwkv > ekv ? rwkv : ekv;
-    }
-    const int unit = 1024 / posb > 1 ? 1024 / posb : 1;
-    rwq = (rwq + unit - 1) / unit * unit;
-    rwkv = (rwkv + unit - 1) / unit * unit;
+    const int rwq = image_row(p.W, K, tw, posb, [&](int x) { return win_start(x, p.W, K); }, [&](int x) { return win_start(x, p.W, K) + K - 1; });
+    const int rwkv = image_row(p.W, K, tw, posb, [&](int x) { return inv_first(x, p.W, K); }, [&](int x) { return inv_last(x, p.W, K); });
     UnitSplit us;
     us.units = tiles_x * tiles_y * p.heads;
     // more workgroups than fit at a time: those next to the borders have up to twice the work, and what waits fills the gaps

@@ -333,14 +333,7 @@ FwdPlan fwd_plan(const Problem &p, bool bias) {
         for (int lg = 3 - lgs; lg >= 0; --lg) {
             const int tw = 4 << lg, th = (32 >> lgs) >> lg, rows = th + K - 1 < p.H ? th + K - 1 : p.H;
             if (th > 16) continue;
-            int rw = 0;   // what the widest tile's patches reach from the image's first column
-            for (int px = 0; px < p.W; px += 4) {
-                const int px3 = px + 3 < p.W - 1 ? px + 3 : p.W - 1, o = win_start(px, p.W, K);
-                const int e = o - win_start(px / tw * tw, p.W, K) + ((win_start(px3, p.W, K) + K - o + 3) & ~3);
-                rw = rw > e ? rw : e;
-            }
-            const int unit = 1024 / posb > 1 ? 1024 / posb : 1;
-            rw = (rw + unit - 1) / unit * unit;
+            const int rw = image_row(p.W, K, tw, posb, [&](int x) { return win_start(x, p.W, K); }, [&](int x) { return win_start(x, p.W, K) + K - 1; });
             int lds;
             int n = image_buffers(table, 2 * step * rw * posb, lds);
             if (n == 2 && lgs > 0 && rows <= step) n = 1, lds = table + 2 * step * rw * posb;   // one step, one tile: nothing to load ahead

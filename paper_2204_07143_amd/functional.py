@@ -6,15 +6,39 @@ between them left to the framework (arXiv 2204.07143, Appendix A, "Implementatio
 through the fused forward and the fused backward, which keep the attention tensor out of memory.
 
 Only argument marshalling and buffer allocation happen here: every gradient comes from the
-library's kernels.  Tensors are ``[B, heads, H, W, D]`` (q, k, v, out), ``[B, heads, H, W, k*k]``
+library's kernels.  ``na2d``, ``na1d`` and ``na2d_unfused`` do it in native code (``na2d_torch.so``, from
+``csrc/host/torch_ops.cpp``): a call on small tensors takes longer in the interpreter than on the GPU.  The functions below
+serve ``na2d_qk_rpb``, ``na2d_av`` and ``na2d_softmax``, and whatever the native code hands back: invalid arguments (the
+binding's errors), functorch transforms, forward-mode differentiation, tracing, tensors that are not plain ones.  Tensors are ``[B, heads, H, W, D]`` (q, k, v, out), ``[B, heads, H, W, k*k]``
 (logits / attention weights) and ``[heads, 2k-1, 2k-1]`` (bias), contiguous, on the GPU; the
 library is loaded on first use and a missing library raises.
 """
 from __future__ import annotations
 
+import importlib.machinery
+import importlib.util
+import os
+
 import torch
 
 from . import binding as na
+
+_NATIVE_PATH = os.path.join(os.path.dirname(os.path.abspath(__file__)), "na2d_torch.so")
+_native_module = None
+
+
+def _native():
+    """The native operators, loaded on first use.  Raises if they or the library have not been built."""
+    global _native_module
+    if _native_module is None:
+        na.load()
+        if not os.path.exists(_NATIVE_PATH):
+            raise FileNotFoundError(f"{_NATIVE_PATH} is missing: build it with `python -m paper_2204_07143_amd.build`")
+        loader = importlib.machinery.ExtensionFileLoader("na2d_torch", _NATIVE_PATH)
+        module = importlib.util.module_from_spec(importlib.util.spec_from_loader("na2d_torch", loader))
+        loader.exec_module(module)
+        _native_module = module
+    return _native_module
 
 
 def _workspace(x: torch.Tensor, kernel_size: int, kind: int) -> torch.Tensor:
@@ -182,12 +206,14 @@ def na2d_av(attn, v, kernel_size: int):
 
 def na2d(q, k, v, rpb=None, kernel_size: int = 7, scale: float | None = None):
     """2D neighbourhood attention, fused; differentiable in q, k, v and rpb."""
-    return _NA2D.apply(q, k, v, rpb, int(kernel_size), _scale_of(q, scale))
+    out = _native().na2d(q, k, v, rpb, int(kernel_size), None if scale is None else float(scale))
+    return out if out is not None else _NA2D.apply(q, k, v, rpb, int(kernel_size), _scale_of(q, scale))
 
 
 def na1d(q, k, v, rpb=None, kernel_size: int = 7, scale: float | None = None):
     """1D neighbourhood attention ([B, heads, L, D]), fused; differentiable in q, k, v and rpb."""
-    return _NA1D.apply(q, k, v, rpb, int(kernel_size), _scale_of(q, scale))
+    out = _native().na1d(q, k, v, rpb, int(kernel_size), None if scale is None else float(scale))
+    return out if out is not None else _NA1D.apply(q, k, v, rpb, int(kernel_size), _scale_of(q, scale))
 
 
 def na2d_softmax(logits, like, kernel_size: int):
@@ -199,5 +225,8 @@ def na2d_softmax(logits, like, kernel_size: int):
 def na2d_unfused(q, k, v, rpb=None, kernel_size: int = 7, scale: float | None = None):
     """The same operator as the paper composes it: QK+RPB, softmax, AV; every step, forward and backward, is a
     library kernel."""
+    out = _native().na2d_unfused(q, k, v, rpb, int(kernel_size), None if scale is None else float(scale))
+    if out is not None:
+        return out
     logits = na2d_qk_rpb(q, k, rpb, kernel_size, scale)
     return na2d_av(na2d_softmax(logits, q, kernel_size), v, kernel_size)
