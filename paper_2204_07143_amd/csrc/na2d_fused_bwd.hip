@@ -29,14 +29,18 @@ template <typename T> __device__ __forceinline__ uint32_t pack2_t(float a, float
 // each; a workgroup keeps one tile position and one head and walks a range of the batch, so the
 // window mask, the bias table and every address are built once; the key and the value halo of a
 // tile reach one of two LDS buffer pairs by direct loads while the previous tile is computed.
-// Two sweeps over the 16-position blocks of the patch halo.  Both evaluate
+// Two sweeps over the 16-position blocks of the patch halo.  The first evaluates
 //   S^T = K_blk Q^T, dP^T = V_blk dout^T    (keys / values as 16-byte A operands, q / dout of the lane's
 //                                            query as B operand)
-// the first only to sum delta = sum P dP (a query's positions are spread over 4 lanes: two cross-lane
-// steps), the second for
+// for P, which stays in registers, and delta = sum P dP (a query's positions are spread over 4 lanes: two
+// cross-lane steps), the second dP^T once more for
 //   dS^T = P (dP - delta)                    in registers, already in the B-operand layout of
 //   dq^T += K_blk^T dS^T                     the half-depth MFMA (keys through the transposing LDS read).
-// Recomputing the two products is cheaper than keeping P and dP of the whole halo in registers.
+// The kernel is bound by vector instructions (75 % of the issue slots at 64 x 2 x 56 x 56, K = 7, f16, with both
+// products and the exponential in both sweeps): P costs 3 + 1 of them per result and one register to keep, dP one
+// MFMA and one LDS read per 16 x 16 block to evaluate again.  Each block's operands are read from LDS one block
+// ahead, and ahead of the table adds, since a wave's LDS operations return in order.  Together with a bound of |dP|
+// in one instruction per two results: 54.7 -> 45.4 us there, 36 -> 32 us at bf16 128 x 8 x 14 x 14.
 // Every dS is also added to its cell of a (2K-1)^2 table in LDS (Eq. 2's B differentiated: the bias cell of a
 // (query, position) pair depends on their offset only).  The tables are 64-bit fixed point with 32 fraction
 // bits and the adds are integer atomics: on this chip an LDS integer add costs a few cycles per wave
@@ -242,25 +246,36 @@ __global__ __launch_bounds__(512, 4) void fbwd_q_kernel(const T *__restrict__ q,
         // the planes and take 28 registers instead of 14
 #pragma unroll
         for (int e = 0; e < P::NEL / 2; ++e) asm volatile("" : "+v"(biasm[e]));
-        auto block = [&](int bk, f32x4 &sacc, f32x4 &pacc) {
-            const int ra = koff[bk] + PAR * C::kStageBytes;
-            const u32x4 ak = *lds_ptr<u32x4>(ra);
-            const u32x4 av = *lds_ptr<u32x4>(ra + C::kHaloBytes);
-            sacc = mfma_16x16x32<T>(ak, qreg, f32x4{0.f, 0.f, 0.f, 0.f});
-            pacc = mfma_16x16x32<T>(av, dreg, f32x4{0.f, 0.f, 0.f, 0.f});
-        };
+        auto key_rows = [&](int bk) { return *lds_ptr<u32x4>(koff[bk] + PAR * C::kStageBytes); };
+        auto value_rows = [&](int bk) { return *lds_ptr<u32x4>(koff[bk] + PAR * C::kStageBytes + C::kHaloBytes); };
         auto weight = [&](int e, float sv) {   // P of result e, 0 outside the window (bias -inf)
             return __builtin_amdgcn_exp2f(__builtin_fmaf(__builtin_fmaf(scale, sv, (float)biasm[e >> 1][e & 1]), kLog2e, -lse2));
         };
-        // sweep 1: delta
+        // sweep 1: P, delta
         float delta = 0.f, dpmax = 0.f;
+        float pw[P::NEL];
+        constexpr bool kAhead = K <= 7;   // operands one block ahead: up to 123 of the 128 registers; K = 9 has none to spare
+        u32x4 kr, vr;
+        if constexpr (kAhead) kr = key_rows(0), vr = value_rows(0);
 #pragma unroll
         for (int bk = 0; bk < P::NBLK; ++bk) {
-            f32x4 sacc, pacc;
-            block(bk, sacc, pacc);
+            if constexpr (!kAhead) kr = key_rows(bk), vr = value_rows(bk);
+            const f32x4 sacc = mfma_16x16x32<T>(kr, qreg, f32x4{0.f, 0.f, 0.f, 0.f});
+            const f32x4 pacc = mfma_16x16x32<T>(vr, dreg, f32x4{0.f, 0.f, 0.f, 0.f});
+            if constexpr (kAhead) {
+                if (bk + 1 < P::NBLK) kr = key_rows(bk + 1);
+                vr = value_rows(bk + 1 < P::NBLK ? bk + 1 : 0);
+                __builtin_amdgcn_sched_barrier(0);
+            }
 #pragma unroll
-            for (int r = 0; r < 4; ++r) delta = __builtin_fmaf(weight(4 * bk + r, sacc[r]), pacc[r], delta);
-            if constexpr (RPB) dpmax = fmaxf(fmaxf(dpmax, fmaxf(fabsf(pacc[0]), fabsf(pacc[1]))), fmaxf(fabsf(pacc[2]), fabsf(pacc[3])));
+            for (int r = 0; r < 4; ++r) {
+                pw[4 * bk + r] = weight(4 * bk + r, sacc[r]);
+                delta = __builtin_fmaf(pw[4 * bk + r], pacc[r], delta);
+            }
+            if constexpr (RPB) {
+#pragma unroll
+                for (int r = 0; r < 4; ++r) dpmax = __builtin_elementwise_maximum(dpmax, __builtin_fabsf(pacc[r]));
+            }
             __builtin_amdgcn_sched_barrier(0);   // keeps the blocks from being evaluated all at once
         }
         delta += __shfl_xor(delta, 16);
@@ -274,17 +289,21 @@ __global__ __launch_bounds__(512, 4) void fbwd_q_kernel(const T *__restrict__ q,
             fx_shift = fx_shift < 0 ? 0 : (fx_shift > 32 ? 32 : fx_shift);
             fx_scale = __builtin_ldexpf(1.f, C::kFracBits - fx_shift);
         }
-        // sweep 2: dS, dq (one block at a time: the half-depth MFMA takes the four positions a lane holds)
+        // sweep 2: dP again, dS, dq (one block at a time: the half-depth MFMA takes the four positions a lane holds)
         f32x4 o[2] = {f32x4{0.f, 0.f, 0.f, 0.f}, f32x4{0.f, 0.f, 0.f, 0.f}};
 #pragma unroll
         for (int bk = 0; bk < P::NBLK; ++bk) {
-            f32x4 sacc, pacc;
-            block(bk, sacc, pacc);
+            if constexpr (!kAhead) vr = value_rows(bk);
+            const f32x4 pacc = mfma_16x16x32<T>(vr, dreg, f32x4{0.f, 0.f, 0.f, 0.f});
+            if (kAhead && bk + 1 < P::NBLK) vr = value_rows(bk + 1);
+            const int ta = tr_addr(lv, bk) + PAR * C::kStageBytes;
+            const u32x2 kt[2] = {lds_read_tr16(ta), lds_read_tr16(ta + 8)};
+            __builtin_amdgcn_sched_barrier(0);   // the reads ahead of the adds: a wave's LDS operations return in order
             float dsv[4];
 #pragma unroll
             for (int r = 0; r < 4; ++r) {
                 const int e = 4 * bk + r;
-                dsv[r] = weight(e, sacc[r]) * (pacc[r] - delta);   // exactly 0 outside the window
+                dsv[r] = pw[e] * (pacc[r] - delta);   // exactly 0 outside the window
                 if constexpr (RPB) {
                     const long long fx = (long long)(int)(dsv[r] * fx_scale) << fx_shift;   // truncated, saturating; NaN -> 0
                     __hip_atomic_fetch_add(lds_ptr<unsigned long long>(mytbl + coff[bk] + 8 * r),
@@ -292,10 +311,9 @@ __global__ __launch_bounds__(512, 4) void fbwd_q_kernel(const T *__restrict__ q,
                 }
             }
             const uint32_t b0 = pack2_t<T>(dsv[0], dsv[1]), b1 = pack2_t<T>(dsv[2], dsv[3]);
-            const int ta = tr_addr(lv, bk) + PAR * C::kStageBytes;
 #pragma unroll
             for (int hf = 0; hf < 2; ++hf) {
-                const u32x2 a2 = lds_read_tr16(ta + hf * 8);
+                const u32x2 a2 = kt[hf];
                 o[hf] = mfma_16x16x16<T>(a2.x, a2.y, b0, b1, o[hf]);
                 if constexpr (Traits<T>::kDtype == NA2D_BF16) {
                     // bf16 keeps 8 significant bits: a second operand carries the rounding remainder of dS so
