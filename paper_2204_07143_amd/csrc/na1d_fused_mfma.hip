@@ -1,0 +1,240 @@
+// Fused 1D neighbourhood attention forward on the matrix cores, f16 / bf16 (arXiv 2204.07143, Section 3.1, Eq. 2-4 on a sequence).
+//
+// The windows of 16 consecutive queries reach 16 + k - 1 consecutive keys: NBLK = ceil((k + 15) / 16) blocks of 16, counted from the first
+// query's window, hold them (2 to 5 for k = 3 .. 63).  Per group of 16 queries
+//   S^T = K_blk Q^T                 one full-depth MFMA per block (a lane holds four keys of its query)
+//   P = exp2(S' + bias - max)       the bias, -inf outside the window, stays in registers: it is the same for every group
+//                                   whose windows are clear of the sequence's ends
+//   out^T += V_blk^T P              values through the transposing LDS read
+// P enters the product as two 16-bit halves, its value rounded and the rounding's remainder, so that it counts with 22 (fp16) or 16 (bf16)
+// digits; in fp16 it is scaled by 2^15 first, for the remainder not to fall below the type's smallest numbers.
+// A workgroup of four waves keeps 64 GPW queries; the keys and values they reach go to LDS by direct loads, all at once.  One group per
+// wave (GPW 1) is for calls whose tiles of four would not fill the chip.
+// A masked product is 0 * x: where a value is not finite it would spoil queries whose window does not hold it, so results that are not
+// finite are computed once more from their own window.
+// Bound by memory: 64 x 2 x 3136 queries (103 MB) take 18.7 us in fp16 at k = 7, 19.7 us in bf16 at k = 31 and 23.5 us at k = 63, 4.4 to
+// 5.5 TB/s; a thread per query with its products on the plain ALU took 24.6, 51.2 and 105 us.
+#include "lds_attr.hpp"
+#include "na1d_kernels.hpp"
+#include "na2d_kernels.hpp"   // the dtype constants
+#include "na2d_mfma.hpp"
+
+namespace na1d {
+
+using namespace na2d;
+
+namespace {
+
+constexpr int kWaves = 4, kThreads = kWaves * kWave, kGroup = 16, kBytes = 64;   // queries of a group, bytes of a head vector
+constexpr float kLog2e = 1.4426950408889634f, kLn2 = 0.6931471805599453f;
+
+template <typename T> __device__ __forceinline__ uint32_t pack2(float a, float b) {
+    typedef float f32x2_t __attribute__((ext_vector_type(2)));
+    typedef T tx2_t __attribute__((ext_vector_type(2)));
+    return __builtin_bit_cast(uint32_t, __builtin_convertvector((f32x2_t){a, b}, tx2_t));
+}
+// x rounded to T (two per word) and what the rounding left
+template <typename T> __device__ __forceinline__ void split2(float a, float b, uint32_t &hi, uint32_t &lo) {
+    typedef T tx2_t __attribute__((ext_vector_type(2)));
+    hi = pack2<T>(a, b);
+    const tx2_t h = __builtin_bit_cast(tx2_t, hi);
+    lo = pack2<T>(a - (float)h[0], b - (float)h[1]);
+}
+
+template <int NBLK, int GPW> struct Cfg {
+    static constexpr int TQ = kWaves * GPW * kGroup, ROWS = TQ - kGroup + 16 * NBLK;   // queries, keys staged
+    static constexpr int kImage = ROWS * kBytes;
+    static constexpr int kLds = 2 * kImage;   // and 2 K - 1 floats of bias
+};
+
+// One query from its own window, as plain sums: lane group g keeps channels 8 g .. 8 g + 7.
+template <typename T>
+__device__ void query_once_more(const T *q, const T *k, const T *v, const T *rpb, float scale, int i, int L, int K, int g, float (&acc)[8], float &lse) {
+    const int s = win_start(i, L, K);
+    Vec32<T> qv, kv;
+    load_vec32(qv, reinterpret_cast<const char *>(q) + (size_t)i * kBytes);
+    float m = -INFINITY, l = 0.f;
+#pragma unroll
+    for (int d = 0; d < 8; ++d) acc[d] = 0.f;
+    for (int a = 0; a < K; ++a) {
+        load_vec32(kv, reinterpret_cast<const char *>(k) + (size_t)(s + a) * kBytes);
+        const float sv = __builtin_fmaf(scale * kLog2e, dot32(qv, kv), rpb ? to_f32(rpb[s + a - i + K - 1]) * kLog2e : 0.f);
+        const float mn = fmaxf(m, sv), c = __builtin_amdgcn_exp2f(m - mn), p = __builtin_amdgcn_exp2f(sv - mn);
+        l = __builtin_fmaf(l, c, p);
+#pragma unroll
+        for (int d = 0; d < 8; ++d) acc[d] = __builtin_fmaf(p, to_f32(v[(size_t)(s + a) * kHeadDim + 8 * g + d]), acc[d] * c);
+        m = mn;
+    }
+#pragma unroll
+    for (int d = 0; d < 8; ++d) acc[d] *= 1.f / l;
+    lse = (m + __builtin_amdgcn_logf(l)) * kLn2;
+}
+
+template <typename T, int NBLK, int GPW>
+__global__ __launch_bounds__(kThreads, 4) void fused1d_mfma_kernel(const T *__restrict__ q, const T *__restrict__ k, const T *__restrict__ v,
+                                                                   const T *__restrict__ rpb, float scale, T *__restrict__ out,
+                                                                   float *__restrict__ lse, int L, int heads, int K, int tiles) {
+    using C = Cfg<NBLK, GPW>;
+    constexpr float kShift = sizeof(T) == 2 && Traits<T>::kDtype == NA2D_F16 ? 15.f : 0.f;
+    extern __shared__ __align__(16) char lds[];
+    const int tid = threadIdx.x, lane = tid % kWave, wave = __builtin_amdgcn_readfirstlane(tid / kWave), j = lane & 15, g = lane >> 4;
+    const int plane = blockIdx.x / tiles, t0 = (blockIdx.x - plane * tiles) * C::TQ, NB = 2 * K - 1;
+    const size_t first = (size_t)plane * L;
+    const int h0 = win_start(t0, L, K), img = lds_addr(lds);
+    float *bias = reinterpret_cast<float *>(lds + C::kLds);
+
+    // keys and values from h0 on, 16 to a piece (past the end of the sequence the last one again: its weights are 0)
+    {
+        const char *kb = reinterpret_cast<const char *>(k) + (first + h0) * kBytes, *vb = reinterpret_cast<const char *>(v) + (first + h0) * kBytes;
+        const int last = L - 1 - h0;
+#pragma unroll
+        for (int p0 = 0; p0 < C::ROWS / 16; p0 += kWaves) {
+            const int p = p0 + wave;
+            if (p < C::ROWS / 16) {
+                const int row = p * 16 + (lane >> 2), at = row < last ? row : last;
+                global_to_lds_16(kb, (unsigned)(at * kBytes + (lane & 3) * 16), img + p * 1024);
+                global_to_lds_16(vb, (unsigned)(at * kBytes + (lane & 3) * 16), img + C::kImage + p * 1024);
+            }
+        }
+    }
+    u32x4 qv[GPW];
+#pragma unroll
+    for (int n = 0; n < GPW; ++n) {
+        const int i = t0 + (wave * GPW + n) * kGroup + j;
+        qv[n] = *reinterpret_cast<const u32x4 *>(reinterpret_cast<const char *>(q) + (first + (i < L ? i : L - 1)) * kBytes + g * 16);
+    }
+    const T *table = rpb ? rpb + (size_t)(plane % heads) * NB : nullptr;
+    for (int u = tid; u < NB; u += kThreads) bias[u] = table ? to_f32(table[u]) * kLog2e : 0.f;
+    wait_global_loads();
+    workgroup_sync();
+
+    const float scale2 = scale * kLog2e;
+    float b[NBLK][4];
+    bool inner = false;   // b[] is that of a group clear of the ends
+#pragma unroll
+    for (int n = 0; n < GPW; ++n) {
+        const int i0 = t0 + (wave * GPW + n) * kGroup;
+        if (i0 >= L) break;
+        const int o = win_start(i0, L, K), i = i0 + j < L ? i0 + j : L - 1;
+        const bool clear = o == i0 - (K >> 1) && i0 + kGroup - 1 + (K >> 1) < L;
+        if (!(clear && inner)) {
+            const int w = win_start(i, L, K) - o;   // the lane's window begins at position w of the blocks
+#pragma unroll
+            for (int c = 0; c < NBLK; ++c)
+#pragma unroll
+                for (int r = 0; r < 4; ++r) {
+                    const int at = 16 * c + 4 * g + r;
+                    const bool in = (unsigned)(at - w) < (unsigned)K;
+                    const float t = bias[in ? at + o - i + K - 1 : 0];
+                    b[c][r] = in ? t : -INFINITY;
+                }
+            inner = clear;
+        }
+        const int kaddr = img + (o - h0 + j) * kBytes + g * 16, vaddr = img + C::kImage + (o - h0 + 4 * g + (j >> 2)) * kBytes + (j & 3) * 16;
+        f32x4 s[NBLK];
+#pragma unroll
+        for (int c = 0; c < NBLK; ++c) s[c] = mfma_16x16x32<T>(*lds_ptr<u32x4>(kaddr + c * 1024), qv[n], f32x4{0.f, 0.f, 0.f, 0.f});
+        float m = -INFINITY;
+#pragma unroll
+        for (int c = 0; c < NBLK; ++c)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                s[c][r] = __builtin_fmaf(scale2, s[c][r], b[c][r]);
+                m = fmaxf(m, s[c][r]);
+            }
+        m = fmaxf(m, __shfl_xor(m, 16));
+        m = fmaxf(m, __shfl_xor(m, 32)) - kShift;
+        float l = 0.f;
+        uint32_t hi[NBLK][2], lo[NBLK][2];
+#pragma unroll
+        for (int c = 0; c < NBLK; ++c) {
+            float p[4];
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                p[r] = __builtin_amdgcn_exp2f(s[c][r] - m);
+                l += p[r];
+            }
+            split2<T>(p[0], p[1], hi[c][0], lo[c][0]);
+            split2<T>(p[2], p[3], hi[c][1], lo[c][1]);
+        }
+        l += __shfl_xor(l, 16);
+        l += __shfl_xor(l, 32);
+        f32x4 acc[2] = {f32x4{0.f, 0.f, 0.f, 0.f}, f32x4{0.f, 0.f, 0.f, 0.f}};
+#pragma unroll
+        for (int c = 0; c < NBLK; c += 2)
+#pragma unroll
+            for (int hf = 0; hf < 2; ++hf) {
+                const u32x2 v0 = lds_read_tr16(vaddr + c * 1024 + hf * 8);
+                if (c + 1 < NBLK) {
+                    const u32x2 v1 = lds_read_tr16(vaddr + (c + 1) * 1024 + hf * 8);
+                    const u32x4 a{v0.x, v0.y, v1.x, v1.y};
+                    const int d = c + 1 < NBLK ? c + 1 : c;
+                    acc[hf] = mfma_16x16x32<T>(a, u32x4{lo[c][0], lo[c][1], lo[d][0], lo[d][1]}, acc[hf]);
+                    acc[hf] = mfma_16x16x32<T>(a, u32x4{hi[c][0], hi[c][1], hi[d][0], hi[d][1]}, acc[hf]);
+                } else {
+                    acc[hf] = mfma_16x16x16<T>(v0.x, v0.y, lo[c][0], lo[c][1], acc[hf]);
+                    acc[hf] = mfma_16x16x16<T>(v0.x, v0.y, hi[c][0], hi[c][1], acc[hf]);
+                }
+            }
+        const float inv = 1.f / l;
+        float x[8], log_sum = (m + __builtin_amdgcn_logf(l)) * kLn2, odd = log_sum * 0.f;   // odd: NaN where something is not finite
+#pragma unroll
+        for (int d = 0; d < 8; ++d) {
+            x[d] = acc[d >> 2][d & 3] * inv;
+            odd = __builtin_fmaf(x[d], 0.f, odd);
+        }
+        const unsigned long long again = __ballot(odd != odd);
+        if (again) {
+            const unsigned cols = (unsigned)((again | (again >> 16) | (again >> 32) | (again >> 48)) & 0xffffu);
+            if ((cols >> j) & 1u)
+                query_once_more<T>(q + first * kHeadDim, k + first * kHeadDim, v + first * kHeadDim, table, scale, i, L, K, g, x, log_sum);
+        }
+        if (i0 + j < L) {
+            store16_stream(reinterpret_cast<char *>(out) + (first + i) * kBytes + g * 16,
+                           u32x4{pack2<T>(x[0], x[1]), pack2<T>(x[2], x[3]), pack2<T>(x[4], x[5]), pack2<T>(x[6], x[7])});
+            if (lse != nullptr && g == 0) lse[first + i] = log_sum;
+        }
+    }
+}
+
+template <typename T, int NBLK, int GPW>
+hipError_t launch_t(const Problem &p, const void *q, const void *k, const void *v, const void *rpb, float scale, void *out, float *lse, hipStream_t s) {
+    using C = Cfg<NBLK, GPW>;
+    auto kern = fused1d_mfma_kernel<T, NBLK, GPW>;
+    constexpr int kMost = C::kLds + (2 * kMaxK - 1) * 4;
+    static LdsAllowed allowed;
+    if (hipError_t e = allow_lds(kern, kMost, allowed); e != hipSuccess) return e;
+    const int tiles = (p.L + C::TQ - 1) / C::TQ;
+    hipLaunchKernelGGL(kern, dim3(p.planes() * tiles), dim3(kThreads), C::kLds + (2 * p.K - 1) * 4, s, static_cast<const T *>(q),
+                       static_cast<const T *>(k), static_cast<const T *>(v), static_cast<const T *>(rpb), scale, static_cast<T *>(out), lse,
+                       p.L, p.heads, p.K, tiles);
+    return hipGetLastError();
+}
+
+template <typename T, int NBLK>
+hipError_t launch_groups(const Problem &p, const void *q, const void *k, const void *v, const void *rpb, float scale, void *out, float *lse, hipStream_t s) {
+    // four groups to a wave stage 64 GPW + 16 NBLK - 16 keys for 64 GPW queries where one group stages twice what it needs and more; from two
+    // tiles per compute unit on that counts more than the longer chain of a wave (small calls are below the launch's own time either way)
+    const size_t tiles = (size_t)p.planes() * ((p.L + 4 * kWaves * kGroup - 1) / (4 * kWaves * kGroup));
+    return tiles >= 512 ? launch_t<T, NBLK, 4>(p, q, k, v, rpb, scale, out, lse, s) : launch_t<T, NBLK, 1>(p, q, k, v, rpb, scale, out, lse, s);
+}
+
+template <typename T>
+hipError_t launch_blocks(const Problem &p, const void *q, const void *k, const void *v, const void *rpb, float scale, void *out, float *lse, hipStream_t s) {
+    switch ((p.K + 15 + 15) / 16) {   // (k from 3 to 63)
+        case 2: return launch_groups<T, 2>(p, q, k, v, rpb, scale, out, lse, s);
+        case 3: return launch_groups<T, 3>(p, q, k, v, rpb, scale, out, lse, s);
+        case 4: return launch_groups<T, 4>(p, q, k, v, rpb, scale, out, lse, s);
+        case 5: return launch_groups<T, 5>(p, q, k, v, rpb, scale, out, lse, s);
+    }
+    return hipErrorInvalidValue;
+}
+
+}  // namespace
+
+hipError_t launch_fused_fwd_16bit(const Problem &p, const void *q, const void *k, const void *v, const void *rpb, float scale, void *out,
+                                  float *lse, hipStream_t s) {
+    return p.dtype == NA2D_F16 ? launch_blocks<f16_t>(p, q, k, v, rpb, scale, out, lse, s) : launch_blocks<bf16_t>(p, q, k, v, rpb, scale, out, lse, s);
+}
+
+}  // namespace na1d

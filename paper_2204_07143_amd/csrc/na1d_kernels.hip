@@ -2,8 +2,8 @@
 // the gradients the paper lists for its package -- q, k, b, a, v -- Appendix A).
 //
 // Per query the 1D operator moves 2*D*e + k*e bytes for 2*k*D flops (3 flop/B at k = 7, f16): far below
-// any arithmetic ridge of the chip, so these kernels are plain-ALU streaming kernels and the matrix
-// cores are not used.  What matters is that every byte crosses HBM once and in 16-byte pieces:
+// any arithmetic ridge of the chip, so these kernels are plain-ALU streaming kernels (in 16 bit the fused
+// forward's products on the plain ALU took longer than its memory traffic: na1d_fused_mfma.hip).  What matters is that every byte crosses HBM once and in 16-byte pieces:
 //   * a workgroup owns TQ consecutive positions of one (batch, head) plane; the union of their windows
 //     (TQ + k - 1 keys; TQ + 2(k-1) queries for the inverse neighbourhood) is staged in LDS once with
 //     coalesced 16-byte loads, a padded per-key stride keeping the later 16-byte LDS reads conflict-free;
@@ -703,8 +703,8 @@ static hipError_t fused_t(const Problem &p, const void *q, const void *k, const 
 }
 hipError_t launch_fused_fwd(const Problem &p, const void *q, const void *k, const void *v, const void *rpb, float scale,
                             void *out, float *lse, hipStream_t s) {
-    NA1D_DISPATCH(p, return (fused_t<T, TQ>(p, q, k, v, rpb, scale, out, lse, s)));
-    return hipErrorInvalidValue;
+    if (p.dtype != NA2D_F32) return launch_fused_fwd_16bit(p, q, k, v, rpb, scale, out, lse, s);
+    return p.K <= 31 ? fused_t<float, 256>(p, q, k, v, rpb, scale, out, lse, s) : fused_t<float, 128>(p, q, k, v, rpb, scale, out, lse, s);
 }
 
 static int rpb_tiles(const Problem &p) { return p.K <= 31 ? tiles_of<256>(p) : tiles_of<128>(p); }

@@ -26,6 +26,8 @@ hipError_t launch_softmax(const Problem &p, const void *logits, void *out, hipSt
 hipError_t launch_softmax_bwd(const Problem &p, const void *attn, const void *dp, void *ds, hipStream_t s);
 hipError_t launch_fused_fwd(const Problem &p, const void *q, const void *k, const void *v, const void *rpb, float scale,
                             void *out, float *lse, hipStream_t s);
+hipError_t launch_fused_fwd_16bit(const Problem &p, const void *q, const void *k, const void *v, const void *rpb, float scale,
+                                  void *out, float *lse, hipStream_t s);   // f16 / bf16
 size_t rpb_workspace_bytes(const Problem &p);
 hipError_t launch_rpb_grad(const Problem &p, const void *ds, float *d_rpb, void *workspace, hipStream_t s);
 // whole backward from q, k, v, rpb, dout and the forward's log-sum-exp (no k-wide tensor in memory)
