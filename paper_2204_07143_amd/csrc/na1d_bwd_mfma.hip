@@ -1,0 +1,404 @@
+// Fused 1D neighbourhood attention backward on the matrix cores, f16 / bf16 (arXiv 2204.07143: Eq. 2-4 differentiated, on a sequence):
+// dq, dk, dv and the bias gradient from q, k, v, dout and the forward's log-sum-exp, in groups of 16 positions against blocks of 16 as in the
+// fused forward.
+//   P[i, j] = exp(scale <q_i, k_j> + B(i, j) - lse_i)   dP[i, j] = <dout_i, v_j>   delta_i = sum_j P dP   dS = P (dP - delta_i)
+// Query side: 16 queries, the NBLK = ceil((k + 15) / 16) blocks of keys their windows reach; P and dP stay in registers, so that one sweep gives
+// delta and dq_i = scale sum_j dS k_j.  Key side: 16 keys and the queries that see them, NBLK blocks at a time (clear of the ends that is all of
+// them): dv_j = sum_i P dout_i, dk_j = scale sum_i dS q_i.
+// P and dS enter the sums as two 16-bit halves (22 digits in fp16, 16 in bf16).  In fp16 a column's dS are scaled by the power of two that
+// brings the largest near 2^15, so that the result does not depend on the scale of dout.
+// Bias gradient: clear of the ends a lane's cells are the same for each of its groups, so that it adds them up in registers; then they join
+// the workgroup's table as 64-bit fixed-point integers (integer additions commute: the result is bitwise reproducible).
+// A masked product is 0 * x: results that are not finite are computed once more from their own window.
+// Measured at 64 x 2 x 3136 queries, fp16, query side + key side (a thread per position on the plain ALU before): k = 7 24.1 + 29.5 us
+// (38.8 + 33.5), bound by memory at 5.3 TB/s; k = 31 26.8 + 32.8; k = 63 35.8 + 44.3, where the vector instructions of 5 blocks show.
+#include "lds_attr.hpp"
+#include "na1d_common.hpp"
+#include "na1d_kernels.hpp"
+
+namespace na1d {
+
+using namespace na2d;
+
+namespace {
+
+constexpr int kWaves = 4, kThreads = kWaves * kWave, kGroups = 4;   // groups per wave
+constexpr int kTile = kWaves * kGroups * kGroup;
+static_assert(kTile == 256, "the partial bias gradients are one per 256 positions");
+
+__host__ __device__ constexpr int up16(int n) { return (n + 15) & ~15; }
+
+// the power of two that brings `most` near 2^15, as an exponent
+__device__ __forceinline__ int lift(float most) {
+    const int e = 15 - __builtin_amdgcn_frexp_expf(most);
+    return e < 100 ? e : 100;   // (2^100 and its inverse are floats)
+}
+
+template <typename T> struct Plane {
+    const T *q, *k, *v, *dout, *rpb;   // rpb: the head's table or null
+};
+// (in pieces of eight channels: the results of a group stay in registers meanwhile)
+template <typename T> __device__ __forceinline__ float dot_memory(const T *a, const T *b) {
+    float acc = 0.f;
+#pragma unroll 1
+    for (int d = 0; d < kHeadDim; d += 8) {
+        VecN<T, 8> x, y;
+        load_vec32(x, a + d);
+        load_vec32(y, b + d);
+        acc += dot32(x, y);
+    }
+    return acc;
+}
+template <typename T>
+__device__ __forceinline__ void pair_weight(const Plane<T> &m, float scale, int i, int key, int K, float lse2, float &p, float &dp) {
+    const float t = m.rpb ? to_f32(m.rpb[key - i + K - 1]) * kLog2e : 0.f;
+    p = __builtin_amdgcn_exp2f(__builtin_fmaf(scale * kLog2e, dot_memory(m.q + (size_t)i * kHeadDim, m.k + (size_t)key * kHeadDim), t) - lse2);
+    dp = dot_memory(m.dout + (size_t)i * kHeadDim, m.v + (size_t)key * kHeadDim);
+}
+__device__ __forceinline__ void add_cell(int table, int cell, float ds) {
+    __hip_atomic_fetch_add(lds_ptr<unsigned long long>(table + cell * 8), (unsigned long long)to_fixed42(ds), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+}
+
+// One query from its own window: delta, channels 8 g .. 8 g + 7 of dq, and (lane group 0) its part of the bias gradient.
+template <typename T>
+__device__ void query_once_more(const Plane<T> &m, float scale, int i, int L, int K, int g, float lse2, int table, float (&x)[8], float &delta) {
+    const int s = win_start(i, L, K);
+    float p, dp;
+    delta = 0.f;
+#pragma unroll 1
+    for (int a = 0; a < K; ++a) {
+        pair_weight(m, scale, i, s + a, K, lse2, p, dp);
+        delta = __builtin_fmaf(p, dp, delta);
+    }
+#pragma unroll
+    for (int d = 0; d < 8; ++d) x[d] = 0.f;
+#pragma unroll 1
+    for (int a = 0; a < K; ++a) {
+        pair_weight(m, scale, i, s + a, K, lse2, p, dp);
+        const float ds = p * (dp - delta);
+#pragma unroll
+        for (int d = 0; d < 8; ++d) x[d] = __builtin_fmaf(ds, to_f32(m.k[(size_t)(s + a) * kHeadDim + 8 * g + d]), x[d]);
+        if (table && g == 0) add_cell(table, s + a - i + K - 1, ds);
+    }
+#pragma unroll
+    for (int d = 0; d < 8; ++d) x[d] *= scale;
+}
+// One key from the queries that see it, likewise.
+template <typename T>
+__device__ void key_once_more(const Plane<T> &m, float scale, int key, int L, int K, int g, const float *lse, const float *delta, float (&xk)[8], float (&xv)[8]) {
+#pragma unroll
+    for (int d = 0; d < 8; ++d) xk[d] = xv[d] = 0.f;
+#pragma unroll 1
+    for (int i = inv_first(key, L, K); i <= inv_last(key, L, K); ++i) {
+        float p, dp;
+        pair_weight(m, scale, i, key, K, lse[i] * kLog2e, p, dp);
+        const float ds = p * (dp - delta[i]);
+#pragma unroll
+        for (int d = 0; d < 8; ++d) {
+            xv[d] = __builtin_fmaf(p, to_f32(m.dout[(size_t)i * kHeadDim + 8 * g + d]), xv[d]);
+            xk[d] = __builtin_fmaf(ds, to_f32(m.q[(size_t)i * kHeadDim + 8 * g + d]), xk[d]);
+        }
+    }
+#pragma unroll
+    for (int d = 0; d < 8; ++d) xk[d] *= scale;
+}
+
+template <int NBLK> constexpr int kQueryRows = kTile - kGroup + 16 * NBLK;   // keys staged
+__host__ __device__ constexpr int query_lds(int nblk, int K) { return 2 * (kTile - kGroup + 16 * nblk) * kBytes + up16((2 * K - 1) * 4) + (2 * K - 1) * 8; }
+
+template <typename T, int NBLK>
+__global__ __launch_bounds__(kThreads, (NBLK > 3 ? 3 : 4)) void bwd1d_q_mfma_kernel(
+    const T *__restrict__ q, const T *__restrict__ k, const T *__restrict__ v, const T *__restrict__ rpb, float scale, const float *__restrict__ lse,
+    const T *__restrict__ dout, T *__restrict__ dq, float *__restrict__ delta_out, long long *__restrict__ partial, int L, int heads, int K, int tiles) {
+    constexpr int kImage = kQueryRows<NBLK> * kBytes;
+    extern __shared__ __align__(16) char lds[];
+    const int tid = threadIdx.x, lane = tid % kWave, wave = __builtin_amdgcn_readfirstlane(tid / kWave), j = lane & 15, g = lane >> 4;
+    const int plane = blockIdx.x / tiles, t0 = (blockIdx.x - plane * tiles) * kTile, NB = 2 * K - 1, R = K >> 1;
+    const size_t first = (size_t)plane * L;
+    const int h0 = win_start(t0, L, K), img = lds_addr(lds), cells = img + 2 * kImage + up16(NB * 4), table = partial ? cells : 0;
+    float *bias = reinterpret_cast<float *>(lds + 2 * kImage);
+    stage_pair<kWaves>(reinterpret_cast<const char *>(k) + (first + h0) * kBytes, reinterpret_cast<const char *>(v) + (first + h0) * kBytes, L - 1 - h0,
+                       kQueryRows<NBLK>, img, img + kImage, wave, lane);
+    const T *own_rpb = rpb ? rpb + (size_t)(plane % heads) * NB : nullptr;
+    for (int u = tid; u < NB; u += kThreads) {
+        bias[u] = own_rpb ? to_f32(own_rpb[u]) * kLog2e : 0.f;
+        if (partial) *lds_ptr<unsigned long long>(cells + u * 8) = 0ull;
+    }
+    u32x4 qv, gv;
+    float lse_i;
+    auto load = [&](int n) {
+        const int i = t0 + (wave * kGroups + n) * kGroup + j;
+        const size_t at = first + (i < L ? i : L - 1);
+        qv = *reinterpret_cast<const u32x4 *>(reinterpret_cast<const char *>(q) + at * kBytes + g * 16);
+        gv = *reinterpret_cast<const u32x4 *>(reinterpret_cast<const char *>(dout) + at * kBytes + g * 16);
+        lse_i = lse[at];
+    };
+    load(0);
+    wait_global_loads();
+    workgroup_sync();
+
+    const float scale2 = scale * kLog2e;
+    float b[NBLK][4], sums[NBLK][4];
+    bool inner = false;   // b[] is that of a group clear of the ends
+#pragma unroll
+    for (int c = 0; c < NBLK; ++c)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) sums[c][r] = 0.f;
+#pragma unroll 1
+    for (int n = 0; n < kGroups; ++n) {
+        const int i0 = t0 + (wave * kGroups + n) * kGroup;
+        if (i0 >= L) break;
+        const int o = win_start(i0, L, K), i = i0 + j < L ? i0 + j : L - 1;
+        const int w = win_start(i, L, K) - o;   // the lane's window begins at position w of the blocks
+        const bool clear = o == i0 - R && i0 + kGroup - 1 + R < L;
+        if (!(clear && inner)) {
+#pragma unroll
+            for (int c = 0; c < NBLK; ++c)
+#pragma unroll
+                for (int r = 0; r < 4; ++r) {
+                    const int at = 16 * c + 4 * g + r;
+                    const bool in = (unsigned)(at - w) < (unsigned)K;
+                    const float t = bias[in ? at + o - i + K - 1 : 0];
+                    b[c][r] = in ? t : -INFINITY;
+                }
+            inner = clear;
+        }
+        const int ka = row_addr(img, o - h0, j, g);
+        const float lse2 = lse_i * kLog2e;
+        f32x4 s[NBLK], dp[NBLK];
+#pragma unroll
+        for (int c = 0; c < NBLK; ++c) {
+            s[c] = mfma_16x16x32<T>(*lds_ptr<u32x4>(ka + c * kGroup * kBytes), qv, f32x4{0.f, 0.f, 0.f, 0.f});
+            dp[c] = mfma_16x16x32<T>(*lds_ptr<u32x4>(ka + kImage + c * kGroup * kBytes), gv, f32x4{0.f, 0.f, 0.f, 0.f});
+        }
+        if (n + 1 < kGroups) load(n + 1);
+        float delta = 0.f;
+#pragma unroll
+        for (int c = 0; c < NBLK; ++c)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                s[c][r] = __builtin_amdgcn_exp2f(__builtin_fmaf(scale2, s[c][r], b[c][r]) - lse2);
+                delta = __builtin_fmaf(s[c][r], dp[c][r], delta);
+            }
+        delta = group_sum(delta);
+        float most = 0.f;
+#pragma unroll
+        for (int c = 0; c < NBLK; ++c)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                s[c][r] *= dp[c][r] - delta;
+                most = fmaxf(most, fabsf(s[c][r]));
+            }
+        const int e = kShift<T> != 0.f ? lift(group_max(most)) : 0;
+        const float up = __builtin_ldexpf(1.f, e);
+        Split4<T> ws[NBLK];
+#pragma unroll
+        for (int c = 0; c < NBLK; ++c) {
+            const float t[4] = {s[c][0] * up, s[c][1] * up, s[c][2] * up, s[c][3] * up};
+            ws[c].set(t);
+        }
+        f32x4 acc[2] = {f32x4{0.f, 0.f, 0.f, 0.f}, f32x4{0.f, 0.f, 0.f, 0.f}};
+        weighted_sum<T, NBLK>(vector_addr(img, o - h0, j, g), ws, acc);
+        const float back = scale * __builtin_ldexpf(1.f, -e);
+        float x[8], odd = delta * 0.f;   // odd: NaN where something is not finite
+#pragma unroll
+        for (int d = 0; d < 8; ++d) {
+            x[d] = acc[d >> 2][d & 3] * back;
+            odd = __builtin_fmaf(x[d], 0.f, odd);
+        }
+        const unsigned again = marked_columns(odd != odd);
+        const bool redo = (again >> j) & 1u, live = i0 + j < L;
+        if (partial) {
+            if (clear && again == 0) {
+#pragma unroll
+                for (int c = 0; c < NBLK; ++c)
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) sums[c][r] += s[c][r];
+            } else {
+#pragma unroll
+                for (int c = 0; c < NBLK; ++c)
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) {
+                        const int at = 16 * c + 4 * g + r;
+                        if (live && !redo && (unsigned)(at - w) < (unsigned)K) add_cell(cells, at + o - i + K - 1, s[c][r]);
+                    }
+            }
+        }
+        if (redo && live) {
+            const Plane<T> m{q + first * kHeadDim, k + first * kHeadDim, v + first * kHeadDim, dout + first * kHeadDim, own_rpb};
+            query_once_more<T>(m, scale, i, L, K, g, lse2, table, x, delta);
+        }
+        if (live) {
+            store_vector<T>(reinterpret_cast<char *>(dq) + (first + i) * kBytes + g * 16, x);
+            if (g == 0) delta_out[first + i] = delta;
+        }
+    }
+    if (partial == nullptr) return;
+#pragma unroll
+    for (int c = 0; c < NBLK; ++c)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            const int a = 16 * c + 4 * g + r - j;   // slot in the window
+            if ((unsigned)a < (unsigned)K) add_cell(cells, a + K - 1 - R, sums[c][r]);
+        }
+    workgroup_sync();
+    for (int u = tid; u < NB; u += kThreads) partial[(size_t)blockIdx.x * NB + u] = (long long)*lds_ptr<unsigned long long>(cells + u * 8);
+}
+
+// The queries that see a tile are at most kTile + 2 (K - 1), and a group's blocks run on by less than NBLK blocks.
+__host__ __device__ constexpr int key_rows(int nblk, int K) { return up16(kTile + 2 * (K - 1)) + 16 * nblk; }
+__host__ __device__ constexpr int key_lds(int nblk, int K) { return key_rows(nblk, K) * (2 * kBytes + 8) + (2 * K - 1) * 4; }
+
+template <typename T, int NBLK>
+__global__ __launch_bounds__(kThreads, (NBLK > 3 ? 3 : 4)) void bwd1d_kv_mfma_kernel(
+    const T *__restrict__ q, const T *__restrict__ k, const T *__restrict__ v, const T *__restrict__ rpb, float scale, const float *__restrict__ lse,
+    const float *__restrict__ delta, const T *__restrict__ dout, T *__restrict__ dk, T *__restrict__ dv, int L, int heads, int K, int tiles) {
+    extern __shared__ __align__(16) char lds[];
+    const int tid = threadIdx.x, lane = tid % kWave, wave = __builtin_amdgcn_readfirstlane(tid / kWave), j = lane & 15, g = lane >> 4;
+    const int plane = blockIdx.x / tiles, t0 = (blockIdx.x - plane * tiles) * kTile, t1 = t0 + kTile - 1 < L - 1 ? t0 + kTile - 1 : L - 1, NB = 2 * K - 1;
+    const size_t first = (size_t)plane * L;
+    const int rows = key_rows(NBLK, K), image = rows * kBytes, img = lds_addr(lds), ld0 = img + 2 * image;
+    const int h0 = inv_first(t0, L, K), used = up16(inv_last(t1, L, K) - h0 + 1) + 16 * NBLK;   // (at most `rows`)
+    float *bias = reinterpret_cast<float *>(lds + 2 * image + rows * 8);
+    stage_pair<kWaves>(reinterpret_cast<const char *>(q) + (first + h0) * kBytes, reinterpret_cast<const char *>(dout) + (first + h0) * kBytes, L - 1 - h0,
+                       used, img, img + image, wave, lane);
+    typedef float f32x2_t __attribute__((ext_vector_type(2)));
+    for (int u = tid; u < used; u += kThreads) {   // log2(e) lse and delta of every query
+        const size_t at = first + (h0 + u < L - 1 ? h0 + u : L - 1);
+        *lds_ptr<f32x2_t>(ld0 + u * 8) = f32x2_t{lse[at] * kLog2e, delta[at]};
+    }
+    const T *own_rpb = rpb ? rpb + (size_t)(plane % heads) * NB : nullptr;
+    for (int u = tid; u < NB; u += kThreads) bias[u] = own_rpb ? to_f32(own_rpb[u]) * kLog2e : 0.f;
+    u32x4 kv, vv;
+    auto load = [&](int n) {
+        const int key = t0 + (wave * kGroups + n) * kGroup + j;
+        const size_t at = (first + (key < L ? key : L - 1)) * kBytes + g * 16;
+        kv = *reinterpret_cast<const u32x4 *>(reinterpret_cast<const char *>(k) + at);
+        vv = *reinterpret_cast<const u32x4 *>(reinterpret_cast<const char *>(v) + at);
+    };
+    load(0);
+    wait_global_loads();
+    workgroup_sync();
+
+    const float scale2 = scale * kLog2e;
+    float b[NBLK][4];
+    bool inner = false;   // b[] is that of a group clear of the ends
+#pragma unroll 1
+    for (int n = 0; n < kGroups; ++n) {
+        const int j0 = t0 + (wave * kGroups + n) * kGroup;
+        if (j0 >= L) break;
+        const int j1 = j0 + kGroup - 1 < L - 1 ? j0 + kGroup - 1 : L - 1, key = j0 + j < L ? j0 + j : L - 1;
+        const int o = inv_first(j0, L, K), blocks = (inv_last(j1, L, K) - o + kGroup) / kGroup;
+        const int lo = inv_first(key, L, K) - o, count = inv_last(key, L, K) - o - lo + 1;   // the queries that see the lane's key
+        const bool clear = j0 >= K && j0 + kGroup - 1 < L - K;
+        f32x4 ak[2] = {f32x4{0.f, 0.f, 0.f, 0.f}, f32x4{0.f, 0.f, 0.f, 0.f}}, av[2] = {ak[0], ak[0]};
+        int e = 100;   // ak counts 2^-e
+#pragma unroll 1
+        for (int c0 = 0; c0 < blocks; c0 += NBLK) {
+            if (!(clear && inner)) {
+#pragma unroll
+                for (int c = 0; c < NBLK; ++c)
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) {
+                        const int at = 16 * (c0 + c) + 4 * g + r;
+                        const bool in = (unsigned)(at - lo) < (unsigned)count;
+                        const float t = bias[in ? key - o - at + K - 1 : 0];
+                        b[c][r] = in ? t + kShift<T> : -INFINITY;
+                    }
+                inner = clear;
+            }
+            const int pos = o - h0 + 16 * c0, qa = row_addr(img, pos, j, g), la = ld0 + (pos + 4 * g) * 8;
+            Split4<T> wp[NBLK], ws[NBLK];
+            f32x4 ds[NBLK];
+            float most = 0.f;
+#pragma unroll
+            for (int c = 0; c < NBLK; ++c) {
+                const f32x4 s = mfma_16x16x32<T>(*lds_ptr<u32x4>(qa + c * kGroup * kBytes), kv, f32x4{0.f, 0.f, 0.f, 0.f});
+                const f32x4 dp = mfma_16x16x32<T>(*lds_ptr<u32x4>(qa + image + c * kGroup * kBytes), vv, f32x4{0.f, 0.f, 0.f, 0.f});
+                float p[4];
+#pragma unroll
+                for (int r = 0; r < 4; ++r) {
+                    const f32x2_t of = *lds_ptr<f32x2_t>(la + (16 * c + r) * 8);
+                    p[r] = __builtin_amdgcn_exp2f(__builtin_fmaf(scale2, s[r], b[c][r]) - of.x);
+                    ds[c][r] = p[r] * (dp[r] - of.y);
+                    most = fmaxf(most, fabsf(ds[c][r]));
+                }
+                wp[c].set(p);
+            }
+            if constexpr (kShift<T> != 0.f) {
+                const int lifted = lift(group_max(most)), both = lifted < e ? lifted : e;
+                if (c0 > 0) {
+                    const float down = __builtin_ldexpf(1.f, both - e);
+                    ak[0] *= down;
+                    ak[1] *= down;
+                }
+                e = both;
+            } else {
+                e = 0;
+            }
+            const float up = __builtin_ldexpf(1.f, e);
+#pragma unroll
+            for (int c = 0; c < NBLK; ++c) {
+                const float t[4] = {ds[c][0] * up, ds[c][1] * up, ds[c][2] * up, ds[c][3] * up};
+                ws[c].set(t);
+            }
+            weighted_sum<T, NBLK>(vector_addr(img + image, pos, j, g), wp, av);
+            weighted_sum<T, NBLK>(vector_addr(img, pos, j, g), ws, ak);
+        }
+        if (n + 1 < kGroups) load(n + 1);
+        const float back_v = __builtin_ldexpf(1.f, (int)-kShift<T>), back_k = scale * __builtin_ldexpf(1.f, -e - (int)kShift<T>);
+        float xk[8], xv[8], odd = 0.f;
+#pragma unroll
+        for (int d = 0; d < 8; ++d) {
+            xk[d] = ak[d >> 2][d & 3] * back_k;
+            xv[d] = av[d >> 2][d & 3] * back_v;
+            odd = __builtin_fmaf(xk[d], 0.f, __builtin_fmaf(xv[d], 0.f, odd));
+        }
+        const unsigned again = marked_columns(odd != odd);
+        if (j0 + j >= L) continue;
+        if ((again >> j) & 1u) {
+            const Plane<T> m{q + first * kHeadDim, k + first * kHeadDim, v + first * kHeadDim, dout + first * kHeadDim, own_rpb};
+            key_once_more<T>(m, scale, key, L, K, g, lse + first, delta + first, xk, xv);
+        }
+        store_vector<T>(reinterpret_cast<char *>(dk) + (first + key) * kBytes + g * 16, xk);
+        store_vector<T>(reinterpret_cast<char *>(dv) + (first + key) * kBytes + g * 16, xv);
+    }
+}
+
+template <typename T, int NBLK>
+hipError_t launch_t(const Problem &p, const void *q, const void *k, const void *v, const void *rpb, float scale, const float *lse, const void *dout,
+                    void *dq, void *dk, void *dv, float *delta, long long *partial, hipStream_t s) {
+    auto kern_q = bwd1d_q_mfma_kernel<T, NBLK>;
+    auto kern_kv = bwd1d_kv_mfma_kernel<T, NBLK>;
+    static LdsAllowed allowed_q, allowed_kv;
+    if (hipError_t e = allow_lds(kern_q, query_lds(NBLK, kMaxK), allowed_q); e != hipSuccess) return e;
+    if (hipError_t e = allow_lds(kern_kv, key_lds(NBLK, kMaxK), allowed_kv); e != hipSuccess) return e;
+    const int tiles = (p.L + kTile - 1) / kTile;
+    const T *tq = static_cast<const T *>(q), *tk = static_cast<const T *>(k), *tv = static_cast<const T *>(v), *tr = static_cast<const T *>(rpb), *td = static_cast<const T *>(dout);
+    hipLaunchKernelGGL(kern_q, dim3(p.planes() * tiles), dim3(kThreads), query_lds(NBLK, p.K), s, tq, tk, tv, tr, scale, lse, td, static_cast<T *>(dq), delta, partial,
+                       p.L, p.heads, p.K, tiles);
+    if (hipError_t e = hipGetLastError(); e != hipSuccess) return e;
+    hipLaunchKernelGGL(kern_kv, dim3(p.planes() * tiles), dim3(kThreads), key_lds(NBLK, p.K), s, tq, tk, tv, tr, scale, lse, delta, td, static_cast<T *>(dk),
+                       static_cast<T *>(dv), p.L, p.heads, p.K, tiles);
+    return hipGetLastError();
+}
+
+template <typename T, typename... Args> hipError_t launch_blocks(const Problem &p, Args... args) {
+    switch ((p.K + 15 + 15) / 16) {   // (k from 3 to 63)
+        case 2: return launch_t<T, 2>(p, args...);
+        case 3: return launch_t<T, 3>(p, args...);
+        case 4: return launch_t<T, 4>(p, args...);
+        case 5: return launch_t<T, 5>(p, args...);
+    }
+    return hipErrorInvalidValue;
+}
+
+}  // namespace
+
+hipError_t launch_fused_bwd_16bit(const Problem &p, const void *q, const void *k, const void *v, const void *rpb, float scale, const float *lse, const void *dout,
+                                  void *dq, void *dk, void *dv, float *delta, long long *partial, hipStream_t s) {
+    return p.dtype == NA2D_F16 ? launch_blocks<f16_t>(p, q, k, v, rpb, scale, lse, dout, dq, dk, dv, delta, partial, s)
+                               : launch_blocks<bf16_t>(p, q, k, v, rpb, scale, lse, dout, dq, dk, dv, delta, partial, s);
+}
+
+}  // namespace na1d

@@ -15,9 +15,8 @@
 // Bound by memory: 64 x 2 x 3136 queries (103 MB) take 18.7 us in fp16 at k = 7, 19.7 us in bf16 at k = 31 and 23.5 us at k = 63, 4.4 to
 // 5.5 TB/s; a thread per query with its products on the plain ALU took 24.6, 51.2 and 105 us.
 #include "lds_attr.hpp"
+#include "na1d_common.hpp"
 #include "na1d_kernels.hpp"
-#include "na2d_kernels.hpp"   // the dtype constants
-#include "na2d_mfma.hpp"
 
 namespace na1d {
 
@@ -25,21 +24,7 @@ using namespace na2d;
 
 namespace {
 
-constexpr int kWaves = 4, kThreads = kWaves * kWave, kGroup = 16, kBytes = 64;   // queries of a group, bytes of a head vector
-constexpr float kLog2e = 1.4426950408889634f, kLn2 = 0.6931471805599453f;
-
-template <typename T> __device__ __forceinline__ uint32_t pack2(float a, float b) {
-    typedef float f32x2_t __attribute__((ext_vector_type(2)));
-    typedef T tx2_t __attribute__((ext_vector_type(2)));
-    return __builtin_bit_cast(uint32_t, __builtin_convertvector((f32x2_t){a, b}, tx2_t));
-}
-// x rounded to T (two per word) and what the rounding left
-template <typename T> __device__ __forceinline__ void split2(float a, float b, uint32_t &hi, uint32_t &lo) {
-    typedef T tx2_t __attribute__((ext_vector_type(2)));
-    hi = pack2<T>(a, b);
-    const tx2_t h = __builtin_bit_cast(tx2_t, hi);
-    lo = pack2<T>(a - (float)h[0], b - (float)h[1]);
-}
+constexpr int kWaves = 4, kThreads = kWaves * kWave;
 
 template <int NBLK, int GPW> struct Cfg {
     static constexpr int TQ = kWaves * GPW * kGroup, ROWS = TQ - kGroup + 16 * NBLK;   // queries, keys staged
@@ -75,7 +60,6 @@ __global__ __launch_bounds__(kThreads, 4) void fused1d_mfma_kernel(const T *__re
                                                                    const T *__restrict__ rpb, float scale, T *__restrict__ out,
                                                                    float *__restrict__ lse, int L, int heads, int K, int tiles) {
     using C = Cfg<NBLK, GPW>;
-    constexpr float kShift = sizeof(T) == 2 && Traits<T>::kDtype == NA2D_F16 ? 15.f : 0.f;
     extern __shared__ __align__(16) char lds[];
     const int tid = threadIdx.x, lane = tid % kWave, wave = __builtin_amdgcn_readfirstlane(tid / kWave), j = lane & 15, g = lane >> 4;
     const int plane = blockIdx.x / tiles, t0 = (blockIdx.x - plane * tiles) * C::TQ, NB = 2 * K - 1;
@@ -83,20 +67,8 @@ __global__ __launch_bounds__(kThreads, 4) void fused1d_mfma_kernel(const T *__re
     const int h0 = win_start(t0, L, K), img = lds_addr(lds);
     float *bias = reinterpret_cast<float *>(lds + C::kLds);
 
-    // keys and values from h0 on, 16 to a piece (past the end of the sequence the last one again: its weights are 0)
-    {
-        const char *kb = reinterpret_cast<const char *>(k) + (first + h0) * kBytes, *vb = reinterpret_cast<const char *>(v) + (first + h0) * kBytes;
-        const int last = L - 1 - h0;
-#pragma unroll
-        for (int p0 = 0; p0 < C::ROWS / 16; p0 += kWaves) {
-            const int p = p0 + wave;
-            if (p < C::ROWS / 16) {
-                const int row = p * 16 + (lane >> 2), at = row < last ? row : last;
-                global_to_lds_16(kb, (unsigned)(at * kBytes + (lane & 3) * 16), img + p * 1024);
-                global_to_lds_16(vb, (unsigned)(at * kBytes + (lane & 3) * 16), img + C::kImage + p * 1024);
-            }
-        }
-    }
+    stage_pair<kWaves>(reinterpret_cast<const char *>(k) + (first + h0) * kBytes, reinterpret_cast<const char *>(v) + (first + h0) * kBytes, L - 1 - h0,
+                       C::ROWS, img, img + C::kImage, wave, lane);
     u32x4 qv[GPW];
 #pragma unroll
     for (int n = 0; n < GPW; ++n) {
@@ -130,7 +102,7 @@ __global__ __launch_bounds__(kThreads, 4) void fused1d_mfma_kernel(const T *__re
                 }
             inner = clear;
         }
-        const int kaddr = img + (o - h0 + j) * kBytes + g * 16, vaddr = img + C::kImage + (o - h0 + 4 * g + (j >> 2)) * kBytes + (j & 3) * 16;
+        const int kaddr = row_addr(img, o - h0, j, g);
         f32x4 s[NBLK];
 #pragma unroll
         for (int c = 0; c < NBLK; ++c) s[c] = mfma_16x16x32<T>(*lds_ptr<u32x4>(kaddr + c * 1024), qv[n], f32x4{0.f, 0.f, 0.f, 0.f});
@@ -142,10 +114,9 @@ __global__ __launch_bounds__(kThreads, 4) void fused1d_mfma_kernel(const T *__re
                 s[c][r] = __builtin_fmaf(scale2, s[c][r], b[c][r]);
                 m = fmaxf(m, s[c][r]);
             }
-        m = fmaxf(m, __shfl_xor(m, 16));
-        m = fmaxf(m, __shfl_xor(m, 32)) - kShift;
+        m = group_max(m) - kShift<T>;
         float l = 0.f;
-        uint32_t hi[NBLK][2], lo[NBLK][2];
+        Split4<T> w[NBLK];
 #pragma unroll
         for (int c = 0; c < NBLK; ++c) {
             float p[4];
@@ -154,28 +125,11 @@ __global__ __launch_bounds__(kThreads, 4) void fused1d_mfma_kernel(const T *__re
                 p[r] = __builtin_amdgcn_exp2f(s[c][r] - m);
                 l += p[r];
             }
-            split2<T>(p[0], p[1], hi[c][0], lo[c][0]);
-            split2<T>(p[2], p[3], hi[c][1], lo[c][1]);
+            w[c].set(p);
         }
-        l += __shfl_xor(l, 16);
-        l += __shfl_xor(l, 32);
+        l = group_sum(l);
         f32x4 acc[2] = {f32x4{0.f, 0.f, 0.f, 0.f}, f32x4{0.f, 0.f, 0.f, 0.f}};
-#pragma unroll
-        for (int c = 0; c < NBLK; c += 2)
-#pragma unroll
-            for (int hf = 0; hf < 2; ++hf) {
-                const u32x2 v0 = lds_read_tr16(vaddr + c * 1024 + hf * 8);
-                if (c + 1 < NBLK) {
-                    const u32x2 v1 = lds_read_tr16(vaddr + (c + 1) * 1024 + hf * 8);
-                    const u32x4 a{v0.x, v0.y, v1.x, v1.y};
-                    const int d = c + 1 < NBLK ? c + 1 : c;
-                    acc[hf] = mfma_16x16x32<T>(a, u32x4{lo[c][0], lo[c][1], lo[d][0], lo[d][1]}, acc[hf]);
-                    acc[hf] = mfma_16x16x32<T>(a, u32x4{hi[c][0], hi[c][1], hi[d][0], hi[d][1]}, acc[hf]);
-                } else {
-                    acc[hf] = mfma_16x16x16<T>(v0.x, v0.y, lo[c][0], lo[c][1], acc[hf]);
-                    acc[hf] = mfma_16x16x16<T>(v0.x, v0.y, hi[c][0], hi[c][1], acc[hf]);
-                }
-            }
+        weighted_sum<T, NBLK>(vector_addr(img + C::kImage, o - h0, j, g), w, acc);
         const float inv = 1.f / l;
         float x[8], log_sum = (m + __builtin_amdgcn_logf(l)) * kLn2, odd = log_sum * 0.f;   // odd: NaN where something is not finite
 #pragma unroll
@@ -183,15 +137,11 @@ __global__ __launch_bounds__(kThreads, 4) void fused1d_mfma_kernel(const T *__re
             x[d] = acc[d >> 2][d & 3] * inv;
             odd = __builtin_fmaf(x[d], 0.f, odd);
         }
-        const unsigned long long again = __ballot(odd != odd);
-        if (again) {
-            const unsigned cols = (unsigned)((again | (again >> 16) | (again >> 32) | (again >> 48)) & 0xffffu);
-            if ((cols >> j) & 1u)
-                query_once_more<T>(q + first * kHeadDim, k + first * kHeadDim, v + first * kHeadDim, table, scale, i, L, K, g, x, log_sum);
-        }
+        const unsigned again = marked_columns(odd != odd);
+        if ((again >> j) & 1u)
+            query_once_more<T>(q + first * kHeadDim, k + first * kHeadDim, v + first * kHeadDim, table, scale, i, L, K, g, x, log_sum);
         if (i0 + j < L) {
-            store16_stream(reinterpret_cast<char *>(out) + (first + i) * kBytes + g * 16,
-                           u32x4{pack2<T>(x[0], x[1]), pack2<T>(x[2], x[3]), pack2<T>(x[4], x[5]), pack2<T>(x[6], x[7])});
+            store_vector<T>(reinterpret_cast<char *>(out) + (first + i) * kBytes + g * 16, x);
             if (lse != nullptr && g == 0) lse[first + i] = log_sum;
         }
     }

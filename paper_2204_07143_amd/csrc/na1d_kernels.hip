@@ -2,8 +2,9 @@
 // the gradients the paper lists for its package -- q, k, b, a, v -- Appendix A).
 //
 // Per query the 1D operator moves 2*D*e + k*e bytes for 2*k*D flops (3 flop/B at k = 7, f16): far below
-// any arithmetic ridge of the chip, so these kernels are plain-ALU streaming kernels (in 16 bit the fused
-// forward's products on the plain ALU took longer than its memory traffic: na1d_fused_mfma.hip).  What matters is that every byte crosses HBM once and in 16-byte pieces:
+// any arithmetic ridge of the chip, so these kernels are plain-ALU streaming kernels (the fused ones in 16 bit, whose
+// products on the plain ALU took longer than their memory traffic, are in na1d_fused_mfma.hip and na1d_bwd_mfma.hip).
+// What matters is that every byte crosses HBM once and in 16-byte pieces:
 //   * a workgroup owns TQ consecutive positions of one (batch, head) plane; the union of their windows
 //     (TQ + k - 1 keys; TQ + 2(k-1) queries for the inverse neighbourhood) is staged in LDS once with
 //     coalesced 16-byte loads, a padded per-key stride keeping the later 16-byte LDS reads conflict-free;
@@ -15,6 +16,7 @@
 // k is a run-time argument (odd, <= 63); TQ is 256, or 128 for k > 31 so that the LDS images fit.
 #include "na1d_kernels.hpp"
 #include "lds_attr.hpp"
+#include "na1d_common.hpp"
 #include "na2d_common.hpp"
 #include "na2d_kernels.hpp"   // the dtype dispatch macro
 
@@ -363,13 +365,6 @@ __global__ __launch_bounds__(TQ) void fused1d_kernel(const T *__restrict__ q, co
 // (all but (k-1)/2 at each end) send slot a to cell (k-1)/2 + a: those are summed across the wave first
 // and one lane adds the wave's total to the workgroup's LDS table; the others add their own.  Per
 // workgroup the table goes to the workspace as integers; a second kernel adds the workgroups' tables.
-
-__device__ __forceinline__ long long to_fixed42(float x) {
-    float y = x * 1024.f;
-    if (!(__builtin_fabsf(y) < 2147483520.f)) y = 0.f;   // non-finite or out of range: counts as 0
-    const float fl = __builtin_floorf(y);
-    return (long long)(((unsigned long long)(uint32_t)(int)fl << 32) | (uint32_t)((y - fl) * 4294967296.f));
-}
 
 template <typename T, int TQ>
 __host__ __device__ constexpr int rpb_lds_bytes(int K) {
@@ -736,49 +731,52 @@ size_t fused_bwd_workspace_bytes(const Problem &p) {
     return delta_bytes + rpb_workspace_bytes(p);
 }
 
-template <typename T, int TQ>
-static hipError_t fused_bwd_t(const Problem &p, const void *q, const void *k, const void *v, const void *rpb, float scale,
-                              const float *lse, const void *dout, void *dq, void *dk, void *dv, float *d_rpb,
-                              void *workspace, hipStream_t s) {
-    const int tiles = tiles_of<TQ>(p), NB = 2 * p.K - 1;
-    float *delta = static_cast<float *>(workspace);
-    const size_t delta_bytes = ((size_t)p.planes() * p.L * sizeof(float) + 255) & ~(size_t)255;
-    long long *partial = d_rpb ? reinterpret_cast<long long *>(static_cast<char *>(workspace) + delta_bytes) : nullptr;
+template <int TQ>
+static hipError_t fused_bwd_f32(const Problem &p, const float *q, const float *k, const float *v, const float *rpb, float scale,
+                                const float *lse, const float *dout, float *dq, float *dk, float *dv, float *delta, long long *partial,
+                                hipStream_t s) {
+    const int tiles = tiles_of<TQ>(p);
     {
-        auto kern = fbwd1d_q_kernel<T, TQ>;
-        static_assert(fbwd_q_lds_bytes<T, TQ>(max_k<TQ>()) <= 160 * 1024, "LDS");
+        auto kern = fbwd1d_q_kernel<float, TQ>;
+        static_assert(fbwd_q_lds_bytes<float, TQ>(max_k<TQ>()) <= 160 * 1024, "LDS");
         static na2d::LdsAllowed attr;
-        if (hipError_t e = allow_lds(kern, fbwd_q_lds_bytes<T, TQ>(max_k<TQ>()), attr); e != hipSuccess) return e;
-        const int bytes = fbwd_q_lds_bytes<T, TQ>(p.K);
-        hipLaunchKernelGGL(kern, dim3(p.planes() * tiles), dim3(TQ), bytes, s,
-                           static_cast<const T *>(q), static_cast<const T *>(k), static_cast<const T *>(v),
-                           static_cast<const T *>(rpb), scale, lse, static_cast<const T *>(dout), static_cast<T *>(dq), delta,
-                           partial, p.L, p.heads, p.K, tiles);
+        if (hipError_t e = allow_lds(kern, fbwd_q_lds_bytes<float, TQ>(max_k<TQ>()), attr); e != hipSuccess) return e;
+        const int bytes = fbwd_q_lds_bytes<float, TQ>(p.K);
+        hipLaunchKernelGGL(kern, dim3(p.planes() * tiles), dim3(TQ), bytes, s, q, k, v, rpb, scale, lse, dout, dq, delta, partial, p.L,
+                           p.heads, p.K, tiles);
         if (hipError_t e = hipGetLastError(); e != hipSuccess) return e;
     }
-    {
-        auto kern = fbwd1d_kv_kernel<T, TQ>;
-        static_assert(fbwd_kv_lds_bytes<T, TQ>(max_k<TQ>()) <= 160 * 1024, "LDS");
-        static na2d::LdsAllowed attr;
-        if (hipError_t e = allow_lds(kern, fbwd_kv_lds_bytes<T, TQ>(max_k<TQ>()), attr); e != hipSuccess) return e;
-        const int bytes = fbwd_kv_lds_bytes<T, TQ>(p.K);
-        hipLaunchKernelGGL(kern, dim3(p.planes() * tiles), dim3(TQ), bytes, s,
-                           static_cast<const T *>(q), static_cast<const T *>(k), static_cast<const T *>(v),
-                           static_cast<const T *>(rpb), scale, lse, delta, static_cast<const T *>(dout), static_cast<T *>(dk),
-                           static_cast<T *>(dv), p.L, p.heads, p.K, tiles);
-        if (hipError_t e = hipGetLastError(); e != hipSuccess) return e;
-    }
-    if (d_rpb) {
-        hipLaunchKernelGGL(rpb_final1d_kernel, dim3(p.heads * NB), dim3(kFinalThreads), 0, s, partial, d_rpb, p.B, p.heads, tiles, NB);
-        return hipGetLastError();
-    }
-    return hipSuccess;
+    auto kern = fbwd1d_kv_kernel<float, TQ>;
+    static_assert(fbwd_kv_lds_bytes<float, TQ>(max_k<TQ>()) <= 160 * 1024, "LDS");
+    static na2d::LdsAllowed attr;
+    if (hipError_t e = allow_lds(kern, fbwd_kv_lds_bytes<float, TQ>(max_k<TQ>()), attr); e != hipSuccess) return e;
+    const int bytes = fbwd_kv_lds_bytes<float, TQ>(p.K);
+    hipLaunchKernelGGL(kern, dim3(p.planes() * tiles), dim3(TQ), bytes, s, q, k, v, rpb, scale, lse, delta, dout, dk, dv, p.L, p.heads,
+                       p.K, tiles);
+    return hipGetLastError();
 }
 hipError_t launch_fused_bwd(const Problem &p, const void *q, const void *k, const void *v, const void *rpb, float scale,
                             const float *lse, const void *dout, void *dq, void *dk, void *dv, float *d_rpb, void *workspace,
                             hipStream_t s) {
-    NA1D_DISPATCH(p, return (fused_bwd_t<T, TQ>(p, q, k, v, rpb, scale, lse, dout, dq, dk, dv, d_rpb, workspace, s)));
-    return hipErrorInvalidValue;
+    float *delta = static_cast<float *>(workspace);
+    const size_t delta_bytes = ((size_t)p.planes() * p.L * sizeof(float) + 255) & ~(size_t)255;
+    long long *partial = d_rpb ? reinterpret_cast<long long *>(static_cast<char *>(workspace) + delta_bytes) : nullptr;
+    const auto f32 = [](const void *x) { return static_cast<const float *>(x); };
+    const auto f32_out = [](void *x) { return static_cast<float *>(x); };
+    hipError_t e;
+    int tiles = tiles_of<256>(p);
+    if (p.dtype != NA2D_F32) {
+        e = launch_fused_bwd_16bit(p, q, k, v, rpb, scale, lse, dout, dq, dk, dv, delta, partial, s);
+    } else if (p.K <= 31) {
+        e = fused_bwd_f32<256>(p, f32(q), f32(k), f32(v), f32(rpb), scale, lse, f32(dout), f32_out(dq), f32_out(dk), f32_out(dv), delta, partial, s);
+    } else {
+        tiles = tiles_of<128>(p);
+        e = fused_bwd_f32<128>(p, f32(q), f32(k), f32(v), f32(rpb), scale, lse, f32(dout), f32_out(dq), f32_out(dk), f32_out(dv), delta, partial, s);
+    }
+    if (e != hipSuccess || d_rpb == nullptr) return e;
+    const int NB = 2 * p.K - 1;
+    hipLaunchKernelGGL(rpb_final1d_kernel, dim3(p.heads * NB), dim3(kFinalThreads), 0, s, partial, d_rpb, p.B, p.heads, tiles, NB);
+    return hipGetLastError();
 }
 
 }  // namespace na1d

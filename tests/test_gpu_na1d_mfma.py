@@ -9,7 +9,7 @@ from oracle import na1d_oracle as o1
 from paper_2204_07143_amd import binding as na
 from paper_2204_07143_amd import synth
 
-from gpu_util import assert_close, to_np
+from gpu_util import assert_close, assert_close_rpb, to_np
 
 pytestmark = pytest.mark.gpu
 
@@ -26,15 +26,71 @@ def forward(p, seed, use_rpb=True, rpb_std=0.02, edit=None):
     return out, lse, o1.fwd(*h, p.default_scale, p.k, return_lse=True)
 
 
-# (the last two: 512 tiles and more, four groups of queries to a wave)
-@pytest.mark.parametrize("dtype", ["f16", "bf16"])
-@pytest.mark.parametrize("B,heads,L,k", [(B, heads, L, k) for B, heads, L, ks in [
+def backward(p, seed, use_rpb=True, rpb_std=0.02, dout_scale=1.0, edit=None):
+    host = synth.make_inputs_1d(p, seed, rpb_std=rpb_std)
+    host["dout"] = host["dout"] * dout_scale
+    if edit:
+        edit(host)
+    q, key, v, dout = (synth.to_device(host[n], p.dtype) for n in ("q", "k", "v", "dout"))
+    rpb = synth.to_device(host["rpb"], p.dtype) if use_rpb else None
+    lse = torch.empty(q.shape[:3], dtype=torch.float32, device="cuda")
+    na.na1d_fused_fwd(q, key, v, rpb, p.default_scale, p.k, torch.empty_like(q), lse)
+    ws = torch.empty(na.na1d_fused_bwd_workspace_bytes(na.problem_1d(p.B, p.heads, p.L, p.D, p.k, q.dtype)), dtype=torch.uint8, device="cuda")
+    grads = [torch.empty_like(q) for _ in range(3)] + [torch.empty((p.heads, 2 * p.k - 1), dtype=torch.float32, device="cuda")]
+    na.na1d_fused_bwd(q, key, v, rpb, p.default_scale, lse, dout, p.k, *grads, ws)
+    h = [t.double().cpu().numpy() for t in (q, key, v)]
+    table = rpb.double().cpu().numpy() if use_rpb else np.zeros((p.heads, 2 * p.k - 1))
+    with np.errstate(all="ignore"):
+        return grads, o1.bwd(*h, table, p.default_scale, dout.double().cpu().numpy(), p.k)
+
+
+# (the last two: 512 tiles and more, four groups of queries to a wave of the forward)
+SIZES = [(B, heads, L, k) for B, heads, L, ks in [
     (2, 2, 63, (3, 17, 19, 33, 35, 49, 51, 63)), (1, 3, 65, (3, 17, 19, 33, 35, 49, 51, 63)), (1, 2, 193, (7, 31, 63)), (2, 1, 1025, (17, 35, 63)),
-    (130, 4, 67, (3, 17, 19, 33, 35, 49, 51, 63)), (90, 2, 531, (3, 33, 63))] for k in ks])
+    (130, 4, 67, (3, 17, 19, 33, 35, 49, 51, 63)), (90, 2, 531, (3, 33, 63))] for k in ks]
+
+
+@pytest.mark.parametrize("dtype", ["f16", "bf16"])
+@pytest.mark.parametrize("B,heads,L,k", SIZES)
 def test_forward_blocks(dtype, B, heads, L, k):
     out, lse, (want, want_lse) = forward(synth.Problem1D(B, heads, L, 32, k, dtype), seed=L + k, use_rpb=L % 2 == 1 and L != 65, rpb_std=0.5)
     assert_close("out", out, want, dtype)
     assert_close("lse", lse, want_lse, "f32")
+
+
+@pytest.mark.parametrize("dtype", ["f16", "bf16"])
+@pytest.mark.parametrize("B,heads,L,k", SIZES)
+def test_backward_blocks(dtype, B, heads, L, k):
+    got, want = backward(synth.Problem1D(B, heads, L, 32, k, dtype), seed=L + k, use_rpb=L % 2 == 1 and L != 65, rpb_std=0.5)
+    for n, x, y in zip(("dq", "dk", "dv"), got, want):
+        assert_close(n, x, y, dtype)
+    assert_close_rpb("d_rpb", got[3], want[3])
+
+
+@pytest.mark.parametrize("dtype,log2_scale", [("f16", -6), ("f16", 8), ("bf16", -15), ("bf16", 10)])
+def test_backward_follows_the_scale_of_dout(dtype, log2_scale):
+    """(fp16: dout far from its subnormals; the bias gradient's integers count 2^-42)"""
+    s = 2.0 ** log2_scale
+    got, want = backward(synth.Problem1D(3, 2, 300, 32, 21, dtype), seed=3, dout_scale=s)
+    for n, x, y in zip(("dq", "dk", "dv"), got, want):
+        assert_close(n, x.double() / s, y / s, dtype)
+    assert_close_rpb("d_rpb", got[3].double() / s, want[3] / s)
+
+
+@pytest.mark.parametrize("dtype", ["f16", "bf16"])
+@pytest.mark.parametrize("what", ["q", "k", "v", "dout"])
+def test_backward_not_finite_stays_in_its_windows(dtype, what):
+    def edit(host):
+        host[what][0, 0, 60, 3] = np.nan
+        host[what][0, 1, 0, 5] = np.nan
+
+    k, L = 7, 200
+    got, want = backward(synth.Problem1D(1, 2, L, 32, k, dtype), seed=9, edit=edit)
+    for n, x, y in zip(("dq", "dk", "dv"), got, want):
+        x = to_np(x)
+        assert np.isfinite(y).all() == (n == "dv" and what == "v") and np.array_equal(np.isfinite(x), np.isfinite(y)), n
+        zero = lambda t: np.where(np.isfinite(y), t, 0.0)
+        assert_close(n, zero(x), zero(y), dtype)
 
 
 @pytest.mark.parametrize("dtype", ["f16", "bf16"])
