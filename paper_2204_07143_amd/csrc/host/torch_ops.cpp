@@ -139,12 +139,12 @@ struct NA2D : torch::autograd::Function<NA2D> {
         const na2d_problem p = *problem_2d(q.sizes(), q.scalar_type(), ctx->saved_data["k"].toInt());
         const Tensor dout = grads[0].contiguous();
         Tensor dq = at::empty(q.sizes(), q.options()), dk = at::empty(q.sizes(), q.options()), dv = at::empty(q.sizes(), q.options());
-        Tensor d32 = want ? fp32(rpb.sizes(), q) : Tensor();
+        Tensor d_rpb = want ? at::empty(rpb.sizes(), rpb.options()) : Tensor();   // (rpb is of q's type)
         const size_t direct = na2d_direct_bwd_workspace_bytes(&p);   // 0: not for this problem
         const Tensor ws = workspace(direct ? direct : na2d_workspace_bytes(&p, NA2D_WS_FUSED_BWD), q);
-        check((direct ? na2d_direct_bwd : na2d_fused_bwd)(&p, ptr(q), ptr(k), ptr(v), ptr(rpb), scale, (const float *)ptr(lse), ptr(dout), ptr(dq), ptr(dk), ptr(dv),
-                                                          (float *)ptr(d32), ptr(ws), (size_t)ws.numel(), stream()));
-        variable_list r{dq, dk, dv, want ? d32.to(rpb.scalar_type()) : Tensor()};
+        check((direct ? na2d_direct_bwd_typed : na2d_fused_bwd_typed)(&p, ptr(q), ptr(k), ptr(v), ptr(rpb), scale, (const float *)ptr(lse), ptr(dout), ptr(dq), ptr(dk), ptr(dv),
+                                                                      ptr(d_rpb), ptr(ws), (size_t)ws.numel(), stream()));
+        variable_list r{dq, dk, dv, d_rpb};
         r.resize(6);
         return r;
     }
@@ -176,11 +176,11 @@ struct NA1D : torch::autograd::Function<NA1D> {
         const na1d_problem p = *problem_1d(q.sizes(), q.scalar_type(), ctx->saved_data["k"].toInt());
         const Tensor dout = grads[0].contiguous();
         Tensor dq = at::empty(q.sizes(), q.options()), dk = at::empty(q.sizes(), q.options()), dv = at::empty(q.sizes(), q.options());
-        Tensor d32 = want ? fp32(rpb.sizes(), q) : Tensor();
+        Tensor d_rpb = want ? at::empty(rpb.sizes(), rpb.options()) : Tensor();
         const Tensor ws = workspace(na1d_fused_bwd_workspace_bytes(&p), q);
-        check(na1d_fused_bwd(&p, ptr(q), ptr(k), ptr(v), ptr(rpb), (float)ctx->saved_data["scale"].toDouble(), (const float *)ptr(lse), ptr(dout), ptr(dq), ptr(dk), ptr(dv),
-                             (float *)ptr(d32), ptr(ws), (size_t)ws.numel(), stream()));
-        variable_list r{dq, dk, dv, want ? d32.to(rpb.scalar_type()) : Tensor()};
+        check(na1d_fused_bwd_typed(&p, ptr(q), ptr(k), ptr(v), ptr(rpb), (float)ctx->saved_data["scale"].toDouble(), (const float *)ptr(lse), ptr(dout), ptr(dq), ptr(dk), ptr(dv),
+                                   ptr(d_rpb), ptr(ws), (size_t)ws.numel(), stream()));
+        variable_list r{dq, dk, dv, d_rpb};
         r.resize(6);
         return r;
     }
@@ -205,7 +205,6 @@ struct QKRPB : torch::autograd::Function<QKRPB> {
         ctx->saved_data["want_q"] = q_.requires_grad();
         ctx->saved_data["want_k"] = k_.requires_grad();
         ctx->saved_data["want_rpb"] = rpb_ && rpb_->requires_grad();
-        ctx->saved_data["type"] = rpb_ ? rpb_->scalar_type() : q.scalar_type();
         return logits;
     }
     static variable_list backward(AutogradContext *ctx, variable_list grads) {
@@ -225,10 +224,9 @@ struct QKRPB : torch::autograd::Function<QKRPB> {
             check(na2d_qk_bwd_k(&p, ptr(ds), ptr(q), scale, ptr(dk), stream()));
         }
         if (ctx->saved_data["want_rpb"].toBool()) {
-            Tensor d32 = fp32({q.size(1), 2 * ks - 1, 2 * ks - 1}, q);
+            d_rpb = at::empty({q.size(1), 2 * ks - 1, 2 * ks - 1}, q.options());
             const Tensor ws = workspace(na2d_workspace_bytes(&p, NA2D_WS_QK_BWD_RPB), q);
-            check(na2d_qk_bwd_rpb(&p, ptr(ds), (float *)ptr(d32), ptr(ws), (size_t)ws.numel(), stream()));
-            d_rpb = d32.to(ctx->saved_data["type"].toScalarType());
+            check(na2d_qk_bwd_rpb_typed(&p, ptr(ds), ptr(d_rpb), ptr(ws), (size_t)ws.numel(), stream()));
         }
         return {dq, dk, d_rpb, Tensor(), Tensor()};
     }

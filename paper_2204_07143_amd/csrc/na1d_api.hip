@@ -129,7 +129,7 @@ int na1d_qk_bwd_rpb(const na1d_problem *p, const void *ds, float *d_rpb, void *w
     NA1D_CHECK_PROBLEM(p);
     NA1D_REQUIRE(ds); NA1D_REQUIRE(d_rpb);
     if (!workspace || misaligned(workspace) || workspace_bytes < rpb_workspace_bytes(to_problem(p))) return NA2D_ERR_WORKSPACE;
-    return from_hip(launch_rpb_grad(to_problem(p), ds, d_rpb, workspace, static_cast<hipStream_t>(stream)));
+    return from_hip(launch_rpb_grad(to_problem(p), ds, na2d::BiasOut{d_rpb, NA2D_F32}, workspace, static_cast<hipStream_t>(stream)));
 }
 
 size_t na1d_fused_bwd_workspace_bytes(const na1d_problem *p) {
@@ -137,10 +137,9 @@ size_t na1d_fused_bwd_workspace_bytes(const na1d_problem *p) {
     return fused_bwd_workspace_bytes(to_problem(p));
 }
 
-int na1d_fused_bwd(const na1d_problem *p, const void *q, const void *k, const void *v, const void *rpb, float scale,
-                   const float *lse, const void *dout, void *dq, void *dk, void *dv, float *d_rpb, void *workspace,
-                   size_t workspace_bytes, void *stream) {
-    NA1D_CHECK_PROBLEM(p);
+static int fused_bwd(const na1d_problem *p, const void *q, const void *k, const void *v, const void *rpb, float scale,
+                     const float *lse, const void *dout, void *dq, void *dk, void *dv, void *d_rpb, int out_dtype,
+                     void *workspace, size_t workspace_bytes, void *stream) {
     NA1D_REQUIRE(q); NA1D_REQUIRE(k); NA1D_REQUIRE(v); NA1D_OPTIONAL(rpb); NA1D_REQUIRE(lse); NA1D_REQUIRE(dout);
     NA1D_REQUIRE(dq); NA1D_REQUIRE(dk); NA1D_REQUIRE(dv); NA1D_OPTIONAL(d_rpb);
     if (!workspace || misaligned(workspace) || workspace_bytes < fused_bwd_workspace_bytes(to_problem(p))) return NA2D_ERR_WORKSPACE;
@@ -150,8 +149,20 @@ int na1d_fused_bwd(const na1d_problem *p, const void *q, const void *k, const vo
         for (const void *i : ins)
             if (o && o == i) return NA2D_ERR_ALIAS;
     if (dq == dk || dq == dv || dk == dv) return NA2D_ERR_ALIAS;
-    return from_hip(launch_fused_bwd(to_problem(p), q, k, v, rpb, scale, lse, dout, dq, dk, dv, d_rpb, workspace,
-                                     static_cast<hipStream_t>(stream)));
+    return from_hip(launch_fused_bwd(to_problem(p), q, k, v, rpb, scale, lse, dout, dq, dk, dv, na2d::BiasOut{d_rpb, out_dtype},
+                                     workspace, static_cast<hipStream_t>(stream)));
+}
+int na1d_fused_bwd(const na1d_problem *p, const void *q, const void *k, const void *v, const void *rpb, float scale,
+                   const float *lse, const void *dout, void *dq, void *dk, void *dv, float *d_rpb, void *workspace,
+                   size_t workspace_bytes, void *stream) {
+    NA1D_CHECK_PROBLEM(p);
+    return fused_bwd(p, q, k, v, rpb, scale, lse, dout, dq, dk, dv, d_rpb, NA2D_F32, workspace, workspace_bytes, stream);
+}
+int na1d_fused_bwd_typed(const na1d_problem *p, const void *q, const void *k, const void *v, const void *rpb, float scale,
+                         const float *lse, const void *dout, void *dq, void *dk, void *dv, void *d_rpb, void *workspace,
+                         size_t workspace_bytes, void *stream) {
+    NA1D_CHECK_PROBLEM(p);
+    return fused_bwd(p, q, k, v, rpb, scale, lse, dout, dq, dk, dv, d_rpb, p->dtype, workspace, workspace_bytes, stream);
 }
 
 }  // extern "C"

@@ -209,7 +209,7 @@ __global__ __launch_bounds__(kThreads, (NBLK > 3 ? 3 : 4)) void bwd1d_q_mfma_ker
         const unsigned again = marked_columns(odd != odd);
         const bool redo = (again >> j) & 1u, live = i0 + j < L;
         if (partial) {
-            if (clear && again == 0) {
+            if (clear && again == 0 && __ballot(most >= 524288.f) == 0) {   // (2^19: the sum of four stays in the integers' range)
 #pragma unroll
                 for (int c = 0; c < NBLK; ++c)
 #pragma unroll

@@ -405,7 +405,7 @@ __global__ __launch_bounds__(TQ) void rpb_partial1d_kernel(const T *__restrict__
 // one workgroup per (head, cell): adds the tables of every (batch, tile) of that head
 constexpr int kFinalThreads = 256;
 __global__ __launch_bounds__(kFinalThreads) void rpb_final1d_kernel(const long long *__restrict__ partial,
-                                                                    float *__restrict__ d_rpb, int B, int heads, int tiles,
+                                                                    BiasOut d_rpb, int B, int heads, int tiles,
                                                                     int NB) {
     __shared__ long long wave_sum[kFinalThreads / kWave];
     const int h = blockIdx.x / NB, u = blockIdx.x % NB;
@@ -427,7 +427,7 @@ __global__ __launch_bounds__(kFinalThreads) void rpb_final1d_kernel(const long l
     if (threadIdx.x == 0) {
         long long tot = 0;
         for (int w = 0; w < kFinalThreads / kWave; ++w) tot += wave_sum[w];
-        d_rpb[(size_t)h * NB + u] = (float)((double)tot * (1.0 / 4398046511104.0));   // 2^-42
+        d_rpb.store((size_t)h * NB + u, (float)((double)tot * (1.0 / 4398046511104.0)));   // 2^-42
     }
 }
 
@@ -709,7 +709,7 @@ size_t rpb_workspace_bytes(const Problem &p) {
 }
 
 template <typename T, int TQ>
-static hipError_t rpb_t(const Problem &p, const void *ds, float *d_rpb, void *workspace, hipStream_t s) {
+static hipError_t rpb_t(const Problem &p, const void *ds, BiasOut d_rpb, void *workspace, hipStream_t s) {
     auto kern = rpb_partial1d_kernel<T, TQ>;
     const int bytes = rpb_lds_bytes<T, TQ>(p.K), tiles = tiles_of<TQ>(p);
     static na2d::LdsAllowed attr;
@@ -721,7 +721,7 @@ static hipError_t rpb_t(const Problem &p, const void *ds, float *d_rpb, void *wo
     hipLaunchKernelGGL(rpb_final1d_kernel, dim3(p.heads * NB), dim3(kFinalThreads), 0, s, partial, d_rpb, p.B, p.heads, tiles, NB);
     return hipGetLastError();
 }
-hipError_t launch_rpb_grad(const Problem &p, const void *ds, float *d_rpb, void *workspace, hipStream_t s) {
+hipError_t launch_rpb_grad(const Problem &p, const void *ds, BiasOut d_rpb, void *workspace, hipStream_t s) {
     NA1D_DISPATCH(p, return (rpb_t<T, TQ>(p, ds, d_rpb, workspace, s)));
     return hipErrorInvalidValue;
 }
@@ -756,7 +756,7 @@ static hipError_t fused_bwd_f32(const Problem &p, const float *q, const float *k
     return hipGetLastError();
 }
 hipError_t launch_fused_bwd(const Problem &p, const void *q, const void *k, const void *v, const void *rpb, float scale,
-                            const float *lse, const void *dout, void *dq, void *dk, void *dv, float *d_rpb, void *workspace,
+                            const float *lse, const void *dout, void *dq, void *dk, void *dv, BiasOut d_rpb, void *workspace,
                             hipStream_t s) {
     float *delta = static_cast<float *>(workspace);
     const size_t delta_bytes = ((size_t)p.planes() * p.L * sizeof(float) + 255) & ~(size_t)255;
@@ -773,7 +773,7 @@ hipError_t launch_fused_bwd(const Problem &p, const void *q, const void *k, cons
         tiles = tiles_of<128>(p);
         e = fused_bwd_f32<128>(p, f32(q), f32(k), f32(v), f32(rpb), scale, lse, f32(dout), f32_out(dq), f32_out(dk), f32_out(dv), delta, partial, s);
     }
-    if (e != hipSuccess || d_rpb == nullptr) return e;
+    if (e != hipSuccess || !d_rpb) return e;
     const int NB = 2 * p.K - 1;
     hipLaunchKernelGGL(rpb_final1d_kernel, dim3(p.heads * NB), dim3(kFinalThreads), 0, s, partial, d_rpb, p.B, p.heads, tiles, NB);
     return hipGetLastError();

@@ -6,6 +6,7 @@
 #include <stdint.h>
 
 #include "na1d.h"
+#include "na2d_common.hpp"
 
 namespace na1d {
 
@@ -29,11 +30,11 @@ hipError_t launch_fused_fwd(const Problem &p, const void *q, const void *k, cons
 hipError_t launch_fused_fwd_16bit(const Problem &p, const void *q, const void *k, const void *v, const void *rpb, float scale,
                                   void *out, float *lse, hipStream_t s);   // f16 / bf16
 size_t rpb_workspace_bytes(const Problem &p);
-hipError_t launch_rpb_grad(const Problem &p, const void *ds, float *d_rpb, void *workspace, hipStream_t s);
+hipError_t launch_rpb_grad(const Problem &p, const void *ds, na2d::BiasOut d_rpb, void *workspace, hipStream_t s);
 // whole backward from q, k, v, rpb, dout and the forward's log-sum-exp (no k-wide tensor in memory)
 size_t fused_bwd_workspace_bytes(const Problem &p);
 hipError_t launch_fused_bwd(const Problem &p, const void *q, const void *k, const void *v, const void *rpb, float scale,
-                            const float *lse, const void *dout, void *dq, void *dk, void *dv, float *d_rpb, void *workspace,
+                            const float *lse, const void *dout, void *dq, void *dk, void *dv, na2d::BiasOut d_rpb, void *workspace,
                             hipStream_t s);
 // f16 / bf16, without the last sum of the bias gradient: partial (null: none wanted) is one table of integers per 256 positions of a plane
 hipError_t launch_fused_bwd_16bit(const Problem &p, const void *q, const void *k, const void *v, const void *rpb, float scale, const float *lse,

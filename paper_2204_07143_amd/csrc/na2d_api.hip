@@ -163,25 +163,32 @@ size_t na2d_workspace_bytes(const na2d_problem *p, int kind) {
     return 0;
 }
 
-int na2d_qk_bwd_rpb(const na2d_problem *p, const void *ds, float *d_rpb, void *workspace, size_t workspace_bytes,
-                    void *stream) {
-    NA2D_CHECK_PROBLEM(p);
+static int qk_bwd_rpb(const na2d_problem *p, const void *ds, void *d_rpb, int out_dtype, void *workspace, size_t workspace_bytes, void *stream) {
     NA2D_REQUIRE(ds); NA2D_REQUIRE(d_rpb);
     if (!workspace || misaligned(workspace) || workspace_bytes < na2d_workspace_bytes(p, NA2D_WS_QK_BWD_RPB))
         return NA2D_ERR_WORKSPACE;
-    return from_hip(launch_rpb_bwd(to_problem(p), ds, d_rpb, workspace, static_cast<hipStream_t>(stream)));
+    return from_hip(launch_rpb_bwd(to_problem(p), ds, BiasOut{d_rpb, out_dtype}, workspace, static_cast<hipStream_t>(stream)));
+}
+int na2d_qk_bwd_rpb(const na2d_problem *p, const void *ds, float *d_rpb, void *workspace, size_t workspace_bytes,
+                    void *stream) {
+    NA2D_CHECK_PROBLEM(p);
+    return qk_bwd_rpb(p, ds, d_rpb, NA2D_F32, workspace, workspace_bytes, stream);
+}
+int na2d_qk_bwd_rpb_typed(const na2d_problem *p, const void *ds, void *d_rpb, void *workspace, size_t workspace_bytes, void *stream) {
+    NA2D_CHECK_PROBLEM(p);
+    return qk_bwd_rpb(p, ds, d_rpb, p->dtype, workspace, workspace_bytes, stream);
 }
 
 int na2d_qk_bwd_rpb_noalloc(const na2d_problem *p, const void *ds, float *d_rpb, void *stream) {
     NA2D_CHECK_PROBLEM(p);
     NA2D_REQUIRE(ds); NA2D_REQUIRE(d_rpb);
     if (rpb_bwd_partial_bytes(to_problem(p)) > (size_t)NA2D_NOALLOC_SCRATCH_BYTES) return NA2D_ERR_WORKSPACE;
-    return from_hip(launch_rpb_bwd_noalloc(to_problem(p), ds, d_rpb, static_cast<hipStream_t>(stream)));
+    return from_hip(launch_rpb_bwd_noalloc(to_problem(p), ds, BiasOut{d_rpb, NA2D_F32}, static_cast<hipStream_t>(stream)));
 }
 
 // The unfused backward on validated arguments: `ws` holds NA2D_WS_BWD bytes.
 static int run_bwd(const Problem &pr, const void *q, const void *k, const void *v, const void *attn, const void *dout,
-                   float scale, void *dq, void *dk, void *dv, float *d_rpb, char *ws, hipStream_t s) {
+                   float scale, void *dq, void *dk, void *dv, BiasOut d_rpb, char *ws, hipStream_t s) {
     void *dpds = ws;   // dp, overwritten in place by ds
     const size_t attn_bytes = (pr.queries() * pr.K * pr.K * pr.elem_bytes() + 255) & ~(size_t)255;
     void *rpb_ws = ws + attn_bytes;
@@ -220,7 +227,7 @@ int na2d_bwd(const na2d_problem *p, const void *q, const void *k, const void *v,
         for (const void *i : ins)
             if (o && o == i) return NA2D_ERR_ALIAS;
     if (dq == dk || dq == dv || dk == dv || d_rpb == dq || d_rpb == dk || d_rpb == dv) return NA2D_ERR_ALIAS;
-    return run_bwd(to_problem(p), q, k, v, attn, dout, scale, dq, dk, dv, d_rpb, static_cast<char *>(workspace),
+    return run_bwd(to_problem(p), q, k, v, attn, dout, scale, dq, dk, dv, BiasOut{d_rpb, NA2D_F32}, static_cast<char *>(workspace),
                    static_cast<hipStream_t>(stream));
 }
 
@@ -237,7 +244,7 @@ static size_t fused_bwd_attn_bytes(const Problem &pr) { return (pr.queries() * p
 
 // What na2d_fused_bwd and na2d_direct_bwd ask of their arguments.
 static int check_fused_bwd(const na2d_problem *p, const void *q, const void *k, const void *v, const void *rpb, const float *lse, const void *dout,
-                           void *dq, void *dk, void *dv, float *d_rpb, void *workspace, size_t workspace_bytes, size_t needed) {
+                           void *dq, void *dk, void *dv, void *d_rpb, void *workspace, size_t workspace_bytes, size_t needed) {
     NA2D_REQUIRE(q); NA2D_REQUIRE(k); NA2D_REQUIRE(v); NA2D_OPTIONAL(rpb); NA2D_REQUIRE(lse); NA2D_REQUIRE(dout);
     NA2D_REQUIRE(dq); NA2D_REQUIRE(dk); NA2D_REQUIRE(dv); NA2D_OPTIONAL(d_rpb);
     if (!workspace || misaligned(workspace) || workspace_bytes < needed)
@@ -251,11 +258,10 @@ static int check_fused_bwd(const na2d_problem *p, const void *q, const void *k, 
     return NA2D_OK;
 }
 
-int na2d_fused_bwd(const na2d_problem *p, const void *q, const void *k, const void *v, const void *rpb, float scale,
-                   const float *lse, const void *dout, void *dq, void *dk, void *dv, float *d_rpb, void *workspace,
-                   size_t workspace_bytes, void *stream) {
-    NA2D_CHECK_PROBLEM(p);
-    if (int st = check_fused_bwd(p, q, k, v, rpb, lse, dout, dq, dk, dv, d_rpb, workspace, workspace_bytes, na2d_workspace_bytes(p, NA2D_WS_FUSED_BWD)); st != NA2D_OK) return st;
+static int fused_bwd(const na2d_problem *p, const void *q, const void *k, const void *v, const void *rpb, float scale,
+                     const float *lse, const void *dout, void *dq, void *dk, void *dv, BiasOut d_rpb, void *workspace,
+                     size_t workspace_bytes, void *stream) {
+    if (int st = check_fused_bwd(p, q, k, v, rpb, lse, dout, dq, dk, dv, d_rpb.to, workspace, workspace_bytes, na2d_workspace_bytes(p, NA2D_WS_FUSED_BWD)); st != NA2D_OK) return st;
     const Problem pr = to_problem(p);
     hipStream_t s = static_cast<hipStream_t>(stream);
     char *ws = static_cast<char *>(workspace);
@@ -277,6 +283,18 @@ int na2d_fused_bwd(const na2d_problem *p, const void *q, const void *k, const vo
     if (launch_softmax(pr, attn, attn, s) != hipSuccess) return from_hip(hipErrorLaunchFailure);
     return run_bwd(pr, q, k, v, attn, dout, scale, dq, dk, dv, d_rpb, ws + fused_bwd_attn_bytes(pr), s);
 }
+int na2d_fused_bwd(const na2d_problem *p, const void *q, const void *k, const void *v, const void *rpb, float scale,
+                   const float *lse, const void *dout, void *dq, void *dk, void *dv, float *d_rpb, void *workspace,
+                   size_t workspace_bytes, void *stream) {
+    NA2D_CHECK_PROBLEM(p);
+    return fused_bwd(p, q, k, v, rpb, scale, lse, dout, dq, dk, dv, BiasOut{d_rpb, NA2D_F32}, workspace, workspace_bytes, stream);
+}
+int na2d_fused_bwd_typed(const na2d_problem *p, const void *q, const void *k, const void *v, const void *rpb, float scale,
+                         const float *lse, const void *dout, void *dq, void *dk, void *dv, void *d_rpb, void *workspace,
+                         size_t workspace_bytes, void *stream) {
+    NA2D_CHECK_PROBLEM(p);
+    return fused_bwd(p, q, k, v, rpb, scale, lse, dout, dq, dk, dv, BiasOut{d_rpb, p->dtype}, workspace, workspace_bytes, stream);
+}
 
 size_t na2d_direct_bwd_workspace_bytes(const na2d_problem *p) {
     if (validate(p) != NA2D_OK) return 0;
@@ -284,14 +302,25 @@ size_t na2d_direct_bwd_workspace_bytes(const na2d_problem *p) {
     return patch_bwd_supported(pr) ? patch_bwd_workspace_bytes(pr) : 0;
 }
 
+static int direct_bwd(const na2d_problem *p, const void *q, const void *k, const void *v, const void *rpb, float scale,
+                      const float *lse, const void *dout, void *dq, void *dk, void *dv, BiasOut d_rpb, void *workspace,
+                      size_t workspace_bytes, void *stream) {
+    const size_t needed = na2d_direct_bwd_workspace_bytes(p);
+    if (int st = check_fused_bwd(p, q, k, v, rpb, lse, dout, dq, dk, dv, d_rpb.to, workspace, workspace_bytes, needed); st != NA2D_OK) return st;
+    if (needed == 0) return NA2D_ERR_WORKSPACE;
+    return from_hip(launch_patch_bwd(to_problem(p), q, k, v, rpb, scale, lse, dout, dq, dk, dv, d_rpb, workspace, static_cast<hipStream_t>(stream)));
+}
 int na2d_direct_bwd(const na2d_problem *p, const void *q, const void *k, const void *v, const void *rpb, float scale,
                     const float *lse, const void *dout, void *dq, void *dk, void *dv, float *d_rpb, void *workspace,
                     size_t workspace_bytes, void *stream) {
     NA2D_CHECK_PROBLEM(p);
-    const size_t needed = na2d_direct_bwd_workspace_bytes(p);
-    if (int st = check_fused_bwd(p, q, k, v, rpb, lse, dout, dq, dk, dv, d_rpb, workspace, workspace_bytes, needed); st != NA2D_OK) return st;
-    if (needed == 0) return NA2D_ERR_WORKSPACE;
-    return from_hip(launch_patch_bwd(to_problem(p), q, k, v, rpb, scale, lse, dout, dq, dk, dv, d_rpb, workspace, static_cast<hipStream_t>(stream)));
+    return direct_bwd(p, q, k, v, rpb, scale, lse, dout, dq, dk, dv, BiasOut{d_rpb, NA2D_F32}, workspace, workspace_bytes, stream);
+}
+int na2d_direct_bwd_typed(const na2d_problem *p, const void *q, const void *k, const void *v, const void *rpb, float scale,
+                          const float *lse, const void *dout, void *dq, void *dk, void *dv, void *d_rpb, void *workspace,
+                          size_t workspace_bytes, void *stream) {
+    NA2D_CHECK_PROBLEM(p);
+    return direct_bwd(p, q, k, v, rpb, scale, lse, dout, dq, dk, dv, BiasOut{d_rpb, p->dtype}, workspace, workspace_bytes, stream);
 }
 
 int na2d_debug_indices(const na2d_problem *p, int32_t *key_index, int32_t *rpb_index, void *stream) {

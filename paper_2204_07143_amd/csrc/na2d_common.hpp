@@ -54,6 +54,17 @@ __host__ __device__ __forceinline__ int inv_last(int j, int L, int K) {
 
 typedef _Float16 f16_t;
 typedef __bf16 bf16_t;
+// Where a bias gradient goes: fp32, or rounded from it to the problem's type by the kernel that forms the last sum (no second launch).
+struct BiasOut {
+    void *to;
+    int dtype;
+    explicit operator bool() const { return to != nullptr; }
+    __device__ __forceinline__ void store(size_t i, float x) const {
+        if (dtype == NA2D_F32) static_cast<float *>(to)[i] = x;
+        else if (dtype == NA2D_F16) static_cast<f16_t *>(to)[i] = (f16_t)x;
+        else static_cast<bf16_t *>(to)[i] = (bf16_t)x;
+    }
+};
 typedef _Float16 f16x2 __attribute__((ext_vector_type(2)));
 typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));

@@ -146,7 +146,7 @@ __global__ __launch_bounds__(256) void rpb_generic_partial_kernel(const T *__res
 // second level: 64 cells of a head per workgroup; wave w adds the partials w, w + 16, ... of the head (plane by plane,
 // row range by row range), then the 16 sums are added in wave order
 constexpr int kFinalWaves = 16;
-__global__ __launch_bounds__(kFinalWaves *kWave) void rpb_generic_final_kernel(const float *__restrict__ partial, float *__restrict__ d_rpb,
+__global__ __launch_bounds__(kFinalWaves *kWave) void rpb_generic_final_kernel(const float *__restrict__ partial, BiasOut d_rpb,
                                                                                int B, int heads, int cells, int groups) {
     __shared__ float sums[kFinalWaves][kWave];
     const int blocks = (cells + kWave - 1) / kWave, h = blockIdx.x / blocks;
@@ -165,7 +165,7 @@ __global__ __launch_bounds__(kFinalWaves *kWave) void rpb_generic_final_kernel(c
         float t = 0.f;
 #pragma unroll
         for (int w = 0; w < kFinalWaves; ++w) t += sums[w][lane];
-        d_rpb[(size_t)h * cells + cell] = t;
+        d_rpb.store((size_t)h * cells + cell, t);
     }
 }
 
@@ -231,7 +231,7 @@ size_t rpb_generic_workspace_bytes(const Problem &p) {
     return (size_t)p.planes() * rpb_generic_groups(p) * nb * nb * sizeof(float);
 }
 
-hipError_t launch_rpb_generic(const Problem &p, const void *ds, float *d_rpb, void *workspace, hipStream_t s) {
+hipError_t launch_rpb_generic(const Problem &p, const void *ds, BiasOut d_rpb, void *workspace, hipStream_t s) {
     const int nb = 2 * p.K - 1, cells = nb * nb, groups = rpb_generic_groups(p);
     NA2D_DISPATCH_T(p.dtype, hipLaunchKernelGGL((rpb_generic_partial_kernel<T>), dim3((unsigned)(((cells + 255) / 256) * (size_t)p.planes() * groups)), dim3(256), 0, s,
                                                 static_cast<const T *>(ds), static_cast<float *>(workspace), shape_of(p), groups));

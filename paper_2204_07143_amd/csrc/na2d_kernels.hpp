@@ -7,6 +7,7 @@
 
 #include "lds_attr.hpp"
 #include "na2d.h"
+#include "na2d_common.hpp"
 
 namespace na2d {
 
@@ -35,7 +36,7 @@ hipError_t launch_softmax_bwd_generic(const Problem &p, const void *attn, const 
 hipError_t launch_fused_strip(const Problem &p, const void *q, const void *k, const void *v, const void *rpb, float scale,
                                 void *out, float *lse, hipStream_t s);
 size_t rpb_generic_workspace_bytes(const Problem &p);
-hipError_t launch_rpb_generic(const Problem &p, const void *ds, float *d_rpb, void *workspace, hipStream_t s);
+hipError_t launch_rpb_generic(const Problem &p, const void *ds, BiasOut d_rpb, void *workspace, hipStream_t s);
 hipError_t launch_indices_generic(const Problem &p, int32_t *key_index, int32_t *rpb_index, hipStream_t s);
 
 // logits = scale * <x, y_window> + bias   (QK+RPB, and grad-a with x = dout, y = v, no bias)
@@ -66,10 +67,10 @@ hipError_t launch_inverse_mfma(const Problem &p, const void *w, const void *x, f
 hipError_t launch_softmax(const Problem &p, const void *logits, void *out, hipStream_t s);
 hipError_t launch_softmax_bwd(const Problem &p, const void *attn, const void *dp, void *ds, hipStream_t s);
 size_t rpb_bwd_workspace_bytes(const Problem &p);
-hipError_t launch_rpb_bwd(const Problem &p, const void *ds, float *d_rpb, void *workspace, hipStream_t s);
+hipError_t launch_rpb_bwd(const Problem &p, const void *ds, BiasOut d_rpb, void *workspace, hipStream_t s);
 // the same with the partials in the library's own device array (NA2D_NOALLOC_SCRATCH_BYTES); bytes it needs
 size_t rpb_bwd_partial_bytes(const Problem &p);
-hipError_t launch_rpb_bwd_noalloc(const Problem &p, const void *ds, float *d_rpb, hipStream_t s);
+hipError_t launch_rpb_bwd_noalloc(const Problem &p, const void *ds, BiasOut d_rpb, hipStream_t s);
 // grad-q that also leaves partial bias gradients (f16 / bf16, K <= 7): workgroup wg of the launch covers
 // tile position wg % npos, head (wg / npos) % heads and batch range wg / (npos * heads) of `splits`
 struct AvRpbSplit {
@@ -84,7 +85,7 @@ bool av_rpb_supported(const Problem &p);
 AvRpbSplit av_rpb_split(const Problem &p);
 hipError_t launch_av_rpb(const Problem &p, const void *w, const void *y, float scale, void *out, float *rpb_partial,
                          hipStream_t s);
-hipError_t launch_rpb_final_av(const Problem &p, const float *partial, float *d_rpb, AvRpbSplit sp, hipStream_t s);
+hipError_t launch_rpb_final_av(const Problem &p, const float *partial, BiasOut d_rpb, AvRpbSplit sp, hipStream_t s);
 // fused backward (two kernels): query patches -> dq, delta, partial bias gradients; key patches -> dk, dv
 bool fused_bwd_supported(const Problem &p);
 AvRpbSplit fused_bwd_split(const Problem &p);
@@ -98,7 +99,7 @@ hipError_t launch_fbwd_kv(const Problem &p, const void *q, const void *k, const 
 bool patch_bwd_supported(const Problem &p);
 size_t patch_bwd_workspace_bytes(const Problem &p);
 hipError_t launch_patch_bwd(const Problem &p, const void *q, const void *k, const void *v, const void *rpb, float scale,
-                            const float *lse, const void *dout, void *dq, void *dk, void *dv, float *d_rpb, void *workspace, hipStream_t s);
+                            const float *lse, const void *dout, void *dq, void *dk, void *dv, BiasOut d_rpb, void *workspace, hipStream_t s);
 // fused forward over query patches, any window side, head dim and storage type while its rows fit the LDS (na2d_patch_fwd.hip)
 bool patch_fwd_preferred(const Problem &p);
 hipError_t launch_patch_fwd(const Problem &p, const void *q, const void *k, const void *v, const void *rpb, float scale, void *out,

@@ -792,8 +792,8 @@ size_t patch_bwd_workspace_bytes(const Problem &p) {
 }
 
 hipError_t launch_patch_bwd(const Problem &p, const void *q, const void *k, const void *v, const void *rpb, float scale, const float *lse,
-                            const void *dout, void *dq, void *dk, void *dv, float *d_rpb, void *workspace, hipStream_t s) {
-    const PatchPlan pl = patch_plan(p, rpb != nullptr, d_rpb != nullptr);
+                            const void *dout, void *dq, void *dk, void *dv, BiasOut d_rpb, void *workspace, hipStream_t s) {
+    const PatchPlan pl = patch_plan(p, rpb != nullptr, (bool)d_rpb);
     if (!pl.ok) return hipErrorInvalidValue;
     char *ws = static_cast<char *>(workspace);
     float *ld = reinterpret_cast<float *>(ws);
@@ -807,7 +807,7 @@ hipError_t launch_patch_bwd(const Problem &p, const void *q, const void *k, cons
         return hipErrorInvalidValue;
     };
     e = run();
-    if (e != hipSuccess || d_rpb == nullptr) return e;
+    if (e != hipSuccess || !d_rpb) return e;
     return launch_rpb_final_av(p, partial, d_rpb, AvRpbSplit{pl.kv.units / p.heads, pl.kv.splits}, s);
 }
 

@@ -182,7 +182,7 @@ struct __attribute__((packed, aligned(4))) RpbQuad {
 };
 constexpr int kRpbFinalLanes = 16, kRpbFinalGroups = kRpbFinalWaves * kWave / kRpbFinalLanes;
 __global__ __launch_bounds__(kRpbFinalWaves *kWave) void rpb_final_kernel(const float *__restrict__ partial,
-                                                                           float *__restrict__ d_rpb, int n, int cells,
+                                                                           BiasOut d_rpb, int n, int cells,
                                                                            int stride) {
     __shared__ f32x4 sub[kRpbFinalGroups][kRpbFinalLanes];
     const int quad_blocks = (stride / 4 + kRpbFinalLanes - 1) / kRpbFinalLanes;
@@ -220,12 +220,12 @@ __global__ __launch_bounds__(kRpbFinalWaves *kWave) void rpb_final_kernel(const 
         if (part == 0 && cell0 < cells) {
 #pragma unroll
             for (int c = 0; c < 4; ++c)
-                if (cell0 + c < cells) d_rpb[(size_t)h * cells + cell0 + c] = t[c];
+                if (cell0 + c < cells) d_rpb.store((size_t)h * cells + cell0 + c, t[c]);
         }
     }
 }
 
-static hipError_t launch_rpb_final(const float *partial, float *d_rpb, int heads, int n, int cells, hipStream_t s) {
+static hipError_t launch_rpb_final(const float *partial, BiasOut d_rpb, int heads, int n, int cells, hipStream_t s) {
     const int stride = rpb_cell_stride(cells);
     hipLaunchKernelGGL(rpb_final_kernel, dim3(heads * ((stride / 4 + kRpbFinalLanes - 1) / kRpbFinalLanes)), dim3(kRpbFinalWaves * kWave), 0, s,
                        partial, d_rpb, n, cells, stride);
@@ -234,7 +234,7 @@ static hipError_t launch_rpb_final(const float *partial, float *d_rpb, int heads
 
 // d_rpb from the partials that the grad-q kernel (or the fused backward's query-patch kernel) leaves: workgroup
 // (position, head, split) of those kernels writes row head * (splits * npos) + split * npos + position.
-hipError_t launch_rpb_final_av(const Problem &p, const float *partial, float *d_rpb, AvRpbSplit sp, hipStream_t s) {
+hipError_t launch_rpb_final_av(const Problem &p, const float *partial, BiasOut d_rpb, AvRpbSplit sp, hipStream_t s) {
     const int nb = 2 * p.K - 1;
     return launch_rpb_final(partial, d_rpb, p.heads, sp.npos * sp.splits, nb * nb, s);
 }
@@ -253,7 +253,7 @@ size_t rpb_bwd_workspace_bytes(const Problem &p) {
 }
 
 template <typename T, int K>
-static hipError_t launch_rpb_bwd_t(const Problem &p, const void *ds, float *d_rpb, void *workspace, hipStream_t s) {
+static hipError_t launch_rpb_bwd_t(const Problem &p, const void *ds, BiasOut d_rpb, void *workspace, hipStream_t s) {
     using C = RpbCfg<T, K>;
     const RpbSplit sp = rpb_split(p.planes(), p.H, p.W, K, (int)sizeof(T));
     auto kern = rpb_partial_kernel<T, K>;
@@ -268,7 +268,7 @@ static hipError_t launch_rpb_bwd_t(const Problem &p, const void *ds, float *d_rp
     return launch_rpb_final(static_cast<const float *>(workspace), d_rpb, p.heads, p.B * sp.groups_per_plane, C::CELLS, s);
 }
 
-hipError_t launch_rpb_bwd(const Problem &p, const void *ds, float *d_rpb, void *workspace, hipStream_t s) {
+hipError_t launch_rpb_bwd(const Problem &p, const void *ds, BiasOut d_rpb, void *workspace, hipStream_t s) {
     if (untuned_window(p)) return launch_rpb_generic(p, ds, d_rpb, workspace, s);
     NA2D_DISPATCH_T(p.dtype, NA2D_DISPATCH_K(p.K, return (launch_rpb_bwd_t<T, K>(p, ds, d_rpb, workspace, s))));
     return hipErrorInvalidValue;
@@ -311,7 +311,7 @@ static hipError_t scratch_address(void **out) {
     return hipSuccess;
 }
 
-hipError_t launch_rpb_bwd_noalloc(const Problem &p, const void *ds, float *d_rpb, hipStream_t s) {
+hipError_t launch_rpb_bwd_noalloc(const Problem &p, const void *ds, BiasOut d_rpb, hipStream_t s) {
     if (rpb_bwd_partial_bytes(p) > sizeof(scratch)) return hipErrorInvalidValue;   // the C ABI layer has refused it already
     void *ptr = nullptr;
     if (hipError_t e = scratch_address(&ptr); e != hipSuccess) return e;
