@@ -60,6 +60,7 @@ struct FusedSmallCfg {
     static constexpr int kLdsBytes = (kOneStage ? 1 : 2) * kStageBytes;
     static constexpr int kKeyBytesG = NS * Traits<T>::kKeyBytes;   // bytes per position in memory
     static constexpr int kWavesPerSimd = kLdsBytes <= 80 * 1024 ? 4 : 2;   // two workgroups, or one, per compute unit
+    static constexpr bool kBiasRuns = !kOneStage && BiasRuns<K>::kBytes <= kStageBytes;
 };
 
 template <typename T, int K, int NS>
@@ -142,7 +143,36 @@ __global__ __launch_bounds__(512, (FusedSmallCfg<T, K, NS>::kWavesPerSimd)) void
     // bias of (this lane's query, halo position), -inf outside the query's window; packed fp16 pairs
     // (half the registers; the fma below reads them as mixed-precision operands; see bias_to_f16)
     f16x2 biasm[P::NEL / 2];
-    {
+    if constexpr (C::kBiasRuns) {
+        // In the order of the halo positions a window is K runs of K positions, PW from one to the next.  The head's table goes to the second
+        // buffer pair, which is still free, in K copies: copy `x` holds row u from its column x on as a run of K entries and PW - K times -inf,
+        // the rows one behind the other.  So a lane's entries follow each other, with the columns outside its window masked; the pairs
+        // outside its rows are masked here (an entry that shares a pair with one of its rows is -inf in the copy).
+        // (A cell and a load from memory per position, as below, were half of a workgroup's vector instructions where it has few
+        // planes: 2 x 2 x 200 x 334 fp16, k = 7 22.9 -> 21.4 us a call; a 14 x 14 map's 21 -> 19.)
+        using B = BiasRuns<K>;
+        const int run0 = lds0 + C::kStageBytes + B::kFront * 2;
+        const T *tbl = rpb != nullptr ? rpb + (size_t)head * C::NB * C::NB : nullptr;
+#pragma unroll
+        for (int n0 = -1; n0 < B::kEntries; n0 += C::kThreads) {
+            const int n = n0 + tid, copy = n / B::kCopy, in = n - copy * B::kCopy, u = in / P::PW, c = in - u * P::PW;
+            const bool entry = n >= 0 && c < K;
+            f16_t x = entry ? (f16_t)0.f : (f16_t)-INFINITY;
+            if (tbl != nullptr && entry && n < B::kEntries) x = bias_to_f16(tbl[(unsigned)(u * C::NB + c + copy)]);
+            if (n < B::kEntries) *lds_ptr<f16_t>(run0 + n * 2) = x;
+        }
+        const int cy = qy < H ? qy : H - 1, cx = qx < W ? qx : W - 1, sy = win_start(cy, H, K), sx = win_start(cx, W, K);
+        const int t0 = 4 * g - (sy - oy) * P::PW - (sx - ox);   // of the lane's first position, counted from its window's first
+        const int mine = run0 + ((sx - cx + K - 1) * B::kCopy + (sy - cy + K - 1) * P::PW + t0) * 2;
+        const int check = q_ok ? t0 + 1 : 1 << 20;
+        workgroup_sync();
+#pragma unroll
+        for (int e = 0; e < P::NEL; e += 2) {
+            const int at = 16 * (e >> 2) + (e & 3);
+            const f16x2 pair{*lds_ptr<f16_t>(mine + at * 2), *lds_ptr<f16_t>(mine + at * 2 + 2)};
+            biasm[e >> 1] = (unsigned)(check + at) < (unsigned)(K * P::PW) ? pair : f16x2{(f16_t)-INFINITY, (f16_t)-INFINITY};
+        }
+    } else {
         const int wy = win_start(qy < H ? qy : H - 1, H, K) - oy, wx = win_start(qx < W ? qx : W - 1, W, K) - ox;
         // Built per group of four consecutive halo positions (e / 4): the positions of a group that lie
         // inside the query's window are in one halo row (a halo row holds K + 3 positions, the window K of

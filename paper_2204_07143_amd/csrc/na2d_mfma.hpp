@@ -71,6 +71,14 @@ template <int K> struct Patch {
     __device__ static __forceinline__ int row_of(int h) { return (int)(((unsigned)h * kMagic) >> 16); }
 };
 
+// The bias table as runs in the order of a patch's halo positions (see its use in the fused forward): `kCopy` entries per copy, K copies; a lane
+// reads up to 3 rows and 3 columns in front of them and, behind, what its blocks run on (those are masked).
+template <int K> struct BiasRuns {
+    using P = Patch<K>;
+    static constexpr int kCopy = (2 * K - 1) * P::PW, kEntries = K * kCopy, kFront = (4 * P::PW + 7) / 8 * 8, kBack = 16 * P::NBLK;
+    static constexpr int kBytes = (kFront + kEntries + kBack) * 2;
+};
+
 // First (virtual, possibly negative) key coordinate of the halo that serves the n consecutive
 // queries q0 .. q0+n-1 on an axis of length L.  It is q0 - R wherever that works: then the bias
 // cell of (query, key) is the same function of their positions inside patch and halo for every
