@@ -17,7 +17,7 @@
 // A masked product is 0 * x: where x is not finite it would spoil positions whose window does not hold it, so results that are not
 // finite are computed once more from their own window only.
 // Measured (us, both parts and the bias gradient, in brackets the steps before: weights recomputed into memory and the unfused backward):
-// 64 x 2 x 56 x 56 queries, fp16, 32 channels, k = 13 82 + 149 + 6 (455); fp32, k = 7 189 + 216 + 6 (700); fp16, 64 channels (one head), k = 7 47 + 66 + 8
+// 64 x 2 x 56 x 56 queries, fp16, 32 channels, k = 13 80 + 146 + 6 (455); fp32, k = 7 189 + 216 + 6 (700); fp16, 64 channels (one head), k = 7 47 + 65 + 8
 // (165); 4 x 2 x 64 x 64, bf16, k = 21 17 + 44 + 5 (220).  By counters at the first shape part 1 issues 60 vector instructions per
 // 16 x 16 products, of which a block needs 40, and waits 43 % of its wave cycles: its four waves per SIMD do not cover the chain from LDS through
 // two products, the exponential and two more.  Part 2 adds the integer additions in LDS (43 us with a bias, 4 copies of the table).  fp32 is
@@ -545,7 +545,7 @@ __global__ __launch_bounds__(kPatchThreads, (kPatchOcc<T, D>)) void patch_bwd_kv
         auto blocks = [&](auto n, int img, int brow, int cell, bool rowok, int bx) {
             constexpr int N = decltype(n)::value;
             const int qa0 = img + aoff + bx * 4 * POSB, da0 = qa0 + img_bytes, qt0 = img + toff + bx * 4 * POSB, dt0 = qt0 + img_bytes;
-            constexpr bool kTight = D == 32 || (sizeof(T) == 2 && D == 64);
+            constexpr bool kTight = sizeof(T) == 4 && D == 32;   // (16 bit has the registers: 2 % faster with all of a block's reads in flight)
             const int l0 = img + 2 * img_bytes + loff + bx * 4 * QB, b0 = brow - bx * 16, c0 = cell - 4 * bx;
             f32x4 s4[N], dp[N];
             Weights4<T> wp[N], ws[N];
