@@ -16,7 +16,7 @@
  *  - Layouts:  q, k, v, out, dout, dq, dk, dv : [B, heads, L, D]    (problem dtype)
  *              logits, p, dp, ds             : [B, heads, L, k]    (problem dtype)
  *              rpb                           : [heads, 2k-1]       (problem dtype)
- *              d_rpb                         : [heads, 2k-1]       (fp32; the problem's dtype in the _typed calls)
+ *              d_rpb                         : [heads, 2k-1]       (always fp32; see na_typed.h)
  *              lse                           : [B, heads, L]       (always fp32)
  *    Window slot a addresses key s(i) + a, s(i) = clamp(i - (k-1)/2, 0, L - k); the bias cell
  *    of (query i, key j) is rpb[head, j - i + k - 1].
@@ -89,10 +89,6 @@ size_t na1d_workspace_bytes(const na1d_problem *p);
 int na1d_fused_bwd(const na1d_problem *p, const void *q, const void *k, const void *v, const void *rpb, float scale,
                    const float *lse, const void *dout, void *dq, void *dk, void *dv, float *d_rpb, void *workspace,
                    size_t workspace_bytes, void *stream);
-/* the same with d_rpb in the problem's dtype, rounded once from the fp32 sums */
-int na1d_fused_bwd_typed(const na1d_problem *p, const void *q, const void *k, const void *v, const void *rpb, float scale,
-                         const float *lse, const void *dout, void *dq, void *dk, void *dv, void *d_rpb, void *workspace,
-                         size_t workspace_bytes, void *stream);
 size_t na1d_fused_bwd_workspace_bytes(const na1d_problem *p);
 
 #ifdef __cplusplus

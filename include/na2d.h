@@ -21,7 +21,7 @@
  *  - Layouts:  q, k, v, out, dout, dq, dk, dv : [B, heads, H, W, D]      (problem dtype)
  *              logits, p, dp, ds             : [B, heads, H, W, k*k]    (problem dtype)
  *              rpb                           : [heads, 2k-1, 2k-1]      (problem dtype)
- *              d_rpb                         : [heads, 2k-1, 2k-1]      (fp32; the problem's dtype in the _typed calls)
+ *              d_rpb                         : [heads, 2k-1, 2k-1]      (always fp32; see na_typed.h)
  *              lse                           : [B, heads, H, W]         (always fp32)
  *    Window slot a*k + c addresses key (s(qy) + a, s(qx) + c), where
  *    s(i) = clamp(i - (k-1)/2, 0, L - k) is the first key coordinate seen by query
@@ -217,15 +217,6 @@ int na2d_direct_bwd(const na2d_problem *p, const void *q, const void *k, const v
                     float scale, const float *lse, const void *dout, void *dq, void *dk, void *dv, float *d_rpb,
                     void *workspace, size_t workspace_bytes, void *stream);
 size_t na2d_direct_bwd_workspace_bytes(const na2d_problem *p);
-
-/* The same calls with the bias gradient in the problem's dtype: the fp32 sums are rounded once as they are stored. */
-int na2d_qk_bwd_rpb_typed(const na2d_problem *p, const void *ds, void *d_rpb, void *workspace, size_t workspace_bytes, void *stream);
-int na2d_fused_bwd_typed(const na2d_problem *p, const void *q, const void *k, const void *v, const void *rpb,
-                         float scale, const float *lse, const void *dout, void *dq, void *dk, void *dv, void *d_rpb,
-                         void *workspace, size_t workspace_bytes, void *stream);
-int na2d_direct_bwd_typed(const na2d_problem *p, const void *q, const void *k, const void *v, const void *rpb,
-                          float scale, const float *lse, const void *dout, void *dq, void *dk, void *dv, void *d_rpb,
-                          void *workspace, size_t workspace_bytes, void *stream);
 
 /* Bytes of device workspace the given call needs for this problem (0 on invalid problems). */
 size_t na2d_workspace_bytes(const na2d_problem *p, int kind);

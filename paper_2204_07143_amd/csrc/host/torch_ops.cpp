@@ -22,8 +22,7 @@
 #include <limits>
 #include <optional>
 
-#include "na1d.h"
-#include "na2d.h"
+#include "na_typed.h"
 
 namespace {
 

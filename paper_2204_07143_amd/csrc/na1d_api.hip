@@ -4,6 +4,7 @@
 
 #include "na1d.h"
 #include "na1d_kernels.hpp"
+#include "na_typed.h"
 
 namespace na1d {
 

@@ -5,6 +5,7 @@
 #include "na2d.h"
 #include "na2d_common.hpp"
 #include "na2d_kernels.hpp"
+#include "na_typed.h"
 #include "na2d_valu_cfg.hpp"
 
 namespace na2d {
