@@ -296,7 +296,7 @@ __device__ __forceinline__ int dynamic_lds(const char *lds) {
 struct PatchShape {
     int H, W, K, heads, tiles_y, units, splits;
     int rw;                // positions per image row
-    int lg_split;          // 2^lg_split waves share a patch, each with its rows of blocks (forward)
+    int lg_split;          // 2^lg_split waves share a patch, each with its rows of blocks (forward; backward, key side: 0 or 1)
     int lg_cols;           // a tile is 2^lg_cols patches wide and (8 >> lg_split) / 2^lg_cols patches high
     int nstage;            // LDS buffers (1: reloaded between steps)
     int copies;            // of the integer bias gradients

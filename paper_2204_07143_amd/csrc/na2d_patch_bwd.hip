@@ -18,7 +18,7 @@
 // finite are computed once more from their own window only.
 // Measured (us, both parts and the bias gradient, in brackets the steps before: weights recomputed into memory and the unfused backward):
 // 64 x 2 x 56 x 56 queries, fp16, 32 channels, k = 13 80 + 146 + 6 (455); fp32, k = 7 189 + 216 + 6 (700); fp16, 64 channels (one head), k = 7 47 + 65 + 8
-// (165); 4 x 2 x 64 x 64, bf16, k = 21 17 + 44 + 5 (220).  By counters at the first shape part 1 issues 60 vector instructions per
+// (165); 4 x 2 x 64 x 64, bf16, k = 21 17 + 40 + 5 (220).  By counters at the first shape part 1 issues 60 vector instructions per
 // 16 x 16 products, of which a block needs 40, and waits 43 % of its wave cycles: its four waves per SIMD do not cover the chain from LDS through
 // two products, the exponential and two more.  Part 2 adds the integer additions in LDS (43 us with a bias, 4 copies of the table).  fp32 is
 // nearer to its matrix cores: 32 instructions of 32 cycles per block, 94 us a part.
@@ -428,14 +428,16 @@ __host__ __device__ constexpr int flag_bytes(int cells) { return (cells + 127) /
 template <typename T> __host__ __device__ constexpr int table_bytes(int cells, int copies) { return (copies > 1 ? copies * int_words(cells) : cells) * BiasSums<T>::kIntBytes; }
 template <typename T> __host__ __device__ constexpr int dbias_bytes(int cells, int copies) { return cells * BiasSums<T>::kSumBytes + table_bytes<T>(cells, copies) + flag_bytes(cells); }
 
-template <typename T, int D>
+// LGS 1: two waves share a patch, the even and the odd rows of blocks, and a workgroup takes one plane (its integers go straight to its partial
+// bias gradient).
+template <typename T, int D, int LGS>
 __global__ __launch_bounds__(kPatchThreads, (kPatchOcc<T, D>)) void patch_bwd_kv_kernel(
     const T *__restrict__ q, const T *__restrict__ k, const T *__restrict__ v, const T *__restrict__ rpb, float scale,
     const float *__restrict__ ld, const uint32_t *__restrict__ bound, const T *__restrict__ dout, T *__restrict__ dk, T *__restrict__ dv,
     float *__restrict__ partial, PatchShape g) {
     using CV = ChanVec<T, D>;
     using Op = PosOp<T, D>;
-    constexpr int POSB = Op::POSB, QB = kQueryWords<T> * 4;
+    constexpr int POSB = Op::POSB, QB = kQueryWords<T> * 4, STEP = 4 << LGS;   // map rows per step
     extern __shared__ __align__(16) char lds[];
     const int wg = xcd_contiguous_block(blockIdx.x, gridDim.x);
     if (wg >= g.units * g.splits) return;
@@ -443,33 +445,34 @@ __global__ __launch_bounds__(kPatchThreads, (kPatchOcc<T, D>)) void patch_bwd_kv
     const int head = work.head, K = g.K, H = g.H, W = g.W, NB = 2 * K - 1, pitch = bias_pitch(K);
     const int tid = threadIdx.x, lane = tid % kWave, wave = __builtin_amdgcn_readfirstlane(tid / kWave);
     const int j = lane & 15, gr = lane >> 4;
+    const int part = wave & ((1 << LGS) - 1), pw = wave >> LGS;   // the wave's row of blocks in a step, and its patch of the tile
     using Table = BiasSums<T>;
-    const int cells = NB * pitch, sums0 = dynamic_lds(lds), table0 = sums0 + (g.with_dbias ? cells * Table::kSumBytes : 0);
+    const int cells = NB * pitch, sums0 = dynamic_lds(lds), table0 = sums0 + (g.with_dbias && LGS == 0 ? cells * Table::kSumBytes : 0);
     const int flags0 = table0 + (g.with_dbias ? table_bytes<T>(cells, g.copies) : 0), bias0 = flags0 + (g.with_dbias ? flag_bytes(cells) : 0);
     const int img0 = bias0 + bias_rows(K, g.with_bias) * pitch * 4;
-    const int img_bytes = 4 * g.rw * POSB, stage_bytes = 2 * img_bytes + 4 * g.rw * QB;
+    const int img_bytes = STEP * g.rw * POSB, stage_bytes = 2 * img_bytes + STEP * g.rw * QB;
 
-    const int lg = g.lg_cols, tw = 4 << lg, th = 32 >> lg, ty0 = work.ty * th, tx0 = work.tx * tw;
+    const int lg = g.lg_cols, tw = 4 << lg, th = (32 >> LGS) >> lg, ty0 = work.ty * th, tx0 = work.tx * tw;
     const int ty1 = ty0 + th - 1 < H - 1 ? ty0 + th - 1 : H - 1, tx1 = tx0 + tw - 1 < W - 1 ? tx0 + tw - 1 : W - 1;
     const int ry0 = inv_first(ty0, H, K), cx0 = inv_first(tx0, W, K);            // first query row and column of the tile
     const int ry1 = inv_last(ty1, H, K), cx1 = inv_last(tx1, W, K);
-    const int nsteps = (ry1 - ry0 + 4) >> 2;
-    const int sy0 = ty0 + 4 * (wave >> lg), px0 = tx0 + 4 * (lg == 2 ? patch_of_wave(wave) : wave & ((1 << lg) - 1));   // this wave's patch
+    const int nsteps = (ry1 - ry0 + STEP) >> (2 + LGS);
+    const int sy0 = ty0 + 4 * (pw >> lg), px0 = tx0 + 4 * (lg == 2 && LGS == 0 ? patch_of_wave(pw) : pw & ((1 << lg) - 1));   // this wave's patch
     const bool active = sy0 < H && px0 < W;
     const int sy3 = sy0 + 3 < H - 1 ? sy0 + 3 : H - 1, px3 = px0 + 3 < W - 1 ? px0 + 3 : W - 1;
     const int pyc = sy0 < H ? sy0 : H - 1, pxc = px0 < W ? px0 : W - 1;
-    const int s_lo = (inv_first(pyc, H, K) - ry0) >> 2, s_hi = (inv_last(sy3, H, K) - ry0) >> 2;
+    const int b_lo = (inv_first(pyc, H, K) - ry0) >> 2, b_hi = (inv_last(sy3, H, K) - ry0) >> 2;   // rows of blocks
     const int ox = inv_first(pxc, W, K), nbx = (inv_last(px3, W, K) - ox + 4) >> 2;
     const int ky = sy0 + (j >> 2), kx = px0 + (j & 3);
     const bool key_ok = ky < H && kx < W;
     const int jx = kx < W ? kx : W - 1;
     // the columns of the queries that see the lane's key: the first (from ox) and their number
     const int fx = inv_first(jx, W, K) - ox, nx = inv_last(jx, W, K) - ox - fx + 1;
-    const int aoff = ((j >> 2) * g.rw + (ox - cx0) + (j & 3)) * POSB + gr * CV::kLaneBytes;
-    const int toff = Op::lane_offset(lane, g.rw) + (ox - cx0) * POSB;
+    const int aoff = ((4 * part + (j >> 2)) * g.rw + (ox - cx0) + (j & 3)) * POSB + gr * CV::kLaneBytes;
+    const int toff = Op::lane_offset(lane, g.rw) + (4 * part * g.rw + ox - cx0) * POSB;
     // columns [clear_lo, clear_hi) see every key of the patch
     const int clear_lo = inv_first(px3, W, K) - ox, clear_hi = inv_last(pxc, W, K) + 1 - ox, no_row = bias_rows(K, g.with_bias) - 1;
-    const int loff = (gr * g.rw + (ox - cx0)) * QB;
+    const int loff = ((4 * part + gr) * g.rw + (ox - cx0)) * QB;
     const int v0 = jx - ox + K - 1 + kBiasPad;     // (the cell falls with the query's row and column)
     const size_t plane_px = (size_t)H * W;
     const auto own_lane = own_lane_index;   // (recomputed where it is used: a register less in the inner loop)
@@ -483,12 +486,12 @@ __global__ __launch_bounds__(kPatchThreads, (kPatchOcc<T, D>)) void patch_bwd_kv
     auto issue = [&](int b, int s, int par) {
         const size_t px = ((size_t)b * g.heads + head) * plane_px;
         const int img = img0 + par * stage_bytes;
-        issue_rows<POSB>(reinterpret_cast<const char *>(q) + px * POSB, reinterpret_cast<const char *>(dout) + px * POSB, H, W, ry0 + 4 * s, cx0, g.rw, img, img_bytes, wave, lane);
+        issue_rows<POSB>(reinterpret_cast<const char *>(q) + px * POSB, reinterpret_cast<const char *>(dout) + px * POSB, H, W, ry0 + STEP * s, cx0, g.rw, img, img_bytes, wave, lane, STEP);
         int w = wave;
         asm volatile("" : "+s"(w));
-        const int row = w & 3, y = ry0 + 4 * s + row < H - 1 ? ry0 + 4 * s + row : H - 1;
+        const int row = w & (STEP - 1), y = ry0 + STEP * s + row < H - 1 ? ry0 + STEP * s + row : H - 1;
         constexpr int LB = kNormalised<T> ? 16 : 4, PER = QB / LB;   // bytes a lane loads, lanes per query
-        for (int s0 = (w >> 2) * kWave; s0 < PER * g.rw; s0 += (kPatchWaves / 4) * kWave) {
+        for (int s0 = (w >> (2 + LGS)) * kWave; s0 < PER * g.rw; s0 += (kPatchWaves / STEP) * kWave) {
             const int c = s0 + lane;
             int x = cx0 + c / PER;
             x = x < W - 1 ? x : W - 1;
@@ -635,10 +638,11 @@ __global__ __launch_bounds__(kPatchThreads, (kPatchOcc<T, D>)) void patch_bwd_kv
                 par ^= 1;
                 if (!last || b + 1 < work.b_end) issue(last ? b + 1 : b, last ? 0 : s + 1, par);
             }
-            if (active && s >= s_lo && s <= s_hi) {
+            const int br = (s << LGS) + part;   // this wave's row of blocks
+            if (active && br >= b_lo && br <= b_hi) {
                 // the lane's row of the block against its key (fp32: worked out anew in each step, for the registers)
                 const int lv = sizeof(T) == 4 ? own_lane_index() : lane;
-                const int qrow = ry0 + 4 * s + (lv >> 4), krow = sy0 + ((lv & 15) >> 2), kc = krow < H ? krow : H - 1, first = inv_first(kc, H, K);
+                const int qrow = ry0 + 4 * br + (lv >> 4), krow = sy0 + ((lv & 15) >> 2), kc = krow < H ? krow : H - 1, first = inv_first(kc, H, K);
                 const bool rowok = krow < H && px0 + (lv & 3) < W && qrow >= first && qrow <= inv_last(kc, H, K);
                 const int u = kc - qrow + K - 1, uc = u < 0 ? 0 : (u < NB - 1 ? u : NB - 1);
                 const int cell = uc * pitch + v0, brow = bias0 + ((rowok ? (g.with_bias ? uc : 0) : no_row) * pitch + v0) * 4;
@@ -665,7 +669,36 @@ __global__ __launch_bounds__(kPatchThreads, (kPatchOcc<T, D>)) void patch_bwd_kv
                     n += *lds_ptr<typename Table::Int>(a);
                     *lds_ptr<typename Table::Int>(a) = 0;
                 }
-                *lds_ptr<typename Table::Sum>(sums0 + i * Table::kSumBytes) += (typename Table::Sum)n * (typename Table::Sum)down;
+                if constexpr (LGS > 0) {
+                    const int u = fdiv(i, g.by_pitch), v = i - u * pitch - kBiasPad;
+                    if ((unsigned)v < (unsigned)NB) {
+                        const bool odd = (*lds_ptr<unsigned>(flags0 + (i >> 5) * 4) >> (i & 31)) & 1u;
+                        partial[(size_t)((head * g.splits + work.split) * g.gd.npos + work.pos) * rpb_cell_stride(NB * NB) + u * NB + v] =
+                            odd ? NAN : (float)((typename Table::Sum)n * (typename Table::Sum)down);
+                    }
+                } else {
+                    *lds_ptr<typename Table::Sum>(sums0 + i * Table::kSumBytes) += (typename Table::Sum)n * (typename Table::Sum)down;
+                }
+            }
+        }
+        if constexpr (LGS > 0) {
+            // the two waves of a patch, joined by the first (one plane per workgroup: nothing is on its way to the images)
+            static_assert(LGS == 1 && sizeof(T) == 2, "pairs of waves");
+            workgroup_sync();
+            const int mine = img0 + pw * Op::NA * 2048 + lane * 16;
+            if (part > 0) {
+#pragma unroll
+                for (int i = 0; i < Op::NA; ++i) {
+                    *lds_ptr<f32x4>(mine + i * 2048) = sk.acc[i];
+                    *lds_ptr<f32x4>(mine + i * 2048 + 1024) = sv.acc[i];
+                }
+            }
+            workgroup_sync();
+            if (part > 0) continue;
+#pragma unroll
+            for (int i = 0; i < Op::NA; ++i) {
+                sk.acc[i] += *lds_ptr<f32x4>(mine + i * 2048);
+                sv.acc[i] += *lds_ptr<f32x4>(mine + i * 2048 + 1024);
             }
         }
         if (!active) continue;
@@ -689,7 +722,7 @@ __global__ __launch_bounds__(kPatchThreads, (kPatchOcc<T, D>)) void patch_bwd_kv
             }
         }
     }
-    if (g.with_dbias) {   // (each thread reads the sums it added up)
+    if (LGS == 0 && g.with_dbias) {   // (each thread reads the sums it added up)
         float *row = partial + (size_t)((head * g.splits + work.split) * g.gd.npos + work.pos) * rpb_cell_stride(NB * NB);
         for (int i = wave * kWave + own_lane(); i < cells; i += kPatchThreads) {
             const int u = fdiv(i, g.by_pitch), v = i - u * pitch - kBiasPad;
@@ -704,9 +737,15 @@ __global__ __launch_bounds__(kPatchThreads, (kPatchOcc<T, D>)) void patch_bwd_kv
 struct PatchPlan {
     PatchShape q, kv;
     int lds_q, lds_kv;
-    bool ok;
+    bool ok, pairs;   // pairs of waves in part 2
 };
 int query_bytes(const Problem &p) { return 4 * (p.dtype == NA2D_F32 ? kQueryWords<float> : kQueryWords<f16_t>); }
+// Pairs of waves in part 2: where one wave per patch leaves half of the chip's 4096 places for waves free, wide windows in 16 bit last as long as
+// the patch of a border takes (81 blocks at k = 21, one inside 36).  us of both parts and the bias gradient, fp16, 32 channels, one wave / two: k = 15
+// 40 / 34 at 256 patches, 44 / 39 at 1300, 43 / 42 at 2048, 60 / 67 at 4096; k = 21 62 / 48, 64 / 53, 66 / 62, 92 / 95.  (Up to k = 13 no choice looks at the batch.)
+bool pairs_wanted(const Problem &p) {
+    return p.dtype != NA2D_F32 && p.K > 13 && p.D <= 64 && (long long)p.planes() * ((p.H + 3) / 4) * ((p.W + 3) / 4) <= 2048;
+}
 PatchPlan patch_plan(const Problem &p, bool bias, bool dbias) {
     PatchPlan pl{};
     const int K = p.K, posb = p.D * p.elem_bytes(), pitch = bias_pitch(K), cells = (2 * K - 1) * pitch;
@@ -745,6 +784,35 @@ PatchPlan patch_plan(const Problem &p, bool bias, bool dbias) {
         pl.lds_kv = lds4;
     }
     pl.ok = pl.q.nstage > 0 && pl.kv.nstage > 0;
+    if (pl.ok && pairs_wanted(p)) {
+        // (whether there are pairs is decided as with both tables: the number of partial bias gradients follows from it)
+        const int most = bias_rows(K, true) * pitch * 4, ints = table_bytes<f16_t>(cells, 1) + flag_bytes(cells), joined = 4 * (p.D / 16) * 2048;
+        long long fewest = LLONG_MAX;
+        for (int l = 2; l >= 0; --l) {
+            const int w = 4 << l, h = 16 >> l, rows = h + K - 1 < p.H ? h + K - 1 : p.H;
+            const int rw = image_row(p.W, K, w, posb, [&](int x) { return inv_first(x, p.W, K); }, [&](int x) { return inv_last(x, p.W, K); });
+            const int step = 2 * 8 * rw * posb + 8 * rw * query_bytes(p), need = step > joined ? step : joined;
+            if (most + ints + need > 80 * 1024) continue;   // two workgroups per compute unit, or the second wave of a patch gains nothing
+            const int tx = (p.W + w - 1) / w, ty = (p.H + h - 1) / h;
+            const long long steps2 = (long long)tx * ty * ((rows + 7) / 8);
+            if (steps2 >= fewest) continue;
+            fewest = steps2;
+            pl.pairs = true;
+            const int fixed = table + (dbias ? ints : 0), fixed4 = table + (dbias ? table_bytes<f16_t>(cells, 4) + flag_bytes(cells) : 0);
+            pl.kv = s;
+            pl.kv.rw = rw;
+            pl.kv.lg_split = 1;
+            pl.kv.lg_cols = l;
+            pl.kv.tiles_y = ty;
+            pl.kv.units = tx * ty * p.heads;
+            pl.kv.splits = p.B;
+            pl.kv.gd = make_grid_decode(tx, ty, p.heads, p.B, p.B);
+            pl.kv.nstage = fixed + 2 * step <= 80 * 1024 ? 2 : 1;
+            pl.lds_kv = fixed + (pl.kv.nstage == 2 ? 2 * step : need);
+            pl.kv.copies = 1;
+            if (dbias && fixed4 - fixed + pl.lds_kv <= 80 * 1024) pl.kv.copies = 4, pl.lds_kv += fixed4 - fixed;
+        }
+    }
     return pl;
 }
 
@@ -754,13 +822,21 @@ size_t bound_count(const Problem &p) { return (size_t)p.planes() * ((p.H + 3) / 
 template <typename T, int D>
 hipError_t launch_patch_bwd_t(const Problem &p, const PatchPlan &pl, const T *q, const T *k, const T *v, const T *rpb, float scale,
                               const float *lse, const T *dout, T *dq, T *dk, T *dv, float *ld, uint32_t *bound, float *partial, hipStream_t s) {
-    static LdsAllowed allowed_q, allowed_kv;
+    static LdsAllowed allowed_q, allowed_kv, allowed_pairs;
     if (hipError_t e = allow_lds(patch_bwd_q_kernel<T, D>, 160 * 1024, allowed_q); e != hipSuccess) return e;
-    if (hipError_t e = allow_lds(patch_bwd_kv_kernel<T, D>, 160 * 1024, allowed_kv); e != hipSuccess) return e;
+    if (hipError_t e = allow_lds(patch_bwd_kv_kernel<T, D, 0>, 160 * 1024, allowed_kv); e != hipSuccess) return e;
     const dim3 grid(xcd_padded_grid(pl.q.units * pl.q.splits));
     hipLaunchKernelGGL((patch_bwd_q_kernel<T, D>), grid, dim3(kPatchThreads), pl.lds_q, s, q, k, v, rpb, scale, lse, dout, dq, ld, bound, pl.q);
     if (hipError_t e = hipGetLastError(); e != hipSuccess) return e;
-    hipLaunchKernelGGL((patch_bwd_kv_kernel<T, D>), grid, dim3(kPatchThreads), pl.lds_kv, s, q, k, v, rpb, scale, ld, bound, dout, dk, dv, partial, pl.kv);
+    if constexpr (D * sizeof(T) <= 128 && sizeof(T) == 2) {
+        if (pl.pairs) {
+            if (hipError_t e = allow_lds(patch_bwd_kv_kernel<T, D, 1>, 160 * 1024, allowed_pairs); e != hipSuccess) return e;
+            hipLaunchKernelGGL((patch_bwd_kv_kernel<T, D, 1>), dim3(xcd_padded_grid(pl.kv.units * pl.kv.splits)), dim3(kPatchThreads), pl.lds_kv, s, q, k, v, rpb, scale,
+                               ld, bound, dout, dk, dv, partial, pl.kv);
+            return hipGetLastError();
+        }
+    }
+    hipLaunchKernelGGL((patch_bwd_kv_kernel<T, D, 0>), grid, dim3(kPatchThreads), pl.lds_kv, s, q, k, v, rpb, scale, ld, bound, dout, dk, dv, partial, pl.kv);
     return hipGetLastError();
 }
 
