@@ -32,27 +32,36 @@ template <int NBLK, int GPW> struct Cfg {
     static constexpr int kLds = 2 * kImage;   // and 2 K - 1 floats of bias
 };
 
-// One query from its own window, as plain sums: lane group g keeps channels 8 g .. 8 g + 7.
+// One query from its own window, as plain sums: lane group g keeps channels 8 g .. 8 g + 7.  An lse that is finite stays.  (What is NaN stays NaN:
+// the rest of the window is left out.)
 template <typename T>
 __device__ void query_once_more(const T *q, const T *k, const T *v, const T *rpb, float scale, int i, int L, int K, int g, float (&acc)[8], float &lse) {
     const int s = win_start(i, L, K);
-    Vec32<T> qv, kv;
-    load_vec32(qv, reinterpret_cast<const char *>(q) + (size_t)i * kBytes);
+    VecN<T, 8> qv, kv, vv;   // (the four lanes of a column work on it, eight channels each)
+    load_vec32(qv, q + (size_t)i * kHeadDim + 8 * g);
     float m = -INFINITY, l = 0.f;
+    const bool keep = fabsf(lse) < INFINITY;
 #pragma unroll
     for (int d = 0; d < 8; ++d) acc[d] = 0.f;
+#pragma unroll 1
     for (int a = 0; a < K; ++a) {
-        load_vec32(kv, reinterpret_cast<const char *>(k) + (size_t)(s + a) * kBytes);
-        const float sv = __builtin_fmaf(scale * kLog2e, dot32(qv, kv), rpb ? to_f32(rpb[s + a - i + K - 1]) * kLog2e : 0.f);
+        load_vec32(kv, k + (size_t)(s + a) * kHeadDim + 8 * g);
+        load_vec32(vv, v + (size_t)(s + a) * kHeadDim + 8 * g);
+        const float sv = __builtin_fmaf(scale * kLog2e, group_sum(dot32(qv, kv)), rpb ? to_f32(rpb[s + a - i + K - 1]) * kLog2e : 0.f);
         const float mn = fmaxf(m, sv), c = __builtin_amdgcn_exp2f(m - mn), p = __builtin_amdgcn_exp2f(sv - mn);
         l = __builtin_fmaf(l, c, p);
 #pragma unroll
-        for (int d = 0; d < 8; ++d) acc[d] = __builtin_fmaf(p, to_f32(v[(size_t)(s + a) * kHeadDim + 8 * g + d]), acc[d] * c);
+        for (int d = 0; d < 8; ++d) acc[d] *= c;
+        axpy32(acc, p, vv);
         m = mn;
+        float open = keep ? 0.f : 1.f;
+#pragma unroll
+        for (int d = 0; d < 8; ++d) open = acc[d] == acc[d] ? 1.f : open;
+        if (l != l || group_sum(open) == 0.f) break;
     }
 #pragma unroll
     for (int d = 0; d < 8; ++d) acc[d] *= 1.f / l;
-    lse = (m + __builtin_amdgcn_logf(l)) * kLn2;
+    if (!keep) lse = (m + __builtin_amdgcn_logf(l)) * kLn2;
 }
 
 template <typename T, int NBLK, int GPW>
