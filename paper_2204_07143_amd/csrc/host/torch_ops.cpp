@@ -98,6 +98,26 @@ void check(int status) {
     PyGILState_Release(gil);
     throw std::move(err);
 }
+// What a backward pass reads comes from autograd: a saved-tensor hook may hand back a tensor of another form, an upstream gradient may be
+// wrapped.  The kernels read memory, so what is not dense, of the expected type and sizes and on `of`'s device is refused, with the errors of the
+// interpreted binding.
+const Tensor &readable(const Tensor &t, const Tensor &of, at::ScalarType type, at::IntArrayRef sizes) {
+    TORCH_CHECK_VALUE(plain(t) && t.device() == of.device(), "na2d takes GPU tensors only");
+    TORCH_CHECK_VALUE(t.is_contiguous(), "na2d takes contiguous tensors only");
+    TORCH_CHECK_VALUE(t.scalar_type() == type, "expected dtype ", type, ", got ", t.scalar_type());
+    TORCH_CHECK_VALUE(t.sizes() == sizes, "expected shape ", sizes, ", got ", t.sizes());
+    return t;
+}
+const Tensor &readable(const Tensor &t, const Tensor &of, at::IntArrayRef sizes) { return readable(t, of, of.scalar_type(), sizes); }
+// the upstream gradient, dense (autograd has checked its type, sizes and device against the output)
+Tensor upstream(const Tensor &grad) {
+    const Tensor g = (grad.is_neg() ? grad.resolve_neg() : grad).contiguous();
+    return readable(g, g, g.sizes());
+}
+template <typename Problem> const Problem &valid(const std::optional<Problem> &p) {
+    TORCH_CHECK_VALUE(p, "not a problem of the forward pass");
+    return *p;
+}
 struct Refused {};   // a forward call that the library refused
 void forward_check(int status) {
     if (status != NA2D_OK) throw Refused{};
@@ -132,11 +152,15 @@ struct NA2D : torch::autograd::Function<NA2D> {
     }
     static variable_list backward(AutogradContext *ctx, variable_list grads) {
         const auto saved = ctx->get_saved_variables();
-        const Tensor &q = saved[0], &k = saved[1], &v = saved[2], &lse = saved[3], &rpb = saved[4];
         const float scale = (float)ctx->saved_data["scale"].toDouble();
         const bool want = ctx->saved_data["want"].toBool();
-        const na2d_problem p = *problem_2d(q.sizes(), q.scalar_type(), ctx->saved_data["k"].toInt());
-        const Tensor dout = grads[0].contiguous();
+        const int64_t ks = ctx->saved_data["k"].toInt();
+        const Tensor dout = upstream(grads[0]);
+        const auto s = dout.sizes();
+        const na2d_problem p = valid(problem_2d(s, dout.scalar_type(), ks));
+        const Tensor &q = readable(saved[0], dout, s), &k = readable(saved[1], dout, s), &v = readable(saved[2], dout, s);
+        const Tensor &lse = readable(saved[3], dout, at::kFloat, s.slice(0, 4));
+        const Tensor &rpb = saved[4].defined() ? readable(saved[4], dout, {s[1], 2 * ks - 1, 2 * ks - 1}) : saved[4];
         Tensor dq = at::empty(q.sizes(), q.options()), dk = at::empty(q.sizes(), q.options()), dv = at::empty(q.sizes(), q.options());
         Tensor d_rpb = want ? at::empty(rpb.sizes(), rpb.options()) : Tensor();   // (rpb is of q's type)
         const size_t direct = na2d_direct_bwd_workspace_bytes(&p);   // 0: not for this problem
@@ -170,10 +194,14 @@ struct NA1D : torch::autograd::Function<NA1D> {
     }
     static variable_list backward(AutogradContext *ctx, variable_list grads) {
         const auto saved = ctx->get_saved_variables();
-        const Tensor &q = saved[0], &k = saved[1], &v = saved[2], &lse = saved[3], &rpb = saved[4];
         const bool want = ctx->saved_data["want"].toBool();
-        const na1d_problem p = *problem_1d(q.sizes(), q.scalar_type(), ctx->saved_data["k"].toInt());
-        const Tensor dout = grads[0].contiguous();
+        const int64_t ks = ctx->saved_data["k"].toInt();
+        const Tensor dout = upstream(grads[0]);
+        const auto s = dout.sizes();
+        const na1d_problem p = valid(problem_1d(s, dout.scalar_type(), ks));
+        const Tensor &q = readable(saved[0], dout, s), &k = readable(saved[1], dout, s), &v = readable(saved[2], dout, s);
+        const Tensor &lse = readable(saved[3], dout, at::kFloat, s.slice(0, 3));
+        const Tensor &rpb = saved[4].defined() ? readable(saved[4], dout, {s[1], 2 * ks - 1}) : saved[4];
         Tensor dq = at::empty(q.sizes(), q.options()), dk = at::empty(q.sizes(), q.options()), dv = at::empty(q.sizes(), q.options());
         Tensor d_rpb = want ? at::empty(rpb.sizes(), rpb.options()) : Tensor();
         const Tensor ws = workspace(na1d_fused_bwd_workspace_bytes(&p), q);
@@ -199,6 +227,7 @@ struct QKRPB : torch::autograd::Function<QKRPB> {
         Tensor logits = attention_like(q, ks);
         forward_check(na2d_qk_rpb(&p, ptr(q), ptr(k), ptr(rpb), (float)scale, ptr(logits), stream()));
         ctx->save_for_backward({q, k});
+        ctx->saved_data["shape"] = q.sizes().vec();
         ctx->saved_data["k"] = ks;
         ctx->saved_data["scale"] = scale;
         ctx->saved_data["want_q"] = q_.requires_grad();
@@ -208,11 +237,12 @@ struct QKRPB : torch::autograd::Function<QKRPB> {
     }
     static variable_list backward(AutogradContext *ctx, variable_list grads) {
         const auto saved = ctx->get_saved_variables();
-        const Tensor &q = saved[0], &k = saved[1];
         const int64_t ks = ctx->saved_data["k"].toInt();
         const float scale = (float)ctx->saved_data["scale"].toDouble();
-        const na2d_problem p = *problem_2d(q.sizes(), q.scalar_type(), ks);
-        const Tensor ds = grads[0].contiguous();
+        const Tensor ds = upstream(grads[0]);
+        const auto shape = ctx->saved_data["shape"].toIntVector();
+        const Tensor &q = readable(saved[0], ds, shape), &k = readable(saved[1], ds, shape);
+        const na2d_problem p = valid(problem_2d(shape, ds.scalar_type(), ks));
         Tensor dq, dk, d_rpb;
         if (ctx->saved_data["want_q"].toBool()) {
             dq = at::empty(q.sizes(), q.options());
@@ -245,9 +275,11 @@ struct AV : torch::autograd::Function<AV> {
     }
     static variable_list backward(AutogradContext *ctx, variable_list grads) {
         const auto saved = ctx->get_saved_variables();
-        const Tensor &attn = saved[0], &v = saved[1];
-        const na2d_problem p = *problem_2d(v.sizes(), v.scalar_type(), ctx->saved_data["k"].toInt());
-        const Tensor dout = grads[0].contiguous();
+        const int64_t ks = ctx->saved_data["k"].toInt();
+        const Tensor dout = upstream(grads[0]);
+        const auto s = dout.sizes();
+        const na2d_problem p = valid(problem_2d(s, dout.scalar_type(), ks));
+        const Tensor &attn = readable(saved[0], dout, {s[0], s[1], s[2], s[3], ks * ks}), &v = readable(saved[1], dout, s);
         Tensor dattn, dv;
         if (ctx->saved_data["want_attn"].toBool()) {
             dattn = at::empty(attn.sizes(), attn.options());
@@ -273,9 +305,10 @@ struct Softmax : torch::autograd::Function<Softmax> {
         return attn;
     }
     static variable_list backward(AutogradContext *ctx, variable_list grads) {
-        const Tensor attn = ctx->get_saved_variables()[0];
-        const na2d_problem p = *problem_2d(ctx->saved_data["like"].toIntVector(), attn.scalar_type(), ctx->saved_data["k"].toInt());
-        const Tensor dattn = grads[0].contiguous();
+        const auto saved = ctx->get_saved_variables();
+        const Tensor dattn = upstream(grads[0]);
+        const Tensor &attn = readable(saved[0], dattn, dattn.sizes());
+        const na2d_problem p = valid(problem_2d(ctx->saved_data["like"].toIntVector(), dattn.scalar_type(), ctx->saved_data["k"].toInt()));
         Tensor ds = at::empty(attn.sizes(), attn.options());
         check(na2d_softmax_bwd(&p, ptr(attn), ptr(dattn), ptr(ds), stream()));
         return {ds, Tensor(), Tensor()};

@@ -89,3 +89,21 @@ def test_what_is_not_plain_goes_to_the_interpreted_functions():
     with fw.dual_level():
         with pytest.raises(RuntimeError):   # no forward-mode rule
             F.na2d(fw.make_dual(q.detach(), torch.ones_like(q)), k, v, b, kernel_size=5)
+
+
+HOOKS = {"strides": lambda t: t.transpose(-1, -2).contiguous().transpose(-1, -2), "type": lambda t: t.to(torch.bfloat16), "sizes": lambda t: t[..., :-1].contiguous(),
+         "expanded": lambda t: t[:1, :1].expand(t.shape), "host": lambda t: t.cpu()}
+
+
+@pytest.mark.parametrize("name", list(OPS))
+@pytest.mark.parametrize("form", list(HOOKS))
+def test_saved_tensors_of_another_form_are_refused(name, form):
+    """A saved-tensor hook may unpack what the kernels cannot read as it lies in memory: an error, as from the interpreted functions."""
+    native, interpreted = OPS[name]
+    (q, k, v, b), dout = inputs(name, torch.float16)
+    for op in (lambda: interpreted(q, k, v, b, 5, None), lambda: native(q, k, v, b, kernel_size=5)):
+        with torch.autograd.graph.saved_tensors_hooks(lambda t: t, HOOKS[form]):
+            out = op()
+        with pytest.raises(ValueError):
+            torch.autograd.grad(out, (q, k, v, b), dout)
+    torch.autograd.grad(native(q, k, v, b, kernel_size=5), (q, k, v, b), dout)   # and nothing is left behind
