@@ -12,7 +12,7 @@
 // Part 2 keeps 4 x 4 key patches and streams queries, upstream gradients, lse and delta: dv_j = sum_i P dout_i,
 // dk_j = scale sum_i dS q_i, and the bias gradient: every dS is added to its cell of a table in LDS, as an integer (additions of
 // integers commute: the result is bitwise reproducible).  Their scale follows a bound of the |dS|
-// that the workgroup meets in a plane (part 1 leaves one per query patch); see BiasSums.
+// that the workgroup meets in a plane (part 1 leaves one per query patch, which its queries that are not finite have no part in); see BiasSums.
 //
 // A masked product is 0 * x: where x is not finite it would spoil positions whose window does not hold it, so results that are not
 // finite are computed once more from their own window only.
@@ -57,10 +57,12 @@ __device__ __forceinline__ uint32_t wave_max(uint32_t x) {
     }
     return x;
 }
-// |dS| = P |dP - delta| is at most this, given the largest P |dP| and P of the window; as bits (NaN above all others, where delta is not finite)
+// |dS| = P |dP - delta| is at most this, given the largest P |dP| and P of the window; as bits (finite where delta is, infinity or NaN elsewhere)
 __device__ __forceinline__ uint32_t ds_bound(float most_pdp, float most_p, float delta) {
-    return __float_as_uint(fabsf(__builtin_fmaf(most_p, fabsf(delta), most_pdp)));
+    const float most = fabsf(__builtin_fmaf(most_p, fabsf(delta), most_pdp));
+    return __float_as_uint(fabsf(delta) < INFINITY ? fminf(most, 3.4028234e38f) : most);
 }
+constexpr uint32_t kNotFinite = 0x7f800000u, kMark = 0x80000000u;
 // Weight and upstream product of one (query, key) pair, from memory.
 template <typename T, int D> struct PlanePtrs {
     const T *q, *k, *v, *dout, *rpb;   // of the plane; the head's bias table or null
@@ -198,8 +200,8 @@ __device__ __forceinline__ int own_lane_index() {
 }
 
 // ---- part 1 ------------------------------------------------------------------------------------------------------------
-// ld: kQueryWords of every query, for part 2; bound: per query patch what no |dS| exceeds (bits of a float; null
-// where no bias gradient is wanted).
+// ld: kQueryWords of every query, for part 2; bound: per query patch what no |dS| of the queries with a finite delta exceeds (bits of
+// a float), and kMark where some delta is not finite; null where no bias gradient is wanted.
 template <typename T, int D>
 __global__ __launch_bounds__(kPatchThreads, (kPatchOcc<T, D>)) void patch_bwd_q_kernel(
     const T *__restrict__ q, const T *__restrict__ k, const T *__restrict__ v, const T *__restrict__ rpb, float scale,
@@ -363,7 +365,7 @@ __global__ __launch_bounds__(kPatchThreads, (kPatchOcc<T, D>)) void patch_bwd_q_
 #pragma unroll
         for (int i = 0; i < Op::NA; ++i) sa.acc[i] -= delta * sp.acc[i];
         const float odd = __builtin_fmaf(delta, 0.f, sa.not_finite());   // NaN where something is not finite
-        uint32_t bits = ds_bound(most * inv, most_p * inv, delta);
+        uint32_t bits = ds_bound(most * inv, most_p * inv, delta), mark = 0;   // (where delta is not finite: once more, below)
         if (q_ok) {
             sa.store(reinterpret_cast<char *>(dq) + plane_off, (unsigned)(qlin * POSB), gr, scale * inv);
             if (gr == 0) store_query<T>(ld + plane * plane_px * kQueryWords<T>, (unsigned)qlin, base, delta, inv);
@@ -385,11 +387,12 @@ __global__ __launch_bounds__(kPatchThreads, (kPatchOcc<T, D>)) void patch_bwd_q_
                 const float b2 = lane_value(base, c);
                 const float dl = query_once_more<T, D>(m, gc, scale, cy, cx, b2, dq + plane * plane_px * D, own, own_inv);
                 if (lane == 0) store_query<T>(ld + plane * plane_px * kQueryWords<T>, (unsigned)(cy * W + cx), b2, dl, own_inv);
-                bits = bits > own ? bits : own;
+                if (own >= kNotFinite) mark = kMark;
+                else bits = bits > own ? bits : own;
             }
         }
         if (bound != nullptr) {
-            bits = wave_max(bits);
+            bits = wave_max(bits) | mark;
             if (lane == 0) bound[(plane * ((H + 3) >> 2) + (sy0 >> 2)) * ((W + 3) >> 2) + (px0 >> 2)] = bits;
         }
     }
@@ -527,8 +530,8 @@ __global__ __launch_bounds__(kPatchThreads, (kPatchOcc<T, D>)) void patch_bwd_kv
             uint32_t most = 0, odd = 0;
             for (int i = own_lane(); i < nbound; i += kWave) {
                 const uint32_t bits = bound[(plane * ph + by0 + i / bw) * pw + bx0 + i % bw];
-                if (bits >= 0x7f800000u) odd = 1;
-                else most = most > bits ? most : bits;
+                odd |= bits & kMark;
+                most = most > (bits & ~kMark) ? most : bits & ~kMark;
             }
             most = wave_max(most);
             poisoned = __ballot(odd != 0) != 0;

@@ -101,6 +101,31 @@ def test_values_that_are_not_finite_reach_their_windows_only(dtype, where):
         assert (g[f] - o[f]).abs().max() <= tol * max(1.0, float(o[f].float().abs().max())), n
 
 
+@pytest.mark.parametrize("B,H,W,D,k,dtype", [(1, 3, 3, 64, 3, "f16"), (2, 3, 4, 64, 3, "bf16"), (1, 4, 4, 16, 3, "f32"), (1, 3, 3, 16, 3, "f32"), (3, 21, 18, 16, 11, "f16"),
+                                             (2, 14, 30, 32, 13, "bf16"), (4, 13, 22, 16, 9, "f32"), (1, 30, 22, 32, 15, "f16")])
+def test_bias_gradient_beside_a_query_that_is_not_finite(oracle, B, H, W, D, k, dtype):
+    """The cells that the query's dS reach are NaN; in the others the rest of its patch counts as ever, also where that patch holds the
+    largest dS of all (or is the only one)."""
+    p = synth.Problem(B, 2, H, W, D, k, dtype)
+    host = synth.make_inputs(p, seed=H + D, rpb_std=0.3)
+    y, x = 1, 1
+    host["dout"][..., :4, :4, :] *= 1024   # (the corner's patch: its queries reach different cells)
+    st = Stages(p, host)
+    st.forward_fused()
+    h = {n: t.astype(np.float64) for n, t in host.items()}
+    h["dout"] = st.dout.double().cpu().numpy()
+    h["dout"][-1, 1, y, x] = 0   # (its dS are 0 then)
+    st.dout[-1, 1, y, x, 5] = float("nan")
+    got = direct(st)[3].double().cpu().numpy()
+    want = oracle.bwd(h["q"], h["k"], h["v"], h["rpb"], st.scale, h["dout"], k)[3]
+    first = lambda i, n: min(max(i - k // 2, 0), n - k) - i + k - 1
+    reached = np.zeros(want.shape, dtype=bool)
+    reached[1, first(y, H):first(y, H) + k, first(x, W):first(x, W) + k] = True
+    assert np.array_equal(np.isnan(got), reached) and not reached.all()
+    for head in range(2):
+        assert np.abs((got - want)[head][~reached[head]]).max() <= 1e-4 * np.abs(want[head][~reached[head]]).max()
+
+
 def test_refused_problems_and_arguments():
     f16, f32 = torch.float16, torch.float32
     size = lambda *a: na.na2d_direct_bwd_workspace_bytes(na.problem(*a))
