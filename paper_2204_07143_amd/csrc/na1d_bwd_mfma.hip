@@ -350,6 +350,8 @@ __global__ __launch_bounds__(kThreads, (NBLK > 3 ? 3 : 4)) void bwd1d_kv_mfma_ke
             weighted_sum<T, NBLK>(vector_addr(img + image, pos, j, g), wp, av);
             weighted_sum<T, NBLK>(vector_addr(img, pos, j, g), ws, ak);
         }
+        settle_products<2>(ak);
+        settle_products<2>(av);
         if (n + 1 < kGroups) load(n + 1);
         const float back_v = __builtin_ldexpf(1.f, (int)-kShift<T>), back_k = scale * __builtin_ldexpf(1.f, -e - (int)kShift<T>);
         float xk[8], xv[8], odd = 0.f;

@@ -46,6 +46,17 @@ template <> __device__ __forceinline__ f32x4 mfma_16x16x16<bf16_t>(uint32_t a0, 
     return __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(__builtin_bit_cast(i16x4_t, a), __builtin_bit_cast(i16x4_t, b), c, 0, 0, 0);
 }
 
+// The wait between matrix products and the first use of their sums, for sums that leave a loop or a branch.  The hardware does not wait by itself (8
+// instructions after a 16-bit product, 10 after an fp32 one); the compiler does it, but where branches lie between it has counted one too many
+// (the 1D key side in bf16: 7 instructions on the way out of the loop over blocks).
+template <int N> __device__ __forceinline__ void settle_products(f32x4 (&x)[N]) {
+    static_assert(N == 1 || N == 2 || N == 4 || N == 8, "accumulators");
+    if constexpr (N == 1) asm volatile("s_nop 9" : "+v"(x[0]));
+    if constexpr (N == 2) asm volatile("s_nop 9" : "+v"(x[0]), "+v"(x[1]));
+    if constexpr (N >= 4) asm volatile("s_nop 9" : "+v"(x[0]), "+v"(x[1]), "+v"(x[2]), "+v"(x[3]));
+    if constexpr (N == 8) asm volatile("s_nop 9" : "+v"(x[4]), "+v"(x[5]), "+v"(x[6]), "+v"(x[7]));
+}
+
 // The fused kernels keep the bias B(i, j) of a (query, position) pair as fp16, two per register, beside the
 // -inf that masks positions outside the window, and add it unscaled to the fp32 logit.  An fp16 table entry is
 // kept bit for bit.  A bf16 entry (8 significant bits) converts exactly while it lies inside fp16's range:

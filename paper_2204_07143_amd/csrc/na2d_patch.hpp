@@ -149,6 +149,7 @@ template <typename T, int D> struct PosSum {
         }
     }
     __device__ __forceinline__ void take(PosSum &part) {   // adds another's sums and clears them
+        part.settle();
 #pragma unroll
         for (int i = 0; i < Op::NA; ++i) {
             acc[i] += part.acc[i];
@@ -166,6 +167,17 @@ template <typename T, int D> struct PosSum {
             add(o1, w1);
         }
     }
+    // one block behind add2()'s: the full depth again, zeros in its other half (16 bit: accumulators meet one instruction only, see the 1D
+    // kernels' weighted_sum)
+    __device__ __forceinline__ void add_last(const Op &o, const Weights4<T> &w) {
+        if constexpr (sizeof(T) == 2) {
+#pragma unroll
+            for (int i = 0; i < Op::NA; ++i) acc[i] = mfma_16x16x32<T>(u32x4{o.c[i].x, o.c[i].y, 0u, 0u}, u32x4{w.p0, w.p1, 0u, 0u}, acc[i]);
+        } else {
+            add(o, w);
+        }
+    }
+    __device__ __forceinline__ void settle() { settle_products<Op::NA>(acc); }
     // NaN if any sum of the lane is not finite, 0 otherwise
     __device__ __forceinline__ float not_finite() const {
         float c = 0.f;

@@ -287,8 +287,8 @@ __global__ __launch_bounds__(kPatchThreads, (kPatchOcc<T, D>)) void patch_bwd_q_
                 va[i].load_lds(va0 + i * 4 * POSB);
 #pragma unroll
                 for (int r = 0; r < 4; ++r) bias[i][r] = *lds_ptr<float>(b0 + i * 16 + r * 4);
-                // columns outside the window: weight 0 (decided here: where a branch came
-                // between a product and the first use of its result, the compiler left out the wait that the use needs)
+                // columns outside the window: weight 0 (decided here: no branch may come between a product and the first use of its
+                // result, see settle_products)
                 if (4 * (bx + i) < clear_lo || 4 * (bx + i) + 4 > K) {
 #pragma unroll
                     for (int r = 0; r < 4; ++r) bias[i][r] = (unsigned)(4 * (bx + i) + r - wx) < (unsigned)K ? bias[i][r] : -INFINITY;
@@ -321,8 +321,13 @@ __global__ __launch_bounds__(kPatchThreads, (kPatchOcc<T, D>)) void patch_bwd_q_
                 ta.add2(kt[0], wa[0], kt[1], wa[1]);
                 tp.add2(kt[0], wp[0], kt[1], wp[1]);
             } else {
-                ta.add(kt[0], wa[0]);
-                tp.add(kt[0], wp[0]);
+                if constexpr (kAtOnceQ<T, D> == 2) {
+                    ta.add_last(kt[0], wa[0]);
+                    tp.add_last(kt[0], wp[0]);
+                } else {
+                    ta.add(kt[0], wa[0]);
+                    tp.add(kt[0], wp[0]);
+                }
             }
         };
         for (int s = 0; s < nsteps; ++s) {
@@ -353,6 +358,10 @@ __global__ __launch_bounds__(kPatchThreads, (kPatchOcc<T, D>)) void patch_bwd_q_
             }
         }
         if (!active) continue;
+        if constexpr (sizeof(T) == 2) {
+            sa.settle();
+            sp.settle();
+        }
         delta += __shfl_xor(delta, 16);
         delta += __shfl_xor(delta, 32);
         float inv = 1.f;
@@ -625,11 +634,13 @@ __global__ __launch_bounds__(kPatchThreads, (kPatchOcc<T, D>)) void patch_bwd_kv
             for (int i = 0; i < N; ++i) t[i].load_lds(dt0 + i * 4 * POSB);
             auto &tk = sizeof(T) == 4 ? row_k : sk, &tv = sizeof(T) == 4 ? row_v : sv;
             if constexpr (N == 2) tv.add2(t[0], wp[0], t[1], wp[1]);
+            else if constexpr (kAtOnceKv<T, D> == 2) tv.add_last(t[0], wp[0]);
             else tv.add(t[0], wp[0]);
             if constexpr (kTight) __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
             for (int i = 0; i < N; ++i) t[i].load_lds(qt0 + i * 4 * POSB);
             if constexpr (N == 2) tk.add2(t[0], ws[0], t[1], ws[1]);
+            else if constexpr (kAtOnceKv<T, D> == 2) tk.add_last(t[0], ws[0]);
             else tk.add(t[0], ws[0]);
         };
         for (int s = 0; s < nsteps; ++s) {
@@ -662,6 +673,10 @@ __global__ __launch_bounds__(kPatchThreads, (kPatchOcc<T, D>)) void patch_bwd_kv
                 workgroup_sync();   // nobody still reads the rows
                 issue(last ? b + 1 : b, last ? 0 : s + 1, 0);
             }
+        }
+        if constexpr (sizeof(T) == 2) {
+            sk.settle();
+            sv.settle();
         }
         if (g.with_dbias) {
             workgroup_sync();   // every wave has added its part; nobody adds more before the next step's barrier

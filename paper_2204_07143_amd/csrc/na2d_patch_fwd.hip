@@ -220,9 +220,11 @@ __global__ __launch_bounds__(kPatchThreads, (kFwdOcc<T, D>)) void patch_fwd_kern
             }
             auto &to = sizeof(T) == 4 ? row : acc;
             if constexpr (N == 2) to.add2(vt[0], hi[0], vt[1], hi[1]);
+            else if constexpr (kAtOnce == 2) to.add_last(vt[0], hi[0]);
             else to.add(vt[0], hi[0]);
             if constexpr (sizeof(T) == 2) {
                 if constexpr (N == 2) to.add2(vt[0], lo[0], vt[1], lo[1]);
+                else if constexpr (kAtOnce == 2) to.add_last(vt[0], lo[0]);
                 else to.add(vt[0], lo[0]);
             }
         };
@@ -250,6 +252,7 @@ __global__ __launch_bounds__(kPatchThreads, (kFwdOcc<T, D>)) void patch_fwd_kern
                 issue(last ? b + 1 : b, last ? 0 : s + 1, 0);
             }
         }
+        if constexpr (sizeof(T) == 2) acc.settle();
         l += __shfl_xor(l, 16);
         l += __shfl_xor(l, 32);
         if (lgs > 0) {
