@@ -55,9 +55,9 @@ template <typename T, int D> __device__ __forceinline__ void settle(ChanVec<T, D
 #pragma unroll
     for (int i = 0; i < ChanVec<T, D>::N; ++i) asm volatile("" : "+v"(v.c[i]));
 }
-// rows: the block's positions (a), columns: the patch's (b)
-template <typename T, int D> __device__ __forceinline__ f32x4 chan_dot(const ChanVec<T, D> &a, const ChanVec<T, D> &b) {
-    f32x4 acc{0.f, 0.f, 0.f, 0.f};
+// rows: the block's positions (a), columns: the patch's (b); from: what the products are added to
+template <typename T, int D> __device__ __forceinline__ f32x4 chan_dot(const ChanVec<T, D> &a, const ChanVec<T, D> &b, f32x4 from = f32x4{0.f, 0.f, 0.f, 0.f}) {
+    f32x4 acc = from;
     if constexpr (ChanVec<T, D>::HALF) {
         acc = mfma_16x16x16<T>(a.c[0].x, a.c[0].y, b.c[0].x, b.c[0].y, acc);
     } else if constexpr (sizeof(T) == 4) {

@@ -8,7 +8,9 @@
 // Part 1 keeps 4 x 4 query patches and streams keys and values once: delta and
 //   dq_i = scale sum_j dS k_j = scale (sum_j P dP k_j - delta_i sum_j P k_j)
 // so that delta need not be known before the sums (a second sweep would evaluate both products again).  In 16 bit P dP and P are
-// rounded to the storage type, as the stored dp and the stored weights of the unfused steps are.
+// rounded to the storage type, as the stored dp and the stored weights of the unfused steps are.  Where the dP of a window have much in
+// common (values with an offset per channel, as a projection with a bias leaves them) the two sums would be large and nearly equal: dP and delta
+// count from near_mean() of the query, which costs one product per patch and plane.
 // Part 2 keeps 4 x 4 key patches and streams queries, upstream gradients, lse and delta: dv_j = sum_i P dout_i,
 // dk_j = scale sum_i dS q_i, and the bias gradient: every dS is added to its cell of a table in LDS, as an integer (additions of
 // integers commute: the result is bitwise reproducible).  Their scale follows a bound of the |dS|
@@ -192,6 +194,22 @@ template <typename T> __device__ __forceinline__ void store_query(float *ld, uns
     else *reinterpret_cast<f32x2 *>(ld + 2 * n) = f32x2{base, delta};
 }
 
+// What a query's dP are counted from, given its products with the values at the patch's 16 positions (in the layout of a block's products): their
+// mean where it is larger than their spread, 0 otherwise (the mean of a few numbers around 0 would only add to the rounding).
+// 2-norm error of dq against 64 bits at 8 x 2 x 40 x 40 queries, k = 13, values of unit variance and offsets per channel of variance 100, without / with
+// it (the unfused steps): bf16 2.4e-2 / 2.6e-3 (1.7e-2), fp16 2.7e-3 / 3.2e-4 (1.9e-3), fp32 3.0e-6 / 8.6e-7 (1.6e-6); without offsets the same
+// bits but for a few queries.  The pass takes 1 % longer (64 x 2 x 56 x 56, fp16, k = 13 277 / 280 us, fp32, k = 7 535 / 541; 64 channels 159 / 161).
+__device__ __forceinline__ float near_mean(const f32x4 &near) {
+    float sum = (near[0] + near[1]) + (near[2] + near[3]);
+    float squares = __builtin_fmaf(near[0], near[0], near[1] * near[1]) + __builtin_fmaf(near[2], near[2], near[3] * near[3]);
+    sum += __shfl_xor(sum, 16);
+    squares += __shfl_xor(squares, 16);
+    sum += __shfl_xor(sum, 32);
+    squares += __shfl_xor(squares, 32);
+    const float mean = sum * (1.f / 16.f);
+    return mean * mean > squares * (1.f / 32.f) ? mean : 0.f;   // (what is not finite: 0)
+}
+
 // the lane's index, worked out anew
 __device__ __forceinline__ int own_lane_index() {
     int zero = 0;
@@ -261,8 +279,13 @@ __global__ __launch_bounds__(kPatchThreads, (kPatchOcc<T, D>)) void patch_bwd_q_
         dO.load(reinterpret_cast<const char *>(dout) + plane_off + (unsigned)(qlin * POSB + gr * CV::kLaneBytes));
         float base = (lse + plane * plane_px)[(unsigned)qlin] * kLog2e;
         if constexpr (kNormalised<T>) base = fabsf(base) < 32.f ? 0.f : __builtin_rintf(base);
+        CV vo;
+        vo.load(reinterpret_cast<const char *>(v) + plane_off + (unsigned)(qlin * POSB + gr * CV::kLaneBytes));
         settle(qo);
         settle(dO);
+        settle(vo);
+        const float from = near_mean(chan_dot<T, D>(vo, dO));
+        const f32x4 less = sizeof(T) == 2 ? f32x4{-from, -from, -from, -from} : f32x4{0.f, 0.f, 0.f, 0.f};   // (fp32: subtracted below, for the registers)
         // sum of P dP k and of P k.  fp32: of a row of blocks at a time, then of the rows (one chain of K * K additions is off by twice as much)
         PosSum<T, D> sa, sp, row_a, row_p;
         sa.clear();
@@ -297,7 +320,7 @@ __global__ __launch_bounds__(kPatchThreads, (kPatchOcc<T, D>)) void patch_bwd_q_
 #pragma unroll
             for (int i = 0; i < N; ++i) {
                 sv[i] = chan_dot<T, D>(ka[i], qo);
-                dp[i] = chan_dot<T, D>(va[i], dO);
+                dp[i] = chan_dot<T, D>(va[i], dO, less);
             }
 #pragma unroll
             for (int i = 0; i < N; ++i) {
@@ -307,7 +330,7 @@ __global__ __launch_bounds__(kPatchThreads, (kPatchOcc<T, D>)) void patch_bwd_q_
                 for (int r = 0; r < 4; ++r) p[r] = exponential<T>(sv[i][r], scale2, scale2_low, bias[i][r], base);
 #pragma unroll
                 for (int r = 0; r < 4; ++r) {
-                    w[r] = p[r] * dp[i][r];
+                    w[r] = p[r] * (sizeof(T) == 4 ? dp[i][r] - from : dp[i][r]);
                     delta += w[r];
                     if constexpr (kNormalised<T>) z += p[r];
                     most = fmaxf(most, fabsf(w[r]));
@@ -377,7 +400,7 @@ __global__ __launch_bounds__(kPatchThreads, (kPatchOcc<T, D>)) void patch_bwd_q_
         uint32_t bits = ds_bound(most * inv, most_p * inv, delta), mark = 0;   // (where delta is not finite: once more, below)
         if (q_ok) {
             sa.store(reinterpret_cast<char *>(dq) + plane_off, (unsigned)(qlin * POSB), gr, scale * inv);
-            if (gr == 0) store_query<T>(ld + plane * plane_px * kQueryWords<T>, (unsigned)qlin, base, delta, inv);
+            if (gr == 0) store_query<T>(ld + plane * plane_px * kQueryWords<T>, (unsigned)qlin, base, delta + from, inv);
         }
         unsigned long long again = __ballot(odd != odd);
         if (again) {

@@ -83,6 +83,23 @@ def test_direct_backward_with_large_logits(oracle):
     check(oracle, synth.Problem(64, 2, 12, 19, 32, 11, "f32"), seed=6, scale=6.0, f32_factor=10.0)
 
 
+@pytest.mark.parametrize("dtype", ["f32", "f16", "bf16"])
+@pytest.mark.parametrize("B,heads,H,W,D,k", [(72, 1, 21, 22, 32, 13), (16, 2, 17, 23, 16, 11), (6, 2, 45, 38, 32, 21)])
+def test_values_with_an_offset_per_channel(oracle, dtype, B, heads, H, W, D, k):
+    """dP of a window then have a large common part, which must not be left to cancel between two rounded sums."""
+    p = synth.Problem(B, heads, H, W, D, k, dtype)
+    host = synth.make_inputs(p, seed=k)
+    host["v"] = synth.round_to(host["v"] + 10 * np.random.default_rng(k).standard_normal(D).astype(np.float32), dtype)
+    st = Stages(p, host)
+    st.forward_fused()
+    got = direct(st)
+    want = oracle.bwd(*(host[n].astype(np.float64) for n in ("q", "k", "v", "rpb")), st.scale, host["dout"].astype(np.float64), k)
+    for n, g, o in zip(("dq", "dk", "dv"), got, want):
+        # 16 bit: P (dP - reference), P and the result rounded, each by half a unit of the last place at most.  fp32: dP is some 10 times as large as
+        # dP - delta and its sum is rounded a few times
+        assert np.linalg.norm(g.double().cpu().numpy() - o) <= {"f32": 1.2e-6, "f16": 2.0 ** -11, "bf16": 2.0 ** -8}[dtype] * np.linalg.norm(o), n
+
+
 @pytest.mark.parametrize("dtype,where", [("f32", "dout"), ("f32", "k"), ("bf16", "v"), ("bf16", "q"), ("f16", "dout")])
 def test_values_that_are_not_finite_reach_their_windows_only(dtype, where):
     """A value that is not finite: the gradients that are not finite are those of the unfused steps, which add up each window by itself."""
