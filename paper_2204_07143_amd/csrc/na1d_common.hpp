@@ -16,6 +16,9 @@ __device__ __forceinline__ long long to_fixed42(float x) {
     return (long long)(((unsigned long long)(uint32_t)(int)fl << 32) | (uint32_t)((y - fl) * 4294967296.f));
 }
 
+// Where a running maximum starts: not -inf, whose difference to a first logit of -inf (a masked bias cell) would be NaN
+constexpr float kLowest = -3.402823466e38f;
+
 // ---- matrix-core kernels (16 bit) ------------------------------------------------------------
 constexpr int kGroup = 16, kBytes = 64;   // positions of a group, bytes of a head vector
 constexpr float kLog2e = 1.4426950408889634f, kLn2 = 0.6931471805599453f;

@@ -39,7 +39,7 @@ __device__ void query_once_more(const T *q, const T *k, const T *v, const T *rpb
     const int s = win_start(i, L, K);
     VecN<T, 8> qv, kv, vv;   // (the four lanes of a column work on it, eight channels each)
     load_vec32(qv, q + (size_t)i * kHeadDim + 8 * g);
-    float m = -INFINITY, l = 0.f;
+    float m = kLowest, l = 0.f;
     const bool keep = fabsf(lse) < INFINITY;
 #pragma unroll
     for (int d = 0; d < 8; ++d) acc[d] = 0.f;
@@ -59,6 +59,7 @@ __device__ void query_once_more(const T *q, const T *k, const T *v, const T *rpb
         for (int d = 0; d < 8; ++d) open = acc[d] == acc[d] ? 1.f : open;
         if (l != l || group_sum(open) == 0.f) break;
     }
+    if (l == 0.f) l = NAN;   // every logit -inf
 #pragma unroll
     for (int d = 0; d < 8; ++d) acc[d] *= 1.f / l;
     if (!keep) lse = (m + __builtin_amdgcn_logf(l)) * kLn2;

@@ -335,13 +335,13 @@ __global__ __launch_bounds__(TQ) void fused1d_kernel(const T *__restrict__ q, co
         const float *bb = bias + (s - i + K - 1);
         const float scale2 = scale * kLog2e;
         // online softmax in the exp2 domain: running maximum m, running sum l, running weighted sum acc
-        float m = -INFINITY, l = 0.f;
+        float m = kLowest, l = 0.f;
         for (int a = 0; a < K; ++a) {
             Vec32<T> kv, vv;
             load_vec32(kv, khalo + off + a * STRIDE);
             const float sv = __builtin_fmaf(scale2, dot32(qv, kv), bb[a]);
             const float mn = fmaxf(m, sv);
-            const float c = __builtin_amdgcn_exp2f(m - mn);   // 0 on the first slot (m = -inf)
+            const float c = __builtin_amdgcn_exp2f(m - mn);   // 0 on the first slot
             const float pw = __builtin_amdgcn_exp2f(sv - mn);
             l = __builtin_fmaf(l, c, pw);
 #pragma unroll

@@ -109,3 +109,23 @@ def test_forward_not_finite_stays_in_its_windows(dtype, what):
     assert not np.isfinite(want).all() and np.array_equal(np.isfinite(got), np.isfinite(want))
     zero = lambda x: np.where(np.isfinite(want), x, 0.0)
     assert_close("out", zero(got), zero(want), dtype)
+
+
+@pytest.mark.parametrize("dtype", ["f32", "f16", "bf16"])
+def test_forward_with_masked_bias_cells(dtype):
+    """Windows whose first keys are masked by a bias of -inf, alone and next to values that are not finite just outside of them."""
+    k, L = 7, 200
+
+    def edit(host):
+        host["rpb"][:, : k // 2 + 2] = -np.inf   # (the first keys, and at the right end those that come first there)
+        host["v"][0, 0, 60, 3] = np.nan
+        host["k"][0, 1, 100, 5] = np.inf
+
+    with np.errstate(all="ignore"):
+        out, lse, (want, want_lse) = forward(synth.Problem1D(1, 2, L, 32, k, dtype), seed=9, edit=edit)
+    got, finite = to_np(out), np.isfinite(want)
+    assert not finite.all() and finite.mean() > 0.9 and np.array_equal(np.isfinite(got), finite)
+    assert_close("out", np.where(finite, got, 0.0), np.where(finite, want, 0.0), dtype)
+    finite = np.isfinite(want_lse)
+    assert np.array_equal(np.isfinite(to_np(lse)), finite)
+    assert_close("lse", np.where(finite, to_np(lse), 0.0), np.where(finite, want_lse, 0.0), "f32")
