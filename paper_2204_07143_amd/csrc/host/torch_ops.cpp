@@ -9,7 +9,6 @@
 #include <Python.h>
 
 #include <ATen/ATen.h>
-#include <ATen/FuncTorchTLS.h>
 #include <ATen/hip/impl/HIPStreamMasqueradingAsCUDA.h>
 #include <c10/core/impl/LocalDispatchKeySet.h>
 #include <torch/csrc/Exceptions.h>
@@ -41,8 +40,8 @@ bool plain_context() {
     static const c10::DispatchKeySet modes{c10::DispatchKey::Python, c10::DispatchKey::PythonTLSSnapshot, c10::DispatchKey::PythonDispatcher,
                                            c10::DispatchKey::FuncTorchDynamicLayerFrontMode, c10::DispatchKey::FuncTorchDynamicLayerBackMode,
                                            c10::DispatchKey::Functionalize, c10::DispatchKey::Tracer, c10::DispatchKey::PreDispatch};
-    return !c10::impl::tls_local_dispatch_key_set().included_.has_any(modes) && !at::functorch::functorchTLSAccessor() &&
-           !torch::jit::tracer::isTracing() && !torch::autograd::ForwardADLevel::try_get_by_idx(0);
+    // (a functorch transform shows in the modes; its thread-local state outlives it)
+    return !c10::impl::tls_local_dispatch_key_set().included_.has_any(modes) && !torch::jit::tracer::isTracing() && !torch::autograd::ForwardADLevel::try_get_by_idx(0);
 }
 
 std::optional<int> dtype_code(at::ScalarType t) {

@@ -107,3 +107,19 @@ def test_saved_tensors_of_another_form_are_refused(name, form):
         with pytest.raises(ValueError):
             torch.autograd.grad(out, (q, k, v, b), dout)
     torch.autograd.grad(native(q, k, v, b, kernel_size=5), (q, k, v, b), dout)   # and nothing is left behind
+
+
+def test_a_transform_does_not_outlive_itself():
+    """After a functorch transform of anything on this thread the native operators serve it again; inside of one they do not."""
+    (q, k, v, b), _ = inputs("na2d", torch.float16)
+    native = type(F.na2d(q, k, v, b, kernel_size=5).grad_fn)
+    assert native.__name__ != type(F._NA2D.apply(q, k, v, b, 5, 0.2).grad_fn).__name__
+    torch.func.vmap(torch.sin)(torch.ones(2))
+    torch.func.grad(lambda x: torch.sin(x).sum())(torch.ones(2))
+    assert type(F.na2d(q, k, v, b, kernel_size=5).grad_fn) is native
+
+    def body(x):
+        with pytest.raises(RuntimeError):   # (Python's autograd functions need rules of their own there)
+            F.na2d(q, k, v, b, kernel_size=5)
+        return x
+    torch.func.vmap(body)(torch.ones(2))
