@@ -2,16 +2,18 @@
 // (na2d.h, na1d.h) without the interpreter in between.  Every gradient comes from the library's kernels, as there.
 //
 // Each function of the module returns the operator's output, or None where something is not as the plain case has it (a tensor that is
-// not dense on one GPU, shapes or types that do not fit, a functorch transform, forward-mode differentiation, tracing, a dispatch mode, a
-// call that the library refuses): the caller then takes the interpreted functions, which serve those or raise.  A pass of a small operator
+// not dense on one GPU or a subclass, shapes or types that do not fit, a functorch transform, forward-mode differentiation, tracing, a dispatch or
+// torch-function mode, a call that the library refuses): the caller then takes the interpreted functions, which serve those or raise.  A pass of a small operator
 // is bound by this path, not by its kernels (us a pass of 1 x 8 x 14 x 14 fp16, k = 7, inference, and of 5 x 3 x 61 x 45 bf16, k = 5, without a
 // bias, forward and backward; through ctypes and Python's autograd functions / here: 20 / 6.4, 159 / 71; of the latter 34 are what a pass of any operator takes in autograd).
 #include <Python.h>
 
 #include <ATen/ATen.h>
+#include <ATen/PythonTorchFunctionTLS.h>
 #include <ATen/hip/impl/HIPStreamMasqueradingAsCUDA.h>
 #include <c10/core/impl/LocalDispatchKeySet.h>
 #include <torch/csrc/Exceptions.h>
+#include <torch/csrc/PyInterpreter.h>
 #include <torch/csrc/autograd/custom_function.h>
 #include <torch/csrc/autograd/forward_grad.h>
 #include <torch/csrc/autograd/python_variable.h>
@@ -41,7 +43,8 @@ bool plain_context() {
                                            c10::DispatchKey::FuncTorchDynamicLayerFrontMode, c10::DispatchKey::FuncTorchDynamicLayerBackMode,
                                            c10::DispatchKey::Functionalize, c10::DispatchKey::Tracer, c10::DispatchKey::PreDispatch};
     // (a functorch transform shows in the modes; its thread-local state outlives it)
-    return !c10::impl::tls_local_dispatch_key_set().included_.has_any(modes) && !torch::jit::tracer::isTracing() && !torch::autograd::ForwardADLevel::try_get_by_idx(0);
+    return !c10::impl::tls_local_dispatch_key_set().included_.has_any(modes) && !torch::jit::tracer::isTracing() &&
+           !torch::autograd::ForwardADLevel::try_get_by_idx(0);
 }
 
 std::optional<int> dtype_code(at::ScalarType t) {
@@ -321,11 +324,29 @@ struct NoGil {
     ~NoGil() { PyEval_RestoreThread(state); }
 };
 
-// args[i] as a tensor; undefined for None where that is allowed.  false: it is neither.
+// args[i] as a tensor (or a parameter; a subclass may have a __torch_function__ to be asked); undefined for None where that is allowed.
+// false: it is neither.
 bool tensor_arg(PyObject *o, Tensor &t, bool optional = false) {
     if (optional && o == Py_None) return true;
-    if (!THPVariable_Check(o)) return false;
+    if (!THPVariable_CheckExact(o)) return false;
     t = THPVariable_Unpack(o);
+    return true;
+}
+// No torch-function mode is to be asked.  (The mode of torch.set_default_device, on for as long as a program likes, only looks at calls that
+// create tensors without naming a device.)
+bool plain_modes() {
+    if (!at::impl::torch_function_mode_enabled()) return true;
+    static PyObject *default_device = nullptr;   // (under the interpreter lock)
+    if (!default_device) {
+        PyObject *module = PyImport_ImportModule("torch.utils._device");
+        if (module) default_device = PyObject_GetAttrString(module, "DeviceContext");
+        Py_XDECREF(module);
+        PyErr_Clear();
+    }
+    for (int64_t i = 0; i < at::impl::PythonTorchFunctionTLS::stack_len(); ++i) {
+        PyObject *mode = at::impl::PythonTorchFunctionTLS::get_stack_at(i)->ptr(getPyInterpreter());
+        if ((PyObject *)Py_TYPE(mode) != default_device) return false;
+    }
     return true;
 }
 std::optional<Tensor> maybe(const Tensor &t) { return t.defined() ? std::optional(t) : std::nullopt; }
@@ -353,7 +374,7 @@ struct Args {
     double scale = 0;
     bool ok = false;
     Args(PyObject *const *a, Py_ssize_t n) {
-        if (n != 6 || !tensor_arg(a[0], q) || !tensor_arg(a[1], k) || !tensor_arg(a[2], v) || !tensor_arg(a[3], rpb, true)) return;
+        if (n != 6 || !plain_modes() || !tensor_arg(a[0], q) || !tensor_arg(a[1], k) || !tensor_arg(a[2], v) || !tensor_arg(a[3], rpb, true)) return;
         ks = PyLong_AsLongLong(a[4]);
         scale = a[5] == Py_None ? (q.dim() > 0 ? std::pow((double)q.size(-1), -0.5) : 0.) : PyFloat_AsDouble(a[5]);
         ok = !PyErr_Occurred();

@@ -123,3 +123,34 @@ def test_a_transform_does_not_outlive_itself():
             F.na2d(q, k, v, b, kernel_size=5)
         return x
     torch.func.vmap(body)(torch.ones(2))
+
+
+class Tagged(torch.Tensor):   # (its __torch_function__ is the inherited one: results are of the subclass)
+    pass
+
+
+@pytest.mark.parametrize("name", list(OPS))
+def test_subclasses_and_torch_function_modes_are_asked(name):
+    native, interpreted = OPS[name]
+    (q, k, v, b), _ = inputs(name, torch.float16)
+    for args in ((q.as_subclass(Tagged), k, v, b), (q, k, v, b.as_subclass(Tagged))):
+        out, want = native(*args, kernel_size=5), interpreted(*args, 5, None)
+        assert type(out) is type(want) and type(out.grad_fn).__name__ == type(want.grad_fn).__name__
+        assert torch.equal(out.as_subclass(torch.Tensor), want.as_subclass(torch.Tensor))
+    assert type(native(q.as_subclass(Tagged), k, v, b, kernel_size=5)) is (Tagged if name != "unfused" else torch.Tensor)
+
+    class Count(torch.overrides.TorchFunctionMode):
+        calls = 0
+
+        def __torch_function__(self, func, types, args=(), kwargs=None):
+            Count.calls += 1
+            return func(*args, **(kwargs or {}))
+
+    with Count():
+        native(q, k, v, b, kernel_size=5)
+    assert Count.calls > 0
+    native_node = type(native(q, k, v, b, kernel_size=5).grad_fn)
+    with torch.device("cpu"):   # (the mode of a default device has nothing to say here)
+        assert type(native(q, k, v, b, kernel_size=5).grad_fn) is native_node
+    parameter = native(torch.nn.Parameter(q.detach()), k, v, b, kernel_size=5)   # (as plain as a tensor)
+    assert type(parameter.grad_fn) is type(native(q, k, v, b, kernel_size=5).grad_fn)
