@@ -150,6 +150,8 @@ def _ptr(t, dtype=None, shape=None):
         raise ValueError("na2d takes GPU tensors only")
     if not t.is_contiguous():
         raise ValueError("na2d takes contiguous tensors only")
+    if t.is_neg():
+        raise ValueError("na2d does not take negated views")
     if dtype is not None and t.dtype != dtype:
         raise ValueError(f"expected dtype {dtype}, got {t.dtype}")
     if shape is not None and tuple(t.shape) != tuple(shape):

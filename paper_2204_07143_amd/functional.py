@@ -41,6 +41,11 @@ def _native():
     return _native_module
 
 
+def _dense(t: torch.Tensor) -> torch.Tensor:
+    """``t`` as it lies in memory: contiguous, and a negated view written out."""
+    return t.resolve_neg().contiguous()
+
+
 def _workspace(x: torch.Tensor, kernel_size: int, kind: int) -> torch.Tensor:
     B, heads, H, W, D = x.shape
     p = na.problem(B, heads, H, W, D, kernel_size, x.dtype)
@@ -56,8 +61,8 @@ class _NA2DQKRPB(torch.autograd.Function):
 
     @staticmethod
     def forward(ctx, q, k, rpb, kernel_size, scale):
-        q, k = q.contiguous(), k.contiguous()
-        rpb_c = None if rpb is None else rpb.contiguous()
+        q, k = _dense(q), _dense(k)
+        rpb_c = None if rpb is None else _dense(rpb)
         logits = torch.empty((*q.shape[:4], kernel_size * kernel_size), dtype=q.dtype, device=q.device)
         na.na2d_qk_rpb(q, k, rpb_c, scale, kernel_size, logits)
         ctx.save_for_backward(q, k)
@@ -69,7 +74,7 @@ class _NA2DQKRPB(torch.autograd.Function):
     def backward(ctx, dlogits):
         q, k = ctx.saved_tensors
         ks, scale = ctx.kernel_size, ctx.scale
-        dlogits = dlogits.contiguous()
+        dlogits = _dense(dlogits)
         dq, dk, d_rpb = None, None, None
         if ctx.needs_input_grad[0]:
             dq = na.na2d_qk_bwd_q(dlogits, k, scale, ks, torch.empty_like(q))
@@ -87,7 +92,7 @@ class _NA2DAV(torch.autograd.Function):
 
     @staticmethod
     def forward(ctx, attn, v, kernel_size):
-        attn, v = attn.contiguous(), v.contiguous()
+        attn, v = _dense(attn), _dense(v)
         out = na.na2d_av(attn, v, kernel_size, torch.empty_like(v))
         ctx.save_for_backward(attn, v)
         ctx.kernel_size = kernel_size
@@ -97,7 +102,7 @@ class _NA2DAV(torch.autograd.Function):
     def backward(ctx, dout):
         attn, v = ctx.saved_tensors
         ks = ctx.kernel_size
-        dout = dout.contiguous()
+        dout = _dense(dout)
         dattn, dv = None, None
         if ctx.needs_input_grad[0]:
             dattn = na.na2d_av_bwd_p(dout, v, ks, torch.empty_like(attn))
@@ -111,8 +116,8 @@ class _NA2D(torch.autograd.Function):
 
     @staticmethod
     def forward(ctx, q, k, v, rpb, kernel_size, scale):
-        q, k, v = q.contiguous(), k.contiguous(), v.contiguous()
-        rpb_c = None if rpb is None else rpb.contiguous()
+        q, k, v = _dense(q), _dense(k), _dense(v)
+        rpb_c = None if rpb is None else _dense(rpb)
         out = torch.empty_like(q)
         lse = torch.empty(q.shape[:4], dtype=torch.float32, device=q.device)
         na.na2d_fused_fwd(q, k, v, rpb_c, scale, kernel_size, out, lse)
@@ -132,10 +137,10 @@ class _NA2D(torch.autograd.Function):
         d32 = torch.empty((q.shape[1], 2 * ks - 1, 2 * ks - 1), dtype=torch.float32, device=q.device) if want_bias else None
         direct = na.na2d_direct_bwd_workspace_bytes(na.problem(*q.shape, ks, q.dtype))   # 0: not for this problem
         if direct:
-            na.na2d_direct_bwd(q, k, v, rpb, ctx.scale, lse, dout.contiguous(), ks, dq, dk, dv, d32,
+            na.na2d_direct_bwd(q, k, v, rpb, ctx.scale, lse, _dense(dout), ks, dq, dk, dv, d32,
                                torch.empty(direct, dtype=torch.uint8, device=q.device))
         else:
-            na.na2d_fused_bwd(q, k, v, rpb, ctx.scale, lse, dout.contiguous(), ks, dq, dk, dv, d32,
+            na.na2d_fused_bwd(q, k, v, rpb, ctx.scale, lse, _dense(dout), ks, dq, dk, dv, d32,
                               _workspace(q, ks, na.WS_FUSED_BWD))
         return dq, dk, dv, (d32.to(rpb.dtype) if want_bias else None), None, None
 
@@ -145,8 +150,8 @@ class _NA1D(torch.autograd.Function):
 
     @staticmethod
     def forward(ctx, q, k, v, rpb, kernel_size, scale):
-        q, k, v = q.contiguous(), k.contiguous(), v.contiguous()
-        rpb_c = None if rpb is None else rpb.contiguous()
+        q, k, v = _dense(q), _dense(k), _dense(v)
+        rpb_c = None if rpb is None else _dense(rpb)
         out = torch.empty_like(q)
         lse = torch.empty(q.shape[:3], dtype=torch.float32, device=q.device)
         na.na1d_fused_fwd(q, k, v, rpb_c, scale, kernel_size, out, lse)
@@ -167,7 +172,7 @@ class _NA1D(torch.autograd.Function):
         d32 = torch.empty((heads, 2 * ks - 1), dtype=torch.float32, device=q.device) if want_bias else None
         ws = torch.empty(max(16, na.na1d_fused_bwd_workspace_bytes(na.problem_1d(B, heads, L, D, ks, q.dtype))),
                          dtype=torch.uint8, device=q.device)
-        na.na1d_fused_bwd(q, k, v, rpb, ctx.scale, lse, dout.contiguous(), ks, dq, dk, dv, d32, ws)
+        na.na1d_fused_bwd(q, k, v, rpb, ctx.scale, lse, _dense(dout), ks, dq, dk, dv, d32, ws)
         return dq, dk, dv, (d32.to(rpb.dtype) if want_bias else None), None, None
 
 
@@ -176,7 +181,7 @@ class _NA2DSoftmax(torch.autograd.Function):
 
     @staticmethod
     def forward(ctx, logits, like, kernel_size):
-        logits = logits.contiguous()
+        logits = _dense(logits)
         attn = na.na2d_softmax(logits, kernel_size, like, torch.empty_like(logits))
         ctx.save_for_backward(attn)
         ctx.kernel_size, ctx.like_shape = kernel_size, like.shape
@@ -186,7 +191,7 @@ class _NA2DSoftmax(torch.autograd.Function):
     def backward(ctx, dattn):
         (attn,) = ctx.saved_tensors
         like = torch.empty(ctx.like_shape, dtype=attn.dtype, device="meta")   # shape and dtype only
-        ds = na.na2d_softmax_bwd(attn, dattn.contiguous(), ctx.kernel_size, like, torch.empty_like(attn))
+        ds = na.na2d_softmax_bwd(attn, _dense(dattn), ctx.kernel_size, like, torch.empty_like(attn))
         return ds, None, None
 
 

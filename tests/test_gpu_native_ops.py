@@ -154,3 +154,17 @@ def test_subclasses_and_torch_function_modes_are_asked(name):
         assert type(native(q, k, v, b, kernel_size=5).grad_fn) is native_node
     parameter = native(torch.nn.Parameter(q.detach()), k, v, b, kernel_size=5)   # (as plain as a tensor)
     assert type(parameter.grad_fn) is type(native(q, k, v, b, kernel_size=5).grad_fn)
+
+
+@pytest.mark.parametrize("name", list(OPS))
+def test_negated_views(name):
+    """A view whose sign is left to its readers, as an input and as the upstream gradient, through both host sides."""
+    (q, k, v, b), dout = inputs(name, torch.float32)
+    negated = lambda t: torch._neg_view(t.detach()).requires_grad_(t.requires_grad)
+    assert negated(dout).contiguous().is_neg()
+    for op in OPS[name][0], lambda *a, kernel_size: OPS[name][1](*a, kernel_size, None):
+        want = [op(-q, k, -v, b, kernel_size=5), *torch.autograd.grad(op(q, k, v, b, kernel_size=5), (q, k, v, b), -dout)]
+        got = [op(negated(q), k, negated(v), b, kernel_size=5), *torch.autograd.grad(op(q, k, v, b, kernel_size=5), (q, k, v, b), negated(dout))]
+        assert all(torch.equal(g, w) for g, w in zip(got, want))
+    with pytest.raises(ValueError):
+        na.na2d_softmax(negated(q), 5, q, q)
