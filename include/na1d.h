@@ -85,8 +85,7 @@ size_t na1d_workspace_bytes(const na1d_problem *p);
  * na1d_fused_fwd stored for every query.  The attention weights are recomputed as
  * exp(scale <q, k> + bias - lse).  `rpb` may be NULL (no bias in the forward).  No output may alias an input
  * or another output.  d_rpb is summed in 64-bit fixed point as in na1d_qk_bwd_rpb (bitwise reproducible).
- * For the 16-bit types the kernels run on the matrix cores (weights and ds as two 16-bit halves each) and add up to four
- * terms of a cell in fp32 before they join the integers.
+ * For the 16-bit types the kernels run on the matrix cores (weights and ds as two 16-bit halves each: 22 digits in fp16, 16 in bf16).
  * `workspace` must hold na1d_fused_bwd_workspace_bytes(p) bytes; no initialisation needed. */
 int na1d_fused_bwd(const na1d_problem *p, const void *q, const void *k, const void *v, const void *rpb, float scale,
                    const float *lse, const void *dout, void *dq, void *dk, void *dv, float *d_rpb, void *workspace,

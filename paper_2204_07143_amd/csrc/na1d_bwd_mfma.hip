@@ -7,8 +7,8 @@
 // them): dv_j = sum_i P dout_i, dk_j = scale sum_i dS q_i.
 // P and dS enter the sums as two 16-bit halves (22 digits in fp16, 16 in bf16).  In fp16 a column's dS are scaled by the power of two that
 // brings the largest near 2^15, so that the result does not depend on the scale of dout.
-// Bias gradient: clear of the ends a lane's cells are the same for each of its groups, so that it adds them up in registers; then they join
-// the workgroup's table as 64-bit fixed-point integers (integer additions commute: the result is bitwise reproducible).
+// Bias gradient: clear of the ends a lane's cells are the same for each of its groups, so that it adds them up in registers, in 64 bits; then they
+// join the workgroup's table as 64-bit fixed-point integers (integer additions commute: the result is bitwise reproducible).
 // A masked product is 0 * x: results that are not finite are computed once more from their own window.
 // Measured at 64 x 2 x 3136 queries, fp16, query side + key side (a thread per position on the plain ALU before): k = 7 24.1 + 29.5 us
 // (38.8 + 33.5), bound by memory at 5.3 TB/s; k = 31 26.8 + 32.8; k = 63 35.8 + 44.3, where the vector instructions of 5 blocks show.
@@ -54,7 +54,7 @@ template <typename T> struct Pair {
         dp = group_sum(dot32(dout, v));
     }
 };
-__device__ __forceinline__ void add_cell(int table, int cell, float ds) {
+template <typename F> __device__ __forceinline__ void add_cell(int table, int cell, F ds) {
     __hip_atomic_fetch_add(lds_ptr<unsigned long long>(table + cell * 8), (unsigned long long)to_fixed42(ds), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
 }
 
@@ -109,7 +109,10 @@ __device__ void key_once_more(const Plane<T> &m, float scale, int key, int L, in
 }
 
 template <int NBLK> constexpr int kQueryRows = kTile - kGroup + 16 * NBLK;   // keys staged
-__host__ __device__ constexpr int query_lds(int nblk, int K) { return 2 * (kTile - kGroup + 16 * nblk) * kBytes + up16((2 * K - 1) * 4) + (2 * K - 1) * 8; }
+// both images, the bias as each lane of a group clear of the ends meets it, the bias and the integers of its gradient
+__host__ __device__ constexpr int query_lds(int nblk, int K) {
+    return 2 * (kTile - kGroup + 16 * nblk) * kBytes + nblk * kWave * 16 + up16((2 * K - 1) * 4) + (2 * K - 1) * 8;
+}
 
 template <typename T, int NBLK>
 __global__ __launch_bounds__(kThreads, (NBLK > 3 ? 3 : 4)) void bwd1d_q_mfma_kernel(
@@ -120,14 +123,22 @@ __global__ __launch_bounds__(kThreads, (NBLK > 3 ? 3 : 4)) void bwd1d_q_mfma_ker
     const int tid = threadIdx.x, lane = tid % kWave, wave = __builtin_amdgcn_readfirstlane(tid / kWave), j = lane & 15, g = lane >> 4;
     const int plane = blockIdx.x / tiles, t0 = (blockIdx.x - plane * tiles) * kTile, NB = 2 * K - 1, R = K >> 1;
     const size_t first = (size_t)plane * L;
-    const int h0 = win_start(t0, L, K), img = lds_addr(lds), cells = img + 2 * kImage + up16(NB * 4), table = partial ? cells : 0;
-    float *bias = reinterpret_cast<float *>(lds + 2 * kImage);
+    constexpr int kInner = NBLK * kWave * 16;
+    const int h0 = win_start(t0, L, K), img = lds_addr(lds), inner = img + 2 * kImage, cells = inner + kInner + up16(NB * 4), table = partial ? cells : 0;
+    float *bias = reinterpret_cast<float *>(lds + 2 * kImage + kInner);
     stage_pair<kWaves>(reinterpret_cast<const char *>(k) + (first + h0) * kBytes, reinterpret_cast<const char *>(v) + (first + h0) * kBytes, L - 1 - h0,
                        kQueryRows<NBLK>, img, img + kImage, wave, lane);
     const T *own_rpb = rpb ? rpb + (size_t)(plane % heads) * NB : nullptr;
     for (int u = tid; u < NB; u += kThreads) {
         bias[u] = own_rpb ? to_f32(own_rpb[u]) * kLog2e : 0.f;
         if (partial) *lds_ptr<unsigned long long>(cells + u * 8) = 0ull;
+    }
+#pragma unroll
+    for (int u = tid; u < NBLK * kWave * 4; u += kThreads) {   // (block, lane, result)
+        const int a = 16 * (u >> 8) + 4 * ((u >> 6) & 3) + (u & 3) - ((u >> 2) & 15);   // slot in the window
+        const bool in = (unsigned)a < (unsigned)K;
+        const float t = own_rpb && in ? to_f32(own_rpb[a + K - 1 - R]) * kLog2e : 0.f;
+        *lds_ptr<float>(inner + u * 4) = in ? t : -INFINITY;
     }
     u32x4 qv, gv;
     float lse_i;
@@ -143,12 +154,11 @@ __global__ __launch_bounds__(kThreads, (NBLK > 3 ? 3 : 4)) void bwd1d_q_mfma_ker
     workgroup_sync();
 
     const float scale2 = scale * kLog2e;
-    float b[NBLK][4], sums[NBLK][4];
-    bool inner = false;   // b[] is that of a group clear of the ends
+    double sums[NBLK][4];   // (four fp32 numbers to 2^-42 and beyond)
 #pragma unroll
     for (int c = 0; c < NBLK; ++c)
 #pragma unroll
-        for (int r = 0; r < 4; ++r) sums[c][r] = 0.f;
+        for (int r = 0; r < 4; ++r) sums[c][r] = 0.;
 #pragma unroll 1
     for (int n = 0; n < kGroups; ++n) {
         const int i0 = t0 + (wave * kGroups + n) * kGroup;
@@ -156,7 +166,11 @@ __global__ __launch_bounds__(kThreads, (NBLK > 3 ? 3 : 4)) void bwd1d_q_mfma_ker
         const int o = win_start(i0, L, K), i = i0 + j < L ? i0 + j : L - 1;
         const int w = win_start(i, L, K) - o;   // the lane's window begins at position w of the blocks
         const bool clear = o == i0 - R && i0 + kGroup - 1 + R < L;
-        if (!(clear && inner)) {
+        f32x4 b[NBLK];
+        if (clear) {
+#pragma unroll
+            for (int c = 0; c < NBLK; ++c) b[c] = *lds_ptr<f32x4>(inner + c * (kWave * 16) + lane * 16);
+        } else {
 #pragma unroll
             for (int c = 0; c < NBLK; ++c)
 #pragma unroll
@@ -166,7 +180,6 @@ __global__ __launch_bounds__(kThreads, (NBLK > 3 ? 3 : 4)) void bwd1d_q_mfma_ker
                     const float t = bias[in ? at + o - i + K - 1 : 0];
                     b[c][r] = in ? t : -INFINITY;
                 }
-            inner = clear;
         }
         const int ka = row_addr(img, o - h0, j, g);
         const float lse2 = lse_i * kLog2e;
@@ -176,7 +189,7 @@ __global__ __launch_bounds__(kThreads, (NBLK > 3 ? 3 : 4)) void bwd1d_q_mfma_ker
             s[c] = mfma_16x16x32<T>(*lds_ptr<u32x4>(ka + c * kGroup * kBytes), qv, f32x4{0.f, 0.f, 0.f, 0.f});
             dp[c] = mfma_16x16x32<T>(*lds_ptr<u32x4>(ka + kImage + c * kGroup * kBytes), gv, f32x4{0.f, 0.f, 0.f, 0.f});
         }
-        if (n + 1 < kGroups) load(n + 1);
+        if (NBLK != 3 && n + 1 < kGroups) load(n + 1);
         float delta = 0.f;
 #pragma unroll
         for (int c = 0; c < NBLK; ++c)
@@ -203,6 +216,7 @@ __global__ __launch_bounds__(kThreads, (NBLK > 3 ? 3 : 4)) void bwd1d_q_mfma_ker
             ws[c].set(t);
         }
         f32x4 acc[2] = {f32x4{0.f, 0.f, 0.f, 0.f}, f32x4{0.f, 0.f, 0.f, 0.f}};
+        if (NBLK == 3 && n + 1 < kGroups) load(n + 1);   // (later, for the registers)
         weighted_sum<T, NBLK>(vector_addr(img, o - h0, j, g), ws, acc);
         const float back = scale * __builtin_ldexpf(1.f, -e);
         float x[8], odd = delta * 0.f;   // odd: NaN where something is not finite

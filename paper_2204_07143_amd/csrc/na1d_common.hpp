@@ -15,6 +15,10 @@ __device__ __forceinline__ long long to_fixed42(float x) {
     const float fl = __builtin_floorf(y);
     return (long long)(((unsigned long long)(uint32_t)(int)fl << 32) | (uint32_t)((y - fl) * 4294967296.f));
 }
+__device__ __forceinline__ long long to_fixed42(double x) {   // (in range)
+    const double y = x * 1024., fl = __builtin_floor(y);
+    return (long long)(((unsigned long long)(uint32_t)(int)fl << 32) | (uint32_t)((y - fl) * 4294967296.));
+}
 
 // Where a running maximum starts: not -inf, whose difference to a first logit of -inf (a masked bias cell) would be NaN
 constexpr float kLowest = -3.402823466e38f;

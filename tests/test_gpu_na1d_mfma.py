@@ -129,3 +129,22 @@ def test_forward_with_masked_bias_cells(dtype):
     finite = np.isfinite(want_lse)
     assert np.array_equal(np.isfinite(to_np(lse)), finite)
     assert_close("lse", np.where(finite, to_np(lse), 0.0), np.where(finite, want_lse, 0.0), "f32")
+
+
+@pytest.mark.parametrize("dtype", ["f16", "bf16"])
+@pytest.mark.parametrize("k", [7, 31, 63])
+def test_bias_gradient_of_large_terms_that_cancel(dtype, k):
+    """Queries 16 positions apart that see the same keys' values: the first sixteen's dS are large, the third's the same with the other sign, and what is
+    left of a cell is the second's, which an fp32 sum of the three would have lost."""
+    def edit(host):
+        for n in ("v", "dout"):
+            host[n][:] = np.sign(host[n])   # (their products are whole numbers: the same with either sign)
+        for n in ("q", "k", "v"):
+            host[n][:] = np.tile(host[n][:, :, :16], (1, 1, 32, 1))
+        dout = host["dout"][:, :, 64:80].copy()
+        small = host["dout"][:, :, 80:96].copy()
+        host["dout"][:] = 0
+        host["dout"][:, :, 64:80], host["dout"][:, :, 80:96], host["dout"][:, :, 96:112] = 2.0 ** 11 * dout, 2.0 ** -9 * small, -2.0 ** 11 * dout
+
+    got, want = backward(synth.Problem1D(1, 2, 512, 32, k, dtype), seed=k, edit=edit)
+    assert_close_rpb("d_rpb", got[3], want[3])
