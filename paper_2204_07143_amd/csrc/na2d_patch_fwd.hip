@@ -6,8 +6,8 @@
 // maximum that is only moved when a logit exceeds it by kSlack: in most blocks no lane has to know another's.  In small calls
 // 2, 4 or 8 waves share a patch, a row of blocks each, and are joined in wave order.
 //
-// In 16 bit a weight enters as a high and a low half, p = hi + lo to 2^-17 of p in bf16.  In fp16 weights are scaled by 2^14 (kUp;
-// their sum likewise): 2^15 at most, to 2^-22 of themselves down to 2^-17 of the largest and to 2^-39 of the largest below.
+// In 16 bit a weight enters as a high and a low half, p = hi + lo to 2^-17 of p in bf16.  In fp16 weights are scaled by 2^15 (kUp;
+// their sum likewise): 65000 at most, to 2^-22 of themselves down to 2^-18 of the largest and to 2^-40 of the largest below.
 //
 // A masked product is 0 * v: outputs that are not finite are worked out once more from their own window only.
 //
@@ -27,9 +27,9 @@ namespace {
 template <typename T, int D> constexpr int kFwdOcc = D * sizeof(T) <= 128 ? 4 : 2;
 template <typename T, int D> constexpr int kFwdAtOnce = D * sizeof(T) <= 64 || kFwdOcc<T, D> == 2 ? 2 : 1;
 template <typename T> constexpr float kUp = 0.f;          // log2 of what the weights are scaled by
-template <> constexpr float kUp<f16_t> = 14.f;
+template <> constexpr float kUp<f16_t> = 15.f;
 template <typename T> constexpr float kSlack = 20.f;      // by how much (log2) a logit may exceed the base
-template <> constexpr float kSlack<f16_t> = 1.f;
+template <> constexpr float kSlack<f16_t> = 0.98f;        // (2^15.98 is the last that fp16 holds with room for the roundings)
 
 // The outputs and the log-sum-exp of one query from its own window, in raster order: the largest logit, then 64 slots' weights at a time (a
 // slot to a lane), then each lane adds up its channels.  A logit that is NaN or +inf makes every output NaN, and once every sum is NaN

@@ -4,8 +4,10 @@ from __future__ import annotations
 
 import numpy as np
 import pytest
+import torch
 
 from gpu_util import Stages, assert_close
+from paper_2204_07143_amd import functional as F
 from paper_2204_07143_amd import synth
 
 pytestmark = pytest.mark.gpu
@@ -50,3 +52,19 @@ def test_maximum_that_moves(oracle, dtype, B):
     host["rpb"][1] = -rise
     host["rpb"][2, : k - 3] = -np.inf
     check(oracle, p, host, planes=(0,), scale=0.05)
+
+
+@pytest.mark.parametrize("planes", [1, 100])   # eight waves to a patch and one
+def test_smallest_fp16_weights(planes):
+    """One key takes all but 2^-27 of a query's weight and has no value; the others weigh 3 * 2^-39 of it each, which fp16 holds exactly once the largest is
+    2^15: with one bit less the output would be a third too large."""
+    H, W, D, k = 62, 31, 16, 31
+    q, key, v = (torch.zeros(planes, 1, H, W, D, dtype=torch.float16, device="cuda") for _ in range(3))
+    v[..., 1::2, :] = 6e4
+    rpb = torch.zeros(1, 2 * k - 1, 2 * k - 1, dtype=torch.float16, device="cuda")
+    rpb[:, k - 1, k - 1] = 39 * np.log(2) - np.log(3)   # (to 2^-7: the weights to 0.8 %)
+    out = F.na2d(q, key, v, rpb, kernel_size=k)[..., 0::2, :].double()
+    large = k * (torch.arange(k).remainder(2) == 1).sum().item()   # (W = k: every window holds all columns)
+    p = torch.exp(-rpb[0, k - 1, k - 1].double())
+    want = large * p * v[0, 0, 0, 1, 0].double() / (1 + (k * k - 1) * p)
+    assert W == k and (out / want - 1).abs().max() < 0.02
