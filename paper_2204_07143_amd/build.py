@@ -11,8 +11,10 @@ from __future__ import annotations
 import argparse
 import concurrent.futures
 import glob
+import importlib.metadata
 import importlib.util
 import os
+import shutil
 import subprocess
 import sys
 import sysconfig
@@ -24,6 +26,7 @@ OBJ_DIR = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libna2d.so")
 HOST_SRC = os.path.join(CSRC, "host", "torch_ops.cpp")
 HOST_LIB = os.path.join(HERE, "na2d_torch.so")
+HOST_STAMP = os.path.join(OBJ_DIR, "na2d_torch.against")   # the torch that na2d_torch.so was built against
 # measurement build (-DNA2D_PROBE_MEMORY_ONLY: loads and stores only in the tiled contraction kernels); bench.py --lib
 PROBE_LIB = os.path.join(OBJ_DIR, "libna2d_probe_memory_only.so")
 
@@ -89,12 +92,21 @@ def _check_no_scratch(src: str, stderr: str) -> None:
 
 
 def _build_host(force: bool) -> None:
-    """na2d_torch.so from csrc/host: the host compiler, torch's headers and libraries, libna2d.so beside it."""
-    if not force and os.path.exists(HOST_LIB) and os.path.getmtime(HOST_LIB) >= max(os.path.getmtime(HOST_SRC), _newest_header()):
+    """na2d_torch.so from csrc/host: the host compiler, torch's headers and libraries, libna2d.so beside it.  The C-ABI library needs neither: without
+    them it is built alone, and functional.py says what it misses."""
+    spec, cxx = importlib.util.find_spec("torch"), os.environ.get("CXX", "g++")
+    missing = "torch" if spec is None else f"the host compiler {cxx}" if shutil.which(cxx) is None else None
+    if missing:
+        sys.stderr.write(f"{os.path.basename(HOST_LIB)} is not built: {missing} was not found (libna2d.so does not need it)\n")
         return
-    torch_dir = importlib.util.find_spec("torch").submodule_search_locations[0]
+    torch_dir = spec.submodule_search_locations[0]
+    against = f"{importlib.metadata.version('torch')} in {torch_dir}\n"
+    built = open(HOST_STAMP).read() if os.path.exists(HOST_STAMP) else None
+    if (not force and built == against and os.path.exists(HOST_LIB)
+            and os.path.getmtime(HOST_LIB) >= max(os.path.getmtime(HOST_SRC), _newest_header())):
+        return
     rocm = os.path.dirname(os.path.dirname(HIPCC))
-    cmd = [os.environ.get("CXX", "g++"), "-std=c++17", "-O2", "-fPIC", "-shared", "-Wall", "-Wno-sign-compare",
+    cmd = [cxx, "-std=c++17", "-O2", "-fPIC", "-shared", "-Wall", "-Wno-sign-compare",
            "-D__HIP_PLATFORM_AMD__", "-DUSE_ROCM", "-isystem", os.path.join(torch_dir, "include"),
            "-isystem", os.path.join(torch_dir, "include", "torch", "csrc", "api", "include"),
            "-isystem", os.path.join(rocm, "include"), "-I", sysconfig.get_paths()["include"], "-I", os.path.join(ROOT, "include"),
@@ -105,6 +117,8 @@ def _build_host(force: bool) -> None:
         raise RuntimeError(f"host build failed:\n{r.stdout}\n{r.stderr}")
     if r.stderr:
         sys.stderr.write(r.stderr)
+    with open(HOST_STAMP, "w") as f:
+        f.write(against)
 
 
 def build_probe(force: bool = False, jobs: int | None = None) -> str:
