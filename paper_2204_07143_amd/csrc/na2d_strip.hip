@@ -10,7 +10,8 @@
 // read or written in place (a 4 x 4 patch would have fewer masked products, but its weights do not lie in one run per row).
 // What bounds it, by counters at 4 x 2 x 64 x 64 x 32, k = 21, bf16 (107520 blocks of 16 x 16 products): the logits (41 us)
 // their 430k stores, two bytes a lane, 59 % of the wave cycles waiting; the weighted sums (44 us, inverse 26) 8 loads per block, 67
-// and 54 % waiting; the fused forward (50 us) its 188 vector instructions per block, 33 us at four cycles each, 20 % waiting.
+// and 54 % waiting; the fused forward (50 us; such calls run over the patches of na2d_patch_fwd.hip now) its 188 vector instructions per block, 33 us at
+// four cycles each, 20 % waiting.
 //
 // Measured against one thread per output element (that shape, forward and backward of the fused operator, together with
 // the steps of na2d_generic.hip): 3099 -> 268 us.
@@ -23,7 +24,7 @@
 //
 // A masked product is 0 * y.  Where y is not finite that would spoil positions whose window does not hold it, so an
 // output that is not finite is computed once more from its own window only, which ends as soon as its sum is NaN.  A call
-// on values of NaN then takes (us, finite values in brackets): fused forward 7 x 100 x 134, D = 128, k = 9, f16 654 (123; a
+// on values of NaN then took (us, finite values in brackets; the fused calls run over patches now): fused forward 7 x 100 x 134, D = 128, k = 9, f16 654 (123; a
 // thread per output that worked out every logit again: 15400), 4 x 2 x 64 x 64, D = 32, k = 21, bf16 66 (45; 1230); weighted sum there 52 (44; with the whole window 178), inverse 39 (25; 263).
 #include <limits.h>
 
@@ -469,21 +470,18 @@ __global__ __launch_bounds__(kStripThreads) void fused_strip_kernel(const T *__r
 // one to itself, the four of a workgroup one below the other: they read nearly the same rows at the same time, and
 // nothing has to be joined.  The weighted sums gain nothing from it (D = 64, k = 9: 198 / 196 us at 21k strips).
 // Measured on 14 x 14, 28 x 28, 33 x 70 and 56 x 56 maps, fp32, and f16 where it comes here, time with one wave over time with
-// four.  k = 3 (three rows leave one of four waves idle) and 5, D = 128 at 1.8k strips 0.80 .. 0.91, D = 64 0.93 (fused) and
-// 0.96 .. 1.10 (logits), narrower 0.96 .. 1.18; all of them 0.77 .. 1.10 at 4k, 0.71 .. 0.92 at 40k.  Fused, k = 7 and 9:
-// 1.08 .. 1.22 at 3k, 0.90 .. 1.15 at 4k, 0.90 .. 1.09 at 6k, 0.84 .. 0.96 at 40k; k >= 11: to 1.39, 1.29, 1.29 and, at 12k,
-// 0.93 .. 1.08, but with D = 128 1.27, 1.21 and 0.84 .. 1.08.  Logits beyond k = 5, D = 64 and 128 to k = 13: 1.02 .. 1.22 at 3k,
-// 0.87 .. 1.08 at 6k, 0.88 .. 1.06 at 12k; narrower heads and wider windows 0.84 .. 1.39, 0.94 .. 1.18, 0.97 .. 1.17, and
-// 0.90 .. 1.19 at 40k: four waves throughout.
-enum class StripOp { logits, fused };
-int strip_split(const Problem &p, StripOp op) {
-    const bool fused = op == StripOp::fused;
-    long long least;   // strips from which on a wave keeps one to itself
-    if (p.K <= 5) least = p.D == 128 || (p.D == 64 && fused) ? 1536 : 3584;
-    else if (fused) least = p.K <= 9 || p.D == 128 ? 6144 : 12288;
-    else least = p.D >= 64 && p.K <= 13 ? 6144 : LLONG_MAX;
+// four.  Logits, k = 3 (three rows leave one of four waves idle) and 5: D = 128 at 1.8k strips 0.80 .. 0.91, D = 64 0.96 .. 1.10, narrower 0.96 .. 1.18; all of
+// them 0.77 .. 1.10 at 4k, 0.71 .. 0.92 at 40k.  Beyond k = 5, D = 64 and 128 to k = 13: 1.02 .. 1.22 at 3k, 0.87 .. 1.08 at 6k, 0.88 .. 1.06 at 12k;
+// narrower heads and wider windows 0.84 .. 1.39, 0.94 .. 1.18, 0.97 .. 1.17, and 0.90 .. 1.19 at 40k: four waves throughout.
+int logits_split(const Problem &p) {
+    const long long least = p.K <= 5 ? (p.D == 128 ? 1536 : 3584) : p.D >= 64 && p.K <= 13 ? 6144 : LLONG_MAX;   // strips from which on a wave keeps one
     return p.strips() >= least ? 1 : kStripWaves;
 }
+// The fused forward, likewise: k >= 11 1.39 at 3k strips, 1.29 at 4k and 6k, 0.93 .. 1.08 at 12k, but with D = 128 1.27, 1.21 and 0.84 .. 1.08.  It only comes here
+// where the patches of na2d_patch_fwd.hip do not fit the LDS with the waves that a call needs: head vectors of 256 bytes and more from k = 7 on in
+// small calls, and in large ones (64 channels of fp32 and 128 of 16 bit from k = 47 on, 128 of fp32 from k = 29 on); shorter ones from k = 31 on, in small calls only.
+template <typename T, int D> constexpr bool kLongVector = D * sizeof(T) >= 256;
+template <typename T, int D> bool fused_one_wave(const Problem &p) { return p.strips() >= (D == 128 ? 6144 : 12288); }
 
 SShape strip_shape(const Problem &p, int split) {
     const int strips = (p.W + kStrip - 1) / kStrip, per = kStripWaves / split, rows = (p.H + per - 1) / per;
@@ -500,9 +498,8 @@ SShape strip_shape(const Problem &p, int split) {
         return hipGetLastError();                                                                                         \
     } while (0)
 // BODY with T, D and SPLIT bound
-#define NA2D_STRIP_DISPATCH(op, ...)                                                                               \
+#define NA2D_STRIP_DISPATCH(split, ...)                                                                            \
     do {                                                                                                          \
-        const int split = strip_split(p, op);                                                                     \
         const SShape g = strip_shape(p, split);                                                                   \
         if (split == 1) { constexpr int SPLIT = 1; NA2D_DISPATCH_T(p.dtype, NA2D_DISPATCH_D(p.D, __VA_ARGS__)); } \
         else { constexpr int SPLIT = kStripWaves; NA2D_DISPATCH_T(p.dtype, NA2D_DISPATCH_D(p.D, __VA_ARGS__)); }  \
@@ -517,7 +514,8 @@ static int qk_row_groups(const Problem &p, int ntiles) {
     return fill < 1 ? 1 : fill < most ? fill : most;
 }
 hipError_t launch_qk_strip(const Problem &p, const void *x, const void *y, const void *rpb, float scale, void *logits, hipStream_t s) {
-    NA2D_STRIP_DISPATCH(StripOp::logits, NA2D_STRIP_LAUNCH_ROWS(qk_row_groups(p, g.ntiles), (qk_strip_kernel<T, D, SPLIT>), static_cast<const T *>(x),
+    const int split = logits_split(p);
+    NA2D_STRIP_DISPATCH(split, NA2D_STRIP_LAUNCH_ROWS(qk_row_groups(p, g.ntiles), (qk_strip_kernel<T, D, SPLIT>), static_cast<const T *>(x),
                                                static_cast<const T *>(y), static_cast<const T *>(rpb), scale, static_cast<T *>(logits)));
     return hipErrorInvalidValue;
 }
@@ -554,17 +552,24 @@ hipError_t launch_inverse_strip(const Problem &p, const void *w, const void *x, 
     return launch_sum_strip<true>(p, w, x, scale, out, s);
 }
 
-// blocks of keys at a time: two while the strip's windows then fit one pass (K <= 17), three for wider ones
-template <int NBX>
+// NBX blocks of keys at a time: two while the strip's windows then fit one pass (K <= 17), three for wider ones
+template <typename T, int D, int NBX, int SPLIT>
 static hipError_t launch_fused_strip_t(const Problem &p, const void *q, const void *k, const void *v, const void *rpb, float scale,
                                        void *out, float *lse, hipStream_t s) {
-    NA2D_STRIP_DISPATCH(StripOp::fused, NA2D_STRIP_LAUNCH((fused_strip_kernel<T, D, NBX, SPLIT>), static_cast<const T *>(q), static_cast<const T *>(k),
-                                          static_cast<const T *>(v), static_cast<const T *>(rpb), scale, static_cast<T *>(out), lse));
-    return hipErrorInvalidValue;
+    const SShape g = strip_shape(p, SPLIT);
+    NA2D_STRIP_LAUNCH((fused_strip_kernel<T, D, NBX, SPLIT>), static_cast<const T *>(q), static_cast<const T *>(k), static_cast<const T *>(v),
+                      static_cast<const T *>(rpb), scale, static_cast<T *>(out), lse);
 }
 hipError_t launch_fused_strip(const Problem &p, const void *q, const void *k, const void *v, const void *rpb, float scale,
                               void *out, float *lse, hipStream_t s) {
-    return p.K <= 17 ? launch_fused_strip_t<2>(p, q, k, v, rpb, scale, out, lse, s) : launch_fused_strip_t<3>(p, q, k, v, rpb, scale, out, lse, s);
+    NA2D_DISPATCH_T(p.dtype, NA2D_DISPATCH_D(p.D, {
+        if constexpr (kLongVector<T, D>) {
+            if (p.K <= 17) return (launch_fused_strip_t<T, D, 2, kStripWaves>(p, q, k, v, rpb, scale, out, lse, s));
+            if (fused_one_wave<T, D>(p)) return (launch_fused_strip_t<T, D, 3, 1>(p, q, k, v, rpb, scale, out, lse, s));
+        }
+        return (launch_fused_strip_t<T, D, 3, kStripWaves>(p, q, k, v, rpb, scale, out, lse, s));
+    }));
+    return hipErrorInvalidValue;
 }
 
 }  // namespace na2d

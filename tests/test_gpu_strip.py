@@ -26,7 +26,7 @@ def test_forward_at_strip_edges(oracle, H, W, D, k, dtype):
 
 
 @pytest.mark.parametrize("dtype", ["f16", "bf16"])            # the types whose weights enter in two halves
-@pytest.mark.parametrize("planes", [1, 100])   # four waves to a strip, and (12400 strips) one
+@pytest.mark.parametrize("planes", [1, 100])   # (over patches, shared by waves and not; in strips: test_gpu_routes.py)
 def test_small_weights_of_large_values(oracle, planes, dtype):
     # One key takes all but 2.5e-8 of every weight and the values next to it are large: where a query's own column holds
     # zeros its output is the sum of some 480 weights below 2^-25 times 6e4 (about 0.7).  The logits are the bias alone.
@@ -120,7 +120,7 @@ def test_infinities_reach_their_windows_only(dtype):
 @pytest.mark.parametrize("dtype", ["f32", "f16", "bf16"])
 @pytest.mark.parametrize("planes,H,W,D,k", [(1, 17, 33, 16, 15), (370, 17, 17, 16, 15), (1, 21, 40, 32, 21), (1, 13, 18, 128, 13), (420, 15, 17, 128, 15)])
 def test_values_that_are_not_finite_change_no_other_output(planes, H, W, D, k, dtype):
-    # four waves to a strip and (more than 12288 strips) one; four, two and one positions side by side in a wave
+    # (the weighted sum in strips: four, two and one positions side by side in a wave; the fused forward over patches, in strips: test_gpu_routes.py)
     torch.manual_seed(3)
     q, key, v = (torch.randn(planes, 1, H, W, D, device="cuda").to(synth.TORCH_DTYPES[dtype]) for _ in range(3))
     attn = F.na2d_softmax(F.na2d_qk_rpb(q, key, None, k), q, k)
