@@ -34,55 +34,69 @@ __device__ __forceinline__ int lift(float most) {
     return e < 100 ? e : 100;   // (2^100 and its inverse are floats)
 }
 
-template <typename T> struct Plane {
-    const T *q, *k, *v, *dout, *rpb;   // rpb: the head's table or null
+// The four lanes of a column work on it, eight channels each (8 g .. 8 g + 7), which they hold on return.  What it meets lies in LDS.
+// (us of the backward at 64 x 2 x 3136, fp16, k = 31, with one infinite key per plane 118, dout all infinite 191, v or dout all NaN 77, finite 62; with the
+// vectors read from memory, one position at a time, 191, 361 and 85.  k = 63: 214, 403, 106 and 85.)
+template <typename T> struct Pairs {   // kOnceMore positions from `at` on: weights, upstream products, the position's two vectors
+    VecN<T, 8> x[kOnceMore], y[kOnceMore];
+    float p[kOnceMore], dp[kOnceMore];
 };
-// The four lanes of a column work on it, eight channels each (8 g .. 8 g + 7), which they hold on return.
-// (us of a training pass at 64 x 2 x 3136, fp16, k = 31, with v or q all NaN 115, dout all NaN 105, all infinite 382, one infinite key per plane 275;
-// finite 82.  Every lane for itself, with the whole product, took 1140 for an infinite dout.)
-template <typename T> struct Pair {
-    VecN<T, 8> q, k, v, dout;
-    float p, dp;
-    __device__ __forceinline__ Pair(const Plane<T> &m, float scale, int i, int key, int K, int g, float lse2) {
-        load_vec32(q, m.q + (size_t)i * kHeadDim + 8 * g);
-        load_vec32(k, m.k + (size_t)key * kHeadDim + 8 * g);
-        const float t = m.rpb ? to_f32(m.rpb[key - i + K - 1]) * kLog2e : 0.f;
-        p = __builtin_amdgcn_exp2f(__builtin_fmaf(scale * kLog2e, group_sum(dot32(q, k)), t) - lse2);
-        __builtin_amdgcn_sched_barrier(0);   // (one product after the other: the results of a group stay in registers meanwhile)
-        load_vec32(dout, m.dout + (size_t)i * kHeadDim + 8 * g);
-        load_vec32(v, m.v + (size_t)key * kHeadDim + 8 * g);
-        dp = group_sum(dot32(dout, v));
+// p and dp of positions at .. at + kOnceMore - 1 against the lane's own two vectors; xa, ya: the lane's part of position 0 in the two images; bias and
+// lse2 of a position
+template <typename T, typename Bias, typename Lse>
+__device__ __forceinline__ void work_out(Pairs<T> &w, const VecN<T, 8> &own_x, const VecN<T, 8> &own_y, int xa, int ya, int at, int n, float scale2, Bias bias, Lse lse2) {
+#pragma unroll
+    for (int e = 0; e < kOnceMore; ++e) {
+        const int pos = at + e < n ? at + e : n - 1;   // (past the end: once more, not added)
+        load8_lds(w.x[e], xa + pos * kBytes);
+        load8_lds(w.y[e], ya + pos * kBytes);
+        w.p[e] = __builtin_amdgcn_exp2f(__builtin_fmaf(scale2, group_sum(dot32(own_x, w.x[e])), bias(pos)) - lse2(pos));
+        w.dp[e] = group_sum(dot32(own_y, w.y[e]));
     }
-};
+}
 template <typename F> __device__ __forceinline__ void add_cell(int table, int cell, F ds) {
     __hip_atomic_fetch_add(lds_ptr<unsigned long long>(table + cell * 8), (unsigned long long)to_fixed42(ds), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
 }
 
-// One query from its own window: delta, channels 8 g .. 8 g + 7 of dq, and (lane group 0) its part of the bias gradient.
+// One query from its own window: delta, channels 8 g .. 8 g + 7 of dq, and (lane group 0) its part of the bias gradient.  own: its q and dout;
+// ka, va: the lane's part of the window's first key and value; bias: of the window's first slot; cell: its cell's number.
 template <typename T>
-__device__ void query_once_more(const Plane<T> &m, float scale, int i, int L, int K, int g, float lse2, int table, float (&x)[8], float &delta) {
-    const int s = win_start(i, L, K);
+__device__ void query_once_more(const VecN<T, 8> (&own)[2], int ka, int va, const float *bias, float scale, int K, int g, float lse2, int table, int cell, float (&x)[8],
+                                float &delta) {
+    const float scale2 = scale * kLog2e;
+    const auto bias_of = [&](int a) { return bias[a]; };
+    const auto lse_of = [&](int) { return lse2; };
     delta = 0.f;
 #pragma unroll 1
-    for (int a = 0; a < K && delta == delta; ++a) {
-        const Pair<T> w(m, scale, i, s + a, K, g, lse2);
-        delta = __builtin_fmaf(w.p, w.dp, delta);
+    for (int a = 0; a < K && delta == delta; a += kOnceMore) {
+        Pairs<T> w;
+        work_out(w, own[0], own[1], ka, va, a, K, scale2, bias_of, lse_of);
+#pragma unroll
+        for (int e = 0; e < kOnceMore; ++e) delta = a + e < K ? __builtin_fmaf(w.p[e], w.dp[e], delta) : delta;
     }
 #pragma unroll
     for (int d = 0; d < 8; ++d) x[d] = delta == delta ? 0.f : NAN;   // (every dS is NaN then, and counts as 0 in the bias gradient)
 #pragma unroll 1
-    for (int a = 0; a < K && delta == delta; ++a) {
-        const Pair<T> w(m, scale, i, s + a, K, g, lse2);
-        const float ds = w.p * (w.dp - delta);
-        axpy32(x, ds, w.k);
-        if (table && g == 0) add_cell(table, s + a - i + K - 1, ds);
+    for (int a = 0; a < K && delta == delta; a += kOnceMore) {
+        Pairs<T> w;
+        work_out(w, own[0], own[1], ka, va, a, K, scale2, bias_of, lse_of);
+#pragma unroll
+        for (int e = 0; e < kOnceMore; ++e)
+            if (a + e < K) {
+                const float ds = w.p[e] * (w.dp[e] - delta);
+                axpy32(x, ds, w.x[e]);
+                if (table && g == 0) add_cell(table, cell + a + e, ds);
+            }
     }
 #pragma unroll
     for (int d = 0; d < 8; ++d) x[d] *= scale;
 }
-// One key from the queries that see it, likewise; a gradient that is finite in all four lanes stays.
+// One key from the n queries that see it, likewise; a gradient that is finite in all four lanes stays.  own: its k and v; qa, da: the lane's part of
+// the first query and its upstream gradient; ld: that query's (lse, delta); bias: of the first query's cell (those that follow lie in front of it).
 template <typename T>
-__device__ void key_once_more(const Plane<T> &m, float scale, int key, int L, int K, int g, const float *lse, const float *delta, float (&xk)[8], float (&xv)[8]) {
+__device__ void key_once_more(const VecN<T, 8> (&own)[2], int qa, int da, int ld, const float *bias, float scale, int n, float (&xk)[8], float (&xv)[8]) {
+    typedef float f32x2_t __attribute__((ext_vector_type(2)));
+    const float scale2 = scale * kLog2e;
     float ak[8], av[8], nk = 0.f, nv = 0.f;
 #pragma unroll
     for (int d = 0; d < 8; ++d) {
@@ -92,10 +106,15 @@ __device__ void key_once_more(const Plane<T> &m, float scale, int key, int L, in
     }
     const bool want_k = group_sum(nk) != 0.f, want_v = group_sum(nv) != 0.f;   // (0 or NaN)
 #pragma unroll 1
-    for (int i = inv_first(key, L, K); i <= inv_last(key, L, K); ++i) {
-        const Pair<T> w(m, scale, i, key, K, g, lse[i] * kLog2e);
-        axpy32(av, w.p, w.dout);
-        axpy32(ak, w.p * (w.dp - delta[i]), w.q);
+    for (int a = 0; a < n; a += kOnceMore) {
+        Pairs<T> w;
+        work_out(w, own[0], own[1], qa, da, a, n, scale2, [&](int u) { return bias[-u]; }, [&](int u) { return (*lds_ptr<f32x2_t>(ld + u * 8)).x; });
+#pragma unroll
+        for (int e = 0; e < kOnceMore; ++e)
+            if (a + e < n) {
+                axpy32(av, w.p[e], w.y[e]);
+                axpy32(ak, w.p[e] * (w.dp[e] - (*lds_ptr<f32x2_t>(ld + (a + e) * 8)).y), w.x[e]);
+            }
         float open = 0.f;   // (what is NaN stays NaN: not 0 while some wanted sum is still a number)
 #pragma unroll
         for (int d = 0; d < 8; ++d) open = (want_k && ak[d] == ak[d]) || (want_v && av[d] == av[d]) ? 1.f : open;
@@ -244,8 +263,11 @@ __global__ __launch_bounds__(kThreads, (NBLK > 3 ? 3 : 4)) void bwd1d_q_mfma_ker
             }
         }
         if (redo && live) {
-            const Plane<T> m{q + first * kHeadDim, k + first * kHeadDim, v + first * kHeadDim, dout + first * kHeadDim, own_rpb};
-            query_once_more<T>(m, scale, i, L, K, g, lse2, table, x, delta);
+            VecN<T, 8> own[2];
+            load_vec32(own[0], q + (first + i) * kHeadDim + 8 * g);
+            load_vec32(own[1], dout + (first + i) * kHeadDim + 8 * g);
+            const int s0 = win_start(i, L, K), at = img + (s0 - h0) * kBytes + g * 16, cell = s0 - i + K - 1;
+            query_once_more<T>(own, at, at + kImage, bias + cell, scale, K, g, lse2, table, cell, x, delta);
         }
         if (live) {
             store_vector<T>(reinterpret_cast<char *>(dq) + (first + i) * kBytes + g * 16, x);
@@ -378,8 +400,11 @@ __global__ __launch_bounds__(kThreads, (NBLK > 3 ? 3 : 4)) void bwd1d_kv_mfma_ke
         const unsigned again = marked_columns(odd != odd);
         if (j0 + j >= L) continue;
         if ((again >> j) & 1u) {
-            const Plane<T> m{q + first * kHeadDim, k + first * kHeadDim, v + first * kHeadDim, dout + first * kHeadDim, own_rpb};
-            key_once_more<T>(m, scale, key, L, K, g, lse + first, delta + first, xk, xv);
+            VecN<T, 8> own[2];
+            load_vec32(own[0], k + (first + key) * kHeadDim + 8 * g);
+            load_vec32(own[1], v + (first + key) * kHeadDim + 8 * g);
+            const int i0 = inv_first(key, L, K), at = img + (i0 - h0) * kBytes + g * 16;
+            key_once_more<T>(own, at, at + image, ld0 + (i0 - h0) * 8, bias + (key - i0 + K - 1), scale, inv_last(key, L, K) - i0 + 1, xk, xv);
         }
         store_vector<T>(reinterpret_cast<char *>(dk) + (first + key) * kBytes + g * 16, xk);
         store_vector<T>(reinterpret_cast<char *>(dv) + (first + key) * kBytes + g * 16, xv);

@@ -83,14 +83,33 @@ __device__ __forceinline__ void stage_pair(const char *a, const char *b, int las
         global_to_lds_16(b, off, img_b + p * kGroup * kBytes);
     }
 }
+// x of the lane 16 (or 32) further, in one instruction that swaps halves instead of two trips through the LDS unit; the four lanes of a
+// column are active together wherever this is called
+template <int D> __device__ __forceinline__ void both_halves(float x, float &a, float &b) {
+    typedef unsigned u32x2_t __attribute__((ext_vector_type(2)));
+    const unsigned u = __float_as_uint(x);
+    const u32x2_t r = D == 16 ? __builtin_amdgcn_permlane16_swap(u, u, false, false) : __builtin_amdgcn_permlane32_swap(u, u, false, false);
+    a = __uint_as_float(r.x);
+    b = __uint_as_float(r.y);
+}
 __device__ __forceinline__ float group_max(float x) {   // over the four lanes of a column
-    x = fmaxf(x, __shfl_xor(x, 16));
-    return fmaxf(x, __shfl_xor(x, 32));
+    float a, b;
+    both_halves<16>(x, a, b);
+    both_halves<32>(fmaxf(a, b), a, b);
+    return fmaxf(a, b);
 }
 __device__ __forceinline__ float group_sum(float x) {
-    x += __shfl_xor(x, 16);
-    return x + __shfl_xor(x, 32);
+    float a, b;
+    both_halves<16>(x, a, b);
+    both_halves<32>(a + b, a, b);
+    return a + b;
 }
+template <typename T> __device__ __forceinline__ void load8_lds(VecN<T, 8> &v, int addr) {
+    const u32x4 t = *lds_ptr<u32x4>(addr);
+    v.w[0] = t.x, v.w[1] = t.y, v.w[2] = t.z, v.w[3] = t.w;
+}
+// Positions that the four lanes of a column look at together where a result is worked out once more: their reads and sums do not wait for each other.
+constexpr int kOnceMore = 2;
 // the columns (bit j) of which some lane is marked
 __device__ __forceinline__ unsigned marked_columns(bool mark) {
     const unsigned long long m = __ballot(mark);

@@ -33,27 +33,40 @@ template <int NBLK, int GPW> struct Cfg {
 };
 
 // One query from its own window, as plain sums: lane group g keeps channels 8 g .. 8 g + 7.  An lse that is finite stays.  (What is NaN stays NaN:
-// the rest of the window is left out.)
+// the rest of the window is left out.)  ka, va: this lane's part of the window's first key and value in LDS; bias: of the window's first slot.
 template <typename T>
-__device__ void query_once_more(const T *q, const T *k, const T *v, const T *rpb, float scale, int i, int L, int K, int g, float (&acc)[8], float &lse) {
-    const int s = win_start(i, L, K);
-    VecN<T, 8> qv, kv, vv;   // (the four lanes of a column work on it, eight channels each)
-    load_vec32(qv, q + (size_t)i * kHeadDim + 8 * g);
+__device__ void query_once_more(const u32x4 &own, int ka, int va, const float *bias, float scale2, int K, float (&acc)[8], float &lse) {
+    VecN<T, 8> qv;   // (the four lanes of a column work on it, eight channels each)
+    qv.w[0] = own.x, qv.w[1] = own.y, qv.w[2] = own.z, qv.w[3] = own.w;
     float m = kLowest, l = 0.f;
     const bool keep = fabsf(lse) < INFINITY;
 #pragma unroll
     for (int d = 0; d < 8; ++d) acc[d] = 0.f;
 #pragma unroll 1
-    for (int a = 0; a < K; ++a) {
-        load_vec32(kv, k + (size_t)(s + a) * kHeadDim + 8 * g);
-        load_vec32(vv, v + (size_t)(s + a) * kHeadDim + 8 * g);
-        const float sv = __builtin_fmaf(scale * kLog2e, group_sum(dot32(qv, kv)), rpb ? to_f32(rpb[s + a - i + K - 1]) * kLog2e : 0.f);
-        const float mn = fmaxf(m, sv), c = __builtin_amdgcn_exp2f(m - mn), p = __builtin_amdgcn_exp2f(sv - mn);
-        l = __builtin_fmaf(l, c, p);
+    for (int a = 0; a < K; a += kOnceMore) {
+        float s[kOnceMore], most = m;
+        VecN<T, 8> v[kOnceMore];
+#pragma unroll
+        for (int e = 0; e < kOnceMore; ++e) {
+            const int at = a + e < K ? a + e : K - 1;   // (past the end: once more, not added)
+            VecN<T, 8> kv;
+            load8_lds(kv, ka + at * kBytes);
+            load8_lds(v[e], va + at * kBytes);
+            s[e] = __builtin_fmaf(scale2, group_sum(dot32(qv, kv)), bias[at]);
+            most = fmaxf(most, s[e]);
+        }
+        const float c = __builtin_amdgcn_exp2f(m - most);
+        m = most;
+        l *= c;
 #pragma unroll
         for (int d = 0; d < 8; ++d) acc[d] *= c;
-        axpy32(acc, p, vv);
-        m = mn;
+#pragma unroll
+        for (int e = 0; e < kOnceMore; ++e)
+            if (a + e < K) {
+                const float p = __builtin_amdgcn_exp2f(s[e] - m);
+                l += p;
+                axpy32(acc, p, v[e]);
+            }
         float open = keep ? 0.f : 1.f;
 #pragma unroll
         for (int d = 0; d < 8; ++d) open = acc[d] == acc[d] ? 1.f : open;
@@ -148,8 +161,10 @@ __global__ __launch_bounds__(kThreads, 4) void fused1d_mfma_kernel(const T *__re
             odd = __builtin_fmaf(x[d], 0.f, odd);
         }
         const unsigned again = marked_columns(odd != odd);
-        if ((again >> j) & 1u)
-            query_once_more<T>(q + first * kHeadDim, k + first * kHeadDim, v + first * kHeadDim, table, scale, i, L, K, g, x, log_sum);
+        if ((again >> j) & 1u) {
+            const int s0 = win_start(i, L, K), ka = img + (s0 - h0) * kBytes + g * 16;
+            query_once_more<T>(qv[n], ka, ka + C::kImage, bias + (s0 - i + K - 1), scale2, K, x, log_sum);
+        }
         if (i0 + j < L) {
             store_vector<T>(reinterpret_cast<char *>(out) + (first + i) * kBytes + g * 16, x);
             if (lse != nullptr && g == 0) lse[first + i] = log_sum;
