@@ -783,7 +783,8 @@ struct PatchPlan {
 int query_bytes(const Problem &p) { return 4 * (p.dtype == NA2D_F32 ? kQueryWords<float> : kQueryWords<f16_t>); }
 // Pairs of waves in part 2: where one wave per patch leaves half of the chip's 4096 places for waves free, wide windows in 16 bit last as long as
 // the patch of a border takes (81 blocks at k = 21, one inside 36).  us of both parts and the bias gradient, fp16, 32 channels, one wave / two: k = 15
-// 40 / 34 at 256 patches, 44 / 39 at 1300, 43 / 42 at 2048, 60 / 67 at 4096; k = 21 62 / 48, 64 / 53, 66 / 62, 92 / 95.  (Up to k = 13 no choice looks at the batch.)
+// 40 / 34 at 256 patches, 44 / 39 at 1300, 43 / 42 at 2048, 60 / 67 at 4096; k = 21 62 / 48, 64 / 53, 66 / 62, 92 / 95.  Between (16 to 64 channels, three
+// maps, two waves' time over one's): k = 15 0.89 .. 1.04 to 2600 patches, 0.93 .. 1.14 from there; k = 21 0.87 .. 1.00 to 2600, 0.91 .. 1.05 from there.  (Up to k = 13 no choice looks at the batch.)
 bool pairs_wanted(const Problem &p) {
     return p.dtype != NA2D_F32 && p.K > 13 && p.D <= 64 && (long long)p.planes() * ((p.H + 3) / 4) * ((p.W + 3) / 4) <= 2048;
 }

@@ -26,6 +26,16 @@ def direct(st: Stages, with_rpb_grad=True):
     return (*grads, d_rpb)
 
 
+def assert_close_16bit(name, got, want, dtype):
+    """Bounds that follow the gradients' size.  P (dP - reference), P and dS enter the sums rounded to the storage type and the result is rounded: half a unit
+    of the last place (u = 2^-11 or 2^-8 of the value) at most each, in a root mean square of 0.6 of that; the terms' errors are independent: 1.2 u of the
+    gradients' rms over all.  Where few keys take most of a query's weight the terms, and their errors, are up to four times those of the others: five
+    standard deviations of that, and the result's own rounding, are what one element of 10^6 may be off."""
+    u, err, rms = {"f16": 2.0 ** -11, "bf16": 2.0 ** -8}[dtype], np.abs(got - want), np.sqrt((want * want).mean())
+    assert np.sqrt((err * err).mean()) <= 1.2 * u * rms, (name, np.sqrt((err * err).mean()) / rms)
+    assert (err <= u * np.abs(want) + 24 * u * rms).all(), (name, (err - u * np.abs(want)).max() / rms)
+
+
 def check(oracle, p, seed, use_rpb=True, dout_scale=1.0, scale=None, rpb_std=0.5, f32_factor=1.0):
     host = synth.make_inputs(p, seed, rpb_std=rpb_std)
     host["dout"] = host["dout"] * dout_scale
@@ -43,6 +53,8 @@ def check(oracle, p, seed, use_rpb=True, dout_scale=1.0, scale=None, rpb_std=0.5
             assert (err <= 1e-5 * f32_factor * np.maximum(o, np.sqrt((o * o).mean()))).all(), (n, err.max())
             continue
         assert_close(n, g.double().cpu().numpy() / dout_scale, o / dout_scale, p.dtype, abs_tol=2e-3 if p.dtype != "bf16" else 2e-2)
+        if p.dtype != "f32":
+            assert_close_16bit(n, g.double().cpu().numpy(), o, p.dtype)
     # dS enters exactly (to 2^-24 of the largest): what remains is the lse's spacing in the weights
     if f32_factor == 1.0:
         assert_close_rpb("d_rpb", got[3].double() / dout_scale, want[3] / dout_scale)
@@ -116,6 +128,8 @@ def test_values_that_are_not_finite_reach_their_windows_only(dtype, where):
         f = torch.isfinite(o)
         tol = {"f32": 1e-5, "f16": 2e-2, "bf16": 1e-1}[dtype]   # (the unfused steps round logits, weights, dp and ds)
         assert (g[f] - o[f]).abs().max() <= tol * max(1.0, float(o[f].float().abs().max())), n
+        rel = {"f32": 1e-6, "f16": 2.0 ** -9, "bf16": 2.0 ** -6}[dtype]   # (four roundings of the unfused steps, three of these)
+        assert float((g[f].double() - o[f].double()).norm()) <= rel * float(o[f].double().norm()), n
 
 
 @pytest.mark.parametrize("B,H,W,D,k,dtype", [(1, 3, 3, 64, 3, "f16"), (2, 3, 4, 64, 3, "bf16"), (1, 4, 4, 16, 3, "f32"), (1, 3, 3, 16, 3, "f32"), (3, 21, 18, 16, 11, "f16"),

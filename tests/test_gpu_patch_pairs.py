@@ -15,7 +15,8 @@ pytestmark = pytest.mark.gpu
 @pytest.mark.parametrize("dtype", ["f16", "bf16"])
 @pytest.mark.parametrize("B,heads,H,W,D,k", [
     (1, 1, 15, 15, 32, 15), (2, 3, 21, 22, 16, 21), (4, 2, 17, 50, 64, 15), (3, 1, 41, 37, 32, 19), (8, 2, 45, 43, 32, 21), (5, 4, 39, 41, 16, 17),
-    (5, 4, 40, 44, 32, 15)])
+    (5, 4, 40, 44, 32, 15),
+    (1, 2, 131, 18, 32, 17), (1, 1, 203, 27, 16, 15), (8, 1, 76, 21, 64, 19)])   # (maps of many tile rows)
 @pytest.mark.parametrize("use_rpb", [True, False])
 def test_backward_in_pairs(oracle, dtype, B, heads, H, W, D, k, use_rpb):
     check(oracle, synth.Problem(B, heads, H, W, D, k, dtype), seed=H + W + k, use_rpb=use_rpb)
