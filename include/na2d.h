@@ -207,9 +207,12 @@ int na2d_fused_bwd_is_fused(const na2d_problem *p);
  * The same gradients, from the same arguments, where na2d_fused_bwd would recompute the k*k weights into memory (wider
  * windows, larger head dims, fp32): two kernels over 4 x 4 patches, query patches (dq, delta) and key patches (dk, dv and,
  * if d_rpb != NULL, the bias gradient), whatever the window side.  Products, weights' exponentials and sums are fp32; in 16 bit
- * P dP, P and dS are rounded to the storage type where they enter a sum.  d_rpb is summed per workgroup in integers whose
- * scale follows the largest |dS| a workgroup can meet in a plane (a term is off by at most 2^-24 of that, in fp32 2^-51), so the
- * results are bitwise reproducible; cells that a dS that is not finite belongs to are NaN.
+ * P (dP - c), P and dS are rounded to the storage type where they enter a sum (c: per query, the mean dP of the values near it
+ * where that is larger than their spread, else 0; delta counts from it too, so that dq does not cancel).  d_rpb is summed per
+ * workgroup in integers whose scale follows a bound of the finite |dS| that a workgroup can meet in a plane, max P |delta - c| + max P |dP - c|
+ * over its queries: with 2^E that bound rounded up to a power of two, a term is off by at most 2^(E-24), in fp32 2^(E-51) (cells that only much
+ * smaller dS reach keep fewer digits).  So the results are bitwise reproducible; cells that a dS that is not finite belongs to are
+ * NaN, the others are not touched by it.
  * na2d_direct_bwd_workspace_bytes(p) says how many bytes `workspace` must hold (no initialisation needed); 0 means that the
  * call refuses the problem (NA2D_ERR_WORKSPACE): it is invalid, or na2d_fused_bwd is the faster one or the only one.
  */

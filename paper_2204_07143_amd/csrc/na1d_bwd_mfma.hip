@@ -10,8 +10,8 @@
 // Bias gradient: clear of the ends a lane's cells are the same for each of its groups, so that it adds them up in registers, in 64 bits; then they
 // join the workgroup's table as 64-bit fixed-point integers (integer additions commute: the result is bitwise reproducible).
 // A masked product is 0 * x: results that are not finite are computed once more from their own window.
-// Measured at 64 x 2 x 3136 queries, fp16, query side + key side (a thread per position on the plain ALU before): k = 7 24.1 + 29.5 us
-// (38.8 + 33.5), bound by memory at 5.3 TB/s; k = 31 26.8 + 32.8; k = 63 35.8 + 44.3, where the vector instructions of 5 blocks show.
+// Measured at 64 x 2 x 3136 queries, fp16, the call (a thread per position on the plain ALU before): k = 7 56.8 us, 24.5 the query side and 29.9 the key
+// side at 5.2 TB/s (72); k = 31 62.4 (163); k = 63 85 (369), where the vector instructions of 5 blocks show.
 #include "lds_attr.hpp"
 #include "na1d_common.hpp"
 #include "na1d_kernels.hpp"

@@ -49,6 +49,8 @@ template <typename T> struct Split4 {   // a lane's four weights against a block
         split2<T>(w[2], w[3], hi[1], lo[1]);
     }
 };
+// Against 64 bits the forward's and the backward's results with halves have the 2-norm error of those with whole fp32 weights to 1e-5 of it (1.66e-3 in
+// bf16, 2.07e-4 in fp16: the result's own rounding; k = 3 .. 63, 16 cases of zero-mean inputs; dq in fp16 with offsets of 3 in k and v and 1 in q 2 to 3 % more).
 // acc += (vectors of NBLK blocks, transposed) x weights; addr: the lane's part of block 0 (see vector_addr).  All products have the full depth:
 // with the half-depth instruction for an odd last block, behind full-depth ones in the same accumulators, one build left two of a lane's
 // eight results wrong.

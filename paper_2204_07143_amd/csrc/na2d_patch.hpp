@@ -212,7 +212,7 @@ template <typename T, int D> struct PosSum {
     }
 };
 
-// `rows` (4, 8 or 16) consecutive map rows of one plane of two tensors, `rw` positions each from column x0 on, into two LDS images
+// `rows` (4, 8, 16 or 32) consecutive map rows of one plane of two tensors, `rw` positions each from column x0 on, into two LDS images
 // (the second img_bytes behind the first) by direct loads.  Positions outside the map are replaced by the nearest one inside it (they
 // only meet zero weights).  A row's 1 KB pieces go to the waves of a workgroup in turn (two waves to a row while there are four;
 // rw is a whole number of pieces).
