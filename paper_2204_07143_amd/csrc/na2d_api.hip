@@ -159,7 +159,7 @@ size_t na2d_workspace_bytes(const na2d_problem *p, int kind) {
         const AvRpbSplit sp = fused_bwd_split(pr);
         const int nbc = 2 * pr.K - 1;
         const size_t partials = ((size_t)sp.npos * pr.heads * sp.splits * rpb_cell_stride(nbc * nbc) * sizeof(float) + 255) & ~(size_t)255;
-        return 2 * ((pr.queries() * sizeof(float) + 255) & ~(size_t)255) + partials;   // delta, lse in the exp2 domain
+        return 2 * ((pr.queries() * sizeof(float) + 255) & ~(size_t)255) + partials;   // (lse, delta)
     }
     return 0;
 }
@@ -237,7 +237,7 @@ int na2d_fused_bwd_is_fused(const na2d_problem *p) {
     return fused_bwd_supported(to_problem(p)) ? 1 : 0;
 }
 
-// Workspace of the fused backward.  Two-kernel path: delta and log2(e) * lse, [B, heads, H, W] fp32 each, then one
+// Workspace of the fused backward.  Two-kernel path: the log-sum-exp and delta of every query (two fp32 numbers side by side), then one
 // partial bias gradient per workgroup of the first kernel.  Otherwise: the recomputed attention weights, then the
 // workspace of the unfused backward.
 static size_t fused_bwd_delta_bytes(const Problem &pr) { return (pr.queries() * sizeof(float) + 255) & ~(size_t)255; }
@@ -267,12 +267,11 @@ static int fused_bwd(const na2d_problem *p, const void *q, const void *k, const 
     hipStream_t s = static_cast<hipStream_t>(stream);
     char *ws = static_cast<char *>(workspace);
     if (fused_bwd_supported(pr)) {
-        float *delta = reinterpret_cast<float *>(ws);
-        float *lse2 = reinterpret_cast<float *>(ws + fused_bwd_delta_bytes(pr));
+        float *stat = reinterpret_cast<float *>(ws);
         float *partial = d_rpb ? reinterpret_cast<float *>(ws + 2 * fused_bwd_delta_bytes(pr)) : nullptr;
-        if (launch_fbwd_q(pr, q, k, v, rpb, scale, lse, dout, dq, delta, lse2, partial, s) != hipSuccess)
+        if (launch_fbwd_q(pr, q, k, v, rpb, scale, lse, dout, dq, stat, partial, s) != hipSuccess)
             return from_hip(hipErrorLaunchFailure);
-        if (launch_fbwd_kv(pr, q, k, v, rpb, scale, lse2, delta, dout, dk, dv, s) != hipSuccess)
+        if (launch_fbwd_kv(pr, q, k, v, rpb, scale, stat, dout, dk, dv, s) != hipSuccess)
             return from_hip(hipErrorLaunchFailure);
         if (d_rpb && launch_rpb_final_av(pr, partial, d_rpb, fused_bwd_split(pr), s) != hipSuccess)
             return from_hip(hipErrorLaunchFailure);

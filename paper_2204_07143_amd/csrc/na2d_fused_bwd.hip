@@ -87,7 +87,7 @@ __global__ __launch_bounds__(512, 4) void fbwd_q_kernel(const T *__restrict__ q,
                                                         const T *__restrict__ v, const T *__restrict__ rpb, float scale,
                                                         const float *__restrict__ lse, const T *__restrict__ dout,
                                                         T *__restrict__ dq,
-                                                        float *__restrict__ delta_out, float *__restrict__ lse2_out,
+                                                        float *__restrict__ stat,
                                                         float *__restrict__ rpb_partial,
                                                         int H, int W, int heads, int nb, int tiles_y, int units, int splits, GridDecode gd,
                                                         int half_dim) {
@@ -237,8 +237,9 @@ __global__ __launch_bounds__(512, 4) void fbwd_q_kernel(const T *__restrict__ q,
         for (int i = tid; i < C::NTBL * (C::kTblBytes / 8); i += C::kThreads) *lds_ptr<unsigned long long>(tbl0 + i * 8) = 0ull;
     }
 
-    auto compute = [&](auto par_c, const u32x4 &qreg, const u32x4 &dreg, float lse2, int b) {
+    auto compute = [&](auto par_c, const u32x4 &qreg, const u32x4 &dreg, float lse1, int b) {
         constexpr int PAR = decltype(par_c)::value;
+        const float lse2 = lse1 * kLog2e;
         if (!active) return;
         int lv = lane;
         asm volatile("" : "+v"(lv));
@@ -332,8 +333,8 @@ __global__ __launch_bounds__(512, 4) void fbwd_q_kernel(const T *__restrict__ q,
                 store16_stream(dst, u32x4{pack2_t<T>(o[0][0] * scale, o[0][1] * scale), pack2_t<T>(o[0][2] * scale, o[0][3] * scale),
                                           pack2_t<T>(o[1][0] * scale, o[1][1] * scale), pack2_t<T>(o[1][2] * scale, o[1][3] * scale)});
             if (g == 0) {   // for the key-patch kernel: delta, and the log-sum-exp in the exp2 domain
-                delta_out[plane * H * W + qlin] = delta;
-                lse2_out[plane * H * W + qlin] = lse2;
+                typedef float f32x2_t __attribute__((ext_vector_type(2)));
+                *reinterpret_cast<f32x2_t *>(stat + 2 * (plane * H * W + qlin)) = f32x2_t{lse1, delta};
             }
         }
     };
@@ -345,16 +346,16 @@ __global__ __launch_bounds__(512, 4) void fbwd_q_kernel(const T *__restrict__ q,
         workgroup_sync();       // ... for every wave, and nobody still reads the other buffer pair
         const bool upper = half_dim && g >= 2;   // lanes whose channels a 16-channel head does not have
         const u32x4 qreg = upper ? u32x4{0u, 0u, 0u, 0u} : qnext, dreg = upper ? u32x4{0u, 0u, 0u, 0u} : dnext;
-        const float lse2 = lnext * kLog2e;
+        const float lse1 = lnext;
         if constexpr (C::kOneStage) {
-            compute(par_c, qreg, dreg, lse2, b);
+            compute(par_c, qreg, dreg, lse1, b);
             if (b + 1 < b_end) {
                 workgroup_sync();   // nobody still reads the halos
                 issue(b + 1, 0);
             }
         } else {
             if (b + 1 < b_end) issue(b + 1, PAR ^ 1);
-            compute(par_c, qreg, dreg, lse2, b);
+            compute(par_c, qreg, dreg, lse1, b);
         }
         ++b;
     };
@@ -381,7 +382,7 @@ __global__ __launch_bounds__(512, 4) void fbwd_q_kernel(const T *__restrict__ q,
 
 template <typename T, int K>
 static hipError_t launch_fbwd_q_t(const Problem &p, const void *q, const void *k, const void *v, const void *rpb,
-                                  float scale, const float *lse, const void *dout, void *dq, float *delta, float *lse2,
+                                  float scale, const float *lse, const void *dout, void *dq, float *stat,
                                   float *rpb_partial, hipStream_t s) {
     using C = FbwdQCfg<T, K>;
     static_assert(C::kLdsBytes <= 80 * 1024, "two workgroups share the LDS of a compute unit");
@@ -393,7 +394,7 @@ static hipError_t launch_fbwd_q_t(const Problem &p, const void *q, const void *k
     if (hipError_t e = allow_lds(kern, C::kLdsBytes, allowed[with_rpb]); e != hipSuccess) return e;
     hipLaunchKernelGGL(kern, dim3(xcd_padded_grid(us.units * us.splits)), dim3(C::kThreads), C::kLdsBytes, s,
                        static_cast<const T *>(q), static_cast<const T *>(k), static_cast<const T *>(v),
-                       static_cast<const T *>(rpb), scale, lse, static_cast<const T *>(dout), static_cast<T *>(dq), delta, lse2,
+                       static_cast<const T *>(rpb), scale, lse, static_cast<const T *>(dout), static_cast<T *>(dq), stat,
                        rpb_partial, p.H, p.W, p.heads, p.B, tiles_y, us.units, us.splits, us.gd, p.D == kHalfDim ? 1 : 0);
     return hipGetLastError();
 }
@@ -403,14 +404,24 @@ static hipError_t launch_fbwd_q_t(const Problem &p, const void *q, const void *k
 // A workgroup owns a 16 x 8 key tile (eight waves, one 4 x 4 key patch each), keeps its position and head
 // and walks a range of the batch.  The queries that see any key of the tile form a rectangle of at most
 // (8 + K-1) x (16 + K-1) positions; per plane their q and dout vectors reach LDS by direct loads in the
-// natural layout, their log-sum-exp and delta as fp32 rows.  Per row of the rectangle that sees the
-// patch (a block of 16 consecutive query positions, the first one the leftmost query that sees the patch):
-//   S = Q_blk K^T, dP = dout_blk V^T         (rows of q / dout as 16-byte A operands, the lane's key as B operand)
-//   P = exp2(log2e S' - lse2), dS = P (dP - delta)   per result; a lane holds 4 consecutive positions of its key
+// natural layout, their log-sum-exp and delta as pairs.  A patch takes its part of the rectangle in 4 x 4 blocks of
+// queries, four rows at a time from the first row that sees it (rows past the last are masked):
+//   S = Q_blk K^T, dP = dout_blk V^T         (queries as 16-byte A operands, the lane's key as B operand)
+//   P = exp2(log2e (S' - lse)), dS = P (dP - delta)   per result; a lane holds 4 neighbouring queries of a row for its key
 //   dv^T += dout_blk^T P, dk^T += Q_blk^T dS the half-depth MFMA (q / dout through the transposing LDS read)
 // The bias of (query, key) depends on their offset only; per block a lane needs four neighbouring cells
 // of one table row.  The table is kept in LDS mirrored left to right and in four copies shifted by one
-// element each, so that every such run of four starts on an 8-byte boundary in one of them.
+// element each, so that every such run of four starts on an 8-byte boundary in one of them, and with a row of -inf below it
+// that stands in for the rows of queries that do not see the lane's key; columns are masked by a packed addition.
+// Why 4 x 4 blocks: 9 of them hold what an interior patch meets at K = 7 (4 at K = 3 and 5, 9 at K = 9), where rows of 16 columns took 10 (6, 8
+// and 12), and the blocks of four rows share a lane's bias row, masks and addresses (immediate offsets between them).  lse and delta of a row's
+// 16 columns are one LDS read, handed to the results by a row broadcast in the instruction that subtracts them.  The images' rows end 32 bytes
+// behind their last position and the transposing reads take 32 contiguous bytes of a position: bank conflicts 4.4e6 -> 0.6e6, LDS busy 13e6 -> 5e6
+// cycles, vector instructions 18.1e6 -> 12.0e6 a launch (64 x 2 x 56 x 56, K = 7, fp16).
+// us, before / now, 56 x 56 x 2 x 64 unless said: fp16 K = 3 34.8 / 32.0, K = 5 42.0 / 32.8, K = 7 49.5 / 41.9, K = 9 78.5 / 66.5; bf16 K = 7 64.2 / 51.2;
+// 14 x 14 x 8 x 128, K = 7, fp16 31.8 / 27.1, bf16 39.8 / 31.2.  The loads and stores alone take 27 us at the first shape (5.6 TB/s of
+// compulsory traffic): what is above that is arithmetic that the other workgroups' loads do not cover.  Two buffers and a 16 x 16 tile per
+// workgroup of 16 waves (one per compute unit) were no faster (48 us): four waves per SIMD do not fill the vector units.
 // COMPACT: images sized for the rectangle of a tile away from the far border, (8 + K-1) x (16 + K-1) positions
 // (three workgroups per compute unit); next to the far border the clamped queries reach R positions
 // further, and a map with such tiles takes the larger images (two workgroups per compute unit).
@@ -418,7 +429,7 @@ template <typename T, int K, bool COMPACT>
 struct FbwdKvCfg {
     static constexpr int R = K / 2;
     static constexpr int PWI = K + R + 3;   // query rows / columns that can see a 4 x 4 key patch
-    static_assert(PWI <= 16, "one MFMA block per row of the query rectangle needs K + R + 3 <= 16");
+    static_assert(PWI <= 16, "four blocks of columns hold K + R + 3 <= 16");
     static constexpr int STRIPS = 2;
     static constexpr int WAVES = 4 * STRIPS;
     static constexpr int TY = 4 * STRIPS;
@@ -428,36 +439,53 @@ struct FbwdKvCfg {
     static constexpr bool CHUNKED = K > 7;
     static_assert(!CHUNKED || !COMPACT, "the chunked images are always the wide ones");
     static constexpr int kRowsMax = TY + K - 1 + (COMPACT ? 0 : R);   // rows of a rectangle, at most
-    static constexpr int RH = CHUNKED ? 16 : kRowsMax, RW = kTileX + K - 1 + (COMPACT ? 0 : R);   // the images
-    static_assert(kRowsMax <= 32 && kRowsMax <= 2 * RH, "row flags; two chunks");
+    static constexpr int RH = CHUNKED ? 16 : kRowsMax, RW = (kTileX + K - 1 + (COMPACT ? 0 : R) + 1) & ~1;   // the images (rows of an even number of positions)
+    static_assert(kRowsMax <= 2 * RH, "two chunks");
     static constexpr int NB = 2 * K - 1;
     static constexpr int kThreads = kWave * WAVES;
-    using XHalo = HaloDma<T, RH, RW, WAVES>;
-    // a block that starts up to 12 columns into the last row reaches 28 positions past the rectangle
-    static constexpr int kXBytes = XHalo::kBytes + 28 * Traits<T>::kKeyBytes;
-    static constexpr int SP = (RW + 3) & ~3;                       // row pitch of the fp32 images (>= RW, 16-byte rows)
-    static_assert(SP >= RW && SP % 4 == 0, "fp32 rows");
-    static constexpr int kSItems = (RH * SP + kWave - 1) / kWave;   // 64-lane loads per fp32 image
-    static_assert(kSItems <= WAVES, "one fp32 load per wave and image");
-    static_assert(!CHUNKED || kSItems * kWave <= RH * SP, "every word of a chunk's fp32 images is a row of the chunk");
-    static constexpr int kSBytes = (kSItems * kWave + 32) * 4;      // + the reach of the last row's blocks
+    // (a row ends 32 bytes behind its last position: the operand reads of four rows and the transposing reads of two then meet every bank once)
+    using XHalo = HaloDma<T, RH, RW, WAVES, 2>;
+    static_assert(RW % 2 == 0, "rows start 8 or 40 banks from each other");
+    // A patch takes its rows four at a time: the last four may reach kOver rows past the images' last (COMPACT: see kv_rows_fit), and the
+    // columns of a patch, which starts in column 12 at most, 28 - RW positions past the last of them
+    static constexpr int kOver = COMPACT ? 2 : 3;
+    static constexpr int kXBytes = (RH + kOver) * XHalo::kRowBytes + (28 - RW) * Traits<T>::kKeyBytes;
+    static_assert(RW <= 28, "columns");
+    static constexpr int kSWords = RH * RW * 2;                             // (lse, delta) per position
+    static constexpr int kSItems = (kSWords + kWave - 1) / kWave;           // 64-lane loads
+    static constexpr int kSPerWave = (kSItems + WAVES - 1) / WAVES;
+    static constexpr int kSBytes = ((RH + kOver) * RW + 28 - RW) * 8;
+    static_assert(kXBytes % 16 == 0 && kSBytes % 16 == 0, "cleared in 16-byte pieces");
     static constexpr int BP = K > 7 ? 28 : 24;                      // row pitch (elements) of a bias copy (a multiple of 4)
     static_assert(NB + 3 + 3 + 3 < BP, "a shifted run of four stays inside its row");
-    static constexpr int kBiasCopy = NB * BP * 2;
-    static constexpr int kBiasBytes = 4 * kBiasCopy;
-    static constexpr int kLdsBytes = 2 * kXBytes + 2 * kSBytes + kBiasBytes;
+    static constexpr int kBiasCopy = (NB + 1) * BP * 2;             // (the last row: -inf)
+    static constexpr int kBiasBytes = 4 * kBiasCopy + 32;           // runs of masked columns go on behind a row
+    static constexpr int kLdsBytes = 2 * kXBytes + kSBytes + kBiasBytes;
     static constexpr int kLdsAlloc = (kLdsBytes + 511) / 512 * 512;
     static constexpr int kWgPerCu = (160 * 1024) / kLdsAlloc < 3 ? (160 * 1024) / kLdsAlloc : 3;
     static_assert(kWgPerCu >= 2, "LDS");
     static constexpr int kWavesPerSimd = kWgPerCu * WAVES / 4;
 };
 
+typedef float f32v2 __attribute__((ext_vector_type(2)));
+typedef uint32_t u32v2 __attribute__((ext_vector_type(2)));
+// two fp16 additions (written out: from a vector addition the compiler makes two, and two registers of what is kept)
+__device__ __forceinline__ f16x2 add_packed(uint32_t a, uint32_t b) {
+    uint32_t r;
+    asm("v_pk_add_f16 %0, %1, %2" : "=v"(r) : "v"(a), "v"(b));
+    return __builtin_bit_cast(f16x2, r);
+}
+// x of lane C of the lane's group of 16, in all of them (a modifier of the instruction that uses it)
+template <int C> __device__ __forceinline__ float column(float x) {
+    return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, x), 0x150 + C, 0xf, 0xf, true));
+}
+
 template <typename T, int K, bool COMPACT>
 __global__ __launch_bounds__(512, (FbwdKvCfg<T, K, COMPACT>::kWavesPerSimd)) void fbwd_kv_kernel(
     const T *__restrict__ q, const T *__restrict__ k, const T *__restrict__ v, const T *__restrict__ rpb, float scale,
-    const float *__restrict__ lse2, const float *__restrict__ delta, const T *__restrict__ dout, T *__restrict__ dk,
+    const float *__restrict__ stat, const T *__restrict__ dout, T *__restrict__ dk,
     T *__restrict__ dv, int H, int W, int heads, int nb, int tiles_y, int units, int splits, GridDecode gd, int half_dim) {
-    // lse2: the log-sum-exp of every query times log2(e), as the query-patch kernel left it beside delta
+    // stat: the log-sum-exp of every query and its delta, as the query-patch kernel left them
     using C = FbwdKvCfg<T, K, COMPACT>;
     using XHalo = typename C::XHalo;
     constexpr float kLog2e = 1.4426950408889634f;
@@ -475,26 +503,23 @@ __global__ __launch_bounds__(512, (FbwdKvCfg<T, K, COMPACT>::kWavesPerSimd)) voi
     const int wave = __builtin_amdgcn_readfirstlane(tid / kWave);
     const int n = lane & 15, g = lane >> 4, ky = n >> 2, kx = n & 3;
     const int lds0 = lds_addr(lds);
-    const int q0 = lds0, d0 = lds0 + C::kXBytes;                           // q and dout of the rectangle
-    const int l0 = d0 + C::kXBytes, e0 = l0 + C::kSBytes, bias0 = e0 + C::kSBytes;   // lse, delta, bias copies
+    const int q0 = lds0, l0 = lds0 + 2 * C::kXBytes, bias0 = l0 + C::kSBytes;   // q and dout of the rectangle; (lse, delta); bias copies
 
     // everything the loads do not write must hold finite numbers (it only ever meets P = 0)
     for (int i = tid * 16; i < C::kLdsBytes - C::kBiasBytes; i += C::kThreads * 16) *lds_ptr<u32x4>(lds0 + i) = u32x4{0u, 0u, 0u, 0u};
-    // bias copies: copy s holds B[u][v] (see bias_to_f16) at element u * BP + (NB-1 - v) + 3 + s, zeros elsewhere
-    for (int i = tid; i < 4 * C::NB * C::BP; i += C::kThreads) {
-        const int s = i / (C::NB * C::BP), rest = i - s * (C::NB * C::BP);
+    // bias copies: copy s holds B[u][v] (see bias_to_f16) at element u * BP + (NB-1 - v) + 3 + s, zeros elsewhere, -inf in row NB
+    for (int i = tid; i < C::kBiasBytes / 2; i += C::kThreads) {
+        const int s = i / ((C::NB + 1) * C::BP), rest = i - s * ((C::NB + 1) * C::BP);
         const int u = rest / C::BP, col = rest - u * C::BP;
         const int vv = C::NB - 1 - (col - 3 - s);
-        f16_t val = (f16_t)0.f;
-        if (rpb != nullptr && (unsigned)vv < (unsigned)C::NB) val = bias_to_f16(rpb[((size_t)head * C::NB + u) * C::NB + vv]);
+        f16_t val = u == C::NB ? (f16_t)-INFINITY : (f16_t)0.f;
+        if (rpb != nullptr && s < 4 && u < C::NB && (unsigned)vv < (unsigned)C::NB) val = bias_to_f16(rpb[((size_t)head * C::NB + u) * C::NB + vv]);
         *lds_ptr<f16_t>(bias0 + i * 2) = val;
     }
 
     const int ty0 = work.ty * C::TY, tx0 = work.tx * kTileX;
-    const int tx1 = tx0 + kTileX - 1 < W - 1 ? tx0 + kTileX - 1 : W - 1;
     const int ty1 = ty0 + C::TY - 1 < H - 1 ? ty0 + C::TY - 1 : H - 1;
-    const int ry0 = inv_first(ty0, H, K);   // the rectangle (fits kRowsMax x RW: checked by the host)
-    const int rx0 = inv_first(tx0, W, K), rx1 = inv_last(tx1, W, K);
+    const int ry0 = inv_first(ty0, H, K), rx0 = inv_first(tx0, W, K);   // the rectangle (fits kRowsMax x RW: checked by the host)
     const int nrows = inv_last(ty1, H, K) - ry0 + 1;
     const int nch = C::CHUNKED && nrows > C::RH ? 2 : 1;   // chunks of the rectangle
     const int org1 = nrows - C::RH;                        // first rectangle row of the second chunk
@@ -506,14 +531,15 @@ __global__ __launch_bounds__(512, (FbwdKvCfg<T, K, COMPACT>::kWavesPerSimd)) voi
     // (half_dim: 16-channel heads; see kHalfDimChunks)
     const int pitch = half_dim ? KB / 2 : KB, chunk_mask = half_dim ? kHalfDimChunks : 3;
     xhalo.offsets(H, W, ry0, rx0, xoff, pitch, chunk_mask);
-    int soff;   // this lane's word of the fp32 images (waves 0 .. kSItems-1), clamped into the map
-    {
-        const int i = wave * kWave + lane;
-        const int rr = i / C::SP, cc = i - rr * C::SP;
+    int soff[C::kSPerWave];   // this lane's words of the pairs, clamped into the map (-1: nothing)
+#pragma unroll
+    for (int i = 0; i < C::kSPerWave; ++i) {
+        const int w = (wave + i * C::WAVES) * kWave + lane, pos = w >> 1;
+        const int rr = pos / C::RW, cc = pos - rr * C::RW;
         int y = ry0 + rr, x = rx0 + cc;
         y = y < H - 1 ? y : H - 1;
         x = x < W - 1 ? x : W - 1;
-        soff = (y * W + x) * 4;
+        soff[i] = w < C::kSWords ? (y * W + x) * 8 + (w & 1) * 4 : -1;
     }
 
     const int strip = wave >> 2, p = patch_of_wave(wave);
@@ -521,48 +547,46 @@ __global__ __launch_bounds__(512, (FbwdKvCfg<T, K, COMPACT>::kWavesPerSimd)) voi
     const bool active = sy0 < H && px0 < W;
     const int jy = sy0 + ky, jx = px0 + kx;                // this lane's key
     const bool key_ok = jy < H && jx < W;
+    const int cy = jy < H ? jy : H - 1, cx = jx < W ? jx : W - 1;
     const int oqy = inv_first(sy0 < H ? sy0 : H - 1, H, K), oqx = inv_first(px0 < W ? px0 : W - 1, W, K);
-    const int sy3 = sy0 + 3 < H - 1 ? sy0 + 3 : H - 1;
-    const int nblk = active ? inv_last(sy3, H, K) - oqy + 1 : 0;   // rows of the rectangle that see the patch (<= RH)
+    const int sy3 = sy0 + 3 < H - 1 ? sy0 + 3 : H - 1, px3 = px0 + 3 < W - 1 ? px0 + 3 : W - 1;
+    const int nrow = active ? inv_last(sy3, H, K) - oqy + 1 : 0;         // rows and blocks of columns that see the patch
+    const int ncol = active ? (inv_last(px3, W, K) - oqx + 4) >> 2 : 0;
     const int row0 = oqy - ry0, col0 = oqx - rx0;
-    // lane-constant address parts inside a rectangle row
-    const int arow = (col0 + n) * KB + g * 16;                       // A operand row: position col0 + n, bytes [16g, 16g+16)
-    const int atr = (col0 + 4 * g + (n >> 2)) * KB + (n & 3) * 16;   // transposing read (channels dealt as in part 1)
-    const int sidx = (col0 + 4 * g) * 4;                             // fp32 images: positions col0 + 4g .. + 3
-    // which of the lane's (position, key) pairs meet: the key must lie in the window of the query
-    unsigned rowok = 0, colok = 0;
+    // lane-constant address parts inside four rows of the rectangle
+    const int arow = q0 + (n >> 2) * XHalo::kRowBytes + (col0 + (n & 3)) * KB + g * 16;   // A operand: query n of a block, bytes [16g, 16g+16)
+    const int atr = q0 + g * XHalo::kRowBytes + (col0 + (n >> 2)) * KB + (n & 3) * 8;     // transposing read: half hf holds channels 16 hf .. 16 hf + 15
+    const int srow = l0 + (g * C::RW + col0 + n) * 8;                                     // pair of column n of row g
+    // which queries see the lane's key: y_count rows (none for a lane without a key), counted so that a block's first row is the lane's row g - y_first ...
+    const int key_first = inv_first(cy, H, K), y_first = key_first - oqy - g, y_count = key_ok ? inv_last(cy, H, K) - key_first + 1 : 0;
+    // ... and columns, as what is added to the bias of two of them
+    const int x_first = inv_first(cx, W, K) - oqx, x_count = inv_last(cx, W, K) - oqx + 1 - x_first;
+    auto mask_of = [&](int c) {
+        return ((unsigned)(c - x_first) < (unsigned)x_count ? 0u : 0xfc00u) | ((unsigned)(c + 1 - x_first) < (unsigned)x_count ? 0u : 0xfc000000u);
+    };
+    uint32_t colmask[4][2];
 #pragma unroll
-    for (int b = 0; b < C::kRowsMax; ++b) {
-        const int iy = oqy + b;
-        const bool ok = b < nblk && key_ok && (unsigned)(jy - win_start(iy < H ? iy : H - 1, H, K)) < (unsigned)K;
-        rowok |= ok ? (1u << b) : 0u;
-    }
-#pragma unroll
-    for (int r = 0; r < 4; ++r) {
-        const int ix = oqx + 4 * g + r;
-        const bool ok = ix <= rx1 && key_ok && (unsigned)(jx - win_start(ix < W ? ix : W - 1, W, K)) < (unsigned)K;
-        colok |= ok ? (1u << r) : 0u;
-    }
-    float colmask[4];
-#pragma unroll
-    for (int r = 0; r < 4; ++r) colmask[r] = ((colok >> r) & 1u) ? 0.f : -INFINITY;
-    // bias: row u = jy - iy + K-1 of the table, mirrored columns NB-1 - (jx - ix + K-1) = vm0 + r
-    const int ub = jy - oqy + K - 1;
-    int vm0 = C::NB - 1 - (jx - (oqx + 4 * g) + K - 1);
-    vm0 = vm0 < -3 ? -3 : (vm0 > C::NB - 1 ? C::NB - 1 : vm0);   // outside the table only where nothing meets
+    for (int c = 0; c < 16; c += 2) colmask[c >> 2][(c >> 1) & 1] = mask_of(c);
+    // bias: row u = jy - iy + K-1 of the table, mirrored columns NB-1 - (jx - ix + K-1) = vm0 + c
+    int vm0 = K - 1 - (cx - oqx);
+    vm0 = vm0 < -3 ? -3 : vm0;   // (outside the table only where nothing meets)
     const int shift = (-(vm0 + 3)) & 3;
-    const int cbase = bias0 + shift * C::kBiasCopy + (vm0 + 3 + shift) * 2;   // 8-byte aligned
+    // of the first row that sees the key; the rows that follow lie in front of it (8-byte aligned)
+    const int cbase = bias0 + shift * C::kBiasCopy + (vm0 + 3 + shift) * 2 + (cy - key_first + K - 1) * (C::BP * 2);
+    const int no_row = bias0 + C::NB * (C::BP * 2);
 
     const size_t plane_px = (size_t)H * W;
+    const unsigned key_off = (unsigned)((cy * W + cx) * pitch);   // (a plane is smaller than 2^31 bytes)
     workgroup_sync();
 
     for (int b = b_begin; b < b_end; ++b) {
         const size_t plane = (size_t)b * heads + head;
         // the lane's key and value: bytes [16g, 16g+16) (B operands)
-        const size_t koff = (plane * plane_px + (size_t)(jy < H ? jy : H - 1) * W + (jx < W ? jx : W - 1)) * pitch + (g & chunk_mask) * 16;
+        const size_t plane_off = plane * plane_px * pitch;
+        const unsigned koff = key_off + (g & chunk_mask) * 16;
         const bool upper = half_dim && g >= 2;   // lanes whose channels a 16-channel head does not have
-        const u32x4 kload = *reinterpret_cast<const u32x4 *>(reinterpret_cast<const char *>(k) + koff);
-        const u32x4 vload = *reinterpret_cast<const u32x4 *>(reinterpret_cast<const char *>(v) + koff);
+        const u32x4 kload = *reinterpret_cast<const u32x4 *>(reinterpret_cast<const char *>(k) + plane_off + koff);
+        const u32x4 vload = *reinterpret_cast<const u32x4 *>(reinterpret_cast<const char *>(v) + plane_off + koff);
         const u32x4 kreg = upper ? u32x4{0u, 0u, 0u, 0u} : kload, vreg = upper ? u32x4{0u, 0u, 0u, 0u} : vload;
         f32x4 ak[2] = {f32x4{0.f, 0.f, 0.f, 0.f}, f32x4{0.f, 0.f, 0.f, 0.f}};   // dk^T, dv^T: channels 8g + 4 hf + r of the lane's key
         f32x4 av[2] = {f32x4{0.f, 0.f, 0.f, 0.f}, f32x4{0.f, 0.f, 0.f, 0.f}};
@@ -576,73 +600,93 @@ __global__ __launch_bounds__(512, (FbwdKvCfg<T, K, COMPACT>::kWavesPerSimd)) voi
 #pragma unroll
             for (int i = 0; i < XHalo::PER_WAVE; ++i) xo[i] = xoff[i] >= 0 ? xoff[i] + org * W * pitch : -1;
             XHalo::issue_at(reinterpret_cast<const char *>(q) + plane * plane_px * pitch, xo, q0, wave);
-            XHalo::issue_at(reinterpret_cast<const char *>(dout) + plane * plane_px * pitch, xo, d0, wave);
+            XHalo::issue_at(reinterpret_cast<const char *>(dout) + plane * plane_px * pitch, xo, q0 + C::kXBytes, wave);
         }
-        if (wave < C::kSItems) {
-            global_to_lds_4(reinterpret_cast<const char *>(lse2) + plane * plane_px * 4, (unsigned)(soff + org * W * 4), l0 + wave * kWave * 4);
-            global_to_lds_4(reinterpret_cast<const char *>(delta) + plane * plane_px * 4, (unsigned)(soff + org * W * 4), e0 + wave * kWave * 4);
-        }
+#pragma unroll
+        for (int i = 0; i < C::kSPerWave; ++i)
+            if (soff[i] >= 0)
+                global_to_lds_4(reinterpret_cast<const char *>(stat) + plane * plane_px * 8, (unsigned)(soff[i] + org * W * 8), l0 + (wave + i * C::WAVES) * kWave * 4);
         wait_global_loads();
         workgroup_sync();
         if (!active) continue;
 
-        // this chunk's part of the rows that see the patch: rectangle rows below RH in the first chunk, the others in
-        // the second
-        const int blk_lo = c ? (C::RH - row0 > 0 ? C::RH - row0 : 0) : 0;
-        const int blk_hi = (nch == 2 && c == 0) ? (nblk < C::RH - row0 ? nblk : C::RH - row0) : nblk;
-        for (int blk = blk_lo; blk < blk_hi; ++blk) {
-            const int xr = (row0 + blk - org) * C::RW * KB;   // this row inside the q / dout images
-            const int sr = (row0 + blk - org) * C::SP * 4;    // ... inside the fp32 images
-            const u32x4 aq = *lds_ptr<u32x4>(q0 + xr + arow);
-            const u32x4 ad = *lds_ptr<u32x4>(d0 + xr + arow);
-            struct __attribute__((packed, aligned(4))) F4 {
-                f32x4 v;
-            };
-            const f32x4 l4 = lds_ptr<F4>(l0 + sr + sidx)->v;
-            const f32x4 e4 = lds_ptr<F4>(e0 + sr + sidx)->v;
-            int u = ub - blk;
-            u = u < 0 ? 0 : (u > C::NB - 1 ? C::NB - 1 : u);
-            typedef uint32_t u32v2 __attribute__((ext_vector_type(2)));
-            const u32v2 b4 = *lds_ptr<u32v2>(cbase + u * C::BP * 2);
+        // the block of columns 4 CB .. 4 CB + 3 of four rows (offset of their first in the images; the lane's row of the bias table; the pair of column n)
+        auto block = [&](auto cb, int pos, int brow, const f32v2 &st) {
+            constexpr int CB = decltype(cb)::value;
+            const int ra = arow + pos + CB * 4 * KB, rt = atr + pos + CB * 4 * KB;
+            const u32x4 aq = *lds_ptr<u32x4>(ra), ad = *lds_ptr<u32x4>(ra + C::kXBytes);
+            const u32v2 b4 = *lds_ptr<u32v2>(brow + CB * 8);
             const f32x4 sacc = mfma_16x16x32<T>(aq, kreg, f32x4{0.f, 0.f, 0.f, 0.f});
             const f32x4 pacc = mfma_16x16x32<T>(ad, vreg, f32x4{0.f, 0.f, 0.f, 0.f});
-            // the window test as an additive mask (0 inside, -inf outside: the weight becomes exactly 0), so that the
-            // block stays free of branches
-            const float rowmask = ((rowok >> blk) & 1u) ? 0.f : -INFINITY;
             float pw[4], ds[4];
+            auto two = [&](auto half) {
+                constexpr int h = decltype(half)::value, c = 4 * CB + 2 * h;   // columns c, c + 1
+                const f16x2 bias = add_packed(h ? b4.y : b4.x, colmask[CB][h]);   // -inf outside the window
+                pw[2 * h] = __builtin_amdgcn_exp2f((__builtin_fmaf(scale, sacc[2 * h], (float)bias[0]) - column<c>(st.x)) * kLog2e);
+                pw[2 * h + 1] = __builtin_amdgcn_exp2f((__builtin_fmaf(scale, sacc[2 * h + 1], (float)bias[1]) - column<c + 1>(st.x)) * kLog2e);
+                ds[2 * h] = pw[2 * h] * (pacc[2 * h] - column<c>(st.y));
+                ds[2 * h + 1] = pw[2 * h + 1] * (pacc[2 * h + 1] - column<c + 1>(st.y));
+            };
+            two(IntC<0>{});
+            two(IntC<1>{});
+            if constexpr (Traits<T>::kDtype == NA2D_BF16) __builtin_amdgcn_sched_barrier(0);   // (one sum after the other: the registers)
+            auto sum = [&](f32x4 (&acc)[2], const float (&w)[4], int at) {
+                const u32x2 t[2] = {lds_read_tr16(at), lds_read_tr16(at + 32)};
+                const uint32_t w0 = pack2_t<T>(w[0], w[1]), w1 = pack2_t<T>(w[2], w[3]);
 #pragma unroll
-            for (int r = 0; r < 4; ++r) {
-                const uint32_t two = r < 2 ? b4.x : b4.y;
-                const float bias = (float)__builtin_bit_cast(f16_t, (uint16_t)((r & 1) ? two >> 16 : two & 0xffffu));
-                const float lg = __builtin_fmaf(scale, sacc[r], bias + (colmask[r] + rowmask));   // the logit, -inf outside the window
-                pw[r] = __builtin_amdgcn_exp2f(__builtin_fmaf(lg, kLog2e, -l4[r]));
-                ds[r] = pw[r] * (pacc[r] - e4[r]);
-            }
-            const uint32_t p0 = pack2_t<T>(pw[0], pw[1]), p1 = pack2_t<T>(pw[2], pw[3]);
-            const uint32_t s0 = pack2_t<T>(ds[0], ds[1]), s1 = pack2_t<T>(ds[2], ds[3]);
-#pragma unroll
-            for (int hf = 0; hf < 2; ++hf) {
-                const u32x2 td = lds_read_tr16(d0 + xr + atr + hf * 8);
-                const u32x2 tq = lds_read_tr16(q0 + xr + atr + hf * 8);
-                av[hf] = mfma_16x16x16<T>(td.x, td.y, p0, p1, av[hf]);
-                ak[hf] = mfma_16x16x16<T>(tq.x, tq.y, s0, s1, ak[hf]);
+                for (int hf = 0; hf < 2; ++hf) acc[hf] = mfma_16x16x16<T>(t[hf].x, t[hf].y, w0, w1, acc[hf]);
                 if constexpr (Traits<T>::kDtype == NA2D_BF16) {
                     // bf16 keeps 8 significant bits: second operands carry the rounding remainders of P and dS
-                    auto rem = [](float x) { return x - to_f32(from_f32<T>(x)); };
-                    av[hf] = mfma_16x16x16<T>(td.x, td.y, pack2_t<T>(rem(pw[0]), rem(pw[1])), pack2_t<T>(rem(pw[2]), rem(pw[3])), av[hf]);
-                    ak[hf] = mfma_16x16x16<T>(tq.x, tq.y, pack2_t<T>(rem(ds[0]), rem(ds[1])), pack2_t<T>(rem(ds[2]), rem(ds[3])), ak[hf]);
+                    const uint32_t l0 = pack_remainders(w0, w[0], w[1]), l1 = pack_remainders(w1, w[2], w[3]);
+#pragma unroll
+                    for (int hf = 0; hf < 2; ++hf) acc[hf] = mfma_16x16x16<T>(t[hf].x, t[hf].y, l0, l1, acc[hf]);
+                    __builtin_amdgcn_sched_barrier(0);
                 }
-            }
+            };
+            sum(av, pw, rt + C::kXBytes);
+            sum(ak, ds, rt);
+        };
+        // this chunk's part of the rows that see the patch: rectangle rows below RH in the first chunk, the others in
+        // the second
+        const int lo = c ? (C::RH - row0 > 0 ? C::RH - row0 : 0) : 0;
+        const int hi = (nch == 2 && c == 0) ? (nrow < C::RH - row0 ? nrow : C::RH - row0) : nrow;
+        int count = y_count;
+        if constexpr (C::CHUNKED) {   // (rows of the second chunk stay away from the first: there are none of them in its images)
+            const int left = hi - (y_first + g);
+            count = key_ok && left < count ? left : count;
         }
+        auto rows = [&](auto cols) {   // (a loop for each number of block columns: the accumulators stay where they are)
+            constexpr int COLS = decltype(cols)::value;
+            if (C::CHUNKED && lo >= hi) return;   // (a patch that is in the map is seen by at least one row)
+            int row = lo;
+            do {
+                const int in = row - y_first;   // the lane's row of the block, counted from the first that sees the key
+                const int brow = (unsigned)in < (unsigned)count ? __mul24(in, -(C::BP * 2)) + cbase : no_row;
+                int at = row0 + row - org;
+                asm volatile("" : "+s"(at));   // (no second set of addresses that runs along)
+                const f32v2 st = *lds_ptr<f32v2>(srow + at * (C::RW * 8));
+                block(IntC<0>{}, at * XHalo::kRowBytes, brow, st);
+                block(IntC<1>{}, at * XHalo::kRowBytes, brow, st);
+                if constexpr (COLS > 2) block(IntC<2>{}, at * XHalo::kRowBytes, brow, st);
+                if constexpr (COLS > 3) block(IntC<3>{}, at * XHalo::kRowBytes, brow, st);
+                row += 4;
+            } while (row < hi);
+        };
+        if (ncol <= 2) rows(IntC<2>{});   // (one: the second is masked)
+        else if (ncol == 3) rows(IntC<3>{});
+        else rows(IntC<4>{});
         }   // chunks
-        if (key_ok && !upper) {
-            const size_t o = (plane * plane_px + (size_t)jy * W + jx) * pitch + g * 16;
-            store16_stream(reinterpret_cast<char *>(dk) + o,
-                           u32x4{pack2_t<T>(ak[0][0] * scale, ak[0][1] * scale), pack2_t<T>(ak[0][2] * scale, ak[0][3] * scale),
-                                 pack2_t<T>(ak[1][0] * scale, ak[1][1] * scale), pack2_t<T>(ak[1][2] * scale, ak[1][3] * scale)});
-            store16_stream(reinterpret_cast<char *>(dv) + o,
-                           u32x4{pack2_t<T>(av[0][0], av[0][1]), pack2_t<T>(av[0][2], av[0][3]), pack2_t<T>(av[1][0], av[1][1]),
-                                 pack2_t<T>(av[1][2], av[1][3])});
+        settle_products<2>(ak);
+        settle_products<2>(av);
+        if (key_ok) {
+            const unsigned o = key_off + g * 8;
+            // channels 4g .. 4g + 3 of either half
+#pragma unroll
+            for (int hf = 0; hf < 2; ++hf) {
+                if (half_dim && hf) continue;
+                *reinterpret_cast<u32v2 *>(reinterpret_cast<char *>(dk) + plane_off + o + hf * 32) = u32v2{pack2_t<T>(ak[hf][0] * scale, ak[hf][1] * scale), pack2_t<T>(ak[hf][2] * scale, ak[hf][3] * scale)};
+                *reinterpret_cast<u32v2 *>(reinterpret_cast<char *>(dv) + plane_off + o + hf * 32) = u32v2{pack2_t<T>(av[hf][0], av[hf][1]), pack2_t<T>(av[hf][2], av[hf][3])};
+            }
         }
     }
 }
@@ -661,9 +705,18 @@ static bool kv_rect_fits(const Problem &p, int rows, int cols) {
     return true;
 }
 
+// Do the rows of every patch, taken in fours, end within two rows of the `rows` that its tile's rectangle has at most?
+static bool kv_rows_fit(const Problem &p, int rows) {
+    for (int sy = 0; sy < p.H; sy += 4) {
+        const int first = inv_first(sy, p.H, p.K), last = inv_last(sy + 3 < p.H - 1 ? sy + 3 : p.H - 1, p.H, p.K);
+        if (first - inv_first(sy & ~7, p.H, p.K) + ((last - first + 4) & ~3) > rows + 2) return false;
+    }
+    return true;
+}
+
 template <typename T, int K, bool COMPACT>
 static hipError_t launch_fbwd_kv_c(const Problem &p, const void *q, const void *k, const void *v, const void *rpb,
-                                   float scale, const float *lse, const float *delta, const void *dout, void *dk, void *dv,
+                                   float scale, const float *stat, const void *dout, void *dk, void *dv,
                                    hipStream_t s) {
     using C = FbwdKvCfg<T, K, COMPACT>;
     const int tiles_x = (p.W + kTileX - 1) / kTileX, tiles_y = (p.H + C::TY - 1) / C::TY;
@@ -675,7 +728,7 @@ static hipError_t launch_fbwd_kv_c(const Problem &p, const void *q, const void *
     if (hipError_t e = allow_lds(kern, C::kLdsBytes, allowed); e != hipSuccess) return e;
     hipLaunchKernelGGL(kern, dim3(xcd_padded_grid(units * splits)), dim3(C::kThreads), C::kLdsBytes, s,
                        static_cast<const T *>(q), static_cast<const T *>(k), static_cast<const T *>(v),
-                       static_cast<const T *>(rpb), scale, lse, delta, static_cast<const T *>(dout), static_cast<T *>(dk),
+                       static_cast<const T *>(rpb), scale, stat, static_cast<const T *>(dout), static_cast<T *>(dk),
                        static_cast<T *>(dv), p.H, p.W, p.heads, p.B, tiles_y, units, splits, make_grid_decode(tiles_x, tiles_y, p.heads, p.B, splits),
                        p.D == kHalfDim ? 1 : 0);
     return hipGetLastError();
@@ -683,25 +736,25 @@ static hipError_t launch_fbwd_kv_c(const Problem &p, const void *q, const void *
 
 template <typename T, int K>
 static hipError_t launch_fbwd_kv_t(const Problem &p, const void *q, const void *k, const void *v, const void *rpb,
-                                   float scale, const float *lse, const float *delta, const void *dout, void *dk, void *dv,
+                                   float scale, const float *stat, const void *dout, void *dk, void *dv,
                                    hipStream_t s) {
     if constexpr (K > 7) {   // (chunked images: one size)
-        return launch_fbwd_kv_c<T, K, false>(p, q, k, v, rpb, scale, lse, delta, dout, dk, dv, s);
+        return launch_fbwd_kv_c<T, K, false>(p, q, k, v, rpb, scale, stat, dout, dk, dv, s);
     } else {
-        return kv_rect_fits(p, 8 + K - 1, kTileX + K - 1)
-                   ? launch_fbwd_kv_c<T, K, true>(p, q, k, v, rpb, scale, lse, delta, dout, dk, dv, s)
-                   : launch_fbwd_kv_c<T, K, false>(p, q, k, v, rpb, scale, lse, delta, dout, dk, dv, s);
+        return kv_rect_fits(p, 8 + K - 1, kTileX + K - 1) && kv_rows_fit(p, 8 + K - 1)
+                   ? launch_fbwd_kv_c<T, K, true>(p, q, k, v, rpb, scale, stat, dout, dk, dv, s)
+                   : launch_fbwd_kv_c<T, K, false>(p, q, k, v, rpb, scale, stat, dout, dk, dv, s);
     }
 }
 
 hipError_t launch_fbwd_kv(const Problem &p, const void *q, const void *k, const void *v, const void *rpb, float scale,
-                          const float *lse, const float *delta, const void *dout, void *dk, void *dv, hipStream_t s) {
+                          const float *stat, const void *dout, void *dk, void *dv, hipStream_t s) {
 #define NA2D_FBKV_K(TT)                                                                                   \
     switch (p.K) {                                                                                        \
-        case 3: return launch_fbwd_kv_t<TT, 3>(p, q, k, v, rpb, scale, lse, delta, dout, dk, dv, s);      \
-        case 5: return launch_fbwd_kv_t<TT, 5>(p, q, k, v, rpb, scale, lse, delta, dout, dk, dv, s);      \
-        case 7: return launch_fbwd_kv_t<TT, 7>(p, q, k, v, rpb, scale, lse, delta, dout, dk, dv, s);      \
-        case 9: return launch_fbwd_kv_t<TT, 9>(p, q, k, v, rpb, scale, lse, delta, dout, dk, dv, s);      \
+        case 3: return launch_fbwd_kv_t<TT, 3>(p, q, k, v, rpb, scale, stat, dout, dk, dv, s);      \
+        case 5: return launch_fbwd_kv_t<TT, 5>(p, q, k, v, rpb, scale, stat, dout, dk, dv, s);      \
+        case 7: return launch_fbwd_kv_t<TT, 7>(p, q, k, v, rpb, scale, stat, dout, dk, dv, s);      \
+        case 9: return launch_fbwd_kv_t<TT, 9>(p, q, k, v, rpb, scale, stat, dout, dk, dv, s);      \
         default: return hipErrorInvalidValue;                                                             \
     }
     if (p.dtype == NA2D_F16) { NA2D_FBKV_K(f16_t) }
@@ -735,14 +788,14 @@ AvRpbSplit fused_bwd_split(const Problem &p) {
 }
 
 hipError_t launch_fbwd_q(const Problem &p, const void *q, const void *k, const void *v, const void *rpb, float scale,
-                         const float *lse, const void *dout, void *dq, float *delta, float *lse2, float *rpb_partial,
+                         const float *lse, const void *dout, void *dq, float *stat, float *rpb_partial,
                          hipStream_t s) {
 #define NA2D_FBQ_K(TT)                                                                                             \
     switch (p.K) {                                                                                                 \
-        case 3: return launch_fbwd_q_t<TT, 3>(p, q, k, v, rpb, scale, lse, dout, dq, delta, lse2, rpb_partial, s);       \
-        case 5: return launch_fbwd_q_t<TT, 5>(p, q, k, v, rpb, scale, lse, dout, dq, delta, lse2, rpb_partial, s);       \
-        case 7: return launch_fbwd_q_t<TT, 7>(p, q, k, v, rpb, scale, lse, dout, dq, delta, lse2, rpb_partial, s);       \
-        case 9: return launch_fbwd_q_t<TT, 9>(p, q, k, v, rpb, scale, lse, dout, dq, delta, lse2, rpb_partial, s);       \
+        case 3: return launch_fbwd_q_t<TT, 3>(p, q, k, v, rpb, scale, lse, dout, dq, stat, rpb_partial, s);       \
+        case 5: return launch_fbwd_q_t<TT, 5>(p, q, k, v, rpb, scale, lse, dout, dq, stat, rpb_partial, s);       \
+        case 7: return launch_fbwd_q_t<TT, 7>(p, q, k, v, rpb, scale, lse, dout, dq, stat, rpb_partial, s);       \
+        case 9: return launch_fbwd_q_t<TT, 9>(p, q, k, v, rpb, scale, lse, dout, dq, stat, rpb_partial, s);       \
         default: return hipErrorInvalidValue;                                                                      \
     }
     if (p.dtype == NA2D_F16) { NA2D_FBQ_K(f16_t) }

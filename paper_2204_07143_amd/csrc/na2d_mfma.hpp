@@ -57,6 +57,14 @@ template <int N> __device__ __forceinline__ void settle_products(f32x4 (&x)[N]) 
     if constexpr (N == 8) asm volatile("s_nop 9" : "+v"(x[4]), "+v"(x[5]), "+v"(x[6]), "+v"(x[7]));
 }
 
+// what the bf16 pair `hi` of (a, b) has left of them, as a pair
+__device__ __forceinline__ uint32_t pack_remainders(uint32_t hi, float a, float b) {
+    typedef float f32x2_t __attribute__((ext_vector_type(2)));
+    typedef bf16_t bf16x2_t __attribute__((ext_vector_type(2)));
+    const f32x2_t rest{a - __uint_as_float(hi << 16), b - __uint_as_float(hi & 0xffff0000u)};
+    return __builtin_bit_cast(uint32_t, __builtin_convertvector(rest, bf16x2_t));
+}
+
 // The fused kernels keep the bias B(i, j) of a (query, position) pair as fp16, two per register, beside the
 // -inf that masks positions outside the window, and add it unscaled to the fp32 logit.  An fp16 table entry is
 // kept bit for bit.  A bf16 entry (8 significant bits) converts exactly while it lies inside fp16's range:
@@ -137,11 +145,13 @@ __device__ __forceinline__ void wait_global_loads() { asm volatile("s_waitcnt vm
 // work items (64 chunks each) are dealt round-robin to NWAVES waves.  Positions outside the
 // map are replaced by the nearest one inside it: the kernels give them zero weight, or drop
 // their results, so any finite value serves.
-template <typename T, int ROWS, int COLS, int NWAVES>
+// ROW_PAD: 16-byte chunks behind every row that nothing is loaded into.
+template <typename T, int ROWS, int COLS, int NWAVES, int ROW_PAD = 0>
 struct HaloDma {
     static_assert(sizeof(T) == 2, "64-byte vectors");
     static constexpr int CPK = Traits<T>::kKeyBytes / 16;
-    static constexpr int TOTAL = ROWS * COLS * CPK;
+    static constexpr int kRowChunks = COLS * CPK + ROW_PAD, kRowBytes = kRowChunks * 16;
+    static constexpr int TOTAL = ROWS * kRowChunks;
     static constexpr int NITEM = (TOTAL + kWave - 1) / kWave;
     static constexpr int PER_WAVE = (NITEM + NWAVES - 1) / NWAVES;
     static constexpr int kBytes = TOTAL * 16;
@@ -151,9 +161,9 @@ struct HaloDma {
 #pragma unroll
         for (int i = 0; i < PER_WAVE; ++i) {
             const int q = (wave + i * NWAVES) * kWave + lane;
-            const int pq = q / CPK, c = q % CPK;
-            const int ry = pq / COLS, rx = pq % COLS;
-            pos[i] = q < TOTAL ? (ry | (rx << 8) | (c << 16)) : -1;
+            const int ry = q / kRowChunks, in_row = q % kRowChunks;
+            const int rx = in_row / CPK, c = in_row % CPK;
+            pos[i] = q < TOTAL && rx < COLS ? (ry | (rx << 8) | (c << 16)) : -1;
         }
     }
     // Split form for loops that copy the same rectangle of many planes: the clamped byte offsets of
