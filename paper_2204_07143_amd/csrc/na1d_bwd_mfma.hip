@@ -293,8 +293,15 @@ __host__ __device__ constexpr int key_lds(int nblk, int K) { return key_rows(nbl
 template <typename T, int NBLK>
 __global__ __launch_bounds__(kThreads, (NBLK > 3 ? 3 : 4)) void bwd1d_kv_mfma_kernel(
     const T *__restrict__ q, const T *__restrict__ k, const T *__restrict__ v, const T *__restrict__ rpb, float scale, const float *__restrict__ lse,
-    const float *__restrict__ delta, const T *__restrict__ dout, T *__restrict__ dk, T *__restrict__ dv, int L, int heads, int K, int tiles) {
+    const float *__restrict__ delta, const T *__restrict__ dout, T *__restrict__ dk, T *__restrict__ dv, int L, int heads, int K, int tiles, RpbTables tables,
+    int own_blocks) {
+    // (workgroups from own_blocks on add up the bias gradient's tables)
     extern __shared__ __align__(16) char lds[];
+    if ((int)blockIdx.x >= own_blocks) {
+        static_assert(kThreads == kFinalThreads, "last sum");
+        rpb_final_cell(tables, blockIdx.x - own_blocks, lds_addr(lds));
+        return;
+    }
     const int tid = threadIdx.x, lane = tid % kWave, wave = __builtin_amdgcn_readfirstlane(tid / kWave), j = lane & 15, g = lane >> 4;
     const int plane = blockIdx.x / tiles, t0 = (blockIdx.x - plane * tiles) * kTile, t1 = t0 + kTile - 1 < L - 1 ? t0 + kTile - 1 : L - 1, NB = 2 * K - 1;
     const size_t first = (size_t)plane * L;
@@ -413,7 +420,7 @@ __global__ __launch_bounds__(kThreads, (NBLK > 3 ? 3 : 4)) void bwd1d_kv_mfma_ke
 
 template <typename T, int NBLK>
 hipError_t launch_t(const Problem &p, const void *q, const void *k, const void *v, const void *rpb, float scale, const float *lse, const void *dout,
-                    void *dq, void *dk, void *dv, float *delta, long long *partial, hipStream_t s) {
+                    void *dq, void *dk, void *dv, float *delta, long long *partial, BiasOut d_rpb, hipStream_t s) {
     auto kern_q = bwd1d_q_mfma_kernel<T, NBLK>;
     auto kern_kv = bwd1d_kv_mfma_kernel<T, NBLK>;
     static LdsAllowed allowed_q, allowed_kv;
@@ -424,9 +431,13 @@ hipError_t launch_t(const Problem &p, const void *q, const void *k, const void *
     hipLaunchKernelGGL(kern_q, dim3(p.planes() * tiles), dim3(kThreads), query_lds(NBLK, p.K), s, tq, tk, tv, tr, scale, lse, td, static_cast<T *>(dq), delta, partial,
                        p.L, p.heads, p.K, tiles);
     if (hipError_t e = hipGetLastError(); e != hipSuccess) return e;
-    hipLaunchKernelGGL(kern_kv, dim3(p.planes() * tiles), dim3(kThreads), key_lds(NBLK, p.K), s, tq, tk, tv, tr, scale, lse, delta, td, static_cast<T *>(dk),
-                       static_cast<T *>(dv), p.L, p.heads, p.K, tiles);
-    return hipGetLastError();
+    const int own_blocks = p.planes() * tiles, NB = 2 * p.K - 1, last_sum = d_rpb ? p.heads * NB : 0;
+    const RpbTables tables{partial, d_rpb, p.B, p.heads, tiles, NB};
+    const bool along = launch_holds((long long)own_blocks + last_sum, kThreads);
+    hipLaunchKernelGGL(kern_kv, dim3(own_blocks + (along ? last_sum : 0)), dim3(kThreads), key_lds(NBLK, p.K), s, tq, tk, tv, tr, scale, lse, delta, td, static_cast<T *>(dk),
+                       static_cast<T *>(dv), p.L, p.heads, p.K, tiles, tables, own_blocks);
+    if (hipError_t e = hipGetLastError(); e != hipSuccess || along) return e;
+    return launch_rpb_final(tables, s);
 }
 
 template <typename T, typename... Args> hipError_t launch_blocks(const Problem &p, Args... args) {
@@ -442,9 +453,9 @@ template <typename T, typename... Args> hipError_t launch_blocks(const Problem &
 }  // namespace
 
 hipError_t launch_fused_bwd_16bit(const Problem &p, const void *q, const void *k, const void *v, const void *rpb, float scale, const float *lse, const void *dout,
-                                  void *dq, void *dk, void *dv, float *delta, long long *partial, hipStream_t s) {
-    return p.dtype == NA2D_F16 ? launch_blocks<f16_t>(p, q, k, v, rpb, scale, lse, dout, dq, dk, dv, delta, partial, s)
-                               : launch_blocks<bf16_t>(p, q, k, v, rpb, scale, lse, dout, dq, dk, dv, delta, partial, s);
+                                  void *dq, void *dk, void *dv, float *delta, long long *partial, BiasOut d_rpb, hipStream_t s) {
+    return p.dtype == NA2D_F16 ? launch_blocks<f16_t>(p, q, k, v, rpb, scale, lse, dout, dq, dk, dv, delta, partial, d_rpb, s)
+                               : launch_blocks<bf16_t>(p, q, k, v, rpb, scale, lse, dout, dq, dk, dv, delta, partial, d_rpb, s);
 }
 
 }  // namespace na1d

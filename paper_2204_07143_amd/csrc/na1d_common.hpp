@@ -20,6 +20,38 @@ __device__ __forceinline__ long long to_fixed42(double x) {   // (in range)
     return (long long)(((unsigned long long)(uint32_t)(int)fl << 32) | (uint32_t)((y - fl) * 4294967296.));
 }
 
+// The last sum of the bias gradient: the tables that the workgroups of a (batch, tile) left, added per head and cell (integers: any order).  A
+// workgroup of kFinalThreads per cell, of a kernel of its own or at the end of the grid of the kernel that follows the one that leaves the tables.
+constexpr int kFinalThreads = 256;
+struct RpbTables {
+    const long long *partial;
+    BiasOut d_rpb;
+    int B, heads, tiles, NB;
+};
+hipError_t launch_rpb_final(const RpbTables &p, hipStream_t s);
+__device__ __forceinline__ void rpb_final_cell(const RpbTables &p, int block, int lds) {   // lds: 8 bytes per wave
+    const int h = block / p.NB, u = block - h * p.NB, total = p.B * p.tiles;
+    long long sum = 0;
+    for (int n0 = threadIdx.x; n0 < total; n0 += 4 * kFinalThreads) {
+        long long v[4];
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            const int n = n0 + j * kFinalThreads;
+            v[j] = n < total ? p.partial[(((size_t)(n / p.tiles) * p.heads + h) * p.tiles + n % p.tiles) * p.NB + u] : 0ll;
+        }
+        sum += (v[0] + v[1]) + (v[2] + v[3]);
+    }
+#pragma unroll
+    for (int sh = 1; sh < kWave; sh <<= 1) sum += __shfl_xor(sum, sh, kWave);
+    if ((threadIdx.x & (kWave - 1)) == 0) *lds_ptr<long long>(lds + threadIdx.x / kWave * 8) = sum;
+    workgroup_sync();
+    if (threadIdx.x == 0) {
+        long long tot = 0;
+        for (int w = 0; w < kFinalThreads / kWave; ++w) tot += *lds_ptr<long long>(lds + w * 8);
+        p.d_rpb.store((size_t)h * p.NB + u, (float)((double)tot * (1.0 / 4398046511104.0)));   // 2^-42
+    }
+}
+
 // Where a running maximum starts: not -inf, whose difference to a first logit of -inf (a masked bias cell) would be NaN
 constexpr float kLowest = -3.402823466e38f;
 

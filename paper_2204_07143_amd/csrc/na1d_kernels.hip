@@ -402,33 +402,13 @@ __global__ __launch_bounds__(TQ) void rpb_partial1d_kernel(const T *__restrict__
     for (int u = tid; u < NB; u += TQ) partial[(size_t)blockIdx.x * NB + u] = (long long)tbl[u];
 }
 
-// one workgroup per (head, cell): adds the tables of every (batch, tile) of that head
-constexpr int kFinalThreads = 256;
-__global__ __launch_bounds__(kFinalThreads) void rpb_final1d_kernel(const long long *__restrict__ partial,
-                                                                    BiasOut d_rpb, int B, int heads, int tiles,
-                                                                    int NB) {
+__global__ __launch_bounds__(kFinalThreads) void rpb_final1d_kernel(RpbTables p) {
     __shared__ long long wave_sum[kFinalThreads / kWave];
-    const int h = blockIdx.x / NB, u = blockIdx.x % NB;
-    const int total = B * tiles;
-    long long sum = 0;
-    for (int n0 = threadIdx.x; n0 < total; n0 += 4 * kFinalThreads) {
-        long long v[4];
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            const int n = n0 + j * kFinalThreads;
-            v[j] = n < total ? partial[(((size_t)(n / tiles) * heads + h) * tiles + n % tiles) * NB + u] : 0ll;
-        }
-        sum += (v[0] + v[1]) + (v[2] + v[3]);
-    }
-#pragma unroll
-    for (int sh = 1; sh < kWave; sh <<= 1) sum += __shfl_xor(sum, sh, kWave);
-    if ((threadIdx.x & (kWave - 1)) == 0) wave_sum[threadIdx.x / kWave] = sum;
-    workgroup_sync();
-    if (threadIdx.x == 0) {
-        long long tot = 0;
-        for (int w = 0; w < kFinalThreads / kWave; ++w) tot += wave_sum[w];
-        d_rpb.store((size_t)h * NB + u, (float)((double)tot * (1.0 / 4398046511104.0)));   // 2^-42
-    }
+    rpb_final_cell(p, blockIdx.x, lds_addr(reinterpret_cast<const char *>(wave_sum)));
+}
+hipError_t launch_rpb_final(const RpbTables &p, hipStream_t s) {
+    hipLaunchKernelGGL(rpb_final1d_kernel, dim3(p.heads * p.NB), dim3(kFinalThreads), 0, s, p);
+    return hipGetLastError();
 }
 
 // ---- fused backward ----------------------------------------------------------------------------
@@ -718,8 +698,7 @@ static hipError_t rpb_t(const Problem &p, const void *ds, BiasOut d_rpb, void *w
     hipLaunchKernelGGL(kern, dim3(p.planes() * tiles), dim3(TQ), bytes, s, static_cast<const T *>(ds), partial, p.L, p.K, tiles);
     if (hipError_t e = hipGetLastError(); e != hipSuccess) return e;
     const int NB = 2 * p.K - 1;
-    hipLaunchKernelGGL(rpb_final1d_kernel, dim3(p.heads * NB), dim3(kFinalThreads), 0, s, partial, d_rpb, p.B, p.heads, tiles, NB);
-    return hipGetLastError();
+    return launch_rpb_final(RpbTables{partial, d_rpb, p.B, p.heads, tiles, NB}, s);
 }
 hipError_t launch_rpb_grad(const Problem &p, const void *ds, BiasOut d_rpb, void *workspace, hipStream_t s) {
     NA1D_DISPATCH(p, return (rpb_t<T, TQ>(p, ds, d_rpb, workspace, s)));
@@ -766,7 +745,7 @@ hipError_t launch_fused_bwd(const Problem &p, const void *q, const void *k, cons
     hipError_t e;
     int tiles = tiles_of<256>(p);
     if (p.dtype != NA2D_F32) {
-        e = launch_fused_bwd_16bit(p, q, k, v, rpb, scale, lse, dout, dq, dk, dv, delta, partial, s);
+        return launch_fused_bwd_16bit(p, q, k, v, rpb, scale, lse, dout, dq, dk, dv, delta, partial, d_rpb, s);
     } else if (p.K <= 31) {
         e = fused_bwd_f32<256>(p, f32(q), f32(k), f32(v), f32(rpb), scale, lse, f32(dout), f32_out(dq), f32_out(dk), f32_out(dv), delta, partial, s);
     } else {
@@ -775,8 +754,7 @@ hipError_t launch_fused_bwd(const Problem &p, const void *q, const void *k, cons
     }
     if (e != hipSuccess || !d_rpb) return e;
     const int NB = 2 * p.K - 1;
-    hipLaunchKernelGGL(rpb_final1d_kernel, dim3(p.heads * NB), dim3(kFinalThreads), 0, s, partial, d_rpb, p.B, p.heads, tiles, NB);
-    return hipGetLastError();
+    return launch_rpb_final(RpbTables{partial, d_rpb, p.B, p.heads, tiles, NB}, s);
 }
 
 }  // namespace na1d

@@ -271,9 +271,7 @@ static int fused_bwd(const na2d_problem *p, const void *q, const void *k, const 
         float *partial = d_rpb ? reinterpret_cast<float *>(ws + 2 * fused_bwd_delta_bytes(pr)) : nullptr;
         if (launch_fbwd_q(pr, q, k, v, rpb, scale, lse, dout, dq, stat, partial, s) != hipSuccess)
             return from_hip(hipErrorLaunchFailure);
-        if (launch_fbwd_kv(pr, q, k, v, rpb, scale, stat, dout, dk, dv, s) != hipSuccess)
-            return from_hip(hipErrorLaunchFailure);
-        if (d_rpb && launch_rpb_final_av(pr, partial, d_rpb, fused_bwd_split(pr), s) != hipSuccess)
+        if (launch_fbwd_kv(pr, q, k, v, rpb, scale, stat, dout, dk, dv, partial, d_rpb, s) != hipSuccess)
             return from_hip(hipErrorLaunchFailure);
         return NA2D_OK;
     }

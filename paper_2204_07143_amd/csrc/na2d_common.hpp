@@ -65,6 +65,8 @@ struct BiasOut {
         else static_cast<bf16_t *>(to)[i] = (bf16_t)x;
     }
 };
+// a launch holds less than 2^32 threads
+static inline bool launch_holds(long long blocks, int threads) { return blocks * threads < (1ll << 32); }
 typedef _Float16 f16x2 __attribute__((ext_vector_type(2)));
 typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));

@@ -14,6 +14,7 @@
 // the workspace for the second); the second keeps 4 x 4 key patches (columns of P: dk, dv).
 #include "na2d_kernels.hpp"
 #include "na2d_mfma.hpp"
+#include "na2d_rpb_final.hpp"
 #include "na2d_tile.hpp"
 
 namespace na2d {
@@ -484,15 +485,21 @@ template <typename T, int K, bool COMPACT>
 __global__ __launch_bounds__(512, (FbwdKvCfg<T, K, COMPACT>::kWavesPerSimd)) void fbwd_kv_kernel(
     const T *__restrict__ q, const T *__restrict__ k, const T *__restrict__ v, const T *__restrict__ rpb, float scale,
     const float *__restrict__ stat, const T *__restrict__ dout, T *__restrict__ dk,
-    T *__restrict__ dv, int H, int W, int heads, int nb, int tiles_y, int units, int splits, GridDecode gd, int half_dim) {
+    T *__restrict__ dv, int H, int W, int heads, int nb, int tiles_y, int units, int splits, GridDecode gd, int half_dim, RpbPartials bias_grad, int own_blocks) {
+    // Workgroups from own_blocks on add up the query-patch kernel's partial bias gradients (there are none without a bias gradient).
     // stat: the log-sum-exp of every query and its delta, as the query-patch kernel left them
     using C = FbwdKvCfg<T, K, COMPACT>;
     using XHalo = typename C::XHalo;
     constexpr float kLog2e = 1.4426950408889634f;
     constexpr int KB = Traits<T>::kKeyBytes;
     extern __shared__ __align__(16) char lds[];
+    if ((int)blockIdx.x >= own_blocks) {
+        static_assert(C::kLdsBytes >= kRpbFinalLdsBytes, "LDS");
+        rpb_final_block<C::kThreads>(bias_grad, blockIdx.x - own_blocks, lds_addr(lds));
+        return;
+    }
 
-    const int wg = xcd_contiguous_block(blockIdx.x, gridDim.x);
+    const int wg = xcd_contiguous_block(blockIdx.x, own_blocks);
     if (wg >= units * splits) return;
     const WorkItem work = decode_work(wg, heads, tiles_y, splits, gd);
     const int head = work.head;
@@ -717,7 +724,7 @@ static bool kv_rows_fit(const Problem &p, int rows) {
 template <typename T, int K, bool COMPACT>
 static hipError_t launch_fbwd_kv_c(const Problem &p, const void *q, const void *k, const void *v, const void *rpb,
                                    float scale, const float *stat, const void *dout, void *dk, void *dv,
-                                   hipStream_t s) {
+                                   const RpbPartials &bias_grad, hipStream_t s) {
     using C = FbwdKvCfg<T, K, COMPACT>;
     const int tiles_x = (p.W + kTileX - 1) / kTileX, tiles_y = (p.H + C::TY - 1) / C::TY;
     const int units = tiles_x * tiles_y * p.heads;
@@ -726,35 +733,40 @@ static hipError_t launch_fbwd_kv_c(const Problem &p, const void *q, const void *
     auto kern = fbwd_kv_kernel<T, K, COMPACT>;
     static LdsAllowed allowed;
     if (hipError_t e = allow_lds(kern, C::kLdsBytes, allowed); e != hipSuccess) return e;
-    hipLaunchKernelGGL(kern, dim3(xcd_padded_grid(units * splits)), dim3(C::kThreads), C::kLdsBytes, s,
+    const int own_blocks = xcd_padded_grid(units * splits), last_sum = bias_grad.d_rpb ? p.heads * rpb_final_blocks(C::NB * C::NB) : 0;
+    const bool along = launch_holds((long long)own_blocks + last_sum, C::kThreads);
+    hipLaunchKernelGGL(kern, dim3(own_blocks + (along ? last_sum : 0)), dim3(C::kThreads), C::kLdsBytes, s,
                        static_cast<const T *>(q), static_cast<const T *>(k), static_cast<const T *>(v),
                        static_cast<const T *>(rpb), scale, stat, static_cast<const T *>(dout), static_cast<T *>(dk),
                        static_cast<T *>(dv), p.H, p.W, p.heads, p.B, tiles_y, units, splits, make_grid_decode(tiles_x, tiles_y, p.heads, p.B, splits),
-                       p.D == kHalfDim ? 1 : 0);
-    return hipGetLastError();
+                       p.D == kHalfDim ? 1 : 0, bias_grad, own_blocks);
+    if (hipError_t e = hipGetLastError(); e != hipSuccess || along) return e;
+    return launch_rpb_final_av(p, bias_grad.partial, bias_grad.d_rpb, fused_bwd_split(p), s);
 }
 
 template <typename T, int K>
 static hipError_t launch_fbwd_kv_t(const Problem &p, const void *q, const void *k, const void *v, const void *rpb,
                                    float scale, const float *stat, const void *dout, void *dk, void *dv,
-                                   hipStream_t s) {
+                                   const RpbPartials &bias_grad, hipStream_t s) {
     if constexpr (K > 7) {   // (chunked images: one size)
-        return launch_fbwd_kv_c<T, K, false>(p, q, k, v, rpb, scale, stat, dout, dk, dv, s);
+        return launch_fbwd_kv_c<T, K, false>(p, q, k, v, rpb, scale, stat, dout, dk, dv, bias_grad, s);
     } else {
         return kv_rect_fits(p, 8 + K - 1, kTileX + K - 1) && kv_rows_fit(p, 8 + K - 1)
-                   ? launch_fbwd_kv_c<T, K, true>(p, q, k, v, rpb, scale, stat, dout, dk, dv, s)
-                   : launch_fbwd_kv_c<T, K, false>(p, q, k, v, rpb, scale, stat, dout, dk, dv, s);
+                   ? launch_fbwd_kv_c<T, K, true>(p, q, k, v, rpb, scale, stat, dout, dk, dv, bias_grad, s)
+                   : launch_fbwd_kv_c<T, K, false>(p, q, k, v, rpb, scale, stat, dout, dk, dv, bias_grad, s);
     }
 }
 
 hipError_t launch_fbwd_kv(const Problem &p, const void *q, const void *k, const void *v, const void *rpb, float scale,
-                          const float *stat, const void *dout, void *dk, void *dv, hipStream_t s) {
+                          const float *stat, const void *dout, void *dk, void *dv, const float *rpb_partial, BiasOut d_rpb, hipStream_t s) {
+    const AvRpbSplit sp = fused_bwd_split(p);
+    const RpbPartials bias_grad{rpb_partial, d_rpb, sp.npos * sp.splits, (2 * p.K - 1) * (2 * p.K - 1)};
 #define NA2D_FBKV_K(TT)                                                                                   \
     switch (p.K) {                                                                                        \
-        case 3: return launch_fbwd_kv_t<TT, 3>(p, q, k, v, rpb, scale, stat, dout, dk, dv, s);      \
-        case 5: return launch_fbwd_kv_t<TT, 5>(p, q, k, v, rpb, scale, stat, dout, dk, dv, s);      \
-        case 7: return launch_fbwd_kv_t<TT, 7>(p, q, k, v, rpb, scale, stat, dout, dk, dv, s);      \
-        case 9: return launch_fbwd_kv_t<TT, 9>(p, q, k, v, rpb, scale, stat, dout, dk, dv, s);      \
+        case 3: return launch_fbwd_kv_t<TT, 3>(p, q, k, v, rpb, scale, stat, dout, dk, dv, bias_grad, s);      \
+        case 5: return launch_fbwd_kv_t<TT, 5>(p, q, k, v, rpb, scale, stat, dout, dk, dv, bias_grad, s);      \
+        case 7: return launch_fbwd_kv_t<TT, 7>(p, q, k, v, rpb, scale, stat, dout, dk, dv, bias_grad, s);      \
+        case 9: return launch_fbwd_kv_t<TT, 9>(p, q, k, v, rpb, scale, stat, dout, dk, dv, bias_grad, s);      \
         default: return hipErrorInvalidValue;                                                             \
     }
     if (p.dtype == NA2D_F16) { NA2D_FBKV_K(f16_t) }

@@ -89,12 +89,13 @@ hipError_t launch_rpb_final_av(const Problem &p, const float *partial, BiasOut d
 // fused backward (two kernels): query patches -> dq, delta, partial bias gradients; key patches -> dk, dv
 bool fused_bwd_supported(const Problem &p);
 AvRpbSplit fused_bwd_split(const Problem &p);
-// (stat: lse and delta of every query, side by side; the first writes them for the second)
+// (stat: lse and delta of every query, side by side; the first writes them for the second, which also adds up its
+// partial bias gradients into d_rpb, if there is one)
 hipError_t launch_fbwd_q(const Problem &p, const void *q, const void *k, const void *v, const void *rpb, float scale,
                          const float *lse, const void *dout, void *dq, float *stat, float *rpb_partial,
                          hipStream_t s);
 hipError_t launch_fbwd_kv(const Problem &p, const void *q, const void *k, const void *v, const void *rpb, float scale,
-                          const float *stat, const void *dout, void *dk, void *dv, hipStream_t s);
+                          const float *stat, const void *dout, void *dk, void *dv, const float *rpb_partial, BiasOut d_rpb, hipStream_t s);
 // the backward without k * k tensors of the problems that fused_bwd_supported() does not take (na2d_patch_bwd.hip)
 bool patch_bwd_supported(const Problem &p);
 size_t patch_bwd_workspace_bytes(const Problem &p);

@@ -15,6 +15,7 @@
 //   2. a second kernel adds the partials of each head, four cells per lane: 16 waves each sum
 //      a strided subset in index order, then the 16 sub-sums are added in wave order.
 #include "na2d_kernels.hpp"
+#include "na2d_rpb_final.hpp"
 #include "na2d_common.hpp"
 #include "na2d_tile.hpp"
 
@@ -173,62 +174,13 @@ __global__ __launch_bounds__(256) void rpb_partial_kernel(const T *__restrict__ 
     }
 }
 
-// d_rpb[h, cell] = sum over i < n of partial[h * n + i][cell], rows of `stride` floats (rpb_cell_stride).
-// One workgroup of 16 waves per head and 64 cells: sixteen lanes own four neighbouring cells each (one 16-byte load per
-// partial); the 64 groups of sixteen lanes take the partials in turn, eight loads in flight, and their sub-sums are added in group
-// order.  (With 256 cells to a workgroup few compute units work: 2 heads of 1024 partials of 625 cells took 8 us, 2048 13.6.)
-struct __attribute__((packed, aligned(4))) RpbQuad {
-    f32x4 v;
-};
-constexpr int kRpbFinalLanes = 16, kRpbFinalGroups = kRpbFinalWaves * kWave / kRpbFinalLanes;
-__global__ __launch_bounds__(kRpbFinalWaves *kWave) void rpb_final_kernel(const float *__restrict__ partial,
-                                                                           BiasOut d_rpb, int n, int cells,
-                                                                           int stride) {
-    __shared__ f32x4 sub[kRpbFinalGroups][kRpbFinalLanes];
-    const int quad_blocks = (stride / 4 + kRpbFinalLanes - 1) / kRpbFinalLanes;
-    const int h = blockIdx.x / quad_blocks;
-    const int group = threadIdx.x / kRpbFinalLanes, lane = threadIdx.x % kRpbFinalLanes;
-    const int cell0 = ((blockIdx.x % quad_blocks) * kRpbFinalLanes + lane) * 4;   // this lane's first cell
-    f32x4 acc = f32x4{0.f, 0.f, 0.f, 0.f};
-    if (cell0 < stride) {
-        const float *base = partial + (size_t)h * n * stride + cell0;
-        constexpr int U = 8;   // loads in flight per lane; past the end they are skipped (adding 0 changes nothing)
-        for (int i = group; i < n; i += U * kRpbFinalGroups) {
-            f32x4 v[U];
-#pragma unroll
-            for (int u = 0; u < U; ++u) {
-                const int iu = i + u * kRpbFinalGroups;
-                v[u] = iu < n ? reinterpret_cast<const RpbQuad *>(base + (size_t)iu * stride)->v : f32x4{0.f, 0.f, 0.f, 0.f};
-            }
-#pragma unroll
-            for (int u = 0; u < U; ++u) acc += v[u];
-        }
-    }
-    sub[group][lane] = acc;
-    workgroup_sync();
-    // four lanes of the first waves per cell quad: sixteen sub-sums each, then the four
-    if (threadIdx.x < 4 * kRpbFinalLanes) {
-        const int part = threadIdx.x / kRpbFinalLanes;
-        f32x4 s = sub[part * 16][lane];
-        for (int w = 1; w < 16; ++w) s += sub[part * 16 + w][lane];
-        f32x4 t;
-#pragma unroll
-        for (int c = 0; c < 4; ++c) {
-            const float a = s[c] + __shfl_xor(s[c], 16);
-            t[c] = a + __shfl_xor(a, 32);
-        }
-        if (part == 0 && cell0 < cells) {
-#pragma unroll
-            for (int c = 0; c < 4; ++c)
-                if (cell0 + c < cells) d_rpb.store((size_t)h * cells + cell0 + c, t[c]);
-        }
-    }
+__global__ __launch_bounds__(kRpbFinalWaves *kWave) void rpb_final_kernel(const float *__restrict__ partial, BiasOut d_rpb, int n, int cells) {
+    __shared__ f32x4 sub[kRpbFinalGroups * kRpbFinalLanes];
+    rpb_final_block<kRpbFinalWaves * kWave>(RpbPartials{partial, d_rpb, n, cells}, blockIdx.x, lds_addr(reinterpret_cast<const char *>(sub)));
 }
 
 static hipError_t launch_rpb_final(const float *partial, BiasOut d_rpb, int heads, int n, int cells, hipStream_t s) {
-    const int stride = rpb_cell_stride(cells);
-    hipLaunchKernelGGL(rpb_final_kernel, dim3(heads * ((stride / 4 + kRpbFinalLanes - 1) / kRpbFinalLanes)), dim3(kRpbFinalWaves * kWave), 0, s,
-                       partial, d_rpb, n, cells, stride);
+    hipLaunchKernelGGL(rpb_final_kernel, dim3(heads * rpb_final_blocks(cells)), dim3(kRpbFinalWaves * kWave), 0, s, partial, d_rpb, n, cells);
     return hipGetLastError();
 }
 
