@@ -315,17 +315,18 @@ struct PatchShape {
     int with_bias, with_dbias;
     GridDecode gd;
     FastDiv by_pitch;
+    int two;               // backward in 16 bit: part 2 takes two patches to a wave (and what part 1 leaves for it)
 };
 
 // Host: positions per image row for tiles of `tw` columns on a map of `W`: what the widest tile's patches reach from the image's first
 // column, in whole pieces.  `first` and `last`: the first and the last position of the streamed operand that a position of the kept one
-// meets.  Tiles clear of both borders are alike: of those one is enough.
-template <typename First, typename Last> inline int image_row(int W, int K, int tw, int posb, First first, Last last) {
+// meets; a wave's patches are `step` columns wide.  Tiles clear of both borders are alike: of those one is enough.
+template <typename First, typename Last> inline int image_row(int W, int K, int tw, int posb, First first, Last last, int step = 4) {
     int rw = 0;
     const int border = 2 * K + 2 * tw, skip_to = (W - border) / tw * tw;   // (at least a tile of the middle is looked at)
-    for (int px = 0; px < W; px += 4) {
+    for (int px = 0; px < W; px += step) {
         if (px >= border + tw && px < skip_to) px = skip_to;
-        const int px3 = px + 3 < W - 1 ? px + 3 : W - 1, o = first(px);
+        const int px3 = px + step - 1 < W - 1 ? px + step - 1 : W - 1, o = first(px);
         const int e = o - first(px / tw * tw) + ((last(px3) - o + 4) & ~3);
         rw = rw > e ? rw : e;
     }

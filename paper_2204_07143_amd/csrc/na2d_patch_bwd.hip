@@ -19,10 +19,10 @@
 // A masked product is 0 * x: where x is not finite it would spoil positions whose window does not hold it, so results that are not
 // finite are computed once more from their own window only.
 // Measured (us, both parts and the bias gradient, in brackets the steps before: weights recomputed into memory and the unfused backward):
-// 64 x 2 x 56 x 56 queries, fp16, 32 channels, k = 13 82 + 147 + 6 (455); fp32, k = 7 196 + 217 + 6 (700); fp16, 64 channels (one head), k = 7 48 + 65 + 9
+// 64 x 2 x 56 x 56 queries, fp16, 32 channels, k = 13 82 + 118 + 4 (455); fp32, k = 7 196 + 217 + 6 (700); fp16, 64 channels (one head), k = 7 48 + 65 + 9
 // (165); 4 x 2 x 64 x 64, bf16, k = 21 18 + 40 + 4 (220).  By counters at the first shape part 1 issues 60 vector instructions per
 // 16 x 16 products, of which a block needs 40, and waits 43 % of its wave cycles: its four waves per SIMD do not cover the chain from LDS through
-// two products, the exponential and two more.  Part 2 adds the integer additions in LDS (43 us with a bias, 4 copies of the table).  fp32 is
+// two products, the exponential and two more.  Part 2 adds the integer additions in LDS.  fp32 is
 // nearer to its matrix cores: 32 instructions of 32 cycles per block, 94 us a part.
 #include <limits.h>
 
@@ -36,6 +36,9 @@ namespace {
 // What part 1 leaves of a query for part 2: the base of its exponents and delta.  In 16 bit the base is log2(e) lse.  In fp32 it is 0
 // (log2(e) lse rounded to a whole number where that is beyond +-32), and the inverse of the sum of the exponentials to that base
 // follows (and a word of padding): P = exp2(t - base) / sum has neither the rounding of lse nor that of the difference in it.
+// For the kernel with two patches to a wave (PatchShape::two): what its products start from, -lse / scale of all of a plane's queries, then
+// -delta of all of them, so that exp2(scale2 (s + start) + bias) and dP need no further subtraction and four neighbours lie in a row.  The others read
+// pairs: they are 2 to 4 % slower with the starts.
 template <typename T> constexpr bool kNormalised = sizeof(T) == 4;
 template <typename T> constexpr int kQueryWords = kNormalised<T> ? 4 : 2;
 
@@ -126,6 +129,12 @@ __device__ __forceinline__ float query_once_more(const PlanePtrs<T, D> &m, const
     return delta;
 }
 
+// scale2 of the kernel with two patches to a wave.  (A scale of 0 counts as 2^-100: what it adds to an exponent is 0 to fp32 for any |s| < 2^70.)
+__device__ __forceinline__ float product_scale(float scale) {
+    const float x = scale * kLog2e;
+    return fabsf(x) < 0x1p-100f ? __builtin_copysignf(0x1p-100f, x) : x;
+}
+
 // dk and dv of one key from the queries that see it, likewise.
 template <typename T, int D>
 __device__ __forceinline__ void key_once_more(const PlanePtrs<T, D> &m, const PatchShape &g, float scale, int y, int x, const float *ld, T *dk, T *dv) {
@@ -136,11 +145,12 @@ __device__ __forceinline__ void key_once_more(const PlanePtrs<T, D> &m, const Pa
     RasterWalk at;
     for (int first = 0; first < total; first += kWave) {
         const int s = first + lane < total ? first + lane : total - 1, iy = y0 + s / nx, ix = x0 + s % nx;
-        const float *of = ld + kQueryWords<T> * ((size_t)iy * g.W + ix);
+        const size_t i_query = (size_t)iy * g.W + ix, plane_px = (size_t)g.H * g.W;
+        const float *of = ld + (g.two ? 1 : kQueryWords<T>) * i_query;
         float p, dp;
-        pair_weight(m, g, scale, iy, ix, y, x, of[0], p, dp);
+        pair_weight(m, g, scale, iy, ix, y, x, g.two ? of[0] * -product_scale(scale) : of[0], p, dp);
         if constexpr (kNormalised<T>) p *= of[2];
-        const float delta = of[1];
+        const float delta = g.two ? -of[plane_px] : of[1];
         const float ds = p * (dp - delta);
         const int n = total - first < kWave ? total - first : kWave;
         constexpr int kChunk = sizeof(T) == 4 ? 2 : 8;
@@ -189,9 +199,16 @@ template <typename T> __device__ __forceinline__ float exponential(float s, floa
     if constexpr (kNormalised<T>) return __builtin_amdgcn_exp2f(exponent_fp32(s, scale2, scale2_low, bias) - base);
     return __builtin_amdgcn_exp2f(__builtin_fmaf(scale2, s, bias - base));
 }
-template <typename T> __device__ __forceinline__ void store_query(float *ld, unsigned n, float base, float delta, float inv) {
-    if constexpr (kNormalised<T>) *reinterpret_cast<f32x4 *>(ld + 4 * n) = f32x4{base, delta, inv, 0.f};
-    else *reinterpret_cast<f32x2 *>(ld + 2 * n) = f32x2{base, delta};
+// ld: of the plane, of plane_px queries; start: -1 / product_scale
+template <typename T> __device__ __forceinline__ void store_query(float *ld, size_t plane_px, unsigned n, int two, float start, float base, float delta, float inv) {
+    if constexpr (kNormalised<T>) {
+        *reinterpret_cast<f32x4 *>(ld + 4 * n) = f32x4{base, delta, inv, 0.f};
+    } else if (two) {
+        ld[n] = start * base;
+        (ld + plane_px)[n] = -delta;
+    } else {
+        *reinterpret_cast<f32x2 *>(ld + 2 * n) = f32x2{base, delta};
+    }
 }
 
 // What a query's dP are counted from, given its products with the values at the patch's 16 positions (in the layout of a block's products): their
@@ -260,6 +277,8 @@ __global__ __launch_bounds__(kPatchThreads, (kPatchOcc<T, D>)) void patch_bwd_q_
     const size_t plane_px = (size_t)H * W;
     const int qlin = iy * W + ix;
     const float scale2 = scale * kLog2e, scale2_low = __builtin_fmaf(scale, kLog2e, -scale2) + scale * kLog2eLow;
+
+    const float start = -1.f / product_scale(scale);
 
     auto issue = [&](int b, int s, int par) {
         const size_t off = ((size_t)b * g.heads + head) * plane_px * POSB;
@@ -400,7 +419,7 @@ __global__ __launch_bounds__(kPatchThreads, (kPatchOcc<T, D>)) void patch_bwd_q_
         uint32_t bits = ds_bound(most * inv, most_p * inv, delta), mark = 0;   // (where delta is not finite: once more, below)
         if (q_ok) {
             sa.store(reinterpret_cast<char *>(dq) + plane_off, (unsigned)(qlin * POSB), gr, scale * inv);
-            if (gr == 0) store_query<T>(ld + plane * plane_px * kQueryWords<T>, (unsigned)qlin, base, delta + from, inv);
+            if (gr == 0) store_query<T>(ld + plane * plane_px * kQueryWords<T>, plane_px, (unsigned)qlin, g.two, start, base, delta + from, inv);
         }
         unsigned long long again = __ballot(odd != odd);
         if (again) {
@@ -418,7 +437,7 @@ __global__ __launch_bounds__(kPatchThreads, (kPatchOcc<T, D>)) void patch_bwd_q_
                 float own_inv;
                 const float b2 = lane_value(base, c);
                 const float dl = query_once_more<T, D>(m, gc, scale, cy, cx, b2, dq + plane * plane_px * D, own, own_inv);
-                if (lane == 0) store_query<T>(ld + plane * plane_px * kQueryWords<T>, (unsigned)(cy * W + cx), b2, dl, own_inv);
+                if (lane == 0) store_query<T>(ld + plane * plane_px * kQueryWords<T>, plane_px, (unsigned)(cy * W + cx), g.two, start, b2, dl, own_inv);
                 if (own >= kNotFinite) mark = kMark;
                 else bits = bits > own ? bits : own;
             }
@@ -431,9 +450,21 @@ __global__ __launch_bounds__(kPatchThreads, (kPatchOcc<T, D>)) void patch_bwd_q_
 }
 
 // ---- part 2 ------------------------------------------------------------------------------------------------------------
+// What part 1 left of four map rows of queries for the kernel with two patches to a wave, rw from column x0 on, into LDS at `dst` by direct loads:
+// 4 x rw starts, then as many -delta; a row each to the waves of a workgroup.  Positions outside the map as in issue_rows().
+__device__ __forceinline__ void issue_starts(const float *ld, size_t plane_px, int H, int W, int y0, int x0, int rw, int dst, int wave, int lane) {
+    asm volatile("" : "+s"(wave));   // (as in issue_rows)
+    const int row = wave & 3, y = y0 + row < H - 1 ? y0 + row : H - 1;
+    const char *from = reinterpret_cast<const char *>(ld + (wave >> 2 ? plane_px : 0));
+    for (int s0 = 0; s0 < rw; s0 += kWave) {
+        const int x = x0 + s0 + lane < W - 1 ? x0 + s0 + lane : W - 1;
+        if (s0 + lane < rw) global_to_lds_4(from, (unsigned)((y * W + x) * 4), dst + (wave * rw + s0) * 4);
+    }
+}
+
 // The bias gradient in LDS.  A plane's dS are added as integers dS 2^(kBits - E), 2^E bounding every |dS| that the workgroup
 // meets in the plane (additions of integers commute, so waves may share the table); then the integers are added to the floating-point
-// sums and cleared.  At most 128 keys of a tile add to a cell.  16 bit: 32-bit integers, a term rounded by 2^(E-24) at most, where
+// sums and cleared.  At most 256 keys of a tile add to a cell.  16 bit: 32-bit integers, a term rounded by 2^(E-24) at most, where
 // the stored ds of the unfused steps is rounded at 2^-12 (fp16) of itself: error of the whole table against 64 bits 0.05 to 0.43 of theirs over 40 cases
 // (k = 7 to 21, logits of unit and threefold scale, values and keys with and without offsets); the cells that only dS far below 2^E reach lose digits
 // (99 % of the cells to 0.4 %, before to 1.5 to 200 %; with the threefold logits to 0.7 to 100 %, before to 13 to 140 %).
@@ -442,9 +473,9 @@ template <typename T> struct BiasSums {
     typedef int Int;
     typedef float Sum;
     static constexpr int kIntBytes = 4, kSumBytes = 4, kBits = 23;
-    __device__ static __forceinline__ void add(int addr, float ds, float up) {   // (a NaN counts as 0)
-        __hip_atomic_fetch_add(lds_ptr<int>(addr), (int)__builtin_rintf(ds * up), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-    }
+    __device__ static __forceinline__ int to_int(float ds, float up) { return (int)__builtin_rintf(ds * up); }   // (a NaN counts as 0)
+    __device__ static __forceinline__ void add_int(int addr, int n) { __hip_atomic_fetch_add(lds_ptr<int>(addr), n, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP); }
+    __device__ static __forceinline__ void add(int addr, float ds, float up) { add_int(addr, to_int(ds, up)); }
 };
 template <> struct BiasSums<float> {
     typedef long long Int;
@@ -465,6 +496,63 @@ __device__ __forceinline__ int copy_offset(int g, int cells) { return g * int_wo
 __host__ __device__ constexpr int flag_bytes(int cells) { return (cells + 127) / 128 * 16; }
 template <typename T> __host__ __device__ constexpr int table_bytes(int cells, int copies) { return (copies > 1 ? copies * int_words(cells) : cells) * BiasSums<T>::kIntBytes; }
 template <typename T> __host__ __device__ constexpr int dbias_bytes(int cells, int copies) { return cells * BiasSums<T>::kSumBytes + table_bytes<T>(cells, copies) + flag_bytes(cells); }
+
+// The scale of a plane's integers, from the bounds of the query patches that the rectangle of queries touches (every wave finds the same): up = 2^(kBits - E),
+// down its inverse; poisoned: some dS of the rectangle is not finite.
+template <typename T>
+__device__ __forceinline__ void bias_scale(const uint32_t *bound, size_t plane, int H, int W, int ry0, int cx0, int ry1, int cx1, int lane, float &up, float &down, bool &poisoned) {
+    const int pw = (W + 3) >> 2, ph = (H + 3) >> 2, by0 = ry0 >> 2, bx0 = cx0 >> 2, bw = (cx1 >> 2) - bx0 + 1, nbound = ((ry1 >> 2) - by0 + 1) * bw;
+    uint32_t most = 0, odd = 0;
+    for (int i = lane; i < nbound; i += kWave) {
+        const uint32_t bits = bound[(plane * ph + by0 + i / bw) * pw + bx0 + i % bw];
+        odd |= bits & kMark;
+        most = most > (bits & ~kMark) ? most : bits & ~kMark;
+    }
+    most = wave_max(most);
+    poisoned = __ballot(odd != 0) != 0;
+    int e = __builtin_amdgcn_readfirstlane((int)((most + 0x10000u) >> 23)) - 126;   // most < (1 - 2^-7) 2^e: 256 integers of kBits bits have a sum of 31
+    e = e < -70 ? -70 : e;                                             // (2^(50 + 70) is a float)
+    up = __builtin_ldexpf(1.f, BiasSums<T>::kBits - e);
+    down = __builtin_ldexpf(1.f, e - BiasSums<T>::kBits);
+}
+// the integers of cell i, which are cleared
+template <typename T> __device__ __forceinline__ typename BiasSums<T>::Int take_ints(int table0, int i, int cells, int copies) {
+    typedef typename BiasSums<T>::Int Int;
+    Int n = 0;
+    for (int c = 0; c < copies; ++c) {
+        const int a = table0 + ((c ? copy_offset(c, cells) : 0) + i) * (int)sizeof(Int);
+        n += *lds_ptr<Int>(a);
+        *lds_ptr<Int>(a) = 0;
+    }
+    return n;
+}
+// a workgroup's partial bias gradient (each thread reads the sums it added up)
+template <typename T>
+__device__ __forceinline__ void write_bias_sums(float *partial, int sums0, int flags0, const WorkItem &work, int head, int cells, int thread, const PatchShape &g) {
+    const int NB = 2 * g.K - 1, pitch = bias_pitch(g.K);
+    float *row = partial + (size_t)((head * g.splits + work.split) * g.gd.npos + work.pos) * rpb_cell_stride(NB * NB);
+    for (int i = thread; i < cells; i += kPatchThreads) {
+        const int u = fdiv(i, g.by_pitch), v = i - u * pitch - kBiasPad;
+        if ((unsigned)v >= (unsigned)NB) continue;
+        const bool odd = (*lds_ptr<unsigned>(flags0 + (i >> 5) * 4) >> (i & 31)) & 1u;
+        row[u * NB + v] = odd ? NAN : (float)*lds_ptr<typename BiasSums<T>::Sum>(sums0 + i * BiasSums<T>::kSumBytes);
+    }
+}
+// the keys of a patch (`again`: lanes) whose sums are not finite
+template <typename T, int D>
+__device__ __forceinline__ void keys_once_more(unsigned long long again, const T *q, const T *k, const T *v, const T *dout, const T *rpb, float scale, const float *ld, T *dk, T *dv,
+                                               size_t plane, int head, int sy0, int px0, const PatchShape &g) {
+    wait_global_loads();   // (the stores come first)
+    PatchShape gc = g;     // (nothing of this is prepared outside of the branch)
+    asm volatile("" : "+s"(gc.H), "+s"(gc.W), "+s"(gc.K));
+    const int NB = 2 * g.K - 1;
+    const size_t px = (size_t)g.H * g.W, at = plane * px * D;
+    const PlanePtrs<T, D> m{q + at, k + at, v + at, dout + at, g.with_bias ? rpb + (size_t)head * NB * NB : nullptr};
+    for (unsigned cols = (unsigned)((again | (again >> 16) | (again >> 32) | (again >> 48)) & 0xffffu); cols; cols &= cols - 1) {
+        const int c = __builtin_ctz(cols), cy = sy0 + (c >> 2), cx = px0 + (c & 3);
+        if (cy < g.H && cx < g.W) key_once_more<T, D>(m, gc, scale, cy, cx, ld + kQueryWords<T> * plane * px, dk + at, dv + at);
+    }
+}
 
 // LGS 1: two waves share a patch, the even and the odd rows of blocks, and a workgroup takes one plane (its integers go straight to its partial
 // bias gradient).
@@ -559,22 +647,7 @@ __global__ __launch_bounds__(kPatchThreads, (kPatchOcc<T, D>)) void patch_bwd_kv
         settle(vo);
         float up = 0.f, down = 0.f;   // 2^(kBits - E) and its inverse
         bool poisoned = false;  // some dS of the plane's rectangle is not finite
-        if (g.with_dbias) {
-            // the bounds of the query patches that the rectangle touches: every wave finds the same maximum
-            const int pw = (W + 3) >> 2, ph = (H + 3) >> 2, by0 = ry0 >> 2, bx0 = cx0 >> 2, bw = (cx1 >> 2) - bx0 + 1, nbound = ((ry1 >> 2) - by0 + 1) * bw;
-            uint32_t most = 0, odd = 0;
-            for (int i = own_lane(); i < nbound; i += kWave) {
-                const uint32_t bits = bound[(plane * ph + by0 + i / bw) * pw + bx0 + i % bw];
-                odd |= bits & kMark;
-                most = most > (bits & ~kMark) ? most : bits & ~kMark;
-            }
-            most = wave_max(most);
-            poisoned = __ballot(odd != 0) != 0;
-            int e = __builtin_amdgcn_readfirstlane((int)(most >> 23)) - 126;   // most < 2^e
-            e = e < -70 ? -70 : e;                                             // (2^(50 + 70) is a float)
-            up = __builtin_ldexpf(1.f, Table::kBits - e);
-            down = __builtin_ldexpf(1.f, e - Table::kBits);
-        }
+        if (g.with_dbias) bias_scale<T>(bound, plane, H, W, ry0, cx0, ry1, cx1, own_lane(), up, down, poisoned);
         PosSum<T, D> sk, sv, row_k, row_v;   // (fp32: of a row of blocks, then of the rows, as in part 1)
         sk.clear();
         sv.clear();
@@ -707,12 +780,7 @@ __global__ __launch_bounds__(kPatchThreads, (kPatchOcc<T, D>)) void patch_bwd_kv
         if (g.with_dbias) {
             workgroup_sync();   // every wave has added its part; nobody adds more before the next step's barrier
             for (int i = wave * kWave + own_lane(); i < cells; i += kPatchThreads) {
-                typename Table::Int n = 0;
-                for (int c = 0; c < g.copies; ++c) {
-                    const int a = table0 + ((c ? copy_offset(c, cells) : 0) + i) * Table::kIntBytes;
-                    n += *lds_ptr<typename Table::Int>(a);
-                    *lds_ptr<typename Table::Int>(a) = 0;
-                }
+                const typename Table::Int n = take_ints<T>(table0, i, cells, g.copies);
                 if constexpr (LGS > 0) {
                     const int u = fdiv(i, g.by_pitch), v = i - u * pitch - kBiasPad;
                     if ((unsigned)v < (unsigned)NB) {
@@ -754,34 +822,256 @@ __global__ __launch_bounds__(kPatchThreads, (kPatchOcc<T, D>)) void patch_bwd_kv
         }
         const float odd = sk.not_finite() + sv.not_finite();
         const unsigned long long again = __ballot(odd != odd);
-        if (again) {
-            wait_global_loads();   // (the stores above come first)
-            PatchShape gc = g;     // (nothing of this is prepared outside of the branch)
-            asm volatile("" : "+s"(gc.H), "+s"(gc.W), "+s"(gc.K));
-            const PlanePtrs<T, D> m{q + plane * plane_px * D, k + plane * plane_px * D, v + plane * plane_px * D, dout + plane * plane_px * D,
-                                    g.with_bias ? rpb + (size_t)head * NB * NB : nullptr};
-            for (unsigned cols = (unsigned)((again | (again >> 16) | (again >> 32) | (again >> 48)) & 0xffffu); cols; cols &= cols - 1) {
-                const int c = __builtin_ctz(cols), cy = sy0 + (c >> 2), cx = px0 + (c & 3);
-                if (cy < H && cx < W) key_once_more<T, D>(m, gc, scale, cy, cx, ld + kQueryWords<T> * plane * plane_px, dk + plane * plane_px * D, dv + plane * plane_px * D);
+        if (again) keys_once_more<T, D>(again, q, k, v, dout, rpb, scale, ld, dk, dv, plane, head, sy0, px0, g);
+    }
+    if (LGS == 0 && g.with_dbias) write_bias_sums<T>(partial, sums0, flags0, work, head, cells, wave * kWave + own_lane(), g);
+}
+
+// Part 2 with two key patches to a wave, side by side (16 bit).  The left patch meets a block of queries in the cells of the bias table in which the
+// right one meets the next block: the two share the reads of the queries, upstream gradients, starts and deltas of a block, the bias row (the
+// right one's is the left one's of the block before) and the integer additions (likewise), and half as many rows of blocks are walked.  That, products that
+// start from -lse / scale and -delta, and no branch between the results of the two: vector instructions of the kernel 49e6 -> 39e6 at 64 x 2 x 56 x 56 fp16, k = 13,
+// 146 -> 118 us.  It is bound by their issue (in a full round three quarters of the slots; a wave's prologue and the barrier of each step, where
+// the waves next to a border have up to half as many blocks more, are the rest).
+template <typename T, int D, bool DBIAS>
+__global__ __launch_bounds__(kPatchThreads, 4) void patch_bwd_kv2_kernel(
+    const T *__restrict__ q, const T *__restrict__ k, const T *__restrict__ v, const T *__restrict__ rpb, float scale,
+    const float *__restrict__ ld, const uint32_t *__restrict__ bound, const T *__restrict__ dout, T *__restrict__ dk, T *__restrict__ dv,
+    float *__restrict__ partial, PatchShape g) {
+    static_assert(sizeof(T) == 2, "16 bit");
+    using CV = ChanVec<T, D>;
+    using Op = PosOp<T, D>;
+    using Table = BiasSums<T>;
+    constexpr int POSB = Op::POSB;
+    extern __shared__ __align__(16) char lds[];
+    const int wg = xcd_contiguous_block(blockIdx.x, gridDim.x);
+    if (wg >= g.units * g.splits) return;
+    const WorkItem work = decode_work(wg, g.heads, g.tiles_y, g.splits, g.gd);
+    const int head = work.head, K = g.K, H = g.H, W = g.W, NB = 2 * K - 1, pitch = bias_pitch(K);
+    const int tid = threadIdx.x, lane = tid % kWave, wave = __builtin_amdgcn_readfirstlane(tid / kWave);
+    const int cells = NB * pitch, sums0 = dynamic_lds(lds), table0 = sums0 + (DBIAS ? cells * Table::kSumBytes : 0);
+    const int flags0 = table0 + (DBIAS ? table_bytes<T>(cells, g.copies) : 0), bias0 = flags0 + (DBIAS ? flag_bytes(cells) : 0);
+    const int img0 = bias0 + bias_rows(K, g.with_bias) * pitch * 4;
+    const int img_bytes = 4 * g.rw * POSB, ld_bytes = 16 * g.rw, stage_bytes = 2 * img_bytes + 2 * ld_bytes;
+
+    const int lg = g.lg_cols, tw = 8 << lg, th = 32 >> lg, ty0 = work.ty * th, tx0 = work.tx * tw;
+    const int ty1 = ty0 + th - 1 < H - 1 ? ty0 + th - 1 : H - 1, tx1 = tx0 + tw - 1 < W - 1 ? tx0 + tw - 1 : W - 1;
+    const int ry0 = inv_first(ty0, H, K), cx0 = inv_first(tx0, W, K);            // first query row and column of the tile
+    const int ry1 = inv_last(ty1, H, K), cx1 = inv_last(tx1, W, K);
+    const int nsteps = (ry1 - ry0 + 4) >> 2;
+    
+    // this wave's left patch: the lower rows of pairs are taken in another order, so that the waves of a SIMD (w and w + 4) do not all get those
+    // next to a border, which meet up to half as many blocks more
+    const int sy0 = ty0 + 4 * (wave >> lg), px0 = tx0 + 8 * ((wave + 2 * (wave >> lg)) & ((1 << lg) - 1));
+    const bool active = sy0 < H && px0 < W, two = px0 + 4 < W;
+    const int sy3 = sy0 + 3 < H - 1 ? sy0 + 3 : H - 1;
+    const int pyc = sy0 < H ? sy0 : H - 1;
+    const int b_lo = (inv_first(pyc, H, K) - ry0) >> 2, b_hi = (inv_last(sy3, H, K) - ry0) >> 2;   // rows of blocks
+    const int pl0 = px0 < W ? px0 : W - 1, pl3 = px0 + 3 < W - 1 ? px0 + 3 : W - 1, pr0 = px0 + 4 < W - 1 ? px0 + 4 : W - 1, pr3 = px0 + 7 < W - 1 ? px0 + 7 : W - 1;
+    // blocks of a row, counted from the left patch's first: the left patch's last, the right one's first and last
+    const int ox = inv_first(pl0, W, K), l_last = (inv_last(pl3, W, K) - ox) >> 2;
+    const int r_first = two ? (inv_first(pr0, W, K) - ox) >> 2 : l_last + 1, r_last = two ? (inv_last(pr3, W, K) - ox) >> 2 : l_last;
+    // the columns of the queries that see the lane's keys: the first (from ox) and their number (0: a key outside the map)
+    const int kx = px0 + (lane & 3), kl = kx < W ? kx : W - 1, kr = kx + 4 < W ? kx + 4 : W - 1;
+    const auto span = [&](int x, int kc) { return (inv_first(kc, W, K) - ox) | ((x < W ? inv_last(kc, W, K) - inv_first(kc, W, K) + 1 : 0) << 16); };   // (below 2^15, two to a register)
+    const int spans[2] = {span(kx, kl), span(kx + 4, kr)};
+    // columns that see every key of a patch
+    const int clear_l0 = inv_first(pl3, W, K) - ox, clear_l1 = px0 + 3 < W ? inv_last(pl0, W, K) + 1 - ox : 0;
+    const int clear_r0 = inv_first(pr3, W, K) - ox, clear_r1 = px0 + 7 < W ? inv_last(pr0, W, K) + 1 - ox : 0;
+    const int no_row = bias_rows(K, g.with_bias) - 1;
+    const size_t plane_px = (size_t)H * W;
+    const auto own_lane = own_lane_index;   // (recomputed where it is used: a register less in the inner loop)
+    const auto key_offset = [&](int lv, int right) {
+        const int y = sy0 + ((lv & 15) >> 2), x = px0 + (lv & 3) + right;
+        return (unsigned)(((y < H - 1 ? y : H - 1) * W + (x < W - 1 ? x : W - 1)) * POSB);
+    };
+    const float scale2 = product_scale(scale);
+
+    auto issue = [&](int b, int s, int par) {
+        const size_t px = ((size_t)b * g.heads + head) * plane_px;
+        const int img = img0 + par * stage_bytes;
+        issue_rows<POSB>(reinterpret_cast<const char *>(q) + px * POSB, reinterpret_cast<const char *>(dout) + px * POSB, H, W, ry0 + 4 * s, cx0, g.rw, img, img_bytes, wave, lane);
+        issue_starts(ld + px * kQueryWords<T>, plane_px, H, W, ry0 + 4 * s, cx0, g.rw, img + 2 * img_bytes, wave, lane);
+    };
+    if (work.b_begin < work.b_end) issue(work.b_begin, 0, 0);
+    stage_bias<T>(g.with_bias ? rpb + (size_t)head * NB * NB : nullptr, K, g.by_pitch, bias0, tid);
+    if (DBIAS)
+        for (int i = sums0 + tid * 16; i < bias0; i += kPatchThreads * 16) *lds_ptr<u32x4>(i) = u32x4{0u, 0u, 0u, 0u};
+
+    int par = 0;
+    for (int b = work.b_begin; b < work.b_end; ++b) {
+        const size_t plane = (size_t)b * g.heads + head;
+        CV ko[2], vo[2];
+        const size_t plane_off = plane * plane_px * POSB;
+        const int lv0 = own_lane();
+#pragma unroll
+        for (int t = 0; t < 2; ++t) {
+            const unsigned key_lane = key_offset(lv0, 4 * t) + (lv0 >> 4) * CV::kLaneBytes;
+            ko[t].load(reinterpret_cast<const char *>(k) + plane_off + key_lane);
+            vo[t].load(reinterpret_cast<const char *>(v) + plane_off + key_lane);
+        }
+#pragma unroll
+        for (int t = 0; t < 2; ++t) settle(ko[t]), settle(vo[t]);
+        float up = 0.f, down = 0.f;   // 2^(kBits - E) and its inverse
+        bool poisoned = false;  // some dS of the plane's rectangle is not finite
+        if (DBIAS) bias_scale<T>(bound, plane, H, W, ry0, cx0, ry1, cx1, own_lane(), up, down, poisoned);
+        PosSum<T, D> sk[2], sv[2];
+#pragma unroll
+        for (int t = 0; t < 2; ++t) sk[t].clear(), sv[t].clear();
+        for (int s = 0; s < nsteps; ++s) {
+            wait_global_loads();
+            workgroup_sync();   // this step's rows have landed for every wave, and nobody still reads the other buffer
+            const int img = img0 + par * stage_bytes;
+            const bool last = s + 1 == nsteps;
+            if (g.nstage == 2) {
+                par ^= 1;
+                if (!last || b + 1 < work.b_end) issue(last ? b + 1 : b, last ? 0 : s + 1, par);
+            }
+            if (active && s >= b_lo && s <= b_hi) {
+                // the lane's row of the block against its keys' row (like the lane's places in the images worked out anew in each step, for the registers)
+                const int lv = own_lane(), j = lv & 15, gr = lv >> 4, x0 = ox - cx0;
+                const int table_lane = table0 + (g.copies > 1 ? copy_offset(gr, cells) * Table::kIntBytes : 0);
+                const int v0 = px0 + (j & 3) - ox + K - 1 + kBiasPad;     // (the cell falls with the query's row and column)
+                const int qrow = ry0 + 4 * s + gr, krow = sy0 + (j >> 2), kc = krow < H ? krow : H - 1, first = inv_first(kc, H, K);
+                const bool rowok = krow < H && qrow >= first && qrow <= inv_last(kc, H, K);
+                const int u = kc - qrow + K - 1, uc = u < 0 ? 0 : (u < NB - 1 ? u : NB - 1);
+                int cell = table_lane + (uc * pitch + v0) * 4, brow = bias0 + ((rowok ? (g.with_bias ? uc : 0) : no_row) * pitch + v0) * 4 - 12;   // (of the last of four columns)
+                int a0 = img + ((j >> 2) * g.rw + x0 + (j & 3)) * POSB + gr * CV::kLaneBytes, t0 = img + Op::lane_offset(lv, g.rw) + x0 * POSB;
+                int l0 = img + 2 * img_bytes + (gr * g.rw + x0) * 4;
+                float before[4];   // the left patch's bias in the block before
+                int held[4];       // and its dS there
+#pragma unroll
+                for (int r = 0; r < 4; ++r) held[r] = 0;
+                if (r_first == 0) {
+#pragma unroll
+                    for (int r = 3; r >= 0; --r) before[r] = *lds_ptr<float>(brow + 28 - r * 4);
+                }
+                // block column bx against the left patch (L), the right one (R) or both
+                const auto block = [&](auto left, auto right, int bx) {
+                    constexpr bool L = decltype(left)::value, R = decltype(right)::value;
+                    CV qa, da;
+                    qa.load_lds(a0);
+                    da.load_lds(a0 + img_bytes);
+                    f32x4 from_s, from_dp;
+                    float here[4], arg[2][4];
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) {
+                        from_s[r] = *lds_ptr<float>(l0 + r * 4);
+                        from_dp[r] = *lds_ptr<float>(l0 + ld_bytes + r * 4);
+                    }
+#pragma unroll
+                    for (int r = 3; r >= 0; --r) {
+                        if (L) arg[0][r] = here[r] = *lds_ptr<float>(brow + 12 - r * 4);
+                        if (R) arg[1][r] = L ? before[r] : *lds_ptr<float>(brow + 28 - r * 4);
+                    }
+                    // queries whose windows do not hold the key: weight 0 (decided before the products, as in part 1)
+#pragma unroll
+                    for (int t = 0; t < 2; ++t) {
+                        if (t == 0 ? !L : !R) continue;
+                        if (4 * bx < (t ? clear_r0 : clear_l0) || 4 * bx + 4 > (t ? clear_r1 : clear_l1)) {
+#pragma unroll
+                            for (int r = 0; r < 4; ++r) arg[t][r] = (unsigned)(4 * bx + r - (spans[t] & 0xffff)) < (unsigned)spans[t] >> 16 ? arg[t][r] : -INFINITY;
+                        }
+                    }
+                    f32x4 s4[2], dp[2];
+#pragma unroll
+                    for (int t = 0; t < 2; ++t) {
+                        if (t == 0 ? !L : !R) continue;
+                        s4[t] = chan_dot<T, D>(qa, ko[t], from_s);
+                        dp[t] = chan_dot<T, D>(da, vo[t], from_dp);
+                    }
+                    Op qt, dt;
+                    dt.load_lds(t0 + img_bytes);
+                    qt.load_lds(t0);
+                    float p[2][4], ds[2][4];
+#pragma unroll
+                    for (int t = 0; t < 2; ++t) {
+                        if (t == 0 ? !L : !R) continue;
+#pragma unroll
+                        for (int r = 0; r < 4; ++r) {
+                            p[t][r] = __builtin_amdgcn_exp2f(__builtin_fmaf(scale2, s4[t][r], arg[t][r]));
+                            ds[t][r] = p[t][r] * dp[t][r];
+                        }
+                    }
+#pragma unroll
+                    for (int t = 0; t < 2; ++t) {
+                        if (t == 0 ? !L : !R) continue;
+                        sv[t].add(dt, Weights4<T>(p[t]));
+                        sk[t].add(qt, Weights4<T>(ds[t]));
+                    }
+                    if (DBIAS) {   // (outside the window, and NaN: 0)
+#pragma unroll
+                        for (int r = 0; r < 4; ++r) {
+                            if (R) Table::add_int(cell + 16 - r * 4, held[r] + Table::to_int(ds[1][r], up));
+                            if (!R && bx > 0) Table::add_int(cell + 16 - r * 4, held[r]);
+                            held[r] = L ? Table::to_int(ds[0][r], up) : 0;
+                        }
+                        if (poisoned) {
+#pragma unroll
+                            for (int t = 0; t < 2; ++t) {
+                                if (t == 0 ? !L : !R) continue;
+#pragma unroll
+                                for (int r = 0; r < 4; ++r) {
+                                    const int c = (cell - table0 - (g.copies > 1 ? copy_offset(own_lane() >> 4, cells) * Table::kIntBytes : 0)) / 4 + 4 * t - r;
+                                    const bool in = rowok && (unsigned)(4 * bx + r - (spans[t] & 0xffff)) < (unsigned)spans[t] >> 16;
+                                    if (in && !(fabsf(ds[t][r]) < INFINITY)) __hip_atomic_fetch_or(lds_ptr<unsigned>(flags0 + (c >> 5) * 4), 1u << (c & 31), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+                                }
+                            }
+                        }
+                    }
+                    if (L) {
+#pragma unroll
+                        for (int r = 0; r < 4; ++r) before[r] = here[r];
+                    }
+                    a0 += 4 * POSB;
+                    t0 += 4 * POSB;
+                    l0 += 16;
+                    cell -= 16;
+                    brow -= 16;
+                };
+                int bx = 0;
+                for (; bx < r_first; ++bx) block(IntC<1>{}, IntC<0>{}, bx);
+                for (; bx <= l_last; ++bx) block(IntC<1>{}, IntC<1>{}, bx);
+                for (; bx <= r_last; ++bx) block(IntC<0>{}, IntC<1>{}, bx);
+                if (DBIAS && r_last == l_last) {   // the left patch's dS of the last block
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) Table::add_int(cell + 16 - r * 4, held[r]);
+                }
+            }
+            if (g.nstage == 1 && (!last || b + 1 < work.b_end)) {
+                workgroup_sync();   // nobody still reads the rows
+                issue(last ? b + 1 : b, last ? 0 : s + 1, 0);
             }
         }
-    }
-    if (LGS == 0 && g.with_dbias) {   // (each thread reads the sums it added up)
-        float *row = partial + (size_t)((head * g.splits + work.split) * g.gd.npos + work.pos) * rpb_cell_stride(NB * NB);
-        for (int i = wave * kWave + own_lane(); i < cells; i += kPatchThreads) {
-            const int u = fdiv(i, g.by_pitch), v = i - u * pitch - kBiasPad;
-            if ((unsigned)v >= (unsigned)NB) continue;
-            const bool odd = (*lds_ptr<unsigned>(flags0 + (i >> 5) * 4) >> (i & 31)) & 1u;
-            row[u * NB + v] = odd ? NAN : (float)*lds_ptr<typename Table::Sum>(sums0 + i * Table::kSumBytes);
+#pragma unroll
+        for (int t = 0; t < 2; ++t) sk[t].settle(), sv[t].settle();
+        if (DBIAS) {
+            workgroup_sync();   // every wave has added its part; nobody adds more before the next step's barrier
+            for (int i = wave * kWave + own_lane(); i < cells; i += kPatchThreads)
+                *lds_ptr<typename Table::Sum>(sums0 + i * Table::kSumBytes) += (typename Table::Sum)take_ints<T>(table0, i, cells, g.copies) * (typename Table::Sum)down;
+        }
+        if (!active) continue;
+#pragma unroll
+        for (int t = 0; t < 2; ++t) {
+            const int lv = own_lane();
+            if (sy0 + ((lv & 15) >> 2) < H && px0 + (lv & 3) + 4 * t < W) {
+                const unsigned o = key_offset(lv, 4 * t);
+                sk[t].store(reinterpret_cast<char *>(dk) + plane_off, o, lv >> 4, scale);
+                sv[t].store(reinterpret_cast<char *>(dv) + plane_off, o, lv >> 4, 1.f);
+            }
+            const float odd = sk[t].not_finite() + sv[t].not_finite();
+            const unsigned long long again = __ballot(odd != odd);
+            if (again) keys_once_more<T, D>(again, q, k, v, dout, rpb, scale, ld, dk, dv, plane, head, sy0, px0 + 4 * t, g);
         }
     }
+    if (DBIAS) write_bias_sums<T>(partial, sums0, flags0, work, head, cells, wave * kWave + own_lane(), g);
 }
 
 // ---- host ------------------------------------------------------------------------------------------------------------
 struct PatchPlan {
     PatchShape q, kv;
     int lds_q, lds_kv;
-    bool ok, pairs;   // pairs of waves in part 2
+    bool ok, pairs, two;   // part 2: pairs of waves to a patch, or two patches to a wave
 };
 int query_bytes(const Problem &p) { return 4 * (p.dtype == NA2D_F32 ? kQueryWords<float> : kQueryWords<f16_t>); }
 // Pairs of waves in part 2: where one wave per patch leaves half of the chip's 4096 places for waves free, wide windows in 16 bit last as long as
@@ -790,6 +1080,13 @@ int query_bytes(const Problem &p) { return 4 * (p.dtype == NA2D_F32 ? kQueryWord
 // maps, two waves' time over one's): k = 15 0.89 .. 1.04 to 2600 patches, 0.93 .. 1.14 from there; k = 21 0.87 .. 1.00 to 2600, 0.91 .. 1.05 from there.  (Up to k = 13 no choice looks at the batch.)
 bool pairs_wanted(const Problem &p) {
     return p.dtype != NA2D_F32 && p.K > 13 && p.D <= 64 && (long long)p.planes() * ((p.H + 3) / 4) * ((p.W + 3) / 4) <= 2048;
+}
+// Two patches to a wave in part 2, in 16 bit with up to 32 channels (64: the registers leave two waves to a SIMD, 123 / 131 us at k = 7), where there are as many
+// patches as the chip has places for waves.  us of both parts and the bias gradient, one patch / two: 64 x 2 x 56 x 56 fp16 k = 11 (bf16) 205 / 191, k = 13
+// 226 / 198, k = 15 272 / 232, k = 21 437 / 348; 128 x 8 x 14 x 14 bf16 k = 13 125 / 102; 5000 patches k = 13 67.8 / 66.9; 4096 patches k = 11 45.3 / 46.4, k = 21 90 / 80; 2100 to 2600
+// patches k = 15 and 21 1.01 to 1.03 times as long, 780 patches k = 13 35 / 42.
+bool two_wanted(const Problem &p) {
+    return p.dtype != NA2D_F32 && p.D <= 32 && (long long)p.planes() * ((p.H + 3) / 4) * ((p.W + 3) / 4) >= (p.K <= 13 ? 4160 : 4096);
 }
 PatchPlan patch_plan(const Problem &p, bool bias, bool dbias) {
     PatchPlan pl{};
@@ -829,6 +1126,35 @@ PatchPlan patch_plan(const Problem &p, bool bias, bool dbias) {
         pl.lds_kv = lds4;
     }
     pl.ok = pl.q.nstage > 0 && pl.kv.nstage > 0;
+    if (pl.ok && two_wanted(p)) {
+        // the tile with the least steps whose buffers leave room for a second workgroup
+        long long fewest = LLONG_MAX;
+        const int room = 80 * 1024;
+        for (int l = 2; l >= 0; --l) {
+            const int w = 8 << l, h = 32 >> l, rows = h + K - 1 < p.H ? h + K - 1 : p.H;
+            const int rw = image_row(p.W, K, w, posb, [&](int x) { return inv_first(x, p.W, K); }, [&](int x) { return inv_last(x, p.W, K); }, 8);
+            const int step = 2 * 4 * rw * posb + 4 * rw * query_bytes(p), tx = (p.W + w - 1) / w, ty = (p.H + h - 1) / h;
+            const long long steps2 = (long long)tx * ty * ((rows + 3) / 4);
+            // (whether there are two is decided as with both tables: the number of partial bias gradients follows from it)
+            const int most = bias_rows(K, true) * pitch * 4 + dbias_bytes<f16_t>(cells, 1), n = most + 2 * step <= room ? 2 : 1;
+            if (most + n * step > room || steps2 >= fewest) continue;
+            fewest = steps2;
+            pl.two = true;
+            pl.kv = s;
+            pl.kv.rw = rw;
+            pl.kv.lg_cols = l;
+            pl.kv.tiles_y = ty;
+            pl.kv.units = tx * ty * p.heads;
+            // a plane per workgroup, so that a compute unit gets tiles next to borders and others alike, until the partial bias gradients would be many
+            pl.kv.splits = 8192 / pl.kv.units;
+            pl.kv.splits = pl.kv.splits < 1 ? 1 : pl.kv.splits < p.B ? pl.kv.splits : p.B;
+            pl.kv.gd = make_grid_decode(tx, ty, p.heads, p.B, pl.kv.splits);
+            pl.kv.nstage = n;
+            pl.q.two = pl.kv.two = 1;
+            pl.kv.copies = dbias && table + sums(4) + n * step <= room ? 4 : 1;
+            pl.lds_kv = table + sums(pl.kv.copies) + n * step;
+        }
+    }
     if (pl.ok && pairs_wanted(p)) {
         // (whether there are pairs is decided as with both tables: the number of partial bias gradients follows from it)
         const int most = bias_rows(K, true) * pitch * 4, ints = table_bytes<f16_t>(cells, 1) + flag_bytes(cells), joined = 4 * (p.D / 16) * 2048;
@@ -843,6 +1169,8 @@ PatchPlan patch_plan(const Problem &p, bool bias, bool dbias) {
             if (steps2 >= fewest) continue;
             fewest = steps2;
             pl.pairs = true;
+            pl.two = false;
+            pl.q.two = 0;
             const int fixed = table + (dbias ? ints : 0), fixed4 = table + (dbias ? table_bytes<f16_t>(cells, 4) + flag_bytes(cells) : 0);
             pl.kv = s;
             pl.kv.rw = rw;
@@ -877,6 +1205,16 @@ hipError_t launch_patch_bwd_t(const Problem &p, const PatchPlan &pl, const T *q,
         if (pl.pairs) {
             if (hipError_t e = allow_lds(patch_bwd_kv_kernel<T, D, 1>, 160 * 1024, allowed_pairs); e != hipSuccess) return e;
             hipLaunchKernelGGL((patch_bwd_kv_kernel<T, D, 1>), dim3(xcd_padded_grid(pl.kv.units * pl.kv.splits)), dim3(kPatchThreads), pl.lds_kv, s, q, k, v, rpb, scale,
+                               ld, bound, dout, dk, dv, partial, pl.kv);
+            return hipGetLastError();
+        }
+    }
+    if constexpr (D <= 32 && sizeof(T) == 2) {
+        if (pl.two) {
+            static LdsAllowed allowed_two, allowed_two_no;
+            const auto kern = partial ? patch_bwd_kv2_kernel<T, D, true> : patch_bwd_kv2_kernel<T, D, false>;
+            if (hipError_t e = allow_lds(kern, 160 * 1024, partial ? allowed_two : allowed_two_no); e != hipSuccess) return e;
+            hipLaunchKernelGGL(kern, dim3(xcd_padded_grid(pl.kv.units * pl.kv.splits)), dim3(kPatchThreads), pl.lds_kv, s, q, k, v, rpb, scale,
                                ld, bound, dout, dk, dv, partial, pl.kv);
             return hipGetLastError();
         }

@@ -1,0 +1,68 @@
+"""Key side of the patch backward with two key patches to a wave (16 bit, 16 and 32 channels, from 4160 patches on, k > 13 from 4096) against the
+oracle: maps whose last pair has one patch or a part of one, pairs at both borders at once, rows of blocks that only the left or the right patch
+meets, each tile shape, and windows whose images are loaded between the steps."""
+import numpy as np
+import pytest
+import torch
+
+from gpu_util import Stages, assert_close, assert_close_rpb
+from paper_2204_07143_amd import functional as F
+from paper_2204_07143_amd import synth
+from test_gpu_direct_bwd import assert_close_16bit, direct
+
+pytestmark = pytest.mark.gpu
+
+
+def check(oracle, p, seed, use_rpb=True, scale=None):
+    """dk, dv and the bias gradient, by the bounds of test_gpu_direct_bwd (dq is the query side's)."""
+    st = Stages(p, synth.make_inputs(p, seed, rpb_std=0.5), use_rpb=use_rpb, scale=scale)
+    st.forward_fused()
+    got = direct(st)
+    host = [t.double().cpu().numpy() for t in (st.q, st.key, st.v)]
+    rpb = st.rpb.double().cpu().numpy() if use_rpb else np.zeros((p.heads, 2 * p.k - 1, 2 * p.k - 1))
+    want = oracle.bwd(*host, rpb, st.scale, st.dout.double().cpu().numpy(), p.k)
+    for n, g, o in zip(("dk", "dv"), got[1:3], want[1:3]):
+        assert_close(n, g.double().cpu().numpy(), o, p.dtype, abs_tol=2e-3 if p.dtype != "bf16" else 2e-2)
+        if st.scale:
+            assert_close_16bit(n, g.double().cpu().numpy(), o, p.dtype)
+    assert_close_rpb("d_rpb", got[3].double(), want[3])
+    for again in (direct(st), direct(st, with_rpb_grad=False)):
+        assert all(torch.equal(a, b) for a, b in zip(again[:3], got))
+
+
+# (patches: 4050 and 4140 take one patch to a wave, the others two)
+@pytest.mark.parametrize("dtype", ["f16", "bf16"])
+@pytest.mark.parametrize("B,heads,H,W,D,k", [
+    (450, 1, 11, 12, 32, 11), (460, 1, 11, 12, 32, 11), (465, 1, 11, 12, 32, 11), (232, 2, 11, 11, 16, 11), (150, 2, 14, 14, 32, 13), (90, 2, 15, 21, 32, 13), (40, 3, 22, 23, 16, 13),
+    (30, 2, 25, 40, 32, 11), (14, 1, 53, 89, 32, 13), (70, 3, 17, 15, 32, 15), (35, 2, 30, 31, 32, 21), (26, 1, 41, 66, 16, 19)])
+@pytest.mark.parametrize("use_rpb", [True, False])
+def test_backward_two_patches_to_a_wave(oracle, dtype, B, heads, H, W, D, k, use_rpb):
+    check(oracle, synth.Problem(B, heads, H, W, D, k, dtype), seed=H + W + k, use_rpb=use_rpb)
+
+
+@pytest.mark.parametrize("scale", [0.0, -0.3])
+def test_scales(oracle, scale):
+    # the products start from -lse / scale
+    check(oracle, synth.Problem(470, 1, 11, 12, 32, 11, "f16"), seed=4, scale=scale)
+
+
+@pytest.mark.parametrize("where", ["q", "k", "v", "dout"])
+@pytest.mark.parametrize("value", [float("nan"), float("inf"), 3e38])
+def test_not_finite(where, value):
+    """The same planes, alone (one patch to a wave) and among many (two): the same elements are finite.  3e38: finite itself, its products are not."""
+    g = torch.Generator(device="cuda").manual_seed(3)
+    one = {n: torch.randn((1, 1, 26, 27, 32), generator=g, device="cuda").bfloat16() for n in ("q", "k", "v", "dout")}
+    one[where][0, 0, 12, 5, 7] = value
+    rpb = torch.zeros((1, 25, 25), device="cuda").bfloat16()
+
+    def grads(B):
+        q, k, v, r = (t.expand(B, *t.shape[1:]).clone().requires_grad_() if t.dim() == 5 else t.clone().requires_grad_()
+                      for t in (one["q"], one["k"], one["v"], rpb))
+        return torch.autograd.grad(F.na2d(q, k, v, r, kernel_size=13), (q, k, v, r), one["dout"].expand(B, -1, -1, -1, -1).contiguous())
+
+    few, many = grads(1), grads(90)
+    for a, b in zip(few[:3], many[:3]):
+        assert torch.equal(a[0].isfinite(), b[0].isfinite())
+        f = a[0].isfinite()
+        assert torch.allclose(a[0][f], b[0][f], rtol=2.0 ** -6, atol=3e-2)   # (added up in another order: two roundings of the weights to 8 bits)
+    assert torch.equal(few[3].isfinite(), many[3].isfinite())
