@@ -19,10 +19,10 @@
 // A masked product is 0 * x: where x is not finite it would spoil positions whose window does not hold it, so results that are not
 // finite are computed once more from their own window only.
 // Measured (us, both parts and the bias gradient, in brackets the steps before: weights recomputed into memory and the unfused backward):
-// 64 x 2 x 56 x 56 queries, fp16, 32 channels, k = 13 82 + 118 + 4 (455); fp32, k = 7 196 + 217 + 6 (700); fp16, 64 channels (one head), k = 7 48 + 65 + 9
-// (165); 4 x 2 x 64 x 64, bf16, k = 21 18 + 40 + 4 (220).  By counters at the first shape part 1 issues 60 vector instructions per
-// 16 x 16 products, of which a block needs 40, and waits 43 % of its wave cycles: its four waves per SIMD do not cover the chain from LDS through
-// two products, the exponential and two more.  Part 2 adds the integer additions in LDS.  fp32 is
+// 64 x 2 x 56 x 56 queries, fp16, 32 channels, k = 13 78 + 118 + 5 (455); fp32, k = 7 196 + 217 + 6 (700); fp16, 64 channels (one head), k = 7 48 + 65 + 9
+// (165); 4 x 2 x 64 x 64, bf16, k = 21 18 + 40 + 4 (220).  By counters with one patch to a wave part 1 issues 60 vector
+// instructions per 16 x 16 products, of which a block needs 40, and waits 43 % of its wave cycles: its four waves per SIMD do not cover the chain from LDS
+// through two products, the exponential and two more.  Part 2 adds the integer additions in LDS.  In 16 bit large calls take two patches to a wave.  fp32 is
 // nearer to its matrix cores: 32 instructions of 32 cycles per block, 94 us a part.
 #include <limits.h>
 
@@ -199,16 +199,14 @@ template <typename T> __device__ __forceinline__ float exponential(float s, floa
     if constexpr (kNormalised<T>) return __builtin_amdgcn_exp2f(exponent_fp32(s, scale2, scale2_low, bias) - base);
     return __builtin_amdgcn_exp2f(__builtin_fmaf(scale2, s, bias - base));
 }
-// ld: of the plane, of plane_px queries; start: -1 / product_scale
-template <typename T> __device__ __forceinline__ void store_query(float *ld, size_t plane_px, unsigned n, int two, float start, float base, float delta, float inv) {
-    if constexpr (kNormalised<T>) {
-        *reinterpret_cast<f32x4 *>(ld + 4 * n) = f32x4{base, delta, inv, 0.f};
-    } else if (two) {
-        ld[n] = start * base;
-        (ld + plane_px)[n] = -delta;
-    } else {
-        *reinterpret_cast<f32x2 *>(ld + 2 * n) = f32x2{base, delta};
-    }
+template <typename T> __device__ __forceinline__ void store_query(float *ld, unsigned n, float base, float delta, float inv) {
+    if constexpr (kNormalised<T>) *reinterpret_cast<f32x4 *>(ld + 4 * n) = f32x4{base, delta, inv, 0.f};
+    else *reinterpret_cast<f32x2 *>(ld + 2 * n) = f32x2{base, delta};
+}
+// (ld: of the plane, of plane_px queries)
+__device__ __forceinline__ void store_starts(float *ld, size_t plane_px, unsigned n, float start, float delta) {
+    ld[n] = start;
+    (ld + plane_px)[n] = -delta;
 }
 
 // What a query's dP are counted from, given its products with the values at the patch's 16 positions (in the layout of a block's products): their
@@ -278,7 +276,6 @@ __global__ __launch_bounds__(kPatchThreads, (kPatchOcc<T, D>)) void patch_bwd_q_
     const int qlin = iy * W + ix;
     const float scale2 = scale * kLog2e, scale2_low = __builtin_fmaf(scale, kLog2e, -scale2) + scale * kLog2eLow;
 
-    const float start = -1.f / product_scale(scale);
 
     auto issue = [&](int b, int s, int par) {
         const size_t off = ((size_t)b * g.heads + head) * plane_px * POSB;
@@ -419,7 +416,7 @@ __global__ __launch_bounds__(kPatchThreads, (kPatchOcc<T, D>)) void patch_bwd_q_
         uint32_t bits = ds_bound(most * inv, most_p * inv, delta), mark = 0;   // (where delta is not finite: once more, below)
         if (q_ok) {
             sa.store(reinterpret_cast<char *>(dq) + plane_off, (unsigned)(qlin * POSB), gr, scale * inv);
-            if (gr == 0) store_query<T>(ld + plane * plane_px * kQueryWords<T>, plane_px, (unsigned)qlin, g.two, start, base, delta + from, inv);
+            if (gr == 0) store_query<T>(ld + plane * plane_px * kQueryWords<T>, (unsigned)qlin, base, delta + from, inv);
         }
         unsigned long long again = __ballot(odd != odd);
         if (again) {
@@ -437,7 +434,7 @@ __global__ __launch_bounds__(kPatchThreads, (kPatchOcc<T, D>)) void patch_bwd_q_
                 float own_inv;
                 const float b2 = lane_value(base, c);
                 const float dl = query_once_more<T, D>(m, gc, scale, cy, cx, b2, dq + plane * plane_px * D, own, own_inv);
-                if (lane == 0) store_query<T>(ld + plane * plane_px * kQueryWords<T>, plane_px, (unsigned)(cy * W + cx), g.two, start, b2, dl, own_inv);
+                if (lane == 0) store_query<T>(ld + plane * plane_px * kQueryWords<T>, (unsigned)(cy * W + cx), b2, dl, own_inv);
                 if (own >= kNotFinite) mark = kMark;
                 else bits = bits > own ? bits : own;
             }
@@ -445,6 +442,231 @@ __global__ __launch_bounds__(kPatchThreads, (kPatchOcc<T, D>)) void patch_bwd_q_
         if (bound != nullptr) {
             bits = wave_max(bits) | mark;
             if (lane == 0) bound[(plane * ((H + 3) >> 2) + (sy0 >> 2)) * ((W + 3) >> 2) + (px0 >> 2)] = bits;
+        }
+    }
+}
+
+// The end of a query patch of a plane for the kernel with two to a wave: delta, dq, what part 2 needs, and the bound of the patch; queries whose results are not finite once more.
+template <typename T, int D>
+__device__ __forceinline__ void finish_queries(PosSum<T, D> &sa, const PosSum<T, D> &sp, float delta, float most, float most_p, float start, float from, bool q_ok,
+                                               int qlin, int lane, int sy0, int px0, size_t plane, int head, const T *q, const T *k, const T *v, const T *rpb, float scale,
+                                               const T *dout, T *dq, float *ld, uint32_t *bound, const PatchShape &g) {
+    using Op = PosOp<T, D>;
+    const int H = g.H, W = g.W, NB = 2 * g.K - 1, j = lane & 15, gr = lane >> 4;
+    const size_t plane_px = (size_t)H * W;
+    delta += __shfl_xor(delta, 16);
+    delta += __shfl_xor(delta, 32);
+#pragma unroll
+    for (int i = 0; i < Op::NA; ++i) sa.acc[i] -= delta * sp.acc[i];
+    const float odd = __builtin_fmaf(delta, 0.f, sa.not_finite());   // NaN where something is not finite
+    uint32_t bits = q_ok ? ds_bound(most, most_p, delta) : 0, mark = 0;   // (where delta is not finite: once more, below)
+    if (q_ok) {
+        sa.store(reinterpret_cast<char *>(dq) + plane * plane_px * Op::POSB, (unsigned)(qlin * Op::POSB), gr, scale);
+        if (gr == 0) store_starts(ld + plane * plane_px * kQueryWords<T>, plane_px, (unsigned)qlin, start, delta + from);
+    }
+    unsigned long long again = __ballot(odd != odd);
+    if (again) {
+        wait_global_loads();   // (the stores above come first)
+        PatchShape gc = g;     // (nothing of this is prepared outside of the branch)
+        asm volatile("" : "+s"(gc.H), "+s"(gc.W), "+s"(gc.K));
+        unsigned cols = (unsigned)((again | (again >> 16) | (again >> 32) | (again >> 48)) & 0xffffu);
+        if ((cols >> j) & 1u) bits = 0;
+        const PlanePtrs<T, D> m{q + plane * plane_px * D, k + plane * plane_px * D, v + plane * plane_px * D, dout + plane * plane_px * D,
+                                g.with_bias ? rpb + (size_t)head * NB * NB : nullptr};
+        for (; cols; cols &= cols - 1) {
+            const int c = __builtin_ctz(cols), cy = sy0 + (c >> 2), cx = px0 + (c & 3);
+            if (cy >= H || cx >= W) continue;
+            uint32_t own;
+            float own_inv;
+            const float s2 = lane_value(start, c);
+            const float dl = query_once_more<T, D>(m, gc, scale, cy, cx, s2 * -product_scale(scale), dq + plane * plane_px * D, own, own_inv);
+            if (lane == 0) store_starts(ld + plane * plane_px * kQueryWords<T>, plane_px, (unsigned)(cy * W + cx), s2, dl);
+            if (own >= kNotFinite) mark = kMark;
+            else bits = bits > own ? bits : own;
+        }
+    }
+    if (bound != nullptr) {
+        bits = wave_max(bits) | mark;
+        if (lane == 0) bound[(plane * ((H + 3) >> 2) + (sy0 >> 2)) * ((W + 3) >> 2) + (px0 >> 2)] = bits;
+    }
+}
+
+// Part 1 with two query patches to a wave, side by side (16 bit): they share the reads of the keys and values of a block and the bias row (the right
+// one's is the left one's of the block before), as in part 2.  85 -> 78 us at 64 x 2 x 56 x 56 fp16, k = 13: 30 vector instructions per 16 x 16 products in the
+// inner loop, as many again around it (a wave's prologue, its two patches' ends, the start of each row of blocks).
+template <typename T, int D>
+__global__ __launch_bounds__(kPatchThreads, 4) void patch_bwd_q2_kernel(
+    const T *__restrict__ q, const T *__restrict__ k, const T *__restrict__ v, const T *__restrict__ rpb, float scale,
+    const float *__restrict__ lse, const T *__restrict__ dout, T *__restrict__ dq, float *__restrict__ ld, uint32_t *__restrict__ bound, PatchShape g) {
+    static_assert(sizeof(T) == 2, "16 bit");
+    using CV = ChanVec<T, D>;
+    using Op = PosOp<T, D>;
+    constexpr int POSB = Op::POSB;
+    extern __shared__ __align__(16) char lds[];
+    const int wg = xcd_contiguous_block(blockIdx.x, gridDim.x);
+    if (wg >= g.units * g.splits) return;
+    const WorkItem work = decode_work(wg, g.heads, g.tiles_y, g.splits, g.gd);
+    const int head = work.head, K = g.K, H = g.H, W = g.W, NB = 2 * K - 1, pitch = bias_pitch(K);
+    const int tid = threadIdx.x, lane = tid % kWave, wave = __builtin_amdgcn_readfirstlane(tid / kWave);
+    const int bias0 = dynamic_lds(lds), img0 = bias0 + bias_rows(K, g.with_bias) * pitch * 4;
+    const int img_bytes = 4 * g.rw * POSB, stage_bytes = 2 * img_bytes;
+
+    const int lg = g.lg_cols, tw = 8 << lg, th = 32 >> lg, ty0 = work.ty * th, tx0 = work.tx * tw;
+    const int ty1 = ty0 + th - 1 < H - 1 ? ty0 + th - 1 : H - 1;
+    const int ry0 = win_start(ty0, H, K), cx0 = win_start(tx0, W, K);            // first key row and column of the tile
+    const int nsteps = (win_start(ty1, H, K) + K - ry0 + 3) >> 2;
+    const int sy0 = ty0 + 4 * (wave >> lg), px0 = tx0 + 8 * ((wave + 2 * (wave >> lg)) & ((1 << lg) - 1));   // this wave's left patch
+    const bool active = sy0 < H && px0 < W, two = px0 + 4 < W;
+    const int sy3 = sy0 + 3 < H - 1 ? sy0 + 3 : H - 1, pyc = sy0 < H ? sy0 : H - 1;
+    const int s_lo = (win_start(pyc, H, K) - ry0) >> 2, s_hi = (win_start(sy3, H, K) + K - 1 - ry0) >> 2;
+    const int pl0 = px0 < W ? px0 : W - 1, pl3 = px0 + 3 < W - 1 ? px0 + 3 : W - 1, pr0 = px0 + 4 < W - 1 ? px0 + 4 : W - 1, pr3 = px0 + 7 < W - 1 ? px0 + 7 : W - 1;
+    // blocks of a row, counted from the left patch's first: the left patch's last, the right one's first and last
+    const int ox = win_start(pl0, W, K), l_last = (win_start(pl3, W, K) + K - 1 - ox) >> 2;
+    const int r_first = two ? (win_start(pr0, W, K) - ox) >> 2 : l_last + 1, r_last = two ? (win_start(pr3, W, K) + K - 1 - ox) >> 2 : l_last;
+    // the first columns of the lane's windows; the columns that every query's window of a patch holds
+    const int kx = px0 + (lane & 3);
+    const int wx[2] = {win_start(kx < W ? kx : W - 1, W, K) - ox, win_start(kx + 4 < W ? kx + 4 : W - 1, W, K) - ox};
+    const int clear_l0 = win_start(pl3, W, K) - ox, clear_l1 = K, clear_r0 = win_start(pr3, W, K) - ox, clear_r1 = win_start(pr0, W, K) + K - ox;
+    const size_t plane_px = (size_t)H * W;
+    const auto own_lane = own_lane_index;   // (recomputed where it is used: the registers)
+    const auto query_of = [&](int lv, int right) {   // the lane's query of the left or the right patch, inside the map
+        const int y = sy0 + ((lv & 15) >> 2), x = px0 + (lv & 3) + right;
+        return (y < H - 1 ? y : H - 1) * W + (x < W - 1 ? x : W - 1);
+    };
+    const float scale2 = product_scale(scale), start = -1.f / scale2;
+
+    auto issue = [&](int b, int s, int par) {
+        const size_t off = ((size_t)b * g.heads + head) * plane_px * POSB;
+        const int img = img0 + par * stage_bytes;
+        issue_rows<POSB>(reinterpret_cast<const char *>(k) + off, reinterpret_cast<const char *>(v) + off, H, W, ry0 + 4 * s, cx0, g.rw, img, img_bytes, wave, lane);
+    };
+    if (work.b_begin < work.b_end) issue(work.b_begin, 0, 0);
+    stage_bias<T>(g.with_bias ? rpb + (size_t)head * NB * NB : nullptr, K, g.by_pitch, bias0, tid);
+
+    int par = 0;
+    for (int b = work.b_begin; b < work.b_end; ++b) {
+        const size_t plane = (size_t)b * g.heads + head;
+        CV qo[2], dO[2], vo[2];
+        f32x4 from_s[2], from_dp[2];   // what the products start from
+        const size_t plane_off = plane * plane_px * POSB;
+        const int lv0 = own_lane();
+#pragma unroll
+        for (int t = 0; t < 2; ++t) {
+            // (a plane is smaller than 2^31 bytes: one 32-bit offset per lane for all tensors)
+            const int at = query_of(lv0, 4 * t);
+            const unsigned off = (unsigned)(at * POSB + (lv0 >> 4) * CV::kLaneBytes);
+            qo[t].load(reinterpret_cast<const char *>(q) + plane_off + off);
+            dO[t].load(reinterpret_cast<const char *>(dout) + plane_off + off);
+            vo[t].load(reinterpret_cast<const char *>(v) + plane_off + off);
+            from_s[t][0] = (lse + plane * plane_px)[(unsigned)at];
+        }
+#pragma unroll
+        for (int t = 0; t < 2; ++t) settle(qo[t]), settle(dO[t]), settle(vo[t]);
+#pragma unroll
+        for (int t = 0; t < 2; ++t) {
+            const float from = near_mean(chan_dot<T, D>(vo[t], dO[t])), s0 = start * (from_s[t][0] * kLog2e);
+            from_s[t] = f32x4{s0, s0, s0, s0};
+            from_dp[t] = f32x4{-from, -from, -from, -from};
+        }
+        PosSum<T, D> sa[2], sp[2];   // sum of P dP k and of P k
+#pragma unroll
+        for (int t = 0; t < 2; ++t) sa[t].clear(), sp[t].clear();
+        float delta[2] = {0.f, 0.f}, most[2] = {0.f, 0.f}, most_p[2] = {0.f, 0.f};
+        for (int s = 0; s < nsteps; ++s) {
+            wait_global_loads();
+            workgroup_sync();   // this step's rows have landed for every wave, and nobody still reads the other buffer
+            const int img = img0 + par * stage_bytes;
+            const bool last = s + 1 == nsteps;
+            if (g.nstage == 2) {
+                par ^= 1;
+                if (!last || b + 1 < work.b_end) issue(last ? b + 1 : b, last ? 0 : s + 1, par);
+            }
+            if (active && s >= s_lo && s <= s_hi) {
+                // the lane's queries' row against its row of the block (like its places in the images worked out anew in each step, for the registers)
+                const int lv = own_lane(), j = lv & 15, gr = lv >> 4, x0 = ox - cx0;
+                const int iy = sy0 + (j >> 2) < H - 1 ? sy0 + (j >> 2) : H - 1, krow = ry0 + 4 * s + gr;
+                const bool rowok = (unsigned)(krow - win_start(iy, H, K)) < (unsigned)K;
+                const int u = krow - iy + K - 1, uc = u < 0 ? 0 : (u < NB - 1 ? u : NB - 1);
+                int brow = bias0 + ((rowok ? (g.with_bias ? uc : 0) : bias_rows(K, g.with_bias) - 1) * pitch + ox - px0 - (j & 3) + K - 1 + kBiasPad) * 4;
+                int a0 = img + ((j >> 2) * g.rw + x0 + (j & 3)) * POSB + gr * CV::kLaneBytes, t0 = img + Op::lane_offset(lv, g.rw) + x0 * POSB;
+                float before[4];   // the left patch's bias in the block before
+                if (r_first == 0) {
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) before[r] = *lds_ptr<float>(brow - 16 + r * 4);
+                }
+                // block column bx against the left patch (L), the right one (R) or both
+                const auto block = [&](auto left, auto right, int bx) {
+                    constexpr bool L = decltype(left)::value, R = decltype(right)::value;
+                    CV ka, va;
+                    ka.load_lds(a0);
+                    va.load_lds(a0 + img_bytes);
+                    float here[4], arg[2][4];
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) {
+                        if (L) arg[0][r] = here[r] = *lds_ptr<float>(brow + r * 4);
+                        if (R) arg[1][r] = L ? before[r] : *lds_ptr<float>(brow - 16 + r * 4);
+                    }
+                    // columns outside the window: weight 0 (decided before the products: no branch may come between one and the first use of its result,
+                    // see settle_products)
+#pragma unroll
+                    for (int t = 0; t < 2; ++t) {
+                        if (t == 0 ? !L : !R) continue;
+                        if (4 * bx < (t ? clear_r0 : clear_l0) || 4 * bx + 4 > (t ? clear_r1 : clear_l1)) {
+#pragma unroll
+                            for (int r = 0; r < 4; ++r) arg[t][r] = (unsigned)(4 * bx + r - wx[t]) < (unsigned)K ? arg[t][r] : -INFINITY;
+                        }
+                    }
+                    f32x4 s4[2], dp[2];
+#pragma unroll
+                    for (int t = 0; t < 2; ++t) {
+                        if (t == 0 ? !L : !R) continue;
+                        s4[t] = chan_dot<T, D>(ka, qo[t], from_s[t]);
+                        dp[t] = chan_dot<T, D>(va, dO[t], from_dp[t]);
+                    }
+                    Op kt;
+                    kt.load_lds(t0);
+#pragma unroll
+                    for (int t = 0; t < 2; ++t) {
+                        if (t == 0 ? !L : !R) continue;
+                        float p[4], w[4];
+#pragma unroll
+                        for (int r = 0; r < 4; ++r) {
+                            p[r] = __builtin_amdgcn_exp2f(__builtin_fmaf(scale2, s4[t][r], arg[t][r]));
+                            w[r] = p[r] * dp[t][r];
+                            delta[t] += w[r];
+                            most[t] = fmaxf(most[t], fabsf(w[r]));
+                            most_p[t] = fmaxf(most_p[t], p[r]);
+                        }
+                        sa[t].add(kt, Weights4<T>(w));
+                        sp[t].add(kt, Weights4<T>(p));
+                    }
+                    if (L) {
+#pragma unroll
+                        for (int r = 0; r < 4; ++r) before[r] = here[r];
+                    }
+                    a0 += 4 * POSB;
+                    t0 += 4 * POSB;
+                    brow += 16;
+                };
+                int bx = 0;
+                for (; bx < r_first; ++bx) block(IntC<1>{}, IntC<0>{}, bx);
+                for (; bx <= l_last; ++bx) block(IntC<1>{}, IntC<1>{}, bx);
+                for (; bx <= r_last; ++bx) block(IntC<0>{}, IntC<1>{}, bx);
+            }
+            if (g.nstage == 1 && (!last || b + 1 < work.b_end)) {
+                workgroup_sync();   // nobody still reads the rows
+                issue(last ? b + 1 : b, last ? 0 : s + 1, 0);
+            }
+        }
+        if (!active) continue;
+#pragma unroll
+        for (int t = 0; t < 2; ++t) sa[t].settle(), sp[t].settle();
+#pragma unroll
+        for (int t = 0; t < 2; ++t) {
+            if (t == 1 && !two) continue;
+            const int lv = own_lane(), qlin = query_of(lv, 4 * t);
+            const bool q_ok = sy0 + ((lv & 15) >> 2) < H && px0 + (lv & 3) + 4 * t < W;
+            finish_queries<T, D>(sa[t], sp[t], delta[t], most[t], most_p[t], from_s[t][0], -from_dp[t][0], q_ok, qlin, lv, sy0, px0 + 4 * t, plane, head, q, k, v, rpb, scale, dout, dq, ld, bound, g);
         }
     }
 }
@@ -1081,9 +1303,9 @@ int query_bytes(const Problem &p) { return 4 * (p.dtype == NA2D_F32 ? kQueryWord
 bool pairs_wanted(const Problem &p) {
     return p.dtype != NA2D_F32 && p.K > 13 && p.D <= 64 && (long long)p.planes() * ((p.H + 3) / 4) * ((p.W + 3) / 4) <= 2048;
 }
-// Two patches to a wave in part 2, in 16 bit with up to 32 channels (64: the registers leave two waves to a SIMD, 123 / 131 us at k = 7), where there are as many
-// patches as the chip has places for waves.  us of both parts and the bias gradient, one patch / two: 64 x 2 x 56 x 56 fp16 k = 11 (bf16) 205 / 191, k = 13
-// 226 / 198, k = 15 272 / 232, k = 21 437 / 348; 128 x 8 x 14 x 14 bf16 k = 13 125 / 102; 5000 patches k = 13 67.8 / 66.9; 4096 patches k = 11 45.3 / 46.4, k = 21 90 / 80; 2100 to 2600
+// Two patches to a wave in both parts, in 16 bit with up to 32 channels (64: the registers leave two waves to a SIMD, 123 / 131 us at k = 7), where there are as many
+// patches as the chip has places for waves.  us of both parts and the bias gradient, one patch / two: 64 x 2 x 56 x 56 fp16 k = 11 (bf16) 205 / 183, k = 13
+// 226 / 194, k = 21 438 / 336; 128 x 8 x 14 x 14 bf16 k = 13 125 / 93; 5000 patches k = 13 68 / 67; 4096 patches k = 11 45.3 / 46.4, k = 21 90 / 84; 2100 to 2600
 // patches k = 15 and 21 1.01 to 1.03 times as long, 780 patches k = 13 35 / 42.
 bool two_wanted(const Problem &p) {
     return p.dtype != NA2D_F32 && p.D <= 32 && (long long)p.planes() * ((p.H + 3) / 4) * ((p.W + 3) / 4) >= (p.K <= 13 ? 4160 : 4096);
@@ -1137,7 +1359,8 @@ PatchPlan patch_plan(const Problem &p, bool bias, bool dbias) {
             const long long steps2 = (long long)tx * ty * ((rows + 3) / 4);
             // (whether there are two is decided as with both tables: the number of partial bias gradients follows from it)
             const int most = bias_rows(K, true) * pitch * 4 + dbias_bytes<f16_t>(cells, 1), n = most + 2 * step <= room ? 2 : 1;
-            if (most + n * step > room || steps2 >= fewest) continue;
+            // (tiles that would take more than 5/8 of the ones of one patch to a wave have too many waves without a pair: 56 x 3 x 21 x 35, k = 11 85 / 91)
+            if (most + n * step > room || steps2 >= fewest || 8 * tx * ty * p.heads > 5 * us.units) continue;
             fewest = steps2;
             pl.two = true;
             pl.kv = s;
@@ -1153,6 +1376,27 @@ PatchPlan patch_plan(const Problem &p, bool bias, bool dbias) {
             pl.q.two = pl.kv.two = 1;
             pl.kv.copies = dbias && table + sums(4) + n * step <= room ? 4 : 1;
             pl.lds_kv = table + sums(pl.kv.copies) + n * step;
+        }
+        // part 1 likewise
+        fewest = LLONG_MAX;
+        for (int l = 2; l >= 0 && pl.two; --l) {
+            const int w = 8 << l, h = 32 >> l, rows = h + K - 1 < p.H ? h + K - 1 : p.H;
+            const int rw = image_row(p.W, K, w, posb, [&](int x) { return win_start(x, p.W, K); }, [&](int x) { return win_start(x, p.W, K) + K - 1; }, 8);
+            const int step = 2 * 4 * rw * posb, tx = (p.W + w - 1) / w, ty = (p.H + h - 1) / h, n = table + 2 * step <= room ? 2 : 1;
+            const long long steps2 = (long long)tx * ty * ((rows + 3) / 4);
+            if (table + n * step > room || steps2 >= fewest) continue;
+            fewest = steps2;
+            pl.q = s;
+            pl.q.rw = rw;
+            pl.q.lg_cols = l;
+            pl.q.tiles_y = ty;
+            pl.q.units = tx * ty * p.heads;
+            pl.q.splits = 8192 / pl.q.units;
+            pl.q.splits = pl.q.splits < 1 ? 1 : pl.q.splits < p.B ? pl.q.splits : p.B;
+            pl.q.gd = make_grid_decode(tx, ty, p.heads, p.B, pl.q.splits);
+            pl.q.nstage = n;
+            pl.q.two = 1;
+            pl.lds_q = table + n * step;
         }
     }
     if (pl.ok && pairs_wanted(p)) {
@@ -1195,32 +1439,26 @@ size_t bound_count(const Problem &p) { return (size_t)p.planes() * ((p.H + 3) / 
 template <typename T, int D>
 hipError_t launch_patch_bwd_t(const Problem &p, const PatchPlan &pl, const T *q, const T *k, const T *v, const T *rpb, float scale,
                               const float *lse, const T *dout, T *dq, T *dk, T *dv, float *ld, uint32_t *bound, float *partial, hipStream_t s) {
-    static LdsAllowed allowed_q, allowed_kv, allowed_pairs;
-    if (hipError_t e = allow_lds(patch_bwd_q_kernel<T, D>, 160 * 1024, allowed_q); e != hipSuccess) return e;
-    if (hipError_t e = allow_lds(patch_bwd_kv_kernel<T, D, 0>, 160 * 1024, allowed_kv); e != hipSuccess) return e;
-    const dim3 grid(xcd_padded_grid(pl.q.units * pl.q.splits));
-    hipLaunchKernelGGL((patch_bwd_q_kernel<T, D>), grid, dim3(kPatchThreads), pl.lds_q, s, q, k, v, rpb, scale, lse, dout, dq, ld, bound, pl.q);
-    if (hipError_t e = hipGetLastError(); e != hipSuccess) return e;
-    if constexpr (D * sizeof(T) <= 128 && sizeof(T) == 2) {
-        if (pl.pairs) {
-            if (hipError_t e = allow_lds(patch_bwd_kv_kernel<T, D, 1>, 160 * 1024, allowed_pairs); e != hipSuccess) return e;
-            hipLaunchKernelGGL((patch_bwd_kv_kernel<T, D, 1>), dim3(xcd_padded_grid(pl.kv.units * pl.kv.splits)), dim3(kPatchThreads), pl.lds_kv, s, q, k, v, rpb, scale,
-                               ld, bound, dout, dk, dv, partial, pl.kv);
-            return hipGetLastError();
-        }
-    }
+    const dim3 grid_q(xcd_padded_grid(pl.q.units * pl.q.splits)), grid_kv(xcd_padded_grid(pl.kv.units * pl.kv.splits)), threads(kPatchThreads);
+    const auto launch = [&](auto kern, LdsAllowed &allowed, dim3 grid, int lds, auto... args) -> hipError_t {
+        if (hipError_t e = allow_lds(kern, 160 * 1024, allowed); e != hipSuccess) return e;
+        hipLaunchKernelGGL(kern, grid, threads, lds, s, args...);
+        return hipGetLastError();
+    };
     if constexpr (D <= 32 && sizeof(T) == 2) {
         if (pl.two) {
-            static LdsAllowed allowed_two, allowed_two_no;
-            const auto kern = partial ? patch_bwd_kv2_kernel<T, D, true> : patch_bwd_kv2_kernel<T, D, false>;
-            if (hipError_t e = allow_lds(kern, 160 * 1024, partial ? allowed_two : allowed_two_no); e != hipSuccess) return e;
-            hipLaunchKernelGGL(kern, dim3(xcd_padded_grid(pl.kv.units * pl.kv.splits)), dim3(kPatchThreads), pl.lds_kv, s, q, k, v, rpb, scale,
-                               ld, bound, dout, dk, dv, partial, pl.kv);
-            return hipGetLastError();
+            static LdsAllowed allowed_q2, allowed_kv2[2];
+            if (hipError_t e = launch(patch_bwd_q2_kernel<T, D>, allowed_q2, grid_q, pl.lds_q, q, k, v, rpb, scale, lse, dout, dq, ld, bound, pl.q); e != hipSuccess) return e;
+            return launch(partial ? patch_bwd_kv2_kernel<T, D, true> : patch_bwd_kv2_kernel<T, D, false>, allowed_kv2[partial != nullptr], grid_kv, pl.lds_kv, q, k, v, rpb, scale, ld,
+                          bound, dout, dk, dv, partial, pl.kv);
         }
     }
-    hipLaunchKernelGGL((patch_bwd_kv_kernel<T, D, 0>), grid, dim3(kPatchThreads), pl.lds_kv, s, q, k, v, rpb, scale, ld, bound, dout, dk, dv, partial, pl.kv);
-    return hipGetLastError();
+    static LdsAllowed allowed_q, allowed_kv, allowed_pairs;
+    if (hipError_t e = launch(patch_bwd_q_kernel<T, D>, allowed_q, grid_q, pl.lds_q, q, k, v, rpb, scale, lse, dout, dq, ld, bound, pl.q); e != hipSuccess) return e;
+    if constexpr (D * sizeof(T) <= 128 && sizeof(T) == 2) {
+        if (pl.pairs) return launch(patch_bwd_kv_kernel<T, D, 1>, allowed_pairs, grid_kv, pl.lds_kv, q, k, v, rpb, scale, ld, bound, dout, dk, dv, partial, pl.kv);
+    }
+    return launch(patch_bwd_kv_kernel<T, D, 0>, allowed_kv, grid_kv, pl.lds_kv, q, k, v, rpb, scale, ld, bound, dout, dk, dv, partial, pl.kv);
 }
 
 }  // namespace

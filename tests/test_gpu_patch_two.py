@@ -1,4 +1,4 @@
-"""Key side of the patch backward with two key patches to a wave (16 bit, 16 and 32 channels, from 4160 patches on, k > 13 from 4096) against the
+"""The patch backward with two patches to a wave (16 bit, 16 and 32 channels, from 4160 patches on, k > 13 from 4096) against the
 oracle: maps whose last pair has one patch or a part of one, pairs at both borders at once, rows of blocks that only the left or the right patch
 meets, each tile shape, and windows whose images are loaded between the steps."""
 import numpy as np
