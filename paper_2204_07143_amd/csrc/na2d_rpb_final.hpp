@@ -16,11 +16,11 @@ struct RpbPartials {
 struct __attribute__((packed, aligned(4))) RpbQuad {
     f32x4 v;
 };
-// A workgroup per head and 64 cells: sixteen lanes own four neighbouring cells each (one 16-byte load per
-// partial); 64 groups of sixteen lanes take the partials in turn, eight loads in flight, and their sub-sums are added in group
-// order (whatever the number of threads that stand for the groups).  (With 256 cells to a workgroup few compute units work: 2 heads of 1024 partials
-// of 625 cells took 8 us, 2048 13.6.)
-constexpr int kRpbFinalLanes = 16, kRpbFinalGroups = 64, kRpbFinalLdsBytes = kRpbFinalGroups * kRpbFinalLanes * 16;
+// A workgroup per head and 16 cells: four lanes own four neighbouring cells each (one 16-byte load per
+// partial); 256 groups of four lanes take the partials in turn, eight loads in flight, and their sub-sums are added in group
+// order (whatever the number of threads that stand for the groups).  The time is the latency of a group's loads, one behind the other from eight
+// on, so few cells to a workgroup: with 64 of them 1 head of 1792 partials of 169 cells took 8.6 us, now 5.4; 2 heads of 1792 partials of 625 5.6, now 4.7.
+constexpr int kRpbFinalLanes = 4, kRpbFinalGroups = 256, kRpbFinalLdsBytes = kRpbFinalGroups * kRpbFinalLanes * 16;
 __host__ __device__ constexpr int rpb_final_blocks(int cells) { return (rpb_cell_stride(cells) / 4 + kRpbFinalLanes - 1) / kRpbFinalLanes; }   // per head
 
 // block `block` of heads * rpb_final_blocks(cells); sub0: kRpbFinalLdsBytes of LDS
@@ -47,18 +47,17 @@ template <int THREADS> __device__ __forceinline__ void rpb_final_block(const Rpb
         *lds_ptr<f32x4>(sub0 + (group * kRpbFinalLanes + lane) * 16) = acc;
     }
     workgroup_sync();
-    // four lanes of the first wave per cell quad: sixteen sub-sums each, then the four
-    if (threadIdx.x < 4 * kRpbFinalLanes) {
+    // sixteen lanes of the first wave per cell quad: sixteen sub-sums each, then the sixteen
+    if (threadIdx.x < kWave) {
+        static_assert(kRpbFinalGroups == 16 * (kWave / kRpbFinalLanes), "sub-sums");
         const int part = threadIdx.x / kRpbFinalLanes;
         const auto sub = [&](int w) { return *lds_ptr<f32x4>(sub0 + ((part * 16 + w) * kRpbFinalLanes + lane) * 16); };
-        f32x4 s = sub(0);
-        for (int w = 1; w < 16; ++w) s += sub(w);
-        f32x4 t;
+        f32x4 t = sub(0);
+        for (int w = 1; w < 16; ++w) t += sub(w);
 #pragma unroll
-        for (int c = 0; c < 4; ++c) {
-            const float a = s[c] + __shfl_xor(s[c], 16);
-            t[c] = a + __shfl_xor(a, 32);
-        }
+        for (int m = kRpbFinalLanes; m < kWave; m *= 2)
+#pragma unroll
+            for (int c = 0; c < 4; ++c) t[c] += __shfl_xor(t[c], m);
         if (part == 0 && cell0 < p.cells) {
 #pragma unroll
             for (int c = 0; c < 4; ++c)
