@@ -222,98 +222,64 @@ Tensor attention_like(const Tensor &q, int64_t ks) {
     return at::empty({s[0], s[1], s[2], s[3], ks * ks}, q.options());
 }
 
-struct QKRPB : torch::autograd::Function<QKRPB> {
-    static Tensor forward(AutogradContext *ctx, const Tensor &q_, const Tensor &k_, const std::optional<Tensor> &rpb_, int64_t ks, double scale) {
-        const Tensor q = q_.contiguous(), k = k_.contiguous(), rpb = rpb_ ? rpb_->contiguous() : Tensor();
-        const na2d_problem p = *problem_2d(q.sizes(), q.scalar_type(), ks);
-        Tensor logits = attention_like(q, ks);
-        forward_check(na2d_qk_rpb(&p, ptr(q), ptr(k), ptr(rpb), (float)scale, ptr(logits), stream()));
-        ctx->save_for_backward({q, k});
-        ctx->saved_data["shape"] = q.sizes().vec();
-        ctx->saved_data["k"] = ks;
-        ctx->saved_data["scale"] = scale;
-        ctx->saved_data["want_q"] = q_.requires_grad();
-        ctx->saved_data["want_k"] = k_.requires_grad();
-        ctx->saved_data["want_rpb"] = rpb_ && rpb_->requires_grad();
-        return logits;
-    }
-    static variable_list backward(AutogradContext *ctx, variable_list grads) {
-        const auto saved = ctx->get_saved_variables();
-        const int64_t ks = ctx->saved_data["k"].toInt();
-        const float scale = (float)ctx->saved_data["scale"].toDouble();
-        const Tensor ds = upstream(grads[0]);
-        const auto shape = ctx->saved_data["shape"].toIntVector();
-        const Tensor &q = readable(saved[0], ds, shape), &k = readable(saved[1], ds, shape);
-        const na2d_problem p = valid(problem_2d(shape, ds.scalar_type(), ks));
-        Tensor dq, dk, d_rpb;
-        if (ctx->saved_data["want_q"].toBool()) {
-            dq = at::empty(q.sizes(), q.options());
-            check(na2d_qk_bwd_q(&p, ptr(ds), ptr(k), scale, ptr(dq), stream()));
-        }
-        if (ctx->saved_data["want_k"].toBool()) {
-            dk = at::empty(k.sizes(), k.options());
-            check(na2d_qk_bwd_k(&p, ptr(ds), ptr(q), scale, ptr(dk), stream()));
-        }
-        if (ctx->saved_data["want_rpb"].toBool()) {
-            d_rpb = at::empty({q.size(1), 2 * ks - 1, 2 * ks - 1}, q.options());
-            const Tensor ws = workspace(na2d_workspace_bytes(&p, NA2D_WS_QK_BWD_RPB), q);
-            check(na2d_qk_bwd_rpb_typed(&p, ptr(ds), ptr(d_rpb), ptr(ws), (size_t)ws.numel(), stream()));
-        }
-        return {dq, dk, d_rpb, Tensor(), Tensor()};
-    }
-};
-
-struct AV : torch::autograd::Function<AV> {
-    static Tensor forward(AutogradContext *ctx, const Tensor &attn_, const Tensor &v_, int64_t ks) {
-        const Tensor attn = attn_.contiguous(), v = v_.contiguous();
-        const na2d_problem p = *problem_2d(v.sizes(), v.scalar_type(), ks);
+// One node for the three steps: the kernels and the results are those of the separate functions, the softmax and its backward work in place, and a pass
+// goes through autograd once (us a pass of 1 x 1 x 8 x 8 fp16, k = 7, forward and backward: three nodes 117, one 91; 64 x 2 x 56 x 56 fp16 180 / 176).
+struct Unfused : torch::autograd::Function<Unfused> {
+    // attn: where the weights are kept for the backward pass
+    static Tensor run(const Tensor &q, const Tensor &k, const Tensor &v, const Tensor &rpb, const na2d_problem &p, double scale, Tensor &attn) {
+        attn = attention_like(q, p.k);
+        forward_check(na2d_qk_rpb(&p, ptr(q), ptr(k), ptr(rpb), (float)scale, ptr(attn), stream()));
+        forward_check(na2d_softmax(&p, ptr(attn), ptr(attn), stream()));
         Tensor out = at::empty(v.sizes(), v.options());
         forward_check(na2d_av(&p, ptr(attn), ptr(v), ptr(out), stream()));
-        ctx->save_for_backward({attn, v});
+        return out;
+    }
+    static Tensor forward(AutogradContext *ctx, const Tensor &q_, const Tensor &k_, const Tensor &v_, const std::optional<Tensor> &rpb_, int64_t ks, double scale) {
+        const Tensor q = q_.contiguous(), k = k_.contiguous(), v = v_.contiguous(), rpb = rpb_ ? rpb_->contiguous() : Tensor();
+        Tensor attn;
+        Tensor out = run(q, k, v, rpb, *problem_2d(q.sizes(), q.scalar_type(), ks), scale, attn);
+        ctx->save_for_backward({q, k, v, attn});
         ctx->saved_data["k"] = ks;
-        ctx->saved_data["want_attn"] = attn_.requires_grad();
-        ctx->saved_data["want_v"] = v_.requires_grad();
+        ctx->saved_data["scale"] = scale;
+        ctx->saved_data["bias"] = (bool)rpb_;
         return out;
     }
     static variable_list backward(AutogradContext *ctx, variable_list grads) {
         const auto saved = ctx->get_saved_variables();
         const int64_t ks = ctx->saved_data["k"].toInt();
+        // (of this pass: what nothing asks for is not computed, as with a node per step)
+        const bool want_q = ctx->needs_input_grad(0), want_k = ctx->needs_input_grad(1), want_v = ctx->needs_input_grad(2);
+        const bool want_rpb = ctx->saved_data["bias"].toBool() && ctx->needs_input_grad(3);
+        const float scale = (float)ctx->saved_data["scale"].toDouble();
         const Tensor dout = upstream(grads[0]);
         const auto s = dout.sizes();
         const na2d_problem p = valid(problem_2d(s, dout.scalar_type(), ks));
-        const Tensor &attn = readable(saved[0], dout, {s[0], s[1], s[2], s[3], ks * ks}), &v = readable(saved[1], dout, s);
-        Tensor dattn, dv;
-        if (ctx->saved_data["want_attn"].toBool()) {
-            dattn = at::empty(attn.sizes(), attn.options());
-            check(na2d_av_bwd_p(&p, ptr(dout), ptr(v), ptr(dattn), stream()));
-        }
-        if (ctx->saved_data["want_v"].toBool()) {
-            dv = at::empty(v.sizes(), v.options());
+        const Tensor &q = readable(saved[0], dout, s), &k = readable(saved[1], dout, s), &v = readable(saved[2], dout, s);
+        const Tensor &attn = readable(saved[3], dout, {s[0], s[1], s[2], s[3], ks * ks});
+        Tensor dq, dk, dv, d_rpb;
+        if (want_v) {
+            dv = at::empty(s, dout.options());
             check(na2d_av_bwd_v(&p, ptr(attn), ptr(dout), ptr(dv), stream()));
         }
-        return {dattn, dv, Tensor()};
-    }
-};
-
-struct Softmax : torch::autograd::Function<Softmax> {
-    static Tensor forward(AutogradContext *ctx, const Tensor &logits_, at::IntArrayRef like, int64_t ks) {
-        const Tensor logits = logits_.contiguous();
-        const na2d_problem p = *problem_2d(like, logits.scalar_type(), ks);
-        Tensor attn = at::empty(logits.sizes(), logits.options());
-        forward_check(na2d_softmax(&p, ptr(logits), ptr(attn), stream()));
-        ctx->save_for_backward({attn});
-        ctx->saved_data["k"] = ks;
-        ctx->saved_data["like"] = like.vec();
-        return attn;
-    }
-    static variable_list backward(AutogradContext *ctx, variable_list grads) {
-        const auto saved = ctx->get_saved_variables();
-        const Tensor dattn = upstream(grads[0]);
-        const Tensor &attn = readable(saved[0], dattn, dattn.sizes());
-        const na2d_problem p = valid(problem_2d(ctx->saved_data["like"].toIntVector(), dattn.scalar_type(), ctx->saved_data["k"].toInt()));
-        Tensor ds = at::empty(attn.sizes(), attn.options());
-        check(na2d_softmax_bwd(&p, ptr(attn), ptr(dattn), ptr(ds), stream()));
-        return {ds, Tensor(), Tensor()};
+        if (want_q || want_k || want_rpb) {
+            const Tensor ds = attention_like(dout, ks);
+            check(na2d_av_bwd_p(&p, ptr(dout), ptr(v), ptr(ds), stream()));
+            check(na2d_softmax_bwd(&p, ptr(attn), ptr(ds), ptr(ds), stream()));
+            if (want_q) {
+                dq = at::empty(s, dout.options());
+                check(na2d_qk_bwd_q(&p, ptr(ds), ptr(k), scale, ptr(dq), stream()));
+            }
+            if (want_k) {
+                dk = at::empty(s, dout.options());
+                check(na2d_qk_bwd_k(&p, ptr(ds), ptr(q), scale, ptr(dk), stream()));
+            }
+            if (want_rpb) {
+                d_rpb = at::empty({s[1], 2 * ks - 1, 2 * ks - 1}, dout.options());
+                const Tensor ws = workspace(na2d_workspace_bytes(&p, NA2D_WS_QK_BWD_RPB), dout);
+                check(na2d_qk_bwd_rpb_typed(&p, ptr(ds), ptr(d_rpb), ptr(ws), (size_t)ws.numel(), stream()));
+            }
+        }
+        return {dq, dk, dv, d_rpb, Tensor(), Tensor()};
     }
 };
 
@@ -407,14 +373,16 @@ PyObject *py_na1d(PyObject *, PyObject *const *a, Py_ssize_t n) {
     });
 }
 
-// QK + bias, softmax and AV as three differentiable steps
+// QK + bias, softmax and AV by their own kernels
 PyObject *py_na2d_unfused(PyObject *, PyObject *const *a, Py_ssize_t n) {
     const Args x(a, n);
     if (!x.ok) Py_RETURN_NONE;
     return guarded([&]() -> Tensor {
-        if (!problem_2d(x.q.sizes(), x.q.scalar_type(), x.ks) || !x.check({x.q.size(1), 2 * x.ks - 1, 2 * x.ks - 1})) return Tensor();
-        const Tensor logits = QKRPB::apply(x.q, x.k, maybe(x.rpb), x.ks, x.scale);
-        return AV::apply(Softmax::apply(logits, x.q.sizes(), x.ks), x.v, x.ks);
+        const auto p = problem_2d(x.q.sizes(), x.q.scalar_type(), x.ks);
+        if (!p || !x.check({x.q.size(1), 2 * x.ks - 1, 2 * x.ks - 1})) return Tensor();
+        if (wants_grad({&x.q, &x.k, &x.v, &x.rpb})) return Unfused::apply(x.q, x.k, x.v, maybe(x.rpb), x.ks, x.scale);
+        Tensor attn;
+        return Unfused::run(x.q.contiguous(), x.k.contiguous(), x.v.contiguous(), x.rpb.defined() ? x.rpb.contiguous() : x.rpb, *p, x.scale, attn);
     });
 }
 

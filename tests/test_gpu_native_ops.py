@@ -168,3 +168,17 @@ def test_negated_views(name):
         assert all(torch.equal(g, w) for g, w in zip(got, want))
     with pytest.raises(ValueError):
         na.na2d_softmax(negated(q), 5, q, q)
+
+
+@pytest.mark.parametrize("which", [(0,), (1,), (2,), (3,), (0, 3), (1, 2)])
+@pytest.mark.parametrize("bias", [True, False])
+def test_unfused_gradients_of_some_inputs(which, bias):
+    """One pass may ask for the gradients of some of the inputs that require them."""
+    if not bias and 3 in which:
+        return
+    native, interpreted = OPS["unfused"]
+    (q, k, v, b), dout = inputs("unfused", torch.float16)
+    b = b if bias else None
+    leaves = [(q, k, v, b)[i] for i in which]
+    for g, w in zip(torch.autograd.grad(native(q, k, v, b, kernel_size=5), leaves, dout), torch.autograd.grad(interpreted(q, k, v, b, 5, None), leaves, dout)):
+        assert torch.equal(g, w)
