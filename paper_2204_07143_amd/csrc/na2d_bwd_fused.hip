@@ -240,8 +240,7 @@ __global__ __launch_bounds__(512, 4) void bwd_fused_small_kernel(const T *__rest
                 if ((e & 15) == 14) __builtin_amdgcn_sched_barrier(0);   // sixteen gathers in flight at a time
             }
         }
-        delta += __shfl_xor(delta, 16);
-        delta += __shfl_xor(delta, 32);
+        delta = column_sum(delta);
         // 4. ds, back into the row run (packed table: the addresses are unpacked again rather than kept since step 2)
         if constexpr (C::PACKED) {
 #pragma unroll

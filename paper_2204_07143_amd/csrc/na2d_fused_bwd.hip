@@ -280,8 +280,7 @@ __global__ __launch_bounds__(512, 4) void fbwd_q_kernel(const T *__restrict__ q,
             }
             __builtin_amdgcn_sched_barrier(0);   // keeps the blocks from being evaluated all at once
         }
-        delta += __shfl_xor(delta, 16);
-        delta += __shfl_xor(delta, 32);
+        delta = column_sum(delta);
         // fixed-point conversion of this lane's dS in this plane: |dS| <= P |dP - delta| <= dpmax + |delta|
         float fx_scale = 0.f;
         int fx_shift = 0;

@@ -225,8 +225,7 @@ __global__ __launch_bounds__(512, (FusedSmallCfg<T, K, NS>::kWavesPerSimd)) void
         float m = s[0];
 #pragma unroll
         for (int e = 1; e < P::NEL; ++e) m = fmaxf(m, s[e]);
-        m = fmaxf(m, __shfl_xor(m, 16));
-        m = fmaxf(m, __shfl_xor(m, 32));
+        m = column_max(m);
         m = q_ok ? m : 0.f;   // lanes without a query: keep the arithmetic finite
         // exp(s - m) as exp2(log2(e) s - m2): the subtraction of the maximum and the change of base are one fma
         const float m2 = m * kLog2e;
@@ -238,8 +237,7 @@ __global__ __launch_bounds__(512, (FusedSmallCfg<T, K, NS>::kWavesPerSimd)) void
         }
 #pragma unroll
         for (int e = P::NEL; e < 4 * C::NBLK2; ++e) s[e] = 0.f;   // padding block of the last pair
-        l += __shfl_xor(l, 16);
-        l += __shfl_xor(l, 32);
+        l = column_sum(l);
         // 4. O^T = V^T * P
         f32x4 o[NS][2];
 #pragma unroll

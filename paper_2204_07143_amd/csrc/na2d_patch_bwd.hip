@@ -54,13 +54,19 @@ __device__ __forceinline__ float wave_sum(float x) {
     for (int m = 1; m < kWave; m *= 2) x += __shfl_xor(x, m);
     return x;
 }
-__device__ __forceinline__ uint32_t wave_max(uint32_t x) {
-#pragma unroll
-    for (int m = 1; m < kWave; m *= 2) {
-        const uint32_t o = (uint32_t)__shfl_xor((int)x, m);
-        x = x > o ? x : o;
-    }
-    return x;
+template <int CTRL> __device__ __forceinline__ uint32_t dpp_max(uint32_t x) {
+    const uint32_t o = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, CTRL, 0xf, 0xf, true);
+    return x > o ? x : o;
+}
+__device__ __forceinline__ uint32_t wave_max(uint32_t x) {   // (the exchanges inside the vector ALU, see column_sum)
+    x = dpp_max<0xB1>(x);    // lane ^ 1
+    x = dpp_max<0x4E>(x);    // lane ^ 2
+    x = dpp_max<0x141>(x);   // the other half of eight lanes
+    x = dpp_max<0x140>(x);   // the other half of sixteen
+    const auto a = __builtin_amdgcn_permlane16_swap(x, x, false, false);
+    x = a[0] > a[1] ? a[0] : a[1];
+    const auto b = __builtin_amdgcn_permlane32_swap(x, x, false, false);
+    return b[0] > b[1] ? b[0] : b[1];
 }
 // |dS| = P |dP - delta| is at most this, given the largest P |dP| and P of the window; as bits (finite where delta is, infinity or NaN elsewhere)
 __device__ __forceinline__ uint32_t ds_bound(float most_pdp, float most_p, float delta) {
@@ -217,10 +223,8 @@ __device__ __forceinline__ void store_starts(float *ld, size_t plane_px, unsigne
 __device__ __forceinline__ float near_mean(const f32x4 &near) {
     float sum = (near[0] + near[1]) + (near[2] + near[3]);
     float squares = __builtin_fmaf(near[0], near[0], near[1] * near[1]) + __builtin_fmaf(near[2], near[2], near[3] * near[3]);
-    sum += __shfl_xor(sum, 16);
-    squares += __shfl_xor(squares, 16);
-    sum += __shfl_xor(sum, 32);
-    squares += __shfl_xor(squares, 32);
+    sum = column_sum(sum);
+    squares = column_sum(squares);
     const float mean = sum * (1.f / 16.f);
     return mean * mean > squares * (1.f / 32.f) ? mean : 0.f;   // (what is not finite: 0)
 }
@@ -401,12 +405,10 @@ __global__ __launch_bounds__(kPatchThreads, (kPatchOcc<T, D>)) void patch_bwd_q_
             sa.settle();
             sp.settle();
         }
-        delta += __shfl_xor(delta, 16);
-        delta += __shfl_xor(delta, 32);
+        delta = column_sum(delta);
         float inv = 1.f;
         if constexpr (kNormalised<T>) {
-            z += __shfl_xor(z, 16);
-            z += __shfl_xor(z, 32);
+            z = column_sum(z);
             inv = 1.f / z;
             delta *= inv;
         }
@@ -454,8 +456,7 @@ __device__ __forceinline__ void finish_queries(PosSum<T, D> &sa, const PosSum<T,
     using Op = PosOp<T, D>;
     const int H = g.H, W = g.W, NB = 2 * g.K - 1, j = lane & 15, gr = lane >> 4;
     const size_t plane_px = (size_t)H * W;
-    delta += __shfl_xor(delta, 16);
-    delta += __shfl_xor(delta, 32);
+    delta = column_sum(delta);
 #pragma unroll
     for (int i = 0; i < Op::NA; ++i) sa.acc[i] -= delta * sp.acc[i];
     const float odd = __builtin_fmaf(delta, 0.f, sa.not_finite());   // NaN where something is not finite
