@@ -10,8 +10,9 @@
 // Bias gradient: clear of the ends a lane's cells are the same for each of its groups, so that it adds them up in registers, in 64 bits; then they
 // join the workgroup's table as 64-bit fixed-point integers (integer additions commute: the result is bitwise reproducible).
 // A masked product is 0 * x: results that are not finite are computed once more from their own window.
-// Measured at 64 x 2 x 3136 queries, fp16, the call (a thread per position on the plain ALU before): k = 7 56.8 us, 24.5 the query side and 29.9 the key
-// side at 5.2 TB/s (72); k = 31 62.4 (163); k = 63 85 (369), where the vector instructions of 5 blocks show.
+// Up to k = 17 one kernel does both sides (below).
+// Measured at 64 x 2 x 3136 queries, fp16, the call (a thread per position on the plain ALU before): k = 7 46.9 us (72), in two kernels 24.5 the query side and 29.9 the key
+// side at 5.2 TB/s; k = 31 62.4 (163); k = 63 85 (369), where the vector instructions of 5 blocks show.
 #include "lds_attr.hpp"
 #include "na1d_common.hpp"
 #include "na1d_kernels.hpp"
@@ -440,9 +441,300 @@ hipError_t launch_t(const Problem &p, const void *q, const void *k, const void *
     return launch_rpb_final(tables, s);
 }
 
+// ---- both sides in one kernel (k <= 17) ---------------------------------------------------------------------------------------
+// A workgroup stages a tile of kWholeTile positions with the 16 in front of it and the 16 behind it once for both sides: every query that sees a key of
+// the tile (R in front, up to k - 1 behind) and the windows of those queries.  The two kernels are at the memory's rate and read q, k, v and dout once
+// each; here that is once in all (with a seventh more for the neighbours, from the L2).  The neighbours' queries are worked out as far as their
+// delta.  Groups lie where the two kernels have them, so the results are the same but for the order of the bias gradient's sums.
+// Measured (us, the call, two kernels / one): 64 x 2 x 3136 fp16, k = 7 58.2 / 46.9 (44 and the bias gradient's last sum, a launch of its own again; 180 MB at 4.1 TB/s),
+// bf16, k = 17 57.2 / 46.2; 256 x 16 x 197 fp16, k = 7 99.7 / 86.4; 1 x 1 x 64 23 / 20.  Wider windows have more neighbours, and their images leave no room for a second
+// workgroup on a compute unit.
+constexpr int kWholeWaves = 8, kWholeThreads = kWholeWaves * kWave, kWholeGroups = 2, kWholeTile = 14 * kGroup, kWholeK = 17;
+static_assert(kWholeWaves * kWholeGroups * kGroup == kWholeTile + 2 * kGroup, "queries of a tile");
+constexpr int kWholeKeyRows = kWholeTile + 2 * kGroup - kGroup + 32, kWholeQueryRows = kWholeTile + 2 * kGroup + 32;
+// the images, (lse, delta) per query, the bias as each lane of a group clear of the ends meets it, the bias and the integers of its gradient
+__host__ __device__ constexpr int whole_lds(int K) {
+    return 2 * (kWholeKeyRows + kWholeQueryRows) * kBytes + kWholeQueryRows * 8 + 2 * kWave * 16 + up16((2 * K - 1) * 4) + (2 * K - 1) * 8;
+}
+static_assert(whole_lds(kWholeK) <= 80 * 1024, "two workgroups share a compute unit");
+
+template <typename T>
+__global__ __launch_bounds__(kWholeThreads, 4) void bwd1d_whole_kernel(
+    const T *__restrict__ q, const T *__restrict__ k, const T *__restrict__ v, const T *__restrict__ rpb, float scale, const float *__restrict__ lse,
+    const T *__restrict__ dout, T *__restrict__ dq, T *__restrict__ dk, T *__restrict__ dv, long long *__restrict__ partial, int L, int heads, int K, int tiles) {
+    constexpr int NBLK = 2, kKeyImage = kWholeKeyRows * kBytes, kQueryImage = kWholeQueryRows * kBytes;
+    typedef float f32x2_t __attribute__((ext_vector_type(2)));
+    extern __shared__ __align__(16) char lds[];
+    const int tid = threadIdx.x, lane = tid % kWave, wave = __builtin_amdgcn_readfirstlane(tid / kWave), j = lane & 15, g = lane >> 4;
+    const int plane = blockIdx.x / tiles, t0 = (blockIdx.x - plane * tiles) * kWholeTile, t1 = t0 + kWholeTile - 1 < L - 1 ? t0 + kWholeTile - 1 : L - 1;
+    const int NB = 2 * K - 1, R = K >> 1;
+    const size_t first = (size_t)plane * L;
+    // the first staged query and key
+    const int h0q = t0 - kGroup > 0 ? t0 - kGroup : 0, h0k = win_start(h0q, L, K);
+    constexpr int kInner = NBLK * kWave * 16, kLd = 2 * (kKeyImage + kQueryImage), kBias = kLd + kWholeQueryRows * 8 + kInner;
+    const int img_k = lds_addr(lds), img_q = img_k + 2 * kKeyImage, ld0 = img_k + kLd, inner = ld0 + kWholeQueryRows * 8, cells = img_k + kBias + up16(NB * 4),
+              table = partial ? cells : 0;
+    float *bias = reinterpret_cast<float *>(lds + kBias);
+    stage_pair<kWholeWaves>(reinterpret_cast<const char *>(k) + (first + h0k) * kBytes, reinterpret_cast<const char *>(v) + (first + h0k) * kBytes, L - 1 - h0k,
+                            kWholeKeyRows, img_k, img_k + kKeyImage, wave, lane);
+    stage_pair<kWholeWaves>(reinterpret_cast<const char *>(q) + (first + h0q) * kBytes, reinterpret_cast<const char *>(dout) + (first + h0q) * kBytes, L - 1 - h0q,
+                            kWholeQueryRows, img_q, img_q + kQueryImage, wave, lane);
+    const T *own_rpb = rpb ? rpb + (size_t)(plane % heads) * NB : nullptr;
+    for (int u = tid; u < NB; u += kWholeThreads) {
+        bias[u] = own_rpb ? to_f32(own_rpb[u]) * kLog2e : 0.f;
+        if (partial) *lds_ptr<unsigned long long>(cells + u * 8) = 0ull;
+    }
+    for (int u = tid; u < kWholeQueryRows; u += kWholeThreads) *lds_ptr<f32x2_t>(ld0 + u * 8) = f32x2_t{0.f, 0.f};   // (rows without a query meet zero weights)
+    {
+        const int u = tid;   // (block, lane, result)
+        static_assert(NBLK * kWave * 4 == kWholeThreads, "entries");
+        const int a = 16 * (u >> 8) + 4 * ((u >> 6) & 3) + (u & 3) - ((u >> 2) & 15);   // slot in the window
+        const bool in = (unsigned)a < (unsigned)K;
+        const float t = own_rpb && in ? to_f32(own_rpb[a + K - 1 - R]) * kLog2e : 0.f;
+        *lds_ptr<float>(inner + u * 4) = in ? t : -INFINITY;
+    }
+    // this wave's two groups of queries, from the one in front of the tile on
+    const int g0 = t0 - kGroup + wave * kWholeGroups * kGroup;
+    const auto lse_of = [&](int i) { return lse[first + (i < 0 ? 0 : i < L ? i : L - 1)]; };
+    float lse0 = lse_of(g0 + j), lse1 = lse_of(g0 + kGroup + j);
+    asm volatile("" : "+v"(lse0), "+v"(lse1));   // (their wait goes here)
+    wait_global_loads();
+    workgroup_sync();
+
+    const float scale2 = scale * kLog2e;
+    double sums[NBLK][4];   // (four fp32 numbers to 2^-42 and beyond)
+#pragma unroll
+    for (int c = 0; c < NBLK; ++c)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) sums[c][r] = 0.;
+#pragma unroll 1
+    for (int n = 0; n < kWholeGroups; ++n) {
+        const int i0 = g0 + n * kGroup;
+        if (i0 < 0 || i0 >= L) continue;
+        const int o = win_start(i0, L, K), i = i0 + j < L ? i0 + j : L - 1;
+        const int w = win_start(i, L, K) - o;   // the lane's window begins at position w of the blocks
+        const bool clear = o == i0 - R && i0 + kGroup - 1 + R < L;
+        f32x4 b[NBLK];
+        if (clear) {
+#pragma unroll
+            for (int c = 0; c < NBLK; ++c) b[c] = *lds_ptr<f32x4>(inner + c * (kWave * 16) + lane * 16);
+        } else {
+#pragma unroll
+            for (int c = 0; c < NBLK; ++c)
+#pragma unroll
+                for (int r = 0; r < 4; ++r) {
+                    const int at = 16 * c + 4 * g + r;
+                    const bool in = (unsigned)(at - w) < (unsigned)K;
+                    const float t = bias[in ? at + o - i + K - 1 : 0];
+                    b[c][r] = in ? t : -INFINITY;
+                }
+        }
+        const int ka = row_addr(img_k, o - h0k, j, g), at_q = row_addr(img_q, i0 - h0q, j, g);
+        const u32x4 qv = *lds_ptr<u32x4>(at_q), gv = *lds_ptr<u32x4>(at_q + kQueryImage);
+        const float lse2 = (n == 0 ? lse0 : lse1) * kLog2e;
+        f32x4 s[NBLK], dp[NBLK];
+#pragma unroll
+        for (int c = 0; c < NBLK; ++c) {
+            s[c] = mfma_16x16x32<T>(*lds_ptr<u32x4>(ka + c * kGroup * kBytes), qv, f32x4{0.f, 0.f, 0.f, 0.f});
+            dp[c] = mfma_16x16x32<T>(*lds_ptr<u32x4>(ka + kKeyImage + c * kGroup * kBytes), gv, f32x4{0.f, 0.f, 0.f, 0.f});
+        }
+        float delta = 0.f;
+#pragma unroll
+        for (int c = 0; c < NBLK; ++c)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                s[c][r] = __builtin_amdgcn_exp2f(__builtin_fmaf(scale2, s[c][r], b[c][r]) - lse2);
+                delta = __builtin_fmaf(s[c][r], dp[c][r], delta);
+            }
+        delta = group_sum(delta);
+        if (i0 < t0 || i0 > t1) {   // the neighbours' queries: their delta is all that is needed
+            const unsigned again = marked_columns(delta * 0.f != 0.f);
+            if (((again >> j) & 1u) && i0 + j < L) {
+                VecN<T, 8> own[2];
+                float x[8];
+                load_vec32(own[0], q + (first + i) * kHeadDim + 8 * g);
+                load_vec32(own[1], dout + (first + i) * kHeadDim + 8 * g);
+                const int s0 = win_start(i, L, K), at = img_k + (s0 - h0k) * kBytes + g * 16, cell = s0 - i + K - 1;
+                query_once_more<T>(own, at, at + kKeyImage, bias + cell, scale, K, g, lse2, 0, cell, x, delta);
+            }
+            if (g == 0 && i0 + j < L) *lds_ptr<f32x2_t>(ld0 + (i - h0q) * 8) = f32x2_t{lse2, delta};
+            continue;
+        }
+        float most = 0.f;
+#pragma unroll
+        for (int c = 0; c < NBLK; ++c)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                s[c][r] *= dp[c][r] - delta;
+                most = fmaxf(most, fabsf(s[c][r]));
+            }
+        const int e = kShift<T> != 0.f ? lift(group_max(most)) : 0;
+        const float up = __builtin_ldexpf(1.f, e);
+        Split4<T> ws[NBLK];
+#pragma unroll
+        for (int c = 0; c < NBLK; ++c) {
+            const float t[4] = {s[c][0] * up, s[c][1] * up, s[c][2] * up, s[c][3] * up};
+            ws[c].set(t);
+        }
+        f32x4 acc[2] = {f32x4{0.f, 0.f, 0.f, 0.f}, f32x4{0.f, 0.f, 0.f, 0.f}};
+        weighted_sum<T, NBLK>(vector_addr(img_k, o - h0k, j, g), ws, acc);
+        const float back = scale * __builtin_ldexpf(1.f, -e);
+        float x[8], odd = delta * 0.f;   // odd: NaN where something is not finite
+#pragma unroll
+        for (int d = 0; d < 8; ++d) {
+            x[d] = acc[d >> 2][d & 3] * back;
+            odd = __builtin_fmaf(x[d], 0.f, odd);
+        }
+        const unsigned again = marked_columns(odd != odd);
+        const bool redo = (again >> j) & 1u, live = i0 + j < L;
+        if (partial) {
+            if (clear && again == 0 && __ballot(most >= 524288.f) == 0) {   // (2^19: the sum of two stays in the integers' range)
+#pragma unroll
+                for (int c = 0; c < NBLK; ++c)
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) sums[c][r] += s[c][r];
+            } else {
+#pragma unroll
+                for (int c = 0; c < NBLK; ++c)
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) {
+                        const int at = 16 * c + 4 * g + r;
+                        if (live && !redo && (unsigned)(at - w) < (unsigned)K) add_cell(cells, at + o - i + K - 1, s[c][r]);
+                    }
+            }
+        }
+        if (redo && live) {
+            VecN<T, 8> own[2];
+            load_vec32(own[0], q + (first + i) * kHeadDim + 8 * g);
+            load_vec32(own[1], dout + (first + i) * kHeadDim + 8 * g);
+            const int s0 = win_start(i, L, K), at = img_k + (s0 - h0k) * kBytes + g * 16, cell = s0 - i + K - 1;
+            query_once_more<T>(own, at, at + kKeyImage, bias + cell, scale, K, g, lse2, table, cell, x, delta);
+        }
+        if (live) {
+            store_vector<T>(reinterpret_cast<char *>(dq) + (first + i) * kBytes + g * 16, x);
+            if (g == 0) *lds_ptr<f32x2_t>(ld0 + (i - h0q) * 8) = f32x2_t{lse2, delta};
+        }
+    }
+    if (partial) {
+#pragma unroll
+        for (int c = 0; c < NBLK; ++c)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                const int a = 16 * c + 4 * g + r - j;   // slot in the window
+                if ((unsigned)a < (unsigned)K) add_cell(cells, a + K - 1 - R, sums[c][r]);
+            }
+    }
+    workgroup_sync();   // every query's delta and part of the bias gradient
+    if (partial)
+        for (int u = tid; u < NB; u += kWholeThreads) partial[(size_t)blockIdx.x * NB + u] = (long long)*lds_ptr<unsigned long long>(cells + u * 8);
+
+    float b[NBLK][4];
+    bool kept = false;   // b[] is that of a group clear of the ends
+#pragma unroll 1
+    for (int n = 0; n < kWholeGroups; ++n) {
+        const int j0 = t0 + (wave * kWholeGroups + n) * kGroup;
+        if (j0 > t1) break;
+        const int j1 = j0 + kGroup - 1 < L - 1 ? j0 + kGroup - 1 : L - 1, key = j0 + j < L ? j0 + j : L - 1;
+        const int o = inv_first(j0, L, K), blocks = (inv_last(j1, L, K) - o + kGroup) / kGroup;
+        const int lo = inv_first(key, L, K) - o, count = inv_last(key, L, K) - o - lo + 1;   // the queries that see the lane's key
+        const bool clear = j0 >= K && j0 + kGroup - 1 < L - K;
+        const int at_k = row_addr(img_k, (j0 - h0k), 0, g) + (key - j0) * kBytes;
+        const u32x4 kv = *lds_ptr<u32x4>(at_k), vv = *lds_ptr<u32x4>(at_k + kKeyImage);
+        f32x4 ak[2] = {f32x4{0.f, 0.f, 0.f, 0.f}, f32x4{0.f, 0.f, 0.f, 0.f}}, av[2] = {ak[0], ak[0]};
+        int e = 100;   // ak counts 2^-e
+#pragma unroll 1
+        for (int c0 = 0; c0 < blocks; c0 += NBLK) {
+            if (!(clear && kept)) {
+#pragma unroll
+                for (int c = 0; c < NBLK; ++c)
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) {
+                        const int at = 16 * (c0 + c) + 4 * g + r;
+                        const bool in = (unsigned)(at - lo) < (unsigned)count;
+                        const float t = bias[in ? key - o - at + K - 1 : 0];
+                        b[c][r] = in ? t + kShift<T> : -INFINITY;
+                    }
+                kept = clear;
+            }
+            const int pos = o - h0q + 16 * c0, qa = row_addr(img_q, pos, j, g), la = ld0 + (pos + 4 * g) * 8;
+            Split4<T> wp[NBLK], ws[NBLK];
+            f32x4 ds[NBLK];
+            float most = 0.f;
+#pragma unroll
+            for (int c = 0; c < NBLK; ++c) {
+                const f32x4 s = mfma_16x16x32<T>(*lds_ptr<u32x4>(qa + c * kGroup * kBytes), kv, f32x4{0.f, 0.f, 0.f, 0.f});
+                const f32x4 dp = mfma_16x16x32<T>(*lds_ptr<u32x4>(qa + kQueryImage + c * kGroup * kBytes), vv, f32x4{0.f, 0.f, 0.f, 0.f});
+                float p[4];
+#pragma unroll
+                for (int r = 0; r < 4; ++r) {
+                    const f32x2_t of = *lds_ptr<f32x2_t>(la + (16 * c + r) * 8);
+                    p[r] = __builtin_amdgcn_exp2f(__builtin_fmaf(scale2, s[r], b[c][r]) - of.x);
+                    ds[c][r] = p[r] * (dp[r] - of.y);
+                    most = fmaxf(most, fabsf(ds[c][r]));
+                }
+                wp[c].set(p);
+            }
+            if constexpr (kShift<T> != 0.f) {
+                const int lifted = lift(group_max(most)), both = lifted < e ? lifted : e;
+                if (c0 > 0) {
+                    const float down = __builtin_ldexpf(1.f, both - e);
+                    ak[0] *= down;
+                    ak[1] *= down;
+                }
+                e = both;
+            } else {
+                e = 0;
+            }
+            const float up = __builtin_ldexpf(1.f, e);
+#pragma unroll
+            for (int c = 0; c < NBLK; ++c) {
+                const float t[4] = {ds[c][0] * up, ds[c][1] * up, ds[c][2] * up, ds[c][3] * up};
+                ws[c].set(t);
+            }
+            weighted_sum<T, NBLK>(vector_addr(img_q + kQueryImage, pos, j, g), wp, av);
+            weighted_sum<T, NBLK>(vector_addr(img_q, pos, j, g), ws, ak);
+        }
+        settle_products<2>(ak);
+        settle_products<2>(av);
+        const float back_v = __builtin_ldexpf(1.f, (int)-kShift<T>), back_k = scale * __builtin_ldexpf(1.f, -e - (int)kShift<T>);
+        float xk[8], xv[8], odd = 0.f;
+#pragma unroll
+        for (int d = 0; d < 8; ++d) {
+            xk[d] = ak[d >> 2][d & 3] * back_k;
+            xv[d] = av[d >> 2][d & 3] * back_v;
+            odd = __builtin_fmaf(xk[d], 0.f, __builtin_fmaf(xv[d], 0.f, odd));
+        }
+        const unsigned again = marked_columns(odd != odd);
+        if (j0 + j >= L) continue;
+        if ((again >> j) & 1u) {
+            VecN<T, 8> own[2];
+            load_vec32(own[0], k + (first + key) * kHeadDim + 8 * g);
+            load_vec32(own[1], v + (first + key) * kHeadDim + 8 * g);
+            const int i0 = inv_first(key, L, K), at = img_q + (i0 - h0q) * kBytes + g * 16;
+            key_once_more<T>(own, at, at + kQueryImage, ld0 + (i0 - h0q) * 8, bias + (key - i0 + K - 1), scale, inv_last(key, L, K) - i0 + 1, xk, xv);
+        }
+        store_vector<T>(reinterpret_cast<char *>(dk) + (first + key) * kBytes + g * 16, xk);
+        store_vector<T>(reinterpret_cast<char *>(dv) + (first + key) * kBytes + g * 16, xv);
+    }
+}
+
+template <typename T>
+hipError_t launch_whole(const Problem &p, const void *q, const void *k, const void *v, const void *rpb, float scale, const float *lse, const void *dout,
+                        void *dq, void *dk, void *dv, long long *partial, BiasOut d_rpb, hipStream_t s) {
+    auto kern = bwd1d_whole_kernel<T>;
+    static LdsAllowed allowed;
+    if (hipError_t e = allow_lds(kern, whole_lds(kWholeK), allowed); e != hipSuccess) return e;
+    const int tiles = (p.L + kWholeTile - 1) / kWholeTile;
+    hipLaunchKernelGGL(kern, dim3(p.planes() * tiles), dim3(kWholeThreads), whole_lds(p.K), s, static_cast<const T *>(q), static_cast<const T *>(k), static_cast<const T *>(v),
+                       static_cast<const T *>(rpb), scale, lse, static_cast<const T *>(dout), static_cast<T *>(dq), static_cast<T *>(dk), static_cast<T *>(dv), partial,
+                       p.L, p.heads, p.K, tiles);
+    if (hipError_t e = hipGetLastError(); e != hipSuccess || !d_rpb) return e;
+    return launch_rpb_final(RpbTables{partial, d_rpb, p.B, p.heads, tiles, 2 * p.K - 1}, s);
+}
+
 template <typename T, typename... Args> hipError_t launch_blocks(const Problem &p, Args... args) {
     switch ((p.K + 15 + 15) / 16) {   // (k from 3 to 63)
-        case 2: return launch_t<T, 2>(p, args...);
+        case 2: return launch_t<T, 2>(p, args...);   // (calls that a launch of the one kernel would not hold)
         case 3: return launch_t<T, 3>(p, args...);
         case 4: return launch_t<T, 4>(p, args...);
         case 5: return launch_t<T, 5>(p, args...);
@@ -454,6 +746,13 @@ template <typename T, typename... Args> hipError_t launch_blocks(const Problem &
 
 hipError_t launch_fused_bwd_16bit(const Problem &p, const void *q, const void *k, const void *v, const void *rpb, float scale, const float *lse, const void *dout,
                                   void *dq, void *dk, void *dv, float *delta, long long *partial, BiasOut d_rpb, hipStream_t s) {
+    // one kernel: its tables, one per kWholeTile positions, lie from the workspace's first byte on (where the two kernels keep delta, which is no smaller than
+    // what they are more than one per 256 positions)
+    if (p.K <= kWholeK && launch_holds((long long)p.planes() * ((p.L + kWholeTile - 1) / kWholeTile), kWholeThreads)) {
+        long long *tables = partial ? reinterpret_cast<long long *>(delta) : nullptr;
+        return p.dtype == NA2D_F16 ? launch_whole<f16_t>(p, q, k, v, rpb, scale, lse, dout, dq, dk, dv, tables, d_rpb, s)
+                                   : launch_whole<bf16_t>(p, q, k, v, rpb, scale, lse, dout, dq, dk, dv, tables, d_rpb, s);
+    }
     return p.dtype == NA2D_F16 ? launch_blocks<f16_t>(p, q, k, v, rpb, scale, lse, dout, dq, dk, dv, delta, partial, d_rpb, s)
                                : launch_blocks<bf16_t>(p, q, k, v, rpb, scale, lse, dout, dq, dk, dv, delta, partial, d_rpb, s);
 }

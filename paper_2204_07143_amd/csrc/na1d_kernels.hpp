@@ -36,7 +36,7 @@ size_t fused_bwd_workspace_bytes(const Problem &p);
 hipError_t launch_fused_bwd(const Problem &p, const void *q, const void *k, const void *v, const void *rpb, float scale,
                             const float *lse, const void *dout, void *dq, void *dk, void *dv, na2d::BiasOut d_rpb, void *workspace,
                             hipStream_t s);
-// f16 / bf16; partial (null: no bias gradient is wanted): one table of integers per 256 positions of a plane
+// f16 / bf16; delta, partial: the two parts of the workspace; partial (null: no bias gradient is wanted): one table of integers per 256 positions of a plane
 hipError_t launch_fused_bwd_16bit(const Problem &p, const void *q, const void *k, const void *v, const void *rpb, float scale, const float *lse,
                                   const void *dout, void *dq, void *dk, void *dv, float *delta, long long *partial, na2d::BiasOut d_rpb, hipStream_t s);
 
