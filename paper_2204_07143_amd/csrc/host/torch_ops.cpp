@@ -222,14 +222,19 @@ Tensor attention_like(const Tensor &q, int64_t ks) {
     return at::empty({s[0], s[1], s[2], s[3], ks * ks}, q.options());
 }
 
-// One node for the three steps: the kernels and the results are those of the separate functions, the softmax and its backward work in place, and a pass
+// One node for the three steps: the kernels and the results are those of the separate functions, and a pass
 // goes through autograd once (us a pass of 1 x 1 x 8 x 8 fp16, k = 7, forward and backward: three nodes 117, one 91; 64 x 2 x 56 x 56 fp16 180 / 176).
 struct Unfused : torch::autograd::Function<Unfused> {
+    // Where the softmax and its backward work in place: the forward from 90 MB on, the backward below that (two of these tensors, or three, beside the
+    // last-level cache's 256 MB).  us of the forward, another tensor / in place: 64 x 2 x 56 x 56 fp16, k = 7 (39 MB) 54.4 / 55.3, k = 9 (65 MB) 74.8 / 75.9, k = 11 (97 MB) 103.6 /
+    // 99.1, k = 13 (136 MB) 139.5 / 124.6; of the backward k = 9 214 / 202, k = 11 294 / 303.
+    static bool large(const Tensor &t) { return t.nbytes() >= (size_t)90 << 20; }
     // attn: where the weights are kept for the backward pass
     static Tensor run(const Tensor &q, const Tensor &k, const Tensor &v, const Tensor &rpb, const na2d_problem &p, double scale, Tensor &attn) {
-        attn = attention_like(q, p.k);
-        forward_check(na2d_qk_rpb(&p, ptr(q), ptr(k), ptr(rpb), (float)scale, ptr(attn), stream()));
-        forward_check(na2d_softmax(&p, ptr(attn), ptr(attn), stream()));
+        const Tensor logits = attention_like(q, p.k);
+        forward_check(na2d_qk_rpb(&p, ptr(q), ptr(k), ptr(rpb), (float)scale, ptr(logits), stream()));
+        attn = large(logits) ? logits : attention_like(q, p.k);
+        forward_check(na2d_softmax(&p, ptr(logits), ptr(attn), stream()));
         Tensor out = at::empty(v.sizes(), v.options());
         forward_check(na2d_av(&p, ptr(attn), ptr(v), ptr(out), stream()));
         return out;
@@ -262,9 +267,10 @@ struct Unfused : torch::autograd::Function<Unfused> {
             check(na2d_av_bwd_v(&p, ptr(attn), ptr(dout), ptr(dv), stream()));
         }
         if (want_q || want_k || want_rpb) {
-            const Tensor ds = attention_like(dout, ks);
-            check(na2d_av_bwd_p(&p, ptr(dout), ptr(v), ptr(ds), stream()));
-            check(na2d_softmax_bwd(&p, ptr(attn), ptr(ds), ptr(ds), stream()));
+            const Tensor dp = attention_like(dout, ks);
+            check(na2d_av_bwd_p(&p, ptr(dout), ptr(v), ptr(dp), stream()));
+            const Tensor ds = large(dp) ? attention_like(dout, ks) : dp;
+            check(na2d_softmax_bwd(&p, ptr(attn), ptr(dp), ptr(ds), stream()));
             if (want_q) {
                 dq = at::empty(s, dout.options());
                 check(na2d_qk_bwd_q(&p, ptr(ds), ptr(k), scale, ptr(dq), stream()));
