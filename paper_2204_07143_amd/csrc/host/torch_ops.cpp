@@ -225,10 +225,11 @@ Tensor attention_like(const Tensor &q, int64_t ks) {
 // One node for the three steps: the kernels and the results are those of the separate functions, and a pass
 // goes through autograd once (us a pass of 1 x 1 x 8 x 8 fp16, k = 7, forward and backward: three nodes 117, one 91; 64 x 2 x 56 x 56 fp16 180 / 176).
 struct Unfused : torch::autograd::Function<Unfused> {
-    // Where the softmax and its backward work in place: the forward from 90 MB on, the backward below that (two of these tensors, or three, beside the
-    // last-level cache's 256 MB).  us of the forward, another tensor / in place: 64 x 2 x 56 x 56 fp16, k = 7 (39 MB) 54.4 / 55.3, k = 9 (65 MB) 74.8 / 75.9, k = 11 (97 MB) 103.6 /
-    // 99.1, k = 13 (136 MB) 139.5 / 124.6; of the backward k = 9 214 / 202, k = 11 294 / 303.
+    // Where the softmax and its backward work in place, and where grad-v stands: by what still lies in the 256 MB last-level cache.  us, 64 x 2 x 56 x 56 fp16,
+    // k = 7, 9, 11, 13 (39, 65, 97, 136 MB of weights): the forward with another tensor / in place 54.4 / 55.3, 74.8 / 75.9, 103.6 / 99.1, 139.5 / 124.6; the whole pass with another
+    // tensor for ds and grad-v behind grad-a 169.3, 288, 396, 488, in place 171.6, 278, 405, 486, with another and grad-v first 171.4, 288, 391, 481.
     static bool large(const Tensor &t) { return t.nbytes() >= (size_t)90 << 20; }
+    static bool in_place(const Tensor &dp) { return dp.nbytes() >= (size_t)48 << 20 && !large(dp); }
     // attn: where the weights are kept for the backward pass
     static Tensor run(const Tensor &q, const Tensor &k, const Tensor &v, const Tensor &rpb, const na2d_problem &p, double scale, Tensor &attn) {
         const Tensor logits = attention_like(q, p.k);
@@ -261,15 +262,20 @@ struct Unfused : torch::autograd::Function<Unfused> {
         const na2d_problem p = valid(problem_2d(s, dout.scalar_type(), ks));
         const Tensor &q = readable(saved[0], dout, s), &k = readable(saved[1], dout, s), &v = readable(saved[2], dout, s);
         const Tensor &attn = readable(saved[3], dout, {s[0], s[1], s[2], s[3], ks * ks});
-        Tensor dq, dk, dv, d_rpb;
-        if (want_v) {
+        Tensor dq, dk, dv, d_rpb, dp;
+        const bool want_ds = want_q || want_k || want_rpb;
+        const auto grad_v = [&] {
             dv = at::empty(s, dout.options());
             check(na2d_av_bwd_v(&p, ptr(attn), ptr(dout), ptr(dv), stream()));
-        }
-        if (want_q || want_k || want_rpb) {
-            const Tensor dp = attention_like(dout, ks);
+        };
+        if (want_v && large(attn)) grad_v();
+        if (want_ds) {
+            dp = attention_like(dout, ks);
             check(na2d_av_bwd_p(&p, ptr(dout), ptr(v), ptr(dp), stream()));
-            const Tensor ds = large(dp) ? attention_like(dout, ks) : dp;
+        }
+        if (want_v && !large(attn)) grad_v();   // (the weights are read once more right behind)
+        if (want_ds) {
+            const Tensor ds = in_place(dp) ? dp : attention_like(dout, ks);
             check(na2d_softmax_bwd(&p, ptr(attn), ptr(dp), ptr(ds), stream()));
             if (want_q) {
                 dq = at::empty(s, dout.options());
