@@ -115,7 +115,7 @@ struct GridDecode {
 };
 
 // Work split of the position-stationary kernels: a unit is a (tile position, head) pair; the batch is
-// cut into `splits` ranges so that about two workgroups per compute unit exist.
+// cut into `splits` ranges (see batch_splits()).
 static inline GridDecode make_grid_decode(int tiles_x, int tiles_y, int heads, int nb, int splits) {
     GridDecode gd;
     gd.npos = tiles_x * tiles_y;
@@ -127,6 +127,28 @@ static inline GridDecode make_grid_decode(int tiles_x, int tiles_y, int heads, i
     gd.range_rem = nb % splits;
     return gd;
 }
+// Ranges of the batch per unit.  As many as fill the 512 places (two workgroups on each of 256 compute units) in one round; more, up to four
+// rounds, where that is expected to take 5 % less.  A workgroup costs its tables (7) and its longest range (5 an item); places that
+// a round leaves empty cost the time all the same, but workgroups that are alone on their compute units, at most 256 of them, take 3/5.
+// fp16, k = 7, D = 32, us of the fused forward / fused backward / logits / weighted sum, one round (or one range) -> by the rule:
+// 288 units (96 x 96 x 4) of 10 items 28.9 / 92.9 / 26.7 / 21.1 -> 26.1 / 87.7 / 23.7 / 19.2 (576 workgroups); 384 (128 x 128 x 3) of 8, bf16
+// 30.4 / 97.2 / 23.7 / 19.0 -> 27.6 / 93.8 / 22.0 / 17.6 (768); 260 (100 x 80 x 4) of 10, k = 3 20.7 / 63.0 / 12.8 / 13.0 -> 15.7 / 54.2 / 11.0 / 10.4.
+// 280 (112 x 80 x 4) of 64 189 / 584 / 150 / 134 -> 139 / 459 / 116 / 106; 600 (80 x 160 x 6) of 8, bf16 51 / 182 / 31 / 30 -> 46 / 151 / 29 / 28.
+// Where it stays with one: 392 (112 x 112 x 4) of 8 24.8 / 90.4 / 23.6 / 18.9, in two ranges 27.5 / 94.7 / 25.2 / 20.0; 1050 (200 x 334 x 2) of 2
+// 22.3 / 69.4 / 20.7 / 15.6, in two 26.6 / 75.8 / 27.2 / 19.0.
+static inline int batch_splits(int units, int nb) {
+    constexpr int kPlaces = 512;
+    const auto cost = [=](int s) {
+        const long long n = (long long)units * s, rest = n % kPlaces;
+        return (5 * (n / kPlaces) + (rest == 0 ? 0 : rest <= kPlaces / 2 ? 3 : 5)) * (7 + 5 * ((nb + s - 1) / s));
+    };
+    int s = kPlaces / units;
+    s = s < 1 ? 1 : s;
+    s = s < nb ? s : nb;
+    for (int t = s + 1; t <= nb && (long long)units * t <= 4 * kPlaces; ++t)
+        if (100 * cost(t) <= 95 * cost(s)) s = t;
+    return s;
+}
 struct UnitSplit {
     int units, splits;
     GridDecode gd;
@@ -134,9 +156,7 @@ struct UnitSplit {
 static inline UnitSplit unit_split(int tiles_x, int tiles_y, int heads, int nb) {
     UnitSplit u;
     u.units = tiles_x * tiles_y * heads;
-    int s = (256 * 2) / u.units;
-    s = s < 1 ? 1 : s;
-    u.splits = s < nb ? s : nb;
+    u.splits = batch_splits(u.units, nb);
     u.gd = make_grid_decode(tiles_x, tiles_y, heads, nb, u.splits);
     return u;
 }

@@ -1,0 +1,42 @@
+"""Calls with more (tile position, head) units than fit the chip at once, or nearly: the batch is cut into ranges so that few places stay
+empty.  An item's results are those of a call of its own, whatever range it is in; the bias gradient is the sum over the items."""
+import pytest
+import torch
+
+from gpu_util import Stages, assert_close_rpb
+from paper_2204_07143_amd import synth
+
+pytestmark = pytest.mark.gpu
+
+
+def item(host, i):
+    return {n: x if n == "rpb" else x[i:i + 1] for n, x in host.items()}
+
+
+# units: 264 (two ranges of 4 and 5 items), 320 (three of 4), 288 at several tiles (two), 180 (four instead of two), 520 (two); 288 of 4 items: one
+@pytest.mark.parametrize("dtype", ["f16", "bf16"])
+@pytest.mark.parametrize("B,heads,H,W,D,k", [
+    (9, 264, 8, 16, 32, 7), (12, 320, 8, 13, 32, 5), (10, 72, 15, 30, 32, 7), (33, 90, 9, 16, 16, 3), (8, 520, 7, 7, 32, 7), (9, 144, 12, 16, 32, 9), (8, 144, 16, 13, 32, 13),
+    (9, 264, 8, 16, 64, 7), (4, 288, 8, 16, 32, 7)])
+def test_items_of_a_range(dtype, B, heads, H, W, D, k):
+    p = synth.Problem(B, heads, H, W, D, k, dtype)
+    host = synth.make_inputs(p, seed=H + W + k, rpb_std=0.5)
+    names = ("logits", "attn", "out", "out_fused", "lse", "dp", "ds", "dv", "dq", "dk")
+
+    def results(p, host):
+        st = Stages(p, host)
+        st.forward_unfused(), st.forward_fused(), st.backward_unfused()
+        fused = st.backward_fused() if k <= 9 and D <= 32 else ()
+        composed = st.backward_composed() if D <= 32 else ()   # (the strips' sums at 64 channels look at the call's size)
+        return [getattr(st, n) for n in names if D <= 32 or n not in ("dv", "dk")] + [*fused[:3], *composed[:3]], [st.d_rpb, *fused[3:], *composed[3:4]]
+
+    whole, sums = results(p, host)
+    parts = [torch.zeros_like(s, dtype=torch.float64) for s in sums]
+    for i in range(B):
+        one, s = results(synth.Problem(1, heads, H, W, D, k, dtype), item(host, i))
+        for n, (a, b) in enumerate(zip(whole, one)):
+            assert torch.equal(a[i:i + 1], b), f"item {i}, result {n}"
+        for t, x in zip(parts, s):
+            t += x
+    for t, x in zip(parts, sums):
+        assert_close_rpb("d_rpb", x.double(), t.cpu().numpy())
