@@ -311,9 +311,11 @@ static hipError_t launch_inverse_ring_t(const Problem &p, const void *w, const v
                                         hipStream_t s) {
     using C = InvRingCfg<T, K>;
     const int tiles_x = (p.W + kTileX - 1) / kTileX, tiles_y = (p.H + C::TY - 1) / C::TY;
-    // segments per column: enough workgroups for the chip's 512 slots, at least two tiles each where possible
-    int nseg = 512 / (p.planes() * tiles_x);
-    nseg = nseg < 1 ? 1 : (nseg > (tiles_y + 1) / 2 ? (tiles_y + 1) / 2 : nseg);
+    // segments per column, two tiles each or more: what a segment reads before its first tile costs about as much of a tile's time as the
+    // tables of the other kernels of an item's, and their rule holds.  One round of the 512 places -> by the rule, us, k = 7: 320 columns of 14 tiles (112 x 80 x
+    // 4 heads x 16) 40.4 -> 33 to 36, 300 of 8 24.4 -> 21.6, 352 of 8 24.8 -> 22.4, 192 of 16 (bf16) 25.2 -> 22.7; it leaves 512 of 7 and 960 of 5 whole
+    // (23.0, in two 27.1; 32.8, 38.5).
+    const int nseg = batch_splits(p.planes() * tiles_x, tiles_y, (tiles_y + 1) / 2);
     const int nwg = p.planes() * tiles_x * nseg;
     auto kern = inverse_ring_kernel<T, K>;
     static LdsAllowed allowed;

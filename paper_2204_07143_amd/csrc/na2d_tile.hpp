@@ -136,7 +136,7 @@ static inline GridDecode make_grid_decode(int tiles_x, int tiles_y, int heads, i
 // 280 (112 x 80 x 4) of 64 189 / 584 / 150 / 134 -> 139 / 459 / 116 / 106; 600 (80 x 160 x 6) of 8, bf16 51 / 182 / 31 / 30 -> 46 / 151 / 29 / 28.
 // Where it stays with one: 392 (112 x 112 x 4) of 8 24.8 / 90.4 / 23.6 / 18.9, in two ranges 27.5 / 94.7 / 25.2 / 20.0; 1050 (200 x 334 x 2) of 2
 // 22.3 / 69.4 / 20.7 / 15.6, in two 26.6 / 75.8 / 27.2 / 19.0.
-static inline int batch_splits(int units, int nb) {
+static inline int batch_splits(int units, int nb, int most) {   // at most `most` ranges
     constexpr int kPlaces = 512;
     const auto cost = [=](int s) {
         const long long n = (long long)units * s, rest = n % kPlaces;
@@ -144,8 +144,8 @@ static inline int batch_splits(int units, int nb) {
     };
     int s = kPlaces / units;
     s = s < 1 ? 1 : s;
-    s = s < nb ? s : nb;
-    for (int t = s + 1; t <= nb && (long long)units * t <= 4 * kPlaces; ++t)
+    s = s < most ? s : most;
+    for (int t = s + 1; t <= most && (long long)units * t <= 4 * kPlaces; ++t)
         if (100 * cost(t) <= 95 * cost(s)) s = t;
     return s;
 }
@@ -156,7 +156,7 @@ struct UnitSplit {
 static inline UnitSplit unit_split(int tiles_x, int tiles_y, int heads, int nb) {
     UnitSplit u;
     u.units = tiles_x * tiles_y * heads;
-    u.splits = batch_splits(u.units, nb);
+    u.splits = batch_splits(u.units, nb, nb);
     u.gd = make_grid_decode(tiles_x, tiles_y, heads, nb, u.splits);
     return u;
 }
