@@ -320,8 +320,10 @@ static hipError_t launch_inverse_mfma_c(const Problem &p, const void *w, const v
     const int tiles_x = (p.W + kTileX - 1) / kTileX, tiles_y = (p.H + C::TY - 1) / C::TY;
     // (tile position, head) units, the batch cut into ranges so that every workgroup slot of the chip is used
     const int units = tiles_x * tiles_y * p.heads;
+    // (two workgroups per compute unit: by the estimate.  One range / two, us, k = 9: 288 units (96 x 96 x 4 heads) of 10 items 64.4 / 56.2, 384 of 8 (bf16)
+    // 52.9 / 50.3, 336 of 10 63.8 / 56.1; it leaves 784 of 4 whole, 53.4 / 54.2, and at k = 7 416 of 8, 28.7 / 35.2)
     int splits = (256 * kWgPerCu) / units;
-    splits = splits < 1 ? 1 : (splits < p.B ? splits : p.B);
+    splits = kWgPerCu == 2 ? batch_splits(units, p.B, p.B) : splits < 1 ? 1 : (splits < p.B ? splits : p.B);
     const int nwg = units * splits;
     const GridDecode gd = make_grid_decode(tiles_x, tiles_y, p.heads, p.B, splits);
     auto kern = inverse_mfma_kernel<T, K, STRIPS, PPW, COMPACT, CHUNK>;

@@ -19,7 +19,9 @@ def item(host, i):
     (9, 264, 8, 16, 32, 7), (12, 320, 8, 13, 32, 5), (10, 72, 15, 30, 32, 7), (33, 90, 9, 16, 16, 3), (8, 520, 7, 7, 32, 7), (9, 144, 12, 16, 32, 9), (8, 144, 16, 13, 32, 13),
     (9, 264, 8, 16, 64, 7), (4, 288, 8, 16, 32, 7),
     # (columns of key tiles: 300 and 270 of 8 tiles, in two segments)
-    (10, 30, 64, 16, 32, 7), (9, 15, 61, 27, 16, 3)])
+    (10, 30, 64, 16, 32, 7), (9, 15, 61, 27, 16, 3),
+    # (the tile kernel of grad-v and grad-k: k = 9, and a map that the ring refuses)
+    (10, 72, 24, 17, 32, 9), (11, 36, 100, 16, 32, 7)])
 def test_items_of_a_range(dtype, B, heads, H, W, D, k):
     p = synth.Problem(B, heads, H, W, D, k, dtype)
     host = synth.make_inputs(p, seed=H + W + k, rpb_std=0.5)
