@@ -16,7 +16,10 @@
 #include <torch/csrc/PyInterpreter.h>
 #include <torch/csrc/autograd/custom_function.h>
 #include <torch/csrc/autograd/forward_grad.h>
+#include <torch/csrc/autograd/function.h>
+#include <torch/csrc/autograd/functions/utils.h>
 #include <torch/csrc/autograd/python_variable.h>
+#include <torch/csrc/autograd/saved_variable.h>
 #include <torch/csrc/jit/frontend/tracer.h>
 
 #include <cmath>
@@ -29,6 +32,7 @@ namespace {
 
 using at::Tensor;
 using torch::autograd::AutogradContext;
+using torch::autograd::SavedVariable;
 using torch::autograd::variable_list;
 
 // ---- checks ------------------------------------------------------------------------------------------------------------
@@ -222,76 +226,99 @@ Tensor attention_like(const Tensor &q, int64_t ks) {
     return at::empty({s[0], s[1], s[2], s[3], ks * ks}, q.options());
 }
 
-// One node for the three steps: the kernels and the results are those of the separate functions, and a pass
-// goes through autograd once (us a pass of 1 x 1 x 8 x 8 fp16, k = 7, forward and backward: three nodes 117, one 91; 64 x 2 x 56 x 56 fp16 180 / 176).
-struct Unfused : torch::autograd::Function<Unfused> {
-    // Where the softmax and its backward work in place, and where grad-v stands: by what still lies in the 256 MB last-level cache.  us, 64 x 2 x 56 x 56 fp16,
-    // k = 7, 9, 11, 13 (39, 65, 97, 136 MB of weights): the forward with another tensor / in place 54.4 / 55.3, 74.8 / 75.9, 103.6 / 99.1, 139.5 / 124.6; the whole pass with another
-    // tensor for ds and grad-v behind grad-a 169.3, 288, 396, 488, in place 171.6, 278, 405, 486, with another and grad-v first 171.4, 288, 391, 481.
-    static bool large(const Tensor &t) { return t.nbytes() >= (size_t)90 << 20; }
-    static bool in_place(const Tensor &dp) { return dp.nbytes() >= (size_t)48 << 20 && !large(dp); }
-    // attn: where the weights are kept for the backward pass
-    static Tensor run(const Tensor &q, const Tensor &k, const Tensor &v, const Tensor &rpb, const na2d_problem &p, double scale, Tensor &attn) {
-        const Tensor logits = attention_like(q, p.k);
-        forward_check(na2d_qk_rpb(&p, ptr(q), ptr(k), ptr(rpb), (float)scale, ptr(logits), stream()));
-        attn = large(logits) ? logits : attention_like(q, p.k);
-        forward_check(na2d_softmax(&p, ptr(logits), ptr(attn), stream()));
-        Tensor out = at::empty(v.sizes(), v.options());
-        forward_check(na2d_av(&p, ptr(attn), ptr(v), ptr(out), stream()));
-        return out;
+// Where the softmax and its backward work in place, and where grad-v stands: by what still lies in the 256 MB last-level cache.  us of the forward and of the whole pass,
+// always with another tensor and grad-v behind grad-a / by the rule: 39 MB of weights (64 x 2 x 56 x 56 fp16, k = 7) 57 and 174 / the same; from 48 MB on the backward in place:
+// 59 MB (96 items) - and 256 / 253, 62 MB (16 x 4 x 56 x 56 fp32, 16 channels, k = 9) - and 408 / 398, 65 MB (k = 9) - and 287 / 277, 79 MB (fp32, k = 7) - and 827 / 816, 512 x 8 x 14 x 14
+// fp16 - and 340 / 343; from 90 MB on the forward in place, grad-v first: 97 MB (k = 11) 102 / 100 and 397 / 390, 136 MB (k = 13) 139 / 126 and 490 / 481, 118 MB (768 x 8 x 14 x 14, k = 7)
+// 161 / 166 and 508 / 514, 157 MB (256 items) 217 / 209 and 636 / 636, 272 MB (128 items, k = 13) 270 / 265 and 955 / 954.
+bool large(const Tensor &t) { return t.nbytes() >= (size_t)90 << 20; }
+bool in_place(const Tensor &dp) { return dp.nbytes() >= (size_t)48 << 20 && !large(dp); }
+
+// attn: where the weights are kept for the backward pass
+Tensor unfused(const Tensor &q, const Tensor &k, const Tensor &v, const Tensor &rpb, const na2d_problem &p, double scale, Tensor &attn) {
+    const Tensor logits = attention_like(q, p.k);
+    forward_check(na2d_qk_rpb(&p, ptr(q), ptr(k), ptr(rpb), (float)scale, ptr(logits), stream()));
+    attn = large(logits) ? logits : attention_like(q, p.k);
+    forward_check(na2d_softmax(&p, ptr(logits), ptr(attn), stream()));
+    Tensor out = at::empty(v.sizes(), v.options());
+    forward_check(na2d_av(&p, ptr(attn), ptr(v), ptr(out), stream()));
+    return out;
+}
+
+// One node for the three steps: the kernels and the results are those of the separate functions, and a pass goes through autograd once
+// (us a pass of 1 x 1 x 8 x 8 fp16, k = 7, forward and backward: three nodes 119, one 100).
+// It keeps, and unpacks in a pass, what the separate nodes would: q and k only for gradients that need them, so that a program that does not ask for those may
+// have changed q and k in between.
+struct Unfused : torch::autograd::Node {
+    SavedVariable q, k, v, attn;
+    int64_t ks;
+    float scale;
+    std::string name() const override { return "NA2DUnfusedBackward"; }
+    void release_variables() override {
+        const std::lock_guard<std::mutex> lock(mutex_);
+        for (SavedVariable *s : {&q, &k, &v, &attn}) s->reset_data();
     }
-    static Tensor forward(AutogradContext *ctx, const Tensor &q_, const Tensor &k_, const Tensor &v_, const std::optional<Tensor> &rpb_, int64_t ks, double scale) {
-        const Tensor q = q_.contiguous(), k = k_.contiguous(), v = v_.contiguous(), rpb = rpb_ ? rpb_->contiguous() : Tensor();
-        Tensor attn;
-        Tensor out = run(q, k, v, rpb, *problem_2d(q.sizes(), q.scalar_type(), ks), scale, attn);
-        ctx->save_for_backward({q, k, v, attn});
-        ctx->saved_data["k"] = ks;
-        ctx->saved_data["scale"] = scale;
-        ctx->saved_data["bias"] = (bool)rpb_;
-        return out;
-    }
-    static variable_list backward(AutogradContext *ctx, variable_list grads) {
-        const auto saved = ctx->get_saved_variables();
-        const int64_t ks = ctx->saved_data["k"].toInt();
-        // (of this pass: what nothing asks for is not computed, as with a node per step)
-        const bool want_q = ctx->needs_input_grad(0), want_k = ctx->needs_input_grad(1), want_v = ctx->needs_input_grad(2);
-        const bool want_rpb = ctx->saved_data["bias"].toBool() && ctx->needs_input_grad(3);
-        const float scale = (float)ctx->saved_data["scale"].toDouble();
-        const Tensor dout = upstream(grads[0]);
+    variable_list apply(variable_list &&grads) override {
+        const std::lock_guard<std::mutex> lock(mutex_);
+        // (of this pass: what nothing asks for is not computed)
+        const bool want_q = task_should_compute_output(0), want_k = task_should_compute_output(1), want_v = task_should_compute_output(2), want_rpb = task_should_compute_output(3);
+        const bool want_ds = want_q || want_k || want_rpb;
+        const Tensor v_ = v.unpack(), attn_ = attn.unpack(), q_ = want_ds ? q.unpack() : Tensor(), k_ = want_ds ? k.unpack() : Tensor();
+        const Tensor dout = upstream(grads[0].defined() ? grads[0] : at::zeros_like(v_));
         const auto s = dout.sizes();
         const na2d_problem p = valid(problem_2d(s, dout.scalar_type(), ks));
-        const Tensor &q = readable(saved[0], dout, s), &k = readable(saved[1], dout, s), &v = readable(saved[2], dout, s);
-        const Tensor &attn = readable(saved[3], dout, {s[0], s[1], s[2], s[3], ks * ks});
+        readable(v_, dout, s), readable(attn_, dout, {s[0], s[1], s[2], s[3], ks * ks});
+        if (want_ds) readable(q_, dout, s), readable(k_, dout, s);
         Tensor dq, dk, dv, d_rpb, dp;
-        const bool want_ds = want_q || want_k || want_rpb;
         const auto grad_v = [&] {
             dv = at::empty(s, dout.options());
-            check(na2d_av_bwd_v(&p, ptr(attn), ptr(dout), ptr(dv), stream()));
+            check(na2d_av_bwd_v(&p, ptr(attn_), ptr(dout), ptr(dv), ::stream()));
         };
-        if (want_v && large(attn)) grad_v();
+        if (want_v && large(attn_)) grad_v();
         if (want_ds) {
             dp = attention_like(dout, ks);
-            check(na2d_av_bwd_p(&p, ptr(dout), ptr(v), ptr(dp), stream()));
+            check(na2d_av_bwd_p(&p, ptr(dout), ptr(v_), ptr(dp), ::stream()));
         }
-        if (want_v && !large(attn)) grad_v();   // (the weights are read once more right behind)
+        if (want_v && !large(attn_)) grad_v();   // (the weights are read once more right behind)
         if (want_ds) {
             const Tensor ds = in_place(dp) ? dp : attention_like(dout, ks);
-            check(na2d_softmax_bwd(&p, ptr(attn), ptr(dp), ptr(ds), stream()));
+            check(na2d_softmax_bwd(&p, ptr(attn_), ptr(dp), ptr(ds), ::stream()));
+            dp.reset();   // (its memory serves the gradients that follow)
             if (want_q) {
                 dq = at::empty(s, dout.options());
-                check(na2d_qk_bwd_q(&p, ptr(ds), ptr(k), scale, ptr(dq), stream()));
+                check(na2d_qk_bwd_q(&p, ptr(ds), ptr(k_), scale, ptr(dq), ::stream()));
             }
             if (want_k) {
                 dk = at::empty(s, dout.options());
-                check(na2d_qk_bwd_k(&p, ptr(ds), ptr(q), scale, ptr(dk), stream()));
+                check(na2d_qk_bwd_k(&p, ptr(ds), ptr(q_), scale, ptr(dk), ::stream()));
             }
             if (want_rpb) {
                 d_rpb = at::empty({s[1], 2 * ks - 1, 2 * ks - 1}, dout.options());
                 const Tensor ws = workspace(na2d_workspace_bytes(&p, NA2D_WS_QK_BWD_RPB), dout);
-                check(na2d_qk_bwd_rpb_typed(&p, ptr(ds), ptr(d_rpb), ptr(ws), (size_t)ws.numel(), stream()));
+                check(na2d_qk_bwd_rpb_typed(&p, ptr(ds), ptr(d_rpb), ptr(ws), (size_t)ws.numel(), ::stream()));
             }
         }
-        return {dq, dk, dv, d_rpb, Tensor(), Tensor()};
+        return {dq, dk, dv, d_rpb};
+    }
+    static Tensor of(const Tensor &q_, const Tensor &k_, const Tensor &v_, const Tensor &rpb_, const na2d_problem &p, double scale, bool record) {
+        Tensor out, attn;
+        std::shared_ptr<Unfused> node;
+        {
+            const at::AutoGradMode off(false);
+            const Tensor q = q_.contiguous(), k = k_.contiguous(), v = v_.contiguous();
+            out = unfused(q, k, v, rpb_.defined() ? rpb_.contiguous() : rpb_, p, scale, attn);
+            if (!record) return out;
+            node = std::shared_ptr<Unfused>(new Unfused, torch::autograd::deleteNode);
+            const bool want_ds = q_.requires_grad() || k_.requires_grad() || (rpb_.defined() && rpb_.requires_grad());
+            if (want_ds) node->q = SavedVariable(q, false), node->k = SavedVariable(k, false);
+            node->v = SavedVariable(v, false);
+            node->attn = SavedVariable(attn, false);
+            node->ks = p.k;
+            node->scale = (float)scale;
+        }
+        node->set_next_edges(torch::autograd::collect_next_edges(q_, k_, v_, rpb_));
+        torch::autograd::set_history(out, node);
+        return out;
     }
 };
 
@@ -392,9 +419,7 @@ PyObject *py_na2d_unfused(PyObject *, PyObject *const *a, Py_ssize_t n) {
     return guarded([&]() -> Tensor {
         const auto p = problem_2d(x.q.sizes(), x.q.scalar_type(), x.ks);
         if (!p || !x.check({x.q.size(1), 2 * x.ks - 1, 2 * x.ks - 1})) return Tensor();
-        if (wants_grad({&x.q, &x.k, &x.v, &x.rpb})) return Unfused::apply(x.q, x.k, x.v, maybe(x.rpb), x.ks, x.scale);
-        Tensor attn;
-        return Unfused::run(x.q.contiguous(), x.k.contiguous(), x.v.contiguous(), x.rpb.defined() ? x.rpb.contiguous() : x.rpb, *p, x.scale, attn);
+        return Unfused::of(x.q, x.k, x.v, x.rpb, *p, x.scale, wants_grad({&x.q, &x.k, &x.v, &x.rpb}));
     });
 }
 

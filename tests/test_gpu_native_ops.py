@@ -182,3 +182,33 @@ def test_unfused_gradients_of_some_inputs(which, bias):
     leaves = [(q, k, v, b)[i] for i in which]
     for g, w in zip(torch.autograd.grad(native(q, k, v, b, kernel_size=5), leaves, dout), torch.autograd.grad(interpreted(q, k, v, b, 5, None), leaves, dout)):
         assert torch.equal(g, w)
+
+
+@pytest.mark.parametrize("keeps", ["needs none", "asks for none"])
+def test_unfused_inputs_changed_before_a_pass_that_does_not_need_them(keeps):
+    """q and k may change in place between the passes where the backward pass is for v alone: because nothing else requires a gradient, or because it is asked
+    for nothing else.  Where their values are needed the change is an error."""
+    for op in OPS["unfused"][0], lambda *a, kernel_size: OPS["unfused"][1](*a, kernel_size, None):
+        (leaf, k, v, b), dout = inputs("unfused", torch.float16)
+        q, k, b = (t.detach() for t in (leaf, k, b)) if keeps == "needs none" else (t * 1 for t in (leaf, k, b))
+        want, = torch.autograd.grad(op(q, k, v, b, kernel_size=5), v, dout)
+        out = op(q, k, v, b, kernel_size=5)
+        q.add_(1), k.add_(1)
+        got, = torch.autograd.grad(out, v, dout, retain_graph=True)
+        assert torch.equal(got, want)
+        if keeps == "asks for none":
+            with pytest.raises(RuntimeError, match="modified by an inplace operation"):
+                torch.autograd.grad(out, leaf, dout, retain_graph=True)
+        torch.autograd.grad(out, v, dout)
+        with pytest.raises(RuntimeError, match="second time"):
+            torch.autograd.grad(out, v, dout)
+
+
+def test_unfused_keeps_what_the_gradients_need():
+    """With a gradient wanted for v alone neither q nor k stays alive for the backward pass."""
+    (q, k, v, b), dout = inputs("unfused", torch.float16)
+    kept = []
+    with torch.autograd.graph.saved_tensors_hooks(lambda t: kept.append(t.data_ptr()) or t, lambda t: t):
+        out = F.na2d_unfused(q.detach(), k.detach(), v, b.detach(), kernel_size=5)
+    assert v.data_ptr() in kept and len(kept) == 2
+    assert torch.autograd.grad(out, v, dout)[0].shape == v.shape
