@@ -10,7 +10,7 @@
 // Bias gradient: clear of the ends a lane's cells are the same for each of its groups, so that it adds them up in registers, in 64 bits; then they
 // join the workgroup's table as 64-bit fixed-point integers (integer additions commute: the result is bitwise reproducible).
 // A masked product is 0 * x: results that are not finite are computed once more from their own window.
-// Up to k = 17 one kernel does both sides (below).
+// Up to k = 17 one kernel does both sides for most calls (below).
 // Measured at 64 x 2 x 3136 queries, fp16, the call (a thread per position on the plain ALU before): k = 7 46.9 us (72), in two kernels 24.5 the query side and 29.9 the key
 // side at 5.2 TB/s; k = 31 62.4 (163); k = 63 85 (369), where the vector instructions of 5 blocks show.
 #include "lds_attr.hpp"
@@ -732,9 +732,21 @@ hipError_t launch_whole(const Problem &p, const void *q, const void *k, const vo
     return launch_rpb_final(RpbTables{partial, d_rpb, p.B, p.heads, tiles, 2 * p.K - 1}, s);
 }
 
+// One kernel or two, by their workgroups: the one kernel has 512 places (two to a compute unit), the key side of the two 768 (three).  us of the call, fp16, k = 7, one kernel / two:
+// - up to a round of the one kernel: 256 sequences of 250 17.9 / 18.4, 128 of 896 18.2 / 19.0, 16 of 4096 17.6 / 18.3;
+// - sequences of 225 to 256, one tile or two: 300 of 226 20.5 / 18.4, 512 of 250 26.0 / 19.0, 1024 of 226 45.6 / 30.6, 2048 of 250 78.7 / 65.0, 4096 of 225 160 / 105, of 256 152 / 126;
+// - fewer tiles of 256, in one round: 128 of 1024 22.3 / 19.0, of 1200 23.6 / 21.3, of 1400 27.0 / 22.5, 256 of 490 22.0 / 19.0, 32 of 6000 27.9 / 23.4; more than one: 128 of 1600 30.1 / 29.0, of
+//   1900 32.5 / 34.0, 32 of 9000 37.0 / 40.5, 640 of 490 41.7 / 43.5, 4096 of 449 224 / 258;
+// - as many of either: 576 of 100 18.3 / 19.0, of 224 20.8 / 20.8, 704 of 224 22.0 / 21.0, 1024 of 200 27.4 / 27.4, 4096 of 224 82 / 102, of 288 159 / 212.
+bool one_kernel(const Problem &p) {
+    if (p.K > kWholeK) return false;
+    const long long one = (long long)p.planes() * ((p.L + kWholeTile - 1) / kWholeTile), two = (long long)p.planes() * ((p.L + kTile - 1) / kTile);
+    return launch_holds(one, kWholeThreads) && (one <= 512 || (one < 2 * two && (one == two || two > 768)));
+}
+
 template <typename T, typename... Args> hipError_t launch_blocks(const Problem &p, Args... args) {
     switch ((p.K + 15 + 15) / 16) {   // (k from 3 to 63)
-        case 2: return launch_t<T, 2>(p, args...);   // (calls that a launch of the one kernel would not hold)
+        case 2: return launch_t<T, 2>(p, args...);
         case 3: return launch_t<T, 3>(p, args...);
         case 4: return launch_t<T, 4>(p, args...);
         case 5: return launch_t<T, 5>(p, args...);
@@ -748,7 +760,7 @@ hipError_t launch_fused_bwd_16bit(const Problem &p, const void *q, const void *k
                                   void *dq, void *dk, void *dv, float *delta, long long *partial, BiasOut d_rpb, hipStream_t s) {
     // one kernel: its tables, one per kWholeTile positions, lie from the workspace's first byte on (where the two kernels keep delta, which is no smaller than
     // what they are more than one per 256 positions)
-    if (p.K <= kWholeK && launch_holds((long long)p.planes() * ((p.L + kWholeTile - 1) / kWholeTile), kWholeThreads)) {
+    if (one_kernel(p)) {
         long long *tables = partial ? reinterpret_cast<long long *>(delta) : nullptr;
         return p.dtype == NA2D_F16 ? launch_whole<f16_t>(p, q, k, v, rpb, scale, lse, dout, dq, dk, dv, tables, d_rpb, s)
                                    : launch_whole<bf16_t>(p, q, k, v, rpb, scale, lse, dout, dq, dk, dv, tables, d_rpb, s);
