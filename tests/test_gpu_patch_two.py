@@ -6,11 +6,24 @@ import pytest
 import torch
 
 from gpu_util import Stages, assert_close, assert_close_rpb
+from paper_2204_07143_amd import binding as na
 from paper_2204_07143_amd import functional as F
 from paper_2204_07143_amd import synth
 from test_gpu_direct_bwd import assert_close_16bit, direct
 
 pytestmark = pytest.mark.gpu
+
+
+def call(st: Stages, with_rpb_grad=True):
+    """The gradients, and whether there were two patches to a wave: those keep -lse / scale of a plane's queries at the head of the workspace, one patch to a wave
+    pairs of log2(e) lse and delta."""
+    p = st.p
+    ws = torch.empty(na.na2d_direct_bwd_workspace_bytes(na.problem(p.B, p.heads, p.H, p.W, p.D, p.k, st.tdtype)), dtype=torch.uint8, device="cuda")
+    grads = [torch.empty_like(st.q) for _ in range(3)]
+    d_rpb = torch.empty((p.heads, 2 * p.k - 1, 2 * p.k - 1), dtype=torch.float32, device="cuda") if with_rpb_grad else None
+    na.na2d_direct_bwd(st.q, st.key, st.v, st.rpb, st.scale, st.lse, st.dout, p.k, *grads, d_rpb, ws)
+    lse = st.lse[0, 0].flatten()
+    return (*grads, d_rpb), torch.allclose(ws[:4 * lse.numel()].view(torch.float32) * -(st.scale or 2.0 ** -100), lse, rtol=1e-5, atol=1e-5)
 
 
 def check(oracle, p, seed, use_rpb=True, scale=None):
@@ -44,6 +57,31 @@ def test_backward_two_patches_to_a_wave(oracle, dtype, B, heads, H, W, D, k, use
 def test_scales(oracle, scale):
     # the products start from -lse / scale
     check(oracle, synth.Problem(470, 1, 11, 12, 32, 11, "f16"), seed=4, scale=scale)
+
+
+@pytest.mark.parametrize("dtype", ["f16", "bf16"])
+def test_large_logits(oracle, dtype):
+    """Logits up to 1600: an exponent is off by a few units of 2^-24 of the lse, 1e-4, with one patch to a wave and with two, whose products start from -lse / scale: rounded
+    once, and the sums once more at that size, it may add 1.25 of the others' error, not 1.5 (three roundings)."""
+    p = synth.Problem(128, 1, 26, 27, 32, 13, dtype)
+    host = synth.make_inputs(p, 5)
+    host["q"], host["k"] = host["q"] * 16, host["k"] * 16
+
+    def results(host, B):
+        st = Stages(synth.Problem(B, 1, 26, 27, 32, 13, dtype), host)
+        st.forward_fused()
+        return call(st)
+
+    many, two = results(host, 128)
+    assert two
+    halves = [results({n: x if n == "rpb" else x[i:i + 64] for n, x in host.items()}, 64) for i in (0, 64)]
+    assert not any(two for _, two in halves)
+    few = [torch.cat(t) if n < 3 else t[0] + t[1] for n, t in enumerate(zip(*(g for g, _ in halves)))]
+    host = {n: x.astype(np.float64) for n, x in host.items()}
+    want = oracle.bwd(host["q"], host["k"], host["v"], host["rpb"], p.default_scale, host["dout"], p.k)
+    for n, a, b, o in zip(("dq", "dk", "dv", "d_rpb"), many, few, want):
+        err = [np.sqrt(((x.double().cpu().numpy() - o) ** 2).mean()) for x in (a, b)]
+        assert err[0] <= 1.25 * err[1], (n, err)
 
 
 @pytest.mark.parametrize("where", ["q", "k", "v", "dout"])
