@@ -1305,16 +1305,21 @@ int query_bytes(const Problem &p) { return 4 * (p.dtype == NA2D_F32 ? kQueryWord
 // Pairs of waves in part 2: where one wave per patch leaves half of the chip's 4096 places for waves free, wide windows in 16 bit last as long as
 // the patch of a border takes (81 blocks at k = 21, one inside 36).  us of both parts and the bias gradient, fp16, 32 channels, one wave / two: k = 15
 // 40 / 34 at 256 patches, 44 / 39 at 1300, 43 / 42 at 2048, 60 / 67 at 4096; k = 21 62 / 48, 64 / 53, 66 / 62, 92 / 95.  Between (16 to 64 channels, three
-// maps, two waves' time over one's): k = 15 0.89 .. 1.04 to 2600 patches, 0.93 .. 1.14 from there; k = 21 0.87 .. 1.00 to 2600, 0.91 .. 1.05 from there.  (Up to k = 13 no choice looks at the batch.)
+// maps, two waves' time over one's): k = 15 0.89 .. 1.04 to 2600 patches, 0.93 .. 1.14 from there; k = 21 0.87 .. 1.00 to 2600, 0.91 .. 1.05 from there.
 bool pairs_wanted(const Problem &p) {
     return p.dtype != NA2D_F32 && p.K > 13 && p.D <= 64 && (long long)p.planes() * ((p.H + 3) / 4) * ((p.W + 3) / 4) <= 2048;
 }
-// Two patches to a wave in both parts, in 16 bit with up to 32 channels (64: the registers leave two waves to a SIMD, 123 / 131 us at k = 7), where there are as many
-// patches as the chip has places for waves.  us of both parts and the bias gradient, one patch / two: 64 x 2 x 56 x 56 fp16 k = 11 (bf16) 205 / 183, k = 13
-// 226 / 194, k = 21 438 / 336; 128 x 8 x 14 x 14 bf16 k = 13 125 / 93; 5000 patches k = 13 68 / 67; 4096 patches k = 11 45.3 / 46.4, k = 21 90 / 84; 2100 to 2600
-// patches k = 15 and 21 1.01 to 1.03 times as long, 780 patches k = 13 35 / 42.
-bool two_wanted(const Problem &p) {
-    return p.dtype != NA2D_F32 && p.D <= 32 && (long long)p.planes() * ((p.H + 3) / 4) * ((p.W + 3) / 4) >= (p.K <= 13 ? 4160 : 4096);
+// Two patches to a wave in both parts, in 16 bit with up to 32 channels (64: the registers leave two waves to a SIMD, 123 / 131 us at k = 7), from as many patches on as the chip
+// has places for waves, where half as many workgroups, which last 1.5 to 1.7 times as long, end earlier.  The rounds of both grids tell (in fifths, one patch / two): us of both parts and the bias
+// gradient, one patch / two, k = 11 and k = 13, 56 x 56 10 / 5 (32 planes) 72 / 65 and 76 / 66, 18 / 10 (62) 116 / 108 and 125 / 110, 35 / 18 (128) 221 / 184 and 241 / 186, 28 x 28 10 / 5 (127) 71 / 63 and 82 / 70, 18 / 10
+// (245) 118 / 113 and 134 / 127, k = 15 and 21 15 / 8 (184) 117 / 113 and 172 / 149; left alone 56 x 56 8 / 5 (22) 60 / 65 and 62 / 65, 13 / 8 (42) 86 / 89 and 94 / 90, 28 x 28 8 / 5 (86) 59 / 62 and 67 / 69, 13 / 8 (166)
+// 88 / 90 and 101 / 103, 64 x 100, k = 15 and 21, 8 / 5 (11) 83 / 79 and 118 / 124.  With up to 256 workgroups 56 x 56 5 / 3 (18) 43 / 49 and 46 / 49.
+// Less is enough where a tile's waves meet the same blocks: on maps at most a pair wider than the window, 14 x 14 8 / 5 (263) 51 / 50 and 56 / 52, 13 x 13 13 / 8 (513) 76 / 71 and 86 / 73, 17 x 17 13 / 8 (224) 74 / 67 and
+// 81 / 69, and in tiles of 8 columns over all rows of a low map, 21 x 35 8 / 5 (78) 61 / 54 and 67 / 60, 20 / 13 (223) 128 / 124 and 142 / 132, 18 x 39, k = 13, 13 / 8 (103) 81 / 73, 25 x 34, k = 21, 8 / 5 (66) 115 / 103; 31 x 37, k = 15, 8 / 5 (52) 75 / 82.
+bool two_wanted(const Problem &p, int one, const PatchShape &two) {   // one: workgroups per item
+    const long long n = (long long)two.units * p.B, r1 = fifths_of_rounds((long long)one * p.B), r2 = fifths_of_rounds(n);
+    const bool alike = p.W <= p.K + 8 || (two.lg_cols == 0 && p.H <= 28);
+    return n > kPlaces / 2 && (alike ? 2 * r1 >= 3 * r2 : 3 * r1 >= 5 * r2);
 }
 PatchPlan patch_plan(const Problem &p, bool bias, bool dbias) {
     PatchPlan pl{};
@@ -1354,55 +1359,45 @@ PatchPlan patch_plan(const Problem &p, bool bias, bool dbias) {
         pl.lds_kv = lds4;
     }
     pl.ok = pl.q.nstage > 0 && pl.kv.nstage > 0;
-    if (pl.ok && two_wanted(p)) {
-        // the tile with the least steps whose buffers leave room for a second workgroup
-        long long fewest = LLONG_MAX;
-        const int room = 80 * 1024;
-        for (int l = 2; l >= 0; --l) {
-            const int w = 8 << l, h = 32 >> l, rows = h + K - 1 < p.H ? h + K - 1 : p.H;
-            const int rw = image_row(p.W, K, w, posb, [&](int x) { return inv_first(x, p.W, K); }, [&](int x) { return inv_last(x, p.W, K); }, 8);
-            const int step = 2 * 4 * rw * posb + 4 * rw * query_bytes(p), tx = (p.W + w - 1) / w, ty = (p.H + h - 1) / h;
-            const long long steps2 = (long long)tx * ty * ((rows + 3) / 4);
-            // (whether there are two is decided as with both tables: the number of partial bias gradients follows from it)
-            const int most = bias_rows(K, true) * pitch * 4 + dbias_bytes<f16_t>(cells, 1), n = most + 2 * step <= room ? 2 : 1;
-            // (tiles that would take more than 5/8 of the ones of one patch to a wave have too many waves without a pair: 56 x 3 x 21 x 35, k = 11 85 / 91)
-            if (most + n * step > room || steps2 >= fewest || 8 * tx * ty * p.heads > 5 * us.units) continue;
-            fewest = steps2;
+    const bool wide = p.dtype != NA2D_F32 && p.D <= 32 && (long long)p.planes() * ((p.H + 3) / 4) * ((p.W + 3) / 4) >= 4096;
+    if (pl.ok && wide) {
+        // Each part: the tile with the least steps whose buffers leave room for a second workgroup.  (What looks at the tables takes both, whatever the call has: the number of
+        // partial bias gradients follows from the choice.)
+        const int room = 80 * 1024, bias_table = bias_rows(K, true) * pitch * 4;
+        const auto shape = [&](int fixed, int record, int most_tiles, auto first, auto last, PatchShape &of) {   // record: bytes per streamed position beside its vectors
+            long long fewest = LLONG_MAX;
+            for (int l = 2; l >= 0; --l) {
+                const int w = 8 << l, h = 32 >> l, rows = h + K - 1 < p.H ? h + K - 1 : p.H;
+                const int rw = image_row(p.W, K, w, posb, first, last, 8), step = 4 * rw * (2 * posb + record), tx = (p.W + w - 1) / w, ty = (p.H + h - 1) / h;
+                const long long steps2 = (long long)tx * ty * ((rows + 3) / 4);
+                if (fixed + step > room || steps2 >= fewest || tx * ty > most_tiles) continue;
+                fewest = steps2;
+                of = s;
+                of.rw = rw;
+                of.lg_cols = l;
+                of.tiles_y = ty;
+                of.units = tx * ty * p.heads;
+                // a plane per workgroup, so that a compute unit gets tiles next to borders and others alike, until the partial bias gradients would be many
+                of.splits = 8192 / of.units;
+                of.splits = of.splits < 1 ? 1 : of.splits < p.B ? of.splits : p.B;
+                of.gd = make_grid_decode(tx, ty, p.heads, p.B, of.splits);
+                of.nstage = fixed + 2 * step <= room ? 2 : 1;
+                of.two = 1;
+            }
+            return fewest < LLONG_MAX;
+        };
+        PatchShape q2, kv2;   // (part 2: with more than 5/8 as many tiles as with one patch to a wave too many waves have no pair)
+        if (shape(bias_table, 0, INT_MAX, [&](int x) { return win_start(x, p.W, K); }, [&](int x) { return win_start(x, p.W, K) + K - 1; }, q2) &&
+            shape(bias_table + dbias_bytes<f16_t>(cells, 1), query_bytes(p), tiles_x * tiles_y * 5 / 8, [&](int x) { return inv_first(x, p.W, K); }, [&](int x) { return inv_last(x, p.W, K); }, kv2) &&
+            two_wanted(p, us.units, kv2)) {
             pl.two = true;
-            pl.kv = s;
-            pl.kv.rw = rw;
-            pl.kv.lg_cols = l;
-            pl.kv.tiles_y = ty;
-            pl.kv.units = tx * ty * p.heads;
-            // a plane per workgroup, so that a compute unit gets tiles next to borders and others alike, until the partial bias gradients would be many
-            pl.kv.splits = 8192 / pl.kv.units;
-            pl.kv.splits = pl.kv.splits < 1 ? 1 : pl.kv.splits < p.B ? pl.kv.splits : p.B;
-            pl.kv.gd = make_grid_decode(tx, ty, p.heads, p.B, pl.kv.splits);
-            pl.kv.nstage = n;
-            pl.q.two = pl.kv.two = 1;
-            pl.kv.copies = dbias && table + sums(4) + n * step <= room ? 4 : 1;
-            pl.lds_kv = table + sums(pl.kv.copies) + n * step;
-        }
-        // part 1 likewise
-        fewest = LLONG_MAX;
-        for (int l = 2; l >= 0 && pl.two; --l) {
-            const int w = 8 << l, h = 32 >> l, rows = h + K - 1 < p.H ? h + K - 1 : p.H;
-            const int rw = image_row(p.W, K, w, posb, [&](int x) { return win_start(x, p.W, K); }, [&](int x) { return win_start(x, p.W, K) + K - 1; }, 8);
-            const int step = 2 * 4 * rw * posb, tx = (p.W + w - 1) / w, ty = (p.H + h - 1) / h, n = table + 2 * step <= room ? 2 : 1;
-            const long long steps2 = (long long)tx * ty * ((rows + 3) / 4);
-            if (table + n * step > room || steps2 >= fewest) continue;
-            fewest = steps2;
-            pl.q = s;
-            pl.q.rw = rw;
-            pl.q.lg_cols = l;
-            pl.q.tiles_y = ty;
-            pl.q.units = tx * ty * p.heads;
-            pl.q.splits = 8192 / pl.q.units;
-            pl.q.splits = pl.q.splits < 1 ? 1 : pl.q.splits < p.B ? pl.q.splits : p.B;
-            pl.q.gd = make_grid_decode(tx, ty, p.heads, p.B, pl.q.splits);
-            pl.q.nstage = n;
-            pl.q.two = 1;
-            pl.lds_q = table + n * step;
+            const int step_q = 4 * q2.rw * 2 * posb, step_kv = 4 * kv2.rw * (2 * posb + query_bytes(p));
+            q2.nstage = table + 2 * step_q <= room ? 2 : 1;
+            kv2.copies = dbias && table + sums(4) + kv2.nstage * step_kv <= room ? 4 : 1;
+            pl.q = q2;
+            pl.kv = kv2;
+            pl.lds_q = table + q2.nstage * step_q;
+            pl.lds_kv = table + sums(kv2.copies) + kv2.nstage * step_kv;
         }
     }
     if (pl.ok && pairs_wanted(p)) {
@@ -1419,8 +1414,6 @@ PatchPlan patch_plan(const Problem &p, bool bias, bool dbias) {
             if (steps2 >= fewest) continue;
             fewest = steps2;
             pl.pairs = true;
-            pl.two = false;
-            pl.q.two = 0;
             const int fixed = table + (dbias ? ints : 0), fixed4 = table + (dbias ? table_bytes<f16_t>(cells, 4) + flag_bytes(cells) : 0);
             pl.kv = s;
             pl.kv.rw = rw;

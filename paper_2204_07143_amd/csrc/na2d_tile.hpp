@@ -127,9 +127,15 @@ static inline GridDecode make_grid_decode(int tiles_x, int tiles_y, int heads, i
     gd.range_rem = nb % splits;
     return gd;
 }
+// The time of a grid of n workgroups, two to a compute unit, in fifths of that of one round of the chip's 512 places: places that a round leaves empty cost the
+// time all the same, but workgroups that are alone on their compute units, at most 256 of them, take 3/5.
+constexpr int kPlaces = 512;
+static inline long long fifths_of_rounds(long long n) {
+    const long long rest = n % kPlaces;
+    return 5 * (n / kPlaces) + (rest == 0 ? 0 : rest <= kPlaces / 2 ? 3 : 5);
+}
 // Ranges of the batch per unit.  As many as fill the 512 places (two workgroups on each of 256 compute units) in one round; more, up to four
-// rounds, where that is expected to take 5 % less.  A workgroup costs its tables (7) and its longest range (5 an item); places that
-// a round leaves empty cost the time all the same, but workgroups that are alone on their compute units, at most 256 of them, take 3/5.
+// rounds, where that is expected to take 5 % less.  A workgroup costs its tables (7) and its longest range (5 an item).
 // fp16, k = 7, D = 32, us of the fused forward / fused backward / logits / weighted sum, one round (or one range) -> by the rule:
 // 288 units (96 x 96 x 4) of 10 items 28.9 / 92.9 / 26.7 / 21.1 -> 26.1 / 87.7 / 23.7 / 19.2 (576 workgroups); 384 (128 x 128 x 3) of 8, bf16
 // 30.4 / 97.2 / 23.7 / 19.0 -> 27.6 / 93.8 / 22.0 / 17.6 (768); 260 (100 x 80 x 4) of 10, k = 3 20.7 / 63.0 / 12.8 / 13.0 -> 15.7 / 54.2 / 11.0 / 10.4.
@@ -137,11 +143,7 @@ static inline GridDecode make_grid_decode(int tiles_x, int tiles_y, int heads, i
 // Where it stays with one: 392 (112 x 112 x 4) of 8 24.8 / 90.4 / 23.6 / 18.9, in two ranges 27.5 / 94.7 / 25.2 / 20.0; 1050 (200 x 334 x 2) of 2
 // 22.3 / 69.4 / 20.7 / 15.6, in two 26.6 / 75.8 / 27.2 / 19.0.
 static inline int batch_splits(int units, int nb, int most) {   // at most `most` ranges
-    constexpr int kPlaces = 512;
-    const auto cost = [=](int s) {
-        const long long n = (long long)units * s, rest = n % kPlaces;
-        return (5 * (n / kPlaces) + (rest == 0 ? 0 : rest <= kPlaces / 2 ? 3 : 5)) * (7 + 5 * ((nb + s - 1) / s));
-    };
+    const auto cost = [=](int s) { return fifths_of_rounds((long long)units * s) * (7 + 5 * ((nb + s - 1) / s)); };
     int s = kPlaces / units;
     s = s < 1 ? 1 : s;
     s = s < most ? s : most;
