@@ -212,3 +212,25 @@ def test_unfused_keeps_what_the_gradients_need():
         out = F.na2d_unfused(q.detach(), k.detach(), v, b.detach(), kernel_size=5)
     assert v.data_ptr() in kept and len(kept) == 2
     assert torch.autograd.grad(out, v, dout)[0].shape == v.shape
+
+
+# (MiB of weights: below 48 the softmax and its backward have another tensor; from there the backward works in place, from 90 the forward, and grad-v comes first)
+@pytest.mark.parametrize("dtype,shape,k,mib", [(torch.float16, (24, 2, 56, 56, 32), 9, 23), (torch.float16, (61, 2, 56, 56, 32), 9, 59), (torch.float32, (40, 2, 57, 56, 32), 7, 47),
+                                               (torch.float32, (44, 2, 57, 56, 32), 7, 52), (torch.float16, (64, 2, 56, 56, 32), 11, 92), (torch.bfloat16, (48, 2, 56, 57, 32), 13, 98)])
+def test_unfused_in_place(dtype, shape, k, mib):
+    """The same bits as the interpreted functions on either side of the sizes from which tensors are overwritten: twice, for some of the gradients, and without any."""
+    native, interpreted = OPS["unfused"]
+    torch.manual_seed(k)
+    q, key, v, dout = (torch.randn(shape, device="cuda").to(dtype) for _ in range(4))
+    b = torch.randn((shape[1], 2 * k - 1, 2 * k - 1), device="cuda").to(dtype)
+    assert shape[0] * shape[1] * shape[2] * shape[3] * k * k * q.element_size() >> 20 == mib
+    with torch.no_grad():
+        want = interpreted(q, key, v, b, k, None)
+        assert torch.equal(native(q, key, v, b, kernel_size=k), want)
+    leaves = [t.requires_grad_() for t in (q, key, v, b)]
+    out, want = native(q, key, v, b, kernel_size=k), interpreted(q, key, v, b, k, None)
+    assert torch.equal(out, want)
+    for which in ((0, 1, 2, 3), (2,), (0, 3), (1, 2), (0, 1, 2, 3)):
+        some = [leaves[i] for i in which]
+        for g, w in zip(torch.autograd.grad(out, some, dout, retain_graph=True), torch.autograd.grad(want, some, dout, retain_graph=True)):
+            assert torch.equal(g, w)
