@@ -283,7 +283,6 @@ struct Unfused : torch::autograd::Node {
         if (want_ds) {
             const Tensor ds = in_place(dp) ? dp : attention_like(dout, ks);
             check(na2d_softmax_bwd(&p, ptr(attn_), ptr(dp), ptr(ds), ::stream()));
-            dp.reset();   // (its memory serves the gradients that follow)
             if (want_q) {
                 dq = at::empty(s, dout.options());
                 check(na2d_qk_bwd_q(&p, ptr(ds), ptr(k_), scale, ptr(dq), ::stream()));
