@@ -332,7 +332,7 @@ __global__ __launch_bounds__(512, 4) void fbwd_q_kernel(const T *__restrict__ q,
             if (!half_dim || g < 2)
                 store16_stream(dst, u32x4{pack2_t<T>(o[0][0] * scale, o[0][1] * scale), pack2_t<T>(o[0][2] * scale, o[0][3] * scale),
                                           pack2_t<T>(o[1][0] * scale, o[1][1] * scale), pack2_t<T>(o[1][2] * scale, o[1][3] * scale)});
-            if (g == 0) {   // for the key-patch kernel: delta, and the log-sum-exp in the exp2 domain
+            if (g == 0) {   // for the key-patch kernel: the log-sum-exp, natural, and delta
                 typedef float f32x2_t __attribute__((ext_vector_type(2)));
                 *reinterpret_cast<f32x2_t *>(stat + 2 * (plane * H * W + qlin)) = f32x2_t{lse1, delta};
             }

@@ -12,8 +12,8 @@
 //      private (2K-1)^2 LDS table one query at a time.  The workgroup's wave tables are added
 //      in wave order and written to the workspace as one partial per workgroup, the partials
 //      of a head next to each other (rpb_cell_stride);
-//   2. a second kernel adds the partials of each head, four cells per lane: 16 waves each sum
-//      a strided subset in index order, then the 16 sub-sums are added in wave order.
+//   2. a second kernel adds the partials of each head, four cells per lane: 256 groups of four lanes each sum a
+//      strided subset in index order, then the sub-sums are added in a fixed order (na2d_rpb_final.hpp).
 #include "na2d_kernels.hpp"
 #include "na2d_rpb_final.hpp"
 #include "na2d_common.hpp"

@@ -136,11 +136,12 @@ static inline long long fifths_of_rounds(long long n) {
 }
 // Ranges of the batch per unit.  As many as fill the 512 places (two workgroups on each of 256 compute units) in one round; more, up to four
 // rounds, where that is expected to take 5 % less.  A workgroup costs its tables (7) and its longest range (5 an item).
-// fp16, k = 7, D = 32, us of the fused forward / fused backward / logits / weighted sum, one round (or one range) -> by the rule:
-// 288 units (96 x 96 x 4) of 10 items 28.9 / 92.9 / 26.7 / 21.1 -> 26.1 / 87.7 / 23.7 / 19.2 (576 workgroups); 384 (128 x 128 x 3) of 8, bf16
-// 30.4 / 97.2 / 23.7 / 19.0 -> 27.6 / 93.8 / 22.0 / 17.6 (768); 260 (100 x 80 x 4) of 10, k = 3 20.7 / 63.0 / 12.8 / 13.0 -> 15.7 / 54.2 / 11.0 / 10.4.
-// 280 (112 x 80 x 4) of 64 189 / 584 / 150 / 134 -> 139 / 459 / 116 / 106; 600 (80 x 160 x 6) of 8, bf16 51 / 182 / 31 / 30 -> 46 / 151 / 29 / 28.
-// Where it stays with one: 392 (112 x 112 x 4) of 8 24.8 / 90.4 / 23.6 / 18.9, in two ranges 27.5 / 94.7 / 25.2 / 20.0; 1050 (200 x 334 x 2) of 2
+// fp16, k = 7, D = 32, us of the fused forward / fused backward (both kernels) / logits / weighted sum, one round (or one range) -> by the rule, three sets of buffers in turn
+// (the last digit but one varies by 5 from run to run):
+// 288 units (96 x 96 x 4) of 10 items 30.1 / 98.1 / 27.8 / 21.5 -> 27.8 / 91.3 / 24.6 / 19.5 (576 workgroups); 384 (128 x 128 x 3) of 8, bf16
+// 30.9 / 98.8 / 23.8 / 19.1 -> 28.0 / 94.6 / 21.8 / 17.5 (768); 260 (100 x 80 x 4) of 10, k = 3 20.8 / 63.1 / 12.8 / 12.9 -> 16.0 / 54.3 / 11.2 / 10.5.
+// 280 (112 x 80 x 4) of 64 185 / 544 / 150 / 134 -> 137 / 454 / 115 / 107; 600 (80 x 160 x 6) of 8, bf16 50 / 153 / 31 / 31 -> 45 / 147 / 29 / 29.
+// Where it stays with one: 392 (112 x 112 x 4) of 8 24.8 / 88.5 / 23.4 / 19.0, in two ranges 27.5 / 94.7 / 25.2 / 20.0; 1050 (200 x 334 x 2) of 2
 // 22.3 / 69.4 / 20.7 / 15.6, in two 26.6 / 75.8 / 27.2 / 19.0.
 static inline int batch_splits(int units, int nb, int most) {   // at most `most` ranges
     const auto cost = [=](int s) { return fifths_of_rounds((long long)units * s) * (7 + 5 * ((nb + s - 1) / s)); };
